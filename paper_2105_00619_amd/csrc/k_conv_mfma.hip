@@ -1407,7 +1407,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
     constexpr bool TAIL = decltype(TAILC)::value != 0;  // 0: steady state without range checks
     const int nstage = stage == 2 ? 0 : stage + 1;
     const bool has_next = TAIL ? j + 1 < n : true;
-    // steady state (j + 4 < n): tiles j + 2 and j + 3 are not the range's last one, all of their rows are inside it
+    // steady state: tiles j + 2 and j + 3 are not the range's last one, all of their rows are inside it
     if (!TAIL || j + 3 < n) gload(IC<1 - p>{}, IC<TAIL ? 1 : 0>{}, j + 3);
     mma_half(0);
     __builtin_amdgcn_sched_barrier(0);
@@ -1421,7 +1421,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
   };
   {
     int stage = 0, j = 0;
-    for (; j + 4 < n; j += 2) {
+    for (; j + 5 < n; j += 2) {  // the second body loads tile j + 4 unchecked: the range goes on behind it
       body(IC<0>{}, IC<0>{}, j, stage);
       stage = stage == 2 ? 0 : stage + 1;
       body(IC<1>{}, IC<0>{}, j + 1, stage);

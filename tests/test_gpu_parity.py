@@ -192,6 +192,29 @@ def test_single_layers_16bit_match_plain_float64(name, variant, precision):
     assert abs(r["loss"] - loss) <= 2e-2 * max(1.0, abs(loss))
 
 
+@pytest.mark.parametrize("precision,cin,cout,hw,b", [
+    (W.BF16, 64, 64, 13, 194), (W.FP16, 128, 512, 17, 57), (W.FP32, 128, 512, 11, 68), (W.FP32, 64, 64, 23, 31),
+    (W.BF16, 256, 256, 17, 227)])
+def test_pointwise_wgrad_with_a_ragged_last_tile(precision, cin, cout, hw, b):
+    """Weight gradient of a 1x1 layer whose pixels do not fill the last depth tile of the last range, with an odd number of
+    tiles (at least five) in that range: its last tile has to be loaded with the range check, whichever of the two bodies
+    of the pipelined loop comes to it.  Against plain float64, with the bars of the single-layer tests (one rounding per
+    stored tensor; 1e-4 in fp32)."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(cin, cout, 1, bn=False, relu=False, bias=True), W.gap_linear_ce(cout, 10)]
+    rnd = {W.FP32: lambda v: v, W.BF16: O.round_to_bf16, W.FP16: O.round_to_fp16}[precision]
+    p = W.make_params(units, hw, hw, 13, perturb=True)
+    sl = W.param_slices(units, hw, hw)["u0.w"]
+    p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, hw, hw, cin, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    _, g = oracle_step(units, p, x, y)
+    errs = plain_errors(units, hw, hw, r["grads"], g)
+    assert max(errs.values()) <= TOL[precision], errs
+
+
 def _unit_trace(tr, xd, n_units):
     """GPU output of every body unit the plan writes to memory: {unit: float64 array}."""
     from paper_2105_00619_amd.binding import OptorchError
