@@ -4,6 +4,8 @@
 // Every lane moves 16 bytes per access along the channel axis; per-channel sums are reduced in a fixed
 // order (lane-private partials -> LDS -> one partial row per block -> one finishing thread per channel,
 // in double), so results do not depend on scheduling.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -39,6 +41,30 @@ struct RedArgs {
   int64_t rows;
   int C, relu, nblk, rows_per_block;
 };
+
+// The block's row of partial sums from its threads' sums (TY rows of TX threads, V channels each): every one of the
+// block's 2 * TX * V sums is added up by a thread of its own, the TY rows in order.  (With the TX threads of row 0 doing
+// it, a 64-channel reduction in 16 bits added 2 x 8 sums of 32 values per thread one after the other.)
+template <int V>
+__device__ __forceinline__ void col_combine(float* smem, const float (&s0)[V], const float (&s1)[V], bool active, int tx,
+                                            int ty, int TX, int TY, int CG, int C, float* __restrict__ partial) {
+  const int W = TX * V;
+  if (active) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) { smem[ty * W + tx * V + i] = s0[i]; smem[(TY + ty) * W + tx * V + i] = s1[i]; }
+  }
+  __syncthreads();
+  for (int o = threadIdx.x; o < 2 * W; o += 256) {
+    const int which = o >= W ? 1 : 0, col = o - which * W;
+    const int c = blockIdx.y * W + col;
+    if (c >= CG * V) continue;
+    const float* p = smem + which * TY * W + col;
+    float t = 0.f;
+#pragma unroll 8
+    for (int y = 0; y < TY; ++y) t += p[y * W];
+    partial[((int64_t)blockIdx.x * 2 + which) * C + c] = t;
+  }
+}
 
 template <class T, int V, int MODE>
 __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
@@ -128,21 +154,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
       accumulate(va, vz, vo, mb);
     }
   }
-  const int W = TX * V;
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) { smem[ty * W + tx * V + i] = s0[i]; smem[(TY + ty) * W + tx * V + i] = s1[i]; }
-  }
-  __syncthreads();
-  if (active && ty == 0) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      float t0 = 0.f, t1 = 0.f;
-      for (int y = 0; y < TY; ++y) { t0 += smem[y * W + tx * V + i]; t1 += smem[(TY + y) * W + tx * V + i]; }
-      g.partial[((int64_t)blockIdx.x * 2 + 0) * g.C + c0 + i] = t0;
-      g.partial[((int64_t)blockIdx.x * 2 + 1) * g.C + c0 + i] = t1;
-    }
-  }
+  col_combine<V>(smem, s0, s1, active, tx, ty, TX, TY, CG, g.C, g.partial);
 }
 
 template <class T, int MODE>
@@ -167,30 +179,75 @@ static void launch_colreduce(hipStream_t st, int dt, const RedArgs& g) {
   else launch_colreduce_t<f16_t, MODE>(st, g);
 }
 
-// finishing kernels: one wavefront per channel; lane l sums the block partials l, l+64, ... in double, then the
-// 64 lane sums are combined by a fixed butterfly, so the result is the same on every run
-__device__ __forceinline__ double wave_sum(double v) {
+// Finishing kernels: the block partials [nblk][2][C] of V neighbouring channels per block of 256 threads (V = 4 where C
+// allows it).  Thread t sums the rows t, t + 256, ... in double, the loads of four rows (V floats each) issued before the
+// first value is used; the lanes of a wavefront are combined by a fixed exchange that halves the number of values a lane
+// carries while it halves the distance, the four wavefronts through LDS in order.  Bound by latency: the rows were written
+// by blocks on other XCDs, so they come from beyond the L2, and a wavefront per channel that waits for one row's two floats
+// at a time takes 4.7-5.5 us for 512 rows; with 16 channels in one block too few CUs share the work (13 us for 2048 rows).
+template <int V>
+__device__ __forceinline__ void partial_sums(const float* __restrict__ partial, int nblk, int C, double (&red)[4][2 * V],
+                                             double& s, double& q) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double v[2 * V];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-__device__ __forceinline__ void partial_sums(const float* __restrict__ partial, int nblk, int C, int c, double& s, double& q) {
-  const int lane = threadIdx.x & 63;
-  s = 0.0; q = 0.0;
-  for (int b = lane; b < nblk; b += 64) {
-    s += (double)partial[((int64_t)b * 2) * C + c];
-    q += (double)partial[((int64_t)b * 2 + 1) * C + c];
+  for (int k = 0; k < 2 * V; ++k) v[k] = 0.0;
+  const float* p = partial + blockIdx.x * V;
+  auto rows = [&](auto UC, int b) {  // UC rows of this thread, which exist (UC = 1) or are checked
+    constexpr int U = decltype(UC)::value;
+    float t[U][2][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = b + u * 256 < nblk ? b + u * 256 : b;
+      load_f32<float, V>(p + (int64_t)(2 * r) * C, t[u][0]);
+      load_f32<float, V>(p + (int64_t)(2 * r + 1) * C, t[u][1]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b + u * 256 < nblk) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) { v[k] += (double)t[u][0][k]; v[V + k] += (double)t[u][1][k]; }
+      }
+  };
+  int b = threadIdx.x;
+  if (nblk > 512)
+    for (; b + 512 < nblk; b += 1024) rows(std::integral_constant<int, 4>{}, b);
+  if (b < nblk) rows(std::integral_constant<int, 2>{}, b);
+  // (each exchange with its own constants: an array indexed by a variable would live in LDS)
+  int which = 0;  // the value a lane ends up with: one bit per halving exchange, the first one highest
+  auto halve = [&](auto NC, int off) {
+    constexpr int n = decltype(NC)::value;
+    const bool up = lane & off;
+    which = which * 2 + (up ? 1 : 0);
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      const double keep = up ? v[n + k] : v[k], give = up ? v[k] : v[n + k];
+      v[k] = keep + __shfl_xor(give, off, 64);
+    }
+  };
+  if constexpr (V == 4) {
+    halve(std::integral_constant<int, 4>{}, 32);
+    halve(std::integral_constant<int, 2>{}, 16);
+    halve(std::integral_constant<int, 1>{}, 8);
+  } else {
+    static_assert(V == 1, "four channels or one");
+    halve(std::integral_constant<int, 1>{}, 32);
   }
-  s = wave_sum(s);
-  q = wave_sum(q);
+#pragma unroll
+  for (int off = 32 / (2 * V); off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+  if ((lane & (64 / (2 * V) - 1)) == 0) red[wave][which] = v[0];
+  __syncthreads();
+  if (threadIdx.x < V) {
+    s = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+    q = ((red[0][V + threadIdx.x] + red[1][V + threadIdx.x]) + red[2][V + threadIdx.x]) + red[3][V + threadIdx.x];
+  }
 }
 
 // Many row blocks (a convolution over a large batch writes one row of sums per 128 pixels): the rows are first added
 // in STAT_FOLD_ROWS fixed ranges, with coalesced reads (thread = channel, four rows in flight per block), so that the
 // finishing kernel, which walks a channel's column with one wavefront, has only that many rows left.
 constexpr int STAT_FOLD_ROWS = 64;
-constexpr int STAT_FOLD_MIN = 512;
+constexpr int STAT_FOLD_MIN = 4096;
 __global__ void __launch_bounds__(256) stat_fold_kernel(const float* __restrict__ partial, int nblk, int C, int rows_per_range,
                                                         float* __restrict__ folded) {
   __shared__ double red[2][4][64];
@@ -226,28 +283,34 @@ __global__ void __launch_bounds__(256) stat_fold_kernel(const float* __restrict_
   }
 }
 
+template <int V>
 __global__ void __launch_bounds__(256) bn_stats_finalize_kernel(const float* __restrict__ partial, int nblk, int C, double m,
                                                                 float eps, float mom, const float* __restrict__ gamma,
                                                                 const float* __restrict__ beta, float* __restrict__ stats,
                                                                 float* __restrict__ running,
                                                                 const int* __restrict__ flags) {
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= C) return;
+  __shared__ double red[4][2 * V];
+  // (requested ahead of the sums, so that their latency does not follow the reduction's)
+  const int cc = blockIdx.x * V + (threadIdx.x < V ? threadIdx.x : 0);
+  const double ga = (double)gamma[cc], be = (double)beta[cc];
+  const float r0 = running ? running[cc] : 0.f, r1 = running ? running[C + cc] : 0.f;
+  const int bad = flags ? flags[1] : 0;
   double s, q;
-  partial_sums(partial, nblk, C, c, s, q);
-  if ((threadIdx.x & 63) != 0) return;
+  partial_sums<V>(partial, nblk, C, red, s, q);
+  const int c = blockIdx.x * V + threadIdx.x;
+  if (threadIdx.x >= V) return;
   const double mean = s / m;
   double var = q / m - mean * mean;
   if (var < 0.0) var = 0.0;
   const double rstd = 1.0 / sqrt(var + (double)eps);
   stats[c] = (float)mean;
   stats[C + c] = (float)rstd;
-  stats[2 * C + c] = (float)((double)gamma[c] * rstd);
-  stats[3 * C + c] = (float)((double)beta[c] - mean * (double)gamma[c] * rstd);
-  if (running && !(flags && flags[1])) {  // a step with an invalid label leaves the running statistics alone
+  stats[2 * C + c] = (float)(ga * rstd);
+  stats[3 * C + c] = (float)(be - mean * ga * rstd);
+  if (running && !bad) {  // a step with an invalid label leaves the running statistics alone
     const double unbiased = m > 1.0 ? var * m / (m - 1.0) : var;
-    running[c] = (float)((1.0 - mom) * (double)running[c] + mom * mean);
-    running[C + c] = (float)((1.0 - mom) * (double)running[C + c] + mom * unbiased);
+    running[c] = (float)((1.0 - mom) * (double)r0 + mom * mean);
+    running[C + c] = (float)((1.0 - mom) * (double)r1 + mom * unbiased);
   }
 }
 
@@ -265,27 +328,29 @@ __global__ void __launch_bounds__(256) bn_eval_stats_kernel(const float* __restr
   stats[3 * C + c] = (float)((double)beta[c] - mean * (double)gamma[c] * rstd);
 }
 
+template <int V>
 __global__ void __launch_bounds__(256) bn_bwd_finalize_kernel(const float* __restrict__ partial, int nblk, int C, double m,
                                                               float* __restrict__ dgamma, float* __restrict__ dbeta,
                                                               float* __restrict__ coef) {
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= C) return;
+  __shared__ double red[4][2 * V];
   double s, q;
-  partial_sums(partial, nblk, C, c, s, q);
-  if ((threadIdx.x & 63) != 0) return;
+  partial_sums<V>(partial, nblk, C, red, s, q);
+  const int c = blockIdx.x * V + threadIdx.x;
+  if (threadIdx.x >= V) return;
   dbeta[c] = (float)s;
   dgamma[c] = (float)q;
   coef[c] = (float)(s / m);
   coef[C + c] = (float)(q / m);
 }
 
+template <int V>
 __global__ void __launch_bounds__(256) bias_finalize_kernel(const float* __restrict__ partial, int nblk, int C,
                                                             float* __restrict__ dbias) {
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= C) return;
+  __shared__ double red[4][2 * V];
   double s, q;
-  partial_sums(partial, nblk, C, c, s, q);
-  if ((threadIdx.x & 63) == 0) dbias[c] = (float)s;
+  partial_sums<V>(partial, nblk, C, red, s, q);
+  const int c = blockIdx.x * V + threadIdx.x;
+  if (threadIdx.x < V) dbias[c] = (float)s;
 }
 
 // ------------------------------------------------------------- BN apply -----
@@ -526,21 +591,7 @@ __global__ void __launch_bounds__(256) bn_bwd_pool_reduce_kernel(const T* __rest
         }
     }
   }
-  const int W = TX * V;
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) { smem[ty * W + tx * V + i] = s0[i]; smem[(TY + ty) * W + tx * V + i] = s1[i]; }
-  }
-  __syncthreads();
-  if (active && ty == 0) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      float t0 = 0.f, t1 = 0.f;
-      for (int y = 0; y < TY; ++y) { t0 += smem[y * W + tx * V + i]; t1 += smem[(TY + y) * W + tx * V + i]; }
-      partial[((int64_t)blockIdx.x * 2 + 0) * g.C + c0 + i] = t0;
-      partial[((int64_t)blockIdx.x * 2 + 1) * g.C + c0 + i] = t1;
-    }
-  }
+  col_combine<V>(smem, s0, s1, active, tx, ty, TX, TY, CG, g.C, partial);
 }
 
 template <class T, int V>
@@ -670,6 +721,13 @@ __global__ void __launch_bounds__(256) maxpool_bwd_kernel(const T* __restrict__ 
     else { if ((C) % 8 == 0) { CALL(f16_t, 8); } else { CALL(f16_t, 1); } }     \
   } while (0)
 
+// a finishing kernel over C channels: four per block, or one where C is not a multiple of four
+#define FIN_LAUNCH(KERNEL, ...)                                                             \
+  do {                                                                                      \
+    if (C % 4 == 0) OSEQ_LAUNCH(KERNEL<4>, dim3(C / 4), dim3(256), __VA_ARGS__);            \
+    else OSEQ_LAUNCH(KERNEL<1>, dim3(C), dim3(256), __VA_ARGS__);                           \
+  } while (0)
+
 void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n) {
   const int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
   if (dt == DT_F32) OSEQ_LAUNCH(cast_in_kernel<float>, dim3(blocks), dim3(256), 0, st, x, (float*)out, n);
@@ -689,7 +747,7 @@ void launch_bn_stats(hipStream_t st, int dt, const void* z, int64_t rows, int C,
                      const int* flags) {
   RedArgs g{}; g.a = z; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
   launch_colreduce<RED_STATS>(st, dt, g);
-  OSEQ_LAUNCH(bn_stats_finalize_kernel, dim3(ceil_div(C, 4)), dim3(256), 0, st, partial, nblk, C, (double)rows,
+  FIN_LAUNCH(bn_stats_finalize_kernel, 0, st, partial, nblk, C, (double)rows,
                      eps, mom, gamma, beta, stats, running, flags);
 }
 
@@ -707,7 +765,7 @@ void launch_bn_stats_finalize(hipStream_t st, float* partial, int64_t rows, int 
     partial = folded;
     nblk = ranges;
   }
-  OSEQ_LAUNCH(bn_stats_finalize_kernel, dim3(ceil_div(C, 4)), dim3(256), 0, st, partial, nblk, C, (double)rows,
+  FIN_LAUNCH(bn_stats_finalize_kernel, 0, st, partial, nblk, C, (double)rows,
                      eps, mom, gamma, beta, stats, running, flags);
 }
 
@@ -767,7 +825,7 @@ void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const 
   else if (aout) launch_colreduce<RED_BN_BWD_AOUT>(st, dt, g);
   else launch_colreduce<RED_BN_BWD>(st, dt, g);
   float* coef = ws + (int64_t)nblk * 2 * C;
-  OSEQ_LAUNCH(bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(256), 0, st, ws, nblk, C, (double)rows, dgamma,
+  FIN_LAUNCH(bn_bwd_finalize_kernel, 0, st, ws, nblk, C, (double)rows, dgamma,
                      dbeta, coef);
 #define APPLY(T, V, MS, DS)                                                                                             \
   OSEQ_LAUNCH((bn_bwd_apply_kernel<T, V, MS, DS>), grid, dim3(256), 0, st, (const T*)da, (const T*)z,             \
@@ -794,7 +852,7 @@ void launch_bn_bwd_pool(hipStream_t st, int dt, const void* dy, const void* z, c
     PoolBwdArgs gr = g; gr.rows_per_block = ceil_div(g.rows, nblk);                                                        \
     OSEQ_LAUNCH((bn_bwd_pool_reduce_kernel<T, V>), dim3(nblk, ytiles), dim3(256), (size_t)2 * TY * TX * V * sizeof(float), \
                 st, (const T*)dy, (const T*)z, stats, ws, gr);                                                             \
-    OSEQ_LAUNCH(bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(256), 0, st, ws, nblk, C, (double)N * H * W, dgamma,    \
+    FIN_LAUNCH(bn_bwd_finalize_kernel, 0, st, ws, nblk, C, (double)N * H * W, dgamma,    \
                 dbeta, coef);                                                                                              \
     PoolBwdArgs ga = g; int per = 2;                                                                                       \
     while (per > 1 && (int64_t)ceil_div(g.rows, (int64_t)TY * per) * ytiles < 1024) per /= 2;                              \
@@ -817,7 +875,7 @@ void launch_relu_bwd(hipStream_t st, int dt, const void* da, const void* a, void
 void launch_bias_grad(hipStream_t st, int dt, const void* dz, int64_t rows, int C, int nblk, float* partial, float* dbias) {
   RedArgs g{}; g.a = dz; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
   launch_colreduce<RED_BIAS>(st, dt, g);
-  OSEQ_LAUNCH(bias_finalize_kernel, dim3(ceil_div(C, 4)), dim3(256), 0, st, partial, nblk, C, dbias);
+  FIN_LAUNCH(bias_finalize_kernel, 0, st, partial, nblk, C, dbias);
 }
 
 void launch_maxpool_fwd(hipStream_t st, int dt, const void* x, void* y, int N, int H, int W, int C) {
