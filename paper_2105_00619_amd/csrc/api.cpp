@@ -95,6 +95,8 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g);
       }
+    for (FOp& f : p.fops)
+      if (f.kind == F_HEAD) f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes);
     // the BatchNorm statistics operation that follows such a convolution only runs its finishing kernel
     for (size_t i = 0; i + 1 < p.fops.size(); ++i)
       if (p.fops[i].kind == F_CONV && p.fops[i].stat_blocks > 0 && p.fops[i + 1].kind == F_BN_STATS &&
@@ -338,7 +340,7 @@ void run_op(const Ctx& c, const SOp& s) {
     case S_HEAD_FWD:
       launch_head_fwd(st, dt, c.at(s.in[0]), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off),
                       c.w32(f.b_off), c.y, h->scale / (float)f.N, (float*)c.at(s.out[0]), (float*)c.at(s.out[1]),
-                      (float*)c.at(s.out[2]), (float*)c.at(s.out[3]), c.loss(), c.flags());
+                      (float*)c.at(s.out[2]), (float*)c.at(s.out[3]), c.loss(), c.flags(), (float*)c.at(s.out[4]));
       break;
     case S_HEAD_BWD:
       launch_head_bwd(st, dt, (const float*)c.at(s.in[0]), (const float*)c.at(s.in[1]), c.w32(f.w_off), f.N, f.H * f.W, f.C,
@@ -555,7 +557,7 @@ static int predict_run(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
       }
       case S_HEAD_FWD: {
         launch_head_logits(st, dt, c.at(s.in[0]), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off),
-                           c.w32(f.b_off), (float*)c.at(s.out[0]), (float*)c.at(s.out[1]));
+                           c.w32(f.b_off), (float*)c.at(s.out[0]), (float*)c.at(s.out[1]), (float*)c.at(s.out[4]));
         hipError_t e = hipMemcpyAsync(logits_dev, c.at(s.out[1]), (size_t)f.N * f.classes * 4, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return hip_fail(h, e, "hipMemcpyAsync(logits)");
         break;

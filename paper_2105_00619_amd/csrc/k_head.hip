@@ -1,81 +1,200 @@
 // Loss head: global average pool / flatten, linear layer, mean softmax cross-entropy, and their backward.
 // All arithmetic in fp32 on fp32 master weights (the head is a few MFLOP; it is kept out of the 16-bit path
 // for stability, in line with keeping loss computation in single precision).  Every sum runs in a fixed order.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace oseq {
 
-// feat[n][f]: GAP -> mean over H*W of channel f ; flatten -> x[n][f]
-// GAP: block (n, g) owns 64 channels of image n; its four wavefronts take every fourth pixel (eight loads in flight
-// per lane) and their sums are added in wavefront order.
-template <class T>
-__global__ void __launch_bounds__(256) head_feat_kernel(const T* __restrict__ x, float* __restrict__ feat, int HW, int C,
-                                                        int gap) {
-  __shared__ float sm[4][64];
-  const int n = blockIdx.x;
-  if (!gap) {
-    const int64_t F = (int64_t)HW * C;
-    for (int64_t i = (int64_t)blockIdx.y * 256 + threadIdx.x; i < F; i += (int64_t)gridDim.y * 256)
-      feat[n * F + i] = to_f32(x[n * F + i]);
-    return;
-  }
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int c = blockIdx.y * 64 + tx;
-  float s = 0.f;
-  if (c < C) {
-    const T* col = x + (int64_t)n * HW * C + c;
-#pragma unroll 8
-    for (int p = ty; p < HW; p += 4) s += to_f32(col[(int64_t)p * C]);
-  }
-  sm[ty][tx] = s;
-  __syncthreads();
-  if (ty == 0 && c < C) feat[(int64_t)n * C + c] = (((sm[0][tx] + sm[1][tx]) + sm[2][tx]) + sm[3][tx]) / (float)HW;
+typedef __attribute__((ext_vector_type(16))) float head_v16f;
+
+// flatten: feat[n][f] = x[n][f] in fp32, V features per thread
+template <class T, int V>
+__global__ void __launch_bounds__(256) flatten_kernel(const T* __restrict__ x, float* __restrict__ feat, int64_t groups) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= groups) return;
+  float v[V];
+  load_f32<T, V>(x + i * V, v);
+  store_f32<float, V>(feat + i * V, v);
 }
 
-// logits[n][j] = b[j] + sum_f feat[n][f] * w[j][f]: lanes stride over the features, then a fixed butterfly, per (sample,
-// class).  A wavefront owns 8 samples x 8 classes, so that every feature and weight value it loads serves eight sums
-// (one wavefront per (sample, class) re-read the whole weight matrix per sample: 508 us at batch 4096, 2048 features).
-// With few samples the tiles are too few to fill the chip: then a wavefront keeps to one (sample, class).
-template <int LIN_TN, int LIN_TJ>
-__global__ void __launch_bounds__(256) linear_fwd_kernel(const float* __restrict__ feat, const float* __restrict__ w,
-                                                         const float* __restrict__ b, float* __restrict__ logits, int N, int F,
-                                                         int J) {
-  const int jt = (J + LIN_TJ - 1) / LIN_TJ;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int n0 = (t / jt) * LIN_TN, j0 = (t % jt) * LIN_TJ, lane = threadIdx.x & 63;
-  if (n0 >= N) return;
-  const float* fp[LIN_TN];
-  const float* wp[LIN_TJ];
+// Global average pool: block (image, group of channels, range of pixels) of TX threads of V channels and TY rows of them;
+// a thread adds every TY-th pixel (eight 16-byte loads in flight), the TY sums of a channel are added in order.  Bound by
+// reading the map once.  With one range the mean is stored; with several (few images of many pixels, which would leave most
+// CUs idle: 4 images of 256 x 256 x 128 in fp32 took 1153 us in one block per image and 64 channels, 27 us like this) the
+// sums go to `partial` [ranges][N][C] and gap_finish_kernel adds the ranges in order.
+template <class T, int V>
+__global__ void __launch_bounds__(256) gap_sum_kernel(const T* __restrict__ x, float* __restrict__ feat,
+                                                      float* __restrict__ partial, int N, int HW, int C, int TX, int per_range) {
+  __shared__ float red[256 * V];
+  const int TY = 256 / TX, tx = threadIdx.x % TX, ty = threadIdx.x / TX;
+  const int n = blockIdx.x;
+  const int cg = blockIdx.y * TX + tx;
+  const bool active = cg < C / V && ty < TY;
+  const int p0 = blockIdx.z * per_range, p1 = p0 + per_range < HW ? p0 + per_range : HW;
+  float s[V];
 #pragma unroll
-  for (int s = 0; s < LIN_TN; ++s) fp[s] = feat + (int64_t)(n0 + s < N ? n0 + s : n0) * F;
+  for (int k = 0; k < V; ++k) s[k] = 0.f;
+  if (active) {
+    const T* col = x + (int64_t)n * HW * C + cg * V;
+    constexpr int U = 8;
+    int p = p0 + ty;
+    for (; p + (U - 1) * TY < p1; p += U * TY) {
+      float v[U][V];
 #pragma unroll
-  for (int c = 0; c < LIN_TJ; ++c) wp[c] = w + (int64_t)(j0 + c < J ? j0 + c : j0) * F;
-  float acc[LIN_TN][LIN_TJ];
+      for (int u = 0; u < U; ++u) load_f32<T, V>(col + (int64_t)(p + u * TY) * C, v[u]);
 #pragma unroll
-  for (int s = 0; s < LIN_TN; ++s)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int c = 0; c < LIN_TJ; ++c) acc[s][c] = 0.f;
-  for (int f = lane; f < F; f += 64) {
-    float x[LIN_TN], v[LIN_TJ];
-#pragma unroll
-    for (int s = 0; s < LIN_TN; ++s) x[s] = fp[s][f];
-#pragma unroll
-    for (int c = 0; c < LIN_TJ; ++c) v[c] = wp[c][f];
-#pragma unroll
-    for (int s = 0; s < LIN_TN; ++s)
-#pragma unroll
-      for (int c = 0; c < LIN_TJ; ++c) acc[s][c] = __fmaf_rn(x[s], v[c], acc[s][c]);
-  }
-#pragma unroll
-  for (int s = 0; s < LIN_TN; ++s)
-#pragma unroll
-    for (int c = 0; c < LIN_TJ; ++c) {
-      float a = acc[s][c];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-      if (lane == 0 && n0 + s < N && j0 + c < J) logits[(int64_t)(n0 + s) * J + j0 + c] = a + b[j0 + c];
+        for (int k = 0; k < V; ++k) s[k] += v[u][k];
     }
+    for (; p < p1; p += TY) {
+      float v[V];
+      load_f32<T, V>(col + (int64_t)p * C, v);
+#pragma unroll
+      for (int k = 0; k < V; ++k) s[k] += v[k];
+    }
+#pragma unroll
+    for (int k = 0; k < V; ++k) red[ty * TX * V + tx * V + k] = s[k];
+  }
+  __syncthreads();
+  const int W = TX * V;
+  for (int o = threadIdx.x; o < W; o += 256) {
+    const int c = blockIdx.y * W + o;
+    if (c >= C) continue;
+    float t = 0.f;
+    for (int y = 0; y < TY; ++y) t += red[y * W + o];
+    if (partial) partial[((int64_t)blockIdx.z * N + n) * C + c] = t;
+    else feat[(int64_t)n * C + c] = t / (float)HW;
+  }
+}
+
+__global__ void __launch_bounds__(256) gap_finish_kernel(const float* __restrict__ partial, float* __restrict__ feat, int64_t n,
+                                                         int ranges, int HW) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float t = 0.f;
+#pragma unroll 16
+  for (int r = 0; r < ranges; ++r) t += partial[(int64_t)r * n + i];
+  feat[i] = t / (float)HW;
+}
+
+// The three products of the linear layer on the fp32 matrix cores: out[row][col] = sum over k of A(row, k) * B(k, col),
+//   HG_FWD  logits[n][j] = b[j] + sum_f feat[n][f] * w[j][f]        rows n, columns j, depth F
+//   HG_DW   dw[j][f]     =        sum_n dlogits[n][j] * feat[n][f]  rows j, columns f (column F: the bias gradient), depth N
+//   HG_DX   dfeat[n][f]  =        sum_j dlogits[n][j] * w[j][f]     rows n, columns f, depth J
+// A block of KW wavefronts owns a 32 x 32 tile; wavefront w takes the 16-deep pieces w, w + KW, ... of the depth (of the
+// range blockIdx.z, when the depth is split), four of them requested at a time, and the KW partial tiles are added in
+// wavefront order through LDS.  Bound by latency and by the fp32 MFMA rate (64 cycles per 32 x 32 x 2); a wavefront per
+// (sample, class), or a thread per feature, re-read one operand per output: with 4096 samples, 1024 features and 100 classes
+// the three took 62, 172 and 54 us (now 24, 36 and 22), with 512 samples and 2048 features the first 74 us (now 22).
+// Lane l of an MFMA holds row (column) l % 32 at depth l / 32; the 16-deep piece gives lane group g the depths [8g, 8g + 8),
+// so that a lane reads eight neighbours where the depth is the fast index.  VEC: those may be read as two 16-byte loads.
+enum { HG_FWD = 0, HG_DW = 1, HG_DX = 2 };
+template <int KIND, int KW>
+__global__ void __launch_bounds__(64 * KW) head_gemm_kernel(const float* __restrict__ a, const float* __restrict__ b,
+                                                            const float* __restrict__ bias, float* __restrict__ out,
+                                                            float* __restrict__ out_bias, int rows, int cols, int depth, int lda,
+                                                            int ldb, int depth_per_range) {
+  constexpr bool A_FAST = KIND != HG_DW, B_FAST = KIND == HG_FWD;  // is the depth the fast index of the operand?
+  constexpr int UP = 4;                                            // pieces requested at a time
+  __shared__ float red[KW > 1 ? KW * 32 * 32 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, l32 = lane & 31;
+  const int row0 = blockIdx.y * 32, col0 = blockIdx.x * 32;
+  const int ar = row0 + l32 < rows ? row0 + l32 : 0;  // (rows and columns outside are read at 0 and not stored)
+  const int bc = col0 + l32 < cols ? col0 + l32 : 0;
+  const bool ones = KIND == HG_DW && col0 + l32 == cols;
+  const int d0 = blockIdx.z * depth_per_range, d1 = d0 + depth_per_range < depth ? d0 + depth_per_range : depth;
+  const float* ap = A_FAST ? a + (int64_t)ar * lda : a + ar;
+  const float* bp = B_FAST ? b + (int64_t)bc * ldb : b + bc;
+  head_v16f acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  auto piece = [&](const float* p, bool fast, int ld, int k, bool full, float (&v)[8]) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const bool in = full || k + t < d1;
+      const float x = p[in ? (fast ? (int64_t)(k + t) : (int64_t)(k + t) * ld) : 0];
+      v[t] = in ? x : 0.f;
+    }
+  };
+  auto pieces = [&](auto NC, int k, bool full) {
+    constexpr int n = decltype(NC)::value;
+    float va[n][8], vb[n][8];
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+      piece(ap, A_FAST, lda, k + u * 16 * KW + 8 * g, full, va[u]);
+      piece(bp, B_FAST, ldb, k + u * 16 * KW + 8 * g, full, vb[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < n; ++u)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        if (KIND == HG_DW) {
+          const int kk = k + u * 16 * KW + 8 * g + t;
+          vb[u][t] = ones ? (full || kk < d1 ? 1.f : 0.f) : vb[u][t];
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[u][t], vb[u][t], acc, 0, 0, 0);
+      }
+  };
+  int k = d0 + wave * 16;
+  for (; k + (UP - 1) * 16 * KW + 16 <= d1; k += UP * 16 * KW) pieces(std::integral_constant<int, UP>{}, k, true);
+#pragma unroll 1
+  for (; k < d1; k += 16 * KW) pieces(std::integral_constant<int, 1>{}, k, false);
+  auto store = [&](int r, int c, float v) {
+    if (r >= rows) return;
+    if (KIND == HG_FWD) {
+      if (c < cols) out[((int64_t)blockIdx.z * rows + r) * cols + c] = bias ? v + bias[c] : v;
+    } else {
+      if (c < cols) out[(int64_t)r * cols + c] = v;
+      else if (KIND == HG_DW && c == cols) out_bias[r] = v;
+    }
+  };
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) store(row0 + 8 * (e >> 2) + 4 * g + (e & 3), col0 + l32, acc[e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave * 1024 + (8 * (e >> 2) + 4 * g + (e & 3)) * 32 + l32] = acc[e];
+    __syncthreads();
+    for (int o = threadIdx.x; o < 1024; o += 64 * KW) {
+      float t = red[o];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) t += red[w * 1024 + o];
+      store(row0 + (o >> 5), col0 + (o & 31), t);
+    }
+  }
+}
+
+// the ranges of a split depth, added in order, and the bias
+__global__ void __launch_bounds__(256) head_reduce_kernel(const float* __restrict__ partial, const float* __restrict__ bias,
+                                                          float* __restrict__ out, int64_t n, int cols, int ranges) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float t = 0.f;
+#pragma unroll 8
+  for (int r = 0; r < ranges; ++r) t += partial[(int64_t)r * n + i];
+  out[i] = t + bias[i % cols];
+}
+
+template <int KIND>
+static void launch_head_gemm(hipStream_t st, const float* a, const float* b, const float* bias, float* out, float* out_bias,
+                             int rows, int cols, int depth, int lda, int ldb, int ranges) {
+  const dim3 grid(ceil_div(cols + (KIND == HG_DW ? 1 : 0), 32), ceil_div(rows, 32), ranges);
+  const int64_t tiles = (int64_t)grid.x * grid.y * grid.z;
+  const int per = ceil_div(ceil_div(depth, ranges), 16) * 16;
+  // wavefronts per tile: about eight per CU in all, no more than there are pieces
+  int kw = tiles >= 2048 ? 1 : tiles >= 512 ? 4 : 8;
+  while (kw > 1 && kw * 16 > per) kw = kw == 8 ? 4 : 1;
+#define HG_LAUNCH(KW_)                                                                                                     \
+  OSEQ_LAUNCH((head_gemm_kernel<KIND, KW_>), grid, dim3(64 * KW_), 0, st, a, b, bias, out, out_bias, rows, cols, depth, lda, \
+              ldb, per)
+  if (kw == 8) HG_LAUNCH(8);
+  else if (kw == 4) HG_LAUNCH(4);
+  else HG_LAUNCH(1);
+#undef HG_LAUNCH
 }
 
 // per sample: loss_n = logsumexp(logits_n) - logits_n[y_n]; dlogits = (softmax - onehot) * gscale
@@ -117,71 +236,6 @@ __global__ void __launch_bounds__(256) loss_mean_kernel(const float* __restrict_
     __syncthreads();
   }
   if (threadIdx.x == 0) out[0] = (float)(sm[0] / (double)N);
-}
-
-// dW[j][f] = sum_n dlogits[n][j] * feat[n][f] ; the extra column f == F is the bias gradient
-// LBW_TJ: classes per block of the weight gradient (more when that still leaves a few blocks per CU)
-template <int LBW_TJ>
-__global__ void __launch_bounds__(256) linear_bwd_w_kernel(const float* __restrict__ dlogits, const float* __restrict__ feat,
-                                                           float* __restrict__ dw, float* __restrict__ db, int N, int F, int J) {
-  // block = LBW_TJ classes and 64 consecutive features (feature index F stands for the bias); the four wavefronts take
-  // samples n = wave, wave + 4, ... and their sums are added in a fixed order.  (One class per block read the features
-  // once per class.)
-  __shared__ float red[LBW_TJ][4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j0 = blockIdx.y * LBW_TJ, f = blockIdx.x * 64 + lane;
-  const bool isw = f < F;
-  const float* fp = feat + (isw ? f : 0);
-  const float one = f == F ? 1.f : 0.f;
-  float acc[LBW_TJ];
-#pragma unroll
-  for (int c = 0; c < LBW_TJ; ++c) acc[c] = 0.f;
-  int jc[LBW_TJ];
-#pragma unroll
-  for (int c = 0; c < LBW_TJ; ++c) jc[c] = j0 + c < J ? j0 + c : j0;
-#pragma unroll 8
-  for (int n = wave; n < N; n += 4) {
-    const float v = isw ? fp[(int64_t)n * F] : one;
-    const float* dl = dlogits + (int64_t)n * J;
-#pragma unroll
-    for (int c = 0; c < LBW_TJ; ++c) acc[c] = __fmaf_rn(dl[jc[c]], v, acc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < LBW_TJ; ++c) red[c][wave][lane] = acc[c];
-  __syncthreads();
-  if (wave == 0) {
-#pragma unroll
-    for (int c = 0; c < LBW_TJ; ++c) {
-      if (j0 + c >= J) break;
-      const float s = ((red[c][0][lane] + red[c][1][lane]) + red[c][2][lane]) + red[c][3][lane];
-      if (isw) dw[(int64_t)(j0 + c) * F + f] = s;
-      else if (f == F) db[j0 + c] = s;
-    }
-  }
-}
-
-// dfeat[n][f] = sum_j dlogits[n][j] * w[j][f], classes in ascending order; a thread owns one feature of 8 samples, so a
-// weight value is loaded once per eight sums
-template <int LBX_TN>
-__global__ void __launch_bounds__(256) linear_bwd_x_kernel(const float* __restrict__ dlogits, const float* __restrict__ w,
-                                                           float* __restrict__ dfeat, int N, int F, int J) {
-  const int f = blockIdx.x * 256 + threadIdx.x;
-  const int n0 = blockIdx.y * LBX_TN;
-  if (f >= F) return;
-  const float* dl[LBX_TN];
-#pragma unroll
-  for (int s = 0; s < LBX_TN; ++s) dl[s] = dlogits + (int64_t)(n0 + s < N ? n0 + s : n0) * J;
-  float acc[LBX_TN];
-#pragma unroll
-  for (int s = 0; s < LBX_TN; ++s) acc[s] = 0.f;
-  for (int j = 0; j < J; ++j) {
-    const float v = w[(int64_t)j * F + f];
-#pragma unroll
-    for (int s = 0; s < LBX_TN; ++s) acc[s] = __fmaf_rn(dl[s][j], v, acc[s]);
-  }
-#pragma unroll
-  for (int s = 0; s < LBX_TN; ++s)
-    if (n0 + s < N) dfeat[(int64_t)(n0 + s) * F + f] = acc[s];
 }
 
 template <class T>
@@ -233,39 +287,76 @@ static void launch_feat_bwd(hipStream_t st, const float* dfeat, void* dx, int N,
   }
 }
 
+// Ranges of pixels (GAP) or of the depth of the linear layer (flatten) over which the head's forward pass is split, from
+// the shape only: about four blocks per CU, ranges of at least 32 rows of threads (GAP) or four pieces per wavefront.
+static int gap_tx(int C, int V) { const int CG = C / V; return CG < 256 ? CG : 256; }
+int head_ranges(int dt, int N, int HW, int C, int gap, int F, int J) {
+  int64_t blocks, most;
+  if (gap) {
+    const int vmax = dt == DT_F32 ? 4 : 8, V = C % vmax == 0 ? vmax : 1, TX = gap_tx(C, V), TY = 256 / TX;
+    blocks = (int64_t)N * ceil_div(C / V, TX);
+    most = HW / (TY * 32);
+  } else {
+    blocks = (int64_t)ceil_div(N, 32) * ceil_div(J, 32) * 2;
+    most = F / (16 * 8 * 4);
+  }
+  int64_t want = (1024 + blocks - 1) / blocks;
+  if (want > most) want = most;
+  if (want > 128) want = 128;
+  return (int)(want < 1 ? 1 : want);
+}
+// floats of workspace the forward pass needs for them
+int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J) {
+  const int r = head_ranges(dt, N, HW, C, gap, F, J);
+  return r > 1 ? (int64_t)r * N * (gap ? C : J) : 0;
+}
+
+template <class T>
+static void launch_feat_t(hipStream_t st, const T* x, int N, int HW, int C, int gap, int ranges, float* feat, float* ws) {
+  constexpr int VM = 16 / (int)sizeof(T);
+  if (!gap) {
+    const int64_t n = (int64_t)N * HW * C;
+    if (C % VM == 0) OSEQ_LAUNCH((flatten_kernel<T, VM>), dim3(ceil_div(n / VM, 256)), dim3(256), 0, st, x, feat, n / VM);
+    else OSEQ_LAUNCH((flatten_kernel<T, 1>), dim3(ceil_div(n, 256)), dim3(256), 0, st, x, feat, n);
+    return;
+  }
+  const int V = C % VM == 0 ? VM : 1, TX = gap_tx(C, V), per = ceil_div(HW, ranges);
+  const dim3 grid(N, ceil_div(C / V, TX), ranges);
+  float* partial = ranges > 1 ? ws : nullptr;
+  if (V == VM) OSEQ_LAUNCH((gap_sum_kernel<T, VM>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per);
+  else OSEQ_LAUNCH((gap_sum_kernel<T, 1>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per);
+  if (partial)
+    OSEQ_LAUNCH(gap_finish_kernel, dim3(ceil_div((int64_t)N * C, 256)), dim3(256), 0, st, partial, feat, (int64_t)N * C, ranges, HW);
+}
+
+// ws: head_ws_floats(...) floats (null if that is 0)
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
-                        const float* b, float* feat, float* logits) {
-  const dim3 feat_grid(N, gap ? ceil_div(C, 64) : 1);
-  if (dt == DT_F32) OSEQ_LAUNCH(head_feat_kernel<float>, feat_grid, dim3(256), 0, st, (const float*)x, feat, HW, C, gap);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(head_feat_kernel<bf16_t>, feat_grid, dim3(256), 0, st, (const bf16_t*)x, feat, HW, C, gap);
-  else OSEQ_LAUNCH(head_feat_kernel<f16_t>, feat_grid, dim3(256), 0, st, (const f16_t*)x, feat, HW, C, gap);
-  if ((int64_t)ceil_div(N, 8) * ceil_div(J, 8) >= 2048)
-    OSEQ_LAUNCH((linear_fwd_kernel<8, 8>), dim3(ceil_div((int64_t)ceil_div(N, 8) * ceil_div(J, 8), 4)), dim3(256), 0, st, feat, w,
-                b, logits, N, F, J);
-  else
-    OSEQ_LAUNCH((linear_fwd_kernel<1, 1>), dim3(ceil_div((int64_t)N * J, 4)), dim3(256), 0, st, feat, w, b, logits, N, F, J);
+                        const float* b, float* feat, float* logits, float* ws) {
+  const int ranges = head_ranges(dt, N, HW, C, gap, F, J);
+  if (dt == DT_F32) launch_feat_t<float>(st, (const float*)x, N, HW, C, gap, ranges, feat, ws);
+  else if (dt == DT_BF16) launch_feat_t<bf16_t>(st, (const bf16_t*)x, N, HW, C, gap, ranges, feat, ws);
+  else launch_feat_t<f16_t>(st, (const f16_t*)x, N, HW, C, gap, ranges, feat, ws);
+  if (gap || ranges == 1) {
+    launch_head_gemm<HG_FWD>(st, feat, w, b, logits, nullptr, N, J, F, F, F, 1);
+  } else {
+    launch_head_gemm<HG_FWD>(st, feat, w, nullptr, ws, nullptr, N, J, F, F, F, ranges);
+    OSEQ_LAUNCH(head_reduce_kernel, dim3(ceil_div((int64_t)N * J, 256)), dim3(256), 0, st, ws, b, logits, (int64_t)N * J, J, ranges);
+  }
 }
 
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
-                     float* loss_n, float* loss_out, int* flags) {
-  launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits);
+                     float* loss_n, float* loss_out, int* flags, float* ws) {
+  launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits, ws);
   OSEQ_LAUNCH(softmax_ce_kernel, dim3(ceil_div(N, 4)), dim3(256), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags);
   OSEQ_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, st, loss_n, N, loss_out);
 }
 
 void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlogits, const float* w, int N, int HW, int C,
                      int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx) {
-  const int strips = ceil_div(F + 1, 64);
-  if ((int64_t)strips * ceil_div(J, 4) >= 512)
-    OSEQ_LAUNCH(linear_bwd_w_kernel<4>, dim3(strips, ceil_div(J, 4)), dim3(256), 0, st, dlogits, feat, dw, db, N, F, J);
-  else
-    OSEQ_LAUNCH(linear_bwd_w_kernel<1>, dim3(strips, J), dim3(256), 0, st, dlogits, feat, dw, db, N, F, J);
+  launch_head_gemm<HG_DW>(st, dlogits, feat, nullptr, dw, db, J, F, N, J, F, 1);
   if (!dx) return;
-  if ((int64_t)ceil_div(F, 256) * ceil_div(N, 8) >= 512)
-    OSEQ_LAUNCH(linear_bwd_x_kernel<8>, dim3(ceil_div(F, 256), ceil_div(N, 8)), dim3(256), 0, st, dlogits, w, dfeat, N, F, J);
-  else
-    OSEQ_LAUNCH(linear_bwd_x_kernel<1>, dim3(ceil_div(F, 256), N), dim3(256), 0, st, dlogits, w, dfeat, N, F, J);
+  launch_head_gemm<HG_DX>(st, dlogits, w, nullptr, dfeat, nullptr, N, F, J, J, F, 1);
   if (dt == DT_F32) launch_feat_bwd<float>(st, dfeat, dx, N, HW, C, gap);
   else if (dt == DT_BF16) launch_feat_bwd<bf16_t>(st, dfeat, dx, N, HW, C, gap);
   else launch_feat_bwd<f16_t>(st, dfeat, dx, N, HW, C, gap);

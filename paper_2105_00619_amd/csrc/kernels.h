@@ -49,10 +49,12 @@ void launch_maxpool_bwd(hipStream_t st, int dt, const void* x, const void* dy, v
 
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
-                     float* loss_n, float* loss_out, int* flags);
+                     float* loss_n, float* loss_out, int* flags, float* ws);
 // forward of the head up to the logits (no loss): inference
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
-                        const float* b, float* feat, float* logits);
+                        const float* b, float* feat, float* logits, float* ws);
+// ws: workspace of the forward pass, where its sums are split over ranges (null if that needs none)
+int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J);
 void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlogits, const float* w, int N, int HW, int C,
                      int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx);
 

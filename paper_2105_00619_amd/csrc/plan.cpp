@@ -339,6 +339,7 @@ struct Scheduler {
         s.in[0] = cur[f.x];
         s.out[0] = value_inst(f.aux[0]); s.out[1] = value_inst(f.aux[1]);
         s.out[2] = value_inst(f.aux[2]); s.out[3] = value_inst(f.out);
+        if (f.head_ws > 0) s.out[4] = new_inst(-1, (uint64_t)f.head_ws * 4, false);
         break;
       }
     }
@@ -477,7 +478,7 @@ struct Scheduler {
 int launches_of(const SOp& op, const FOp& f) {
   switch (op.kind) {
     case S_BN_STATS: return f.stat_blocks > 0 ? (f.stat_fold > 0 ? 2 : 1) : 2;
-    case S_HEAD_FWD: return 4;
+    case S_HEAD_FWD: return f.head_ws > 0 ? 5 : 4;
     case S_HEAD_BWD: return op.out[0] >= 0 ? 4 : 2;
     case S_BN_BWD: return 3;
     case S_BIAS_GRAD: return 2;

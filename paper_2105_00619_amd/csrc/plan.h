@@ -49,6 +49,7 @@ struct FOp {
   int64_t w_off = -1, b_off = -1, gamma_off = -1, beta_off = -1;  // element offsets, flat parameter vector
   int64_t rs_off = -1;       // element offset of (running mean, running var) in the running-stat block
   int gap = 0, feat_dim = 0, classes = 0;
+  int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
   int fwd_splits = 1, dgrad_splits = 1;  // fixed by shape only: deterministic split of the GEMM depth
@@ -81,7 +82,7 @@ struct SOp {
   int fop = -1;
   int phase = 0, seg = 0;
   int in[4] = {-1, -1, -1, -1};
-  int out[4] = {-1, -1, -1, -1};
+  int out[5] = {-1, -1, -1, -1, -1};
   int variant = 0;  // S_BN_BWD: 1 = in[0] is the gradient of the 2x2 max-pool behind the activation (pooled size);
                     // 2 = in[3] is a bit mask of ReLU decisions (FOp::mask) to apply to in[0], not an activation.
                     // S_DGRAD: in[2] >= 0 is such a mask for the addend in[1]

@@ -215,6 +215,27 @@ def test_pointwise_wgrad_with_a_ragged_last_tile(precision, cin, cout, hw, b):
     assert max(errs.values()) <= TOL[precision], errs
 
 
+@pytest.mark.parametrize("n,h,w,c,classes,gap,precision", [
+    (1, 1, 1, 8, 2, True, W.FP32), (33, 5, 7, 36, 10, True, W.FP32), (5, 3, 3, 6, 33, True, W.FP32),
+    (2, 128, 128, 8, 10, True, W.FP32), (2, 128, 130, 16, 10, True, W.BF16), (2048, 1, 1, 1024, 100, True, W.FP32),
+    (70, 12, 12, 48, 100, False, W.FP32), (3, 4, 5, 20, 37, False, W.FP32), (520, 2, 2, 24, 33, False, W.FP16)])
+def test_head_products_at_tile_edges(n, h, w, c, classes, gap, precision):
+    """The head's pooling and its three products around their 32 x 32 tiles and 16-deep pieces: single rows and columns,
+    remainders, channel counts without 16-byte groups, pooling over several ranges of pixels, a split feature depth.
+    Against plain float64: loss and every gradient, the first layer's fed by the feature gradient."""
+    units = [W.conv(3, c, 1, bn=False, relu=False, bias=True),
+             (W.gap_linear_ce if gap else W.flatten_linear_ce)(c, classes)]
+    p = W.make_params(units, h, w, 17, perturb=True)
+    x = W.make_images(n, h, w, 3, 17, "gauss")
+    y = W.make_labels(n, classes, 17)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=classes, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    loss, g = oracle_step(units, p, x, y, precision, _scale(precision))
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+    errs = plain_errors(units, h, w, r["grads"], g)
+    assert max(errs.values()) <= TOL[precision], errs
+
+
 def _unit_trace(tr, xd, n_units):
     """GPU output of every body unit the plan writes to memory: {unit: float64 array}."""
     from paper_2105_00619_amd.binding import OptorchError
