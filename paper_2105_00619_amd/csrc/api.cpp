@@ -32,6 +32,7 @@ struct optorch_seq {
   int growth_interval = 0, clean = 0;
   bool dynamic_scale = false;
   float* host_rb = nullptr;  // pinned read-back buffer: loss + flags
+  std::vector<EvalJob> eval_jobs;            // every BatchNorm, for the inference-mode scale / shift table
   std::vector<TransposeJob> transpose_jobs;  // layers whose data gradient reads a transposed weight copy
   mutable std::string err;
   // profiling: an event pair per kernel launch of the timed entries, harvested on read
@@ -127,6 +128,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         cv.fold_src = (int)i;
       }
     }
+    build_inference(p);
     // k_segments 0 and storage_mode -1 leave the choice to the plan: the cheapest candidate in step time whose
     // arena fits the budget -- fewest segments first (each further segment replays more of the forward pass),
     // and at equal segments keeping activations before rebuilding them
@@ -179,6 +181,11 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
   h->off_run = o; o = align_up(o + p.n_running * 4);
   h->off_scal = o; o = align_up(o + 256);
   h->param_arena_bytes = o;
+  for (size_t i = 0; i < p.fops.size(); ++i)
+    if (p.fops[i].kind == F_BN_STATS) {
+      const FOp& f = p.fops[i];
+      h->eval_jobs.push_back(EvalJob{f.gamma_off, f.beta_off, p.fops[i - 1].has_bias ? p.fops[i - 1].b_off : -1, f.rs_off, f.C, 0});
+    }
   for (const FOp& f : p.fops)
     if (f.kind == F_CONV && f.dgrad_algo == ALGO_MFMA && p.tensors[f.x].needs_grad)
       h->transpose_jobs.push_back(TransposeJob{f.w_off, f.K, f.R * f.S, f.C, 0});
@@ -534,6 +541,55 @@ extern "C" int optorch_seq_profile_read_entries(optorch_seq_t* h, int32_t capaci
   return OPTORCH_OK;
 }
 
+// Inference on the plan's own schedule: every BatchNorm's scale and shift from the running statistics in one launch, then
+// the forward operations with those BatchNorms (and the skip connections and ReLUs behind them) in the convolutions'
+// epilogues.  Of a convolution's output only the activation is ever written.
+static void infer_fused(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
+  const Plan& p = h->plan;
+  hipStream_t st = h->stream;
+  const int dt = h->dt;
+  auto at = [&](int64_t off) { return off < 0 ? nullptr : (void*)(c.abase + off); };
+  // the table lies in the gradients' part of the parameter arena, which holds nothing between steps and has room for it
+  // (a BatchNorm has as many parameters as running statistics)
+  float* affine = c.g32(0);
+  if (!h->eval_jobs.empty())
+    launch_bn_eval_affine(st, c.w32(0), (const float*)(h->pbase + h->off_run), h->eps, affine, h->eval_jobs.data(),
+                          (int)h->eval_jobs.size());
+  for (const IOp& o : p.infer) {
+    const FOp& f = p.fops[o.fop];
+    switch (o.kind) {
+      case S_CONV_FWD: {
+        ConvEval ev;
+        int relu = f.relu;
+        const float* bias = f.has_bias ? c.w32(f.b_off) : nullptr;
+        if (o.apply >= 0) {
+          const FOp& ap = p.fops[o.apply];
+          ev.affine = affine + ap.rs_off;
+          ev.skip = at(o.skip);
+          relu = ap.relu;
+          bias = nullptr;  // folded into the shift
+        }
+        if (f.fwd_algo == ALGO_MFMA)
+          launch_conv_fwd_mfma(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), (float*)at(o.ws), nullptr, f.fwd_splits, geom(f),
+                               relu, nullptr, ev);
+        else if (f.fwd_algo == ALGO_SMALLC)
+          launch_conv_fwd_smallc(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), geom(f), relu, ev);
+        else
+          launch_conv_fwd_direct(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), geom(f), relu, ev);
+        break;
+      }
+      case S_HEAD_FWD:
+        launch_head_logits(st, dt, at(o.in), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off), c.w32(f.b_off),
+                           (float*)at(o.out), logits_dev, (float*)at(o.ws));
+        break;
+      case S_POOL_FWD: launch_maxpool_fwd(st, dt, at(o.in), at(o.out), f.N, f.H, f.W, f.C); break;
+      default:  // S_CAST_IN
+        if (c.xa) launch_decode_cast(st, dt, c.xa, f.N, (int64_t)f.H * f.W * f.C, c.xz, f.C, c.xscale, c.xshift, at(o.out));
+        else launch_cast_in(st, dt, c.x, at(o.out), (int64_t)f.N * f.H * f.W * f.C);
+    }
+  }
+}
+
 // Inference: the forward entries of the schedule (all segments without keeping, then the last segment), with the
 // BatchNorm constants taken from the running statistics and the head stopped at the logits.  The arena offsets of
 // those entries are valid on their own: the entries run in schedule order and the plan never lets two live tensors
@@ -541,7 +597,10 @@ extern "C" int optorch_seq_profile_read_entries(optorch_seq_t* h, int32_t capaci
 static int predict_run(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
   hipStream_t st = h->stream;
   const int dt = h->dt;
+  const bool fused = h->plan.infer_bytes <= h->plan.arena_bytes;
+  if (fused) infer_fused(h, c, logits_dev);
   for (const SOp& s : h->plan.sched) {
+    if (fused) break;
     if (!s.live || (s.phase != PH_FWD_NOSAVE && s.phase != PH_FWD_LAST)) continue;
     const FOp& f = h->plan.fops[s.fop];
     switch (s.kind) {

@@ -18,11 +18,14 @@ typedef __attribute__((ext_vector_type(4))) float epi_v4f;
 // rowoff(row): element offset of block row `row`'s first channel in the output tensor, or -1 if the row is not stored
 // amask (with an addend; may be null): ReLU decisions as bits, byte e / V for the V = 16 / sizeof(T) elements from
 // element offset e of the addend; an addend element whose bit is clear counts as zero.
-template <int NT, class T, int BN, int HR, bool HB, bool HA, bool STAT, class RowOff>
+// HB: what `bias` is: 0 not used, 1 a bias per channel, EPI_AFFINE the scale of an inference-mode BatchNorm per channel,
+// its shift aff_ld floats behind it (one fused multiply-add on the fp32 sum)
+constexpr int EPI_AFFINE = 2;
+template <int NT, class T, int BN, int HR, int HB, bool HA, bool STAT, class RowOff>
 __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int n0, const float* __restrict__ bias,
                                                const T* __restrict__ addend, const uint8_t* __restrict__ amask,
                                                T* __restrict__ out, int relu, RowOff rowoff,
-                                               float (&ss)[8], float (&qq)[8]) {
+                                               float (&ss)[8], float (&qq)[8], int aff_ld = 0) {
   constexpr int EP_PITCH = BN + 4;
   constexpr int GROUPS = BN / 8;                // 8-channel groups per row
   constexpr int PER_THREAD = HR * GROUPS / NT;  // rows per thread
@@ -33,10 +36,14 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
   int64_t ro[PER_THREAD];
 #pragma unroll
   for (int it = 0; it < PER_THREAD; ++it) ro[it] = rowoff(erow + it * RG);
-  float bv[8];
+  float bv[8], sv[8];
   if (HB) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) bv[k] = bias[col + k];
+    for (int k = 0; k < 8; ++k) bv[k] = bias[(HB == EPI_AFFINE ? aff_ld : 0) + col + k];
+  }
+  if (HB == EPI_AFFINE) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) sv[k] = bias[col + k];
   }
   Vec<T, 8> ad[PER_THREAD];
   unsigned mb[PER_THREAD];
@@ -66,7 +73,7 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
     float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
     if (HB) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] += bv[k];
+      for (int k = 0; k < 8; ++k) v[k] = HB == EPI_AFFINE ? bn_affine(v[k], sv[k], bv[k]) : v[k] + bv[k];
     }
     if (HA) {
 #pragma unroll
@@ -166,11 +173,11 @@ __device__ __forceinline__ void epi_store_pass_nt(const float* ep, int tid, int 
                                                   T* __restrict__ out, int relu, RowOff rowoff,
                                                   float (&ss)[8], float (&qq)[8]) {
   if (CAN_BIAS && bias) {
-    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, true, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
-    else epi_store_rows_nt<NT, T, BN, HR, true, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 1, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    else epi_store_rows_nt<NT, T, BN, HR, 1, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
   } else {
-    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, false, true, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
-    else epi_store_rows_nt<NT, T, BN, HR, false, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 0, true, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    else epi_store_rows_nt<NT, T, BN, HR, 0, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
   }
 }
 template <class T, int BN, int HR, bool CAN_BIAS, bool CAN_ADD, bool STAT, class RowOff>
@@ -179,6 +186,17 @@ __device__ __forceinline__ void epi_store_pass(const float* ep, int tid, int n0,
                                                T* __restrict__ out, int relu, RowOff rowoff,
                                                float (&ss)[8], float (&qq)[8]) {
   epi_store_pass_nt<256, T, BN, HR, CAN_BIAS, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+}
+
+// The store pass of a convolution with the inference-mode BatchNorm behind it: the activation itself is stored, with the
+// skip connection (or null) added, so that neither z nor a separate pass over it exists.
+// affine: [2][aff_ld] scale and shift
+template <int NT, class T, int BN, int HR, class RowOff>
+__device__ __forceinline__ void epi_eval_pass_nt(const float* ep, int tid, int n0, const float* __restrict__ affine, int aff_ld,
+                                                 const T* __restrict__ skip, T* __restrict__ out, int relu, RowOff rowoff) {
+  float ss[8], qq[8];  // (no sums)
+  if (skip) epi_store_rows_nt<NT, T, BN, HR, EPI_AFFINE, true, false>(ep, tid, n0, affine, skip, nullptr, out, relu, rowoff, ss, qq, aff_ld);
+  else epi_store_rows_nt<NT, T, BN, HR, EPI_AFFINE, false, false>(ep, tid, n0, affine, skip, nullptr, out, relu, rowoff, ss, qq, aff_ld);
 }
 
 // raw fp32 sums of a depth range (no epilogue arithmetic): dst + rowoff(row) + channel

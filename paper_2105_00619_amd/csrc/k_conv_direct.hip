@@ -10,7 +10,8 @@ namespace oseq {
 template <class T>
 __global__ void __launch_bounds__(256) conv_fwd_direct_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                               const float* __restrict__ bias, T* __restrict__ out,
-                                                              ConvGeom g, int relu) {
+                                                              ConvGeom g, int relu, const float* __restrict__ affine,
+                                                              const T* __restrict__ skip) {
   const int64_t total = (int64_t)g.N * g.P * g.Q * g.K;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
@@ -31,7 +32,12 @@ __global__ void __launch_bounds__(256) conv_fwd_direct_kernel(const T* __restric
       for (int c = 0; c < g.C; ++c) acc = __fmaf_rn(to_f32(xp[c]), to_f32(wp[c]), acc);
     }
   }
-  if (bias) acc += bias[k];
+  if (affine) {  // the inference-mode BatchNorm behind the layer (affine: [2][K] scale and shift)
+    acc = bn_affine(acc, affine[k], affine[g.K + k]);
+    if (skip) acc += to_f32(skip[i]);
+  } else if (bias) {
+    acc += bias[k];
+  }
   if (relu) acc = fmaxf(acc, 0.f);
   out[i] = from_f32<T>(acc);
 }
@@ -117,7 +123,8 @@ constexpr int SMALLC_MAX = 36;
 template <class T, int C>
 __global__ void __launch_bounds__(256) conv_fwd_smallc_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                               const float* __restrict__ bias, T* __restrict__ out,
-                                                              ConvGeom g, int relu, FastDiv divQ, FastDiv divPQ) {
+                                                              ConvGeom g, int relu, FastDiv divQ, FastDiv divPQ,
+                                                              const float* __restrict__ affine, const T* __restrict__ skip) {
   // block = 128 pixels x 64 output channels (blockIdx.y selects the group of 64); thread = 4 pixels x 8 channels,
   // the 8 threads of a pixel next to each other so that a wavefront writes 8 whole rows of 64 channels, and every
   // weight read from LDS serves four pixels.  The 8 threads of a pixel share the loading of its R*S*C inputs
@@ -192,7 +199,13 @@ __global__ void __launch_bounds__(256) conv_fwd_smallc_kernel(const T* __restric
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       float a = acc[i][j];
-      if (bias) a += bias[kbase + grp * 8 + j];
+      const int k = kbase + grp * 8 + j;
+      if (affine) {  // the inference-mode BatchNorm behind the layer (affine: [2][K] scale and shift)
+        a = bn_affine(a, affine[k], affine[g.K + k]);
+        if (skip) a += to_f32(skip[(int64_t)m[i] * g.K + k]);
+      } else if (bias) {
+        a += bias[k];
+      }
       acc[i][j] = relu ? fmaxf(a, 0.f) : a;
     }
     store_f32<T, 8>(out + (int64_t)m[i] * g.K + kbase + grp * 8, acc[i]);
@@ -217,10 +230,12 @@ template <> struct StemMma<f16_t> {
   __device__ static __forceinline__ A run(V a, V b, A c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 
-template <class T, int C>
+template <class T, int C, bool EVAL>
 __global__ void __launch_bounds__(256) conv_fwd_smallc_mfma_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                                    const float* __restrict__ bias, T* __restrict__ out,
-                                                                   ConvGeom g, int relu, FastDiv divQ, FastDiv divPQ) {
+                                                                   ConvGeom g, int relu, FastDiv divQ, FastDiv divPQ,
+                                                                   const T* __restrict__ skip) {
+  // (EVAL: bias is the [2][K] scale and shift of the inference-mode BatchNorm behind the layer)
   typedef typename StemMma<T>::V FV;
   typedef typename StemMma<T>::A v16f;
   constexpr int RSC = 9 * C;       // <= 32
@@ -304,8 +319,11 @@ __global__ void __launch_bounds__(256) conv_fwd_smallc_mfma_kernel(const T* __re
       const int64_t m = (int64_t)blockIdx.x * 128 + u * 64 + row;
       return m < pixels ? m * g.K : -1;
     };
-    epi_store_pass<T, 64, 64, true, false, false>(ep, tid, kbase, bias, (const T*)nullptr, (const uint8_t*)nullptr, out, relu,
-                                                  rowoff, ss, qq);
+    if (EVAL)
+      epi_eval_pass_nt<256, T, 64, 64>(ep, tid, kbase, bias, g.K, skip, out, relu, rowoff);
+    else
+      epi_store_pass<T, 64, 64, true, false, false>(ep, tid, kbase, bias, (const T*)nullptr, (const uint8_t*)nullptr, out, relu,
+                                                    rowoff, ss, qq);
   }
 }
 
@@ -485,32 +503,41 @@ int conv_smallc_wgrad_splits(const ConvGeom& g) {
 
 template <class T>
 static void launch_fwd_smallc_t(hipStream_t st, const void* x, const void* w, const float* bias, void* out, const ConvGeom& g,
-                                int relu) {
+                                int relu, const ConvEval& ev) {
   dim3 grid(ceil_div((int64_t)g.N * g.P * g.Q, 128), ceil_div(g.K, 64)), block(256);
   const FastDiv dq = make_fastdiv((uint32_t)g.Q), dpq = make_fastdiv((uint32_t)(g.P * g.Q));
+  const T* skip = (const T*)ev.skip;
   if constexpr (sizeof(T) == 2) {
     if (g.K % 64 == 0 && g.C <= 3) {  // 16-bit modes: on the matrix cores
-      switch (g.C) {
-        case 1: OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, 1>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-        case 2: OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, 2>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-        default: OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, 3>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-      }
+#define SMALLC_MFMA(C_)                                                                                                       \
+  {                                                                                                                           \
+    if (ev.affine) OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, C_, true>), grid, block, 0, st, (const T*)x, (const T*)w,      \
+                               ev.affine, (T*)out, g, relu, dq, dpq, skip);                                                   \
+    else OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, C_, false>), grid, block, 0, st, (const T*)x, (const T*)w, bias,         \
+                     (T*)out, g, relu, dq, dpq, skip);                                                                        \
+  }
+      if (g.C == 1) SMALLC_MFMA(1) else if (g.C == 2) SMALLC_MFMA(2) else SMALLC_MFMA(3)
+#undef SMALLC_MFMA
       return;
     }
   }
+#define SMALLC_FMA(C_)                                                                                                \
+  OSEQ_LAUNCH((conv_fwd_smallc_kernel<T, C_>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, \
+              dq, dpq, ev.affine, skip)
   switch (g.C) {
-    case 1: OSEQ_LAUNCH((conv_fwd_smallc_kernel<T, 1>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-    case 2: OSEQ_LAUNCH((conv_fwd_smallc_kernel<T, 2>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-    case 3: OSEQ_LAUNCH((conv_fwd_smallc_kernel<T, 3>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
-    default: OSEQ_LAUNCH((conv_fwd_smallc_kernel<T, 4>), grid, block, 0, st, (const T*)x, (const T*)w, bias, (T*)out, g, relu, dq, dpq); break;
+    case 1: SMALLC_FMA(1); break;
+    case 2: SMALLC_FMA(2); break;
+    case 3: SMALLC_FMA(3); break;
+    default: SMALLC_FMA(4); break;
   }
+#undef SMALLC_FMA
 }
 
 void launch_conv_fwd_smallc(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu) {
-  if (dt == DT_F32) launch_fwd_smallc_t<float>(st, x, w, bias, out, g, relu);
-  else if (dt == DT_BF16) launch_fwd_smallc_t<bf16_t>(st, x, w, bias, out, g, relu);
-  else launch_fwd_smallc_t<f16_t>(st, x, w, bias, out, g, relu);
+                            const ConvGeom& g, int relu, const ConvEval& ev) {
+  if (dt == DT_F32) launch_fwd_smallc_t<float>(st, x, w, bias, out, g, relu, ev);
+  else if (dt == DT_BF16) launch_fwd_smallc_t<bf16_t>(st, x, w, bias, out, g, relu, ev);
+  else launch_fwd_smallc_t<f16_t>(st, x, w, bias, out, g, relu, ev);
 }
 
 // partial: [splits][K][R*S*C] floats; splits = conv_smallc_wgrad_splits(g)
@@ -532,12 +559,12 @@ void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void*
 }
 
 void launch_conv_fwd_direct(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu) {
+                            const ConvGeom& g, int relu, const ConvEval& ev) {
   const int64_t total = (int64_t)g.N * g.P * g.Q * g.K;
   dim3 grid(ceil_div(total, 256)), block(256);
-  if (dt == DT_F32) OSEQ_LAUNCH(conv_fwd_direct_kernel<float>, grid, block, 0, st, (const float*)x, (const float*)w, bias, (float*)out, g, relu);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_fwd_direct_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)out, g, relu);
-  else OSEQ_LAUNCH(conv_fwd_direct_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)w, bias, (f16_t*)out, g, relu);
+  if (dt == DT_F32) OSEQ_LAUNCH(conv_fwd_direct_kernel<float>, grid, block, 0, st, (const float*)x, (const float*)w, bias, (float*)out, g, relu, ev.affine, (const float*)ev.skip);
+  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_fwd_direct_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)out, g, relu, ev.affine, (const bf16_t*)ev.skip);
+  else OSEQ_LAUNCH(conv_fwd_direct_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)w, bias, (f16_t*)out, g, relu, ev.affine, (const f16_t*)ev.skip);
 }
 
 void launch_conv_dgrad_direct(hipStream_t st, int dt, const void* dz, const void* w, const void* addend, void* dx,

@@ -30,7 +30,7 @@ typedef __attribute__((ext_vector_type(4))) float v4f;
 
 // 16 bytes in flight between global memory and LDS: a first-class vector value, never a stack object
 
-enum { IG_FWD = 0, IG_DGRAD = 1 };
+enum { IG_FWD = 0, IG_DGRAD = 1, IG_EVAL = 2 };  // IG_EVAL: forward with the inference-mode BatchNorm in the epilogue
 
 struct IGemmArgs {
   int srcH, srcW, srcC;   // gathered tensor
@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
     for (int i = 0; i < A_CH; ++i) {
       int y, x;
       bool ok = pn[i] >= 0;
-      if (MODE == IG_FWD) {
+      if (MODE != IG_DGRAD) {
         y = pa[i] * stride + r - pad;
         x = pb[i] * stride + s - pad;
       } else {
@@ -335,6 +335,8 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
       };
       if (SPLIT) {
         epi_store_partial<BN, HR>(ep, tid, n0, partial + (int64_t)blockIdx.z * a.M * a.Ng, rowoff);
+      } else if (MODE == IG_EVAL) {
+        epi_eval_pass_nt<256, T, BN, HR>(ep, tid, n0, bias, a.Ng, addend, out, a.relu, rowoff);
       } else if (STAT && stat_partial) {
         epi_store_pass<T, BN, HR, MODE == IG_FWD, MODE == IG_DGRAD, true>(ep, tid, n0, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
       } else {
@@ -377,6 +379,7 @@ struct PatchArgs {
                              // 2: so that the channel blocks and depth ranges of one row tile do (row_blocks: row tiles)
   int row_blocks;
   const uint8_t* amask;      // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
+  int eval;                  // 1: the EVAL instantiation
   const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
                              // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
                              // to LDS; positions outside the image stay zero
@@ -384,7 +387,8 @@ struct PatchArgs {
 
 constexpr int PATCH_MAX_POS = 256;  // positions per sub-tile
 
-template <class T, int BN, int MI, int SUBT, bool STAT, bool FOLD = false>
+// EVAL: `bias` is the [2][Ng] scale and shift of the inference-mode BatchNorm behind the layer, `addend` its skip connection
+template <class T, int BN, int MI, int SUBT, bool STAT, bool FOLD = false, bool EVAL = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BN == 64 ? 3 : 1, BN == 64 ? 3 : 2)))
 conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const float* __restrict__ bias,
                      const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ partial,
@@ -661,6 +665,8 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
       auto rowoff = [&](int row) -> int64_t { return out_off[u * HR + row]; };
       if (partial)
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
+      else if (EVAL)
+        epi_eval_pass_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff);
       else
         epi_store_pass<T, BN, HR, true, !STAT, STAT>(ep, tid, n0c, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
     }
@@ -681,7 +687,8 @@ template <class T>
 __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __restrict__ partial, int splits, int64_t M, int Ng,
                                                               const float* __restrict__ bias, const T* __restrict__ addend,
                                                               const uint8_t* __restrict__ amask, T* __restrict__ out,
-                                                              float* __restrict__ stat_partial, int relu) {
+                                                              float* __restrict__ stat_partial, int relu,
+                                                              const float* __restrict__ affine) {
   __shared__ float red[2][16][64];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int col = blockIdx.y * 64 + tx * 4;
@@ -690,6 +697,11 @@ __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __res
   if (bias) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) bv[e] = bias[col + e];
+  }
+  float sv[4] = {1.f, 1.f, 1.f, 1.f};
+  if (affine) {  // (no bias then)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { sv[e] = affine[col + e]; bv[e] = affine[Ng + col + e]; }
   }
   float ss[4] = {0.f, 0.f, 0.f, 0.f}, qq[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -705,7 +717,7 @@ __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __res
       if (addend && amask) mb = sizeof(T) == 2 ? (amask[i >> 3] >> (i & 4)) & 15u : amask[i >> 2] & 15u;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float v = acc[e] + bv[e];
+        float v = affine ? bn_affine(acc[e], sv[e], bv[e]) : acc[e] + bv[e];
         if (addend && ((mb >> e) & 1u)) v += to_f32(addend[i + e]);
         r[e] = relu ? fmaxf(v, 0.f) : v;
       }
@@ -735,10 +747,11 @@ __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __res
 
 template <class T>
 static void launch_splitk_epilogue(hipStream_t st, const float* partial, int splits, int64_t M, int Ng, const float* bias,
-                                   const void* addend, const uint8_t* amask, void* out, float* stat_partial, int relu) {
+                                   const void* addend, const uint8_t* amask, void* out, float* stat_partial, int relu,
+                                   const float* affine = nullptr) {
   dim3 grid(ceil_div(M, SPLIT_EPI_ROWS), Ng / 64);  // Ng % 64 == 0 for every MFMA convolution
   OSEQ_LAUNCH(splitk_epilogue_kernel<T>, grid, dim3(256), 0, st, partial, splits, M, Ng, bias, (const T*)addend, amask,
-                     (T*)out, stat_partial, relu);
+                     (T*)out, stat_partial, relu, affine);
 }
 
 // LDS of the patch kernel: two patch buffers of patch_elems elements, three weight stages, the address tables
@@ -866,6 +879,18 @@ static void launch_patch_v(hipStream_t st, const void* src, const void* wmat, co
     grid.x = (grid.x + 7) / 8 * 8;
   }
   const size_t sm = patch_smem_bytes<T>(BN, SUBT, pe);
+  if constexpr (!FOLD) {
+    if (a.eval && splits == 1) {
+      static bool eval_attr = false;
+      if (!eval_attr) {
+        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, BN, MI, SUBT, false, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+        eval_attr = true;
+      }
+      OSEQ_LAUNCH((conv3x3_patch_kernel<T, BN, MI, SUBT, false, false, true>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+                  (const T*)addend, (T*)out, (float*)nullptr, (float*)nullptr, a);
+      return;
+    }
+  }
   static bool attr_done = false;
   if (!attr_done) {
     (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, BN, MI, SUBT, false, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
@@ -905,7 +930,8 @@ static void launch_patch_t(hipStream_t st, const void* src, const void* wmat, co
     }
   }
   if (sp > 1)
-    launch_splitk_epilogue<T>(st, partial, sp, (int64_t)a.N * a.dstH * a.dstW, a.Ng, bias, addend, a.amask, out, stat_partial, a.relu);
+    launch_splitk_epilogue<T>(st, partial, sp, (int64_t)a.N * a.dstH * a.dstW, a.Ng, a.eval ? nullptr : bias, addend, a.amask, out,
+                              stat_partial, a.relu, a.eval ? bias : nullptr);
 }
 
 static void launch_patch(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
@@ -940,17 +966,21 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
     constexpr size_t big_ = sm_ > kSpreadLds ? sm_ : kSpreadLds;                                                         \
     static bool attr_ = false;                                                                                           \
     if (!attr_) {                                                                                                        \
-      (void)hipFuncSetAttribute((const void*)conv_igemm_kernel<T, BM_, BN_, MODE, SPLIT_>,                               \
+      (void)hipFuncSetAttribute((const void*)conv_igemm_kernel<T, BM_, BN_, MODE_, SPLIT_>,                               \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)big_);                                  \
       attr_ = true;                                                                                                      \
     }                                                                                                                    \
-    OSEQ_LAUNCH((conv_igemm_kernel<T, BM_, BN_, MODE, SPLIT_>), grid, block, spread ? big_ : sm_, st,             \
+    OSEQ_LAUNCH((conv_igemm_kernel<T, BM_, BN_, MODE_, SPLIT_>), grid, block, spread ? big_ : sm_, st,             \
                        (const T*)src, (const T*)wmat, bias, (const T*)addend, (T*)out, partial, stat_partial, a);        \
   }
   if (splits > 1) {
+    // (the depth ranges are stored as they are: the forward and the inference instantiation would be the same kernel)
+    constexpr int MODE_ = MODE == IG_EVAL ? IG_FWD : MODE;
     if (wide) IGEMM_LAUNCH(128, 128, true) else IGEMM_LAUNCH(128, 64, true)
-    launch_splitk_epilogue<T>(st, partial, splits, a.M, a.Ng, bias, addend, a.amask, out, stat_partial, a.relu);
+    launch_splitk_epilogue<T>(st, partial, splits, a.M, a.Ng, MODE == IG_EVAL ? nullptr : bias, addend, a.amask, out, stat_partial,
+                              a.relu, MODE == IG_EVAL ? bias : nullptr);
   } else {
+    constexpr int MODE_ = MODE;
     if (wide) IGEMM_LAUNCH(128, 128, false) else IGEMM_LAUNCH(128, 64, false)
   }
 #undef IGEMM_LAUNCH
@@ -1025,21 +1055,25 @@ bool conv_fold_fwd_ok(int dt, const ConvGeom& g) {
 }
 
 void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                          float* partial, float* stat_partial, int splits, const ConvGeom& g, int relu, const float* fold) {
+                          float* partial, float* stat_partial, int splits, const ConvGeom& g, int relu, const float* fold,
+                          const ConvEval& ev) {
   PatchShape pv; PatchArgs pa{};
   if (conv_pointwise_fwd_ok(dt, g)) {
-    launch_conv_fwd_pointwise(st, dt, x, w, bias, out, stat_partial, g, relu, fold);
+    launch_conv_fwd_pointwise(st, dt, x, w, bias, out, stat_partial, g, relu, fold, ev);
     return;
   }
+  const bool eval = ev.affine != nullptr;
   if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.H; pa.srcW = g.W; pa.srcC = g.C; pa.dstH = g.P; pa.dstW = g.Q; pa.Ng = g.K;
     pa.pad = g.pad; pa.flip = 0; pa.relu = relu;
     pa.fold = dt == DT_F32 ? nullptr : fold;
-    launch_patch(st, dt, x, w, bias, nullptr, out, partial, stat_partial, pv, pa);
+    pa.eval = eval;
+    launch_patch(st, dt, x, w, eval ? ev.affine : bias, ev.skip, out, partial, stat_partial, pv, pa);
     return;
   }
   IGemmArgs a{g.H, g.W, g.C, g.P, g.Q, g.N * g.P * g.Q, g.K, g.R * g.S * g.C, g.R, g.S, g.stride, g.pad, relu, 0};
-  launch_igemm<IG_FWD>(st, dt, x, w, bias, nullptr, out, partial, stat_partial, splits, a);
+  if (eval) launch_igemm<IG_EVAL>(st, dt, x, w, ev.affine, ev.skip, out, partial, nullptr, splits, a);
+  else launch_igemm<IG_FWD>(st, dt, x, w, bias, nullptr, out, partial, stat_partial, splits, a);
 }
 
 // wt: the (C_in, kh, kw, C_out) transpose of the weights, in the compute type

@@ -50,6 +50,8 @@ struct PwArgs {
   int dstH, dstW, srcH, srcW;
   FastDiv div_w, div_hw;  // by dstW and dstH * dstW
   const uint8_t* amask;   // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
+  int eval;               // 1: the EVAL instantiations (inference-mode BatchNorm in the epilogue, `bias` is its [2][Ng]
+                          // scale and shift and `addend` its skip connection)
   const float* fold;      // forward: X is the z of a BatchNorm + ReLU whose [4][Kd] statistics tensor this is; the rows are
                           //          turned into the activation (scale, shift, ReLU, one rounding) on their way to LDS
 };
@@ -110,7 +112,7 @@ __device__ __forceinline__ void scatter_rows(const float* ep, int tid, int n0, i
 
 // DGRAD: the data-gradient instantiation (addend and scatter, no bias / ReLU / sums); else the forward one
 // (FOLD needs some forty registers more: two blocks per CU instead of three)
-template <class T, int BN, bool DGRAD, bool FOLD = false>
+template <class T, int BN, bool DGRAD, bool FOLD = false, bool EVAL = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOLD ? 2 : 3, FOLD ? 2 : 3)))
 conv1x1_kernel(const T* __restrict__ X, const T* __restrict__ W, const float* __restrict__ bias, const T* __restrict__ addend,
                T* __restrict__ out, float* __restrict__ stat_partial, PwArgs a) {
@@ -260,12 +262,14 @@ conv1x1_kernel(const T* __restrict__ X, const T* __restrict__ W, const float* __
     if (DGRAD) {
       if (a.scatter) scatter_rows<T, BN>(ep, tid, n0, m0 + u * 64, addend, out, a);
       else epi_store_pass<T, BN, 64, false, true, false>(ep, tid, n0, bias, addend, a.amask, out, 0, rowoff, ss, qq);
+    } else if (EVAL) {
+      epi_eval_pass_nt<256, T, BN, 64>(ep, tid, n0, bias, a.Ng, addend, out, a.relu, rowoff);
     } else {
       if (stat_partial) epi_store_pass<T, BN, 64, true, false, true>(ep, tid, n0, bias, addend, nullptr, out, a.relu, rowoff, ss, qq);
       else epi_store_pass<T, BN, 64, true, false, false>(ep, tid, n0, bias, addend, nullptr, out, a.relu, rowoff, ss, qq);
     }
   }
-  if (!DGRAD && stat_partial)
+  if (!DGRAD && !EVAL && stat_partial)
     epi_stat_combine<BN>(ep, tid, ss, qq, stat_partial + ((int64_t)mt * 2 + 0) * a.Ng + n0,
                          stat_partial + ((int64_t)mt * 2 + 1) * a.Ng + n0);
 }
@@ -288,7 +292,7 @@ template <int BM, int BN> constexpr size_t pwl_smem_bytes() {
 }
 
 // BM x BN tile, WGM x WGN wavefronts (wave tile BM / WGM x BN / WGN, at least 64 rows)
-template <class T, bool DGRAD, int BM, int BN, int WGM, int WGN, bool FOLD = false>
+template <class T, bool DGRAD, int BM, int BN, int WGM, int WGN, bool FOLD = false, bool EVAL = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2, 2)))
 conv1x1_large_kernel(const T* __restrict__ X, const T* __restrict__ W, const float* __restrict__ bias,
                      const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ stat_partial, PwArgs a) {
@@ -438,12 +442,14 @@ conv1x1_large_kernel(const T* __restrict__ X, const T* __restrict__ W, const flo
       epi_store_rows_pre_nt<NT, T, BN, 64>(ep, tid, n0, ad, mb, out, rowoff);
     } else if (DGRAD) {
       epi_store_pass_nt<NT, T, BN, 64, false, true, false>(ep, tid, n0, bias, addend, a.amask, out, 0, rowoff, ss, qq);
+    } else if (EVAL) {
+      epi_eval_pass_nt<NT, T, BN, 64>(ep, tid, n0, bias, a.Ng, addend, out, a.relu, rowoff);
     } else {
       if (stat_partial) epi_store_pass_nt<NT, T, BN, 64, true, false, true>(ep, tid, n0, bias, addend, nullptr, out, a.relu, rowoff, ss, qq);
       else epi_store_pass_nt<NT, T, BN, 64, true, false, false>(ep, tid, n0, bias, addend, nullptr, out, a.relu, rowoff, ss, qq);
     }
   }
-  if (!DGRAD && stat_partial)
+  if (!DGRAD && !EVAL && stat_partial)
     epi_stat_combine_nt<NT, BN>(ep, tid, ss, qq, stat_partial + ((int64_t)mt * 2 + 0) * a.Ng + n0,
                                 stat_partial + ((int64_t)mt * 2 + 1) * a.Ng + n0);
 }
@@ -655,10 +661,14 @@ template <int KD> constexpr size_t pws_smem_bytes() {
   return (size_t)pws_bm(KD) * (KD + 8) * 2 + (size_t)pws_bm(KD) * (PWS_BN + 8) * 2 + (size_t)2 * 2 * PWS_BN * 4 + (size_t)2 * KD * 4;
 }
 
-template <class T, bool FOLD, int KD>
+//
+// EVAL: the inference-mode BatchNorm behind the layer on the accumulators (`bias` is its [2][Ng] scale and shift).  The
+// skip connection's tile is requested with the tile of X and laid into `stg` by the threads that have just stored their
+// pieces from there; a lane then adds its elements in fp32 before the one rounding.
+template <class T, bool FOLD, int KD, bool EVAL = false>
 __global__ void __launch_bounds__(512)
 conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float* __restrict__ bias, T* __restrict__ out,
-                  float* __restrict__ stat_partial, PwArgs a) {
+                  float* __restrict__ stat_partial, const T* __restrict__ skip, PwArgs a) {
   typedef typename Mma<T>::V FV;
   typedef typename Dot2<T>::V T2;
   constexpr int NT = 512, BM = pws_bm(KD), BN = PWS_BN, APITCH = KD + 8, EPITCH = BN + 8;
@@ -693,7 +703,8 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
   if (FOLD) {
     for (int i = tid; i < KD; i += NT) { ftab[i] = a.fold[2 * KD + i]; ftab[KD + i] = a.fold[3 * KD + i]; }
   }
-  const float bj = bias ? bias[n0 + cj] : 0.f;
+  const float bj = bias ? bias[(EVAL ? a.Ng : 0) + n0 + cj] : 0.f;
+  const float sj = EVAL ? bias[n0 + cj] : 1.f;
 
   const int cc = tid % CPR, r0 = tid / CPR;
   Chunk ra[A_CH];
@@ -716,6 +727,22 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
   };
   const int afrag = l32 * APITCH + g * 16;
   const int c8 = (tid % (BN / 8)) * 8, erow = tid / (BN / 8);
+  // EVAL: this thread's pieces of the skip connection's tile, requested as those of X (rows past the last pixel read row 0)
+  constexpr int E_CH = BM * (BN / 8) / NT, ERPI = NT / (BN / 8);
+  Chunk rs[EVAL ? E_CH : 1];
+  auto sload = [&](int t) {
+    if (!EVAL || !skip) return;
+#pragma unroll
+    for (int i = 0; i < E_CH; ++i) {
+      const int64_t m = (int64_t)t * BM + erow + i * ERPI;
+      rs[i] = *reinterpret_cast<const Chunk*>(skip + (m < a.M ? m : 0) * a.Ng + n0 + c8);
+    }
+  };
+  auto sput = [&]() {
+    if (!EVAL || !skip) return;
+#pragma unroll
+    for (int i = 0; i < E_CH; ++i) *reinterpret_cast<Chunk*>(&stg[(erow + i * ERPI) * EPITCH + c8]) = rs[i];
+  };
   float S1 = 0.f, S2 = 0.f;
   T2 one2;
   one2[0] = from_f32<T>(1.f); one2[1] = from_f32<T>(1.f);
@@ -731,7 +758,8 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
     }
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) *reinterpret_cast<Chunk*>(&abuf[(r0 + i * RPI) * APITCH + cc * 8]) = ra[i];
-    if (tnext < MT) gload(tnext);
+    sput();
+    if (tnext < MT) { gload(tnext); sload(tnext); }
   };
 
   // Two barriers per row tile: the MFMAs of tile t and the rounding of its results into `stg` between them; then the
@@ -739,6 +767,7 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
   // in-order counter: the rows a tile waits for were requested before the stores of the tile before it.
   int t = rg;  // < MT
   gload(t);
+  sload(t);
   if (FOLD) __syncthreads();  // the scale / shift table
   stage_tile(t + RGN);
   for (;;) {
@@ -772,15 +801,20 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
         for (int e = 0; e < 16; e += 2) {
           const int r = i * 32 + 8 * (e >> 2) + 4 * g + (e & 3);  // and r + 1
           float v0 = acc[i][e], v1 = acc[i][e + 1];
-          if (general) { v0 += bj; v1 += bj; }
+          if (EVAL) {
+            v0 = bn_affine(v0, sj, bj); v1 = bn_affine(v1, sj, bj);
+            if (skip) { v0 += to_f32(stg[r * EPITCH + cj]); v1 += to_f32(stg[(r + 1) * EPITCH + cj]); }
+          } else if (general) { v0 += bj; v1 += bj; }
           if (relu) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
           if (rag) {  // rows past the last pixel count as zero
             if (m0 + r >= a.M) v0 = 0.f;
             if (m0 + r + 1 >= a.M) v1 = 0.f;
           }
           const T2 p2 = from_f32x2<T>(v0, v1);
-          s1 = Dot2<T>::run(p2, one2, s1);
-          s2 = Dot2<T>::run(p2, p2, s2);
+          if (!EVAL) {
+            s1 = Dot2<T>::run(p2, one2, s1);
+            s2 = Dot2<T>::run(p2, p2, s2);
+          }
           stg[r * EPITCH + cj] = p2[0];
           stg[(r + 1) * EPITCH + cj] = p2[1];
         }
@@ -806,7 +840,7 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
     if (t >= MT) break;
     stage_tile(t + RGN);
   }
-  if (stat_partial) {  // the two lane groups of a channel in a fixed order
+  if (!EVAL && stat_partial) {  // the two lane groups of a channel in a fixed order
     red[g * BN + cj] = S1;
     red[(2 + g) * BN + cj] = S2;
     __syncthreads();
@@ -817,18 +851,19 @@ conv1x1_ws_kernel(const T* __restrict__ X, const T* __restrict__ W, const float*
   }
 }
 
-template <class T, bool FOLD, int KD>
-void launch_pw_ws(hipStream_t st, const void* X, const void* W, const float* bias, void* out, float* stat_partial, PwArgs a) {
+template <class T, bool FOLD, int KD, bool EVAL = false>
+void launch_pw_ws(hipStream_t st, const void* X, const void* W, const float* bias, const void* skip, void* out, float* stat_partial,
+                  PwArgs a) {
   constexpr size_t sm = pws_smem_bytes<KD>();
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv1x1_ws_kernel<T, FOLD, KD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    (void)hipFuncSetAttribute((const void*)conv1x1_ws_kernel<T, FOLD, KD, EVAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     attr_done = true;
   }
   a.MT = ceil_div(a.M, pws_bm(KD));
   a.NT = a.Ng / PWS_BN;
-  OSEQ_LAUNCH((conv1x1_ws_kernel<T, FOLD, KD>), dim3(PWS_BLOCKS), dim3(512), sm, st, (const T*)X, (const T*)W, bias, (T*)out,
-              stat_partial, a);
+  OSEQ_LAUNCH((conv1x1_ws_kernel<T, FOLD, KD, EVAL>), dim3(PWS_BLOCKS), dim3(512), sm, st, (const T*)X, (const T*)W, bias, (T*)out,
+              stat_partial, (const T*)skip, a);
 }
 
 // from the shape only: depth 64, 128 or 256 and at least twice as many output channels; 1, 2, 4 ... 32 channel groups;
@@ -841,9 +876,11 @@ bool pw_ws_ok(int64_t M, int Ng, int Kd, int stride) {
 }
 
 template <class T, int KD>
-void launch_pw_ws_t(hipStream_t st, const void* X, const void* W, const float* bias, void* out, float* stat_partial, const PwArgs& a) {
-  if (a.fold) launch_pw_ws<T, true, KD>(st, X, W, bias, out, stat_partial, a);
-  else launch_pw_ws<T, false, KD>(st, X, W, bias, out, stat_partial, a);
+void launch_pw_ws_t(hipStream_t st, const void* X, const void* W, const float* bias, const void* skip, void* out,
+                    float* stat_partial, const PwArgs& a) {
+  if (a.eval) launch_pw_ws<T, false, KD, true>(st, X, W, bias, skip, out, stat_partial, a);
+  else if (a.fold) launch_pw_ws<T, true, KD>(st, X, W, bias, nullptr, out, stat_partial, a);
+  else launch_pw_ws<T, false, KD>(st, X, W, bias, nullptr, out, stat_partial, a);
 }
 
 template <class T, int KD>
@@ -867,20 +904,20 @@ bool pw_rows_ok(int64_t M, int Ng, int Kd, int stride, bool scatter) {
 
 constexpr int PW_FOLD_MAX_DEPTH = 1024;  // the scale / shift table of a folded BatchNorm takes 8 bytes of LDS per channel
 
-template <class T, bool DGRAD, int BM, int BN, int WGM, int WGN, bool FOLD>
+template <class T, bool DGRAD, int BM, int BN, int WGM, int WGN, bool FOLD, bool EVAL = false>
 void launch_pw_large(hipStream_t st, const void* X, const void* W, const float* bias, const void* addend, void* out,
                      float* stat_partial, PwArgs a) {
   constexpr size_t sm = pwl_smem_bytes<BM, BN>();
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv1x1_large_kernel<T, DGRAD, BM, BN, WGM, WGN, FOLD>,
+    (void)hipFuncSetAttribute((const void*)conv1x1_large_kernel<T, DGRAD, BM, BN, WGM, WGN, FOLD, EVAL>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sm + (FOLD ? PW_FOLD_MAX_DEPTH * 8 : 0)));
     attr_done = true;
   }
   a.MT = ceil_div(a.M, BM);
   a.NT = a.Ng / BN;
   const int grid = ((a.MT + 7) / 8) * 8 * a.NT;
-  OSEQ_LAUNCH((conv1x1_large_kernel<T, DGRAD, BM, BN, WGM, WGN, FOLD>), dim3(grid), dim3(64 * WGM * WGN),
+  OSEQ_LAUNCH((conv1x1_large_kernel<T, DGRAD, BM, BN, WGM, WGN, FOLD, EVAL>), dim3(grid), dim3(64 * WGM * WGN),
               sm + (FOLD ? (size_t)a.Kd * 8 : 0), st, (const T*)X, (const T*)W, bias, (const T*)addend, (T*)out, stat_partial, a);
 }
 
@@ -890,18 +927,18 @@ bool pw_large_ok(int64_t M, int Ng, int Kd, int stride, bool scatter) {
   return (int64_t)ceil_div(M, PWL_BM) * (Ng / PWL_BN) >= 512;
 }
 
-template <class T, int BN, bool DGRAD, bool FOLD>
+template <class T, int BN, bool DGRAD, bool FOLD, bool EVAL = false>
 void launch_pw_v(hipStream_t st, const void* X, const void* W, const float* bias, const void* addend, void* out,
                  float* stat_partial, const PwArgs& a) {
   constexpr size_t sm = pw_smem_bytes<BN>();
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv1x1_kernel<T, BN, DGRAD, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void*)conv1x1_kernel<T, BN, DGRAD, FOLD, EVAL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(sm + (FOLD ? PW_FOLD_MAX_DEPTH * 8 : 0)));
     attr_done = true;
   }
   const int grid = ((a.MT + 7) / 8) * 8 * a.NT;
-  OSEQ_LAUNCH((conv1x1_kernel<T, BN, DGRAD, FOLD>), dim3(grid), dim3(256), sm + (FOLD ? (size_t)a.Kd * 8 : 0), st,
+  OSEQ_LAUNCH((conv1x1_kernel<T, BN, DGRAD, FOLD, EVAL>), dim3(grid), dim3(256), sm + (FOLD ? (size_t)a.Kd * 8 : 0), st,
               (const T*)X, (const T*)W, bias, (const T*)addend, (T*)out, stat_partial, a);
 }
 
@@ -911,6 +948,9 @@ void launch_pw_t(hipStream_t st, bool dgrad, int bn, const void* X, const void* 
   if (dgrad) {
     if (bn == 128) launch_pw_v<T, 128, true, false>(st, X, W, bias, addend, out, stat_partial, a);
     else launch_pw_v<T, 64, true, false>(st, X, W, bias, addend, out, stat_partial, a);
+  } else if (a.eval) {
+    if (bn == 128) launch_pw_v<T, 128, false, false, true>(st, X, W, bias, addend, out, stat_partial, a);
+    else launch_pw_v<T, 64, false, false, true>(st, X, W, bias, addend, out, stat_partial, a);
   } else if (a.fold) {
     if (bn == 128) launch_pw_v<T, 128, false, true>(st, X, W, bias, addend, out, stat_partial, a);
     else launch_pw_v<T, 64, false, true>(st, X, W, bias, addend, out, stat_partial, a);
@@ -930,6 +970,7 @@ void launch_pw_large_t(hipStream_t st, bool dgrad, const void* X, const void* W,
                        void* out, float* stat_partial, const PwArgs& a) {
   if (dgrad && addend) launch_pw_large<T, true, PWL_BM, PWL_BN / 2, 2, 2, false>(st, X, W, bias, addend, out, stat_partial, a);
   else if (dgrad) launch_pw_large<T, true, PWL_BM, PWL_BN, 2, 4, false>(st, X, W, bias, addend, out, stat_partial, a);
+  else if (a.eval) launch_pw_large<T, false, PWL_BM, PWL_BN, 2, 4, false, true>(st, X, W, bias, addend, out, stat_partial, a);
   else if (a.fold) launch_pw_large<T, false, PWL_BM, PWL_BN, 2, 4, true>(st, X, W, bias, addend, out, stat_partial, a);
   else launch_pw_large<T, false, PWL_BM, PWL_BN, 2, 4, false>(st, X, W, bias, addend, out, stat_partial, a);
 }
@@ -938,13 +979,13 @@ void launch_pw(hipStream_t st, int dt, bool dgrad, const void* X, const void* W,
                void* out, float* stat_partial, PwArgs a) {
   if (!dgrad && pw_ws_ok(a.M, a.Ng, a.Kd, a.stride)) {
     if (dt == DT_BF16) {
-      if (a.Kd == 256) launch_pw_ws_t<bf16_t, 256>(st, X, W, bias, out, stat_partial, a);
-      else if (a.Kd == 128) launch_pw_ws_t<bf16_t, 128>(st, X, W, bias, out, stat_partial, a);
-      else launch_pw_ws_t<bf16_t, 64>(st, X, W, bias, out, stat_partial, a);
+      if (a.Kd == 256) launch_pw_ws_t<bf16_t, 256>(st, X, W, bias, addend, out, stat_partial, a);
+      else if (a.Kd == 128) launch_pw_ws_t<bf16_t, 128>(st, X, W, bias, addend, out, stat_partial, a);
+      else launch_pw_ws_t<bf16_t, 64>(st, X, W, bias, addend, out, stat_partial, a);
     } else {
-      if (a.Kd == 256) launch_pw_ws_t<f16_t, 256>(st, X, W, bias, out, stat_partial, a);
-      else if (a.Kd == 128) launch_pw_ws_t<f16_t, 128>(st, X, W, bias, out, stat_partial, a);
-      else launch_pw_ws_t<f16_t, 64>(st, X, W, bias, out, stat_partial, a);
+      if (a.Kd == 256) launch_pw_ws_t<f16_t, 256>(st, X, W, bias, addend, out, stat_partial, a);
+      else if (a.Kd == 128) launch_pw_ws_t<f16_t, 128>(st, X, W, bias, addend, out, stat_partial, a);
+      else launch_pw_ws_t<f16_t, 64>(st, X, W, bias, addend, out, stat_partial, a);
     }
     return;
   }
@@ -1008,13 +1049,14 @@ bool conv_pointwise_fold_ok(int dt, const ConvGeom& g) { return conv_pointwise_f
 
 // fold: null, or the [4][C_in] statistics tensor of the BatchNorm whose z the tensor x is (see PwArgs::fold)
 void launch_conv_fwd_pointwise(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                               float* stat_partial, const ConvGeom& g, int relu, const float* fold) {
+                               float* stat_partial, const ConvGeom& g, int relu, const float* fold, const ConvEval& ev) {
   PwArgs a{};
   a.fold = fold;
+  a.eval = ev.affine != nullptr;
   a.M = (int64_t)g.N * g.P * g.Q; a.Ng = g.K; a.Kd = g.C; a.relu = relu; a.stride = g.stride;
   a.dstH = g.P; a.dstW = g.Q; a.srcH = g.H; a.srcW = g.W;
   a.div_w = make_fastdiv((uint32_t)g.Q); a.div_hw = make_fastdiv((uint32_t)(g.P * g.Q));
-  launch_pw(st, dt, false, x, w, bias, nullptr, out, stat_partial, a);
+  launch_pw(st, dt, false, x, w, a.eval ? ev.affine : bias, ev.skip, out, stat_partial, a);
 }
 
 // wt: the (C_in, C_out) transpose of the weights in the compute type

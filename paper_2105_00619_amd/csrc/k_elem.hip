@@ -328,6 +328,25 @@ __global__ void __launch_bounds__(256) bn_eval_stats_kernel(const float* __restr
   stats[3 * C + c] = (float)((double)beta[c] - mean * (double)gamma[c] * rstd);
 }
 
+// inference mode, all BatchNorms of the network in one launch (a launch per BatchNorm was 6 % of a 50-layer network's
+// inference at batch 512, an eighth at batch 16): scale and shift, the bias of the convolution in front folded in
+__global__ void __launch_bounds__(256) bn_eval_affine_kernel(const float* __restrict__ w, const float* __restrict__ running,
+                                                             float eps, float* __restrict__ affine, EvalBatch jobs) {
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first_block) ++j;
+  const EvalJob& e = jobs.job[j];
+  const int c = ((int)blockIdx.x - e.first_block) * 256 + (int)threadIdx.x;
+  if (c >= e.C) return;
+  const float* run = running + e.rs_off;
+  const double gamma = (double)w[e.gamma_off + c], beta = (double)w[e.beta_off + c];
+  const double mean = (double)run[c], rstd = 1.0 / sqrt((double)run[e.C + c] + (double)eps);
+  const float scale = (float)(gamma * rstd);
+  double shift = beta - mean * gamma * rstd;
+  if (e.bias_off >= 0) shift += gamma * rstd * (double)w[e.bias_off + c];
+  affine[e.rs_off + c] = scale;
+  affine[e.rs_off + e.C + c] = (float)shift;
+}
+
 template <int V>
 __global__ void __launch_bounds__(256) bn_bwd_finalize_kernel(const float* __restrict__ partial, int nblk, int C, double m,
                                                               float* __restrict__ dgamma, float* __restrict__ dbeta,
@@ -787,6 +806,21 @@ static void row_tiling(int64_t rows, int C, int V, RowArgs& g, dim3& grid) {
 void launch_bn_eval_stats(hipStream_t st, const float* running, const float* gamma, const float* beta, float eps, int C,
                           float* stats) {
   OSEQ_LAUNCH(bn_eval_stats_kernel, dim3(ceil_div(C, 256)), dim3(256), 0, st, running, gamma, beta, eps, C, stats);
+}
+
+void launch_bn_eval_affine(hipStream_t st, const float* w, const float* running, float eps, float* affine, const EvalJob* jobs,
+                           int njobs) {
+  for (int j0 = 0; j0 < njobs; j0 += EvalBatch::MAX_JOBS) {
+    EvalBatch b{};
+    b.n = njobs - j0 < EvalBatch::MAX_JOBS ? njobs - j0 : EvalBatch::MAX_JOBS;
+    int blocks = 0;
+    for (int j = 0; j < b.n; ++j) {
+      b.job[j] = jobs[j0 + j];
+      b.job[j].first_block = blocks;
+      blocks += ceil_div(b.job[j].C, 256);
+    }
+    OSEQ_LAUNCH(bn_eval_affine_kernel, dim3(blocks), dim3(256), 0, st, w, running, eps, affine, b);
+  }
 }
 
 void launch_bn_apply(hipStream_t st, int dt, const void* z, const float* stats, const void* skip, void* out, void* mask,

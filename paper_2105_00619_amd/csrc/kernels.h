@@ -10,6 +10,18 @@ enum { DT_F32 = 0, DT_BF16 = 1, DT_F16 = 2 };
 
 struct ConvGeom { int N, H, W, C, K, R, S, stride, pad, P, Q; };
 
+// The inference-mode BatchNorm behind a convolution, done in the convolution's epilogue: out = [ReLU](scale * sum + shift
+// [+ skip]), one rounding.  affine: [2][C_out] scale and shift, null for a convolution on its own; skip: null or the
+// activation of the skip connection, shaped as the output.
+struct ConvEval { const float* affine = nullptr; const void* skip = nullptr; };
+
+// scale and shift of every BatchNorm of the network from the running statistics, all in one launch per 96 of them
+struct EvalJob { int64_t gamma_off, beta_off, bias_off, rs_off; int C, first_block; };  // bias_off: the convolution's, or -1
+struct EvalBatch { static constexpr int MAX_JOBS = 96; EvalJob job[MAX_JOBS]; int n; };
+// w: master weights; running: [..](mean[C], var[C]) at rs_off; affine: [..](scale[C], shift[C]) at rs_off
+void launch_bn_eval_affine(hipStream_t st, const float* w, const float* running, float eps, float* affine, const EvalJob* jobs,
+                           int njobs);
+
 void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n);
 // storage type -> fp32 (read-back of an activation for inspection)
 void launch_cast_out(hipStream_t st, int dt, const void* x, float* out, int64_t n);
@@ -59,7 +71,7 @@ void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlo
                      int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx);
 
 void launch_conv_fwd_direct(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu);
+                            const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());
 void launch_conv_dgrad_direct(hipStream_t st, int dt, const void* dz, const void* w, const void* addend, void* dx,
                               const ConvGeom& g);
 void launch_conv_wgrad_direct(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
@@ -70,7 +82,7 @@ bool conv_smallc_fwd_ok(const ConvGeom& g);
 bool conv_smallc_wgrad_ok(const ConvGeom& g);
 int conv_smallc_wgrad_splits(const ConvGeom& g);
 void launch_conv_fwd_smallc(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu);
+                            const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());
 void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                               const ConvGeom& g);
 
@@ -89,7 +101,7 @@ bool conv_fold_fwd_ok(int dt, const ConvGeom& g);
 bool conv_fold_wgrad_ok(int dt, const ConvGeom& g);
 void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
                           float* partial, float* stat_partial, int splits, const ConvGeom& g, int relu,
-                          const float* fold = nullptr);
+                          const float* fold = nullptr, const ConvEval& ev = ConvEval());
 // addend_mask (null, or with an addend): ReLU decisions as bits (as launch_bn_apply writes them); the addend counts
 // as zero where its bit is clear
 void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
@@ -100,7 +112,7 @@ bool conv_pointwise_dgrad_ok(int dt, const ConvGeom& g);
 int conv_pointwise_stat_blocks(const ConvGeom& g);
 bool conv_pointwise_fold_ok(int dt, const ConvGeom& g);
 void launch_conv_fwd_pointwise(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                               float* stat_partial, const ConvGeom& g, int relu, const float* fold);
+                               float* stat_partial, const ConvGeom& g, int relu, const float* fold, const ConvEval& ev);
 void launch_conv_dgrad_pointwise(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
                                  const uint8_t* addend_mask, void* dx, const ConvGeom& g);
 // 3x3 stride-1 weight gradient with all nine taps per block (k_conv_wgrad3x3.hip); used by the MFMA launcher below

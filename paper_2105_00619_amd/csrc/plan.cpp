@@ -568,6 +568,58 @@ bool build_schedule(Plan& p) {
   return true;
 }
 
+void build_inference(Plan& p) {
+  p.infer.clear();
+  const int n = (int)p.fops.size();
+  std::vector<int> last(p.tensors.size(), -1);  // last operation that reads a tensor
+  for (int i = 0; i < n; ++i) {
+    const FOp& f = p.fops[i];
+    if (f.kind == F_BN_STATS) continue;
+    if (f.x >= 0) last[f.x] = i;
+    if (f.skip >= 0) last[f.skip] = i;
+  }
+  std::vector<int64_t> at(p.tensors.size(), -1);
+  FreeList fl;
+  auto done = [&](int t, int i) {  // operation i has read tensor t
+    if (t >= 0 && last[t] == i && at[t] >= 0) { fl.release((uint64_t)at[t], p.tensors[t].bytes); at[t] = -1; }
+  };
+  for (int i = 0; i < n; ++i) {
+    const FOp& f = p.fops[i];
+    IOp o;
+    o.fop = i;
+    if (f.x >= 0) o.in = at[f.x];
+    uint64_t ws = 0;
+    switch (f.kind) {
+      case F_CAST_IN: o.kind = S_CAST_IN; o.out = at[f.out] = (int64_t)fl.alloc(p.tensors[f.out].bytes); break;
+      case F_CONV: {
+        o.kind = S_CONV_FWD;
+        int out = f.out;
+        if (f.has_bn) {  // followed by its statistics and apply operations
+          o.apply = i + 2;
+          const FOp& ap = p.fops[o.apply];
+          out = ap.out;
+          if (ap.skip >= 0) o.skip = at[ap.skip];
+        }
+        o.out = at[out] = (int64_t)fl.alloc(p.tensors[out].bytes);
+        if (f.fwd_splits > 1) ws = (uint64_t)f.fwd_splits * f.N * f.P * f.Q * f.K * 4;
+        break;
+      }
+      case F_BN_STATS: continue;
+      case F_BN_APPLY: done(f.skip, i); continue;  // (its x is the convolution's output, which does not exist)
+      case F_POOL: o.kind = S_POOL_FWD; o.out = at[f.out] = (int64_t)fl.alloc(p.tensors[f.out].bytes); break;
+      case F_HEAD:
+        o.kind = S_HEAD_FWD;
+        o.out = (int64_t)fl.alloc(p.tensors[f.aux[0]].bytes);
+        ws = (uint64_t)f.head_ws * 4;
+        break;
+    }
+    if (ws) { o.ws = (int64_t)fl.alloc(ws); fl.release((uint64_t)o.ws, ws); }
+    done(f.x, i);
+    p.infer.push_back(o);
+  }
+  p.infer_bytes = fl.high_;
+}
+
 // Per-unit byte model of what a segment holds for its backward pass, read off a k = 1 schedule.  A tensor kept for
 // backward counts for the unit that made it, except a unit's output: that is kept as the input of the next unit (whose
 // backward reads it), so inside a segment it counts for every unit but the last, and for the last one only where the

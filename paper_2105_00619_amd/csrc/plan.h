@@ -91,6 +91,14 @@ struct SOp {
   bool live = true;
 };
 
+// One entry of the inference schedule: a forward operation with the BatchNorm behind a convolution done in that
+// convolution's epilogue.  Offsets into the activation arena, -1: none.
+struct IOp {
+  SKind kind = S_CONV_FWD;
+  int fop = -1, apply = -1;  // apply: the F_BN_APPLY operation of the BatchNorm behind the convolution, or -1
+  int64_t in = -1, skip = -1, out = -1, ws = -1;  // head: out = features, skip unused
+};
+
 struct Plan {
   // inputs
   std::vector<optorch_unit_t> units;
@@ -112,6 +120,9 @@ struct Plan {
   uint64_t peak_saved_bytes = 0;  // exact tensor sizes, no alignment
   uint64_t peak_live_bytes = 0;   // all live tensors incl. transients, exact sizes
   int n_launches = 0, n_replay_launches = 0;
+  // inference: its own schedule and offsets in the same arena
+  std::vector<IOp> infer;
+  uint64_t infer_bytes = 0;
   std::string error;
 };
 
@@ -121,6 +132,8 @@ bool build_graph(Plan& p);
 bool choose_segments(Plan& p);
 // Builds schedule, lifetimes, offsets and peak figures for plan.seg_begin.
 bool build_schedule(Plan& p);
+// Builds the inference schedule; needs the kernel choices of the convolutions (workspaces of split depths).
+void build_inference(Plan& p);
 // Peak saved bytes of the partition given by seg_begin, from the closed form
 //   max_j ( sum_{i<=j} checkpoint_i + saved_j ),
 // with per-unit saved bytes taken from the all-stored schedule.  Used by the min-peak planner.

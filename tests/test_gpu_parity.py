@@ -736,6 +736,35 @@ def test_running_statistics_and_inference_match_oracle(name, precision):
         running = o["running"].astype(np.float64)  # errors are not carried from step to step
 
 
+INFER_NETS = {  # input channels, H = W, batch, units: one network per kernel whose epilogue applies the BatchNorm
+    "stem_basic_17": (3, 17, 24, [W.conv(3, 64), W.basic_block(64, 64), W.basic_block(64, 128, 2), W.gap_linear_ce(128, 10)]),
+    "split_depth_4": (512, 4, 9, [W.basic_block(512, 512), W.conv(512, 512, relu=False, bias=True), W.gap_linear_ce(512, 10)]),
+    "patch_pool_16": (64, 16, 70, [W.conv(64, 128), W.maxpool(), W.basic_block(128, 128), W.flatten_linear_ce(128, 10)]),
+    "bottlenecks_9": (64, 9, 5, [W.bottleneck(64, 256, 1), W.bottleneck(256, 512, 2), W.gap_linear_ce(512, 10)]),
+    "stationary_64": (64, 33, 121, [W.conv(64, 256, ksize=1), W.bottleneck(256, 256), W.gap_linear_ce(256, 10)]),
+    "stationary_128": (64, 33, 61, [W.conv(64, 512, ksize=1), W.bottleneck(512, 512), W.gap_linear_ce(512, 10)]),
+    "stationary_256": (64, 17, 115, [W.conv(64, 1024, ksize=1), W.bottleneck(1024, 1024), W.gap_linear_ce(1024, 10)]),
+    "large_tile_256": (64, 33, 121, [W.conv(64, 256, ksize=1), W.conv(256, 256, ksize=1), W.gap_linear_ce(256, 10)]),
+}
+
+
+@pytest.mark.parametrize("name", sorted(INFER_NETS))
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
+def test_inference_epilogues_match_oracle(name, precision):
+    """Inference logits of networks that take every forward kernel with the BatchNorm, skip connection and ReLU in its
+    epilogue (ragged last tiles among them), at the library's own weights and running statistics after one step."""
+    from oracle import seqnet_oracle as O
+    from tests.gpu_util import STORAGE
+    cin, hw, b, units = INFER_NETS[name]
+    if precision == W.FP32 and hw > 17 or precision == W.FP32 and name == "stationary_256":
+        pytest.skip("the kernel this case is for exists in the 16-bit modes only")
+    p, x, y = _inputs(units, b, hw, hw, 10, seed=23, channels=cin)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=2, classes=10, lr=0.01, predict_x=x[::-1].copy(),
+                    loss_scale_init=_scale(precision), bn_momentum=1.0)
+    ref = O.predict(units, r["params"].astype(np.float64), r["running"].astype(np.float64), x[::-1], storage=STORAGE[precision])
+    assert np.linalg.norm(r["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
+
+
 def test_inference_at_benchmark_size_matches_oracle():
     """Inference on the benchmark network at its full batch after one training step (fp32 mode)."""
     from oracle import seqnet_oracle as O
