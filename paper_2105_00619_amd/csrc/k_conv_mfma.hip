@@ -679,11 +679,13 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
 #undef B_LOAD
 #undef B_STORE
 
-// Sum of the depth ranges in order, then bias / residual addend / ReLU, one rounding, store.  A block covers 64 rows
+// Sum of the depth ranges in order, then bias / residual addend / ReLU, one rounding, store.  A block covers ROWS rows
 // x 64 channels (thread = 4 channels of every 16th row), so that it can also produce the per-channel sums of the
-// stored values for the BatchNorm that follows: stat_partial [ceil(M / 64)][2][Ng], or null.
-constexpr int SPLIT_EPI_ROWS = 64;
-template <class T>
+// stored values for the BatchNorm that follows: stat_partial [ceil(M / ROWS)][2][Ng], or null.  Bound by latency at the
+// few pixels this is for: the loads of eight ranges are issued before the first is added, and with 64 rows per block a
+// layer of 256 pixels and 512 channels left 224 CUs idle (12 us for its 32 ranges); 16 rows where 64 give under 512 blocks.
+static int split_epi_rows(int64_t M, int Ng) { return (int64_t)((M + 63) / 64) * (Ng / 64) >= 512 ? 64 : 16; }
+template <class T, int ROWS>
 __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __restrict__ partial, int splits, int64_t M, int Ng,
                                                               const float* __restrict__ bias, const T* __restrict__ addend,
                                                               const uint8_t* __restrict__ amask, T* __restrict__ out,
@@ -705,12 +707,19 @@ __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const float* __res
   }
   float ss[4] = {0.f, 0.f, 0.f, 0.f}, qq[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int it = 0; it < SPLIT_EPI_ROWS / 16; ++it) {
-    const int64_t row = (int64_t)blockIdx.x * SPLIT_EPI_ROWS + it * 16 + ty;
+  for (int it = 0; it < ROWS / 16; ++it) {
+    const int64_t row = (int64_t)blockIdx.x * ROWS + it * 16 + ty;
     if (row < M) {
       const int64_t i = row * Ng + col;
-      v4f acc = *reinterpret_cast<const v4f*>(partial + i);
-      for (int z = 1; z < splits; ++z) acc += *reinterpret_cast<const v4f*>(partial + (int64_t)z * n + i);
+      v4f acc = {0.f, 0.f, 0.f, 0.f};
+      for (int z0 = 0; z0 < splits; z0 += 8) {  // (ranges past the last one read the last one and are not added)
+        v4f t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const v4f*>(partial + (int64_t)(z0 + u < splits ? z0 + u : splits - 1) * n + i);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (z0 + u < splits) acc += t[u];
+      }
       float r[4];
       // the addend's ReLU bits, if it has any: four consecutive elements lie in one byte (i is a multiple of 4)
       unsigned mb = 0xfu;
@@ -749,9 +758,14 @@ template <class T>
 static void launch_splitk_epilogue(hipStream_t st, const float* partial, int splits, int64_t M, int Ng, const float* bias,
                                    const void* addend, const uint8_t* amask, void* out, float* stat_partial, int relu,
                                    const float* affine = nullptr) {
-  dim3 grid(ceil_div(M, SPLIT_EPI_ROWS), Ng / 64);  // Ng % 64 == 0 for every MFMA convolution
-  OSEQ_LAUNCH(splitk_epilogue_kernel<T>, grid, dim3(256), 0, st, partial, splits, M, Ng, bias, (const T*)addend, amask,
-                     (T*)out, stat_partial, relu, affine);
+  const int rows = split_epi_rows(M, Ng);
+  dim3 grid(ceil_div(M, rows), Ng / 64);  // Ng % 64 == 0 for every MFMA convolution
+  if (rows == 64)
+    OSEQ_LAUNCH((splitk_epilogue_kernel<T, 64>), grid, dim3(256), 0, st, partial, splits, M, Ng, bias, (const T*)addend, amask,
+                (T*)out, stat_partial, relu, affine);
+  else
+    OSEQ_LAUNCH((splitk_epilogue_kernel<T, 16>), grid, dim3(256), 0, st, partial, splits, M, Ng, bias, (const T*)addend, amask,
+                (T*)out, stat_partial, relu, affine);
 }
 
 // LDS of the patch kernel: two patch buffers of patch_elems elements, three weight stages, the address tables
@@ -1040,8 +1054,8 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g) {
   const int64_t M = (int64_t)g.N * g.P * g.Q;
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_stat_blocks(g);
   if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
-    return pv.splits > 1 ? ceil_div(M, SPLIT_EPI_ROWS) : (pa.NT + pv.subt - 1) / pv.subt;
-  if (igemm_splits(dt, M, g.K, g.R * g.S * g.C) > 1) return ceil_div(M, SPLIT_EPI_ROWS);
+    return pv.splits > 1 ? ceil_div(M, split_epi_rows(M, g.K)) : (pa.NT + pv.subt - 1) / pv.subt;
+  if (igemm_splits(dt, M, g.K, g.R * g.S * g.C) > 1) return ceil_div(M, split_epi_rows(M, g.K));
   return ceil_div(M, IGEMM_BM);
 }
 
