@@ -7,16 +7,19 @@
 
 namespace oseq {
 
-template <class T>
+// I: the index type, int where every tensor has fewer than 2^30 elements (64-bit divisions and address arithmetic are
+// most of these kernels' instructions).  V: channels per load, 4 where the channel counts allow it.
+template <class T, class I, int V>
 __global__ void __launch_bounds__(256) conv_fwd_direct_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                               const float* __restrict__ bias, T* __restrict__ out,
                                                               ConvGeom g, int relu, const float* __restrict__ affine,
                                                               const T* __restrict__ skip) {
-  const int64_t total = (int64_t)g.N * g.P * g.Q * g.K;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
+  const I total = (I)g.N * g.P * g.Q * g.K;
+  const int64_t i64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i64 >= (int64_t)total) return;
+  const I i = (I)i64;
   const int k = (int)(i % g.K);
-  int64_t t = i / g.K;
+  I t = i / g.K;
   const int q = (int)(t % g.Q); t /= g.Q;
   const int p = (int)(t % g.P);
   const int n = (int)(t / g.P);
@@ -24,12 +27,19 @@ __global__ void __launch_bounds__(256) conv_fwd_direct_kernel(const T* __restric
   for (int r = 0; r < g.R; ++r) {
     const int ih = p * g.stride + r - g.pad;
     if (ih < 0 || ih >= g.H) continue;
+#pragma unroll 3
     for (int s = 0; s < g.S; ++s) {
       const int iw = q * g.stride + s - g.pad;
-      if (iw < 0 || iw >= g.W) continue;
-      const T* xp = x + (((int64_t)n * g.H + ih) * g.W + iw) * g.C;
-      const T* wp = w + (((int64_t)k * g.R + r) * g.S + s) * g.C;
-      for (int c = 0; c < g.C; ++c) acc = __fmaf_rn(to_f32(xp[c]), to_f32(wp[c]), acc);
+      const bool in = iw >= 0 && iw < g.W;  // (a tap outside reads the row's first pixel and adds nothing)
+      const T* xp = x + (((I)n * g.H + ih) * g.W + (in ? iw : 0)) * g.C;
+      const T* wp = w + (((I)k * g.R + r) * g.S + s) * g.C;
+      for (int c = 0; c < g.C; c += V) {
+        float xv[V], wv[V];
+        load_f32<T, V>(xp + c, xv);
+        load_f32<T, V>(wp + c, wv);
+#pragma unroll
+        for (int u = 0; u < V; ++u) acc = in ? __fmaf_rn(xv[u], wv[u], acc) : acc;
+      }
     }
   }
   if (affine) {  // the inference-mode BatchNorm behind the layer (affine: [2][K] scale and shift)
@@ -43,33 +53,42 @@ __global__ void __launch_bounds__(256) conv_fwd_direct_kernel(const T* __restric
 }
 
 // dx[n,h,w,c] = sum_{r,s,k} dz[n,p,q,k] * w[k,r,s,c] over the (p,q) with p*stride + r - pad == h, q*stride + s - pad == w
-template <class T>
+template <class T, class I, int V>
 __global__ void __launch_bounds__(256) conv_dgrad_direct_kernel(const T* __restrict__ dz, const T* __restrict__ w,
                                                                 const T* __restrict__ addend, T* __restrict__ dx,
                                                                 ConvGeom g) {
-  const int64_t total = (int64_t)g.N * g.H * g.W * g.C;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
+  const I total = (I)g.N * g.H * g.W * g.C;
+  const int64_t i64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i64 >= (int64_t)total) return;
+  const I i = (I)i64;
   const int c = (int)(i % g.C);
-  int64_t t = i / g.C;
+  I t = i / g.C;
   const int wq = (int)(t % g.W); t /= g.W;
   const int h = (int)(t % g.H);
   const int n = (int)(t / g.H);
+  const I wk = (I)g.R * g.S * g.C;
   float acc = 0.f;
   for (int r = 0; r < g.R; ++r) {
     const int ph = h + g.pad - r;
     if (ph < 0 || ph % g.stride) continue;
     const int p = ph / g.stride;
     if (p >= g.P) continue;
+#pragma unroll 3
     for (int s = 0; s < g.S; ++s) {
       const int qw = wq + g.pad - s;
-      if (qw < 0 || qw % g.stride) continue;
-      const int q = qw / g.stride;
-      if (q >= g.Q) continue;
-      const T* zp = dz + (((int64_t)n * g.P + p) * g.Q + q) * g.K;
-      const T* wp = w + ((int64_t)r * g.S + s) * g.C + c;
-      const int64_t wk = (int64_t)g.R * g.S * g.C;
-      for (int k = 0; k < g.K; ++k) acc = __fmaf_rn(to_f32(zp[k]), to_f32(wp[k * wk]), acc);
+      const int q = qw >= 0 ? qw / g.stride : 0;
+      const bool in = qw >= 0 && qw % g.stride == 0 && q < g.Q;
+      const T* zp = dz + (((I)n * g.P + p) * g.Q + (in ? q : 0)) * g.K;
+      const T* wp = w + ((I)r * g.S + s) * g.C + c;
+      for (int k = 0; k < g.K; k += V) {
+        float zv[V];
+        load_f32<T, V>(zp + k, zv);
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          const float wv = to_f32(wp[(I)(k + u) * wk]);
+          acc = in ? __fmaf_rn(zv[u], wv, acc) : acc;
+        }
+      }
     }
   }
   if (addend) acc += to_f32(addend[i]);
@@ -77,40 +96,44 @@ __global__ void __launch_bounds__(256) conv_dgrad_direct_kernel(const T* __restr
 }
 
 // dw[k,r,s,c] = sum over pixels (n,p,q) of dz[n,p,q,k] * x[n, p*stride+r-pad, q*stride+s-pad, c];
-// blockIdx.y selects a fixed chunk of the pixel range; chunks are summed afterwards in order.
-template <class T>
+// blockIdx.y selects a fixed chunk of the pixel range; chunks are summed afterwards in order.  The pixel's coordinates are
+// counted up, four pixels are loaded before the first is added (a pixel outside the image reads the tensor's first
+// element and adds zero).
+template <class T, class I>
 __global__ void __launch_bounds__(256) conv_wgrad_direct_kernel(const T* __restrict__ x, const T* __restrict__ dz,
                                                                 float* __restrict__ out, ConvGeom g, int64_t chunk) {
-  const int64_t outputs = (int64_t)g.K * g.R * g.S * g.C;
-  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= outputs) return;
+  const I outputs = (I)g.K * g.R * g.S * g.C;
+  const int64_t o64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (o64 >= (int64_t)outputs) return;
+  const I o = (I)o64;
   const int c = (int)(o % g.C);
-  int64_t t = o / g.C;
+  I t = o / g.C;
   const int s = (int)(t % g.S); t /= g.S;
   const int r = (int)(t % g.R);
   const int k = (int)(t / g.R);
-  const int64_t pixels = (int64_t)g.N * g.P * g.Q;
-  const int64_t m0 = (int64_t)blockIdx.y * chunk;
-  const int64_t m1 = m0 + chunk < pixels ? m0 + chunk : pixels;
+  const I pixels = (I)g.N * g.P * g.Q;
+  const int64_t first = (int64_t)blockIdx.y * chunk;
+  const I m0 = first < (int64_t)pixels ? (I)first : pixels;
+  const I m1 = first + chunk < (int64_t)pixels ? (I)(first + chunk) : pixels;
+  int q = (int)(m0 % g.Q);
+  const I mq = m0 / g.Q;
+  int p = (int)(mq % g.P), n = (int)(mq / g.P);
   float acc = 0.f;
-  for (int64_t m = m0; m < m1; ++m) {
-    const int q = (int)(m % g.Q);
-    const int64_t u = m / g.Q;
-    const int p = (int)(u % g.P);
-    const int n = (int)(u / g.P);
-    const int ih = p * g.stride + r - g.pad, iw = q * g.stride + s - g.pad;
-    if (ih < 0 || ih >= g.H || iw < 0 || iw >= g.W) continue;
-    acc = __fmaf_rn(to_f32(dz[m * g.K + k]), to_f32(x[(((int64_t)n * g.H + ih) * g.W + iw) * g.C + c]), acc);
+  for (I m = m0; m < m1; m += 4) {
+    float zv[4], xv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int ih = p * g.stride + r - g.pad, iw = q * g.stride + s - g.pad;
+      const bool in = m + u < m1 && ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+      const float a = to_f32(dz[in ? (m + u) * g.K + k : 0]), b = to_f32(x[in ? (((I)n * g.H + ih) * g.W + iw) * g.C + c : 0]);
+      zv[u] = in ? a : 0.f;
+      xv[u] = in ? b : 0.f;
+      if (++q == g.Q) { q = 0; if (++p == g.P) { p = 0; ++n; } }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc = __fmaf_rn(zv[u], xv[u], acc);
   }
   out[(int64_t)blockIdx.y * outputs + o] = acc;
-}
-
-__global__ void splitk_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out, int64_t n, int splits) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float acc = 0.f;
-  for (int s = 0; s < splits; ++s) acc += partial[(int64_t)s * n + i];
-  out[i] = acc;
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -350,15 +373,18 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
   const int m1 = m0 + chunk < pixels ? m0 + chunk : pixels;
   const int nt = m1 > m0 ? (m1 - m0 + 63) / 64 : 0;
 
-  // tile-independent part of this thread's im2col elements: pixel row, filter offset, channel
-  int xpx[NX], xdy[NX], xdx[NX], xc[NX], xdst[NX];
+  // This thread's im2col elements: one pixel of the tile (its lane) and the columns e = wave + 4u, so that a tile costs
+  // one index decomposition per thread; whether a column's filter tap lies inside the image is one bit of a nine-bit mask
+  // per pixel.  (With the elements dealt out in memory order every one of them had its own pixel to decompose: 49 us
+  // instead of 20 for 262 144 pixels in bf16.)
+  const int xtap0 = wave;  // e = xtap0 + 4u
+  int xoff[NX], xbit[NX];
 #pragma unroll
-  for (int it = 0; it < NX; ++it) {
-    const int i = tid + it * 256;
-    const bool on = i < 64 * rsc;
-    const int px = on ? i / rsc : 0, e = on ? i - px * rsc : 0;
+  for (int u = 0; u < NX; ++u) {
+    const int e = xtap0 + 4 * u < rsc ? xtap0 + 4 * u : 0;
     const int c = e % C, tap = e / C, s = tap % g.S, r = tap / g.S;
-    xpx[it] = on ? px : -1; xdy[it] = r - g.pad; xdx[it] = s - g.pad; xc[it] = c; xdst[it] = px * XP + e;
+    xoff[u] = ((r - g.pad) * W + (s - g.pad)) * C + c;
+    xbit[u] = xtap0 + 4 * u < rsc ? tap : -1;
   }
   Chunk rd[DCH];
   float rx[NX];
@@ -374,18 +400,24 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
       rd[i] = *reinterpret_cast<const Chunk*>(dz + (int64_t)(ok ? mt + px : m0) * K + (ok ? kv * EV : 0));
       dm |= ok ? (1u << i) : 0u;
     }
-#pragma unroll
-    for (int it = 0; it < NX; ++it) {
-      const int m = mt + xpx[it];
-      bool ok = xpx[it] >= 0 && m < m1;
-      const uint32_t mm = ok ? (uint32_t)m : (uint32_t)m0;
+    {
+      const int m = mt + lane;
+      const bool in = m < m1;
+      const uint32_t mm = in ? (uint32_t)m : (uint32_t)m0;
       const uint32_t n_ = divPQ.div(mm), rem = mm - n_ * divPQ.d;
       const uint32_t p_ = divQ.div(rem), q_ = rem - p_ * divQ.d;
-      const int ih = (int)p_ * cstride + xdy[it], iw = (int)q_ * cstride + xdx[it];
-      ok = ok && ih >= 0 && ih < H && iw >= 0 && iw < W;
-      const int64_t off = ok ? (((int64_t)n_ * H + ih) * W + iw) * C + xc[it] : 0;
-      rx[it] = to_f32(x[off]);
-      xm |= ok ? (1u << it) : 0u;
+      const int ih0 = (int)p_ * cstride - g.pad, iw0 = (int)q_ * cstride - g.pad;
+      const int64_t base = (((int64_t)n_ * H + (int)p_ * cstride) * W + (int)q_ * cstride) * C;
+      unsigned taps = 0u;  // bit r * S + s: the tap lies inside the image
+      for (int r = 0, b = 0; r < g.R; ++r)
+        for (int s = 0; s < g.S; ++s, ++b)
+          taps |= (in && ih0 + r >= 0 && ih0 + r < H && iw0 + s >= 0 && iw0 + s < W) ? (1u << b) : 0u;
+#pragma unroll
+      for (int u = 0; u < NX; ++u) {
+        const bool ok = xbit[u] >= 0 && ((taps >> (xbit[u] & 31)) & 1u);
+        rx[u] = to_f32(x[ok ? base + xoff[u] : 0]);
+        xm |= ok ? (1u << u) : 0u;
+      }
     }
     dmask = dm; xmask = xm;
   };
@@ -411,8 +443,8 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
       }
     }
 #pragma unroll
-    for (int it = 0; it < NX; ++it)
-      if (xpx[it] >= 0) xs[stage][xdst[it]] = ((xmask >> it) & 1u) ? rx[it] : 0.f;
+    for (int u = 0; u < NX; ++u)
+      if (xtap0 + 4 * u < rsc) xs[stage][lane * XP + xtap0 + 4 * u] = ((xmask >> u) & 1u) ? rx[u] : 0.f;
   };
 
   v16f acc[2][2];
@@ -475,16 +507,29 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
   }
 }
 
-// one wavefront per output: lanes sum the block partials l, l+64, ... then a fixed butterfly
-__global__ void __launch_bounds__(256) wave_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out, int64_t n,
-                                                          int splits) {
-  const int64_t o = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= n) return;
+// 16 outputs per block: thread (output, row group) sums the partials of rows group, group + 16, ... (four in flight), the
+// 16 group sums of an output are added in order.  (One thread per output walking 256 rows took 57 us for 576 outputs, one
+// wavefront per output reads a whole memory line for every four bytes.)
+__global__ void __launch_bounds__(256) partial_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out, int64_t n,
+                                                             int splits) {
+  __shared__ float red[16][17];
+  const int ox = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int64_t o = (int64_t)blockIdx.x * 16 + ox;
+  const float* p = partial + (o < n ? o : 0);
   float v = 0.f;
-  for (int s = threadIdx.x & 63; s < splits; s += 64) v += partial[(int64_t)s * n + o];
+  int s = grp;
+  for (; s + 48 < splits; s += 64) {
+    const float t0 = p[(int64_t)s * n], t1 = p[(int64_t)(s + 16) * n], t2 = p[(int64_t)(s + 32) * n], t3 = p[(int64_t)(s + 48) * n];
+    v += t0; v += t1; v += t2; v += t3;
+  }
+  for (; s < splits; s += 16) v += p[(int64_t)s * n];
+  red[grp][ox] = v;
+  __syncthreads();
+  if (grp == 0 && o < n) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) out[o] = v;
+    for (int g = 1; g < 16; ++g) v += red[g][ox];
+    out[o] = v;
+  }
 }
 
 bool conv_smallc_fwd_ok(const ConvGeom& g) {
@@ -497,7 +542,9 @@ bool conv_smallc_wgrad_ok(const ConvGeom& g) {
 }
 int conv_smallc_wgrad_splits(const ConvGeom& g) {
   const int64_t pixels = (int64_t)g.N * g.P * g.Q;
+  // four tiles of 64 pixels per block, fewer where that would leave CUs idle
   int64_t b = (pixels + 255) / 256;
+  if (b < 512) b = (pixels + 63) / 64 < 512 ? (pixels + 63) / 64 : 512;
   return (int)(b < 1 ? 1 : (b > 1024 ? 1024 : b));
 }
 
@@ -554,26 +601,47 @@ void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void*
   else OSEQ_LAUNCH(conv_wgrad_smallc_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)dz, dst, g, chunk, dq, dpq);
   if (splits > 1) {
     const int64_t n = (int64_t)g.K * g.R * g.S * g.C;
-    OSEQ_LAUNCH(wave_reduce_kernel, dim3(ceil_div(n, 4)), dim3(256), 0, st, partial, dw, n, splits);
+    OSEQ_LAUNCH(partial_reduce_kernel, dim3(ceil_div(n, 16)), dim3(256), 0, st, partial, dw, n, splits);
   }
 }
+
+// 32-bit indices: every tensor of the layer has fewer than 2^30 elements (a step past the end still counts)
+static bool direct_small(const ConvGeom& g) {
+  const int64_t most = (int64_t)1 << 30;
+  return (int64_t)g.N * g.P * g.Q * g.K < most && (int64_t)g.N * g.H * g.W * g.C < most && (int64_t)g.K * g.R * g.S * g.C < most;
+}
+// the choice of index type and vector width (V: channels per load; their tensors start on 16-byte boundaries or, the
+// weights, at any element: `aligned` says whether those allow it)
+#define DIRECT_LAUNCH(KERNEL, T, VEC, ...)                                                       \
+  {                                                                                              \
+    if (direct_small(g)) {                                                                       \
+      if (VEC) OSEQ_LAUNCH((KERNEL<T, int, 4>), grid, block, 0, st, __VA_ARGS__);                \
+      else OSEQ_LAUNCH((KERNEL<T, int, 1>), grid, block, 0, st, __VA_ARGS__);                    \
+    } else {                                                                                     \
+      OSEQ_LAUNCH((KERNEL<T, int64_t, 1>), grid, block, 0, st, __VA_ARGS__);                     \
+    }                                                                                            \
+  }
 
 void launch_conv_fwd_direct(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
                             const ConvGeom& g, int relu, const ConvEval& ev) {
   const int64_t total = (int64_t)g.N * g.P * g.Q * g.K;
   dim3 grid(ceil_div(total, 256)), block(256);
-  if (dt == DT_F32) OSEQ_LAUNCH(conv_fwd_direct_kernel<float>, grid, block, 0, st, (const float*)x, (const float*)w, bias, (float*)out, g, relu, ev.affine, (const float*)ev.skip);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_fwd_direct_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)out, g, relu, ev.affine, (const bf16_t*)ev.skip);
-  else OSEQ_LAUNCH(conv_fwd_direct_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)w, bias, (f16_t*)out, g, relu, ev.affine, (const f16_t*)ev.skip);
+  const uintptr_t mask = dt == DT_F32 ? 15 : 7;  // four elements
+  const bool vec = g.C % 4 == 0 && (((uintptr_t)x | (uintptr_t)w) & mask) == 0;
+#define CALL(T)                                                                                                              \
+  DIRECT_LAUNCH(conv_fwd_direct_kernel, T, vec, (const T*)x, (const T*)w, bias, (T*)out, g, relu, ev.affine, (const T*)ev.skip)
+  if (dt == DT_F32) CALL(float) else if (dt == DT_BF16) CALL(bf16_t) else CALL(f16_t)
+#undef CALL
 }
 
 void launch_conv_dgrad_direct(hipStream_t st, int dt, const void* dz, const void* w, const void* addend, void* dx,
                               const ConvGeom& g) {
   const int64_t total = (int64_t)g.N * g.H * g.W * g.C;
   dim3 grid(ceil_div(total, 256)), block(256);
-  if (dt == DT_F32) OSEQ_LAUNCH(conv_dgrad_direct_kernel<float>, grid, block, 0, st, (const float*)dz, (const float*)w, (const float*)addend, (float*)dx, g);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_dgrad_direct_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)dz, (const bf16_t*)w, (const bf16_t*)addend, (bf16_t*)dx, g);
-  else OSEQ_LAUNCH(conv_dgrad_direct_kernel<f16_t>, grid, block, 0, st, (const f16_t*)dz, (const f16_t*)w, (const f16_t*)addend, (f16_t*)dx, g);
+  const bool vec = g.K % 4 == 0 && ((uintptr_t)dz & (dt == DT_F32 ? 15 : 7)) == 0;
+#define CALL(T) DIRECT_LAUNCH(conv_dgrad_direct_kernel, T, vec, (const T*)dz, (const T*)w, (const T*)addend, (T*)dx, g)
+  if (dt == DT_F32) CALL(float) else if (dt == DT_BF16) CALL(bf16_t) else CALL(f16_t)
+#undef CALL
 }
 
 void launch_conv_wgrad_direct(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
@@ -583,11 +651,15 @@ void launch_conv_wgrad_direct(hipStream_t st, int dt, const void* x, const void*
   const int64_t chunk = (pixels + splits - 1) / splits;
   float* dst = splits > 1 ? partial : dw;
   dim3 grid(ceil_div(outputs, 256), splits), block(256);
-  if (dt == DT_F32) OSEQ_LAUNCH(conv_wgrad_direct_kernel<float>, grid, block, 0, st, (const float*)x, (const float*)dz, dst, g, chunk);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_wgrad_direct_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)dz, dst, g, chunk);
-  else OSEQ_LAUNCH(conv_wgrad_direct_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)dz, dst, g, chunk);
+#define CALL(T)                                                                                                              \
+  {                                                                                                                          \
+    if (direct_small(g)) OSEQ_LAUNCH((conv_wgrad_direct_kernel<T, int>), grid, block, 0, st, (const T*)x, (const T*)dz, dst, g, chunk); \
+    else OSEQ_LAUNCH((conv_wgrad_direct_kernel<T, int64_t>), grid, block, 0, st, (const T*)x, (const T*)dz, dst, g, chunk);  \
+  }
+  if (dt == DT_F32) CALL(float) else if (dt == DT_BF16) CALL(bf16_t) else CALL(f16_t)
+#undef CALL
   if (splits > 1)
-    OSEQ_LAUNCH(splitk_reduce_kernel, dim3(ceil_div(outputs, 256)), dim3(256), 0, st, partial, dw, outputs, splits);
+    OSEQ_LAUNCH(partial_reduce_kernel, dim3(ceil_div(outputs, 16)), dim3(256), 0, st, partial, dw, outputs, splits);
 }
 
 }  // namespace oseq
