@@ -93,8 +93,9 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.fwd_algo == ALGO_MFMA) f.fwd_splits = conv_mfma_fwd_splits(dt, g);
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_splits = conv_mfma_dgrad_splits(dt, g);
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g);
-        if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(g);
+        if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g);
+        if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
       }
     for (FOp& f : p.fops)
       if (f.kind == F_HEAD) f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes);
@@ -318,7 +319,7 @@ void run_op(const Ctx& c, const SOp& s) {
                              (const float*)c.at(s.in[1]));
       else if (f.fwd_algo == ALGO_SMALLC)
         launch_conv_fwd_smallc(st, dt, c.at(s.in[0]), c.wc(f.w_off), f.has_bias ? c.w32(f.b_off) : nullptr, c.at(s.out[0]),
-                               geom(f), f.relu);
+                               (float*)c.at(s.out[2]), geom(f), f.relu);
       else
         launch_conv_fwd_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), f.has_bias ? c.w32(f.b_off) : nullptr, c.at(s.out[0]),
                                geom(f), f.relu);
@@ -573,7 +574,7 @@ static void infer_fused(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
           launch_conv_fwd_mfma(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), (float*)at(o.ws), nullptr, f.fwd_splits, geom(f),
                                relu, nullptr, ev);
         else if (f.fwd_algo == ALGO_SMALLC)
-          launch_conv_fwd_smallc(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), geom(f), relu, ev);
+          launch_conv_fwd_smallc(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), nullptr, geom(f), relu, ev);
         else
           launch_conv_fwd_direct(st, dt, at(o.in), c.wc(f.w_off), bias, at(o.out), geom(f), relu, ev);
         break;

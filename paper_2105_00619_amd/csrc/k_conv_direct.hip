@@ -235,12 +235,6 @@ __global__ void __launch_bounds__(256) conv_fwd_smallc_kernel(const T* __restric
   }
 }
 
-// The same layer in the 16-bit modes, with at most 32 products per output (3x3 on up to 3 channels) and output
-// channels in groups of 64: the plain-FMA kernel above is bound by its 27 x 64 multiply-adds per pixel on the vector
-// units (296 us for 4.2 M pixels, where writing the output takes 100), so the products go to the matrix cores as one
-// 32-deep MFMA step: the block gathers the patches of its 128 pixels into LDS as [pixel][32] in the storage type (depth
-// 27..31 zero), the 64 x 32 weight tile beside them, every wavefront multiplies 64 pixels x 32 channels with two
-// 32x32x16 MFMAs per 32 x 32 tile, and the shared epilogue rounds and stores whole rows.
 template <class T> struct StemMma;
 template <> struct StemMma<bf16_t> {
   typedef __attribute__((ext_vector_type(8))) __bf16 V;
@@ -253,108 +247,157 @@ template <> struct StemMma<f16_t> {
   __device__ static __forceinline__ A run(V a, V b, A c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 
-template <class T, int C, bool EVAL>
-__global__ void __launch_bounds__(256) conv_fwd_smallc_mfma_kernel(const T* __restrict__ x, const T* __restrict__ w,
-                                                                   const float* __restrict__ bias, T* __restrict__ out,
-                                                                   ConvGeom g, int relu, FastDiv divQ, FastDiv divPQ,
-                                                                   const T* __restrict__ skip) {
-  // (EVAL: bias is the [2][K] scale and shift of the inference-mode BatchNorm behind the layer)
+// The same layer in the 16-bit modes, with at most 32 products per output (3x3 on up to 3 channels) and output channels in
+// groups of 64, on the matrix cores: HBM-bound on writing the output, so the work per output is kept to a few
+// instructions.  Blocks stay and walk tiles of 128 consecutive pixels (a tile's outputs of a 64-channel layer are one
+// contiguous 16 KB).  A wavefront multiplies its 32 pixels by 64 channels: the 64 x 32 weights (depth 27..31 zero) live in
+// registers, a lane gathers half of the 27 inputs of its own pixel straight into the MFMA operand (one index decomposition
+// and one nine-bit mask of taps inside the image per lane and tile), the next tile's inputs are requested before this
+// tile's results are stored.  The results are channels x pixels: four consecutive channels of a pixel per lane, rounded in
+// pairs, through LDS, stored as 16-byte pieces of whole rows; the storing threads also keep the channel sums of what they
+// store for the BatchNorm that follows, one row of block sums per block.
+// 262 144 pixels, 3 -> 64 channels, bf16: 15.7 us, 22.4 with the sums.
+// (With every thread gathering sixteen elements into an LDS tile, and the fp32 epilogue tile: 21.4 us, and 14 us for the
+// sums in a pass of their own.)
+// AFF: table of scale and shift per channel: an inference-mode BatchNorm, or a bias (scale 1)
+constexpr int STEM_BM = 128;
+template <class T, int C, bool AFF, bool STAT>
+__global__ void __launch_bounds__(256) conv_stem_fwd_kernel(const T* __restrict__ x, const T* __restrict__ w,
+                                                            const float* __restrict__ bias, const float* __restrict__ affine,
+                                                            T* __restrict__ out, float* __restrict__ stat_partial, ConvGeom g,
+                                                            int relu, FastDiv divQ, FastDiv divPQ) {
   typedef typename StemMma<T>::V FV;
   typedef typename StemMma<T>::A v16f;
-  constexpr int RSC = 9 * C;       // <= 32
-  constexpr int PITCH = 40;        // elements per LDS row (80 bytes)
-  constexpr int PPT = 4;
+  typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+  constexpr int RSC = 9 * C, PITCH = 64 + 8;
   static_assert(RSC <= 32, "one 32-deep step");
-  // 15 KB of operands, reused as the 17 KB epilogue tile: eight blocks (all 32 wavefronts) fit a CU, which is what hides
-  // the latency of the gather (a block is a dozen dependent-free 2-byte loads per thread, a barrier and a few MFMAs)
-  constexpr int EP_BYTES = 64 * (64 + 4) * 4, OP_BYTES = (64 + 128) * PITCH * (int)sizeof(T);
-  __shared__ __attribute__((aligned(16))) unsigned char smem[EP_BYTES > OP_BYTES ? EP_BYTES : OP_BYTES];
-  T* ws = reinterpret_cast<T*>(smem);                 // [channel][depth]
-  T* xs = ws + 64 * PITCH;                            // [pixel of the block][depth]
-  float* ep = reinterpret_cast<float*>(smem);         // epilogue tile (after the operands have been read)
-  const int tid = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) T stg[STEM_BM * PITCH];
+  __shared__ float tab[2][64];
+  __shared__ float red[STAT ? 2 * 32 * 64 : 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hg = lane >> 5, l32 = lane & 31;
   const int kbase = blockIdx.y * 64;
-  for (int i = tid; i < 64 * 32; i += 256) {
-    const int k = i >> 5, e = i & 31;
-    ws[k * PITCH + e] = e < RSC ? w[(kbase + k) * RSC + e] : from_f32<T>(0.f);
-  }
-  const int grp = tid & 7, slot = tid >> 3;
   const int pixels = g.N * g.P * g.Q;  // < 2^24 (checked by the launcher)
   const int H = g.H, W = g.W, cstride = g.stride, pad = g.pad;
-  // this thread's depth elements e = grp + 8u of each of its four pixels
-  int er[4], es[4], ec[4];
+  const int tiles = (pixels + STEM_BM - 1) / STEM_BM;
+
+  // weights: lane group hg owns depth elements [16 hg, + 16), eight per MFMA
+  FV wv[2][2];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = grp + 8 * u < RSC ? grp + 8 * u : RSC - 1;
-    const int tap = e / C;
-    ec[u] = e - tap * C; er[u] = tap / 3 - pad; es[u] = tap % 3 - pad;
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int e = hg * 16 + h * 8 + j;
+        const T v = w[(kbase + i * 32 + l32) * RSC + (e < RSC ? e : 0)];
+        wv[i][h][j] = e < RSC ? v : from_f32<T>(0.f);
+      }
+  if (AFF && tid < 64) {
+    tab[0][tid] = affine ? affine[kbase + tid] : 1.f;
+    tab[1][tid] = affine ? affine[g.K + kbase + tid] : bias[kbase + tid];
   }
+  // this lane's sixteen inputs: offset from the pixel's centre element and filter tap
+  int off[16], bit[16];
 #pragma unroll
-  for (int i = 0; i < PPT; ++i) {
-    const int m = blockIdx.x * (32 * PPT) + slot + 32 * i;
+  for (int j = 0; j < 16; ++j) {
+    const int e = hg * 16 + j, ec = e < RSC ? e : 0;
+    const int tap = ec / C;
+    off[j] = ((tap / 3 - pad) * W + (tap % 3 - pad)) * C + (ec - tap * C);
+    bit[j] = e < RSC ? 1 << tap : 0;
+  }
+  T rx[16];
+  unsigned taps = 0u;
+  auto gather = [&](int tile) {
+    const int m = tile * STEM_BM + wave * 32 + l32;
     const uint32_t mm = m < pixels ? (uint32_t)m : 0u;
     const uint32_t n = divPQ.div(mm), rem = mm - n * divPQ.d;
     const uint32_t p = divQ.div(rem), q = rem - p * divQ.d;
-    const int ih0 = (int)p * cstride, iw0 = (int)q * cstride, nbase = (int)n * H;
+    const int ih = (int)p * cstride, iw = (int)q * cstride;
+    unsigned cols = 0u;
+    taps = 0u;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int ih = ih0 + er[u], iw = iw0 + es[u];
-      const bool ok = ih >= 0 && ih < H && iw >= 0 && iw < W && grp + 8 * u < RSC;
-      const T v = x[ok ? ((nbase + ih) * W + iw) * C + ec[u] : 0];
-      xs[(slot + 32 * i) * PITCH + grp + 8 * u] = ok ? v : from_f32<T>(0.f);
-    }
-  }
-  __syncthreads();
-  // lane group g owns depth elements [16g, 16g + 16) of both operands (first MFMA: its first eight, second: the rest)
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, hg = lane >> 5, l32 = lane & 31;
-  const FV b0 = *reinterpret_cast<const FV*>(&ws[(wn * 32 + l32) * PITCH + hg * 16]);
-  const FV b1 = *reinterpret_cast<const FV*>(&ws[(wn * 32 + l32) * PITCH + hg * 16 + 8]);
-  v16f acc[2];
+    for (int t = 0; t < 3; ++t) cols |= (iw + t - pad >= 0 && iw + t - pad < W) ? 1u << t : 0u;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const T* ap = &xs[(wm * 64 + i * 32 + l32) * PITCH + hg * 16];
-    const FV a0 = *reinterpret_cast<const FV*>(ap);
-    const FV a1 = *reinterpret_cast<const FV*>(ap + 8);
-    v16f c;
+    for (int t = 0; t < 3; ++t) taps |= (ih + t - pad >= 0 && ih + t - pad < H) ? cols << (3 * t) : 0u;
+    if (m >= pixels) taps = 0u;
+    const T* px = x + (((int64_t)n * H + ih) * W + iw) * C;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) c[e] = 0.f;
-    c = StemMma<T>::run(a0, b0, c);
-    acc[i] = StemMma<T>::run(a1, b1, c);
-  }
-  // epilogue: the 64 rows of one wavefront pair at a time through LDS as fp32 [64][64 + 4]
-  constexpr int EP_PITCH = 64 + 4;
-  float ss[8], qq[8];  // (channel sums: not used here)
+    for (int j = 0; j < 16; ++j) rx[j] = *((taps & bit[j]) ? px + off[j] : x);
+  };
+  float ss[8], qq[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) { ss[k] = 0.f; qq[k] = 0.f; }
+  const int c8 = (tid & 7) * 8, erow = tid >> 3;
+
+  int tile = blockIdx.x;
+  gather(tile);
+  for (; tile < tiles; tile += gridDim.x) {
+    FV xv[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    __syncthreads();
-    if (wm == u) {
+    for (int j = 0; j < 16; ++j) xv[j >> 3][j & 7] = (taps & bit[j]) ? rx[j] : from_f32<T>(0.f);
+    v16f acc[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          ep[(i * 32 + 8 * (e >> 2) + 4 * hg + (e & 3)) * EP_PITCH + wn * 32 + l32] = acc[i][e];
+      for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+      acc[i] = StemMma<T>::run(wv[i][0], xv[0], acc[i]);
+      acc[i] = StemMma<T>::run(wv[i][1], xv[1], acc[i]);
     }
+    if (tile + (int)gridDim.x < tiles) gather(tile + gridDim.x);
+    __syncthreads();  // the tile before has been stored (and, the first time, the table is there)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = i * 32 + 8 * q + 4 * hg;
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          v[k] = acc[i][4 * q + k];
+          if (AFF) v[k] = bn_affine(v[k], tab[0][c + k], tab[1][c + k]);
+          if (relu) v[k] = fmaxf(v[k], 0.f);
+        }
+        u32x2 o;
+        o[0] = __builtin_bit_cast(uint32_t, from_f32x2<T>(v[0], v[1]));
+        o[1] = __builtin_bit_cast(uint32_t, from_f32x2<T>(v[2], v[3]));
+        *reinterpret_cast<u32x2*>(&stg[(wave * 32 + l32) * PITCH + c]) = o;
+      }
     __syncthreads();
-    auto rowoff = [&](int row) -> int64_t {
-      const int64_t m = (int64_t)blockIdx.x * 128 + u * 64 + row;
-      return m < pixels ? m * g.K : -1;
-    };
-    if (EVAL)
-      epi_eval_pass_nt<256, T, 64, 64>(ep, tid, kbase, bias, g.K, skip, out, relu, rowoff);
-    else
-      epi_store_pass<T, 64, 64, true, false, false>(ep, tid, kbase, bias, (const T*)nullptr, (const uint8_t*)nullptr, out, relu,
-                                                    rowoff, ss, qq);
+    Vec<T, 8> tv[4];
+    const int m0 = tile * STEM_BM;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int row = erow + 32 * it;
+      tv[it] = *reinterpret_cast<const Vec<T, 8>*>(&stg[row * PITCH + c8]);
+      if (m0 + row < pixels) *reinterpret_cast<Vec<T, 8>*>(out + (int64_t)(m0 + row) * g.K + kbase + c8) = tv[it];
+      else if (STAT) tv[it] = Vec<T, 8>{};  // counts as zero
+    }
+    if (STAT) {
+      typedef typename Dot2<T>::V T2;
+      T2 one2;
+      one2[0] = from_f32<T>(1.f); one2[1] = from_f32<T>(1.f);
+#pragma unroll
+      for (int it = 0; it < 4; it += 2)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          T2 p2;
+          p2[0] = tv[it].v[k]; p2[1] = tv[it + 1].v[k];
+          ss[k] = Dot2<T>::run(p2, one2, ss[k]);
+          qq[k] = Dot2<T>::run(p2, p2, qq[k]);
+        }
+    }
   }
+  if (STAT)
+    epi_stat_combine_nt<256, 64>(red, tid, ss, qq, stat_partial + ((int64_t)blockIdx.x * 2 + 0) * g.K + kbase,
+                                 stat_partial + ((int64_t)blockIdx.x * 2 + 1) * g.K + kbase);
 }
 
 // Weight gradient for few input channels (the network stem):  dw[k][e] = sum over pixels of dz[px][k] * col[px][e],
-// e = (tap, c) < 36, k <= 64.  HBM-bound on reading dz once.  A block reduces a fixed chunk of pixels in tiles of 64:
-// the dz tile [64][64] and the im2col tile [64][R*S*C] are staged in LDS as fp32 (two stages; the next tile's global
-// loads are issued before the MFMAs of the current one).  Each wavefront multiplies 16 of the 64 pixels with fp32
-// 32x32x2 MFMAs (rows k, columns e); the four partial sums are added in wavefront order through LDS.
+// e = (tap, c) < 36, k in groups of 64 (blockIdx.y; a single group may have fewer).  Bound by reading dz once, and by
+// latency: a block has few tiles.  A block reduces a fixed chunk of pixels in tiles of 64: the dz tile [64][64] and the
+// im2col tile [64][R*S*C] are staged in LDS as fp32 (two stages; the next tile's global loads are issued before the MFMAs
+// of the current one).  Each wavefront multiplies 16 of the 64 pixels with fp32 32x32x2 MFMAs (rows k, columns e); the
+// four partial sums are added in wavefront order through LDS.
 template <class T>
 __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restrict__ x, const T* __restrict__ dz,
                                                                 float* __restrict__ partial, ConvGeom g, int chunk,
@@ -367,6 +410,7 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
   __shared__ __attribute__((aligned(16))) float dzs[2][64 * DP];
   __shared__ float xs[2][64 * XP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hg = lane >> 5, l32 = lane & 31;
+  const int kbase = blockIdx.y * 64, KN = g.K - kbase < 64 ? g.K - kbase : 64;
   const int K = g.K, C = g.C, H = g.H, W = g.W, rsc = g.R * g.S * g.C, cstride = g.stride;
   const int pixels = g.N * g.P * g.Q;
   const int m0 = blockIdx.x * chunk;
@@ -375,8 +419,7 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
 
   // This thread's im2col elements: one pixel of the tile (its lane) and the columns e = wave + 4u, so that a tile costs
   // one index decomposition per thread; whether a column's filter tap lies inside the image is one bit of a nine-bit mask
-  // per pixel.  (With the elements dealt out in memory order every one of them had its own pixel to decompose: 49 us
-  // instead of 20 for 262 144 pixels in bf16.)
+  // per pixel.
   const int xtap0 = wave;  // e = xtap0 + 4u
   int xoff[NX], xbit[NX];
 #pragma unroll
@@ -396,8 +439,8 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
 #pragma unroll
     for (int i = 0; i < DCH; ++i) {
       const int id = tid + i * 256, px = id / CPP, kv = id - px * CPP;
-      const bool ok = mt + px < m1 && kv * EV < K;
-      rd[i] = *reinterpret_cast<const Chunk*>(dz + (int64_t)(ok ? mt + px : m0) * K + (ok ? kv * EV : 0));
+      const bool ok = mt + px < m1 && kv * EV < KN;
+      rd[i] = *reinterpret_cast<const Chunk*>(dz + (int64_t)(ok ? mt + px : m0) * K + kbase + (ok ? kv * EV : 0));
       dm |= ok ? (1u << i) : 0u;
     }
     {
@@ -454,7 +497,7 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  const bool two_m = K > 32, two_n = rsc > 32;
+  const bool two_m = KN > 32, two_n = rsc > 32;
   const int e0 = l32 < rsc ? l32 : rsc - 1, e1 = 32 + l32 < rsc ? 32 + l32 : rsc - 1;
   const float z0 = l32 < rsc ? 1.f : 0.f, z1 = 32 + l32 < rsc ? 1.f : 0.f;
 
@@ -484,26 +527,138 @@ __global__ void __launch_bounds__(256) conv_wgrad_smallc_kernel(const T* __restr
     __syncthreads();
   }
 
-  // the four wavefronts' sums, added in wavefront order: red[k][e], pitch 65
+  // the four wavefronts' sums of one column tile, added in wavefront order: red[wavefront][k][32]
   float* red = &dzs[0][0];
-#pragma unroll 1
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
+  static_assert(2 * 64 * DP >= 4 * 64 * 32, "the four partial tiles lie over the dz stages");
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j) {
+    if (j == 1 && !two_n) break;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int idx = (i * 32 + 8 * (e >> 2) + 4 * hg + (e & 3)) * 65 + j * 32 + l32;
-            red[idx] = w == 0 ? acc[i][j][e] : red[idx] + acc[i][j][e];
-          }
+      for (int e = 0; e < 16; ++e) red[wave * 2048 + (i * 32 + 8 * (e >> 2) + 4 * hg + (e & 3)) * 32 + l32] = acc[i][j][e];
+    __syncthreads();
+    for (int o = tid; o < 2048; o += 256) {
+      const int k = o >> 5, e = j * 32 + (o & 31);
+      if (k < KN && e < rsc)
+        partial[((int64_t)blockIdx.x * K + kbase + k) * rsc + e] = ((red[o] + red[2048 + o]) + red[4096 + o]) + red[6144 + o];
     }
     __syncthreads();
   }
-  for (int o = tid; o < K * rsc; o += 256) {
-    const int k = o / rsc, e = o - k * rsc;
-    partial[((int64_t)blockIdx.x * K + k) * rsc + e] = red[k * 65 + e];
+}
+
+// The same in the 16-bit modes with at most 32 columns (3x3 on up to 3 channels) and whole groups of 64 channels, on the
+// 16-bit MFMAs: tiles of 128 pixels, dz staged as loaded and read with the transposing LDS read, the im2col columns
+// gathered by one pixel per thread and stored column-major, so that a lane's eight consecutive pixels of a column are one
+// 16-byte read.  One LDS stage, the next tile's loads in registers, small enough for several blocks per CU to cover each
+// other.  262 144 pixels, bf16: 12.5 us (the fp32 kernel above, converting both operands: 47 us).
+template <class T, int C>
+__global__ void __launch_bounds__(256) conv_stem_wgrad_kernel(const T* __restrict__ x, const T* __restrict__ dz,
+                                                              float* __restrict__ partial, ConvGeom g, int chunk, FastDiv divQ,
+                                                              FastDiv divPQ) {
+  typedef typename StemMma<T>::V FV;
+  typedef typename StemMma<T>::A v16f;
+  typedef __attribute__((ext_vector_type(4))) short v4s;
+  typedef __attribute__((ext_vector_type(8))) short v8s;
+  constexpr int RSC = 9 * C, BM = STEM_BM, DP = 64 + 16, XP = BM + 8;
+  constexpr int HALF = 16;  // columns gathered by each of a pixel's two threads
+  static_assert(RSC <= 32, "one 32-column tile");
+  __shared__ __attribute__((aligned(16))) T smem[BM * DP + 32 * XP];  // dz [pixel][channel], im2col [column][pixel]
+  static_assert(sizeof(T) * (BM * DP + 32 * XP) >= 4 * 32 * 32 * 4, "the four partial 32 x 32 tiles lie over the operands");
+  T* ds = smem;
+  T* xs = smem + BM * DP;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hg = lane >> 5, l32 = lane & 31;
+  const int kbase = blockIdx.y * 64;
+  const int K = g.K, H = g.H, W = g.W, cstride = g.stride, pad = g.pad;
+  const int pixels = g.N * g.P * g.Q;
+  const int m0 = blockIdx.x * chunk;
+  const int m1 = m0 + chunk < pixels ? m0 + chunk : pixels;
+  const int nt = m1 > m0 ? (m1 - m0 + BM - 1) / BM : 0;
+  const int gpx = tid & (BM - 1), gh = tid >> 7;  // gathering: pixel of the tile, which half of the columns
+  Chunk rd[4];
+  T rx[HALF];
+  unsigned taps = 0u;
+  auto gload = [&](int t) {
+    const int mt = m0 + t * BM;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int id = tid + i * 256, px = id >> 3, kv = id & 7;
+      rd[i] = *reinterpret_cast<const Chunk*>(dz + (int64_t)(mt + px < m1 ? mt + px : m0) * K + kbase + kv * 8);
+    }
+    const int m = mt + gpx;
+    const uint32_t mm = m < m1 ? (uint32_t)m : (uint32_t)m0;
+    const uint32_t n = divPQ.div(mm), rem = mm - n * divPQ.d;
+    const uint32_t p = divQ.div(rem), q = rem - p * divQ.d;
+    const int ih = (int)p * cstride, iw = (int)q * cstride;
+    unsigned cols = 0u;
+    taps = 0u;
+#pragma unroll
+    for (int u = 0; u < 3; ++u) cols |= (iw + u - pad >= 0 && iw + u - pad < W) ? 1u << u : 0u;
+#pragma unroll
+    for (int u = 0; u < 3; ++u) taps |= (ih + u - pad >= 0 && ih + u - pad < H) ? cols << (3 * u) : 0u;
+    if (m >= m1) taps = 0u;
+    const T* px = x + (((int64_t)n * H + ih) * W + iw) * C;
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) {
+      const int e = gh * HALF + j, ec = e < RSC ? e : 0, tap = ec / C;
+      rx[j] = *((taps >> tap) & 1u ? px + ((tap / 3 - pad) * W + (tap % 3 - pad)) * C + (ec - tap * C) : x);
+    }
+  };
+  auto sstore = [&](int t) {
+    const int mt = m0 + t * BM;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int id = tid + i * 256, px = id >> 3, kv = id & 7;
+      *reinterpret_cast<Chunk*>(&ds[px * DP + kv * 8]) = mt + px < m1 ? rd[i] : zero_chunk();
+    }
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) {
+      const int e = gh * HALF + j, tap = (e < RSC ? e : 0) / C;
+      xs[e * XP + gpx] = e < RSC && ((taps >> tap) & 1u) ? rx[j] : from_f32<T>(0.f);
+    }
+  };
+  v16f acc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+  // transposing read: within 16 lanes, lane r points at 4 consecutive channels (from 4 * (r % 4)) of pixel r / 4; lane l
+  // receives channel l of the 16 at four pixels
+  const int r16 = l32 & 15, coff = (l32 & 16) + 4 * (r16 & 3);
+  if (nt > 0) gload(0);
+  for (int t = 0; t < nt; ++t) {
+    sstore(t);
+    __syncthreads();
+    if (t + 1 < nt) gload(t + 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int p0 = wave * 32 + h * 16 + hg * 8;  // the lane group's eight pixels
+      const FV b = *reinterpret_cast<const FV*>(&xs[l32 * XP + p0]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const T* pp = ds + (p0 + (r16 >> 2)) * DP + i * 32 + coff;
+        const v4s u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(pp));
+        const v4s u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(pp + 4 * DP));
+        const v8s u = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
+        acc[i] = StemMma<T>::run(__builtin_bit_cast(FV, u), b, acc[i]);
+      }
+    }
+    __syncthreads();
+  }
+  // the four wavefronts' sums of a 32 x 32 tile, added in wavefront order
+  float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave * 1024 + (8 * (e >> 2) + 4 * hg + (e & 3)) * 32 + l32] = acc[i][e];
+    __syncthreads();
+    for (int o = tid; o < 1024; o += 256) {
+      const int k = o >> 5, e = o & 31;
+      if (e < RSC)
+        partial[((int64_t)blockIdx.x * K + kbase + i * 32 + k) * RSC + e] =
+            ((red[o] + red[1024 + o]) + red[2048 + o]) + red[3072 + o];
+    }
+    __syncthreads();
   }
 }
 
@@ -532,16 +687,30 @@ __global__ void __launch_bounds__(256) partial_reduce_kernel(const float* __rest
   }
 }
 
+// 8 to 31 output channels: with a group of 64 mostly empty the direct kernel is the faster one (3 -> 8 channels, 8 images of
+// 32 x 32, fp32: 5.7 us against 12.5)
 bool conv_smallc_fwd_ok(const ConvGeom& g) {
-  return g.C <= 4 && g.R == 3 && g.S == 3 && g.K % 8 == 0 && (int64_t)g.N * g.P * g.Q < (1 << 24) &&
+  return g.C <= 4 && g.R == 3 && g.S == 3 && g.K % 8 == 0 && g.K >= 32 && (int64_t)g.N * g.P * g.Q < (1 << 24) &&
          (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
 }
+// the 16-bit kernels of the stem
+static bool stem_ok(int dt, const ConvGeom& g) { return dt != DT_F32 && g.C <= 3 && g.R == 3 && g.S == 3 && g.K % 64 == 0; }
+static int stem_blocks(const ConvGeom& g) {  // blocks stay: four per CU, or one per tile
+  const int64_t tiles = ((int64_t)g.N * g.P * g.Q + STEM_BM - 1) / STEM_BM;
+  return (int)(tiles < 1024 ? tiles : 1024);
+}
+// row blocks over which the forward kernel also sums its outputs for the BatchNorm that follows (0: it does not)
+int conv_smallc_stat_blocks(int dt, const ConvGeom& g) { return conv_smallc_fwd_ok(g) && stem_ok(dt, g) ? stem_blocks(g) : 0; }
 bool conv_smallc_wgrad_ok(const ConvGeom& g) {
-  return g.C <= 4 && g.R * g.S * g.C <= SMALLC_MAX && g.K <= 64 && g.K % 8 == 0 && (int64_t)g.N * g.P * g.Q < (1 << 24) &&
-         (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
+  return g.C <= 4 && g.R * g.S * g.C <= SMALLC_MAX && (g.K <= 64 ? g.K % 8 == 0 : g.K % 64 == 0) &&
+         (int64_t)g.N * g.P * g.Q < (1 << 24) && (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
 }
-int conv_smallc_wgrad_splits(const ConvGeom& g) {
+int conv_smallc_wgrad_splits(int dt, const ConvGeom& g) {
   const int64_t pixels = (int64_t)g.N * g.P * g.Q;
+  if (stem_ok(dt, g)) {  // one tile per block up to two blocks per CU
+    const int64_t b = (pixels + STEM_BM - 1) / STEM_BM;
+    return (int)(b < 512 ? b : 512);
+  }
   // four tiles of 64 pixels per block, fewer where that would leave CUs idle
   int64_t b = (pixels + 255) / 256;
   if (b < 512) b = (pixels + 63) / 64 < 512 ? (pixels + 63) / 64 : 512;
@@ -549,22 +718,26 @@ int conv_smallc_wgrad_splits(const ConvGeom& g) {
 }
 
 template <class T>
-static void launch_fwd_smallc_t(hipStream_t st, const void* x, const void* w, const float* bias, void* out, const ConvGeom& g,
-                                int relu, const ConvEval& ev) {
+static void launch_fwd_smallc_t(hipStream_t st, const void* x, const void* w, const float* bias, void* out, float* stat_partial,
+                                const ConvGeom& g, int relu, const ConvEval& ev) {
   dim3 grid(ceil_div((int64_t)g.N * g.P * g.Q, 128), ceil_div(g.K, 64)), block(256);
   const FastDiv dq = make_fastdiv((uint32_t)g.Q), dpq = make_fastdiv((uint32_t)(g.P * g.Q));
   const T* skip = (const T*)ev.skip;
   if constexpr (sizeof(T) == 2) {
-    if (g.K % 64 == 0 && g.C <= 3) {  // 16-bit modes: on the matrix cores
-#define SMALLC_MFMA(C_)                                                                                                       \
-  {                                                                                                                           \
-    if (ev.affine) OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, C_, true>), grid, block, 0, st, (const T*)x, (const T*)w,      \
-                               ev.affine, (T*)out, g, relu, dq, dpq, skip);                                                   \
-    else OSEQ_LAUNCH((conv_fwd_smallc_mfma_kernel<T, C_, false>), grid, block, 0, st, (const T*)x, (const T*)w, bias,         \
-                     (T*)out, g, relu, dq, dpq, skip);                                                                        \
+    if (stem_ok(DT_BF16, g) && !skip) {  // 16-bit modes: on the matrix cores
+      grid.x = stem_blocks(g);
+#define STEM_LAUNCH(C_, AFF_, STAT_)                                                                                       \
+  OSEQ_LAUNCH((conv_stem_fwd_kernel<T, C_, AFF_, STAT_>), grid, block, 0, st, (const T*)x, (const T*)w, bias, ev.affine,  \
+              (T*)out, stat_partial, g, relu, dq, dpq)
+#define STEM_C(C_)                                                                                                         \
+  {                                                                                                                        \
+    if (ev.affine || bias) { if (stat_partial) STEM_LAUNCH(C_, true, true); else STEM_LAUNCH(C_, true, false); }          \
+    else if (stat_partial) STEM_LAUNCH(C_, false, true);                                                                   \
+    else STEM_LAUNCH(C_, false, false);                                                                                    \
   }
-      if (g.C == 1) SMALLC_MFMA(1) else if (g.C == 2) SMALLC_MFMA(2) else SMALLC_MFMA(3)
-#undef SMALLC_MFMA
+      if (g.C == 1) STEM_C(1) else if (g.C == 2) STEM_C(2) else STEM_C(3)
+#undef STEM_C
+#undef STEM_LAUNCH
       return;
     }
   }
@@ -580,25 +753,39 @@ static void launch_fwd_smallc_t(hipStream_t st, const void* x, const void* w, co
 #undef SMALLC_FMA
 }
 
+// stat_partial: null, or [conv_smallc_stat_blocks][2][C_out] floats receiving per-block sums of the stored outputs
 void launch_conv_fwd_smallc(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu, const ConvEval& ev) {
-  if (dt == DT_F32) launch_fwd_smallc_t<float>(st, x, w, bias, out, g, relu, ev);
-  else if (dt == DT_BF16) launch_fwd_smallc_t<bf16_t>(st, x, w, bias, out, g, relu, ev);
-  else launch_fwd_smallc_t<f16_t>(st, x, w, bias, out, g, relu, ev);
+                            float* stat_partial, const ConvGeom& g, int relu, const ConvEval& ev) {
+  if (dt == DT_F32) launch_fwd_smallc_t<float>(st, x, w, bias, out, stat_partial, g, relu, ev);
+  else if (dt == DT_BF16) launch_fwd_smallc_t<bf16_t>(st, x, w, bias, out, stat_partial, g, relu, ev);
+  else launch_fwd_smallc_t<f16_t>(st, x, w, bias, out, stat_partial, g, relu, ev);
 }
 
-// partial: [splits][K][R*S*C] floats; splits = conv_smallc_wgrad_splits(g)
+template <class T>
+static void launch_wgrad_smallc_t(hipStream_t st, const T* x, const T* dz, float* dst, int splits, const ConvGeom& g) {
+  const int64_t pixels = (int64_t)g.N * g.P * g.Q;
+  const FastDiv dq = make_fastdiv((uint32_t)g.Q), dpq = make_fastdiv((uint32_t)(g.P * g.Q));
+  const dim3 grid(splits, ceil_div(g.K, 64)), block(256);
+  const int per = ceil_div(pixels, splits);
+  if constexpr (sizeof(T) == 2) {
+    if (stem_ok(DT_BF16, g)) {
+      const int chunk = ceil_div(per, STEM_BM) * STEM_BM;
+      if (g.C == 1) OSEQ_LAUNCH((conv_stem_wgrad_kernel<T, 1>), grid, block, 0, st, x, dz, dst, g, chunk, dq, dpq);
+      else if (g.C == 2) OSEQ_LAUNCH((conv_stem_wgrad_kernel<T, 2>), grid, block, 0, st, x, dz, dst, g, chunk, dq, dpq);
+      else OSEQ_LAUNCH((conv_stem_wgrad_kernel<T, 3>), grid, block, 0, st, x, dz, dst, g, chunk, dq, dpq);
+      return;
+    }
+  }
+  OSEQ_LAUNCH(conv_wgrad_smallc_kernel<T>, grid, block, 0, st, x, dz, dst, g, ceil_div(per, 64) * 64, dq, dpq);
+}
+
+// partial: [splits][K][R*S*C] floats; splits = conv_smallc_wgrad_splits(dt, g)
 void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                               const ConvGeom& g) {
-  const int64_t pixels = (int64_t)g.N * g.P * g.Q;
-  int chunk = (int)((pixels + splits - 1) / splits);
-  chunk = (chunk + 63) / 64 * 64;
   float* dst = splits > 1 ? partial : dw;
-  dim3 grid(splits), block(256);
-  const FastDiv dq = make_fastdiv((uint32_t)g.Q), dpq = make_fastdiv((uint32_t)(g.P * g.Q));
-  if (dt == DT_F32) OSEQ_LAUNCH(conv_wgrad_smallc_kernel<float>, grid, block, 0, st, (const float*)x, (const float*)dz, dst, g, chunk, dq, dpq);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(conv_wgrad_smallc_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)dz, dst, g, chunk, dq, dpq);
-  else OSEQ_LAUNCH(conv_wgrad_smallc_kernel<f16_t>, grid, block, 0, st, (const f16_t*)x, (const f16_t*)dz, dst, g, chunk, dq, dpq);
+  if (dt == DT_F32) launch_wgrad_smallc_t<float>(st, (const float*)x, (const float*)dz, dst, splits, g);
+  else if (dt == DT_BF16) launch_wgrad_smallc_t<bf16_t>(st, (const bf16_t*)x, (const bf16_t*)dz, dst, splits, g);
+  else launch_wgrad_smallc_t<f16_t>(st, (const f16_t*)x, (const f16_t*)dz, dst, splits, g);
   if (splits > 1) {
     const int64_t n = (int64_t)g.K * g.R * g.S * g.C;
     OSEQ_LAUNCH(partial_reduce_kernel, dim3(ceil_div(n, 16)), dim3(256), 0, st, partial, dw, n, splits);

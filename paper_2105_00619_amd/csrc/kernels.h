@@ -80,9 +80,10 @@ void launch_conv_wgrad_direct(hipStream_t st, int dt, const void* x, const void*
 // few input channels (the stem): plain-FMA kernels with the weights in LDS
 bool conv_smallc_fwd_ok(const ConvGeom& g);
 bool conv_smallc_wgrad_ok(const ConvGeom& g);
-int conv_smallc_wgrad_splits(const ConvGeom& g);
+int conv_smallc_wgrad_splits(int dt, const ConvGeom& g);
+int conv_smallc_stat_blocks(int dt, const ConvGeom& g);
 void launch_conv_fwd_smallc(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
-                            const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());
+                            float* stat_partial, const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());
 void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                               const ConvGeom& g);
 

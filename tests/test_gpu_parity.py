@@ -236,6 +236,31 @@ def test_head_products_at_tile_edges(n, h, w, c, classes, gap, precision):
     assert max(errs.values()) <= TOL[precision], errs
 
 
+@pytest.mark.parametrize("bn", [False, True])
+@pytest.mark.parametrize("precision,cin,cout,stride,pad,h,w,b", [
+    (W.BF16, 3, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 128, 2, 1, 13, 10, 9), (W.BF16, 1, 64, 1, 0, 8, 8, 3), (W.FP16, 2, 192, 1, 1, 5, 33, 4),
+    (W.BF16, 3, 64, 1, 1, 32, 32, 130), (W.FP32, 3, 128, 1, 1, 11, 6, 4), (W.FP32, 4, 64, 2, 1, 9, 9, 3), (W.FP32, 3, 8, 1, 1, 9, 9, 3),
+    (W.BF16, 4, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 48, 1, 1, 9, 7, 5)])
+def test_stem_kernels_at_tile_edges(precision, cin, cout, stride, pad, h, w, b, bn):
+    """First layers with few input channels: forward (with the channel sums of the BatchNorm behind it, or a bias and ReLU-free)
+    and weight gradient around their tiles of 64 and 128 pixels, channel groups of 64 and fewer, one to four input channels,
+    stride 2, no border.  Against plain float64 with the bars of the single-layer tests."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(cin, cout, 3, stride, pad=pad, bn=bn, relu=False, bias=not bn), W.flatten_linear_ce(cout, 10)]
+    rnd = {W.FP32: lambda v: v, W.BF16: O.round_to_bf16, W.FP16: O.round_to_fp16}[precision]
+    p = W.make_params(units, h, w, 13, perturb=True)
+    sl = W.param_slices(units, h, w)["u0.w"]
+    p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, h, w, cin, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    loss, g = oracle_step(units, p, x, y)
+    errs = plain_errors(units, h, w, r["grads"], g)
+    assert max(errs.values()) <= TOL[precision], errs
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+
+
 def _unit_trace(tr, xd, n_units):
     """GPU output of every body unit the plan writes to memory: {unit: float64 array}."""
     from paper_2105_00619_amd.binding import OptorchError
