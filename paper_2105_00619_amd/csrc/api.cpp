@@ -128,6 +128,14 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         b.fold = 1;
         cv.fold_src = (int)i;
       }
+      // The BatchNorm of a projection shortcut: done by the apply operation that adds it.
+      for (FOp& a : p.fops) {
+        if (a.kind != F_BN_APPLY || a.skip < 0 || readers[a.skip] != 1) continue;
+        for (size_t i = 0; i < p.fops.size(); ++i) {
+          FOp& b = p.fops[i];
+          if (b.kind == F_BN_APPLY && b.out == a.skip && b.unit == a.unit && !b.relu && b.skip < 0) { b.fold = 1; a.fold_skip = (int)i; }
+        }
+      }
     }
     build_inference(p);
     // k_segments 0 and storage_mode -1 leave the choice to the plan: the cheapest candidate in step time whose
@@ -339,8 +347,8 @@ void run_op(const Ctx& c, const SOp& s) {
         launch_bn_apply_pool(st, dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.at(s.out[0]), c.at(s.out[1]), f.N, f.P,
                              f.Q, f.C, f.relu);
       else
-        launch_bn_apply(st, dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.at(s.in[2]), c.at(s.out[0]), c.at(s.out[2]),
-                        (int64_t)f.N * f.P * f.Q, f.C, f.relu);
+        launch_bn_apply(st, dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.at(s.in[2]), (const float*)c.at(s.in[3]),
+                        c.at(s.out[0]), c.at(s.out[2]), (int64_t)f.N * f.P * f.Q, f.C, f.relu);
       break;
     case S_POOL_FWD:
       launch_maxpool_fwd(st, dt, c.at(s.in[0]), c.at(s.out[0]), f.N, f.H, f.W, f.C);

@@ -39,8 +39,10 @@ void launch_bn_eval_stats(hipStream_t st, const float* running, const float* gam
                           float* stats);
 // mask (null, or with a skip connection and C a multiple of 16 / element size): receives the ReLU decisions as bits,
 // byte (row * C + c) / V for the V = 16 / element size channels from c
-void launch_bn_apply(hipStream_t st, int dt, const void* z, const float* stats, const void* skip, void* out, void* mask,
-                     int64_t rows, int C, int relu);
+// skip_stats (null: none): skip is not the skip connection but the z of its BatchNorm (a projection shortcut's, without
+// ReLU) and this that BatchNorm's statistics tensor
+void launch_bn_apply(hipStream_t st, int dt, const void* z, const float* stats, const void* skip, const float* skip_stats,
+                     void* out, void* mask, int64_t rows, int C, int relu);
 // BatchNorm apply and the 2x2 max-pool behind it in one pass (H, W even): z [N][H][W][C] -> a (may be null: not kept)
 // and y [N][H/2][W/2][C]
 void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* stats, void* a, void* y, int N, int H, int W,

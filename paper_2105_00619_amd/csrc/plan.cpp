@@ -321,9 +321,10 @@ struct Scheduler {
         break;
       }
       case F_BN_APPLY: {
-        if (f.fold) break;  // done by the convolution that reads it
+        if (f.fold) break;  // done by the operation that reads it
         SOp& s = push(S_BN_APPLY, fi, phase, seg);
         s.in[0] = cur[f.x]; s.in[1] = cur[f.stats]; s.in[2] = f.skip >= 0 ? cur[f.skip] : -1;
+        if (f.fold_skip >= 0) { s.in[2] = cur[p.fops[f.fold_skip].x]; s.in[3] = cur[p.fops[f.fold_skip].stats]; }
         s.out[0] = value_inst(f.out);
         if (pool_fused(fi + 1, seg)) s.out[1] = value_inst(p.fops[fi + 1].out);  // the same kernel also pools
         if (f.mask >= 0) s.out[2] = value_inst(f.mask);

@@ -43,6 +43,8 @@ struct FOp {
   int fold = 0;       // F_BN_APPLY: 1 = never run; the one convolution that reads its output applies scale, shift and
                       // ReLU to z while it stages its operand (forward and weight gradient), so the output is never stored
   int fold_src = -1;  // F_CONV: the folded F_BN_APPLY operation its input comes from, or -1
+  int fold_skip = -1; // F_BN_APPLY with a skip connection: the F_BN_APPLY of the projection shortcut that it does as well
+                      // (that one's fold is 1: it reads the shortcut's z and statistics instead of its output), or -1
   int aux[3] = {-1, -1, -1};                     // head: feat, logits, dlogits
   int N = 0, H = 0, W = 0, C = 0, K = 0, R = 1, S = 1, stride = 1, pad = 0, P = 0, Q = 0;
   int relu = 0, has_bias = 0, has_bn = 0;
@@ -88,6 +90,8 @@ struct SOp {
                     // S_DGRAD: in[2] >= 0 is such a mask for the addend in[1]
                     // S_CONV_FWD with in[1] >= 0, S_WGRAD with in[2] >= 0: in[0] is the z of a folded BatchNorm apply
                     // and that slot its statistics tensor (FOp::fold_src)
+                    // S_BN_APPLY with in[3] >= 0: in[2] is the z of the projection shortcut's BatchNorm, in[3] its
+                    // statistics tensor (FOp::fold_skip)
   bool live = true;
 };
 
