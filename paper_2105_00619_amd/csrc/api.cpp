@@ -360,7 +360,7 @@ void run_op(const Ctx& c, const SOp& s) {
       break;
     case S_HEAD_BWD:
       launch_head_bwd(st, dt, (const float*)c.at(s.in[0]), (const float*)c.at(s.in[1]), c.w32(f.w_off), f.N, f.H * f.W, f.C,
-                      f.gap, f.feat_dim, f.classes, c.g32(f.w_off), c.g32(f.b_off), (float*)c.at(s.out[1]), c.at(s.out[0]));
+                      f.gap, f.feat_dim, f.classes, c.g32(f.w_off), c.g32(f.b_off), (float*)c.at(s.out[1]), c.at(s.out[0]), c.at(s.out[2]));
       break;
     case S_BN_BWD:
       if (s.variant == 1) {  // in[0] is the gradient of the max-pool behind the activation
@@ -372,7 +372,7 @@ void run_op(const Ctx& c, const SOp& s) {
       launch_bn_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? nullptr : c.at(s.in[3]),
                     s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]), (int64_t)f.N * f.P * f.Q, f.C,
                     f.relu, f.red_blocks, (float*)c.at(s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
-                    c.at(s.out[1]));
+                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0);
       break;
     case S_RELU_BWD:
       launch_relu_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), (int64_t)f.N * f.P * f.Q, f.K);
@@ -445,7 +445,8 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
       if (s.variant == 1) { *bytes = e * out_px * f.C * (2 * 1.25 + 1); break; }  // twice (z, pooled gradient), dz
       {  // the reduction reads dA, z and the ReLU source; the apply pass reads them again and writes dz (+ the skip gradient)
         const double src = s.in[3] < 0 ? 0.0 : s.variant == 2 ? 1.0 / 16 : 1.0;  // a bit mask is a sixteenth of a tensor
-        *bytes = e * out_px * f.C * (2 + src + 3 + src + (s.out[1] >= 0 ? 1 : 0));
+        const double da = s.per_image ? 0.0 : 1.0;  // (a gradient per image is next to nothing)
+        *bytes = e * out_px * f.C * (1 + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
       break;
     case S_POOL_FWD: *bytes = e * (in_px + out_px) * f.C; break;

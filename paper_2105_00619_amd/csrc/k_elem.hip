@@ -40,6 +40,7 @@ struct RedArgs {
   float* partial;      // [nblk][2][C]
   int64_t rows;
   int C, relu, nblk, rows_per_block;
+  FastDiv div_hw;      // GV: rows per image
 };
 
 // The block's row of partial sums from its threads' sums (TY rows of TX threads, V channels each): every one of the
@@ -66,7 +67,9 @@ __device__ __forceinline__ void col_combine(float* smem, const float (&s0)[V], c
   }
 }
 
-template <class T, int V, int MODE>
+// GV (the BatchNorm-backward modes): a is the gradient per image, [images][C], of a block output that only a global average
+// pool reads -- the same value at every pixel, so the tensor it would fill is neither written nor read
+template <class T, int V, int MODE, bool GV = false>
 __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
   extern __shared__ float smem[];  // [2][TY][TX*V]
   const int CG = g.C / V;
@@ -121,8 +124,8 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
     };
     // RT rows per trip while RT remain: their loads are all issued before the first value is used; the rows are still
     // added in the same order.  (Two tensors per row in the BatchNorm-backward modes: two rows per trip measured as
-    // well as four or a little better, with fewer registers.)
-    constexpr int RT = BWD ? 2 : 4;
+    // well as four or a little better, with fewer registers; with the gradient per image it is one tensor again.)
+    constexpr int RT = BWD && !GV ? 2 : 4;
     int64_t r = r0 + ty;
     for (; r + (RT - 1) * (int64_t)TY < r1; r += RT * (int64_t)TY) {
       float va[RT][V], vz[RT][V], vo[RT][V];
@@ -130,7 +133,8 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
 #pragma unroll
       for (int u = 0; u < RT; ++u) {
         const int64_t off = (r + (int64_t)u * TY) * g.C + c0;
-        load_f32_nt<T, V>(a + off, va[u]);
+        if (GV) load_f32<T, V>(a + (int64_t)g.div_hw.div((uint32_t)(r + (int64_t)u * TY)) * g.C + c0, va[u]);
+        else load_f32_nt<T, V>(a + off, va[u]);
         mb[u] = 0u;
         if (BWD) {
           load_f32_nt<T, V>(z + off, vz[u]);
@@ -145,7 +149,8 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
       const int64_t off = r * g.C + c0;
       float va[V], vz[V], vo[V];
       unsigned mb = 0u;
-      load_f32_nt<T, V>(a + off, va);
+      if (GV) load_f32<T, V>(a + (int64_t)g.div_hw.div((uint32_t)r) * g.C + c0, va);
+      else load_f32_nt<T, V>(a + off, va);
       if (BWD) {
         load_f32_nt<T, V>(z + off, vz);
         if (MODE == RED_BN_BWD_MASK) mb = mk[r * CG + cg];
@@ -157,7 +162,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
   col_combine<V>(smem, s0, s1, active, tx, ty, TX, TY, CG, g.C, g.partial);
 }
 
-template <class T, int MODE>
+template <class T, int MODE, bool GV>
 static void launch_colreduce_t(hipStream_t st, const RedArgs& g0) {
   RedArgs g = g0;
   const int vmax = 16 / (int)sizeof(T);
@@ -168,15 +173,15 @@ static void launch_colreduce_t(hipStream_t st, const RedArgs& g0) {
   g.rows_per_block = ceil_div(g.rows, g.nblk);
   dim3 grid(g.nblk, ceil_div(CG, TX));
   const size_t sm = (size_t)2 * TY * TX * V * sizeof(float);
-  if (V == vmax) OSEQ_LAUNCH((colreduce_kernel<T, 16 / sizeof(T), MODE>), grid, dim3(256), sm, st, g);
-  else OSEQ_LAUNCH((colreduce_kernel<T, 1, MODE>), grid, dim3(256), sm, st, g);
+  if (V == vmax) OSEQ_LAUNCH((colreduce_kernel<T, 16 / sizeof(T), MODE, GV>), grid, dim3(256), sm, st, g);
+  else if constexpr (!GV) OSEQ_LAUNCH((colreduce_kernel<T, 1, MODE>), grid, dim3(256), sm, st, g);  // (GV: whole groups only)
 }
 
-template <int MODE>
+template <int MODE, bool GV = false>
 static void launch_colreduce(hipStream_t st, int dt, const RedArgs& g) {
-  if (dt == DT_F32) launch_colreduce_t<float, MODE>(st, g);
-  else if (dt == DT_BF16) launch_colreduce_t<bf16_t, MODE>(st, g);
-  else launch_colreduce_t<f16_t, MODE>(st, g);
+  if (dt == DT_F32) launch_colreduce_t<float, MODE, GV>(st, g);
+  else if (dt == DT_BF16) launch_colreduce_t<bf16_t, MODE, GV>(st, g);
+  else launch_colreduce_t<f16_t, MODE, GV>(st, g);
 }
 
 // Finishing kernels: the block partials [nblk][2][C] of V neighbouring channels per block of 256 threads (V = 4 where C
@@ -380,6 +385,7 @@ __global__ void __launch_bounds__(256) bias_finalize_kernel(const float* __restr
 struct RowArgs {
   int64_t rows;
   int C, relu, rows_per_block;
+  FastDiv div_hw;  // GV: rows per image
 };
 
 // (the forward apply kernel, with one load and one store stream, measured faster as one group of V channels per
@@ -473,7 +479,8 @@ __global__ void __launch_bounds__(256) bn_apply_pool_kernel(const T* __restrict_
 // AOUT: the ReLU mask comes from the block output (a residual sum) instead of being rebuilt from z; DSKIP: the masked
 // gradient is also written out for the skip branch
 // MS: where the ReLU decisions come from: 0 redone from z, 1 the sign of the block output aout, 2 the bits of mask
-template <class T, int V, int MS, bool DSKIP>
+// GV: da is the gradient per image, [images][C] (as in colreduce_kernel)
+template <class T, int V, int MS, bool DSKIP, bool GV = false>
 __global__ void __launch_bounds__(256) bn_bwd_apply_kernel(const T* __restrict__ da, const T* __restrict__ z,
                                                            const T* __restrict__ aout, const uint8_t* __restrict__ mask,
                                                            const float* __restrict__ stats,
@@ -519,7 +526,7 @@ __global__ void __launch_bounds__(256) bn_bwd_apply_kernel(const T* __restrict__
 #pragma unroll
     for (int u = 0; u < RT; ++u) {
       const int64_t off = (r + (int64_t)u * TY) * g.C + c0;
-      load_f32<T, V>(da + off, va[u]);
+      load_f32<T, V>(GV ? da + (int64_t)g.div_hw.div((uint32_t)(r + (int64_t)u * TY)) * g.C + c0 : da + off, va[u]);
       load_f32<T, V>(z + off, vz[u]);
       if (AOUT) load_f32<T, V>(aout + off, vo[u]);
       mb[u] = MS == 2 ? mask[(r + (int64_t)u * TY) * CG + cg] : 0u;
@@ -537,7 +544,7 @@ __global__ void __launch_bounds__(256) bn_bwd_apply_kernel(const T* __restrict__
     const int64_t off = r * g.C + c0;
     float va[V], vz[V], vo[V], rz[V], rs[V];
     unsigned mb = 0u;
-    load_f32<T, V>(da + off, va);
+    load_f32<T, V>(GV ? da + (int64_t)g.div_hw.div((uint32_t)r) * g.C + c0 : da + off, va);
     load_f32<T, V>(z + off, vz);
     if (AOUT) load_f32<T, V>(aout + off, vo);
     if (MS == 2) mb = mask[r * CG + cg];
@@ -867,23 +874,27 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
 
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip) {
-  RedArgs g{}; g.a = da; g.z = z; g.aout = aout; g.mask = (const uint8_t*)mask; g.stats = stats; g.partial = ws; g.rows = rows;
+                   void* dz, void* dskip, int per_image) {
+  RedArgs g{}; g.div_hw = make_fastdiv(per_image ? (uint32_t)per_image : 1u); g.a = da; g.z = z; g.aout = aout; g.mask = (const uint8_t*)mask; g.stats = stats; g.partial = ws; g.rows = rows;
   g.C = C; g.relu = relu; g.nblk = nblk;
   // the same choice of the ReLU decisions' source as the apply kernel below makes
   const int vmax = dt == DT_F32 ? 4 : 8;
-  if (mask && C % vmax == 0) launch_colreduce<RED_BN_BWD_MASK>(st, dt, g);
+  if (per_image) {
+    if (mask) launch_colreduce<RED_BN_BWD_MASK, true>(st, dt, g);
+    else launch_colreduce<RED_BN_BWD, true>(st, dt, g);
+  } else if (mask && C % vmax == 0) launch_colreduce<RED_BN_BWD_MASK>(st, dt, g);
   else if (aout) launch_colreduce<RED_BN_BWD_AOUT>(st, dt, g);
   else launch_colreduce<RED_BN_BWD>(st, dt, g);
   float* coef = ws + (int64_t)nblk * 2 * C;
   FIN_LAUNCH(bn_bwd_finalize_kernel, 0, st, ws, nblk, C, (double)rows, dgamma,
                      dbeta, coef);
-#define APPLY(T, V, MS, DS)                                                                                             \
-  OSEQ_LAUNCH((bn_bwd_apply_kernel<T, V, MS, DS>), grid, dim3(256), 0, st, (const T*)da, (const T*)z,             \
+#define APPLY(T, V, MS, ...)                                                                                            \
+  OSEQ_LAUNCH((bn_bwd_apply_kernel<T, V, MS, __VA_ARGS__>), grid, dim3(256), 0, st, (const T*)da, (const T*)z,             \
                      (const T*)aout, (const uint8_t*)mask, stats, coef, (T*)dz, (T*)dskip, ra)
 #define CALL(T, V)                                                                                                      \
-  { RowArgs ra{}; dim3 grid; row_tiling(rows, C, V, ra, grid); ra.relu = relu;                                           \
-    if (mask && V > 1) { if (dskip) APPLY(T, V, 2, true); else APPLY(T, V, 2, false); }                                  \
+  { RowArgs ra{}; dim3 grid; row_tiling(rows, C, V, ra, grid); ra.relu = relu; ra.div_hw = g.div_hw;                     \
+    if (per_image && V > 1) { if (mask) APPLY(T, V, 2, false, true); else APPLY(T, V, 0, false, true); }                 \
+    else if (mask && V > 1) { if (dskip) APPLY(T, V, 2, true); else APPLY(T, V, 2, false); }                                  \
     else if (aout) { if (dskip) APPLY(T, V, 1, true); else APPLY(T, V, 1, false); }                                      \
     else { if (dskip) APPLY(T, V, 0, true); else APPLY(T, V, 0, false); } }
   DISPATCH_TV(dt, C, CALL);

@@ -248,6 +248,13 @@ __global__ void head_feat_bwd_kernel(const float* __restrict__ dfeat, T* __restr
   dx[i] = from_f32<T>(dfeat[n * C + c] / (float)HW);
 }
 
+// the gradient per image of a map that is only averaged: the value every one of its pixels has
+template <class T>
+__global__ void __launch_bounds__(256) gap_bwd_image_kernel(const float* __restrict__ dfeat, T* __restrict__ dx, int64_t n, int HW) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dx[i] = from_f32<T>(dfeat[i] / (float)HW);
+}
+
 // GAP backward for channel counts that are a multiple of V: block (chunk of rows, image n); a thread owns V channels,
 // reads their gradient once and writes it to every TY-th pixel of the block's rows (16-byte stores, no divisions
 // per element)
@@ -353,10 +360,18 @@ void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C
 }
 
 void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlogits, const float* w, int N, int HW, int C,
-                     int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx) {
+                     int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx, void* dx_image) {
   launch_head_gemm<HG_DW>(st, dlogits, feat, nullptr, dw, db, J, F, N, J, F, 1);
-  if (!dx) return;
+  if (!dx && !dx_image) return;
   launch_head_gemm<HG_DX>(st, dlogits, w, nullptr, dfeat, nullptr, N, F, J, J, F, 1);
+  if (dx_image) {
+    const int64_t n = (int64_t)N * C;
+    const dim3 grid(ceil_div(n, 256)), block(256);
+    if (dt == DT_F32) OSEQ_LAUNCH(gap_bwd_image_kernel<float>, grid, block, 0, st, dfeat, (float*)dx_image, n, HW);
+    else if (dt == DT_BF16) OSEQ_LAUNCH(gap_bwd_image_kernel<bf16_t>, grid, block, 0, st, dfeat, (bf16_t*)dx_image, n, HW);
+    else OSEQ_LAUNCH(gap_bwd_image_kernel<f16_t>, grid, block, 0, st, dfeat, (f16_t*)dx_image, n, HW);
+  }
+  if (!dx) return;
   if (dt == DT_F32) launch_feat_bwd<float>(st, dfeat, dx, N, HW, C, gap);
   else if (dt == DT_BF16) launch_feat_bwd<bf16_t>(st, dfeat, dx, N, HW, C, gap);
   else launch_feat_bwd<f16_t>(st, dfeat, dx, N, HW, C, gap);

@@ -47,11 +47,13 @@ void launch_bn_apply(hipStream_t st, int dt, const void* z, const float* stats, 
 // and y [N][H/2][W/2][C]
 void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* stats, void* a, void* y, int N, int H, int W,
                           int C, int relu);
+// per_image (0: no): da is the gradient per image, [rows / per_image][C], of a tensor that only a global average pool reads;
+// then C is a multiple of 16 / element size, aout and dskip are null, rows < 2^32 and rows * per_image < 2^48
 // ReLU decisions: from mask (bits as launch_bn_apply writes them, applied whatever relu says) if given, else from the
 // sign of aout if given, else redone from z when relu is set
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip);
+                   void* dz, void* dskip, int per_image);
 // the same where dy is the gradient of the 2x2 max-pool that follows the activation ([N][H/2][W/2][C]; H, W even): the
 // pool's own backward pass is not run
 void launch_bn_bwd_pool(hipStream_t st, int dt, const void* dy, const void* z, const float* stats, int N, int H, int W, int C,
@@ -69,8 +71,9 @@ void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, in
                         const float* b, float* feat, float* logits, float* ws);
 // ws: workspace of the forward pass, where its sums are split over ranges (null if that needs none)
 int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J);
+// dx: gradient of the head's input, or null; dx_image (GAP): the same per image, [N][C] in the storage type, or null
 void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlogits, const float* w, int N, int HW, int C,
-                     int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx);
+                     int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx, void* dx_image);
 
 void launch_conv_fwd_direct(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
                             const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());

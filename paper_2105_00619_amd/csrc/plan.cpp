@@ -247,10 +247,13 @@ struct Scheduler {
   std::vector<int> gmask;        // [LTensor] -> Inst id of a ReLU bit mask that grad[t] still has to be multiplied by
                                  //              (the gradient through a skip connection is not written out: its
                                  //              reader applies the mask to the block output's gradient itself), or -1
+  std::vector<char> per_image;   // [LTensor] -> grad[t] (or image_grad[t]) holds one value per image and channel
+  std::vector<int> image_grad;   // [LTensor] -> Inst id of the gradient per image of the global average pool's input, or -1
   explicit Scheduler(Plan& pl)
       : p(pl), cur(pl.tensors.size(), -1), grad(pl.tensors.size(), -1), stat_ws(pl.tensors.size(), -1),
         bn_apply_of(pl.tensors.size(), -1), rebuilt(pl.tensors.size(), 0), readers(pl.tensors.size(), 0),
-        via_pool(pl.tensors.size(), -1), gmask(pl.tensors.size(), -1) {
+        via_pool(pl.tensors.size(), -1), gmask(pl.tensors.size(), -1), per_image(pl.tensors.size(), 0),
+        image_grad(pl.tensors.size(), -1) {
     for (size_t fi = 0; fi < pl.fops.size(); ++fi) {
       const FOp& f = pl.fops[fi];
       if (f.kind == F_BN_APPLY) bn_apply_of[f.out] = (int)fi;
@@ -374,6 +377,24 @@ struct Scheduler {
     return false;
   }
 
+  // The projection shortcut's BatchNorm apply whose output operation fi adds, or -1.
+  int projection_of(int fi) const {
+    const FOp& f = p.fops[fi];
+    if (f.skip < 0) return -1;
+    const int b = bn_apply_of[f.skip];
+    return b >= 0 && p.fops[b].unit == f.unit ? b : -1;
+  }
+
+  // May the BatchNorm backward of operation fi, whose output only the global average pool `head` reads, take the gradient
+  // per image?  Its kernels do in whole groups of 16 / esize channels; a skip connection's gradient must not need a tensor
+  // written from it.
+  bool per_image_ok(int fi, const FOp& head) const {
+    const FOp& f = p.fops[fi];
+    const double rows = (double)f.N * f.P * f.Q;
+    if (f.C % (16 / p.esize) != 0 || rows >= 4294967296.0 || rows * head.H * head.W >= 281474976710656.0) return false;
+    return f.skip < 0 || masked_skip_grad_ok(fi);
+  }
+
   bool emit_fop_backward(int fi, int seg) {
     const FOp& f = p.fops[fi];
     switch (f.kind) {
@@ -381,18 +402,32 @@ struct Scheduler {
       case F_HEAD: {
         SOp& s = push(S_HEAD_BWD, fi, PH_BWD, seg);
         s.in[0] = cur[f.aux[0]]; s.in[1] = cur[f.aux[2]];
-        if (p.tensors[f.x].needs_grad) { s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; }
+        if (p.tensors[f.x].needs_grad) {
+          const int ap = bn_apply_of[f.x];
+          bool whole = true;  // the gradient as a whole tensor
+          if (f.gap && ap >= 0 && readers[f.x] == 1 && per_image_ok(ap, f)) {
+            s.out[2] = image_grad[f.x] = new_inst(-1, (uint64_t)f.N * f.C * p.esize, false);
+            // an identity shortcut's data gradient adds it as a tensor
+            const int skip = p.fops[ap].skip;
+            whole = skip >= 0 && projection_of(ap) < 0 && p.tensors[skip].needs_grad;
+          }
+          if (whole) { s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; }
+        }
         s.out[1] = new_inst(-1, (uint64_t)f.N * f.feat_dim * 4, false);
         return true;
       }
       case F_BN_APPLY: {
         int gin = grad[f.out], variant = 0;
+        bool image = per_image[f.out] != 0;
+        const int whole = gin;  // (the skip connection's reader of an identity shortcut)
+        if (image_grad[f.out] >= 0) { gin = image_grad[f.out]; image = true; }
         if (gin < 0 && via_pool[f.out] >= 0) { gin = via_pool[f.out]; variant = 1; }  // through the pool behind it
         if (gin < 0) { p.error = "internal: BN output has no gradient"; return false; }
         if (f.skip >= 0 && !f.relu) { p.error = "skip connection without ReLU is not supported"; return false; }
         const int gin_mask = gmask[f.out];  // the incoming gradient still wants a mask (projection shortcut's BatchNorm)
         SOp& s = push(S_BN_BWD, fi, PH_BWD, seg);
         s.variant = variant;
+        s.per_image = image;
         s.in[0] = gin; s.in[1] = cur[f.x]; s.in[2] = cur[f.stats];
         s.in[3] = (f.skip >= 0) ? cur[f.out] : -1;
         if (gin_mask >= 0) {
@@ -404,7 +439,10 @@ struct Scheduler {
         s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
         if (f.skip >= 0 && p.tensors[f.skip].needs_grad) {
           if (grad[f.skip] >= 0) { p.error = "internal: skip gradient must be the first contribution"; return false; }
-          if (masked_skip_grad_ok(fi)) { grad[f.skip] = gin; gmask[f.skip] = cur[f.mask]; }  // nothing written
+          if (masked_skip_grad_ok(fi)) {  // nothing written
+            const bool vec = image && projection_of(fi) >= 0;
+            grad[f.skip] = vec ? gin : whole; per_image[f.skip] = vec; gmask[f.skip] = cur[f.mask];
+          }
           else { s.out[1] = grad_inst(f.skip); grad[f.skip] = s.out[1]; gmask[f.skip] = -1; }
         }
         s.out[2] = new_inst(-1, ((uint64_t)f.red_blocks * 2 + 2) * f.C * 4, false);
@@ -480,7 +518,7 @@ int launches_of(const SOp& op, const FOp& f) {
   switch (op.kind) {
     case S_BN_STATS: return f.stat_blocks > 0 ? (f.stat_fold > 0 ? 2 : 1) : 2;
     case S_HEAD_FWD: return f.head_ws > 0 ? 5 : 4;
-    case S_HEAD_BWD: return op.out[0] >= 0 ? 4 : 2;
+    case S_HEAD_BWD: return op.out[0] >= 0 || op.out[2] >= 0 ? 4 : 2;
     case S_BN_BWD: return 3;
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;

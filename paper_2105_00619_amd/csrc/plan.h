@@ -92,6 +92,8 @@ struct SOp {
                     // and that slot its statistics tensor (FOp::fold_src)
                     // S_BN_APPLY with in[3] >= 0: in[2] is the z of the projection shortcut's BatchNorm, in[3] its
                     // statistics tensor (FOp::fold_skip)
+  bool per_image = false;  // S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
+                           // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
   bool live = true;
 };
 
