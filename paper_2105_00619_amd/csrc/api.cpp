@@ -94,7 +94,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_splits = conv_mfma_dgrad_splits(dt, g);
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g);
-        if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g);
+        if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
         if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
       }
     for (FOp& f : p.fops)

@@ -1019,8 +1019,13 @@ static int igemm_splits(int dt, int64_t M, int Ng, int Kg) {
   if (s > 32) s = 32;
   return (int)(s < 1 ? 1 : s);
 }
+static bool fwd_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride); }
+static bool dgrad_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride); }
+// (a layer that takes the weights-stationary 3x3 kernel never splits its depth, nor would the kernel that takes it when
+// something is done to its result: it has at least 1024 tiles of 128 pixels)
 int conv_mfma_fwd_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
+  if (fwd_ws3x3(dt, g)) return 1;
   if (conv_pointwise_fwd_ok(dt, g)) return 1;
   if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, pa)) return v.splits;
   return igemm_splits(dt, (int64_t)g.N * g.P * g.Q, g.K, g.R * g.S * g.C);
@@ -1032,6 +1037,7 @@ static bool dgrad_by_classes(const ConvGeom& g) {
 }
 int conv_mfma_dgrad_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
+  if (dgrad_ws3x3(dt, g)) return 1;
   if (conv_pointwise_dgrad_ok(dt, g)) return 1;
   if (patch_pick(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
   if (dgrad_by_classes(g)) return 1;
@@ -1049,10 +1055,11 @@ bool conv_mfma_dgrad_ok(int dt, const ConvGeom& g) {
 
 // Row blocks over which the forward path produces the per-channel sums for BatchNorm: the blocks of the convolution
 // kernel, or of the kernel that adds the depth ranges when the depth is split.  From the layer shape only.
-int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g) {
+int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias) {
   PatchShape pv; PatchArgs pa{};
   const int64_t M = (int64_t)g.N * g.P * g.Q;
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_stat_blocks(g);
+  if (!bias && fwd_ws3x3(dt, g)) return conv_ws3x3_stat_blocks(g);
   if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
     return pv.splits > 1 ? ceil_div(M, split_epi_rows(M, g.K)) : (pa.NT + pv.subt - 1) / pv.subt;
   if (igemm_splits(dt, M, g.K, g.R * g.S * g.C) > 1) return ceil_div(M, split_epi_rows(M, g.K));
@@ -1076,6 +1083,10 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
     launch_conv_fwd_pointwise(st, dt, x, w, bias, out, stat_partial, g, relu, fold, ev);
     return;
   }
+  if (!ev.affine && !bias && !relu && fwd_ws3x3(dt, g)) {
+    launch_conv_fwd_ws3x3(st, dt, x, w, out, stat_partial, g, fold);
+    return;
+  }
   const bool eval = ev.affine != nullptr;
   if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.H; pa.srcW = g.W; pa.srcC = g.C; pa.dstH = g.P; pa.dstW = g.Q; pa.Ng = g.K;
@@ -1097,6 +1108,10 @@ void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* 
   const uint8_t* amask = addend ? (const uint8_t*)addend_mask : nullptr;
   if (conv_pointwise_dgrad_ok(dt, g)) {
     launch_conv_dgrad_pointwise(st, dt, dz, wt, addend, amask, dx, g);
+    return;
+  }
+  if (!addend && dgrad_ws3x3(dt, g)) {
+    launch_conv_dgrad_ws3x3(st, dt, dz, wt, dx, g);
     return;
   }
   if (patch_pick(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {

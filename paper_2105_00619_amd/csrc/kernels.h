@@ -98,7 +98,7 @@ bool conv_mfma_dgrad_ok(int dt, const ConvGeom& g);
 int conv_mfma_fwd_splits(int dt, const ConvGeom& g);
 int conv_mfma_dgrad_splits(int dt, const ConvGeom& g);
 // partial: fp32 workspace of splits * (output elements) floats when splits > 1, else unused
-int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g);
+int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias);  // bias: the layer adds one in front of its BatchNorm
 // fold (null: none): x is not the input activation but the z of the BatchNorm + ReLU in front of the layer, and fold
 // that BatchNorm's [4][C_in] statistics tensor (mean, rstd, scale, shift): the kernel turns z into the activation --
 // the very values the apply kernel would have stored -- while it stages its operand.  Only where conv_fold_fwd_ok /
@@ -121,6 +121,13 @@ void launch_conv_fwd_pointwise(hipStream_t st, int dt, const void* x, const void
                                float* stat_partial, const ConvGeom& g, int relu, const float* fold, const ConvEval& ev);
 void launch_conv_dgrad_pointwise(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
                                  const uint8_t* addend_mask, void* dx, const ConvGeom& g);
+// 3x3 stride-1 layers of 64 input channels and many pixels with the weights stationary (k_conv_ws3x3.hip); used by the MFMA
+// launchers above where nothing is added to the result
+bool conv_ws3x3_ok(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride);
+int conv_ws3x3_stat_blocks(const ConvGeom& g);
+void launch_conv_fwd_ws3x3(hipStream_t st, int dt, const void* x, const void* w, void* out, float* stat_partial, const ConvGeom& g,
+                           const float* fold);
+void launch_conv_dgrad_ws3x3(hipStream_t st, int dt, const void* dz, const void* wt, void* dx, const ConvGeom& g);
 // 3x3 stride-1 weight gradient with all nine taps per block (k_conv_wgrad3x3.hip); used by the MFMA launcher below
 bool conv_wgrad3x3_ok(int dt, const ConvGeom& g);
 int conv_wgrad3x3_splits(int dt, const ConvGeom& g);

@@ -109,6 +109,8 @@ LAYER_NETS = {
     # and the last one is only partly inside the batch
     "whole_image_tiles_8x8_odd": (256, 8, 193, [W.conv(256, 256), W.conv(256, 256), W.gap_linear_ce(256, 10)]),
     "whole_image_tiles_4x4_odd": (512, 4, 67, [W.conv(512, 512), W.conv(512, 512), W.gap_linear_ce(512, 10)]),
+    # 64 channels, 131 072 pixels and more: the 3x3 kernel that keeps its weights, forward on a folded BatchNorm
+    "stationary_64_at24": (64, 24, 229, [W.basic_block(64, 64), W.gap_linear_ce(64, 10)]),
     "pointwise_bottlenecks": (64, 16, 64, [W.conv(64, 64, ksize=1), W.bottleneck(64, 256, 1), W.bottleneck(256, 512, 2),
                                            W.gap_linear_ce(512, 10)]),
 }
@@ -257,6 +259,38 @@ def test_stem_kernels_at_tile_edges(precision, cin, cout, stride, pad, h, w, b, 
     assert not r["skipped"]
     loss, g = oracle_step(units, p, x, y)
     errs = plain_errors(units, h, w, r["grads"], g)
+    assert max(errs.values()) <= TOL[precision], errs
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+
+
+@pytest.mark.parametrize("precision,cout,pad,h,w,b", [
+    (W.BF16, 64, 1, 32, 32, 128), (W.FP16, 128, 1, 37, 45, 79), (W.BF16, 64, 0, 12, 11, 2800), (W.FP16, 192, 1, 8, 8, 2051),
+    (W.BF16, 64, 1, 5, 3, 8741), (W.FP16, 64, 1, 300, 70, 7), (W.BF16, 128, 1, 1, 400, 331), (W.FP16, 64, 1, 16, 17, 515)])
+def test_weights_stationary_3x3_at_tile_edges(precision, cout, pad, h, w, b):
+    """3x3 layers with 64 input channels and 131 072 pixels or more: tiles of whole rows and of parts of rows, several images a
+    tile with some missing in the last, one to three channel groups, with and without a border, images larger than a tile either
+    way.  The first layer is for the forward pass with the sums of its BatchNorm, the second for the one whose bias beside the
+    BatchNorm keeps it off that kernel, the third's data gradient for the weight gradients in front of it.  No ReLU, so against
+    plain float64 with the bars of the single-layer tests (three roundings of 2^-9 or less in a row)."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(64, 64, 3, pad=pad, bn=True, relu=False, bias=False),
+             W.conv(64, cout, 3, pad=pad, bn=True, relu=False, bias=cout != 64),
+             W.conv(cout, 64, 3, pad=pad, bn=True, relu=False, bias=False),
+             W.conv(64, 8, 1, bn=False, relu=False, bias=True), W.flatten_linear_ce(8, 10)]
+    rnd = O.round_to_bf16 if precision == W.BF16 else O.round_to_fp16
+    p = W.make_params(units, h, w, 13, perturb=True)
+    slices = W.param_slices(units, h, w)
+    for nm, sl in slices.items():
+        if nm.endswith(".w") and ".lin." not in nm:
+            p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, h, w, 64, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    loss, g = oracle_step(units, p, x, y)
+    # a constant in front of a BatchNorm has no gradient: the bias, and away from the border the beta of the layer before (the
+    # BatchNorm behind the next convolution takes it out); what is left there is compared with the whole gradient's RMS
+    errs = plain_errors(units, h, w, r["grads"], g, zero_names=("u1.b", "u0.beta", "u1.beta"))
     assert max(errs.values()) <= TOL[precision], errs
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
 
