@@ -154,20 +154,49 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   const int vec = tid & 3, row0 = tid >> 2;  // this thread's chunk column and first row
 
-  // pixel coordinates of this thread's A rows
+  // This thread's A rows: element offset of the pixel that tap (0, 0) reads and a bit per tap that stays inside the image.
+  // Every tap is a fixed distance from there, the same for all pixels (in a strided data gradient also: the taps that meet a
+  // pixel have its parity), so a depth tile costs a row one select and one add.  (With the coordinates, three 64-bit
+  // products per row and two divisions per depth tile were a serial chain in front of every tile's loads.  3x3 stride-2 layers
+  // in fp16, us: forward with 256 x 2 blocks of 72 depth tiles 72 -> 60, 64 x 4 of 144 95 -> 71, data gradient by classes of
+  // 32 x 2 blocks, the longest of 64 tiles, 53 -> 36; fp32, 2048 blocks: 368 -> 338 and 462 -> 395.)
   const int cz = a.cls ? blockIdx.z : 0;              // parity class
   const int cph = cz >> 1, cpw = cz & 1;
   const int ctaps = a.cls ? a.taps[cz] : 0;
-  int pn[A_CH], pa[A_CH], pb[A_CH];
+  int64_t aoff[A_CH];
+  unsigned inside[A_CH];
 #pragma unroll
   for (int i = 0; i < A_CH; ++i) {
     const int m = m0 + row0 + i * 64;
     const int mm = m < a.M ? m : 0;
-    pb[i] = mm % a.dstW;
+    int pb = mm % a.dstW;
     const int t = mm / a.dstW;
-    pa[i] = t % a.dstH;
-    pn[i] = m < a.M ? t / a.dstH : -1;  // -1: row beyond the last pixel
-    if (a.cls) { pa[i] = 2 * pa[i] + cph; pb[i] = 2 * pb[i] + cpw; }
+    int pa = t % a.dstH;
+    const int pn = t / a.dstH;
+    if (a.cls) { pa = 2 * pa + cph; pb = 2 * pb + cpw; }
+    int y0, x0;
+    unsigned rv = 0u, cv = 0u;  // bit r (s): filter row r (column s) stays inside
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {  // 1x1 and 3x3 filters
+      int y, x;
+      bool yok = k < a.R, xok = k < S_;
+      if (MODE != IG_DGRAD) {
+        y = pa * stride + k - pad; x = pb * stride + k - pad;
+      } else {
+        const int ty = pa + pad - k, tx = pb + pad - k;
+        if (stride == 2) { yok = yok && !(ty & 1); xok = xok && !(tx & 1); y = ty >> 1; x = tx >> 1; } else { y = ty; x = tx; }
+      }
+      rv |= yok && y >= 0 && y < srcH ? 1u << k : 0u;
+      cv |= xok && x >= 0 && x < srcW ? 1u << k : 0u;
+    }
+    if (MODE != IG_DGRAD) { y0 = pa * stride - pad; x0 = pb * stride - pad; }
+    else if (stride == 2) { y0 = (pa + pad) >> 1; x0 = (pb + pad) >> 1; }
+    else { y0 = pa + pad; x0 = pb + pad; }
+    aoff[i] = (((int64_t)pn * srcH + y0) * srcW + x0) * srcC + vec * EV;
+    unsigned in = 0u;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) in |= (rv >> r) & 1u ? cv << (r * S_) : 0u;
+    inside[i] = m < a.M ? in : 0u;  // nothing of a row beyond the last pixel
   }
   const T* brow[B_CH];
 #pragma unroll
@@ -177,34 +206,29 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   // applied when the chunk is written to LDS: straight-line loads let the hardware keep several generations in flight.
   Chunk ra[2][A_CH], rb[2][B_CH];
   unsigned okm[2] = {0u, 0u};  // per generation: bit i set if A chunk i is inside the image
-  auto gload = [&, srcH, srcW, srcC, S_, stride, pad](auto P, int kt) {
+  const int kt0 = SPLIT ? blockIdx.z * a.kt_per_split : 0;
+  int tapi = kt0 * BK / srcC, c0 = kt0 * BK - tapi * srcC;  // next depth tile to load: entry of the tap list, first channel
+  auto gload = [&, srcW, srcC, S_, stride](auto P) {
     constexpr int p = decltype(P)::value;
-    const int kk0 = kt * BK;
-    const int tapi = kk0 / srcC, c0 = kk0 - tapi * srcC;
     const int tap = a.cls ? (ctaps >> (8 * tapi)) & 0xff : tapi;  // filter tap r*S + s of this depth tile
-    const int r = tap / S_, s = tap - r * S_;
+    const int r = S_ == 3 ? (tap * 11) >> 5 : tap;                // tap / S, S being 3 or 1
+    const int s = tap - r * S_;
     const int kkw = tap * srcC + c0;                              // its depth offset in the weight rows
+    const int sh = MODE == IG_DGRAD && stride == 2 ? 1 : 0;
+    const int d = ((r >> sh) * srcW + (s >> sh)) * srcC;
+    const int toff = (MODE == IG_DGRAD ? -d : d) + c0;
     unsigned m = 0u;
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
-      int y, x;
-      bool ok = pn[i] >= 0;
-      if (MODE != IG_DGRAD) {
-        y = pa[i] * stride + r - pad;
-        x = pb[i] * stride + s - pad;
-      } else {
-        const int ty = pa[i] + pad - r, tx = pb[i] + pad - s;
-        ok = ok && ty >= 0 && tx >= 0;
-        if (stride == 2) { ok = ok && !((ty | tx) & 1); y = ty >> 1; x = tx >> 1; } else { y = ty; x = tx; }
-      }
-      ok = ok && y >= 0 && y < srcH && x >= 0 && x < srcW;
-      const int yc = ok ? y : 0, xc = ok ? x : 0, nc = ok ? pn[i] : 0;
-      ra[p][i] = *reinterpret_cast<const Chunk*>(src + (((int64_t)nc * srcH + yc) * srcW + xc) * srcC + c0 + vec * EV);
+      const bool ok = (inside[i] >> tap) & 1u;
+      ra[p][i] = *reinterpret_cast<const Chunk*>(src + (ok ? aoff[i] + toff : (int64_t)(vec * EV)));
       m |= ok ? (1u << i) : 0u;
     }
     okm[p] = m;
 #pragma unroll
     for (int i = 0; i < B_CH; ++i) rb[p][i] = *reinterpret_cast<const Chunk*>(brow[i] + kkw);
+    c0 += BK;
+    if (c0 >= srcC) { c0 = 0; ++tapi; }
   };
   auto sstore = [&](auto P, int stage) {  // register generation p -> LDS stage
     constexpr int p = decltype(P)::value;
@@ -224,14 +248,13 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  const int kt0 = SPLIT ? blockIdx.z * a.kt_per_split : 0;
   const int nkt = (a.cls ? a.ntaps[cz] * srcC : a.Kg) / BK;  // depth tiles of this GEMM
   const int kt1 = SPLIT ? (kt0 + a.kt_per_split < nkt ? kt0 + a.kt_per_split : nkt) : nkt;
   const int n = kt1 > kt0 ? kt1 - kt0 : 0;
   // prologue: tiles 0 and 1 into LDS stages 0 and 1, tile 2 on its way in generation 0
-  if (n > 0) { gload(IC<0>{}, kt0); sstore(IC<0>{}, 0); }
-  if (n > 1) { gload(IC<1>{}, kt0 + 1); sstore(IC<1>{}, 1); }
-  if (n > 2) gload(IC<0>{}, kt0 + 2);
+  if (n > 0) { gload(IC<0>{}); sstore(IC<0>{}, 0); }
+  if (n > 1) { gload(IC<1>{}); sstore(IC<1>{}, 1); }
+  if (n > 2) gload(IC<0>{});
   __syncthreads();
   const int afrag = (wm * (BM / 2) + l32) * PITCH + Frag<T>::lane_off(g);
   const int bfrag = (BM + wn * (BN / 2) + l32) * PITCH + Frag<T>::lane_off(g);
@@ -250,7 +273,7 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
     constexpr bool TAIL = decltype(TAILC)::value != 0;
     const T* nxt = lds + (stage == 2 ? 0 : stage + 1) * STAGE;
     const bool has_next = TAIL ? j + 1 < n : true;
-    if (!TAIL || j + 3 < n) gload(IC<1 - p>{}, kt0 + j + 3);
+    if (!TAIL || j + 3 < n) gload(IC<1 - p>{});
 #pragma unroll
     for (int st = 0; st < Frag<T>::HALF_STEPS; ++st)
 #pragma unroll

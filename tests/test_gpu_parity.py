@@ -263,6 +263,32 @@ def test_stem_kernels_at_tile_edges(precision, cin, cout, stride, pad, h, w, b, 
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
 
 
+@pytest.mark.parametrize("precision", [W.FP32, W.FP16])
+@pytest.mark.parametrize("cin,cout,ksize,stride,pad,h,w,b", [
+    (64, 128, 3, 2, 0, 9, 11, 5), (96, 64, 3, 2, 0, 8, 12, 3), (64, 64, 3, 2, 1, 7, 10, 4), (128, 192, 3, 2, 1, 2, 2, 7),
+    (64, 64, 3, 1, 0, 5, 4, 9), (192, 64, 3, 1, 1, 1, 3, 33), (64, 128, 1, 2, 0, 7, 5, 3), (576, 64, 3, 2, 1, 3, 4, 5)])
+def test_gathered_convolutions_at_the_border(precision, cin, cout, ksize, stride, pad, h, w, b):
+    """The implicit GEMM's tap bits and distances: forward, weight and data gradient of strided and small 3x3 layers, with and
+    without a border, odd and even images (a data gradient by parity classes and by masked taps), depths that a split cuts in
+    the middle of a tap.  No ReLU; plain float64 and the bars of the single-layer tests."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(8, cin, 1, bn=False, relu=False, bias=True),
+             W.conv(cin, cout, ksize, stride, pad=pad, bn=False, relu=False, bias=True), W.flatten_linear_ce(cout, 10)]
+    rnd = (lambda v: v) if precision == W.FP32 else O.round_to_fp16
+    p = W.make_params(units, h, w, 13, perturb=True)
+    for nm, sl in W.param_slices(units, h, w).items():
+        if nm.endswith(".w") and ".lin." not in nm:
+            p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, h, w, 8, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    loss, g = oracle_step(units, p, x, y)
+    errs = plain_errors(units, h, w, r["grads"], g)
+    assert max(errs.values()) <= TOL[precision], errs
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+
+
 @pytest.mark.parametrize("precision,cout,pad,h,w,b", [
     (W.BF16, 64, 1, 32, 32, 128), (W.FP16, 128, 1, 37, 45, 79), (W.BF16, 64, 0, 12, 11, 2800), (W.FP16, 192, 1, 8, 8, 2051),
     (W.BF16, 64, 1, 5, 3, 8741), (W.FP16, 64, 1, 300, 70, 7), (W.BF16, 128, 1, 1, 400, 331), (W.FP16, 64, 1, 16, 17, 515)])
