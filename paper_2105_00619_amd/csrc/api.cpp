@@ -193,7 +193,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
   for (size_t i = 0; i < p.fops.size(); ++i)
     if (p.fops[i].kind == F_BN_STATS) {
       const FOp& f = p.fops[i];
-      h->eval_jobs.push_back(EvalJob{f.gamma_off, f.beta_off, p.fops[i - 1].has_bias ? p.fops[i - 1].b_off : -1, f.rs_off, f.C, 0});
+      h->eval_jobs.push_back(EvalJob{f.gamma_off, f.beta_off, p.fops[i - 1].has_bias ? p.fops[i - 1].b_off : -1, f.rs_off, f.C});
     }
   for (const FOp& f : p.fops)
     if (f.kind == F_CONV && f.dgrad_algo == ALGO_MFMA && p.tensors[f.x].needs_grad)

@@ -16,7 +16,7 @@ struct ConvGeom { int N, H, W, C, K, R, S, stride, pad, P, Q; };
 struct ConvEval { const float* affine = nullptr; const void* skip = nullptr; };
 
 // scale and shift of every BatchNorm of the network from the running statistics, all in one launch per 96 of them
-struct EvalJob { int64_t gamma_off, beta_off, bias_off, rs_off; int C, first_block; };  // bias_off: the convolution's, or -1
+struct EvalJob { int64_t gamma_off, beta_off, bias_off, rs_off; int C; };  // bias_off: the convolution's, or -1
 struct EvalBatch { static constexpr int MAX_JOBS = 96; EvalJob job[MAX_JOBS]; int n; };
 // w: master weights; running: [..](mean[C], var[C]) at rs_off; affine: [..](scale[C], shift[C]) at rs_off
 void launch_bn_eval_affine(hipStream_t st, const float* w, const float* running, float eps, float* affine, const EvalJob* jobs,
