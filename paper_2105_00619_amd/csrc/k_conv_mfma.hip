@@ -1285,8 +1285,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN, g = lane >> 5, l32 = lane & 31;
-  // Block coordinates: (output-channel tile, tap and input-channel tile, pixel range).  xcd_group (1x1 layers): the
-  // tiles of one pixel range all read the same rows of x and dz; workgroups go to the 8 XCDs round-robin by their linear
+  // Block coordinates: (output-channel tile, tap and input-channel tile, pixel range).  xcd_group: the tiles
+  // (and taps) of one pixel range all read the same rows of x and dz; workgroups go to the 8 XCDs round-robin by their linear
   // index and every XCD has an L2 of its own, so the tiles of a range are renumbered onto one XCD, which then fetches
   // those rows once.  The grid's z extent is the number of ranges rounded up to a multiple of 8.
   int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
@@ -1596,7 +1596,10 @@ static void launch_wgrad_t(hipStream_t st, const void* x, const void* dz, float*
   a.divPQ = make_fastdiv((uint32_t)(g.P * g.Q));
   a.fold = fold;
   a.ranges = splits;
-  a.xcd_group = g.R * g.S == 1 && splits >= 8;
+  // 3x3: where the ranges spread evenly over the XCDs, in 16 bits (nine taps read every row of dz; 128 -> 128 channels,
+  // stride 2, 131 072 pixels in fp16 109 -> 96 us, 64 -> 128 at 65 536 in bf16 36 -> 31; fp32 waits for its matrix
+  // instructions instead: 504 -> 537)
+  a.xcd_group = g.R * g.S == 1 ? splits >= 8 : sizeof(T) == 2 && splits % 8 == 0;
   const int gz = a.xcd_group ? (splits + 7) / 8 * 8 : splits;
   if constexpr (sizeof(T) == 2) {
     if (wgrad_large_ok(DT_BF16, g)) {
