@@ -201,25 +201,55 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     const int ri = t2 % a.tiles_r, ii = t2 / a.tiles_r;
     const int nb = ii * TI, yb = ri * TR, xb = ci * TC;
     unsigned xm = 0u, dm = 0u;
+    if constexpr (!FOLD) {
+      // Pixels are counted from the sub-tile's first image (one uniform base per tensor): fewer than 2^24, so that every product
+      // is a full-rate 24-bit one.  A position outside reads that image's first pixel.
+      // us, 64-bit products -> this: 64 -> 64 channels at 65 536 pixels in bf16 47 -> 37, at 1 048 576 in fp32 833 -> 794;
+      // with the BatchNorm folded in, whose registers leave the loads less room, 78 -> 86 at 262 144: that keeps the former.
+      const T* xt = x + (int64_t)nb * H * W * C + c0;
+      const T* dt = dz + (int64_t)nb * P * Q * K + k0;
+      const uint32_t c24 = (uint32_t)C & 0xffffffu, k24 = (uint32_t)K & 0xffffffu;
 #pragma unroll
-    for (int sl = 0; sl < XSLOTS; ++sl) {
-      const int info = xinfo[sl];
-      const int n = nb + (info >> 20), y = yb - pad + ((info >> 10) & 1023), xx = xb - pad + (info & 1023);
-      const bool ok = info >= 0 && n < N && y >= 0 && y < H && xx >= 0 && xx < W;
-      const int v = (sl * NTH + tid) % XCP;
-      const int64_t off = ok ? (((int64_t)n * H + y) * W + xx) * C : 0;
-      xr[sl] = *reinterpret_cast<const Chunk*>(x + off + c0 + v * EV);
-      xm |= ok ? (1u << sl) : 0u;
-    }
+      for (int sl = 0; sl < XSLOTS; ++sl) {
+        const int info = xinfo[sl], ti = info >> 20;
+        const int y = yb - pad + ((info >> 10) & 1023), xx = xb - pad + (info & 1023);
+        const bool ok = info >= 0 && nb + ti < N && (unsigned)y < (unsigned)H && (unsigned)xx < (unsigned)W;
+        const uint32_t pix = ok ? (uint32_t)(__mul24(__mul24(ti, H) + y, W) + xx) : 0u;
+        const int v = (sl * NTH + tid) % XCP;
+        xr[sl] = *reinterpret_cast<const Chunk*>(xt + (uint64_t)(pix & 0xffffffu) * (uint64_t)c24 + v * EV);
+        xm |= ok ? (1u << sl) : 0u;
+      }
 #pragma unroll
-    for (int sl = 0; sl < DSLOTS; ++sl) {
-      const int info = dinfo[sl];
-      const int n = nb + (info >> 20), p = yb + ((info >> 10) & 1023), q = xb + (info & 1023);
-      const bool ok = info >= 0 && n < N && p < P && q < Q;
-      const int v = (sl * NTH + tid) % DCP;
-      const int64_t off = ok ? (((int64_t)n * P + p) * Q + q) * K : 0;
-      dr[sl] = *reinterpret_cast<const Chunk*>(dz + off + k0 + v * EV);
-      dm |= ok ? (1u << sl) : 0u;
+      for (int sl = 0; sl < DSLOTS; ++sl) {
+        const int info = dinfo[sl], ti = info >> 20;
+        const int p = yb + ((info >> 10) & 1023), q = xb + (info & 1023);
+        const bool ok = info >= 0 && nb + ti < N && p < P && q < Q;
+        const uint32_t pix = ok ? (uint32_t)(__mul24(__mul24(ti, P) + p, Q) + q) : 0u;
+        const int v = (sl * NTH + tid) % DCP;
+        dr[sl] = *reinterpret_cast<const Chunk*>(dt + (uint64_t)(pix & 0xffffffu) * (uint64_t)k24 + v * EV);
+        dm |= ok ? (1u << sl) : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int sl = 0; sl < XSLOTS; ++sl) {
+        const int info = xinfo[sl];
+        const int n = nb + (info >> 20), y = yb - pad + ((info >> 10) & 1023), xx = xb - pad + (info & 1023);
+        const bool ok = info >= 0 && n < N && y >= 0 && y < H && xx >= 0 && xx < W;
+        const int v = (sl * NTH + tid) % XCP;
+        const int64_t off = ok ? (((int64_t)n * H + y) * W + xx) * C : 0;
+        xr[sl] = *reinterpret_cast<const Chunk*>(x + off + c0 + v * EV);
+        xm |= ok ? (1u << sl) : 0u;
+      }
+#pragma unroll
+      for (int sl = 0; sl < DSLOTS; ++sl) {
+        const int info = dinfo[sl];
+        const int n = nb + (info >> 20), p = yb + ((info >> 10) & 1023), q = xb + (info & 1023);
+        const bool ok = info >= 0 && n < N && p < P && q < Q;
+        const int v = (sl * NTH + tid) % DCP;
+        const int64_t off = ok ? (((int64_t)n * P + p) * Q + q) * K : 0;
+        dr[sl] = *reinterpret_cast<const Chunk*>(dz + off + k0 + v * EV);
+        dm |= ok ? (1u << sl) : 0u;
+      }
     }
     xok = xm; dok = dm;
   };
@@ -355,6 +385,7 @@ bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
 struct W9Plan { W9Args a; int mi, splits; };
 bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
   if (g.R != 3 || g.S != 3 || g.stride != 1 || g.C % 64 != 0 || g.K % 64 != 0) return false;
+  if (g.C >= 1 << 24 || g.K >= 1 << 24) return false;  // 24-bit products
   if (g.H >= 1024 || g.W >= 1024) return false;  // packed (image within the sub-tile, row, column) fields
   const int cap = dt == DT_F32 ? W9Cfg<float>::CAP : W9Cfg<bf16_t>::CAP;
   const int maxpos = dt == DT_F32 ? W9Cfg<float>::MAXPOS : W9Cfg<bf16_t>::MAXPOS;
@@ -362,13 +393,16 @@ bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
   if (!w9_geometry(g.N, g.P, g.Q, cap, maxpos, a)) return false;
   if (a.TP * 2 < cap) return false;  // short sub-tiles: too little work between barriers
   a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
-  // fp32: 64 output channels per block.  16-bit: 128 when possible (fewer operand fetches per MFMA), unless the blocks
+  // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD; in fp32 where a
+  // sub-tile is part of an image, whose addresses take longer: 128 -> 128 channels at 64 x 64, 262 144 pixels, 847 us with 64
+  // and 690 with 128, but 92.5 and 95 for 128 -> 256 on whole 8 x 8 images), unless the blocks
   // would then get fewer than g_w9_wide_min sub-tiles each: a block's accumulators (9 taps x 64*MI x 64 floats) are
   // written out once per pixel range and read again by the reduction, and with few sub-tiles per range that traffic
   // outweighs the operand reuse (128->128 at 16x16, batch 256, bf16: 49.6 us with 64-channel blocks, 48.1 with
   // 128-channel blocks of four sub-tiles each).  At that size the 75 MB of partial sums written and read back are most
   // of the time: 19 GFLOP would take 8 us at the matrix cores' peak.
-  for (int mi = (dt != DT_F32 && g.K % 128 == 0) ? 2 : 1; mi >= 1; --mi) {
+  const bool wide = g.K % 128 == 0 && (dt != DT_F32 || a.tiles_r * a.tiles_c > 1);
+  for (int mi = wide ? 2 : 1; mi >= 1; --mi) {
     const int64_t tiles = (int64_t)(g.K / (64 * mi)) * (g.C / 64);
     int64_t s = tiles >= 256 ? 1 : (256 + tiles / 2) / tiles;  // about one block per CU
     if (s > a.NT) s = a.NT;
@@ -387,10 +421,12 @@ bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
 template <class T, int MI, int WGM, bool FOLD>
 void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const W9Plan& pl) {
   constexpr size_t sm = W9Lds<T, MI, WGM>::bytes;
+  constexpr bool WHOLE_TOO = sizeof(T) == 2 || WGM == 2;  // the plan gives whole images in fp32 to the narrow blocks
   static bool attr_done = false;
   if (!attr_done) {
     (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    if constexpr (WHOLE_TOO)
+      (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     attr_done = true;
   }
   W9Args a = pl.a;
@@ -402,8 +438,13 @@ void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const 
   const bool whole = a.tiles_r == 1 && a.tiles_c == 1 && a.TR == a.P && a.TC == a.Q && a.H == a.P && a.W == a.Q &&
                      (int64_t)a.N * a.H * a.W + (int64_t)a.TI * a.H * a.W < (1 << 24) && a.C < (1 << 24) && a.K < (1 << 24) &&
                      a.TI < 256 && (int64_t)a.TI * a.H * a.W < (1 << 20);
-  if (whole) OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
-  else OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
+  if constexpr (WHOLE_TOO) {
+    if (whole) {
+      OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
+      return;
+    }
+  }
+  OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
 }
 
 template <class T>
@@ -436,7 +477,8 @@ void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz,
   W9Plan pl;
   if (!w9_plan(dt, g, pl)) return;
   pl.a.fold = dt == DT_F32 ? nullptr : fold;
-  if (dt == DT_F32) launch_w9<float, 1, 2, false>(st, x, dz, dst, pl);
+  if (dt == DT_F32 && pl.mi == 2) launch_w9<float, 1, 4, false>(st, x, dz, dst, pl);
+  else if (dt == DT_F32) launch_w9<float, 1, 2, false>(st, x, dz, dst, pl);
   else if (dt == DT_BF16) launch_w9_16<bf16_t>(st, x, dz, dst, pl);
   else launch_w9_16<f16_t>(st, x, dz, dst, pl);
 }
