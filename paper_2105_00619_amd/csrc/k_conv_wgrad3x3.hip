@@ -12,7 +12,7 @@
 //
 //   block = WGM x 2 wavefronts: wavefront (wm, wn) owns k rows [wm*32*MI, +32*MI) and c columns [wn*32, +32) of
 //   every tap: MI x 9 accumulator tiles of 32x32.  64 output channels: 2 x 2 wavefronts, one per SIMD.  128 output
-//   channels (16-bit modes): 4 x 2 wavefronts with MI = 1, two per SIMD (144 accumulator registers each), so that one
+//   channels (the plan says where): 4 x 2 wavefronts with MI = 1, two per SIMD (144 accumulator registers each), so that one
 //   wavefront's LDS reads and address arithmetic run under the other's MFMAs: 256 -> 256 channels at 8 x 8, batch
 //   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 326 us with 4 x 2 (the one-tap-per-block kernel: 479 us).
 //   fp32: MFMA 32x32x2, lanes read single floats of the pixel-major tiles (channel = lane).
