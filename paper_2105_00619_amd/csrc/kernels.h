@@ -48,7 +48,7 @@ void launch_bn_apply(hipStream_t st, int dt, const void* z, const float* stats, 
 void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* stats, void* a, void* y, int N, int H, int W,
                           int C, int relu);
 // per_image (0: no): da is the gradient per image, [rows / per_image][C], of a tensor that only a global average pool reads;
-// then C is a multiple of 16 / element size, aout and dskip are null, rows < 2^32 and rows * per_image < 2^48
+// then C is a multiple of 16 / element size, aout and dskip are null, rows < 2^32
 // ReLU decisions: from mask (bits as launch_bn_apply writes them, applied whatever relu says) if given, else from the
 // sign of aout if given, else redone from z when relu is set
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,

@@ -385,13 +385,12 @@ struct Scheduler {
     return b >= 0 && p.fops[b].unit == f.unit ? b : -1;
   }
 
-  // May the BatchNorm backward of operation fi, whose output only the global average pool `head` reads, take the gradient
-  // per image?  Its kernels do in whole groups of 16 / esize channels; a skip connection's gradient must not need a tensor
-  // written from it.
-  bool per_image_ok(int fi, const FOp& head) const {
+  // May the BatchNorm backward of operation fi, whose output only a global average pool reads, take the gradient
+  // per image?  Its kernels do in whole groups of 16 / esize channels and count rows in 32 bits; a skip connection's gradient
+  // must not need a tensor written from it.
+  bool per_image_ok(int fi) const {
     const FOp& f = p.fops[fi];
-    const double rows = (double)f.N * f.P * f.Q;
-    if (f.C % (16 / p.esize) != 0 || rows >= 4294967296.0 || rows * head.H * head.W >= 281474976710656.0) return false;
+    if (f.C % (16 / p.esize) != 0 || (int64_t)f.N * f.P * f.Q >= (int64_t)1 << 32) return false;
     return f.skip < 0 || masked_skip_grad_ok(fi);
   }
 
@@ -405,7 +404,7 @@ struct Scheduler {
         if (p.tensors[f.x].needs_grad) {
           const int ap = bn_apply_of[f.x];
           bool whole = true;  // the gradient as a whole tensor
-          if (f.gap && ap >= 0 && readers[f.x] == 1 && per_image_ok(ap, f)) {
+          if (f.gap && ap >= 0 && readers[f.x] == 1 && per_image_ok(ap)) {
             s.out[2] = image_grad[f.x] = new_inst(-1, (uint64_t)f.N * f.C * p.esize, false);
             // an identity shortcut's data gradient adds it as a tensor
             const int skip = p.fops[ap].skip;

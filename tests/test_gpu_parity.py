@@ -321,6 +321,29 @@ def test_weights_stationary_3x3_at_tile_edges(precision, cout, pad, h, w, b):
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
 
 
+@pytest.mark.parametrize("precision,cin,cout,ksize,stride,hw,b", [
+    (W.FP32, 3, 64, 3, 1, 2, 80000), (W.BF16, 3, 64, 3, 1, 2, 80000), (W.FP16, 2, 64, 3, 1, 1, 131073),
+    (W.FP16, 64, 128, 1, 2, 2, 80000)])
+def test_more_than_65536_images(precision, cin, cout, ksize, stride, hw, b):
+    """Small images in a batch whose index needs more than 16 bits: the pixel index is split into image, row and column in the
+    stem, small-channel and strided 1x1 kernels, and a row into its image where the average pool's gradient comes per image.
+    No ReLU; plain float64 and the bars of the single-layer tests (in 16 bits the gradients behind the average pool are those of
+    the oracle's 16-bit evaluation: every pixel of an image rounds alike there)."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(cin, cout, ksize, stride, bn=True, relu=False, bias=False), W.gap_linear_ce(cout, 10)]
+    rnd = {W.FP32: lambda v: v, W.BF16: O.round_to_bf16, W.FP16: O.round_to_fp16}[precision]
+    p = W.make_params(units, hw, hw, 13, perturb=True)
+    sl = W.param_slices(units, hw, hw)["u0.w"]
+    p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, hw, hw, cin, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    loss, g = oracle_step(units, p, x, y, precision, _scale(precision))
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+    assert_parity(units, hw, hw, r["grads"], g, TOL[precision])
+
+
 def _unit_trace(tr, xd, n_units):
     """GPU output of every body unit the plan writes to memory: {unit: float64 array}."""
     from paper_2105_00619_amd.binding import OptorchError
