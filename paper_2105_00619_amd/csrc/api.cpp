@@ -161,6 +161,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
       return OPTORCH_E_BUDGET;
     }
   }
+  if (ok && p.infer_bytes > p.arena_bytes) inference_in_schedule(p);
   p.cfg.boundaries = nullptr;  // the copy dies with this call; seg_begin holds the result
   if (!ok) { g_create_error = p.error; delete h; return OPTORCH_E_INVALID; }
   if (cfg->activation_budget_bytes && p.arena_bytes > cfg->activation_budget_bytes) {
@@ -553,8 +554,8 @@ extern "C" int optorch_seq_profile_read_entries(optorch_seq_t* h, int32_t capaci
 
 // Inference on the plan's own schedule: every BatchNorm's scale and shift from the running statistics in one launch, then
 // the forward operations with those BatchNorms (and the skip connections and ReLUs behind them) in the convolutions'
-// epilogues.  Of a convolution's output only the activation is ever written.
-static void infer_fused(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
+// epilogues.  Of a convolution's output only the activation is ever written.  c describes the batch (fp32 or encoded).
+static int predict_run(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
   const Plan& p = h->plan;
   hipStream_t st = h->stream;
   const int dt = h->dt;
@@ -593,46 +594,14 @@ static void infer_fused(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
                            (float*)at(o.out), logits_dev, (float*)at(o.ws));
         break;
       case S_POOL_FWD: launch_maxpool_fwd(st, dt, at(o.in), at(o.out), f.N, f.H, f.W, f.C); break;
+      case S_BN_APPLY: {  // the activation, written by the convolution, to where its readers look for it
+        hipError_t e = hipMemcpyAsync(at(o.out), at(o.in), p.tensors[f.out].bytes, hipMemcpyDeviceToDevice, st);
+        if (e != hipSuccess) return hip_fail(h, e, "hipMemcpyAsync(activation)");
+        break;
+      }
       default:  // S_CAST_IN
         if (c.xa) launch_decode_cast(st, dt, c.xa, f.N, (int64_t)f.H * f.W * f.C, c.xz, f.C, c.xscale, c.xshift, at(o.out));
         else launch_cast_in(st, dt, c.x, at(o.out), (int64_t)f.N * f.H * f.W * f.C);
-    }
-  }
-}
-
-// Inference: the forward entries of the schedule (all segments without keeping, then the last segment), with the
-// BatchNorm constants taken from the running statistics and the head stopped at the logits.  The arena offsets of
-// those entries are valid on their own: the entries run in schedule order and the plan never lets two live tensors
-// overlap.  c describes the batch (fp32 or encoded).
-static int predict_run(optorch_seq_t* h, const Ctx& c, float* logits_dev) {
-  hipStream_t st = h->stream;
-  const int dt = h->dt;
-  const bool fused = h->plan.infer_bytes <= h->plan.arena_bytes;
-  if (fused) infer_fused(h, c, logits_dev);
-  for (const SOp& s : h->plan.sched) {
-    if (fused) break;
-    if (!s.live || (s.phase != PH_FWD_NOSAVE && s.phase != PH_FWD_LAST)) continue;
-    const FOp& f = h->plan.fops[s.fop];
-    switch (s.kind) {
-      case S_BN_STATS:
-        launch_bn_eval_stats(st, (const float*)(h->pbase + h->off_run) + f.rs_off, c.w32(f.gamma_off), c.w32(f.beta_off),
-                             h->eps, f.C, (float*)c.at(s.out[0]));
-        break;
-      case S_CONV_FWD: {  // as in training, without the per-block channel sums
-        SOp t = s;
-        t.out[2] = -1;
-        run_op(c, t);
-        break;
-      }
-      case S_HEAD_FWD: {
-        launch_head_logits(st, dt, c.at(s.in[0]), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off),
-                           c.w32(f.b_off), (float*)c.at(s.out[0]), (float*)c.at(s.out[1]), (float*)c.at(s.out[4]));
-        hipError_t e = hipMemcpyAsync(logits_dev, c.at(s.out[1]), (size_t)f.N * f.classes * 4, hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return hip_fail(h, e, "hipMemcpyAsync(logits)");
-        break;
-      }
-      default:
-        run_op(c, s);
     }
   }
   hipError_t e = hipGetLastError();

@@ -34,9 +34,6 @@ void launch_bn_stats(hipStream_t st, int dt, const void* z, int64_t rows, int C,
 int bn_stats_fold_rows(int nblk);
 void launch_bn_stats_finalize(hipStream_t st, float* partial, int64_t rows, int C, int nblk, float eps, float mom,
                               const float* gamma, const float* beta, float* stats, float* running, const int* flags);
-// inference mode: (mean, rstd, scale, shift) from the running statistics [2][C] instead of the batch
-void launch_bn_eval_stats(hipStream_t st, const float* running, const float* gamma, const float* beta, float eps, int C,
-                          float* stats);
 // mask (null, or with a skip connection and C a multiple of 16 / element size): receives the ReLU decisions as bits,
 // byte (row * C + c) / V for the V = 16 / element size channels from c
 // skip_stats (null: none): skip is not the skip connection but the z of its BatchNorm (a projection shortcut's, without

@@ -658,6 +658,55 @@ void build_inference(Plan& p) {
   p.infer_bytes = fl.high_;
 }
 
+// Training keeps a convolution's output z until its BatchNorm apply has read it, and the skip connection with it; nothing else
+// lies there meanwhile.  So the convolution writes the activation itself to the place of z, and the apply operation becomes a
+// copy to the activation's place (or the pooling behind it); where the apply is folded into its reader, that reads the place of
+// z.  The kernels and their operands are those of build_inference, hence the same bits for every partition and every budget.
+void inference_in_schedule(Plan& p) {
+  p.infer.clear();
+  p.infer_bytes = p.arena_bytes;
+  std::vector<int64_t> at(p.tensors.size(), -1);  // place of an activation
+  auto place = [&](int inst) { return inst < 0 ? (int64_t)-1 : (int64_t)p.insts[inst].offset; };
+  for (const SOp& s : p.sched) {
+    if (!s.live || (s.phase != PH_FWD_NOSAVE && s.phase != PH_FWD_LAST)) continue;
+    const FOp& f = p.fops[s.fop];
+    IOp o;
+    o.kind = s.kind;
+    o.fop = s.fop;
+    o.in = place(s.in[0]);
+    o.out = place(s.out[0]);
+    switch (s.kind) {
+      case S_CONV_FWD: {
+        int out = f.out;
+        if (f.has_bn) {
+          o.apply = s.fop + 2;
+          const FOp& ap = p.fops[o.apply];
+          out = ap.out;
+          if (ap.skip >= 0) o.skip = at[ap.skip];
+        }
+        at[out] = o.out;
+        o.ws = place(s.out[1]);
+        break;
+      }
+      case S_BN_STATS: continue;
+      case S_BN_APPLY:
+        if (s.out[1] >= 0) {
+          IOp pool = o;
+          pool.kind = S_POOL_FWD;
+          pool.fop = s.fop + 1;
+          pool.out = at[p.fops[pool.fop].out] = place(s.out[1]);
+          p.infer.push_back(pool);
+          if (s.out[0] < 0) continue;
+        }
+        at[f.out] = o.out;
+        break;
+      case S_HEAD_FWD: o.ws = place(s.out[4]); break;
+      default: at[f.out] = o.out;  // the input's cast, a pool of its own
+    }
+    p.infer.push_back(o);
+  }
+}
+
 // Per-unit byte model of what a segment holds for its backward pass, read off a k = 1 schedule.  A tensor kept for
 // backward counts for the unit that made it, except a unit's output: that is kept as the input of the next unit (whose
 // backward reads it), so inside a segment it counts for every unit but the last, and for the last one only where the

@@ -98,7 +98,8 @@ struct SOp {
 };
 
 // One entry of the inference schedule: a forward operation with the BatchNorm behind a convolution done in that
-// convolution's epilogue.  Offsets into the activation arena, -1: none.
+// convolution's epilogue.  Offsets into the activation arena, -1: none.  S_BN_APPLY: a copy from `in` to `out`
+// (inference_in_schedule).
 struct IOp {
   SKind kind = S_CONV_FWD;
   int fop = -1, apply = -1;  // apply: the F_BN_APPLY operation of the BatchNorm behind the convolution, or -1
@@ -138,8 +139,12 @@ bool build_graph(Plan& p);
 bool choose_segments(Plan& p);
 // Builds schedule, lifetimes, offsets and peak figures for plan.seg_begin.
 bool build_schedule(Plan& p);
-// Builds the inference schedule; needs the kernel choices of the convolutions (workspaces of split depths).
+// Builds the inference schedule with offsets of its own; needs the kernel choices of the convolutions (workspaces of split
+// depths).
 void build_inference(Plan& p);
+// The same operations at the offsets of the training schedule's forward entries, for a plan whose arena is too small for
+// those offsets (holes between tensors of different sizes).
+void inference_in_schedule(Plan& p);
 // Peak saved bytes of the partition given by seg_begin, from the closed form
 //   max_j ( sum_{i<=j} checkpoint_i + saved_j ),
 // with per-unit saved bytes taken from the all-stored schedule.  Used by the min-peak planner.

@@ -3,7 +3,11 @@
 // the planner's own sources, then walks the schedule and checks what the kernels rely on:
 //   * every operation reads only tensors that an earlier live operation produced and that are not yet released;
 //   * no two tensors that are alive at the same time overlap in the activation arena, and all lie inside it;
-//   * the reported peaks are what the walk finds.
+//   * the reported peaks are what the walk finds;
+//   * inference, at offsets of its own and at those of the schedule: every operation finds the activations it reads whole
+//     where it looks for them, writes neither over them nor over its own workspace, and stays inside its arena.
+// All of it twice: with the planner's defaults, and with workspaces for split depths and with BatchNorms folded into their
+// readers as the library's kernel choices would have it.
 // Input: "k plan_mode precision batch height width channels classes storage_mode n_units" then n_units lines of
 // "kind cin cout ksize stride pad has_bn has_relu has_bias".  Output: "ok <arena> <peak_saved> <launches>" or an error.
 #include <cstdio>
@@ -19,19 +23,7 @@ static int fail(const char* what, int op, int inst) {
   return 1;
 }
 
-int main() {
-  Plan p;
-  int n_units = 0;
-  optorch_seq_config_t& c = p.cfg;
-  if (std::scanf("%d %d %d %d %d %d %d %d %d %d", &c.k_segments, &c.plan_mode, &c.precision, &c.batch, &c.height, &c.width,
-                 &c.channels, &c.num_classes, &c.storage_mode, &n_units) != 10) return fail("bad header", -1, -1);
-  for (int i = 0; i < n_units; ++i) {
-    optorch_unit_t u{};
-    if (std::scanf("%d %d %d %d %d %d %d %d %d", &u.kind, &u.cin, &u.cout, &u.ksize, &u.stride, &u.pad, &u.has_bn, &u.has_relu,
-                   &u.has_bias) != 9) return fail("bad unit", i, -1);
-    p.units.push_back(u);
-  }
-  if (!build_graph(p) || !choose_segments(p) || !build_schedule(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
+static int check_schedule(const Plan& p) {
   const int n = (int)p.sched.size();
   std::vector<char> alive(p.insts.size(), 0);
   std::vector<int> live_list;
@@ -74,6 +66,110 @@ int main() {
     if (alive[t]) return fail("never released", n, (int)t);
   if (peak_saved != p.peak_saved_bytes) return fail("peak of saved bytes differs from the plan's", -1, -1);
   if (launches != p.n_launches) return fail("launch count differs from the plan's", -1, -1);
-  std::printf("ok %llu %llu %d\n", (unsigned long long)p.arena_bytes, (unsigned long long)p.peak_saved_bytes, p.n_launches);
+  return 0;
+}
+
+static int check_inference(const Plan& p) {
+  struct Region { uint64_t a, b; int tensor; };  // what the last writer left there; -1: workspace
+  std::vector<Region> mem;
+  std::vector<int> ran(p.fops.size(), 0);
+  for (size_t i = 0; i < p.infer.size(); ++i) {
+    const IOp& o = p.infer[i];
+    const FOp& f = p.fops[o.fop];
+    const int op = (int)i;
+    const bool conv = o.kind == S_CONV_FWD, head = o.kind == S_HEAD_FWD, copy = o.kind == S_BN_APPLY;
+    ++ran[o.fop];
+    const int in = o.kind == S_CAST_IN ? -1 : copy ? f.out : f.x;
+    const int skip = conv && o.apply >= 0 ? p.fops[o.apply].skip : -1;
+    const int out = head ? f.aux[0] : conv && o.apply >= 0 ? p.fops[o.apply].out : f.out;
+    if (conv && f.has_bn && (o.apply < 0 || p.fops[o.apply].kind != F_BN_APPLY || p.fops[o.apply].x != f.out))
+      return fail("inference: not the BatchNorm behind the convolution", op, out);
+    const uint64_t ws = conv && f.fwd_splits > 1 ? (uint64_t)f.fwd_splits * f.N * f.P * f.Q * f.K * 4 : head ? (uint64_t)f.head_ws * 4 : 0;
+    std::vector<Region> mine;  // read by this operation
+    for (int r = 0; r < 2; ++r) {
+      const int t = r ? skip : in;
+      const int64_t at = r ? o.skip : o.in;
+      if (t < 0) continue;
+      bool found = false;
+      for (const Region& m : mem) found = found || (m.tensor == t && (int64_t)m.a == at && m.b - m.a == p.tensors[t].bytes);
+      if (!found) return fail("inference: an activation is not where it is read", op, t);
+      mine.push_back(Region{(uint64_t)at, at + p.tensors[t].bytes, t});
+    }
+    for (int w = 0; w < 2; ++w) {
+      const int64_t at = w ? o.ws : o.out;
+      const uint64_t bytes = w ? ws : p.tensors[out].bytes;
+      if (bytes == 0) continue;
+      if (at < 0 || at % kAlign != 0 || at + bytes > p.infer_bytes) return fail("inference: outside the arena", op, w ? -1 : out);
+      for (const Region& m : mine)
+        if ((uint64_t)at < m.b && m.a < at + bytes) return fail("inference: writes over what it uses", op, m.tensor);
+      const Region made{(uint64_t)at, at + bytes, w ? -1 : out};
+      std::vector<Region> kept;
+      for (const Region& m : mem)
+        if (!(made.a < m.b && m.a < made.b)) kept.push_back(m);
+      kept.push_back(made);
+      mem.swap(kept);
+      mine.push_back(made);
+    }
+  }
+  for (size_t i = 0; i < p.fops.size(); ++i) {
+    const FKind kind = p.fops[i].kind;
+    if (kind != F_BN_STATS && kind != F_BN_APPLY && ran[i] != 1) return fail("inference: an operation does not run once", (int)i, -1);
+  }
+  return 0;
+}
+
+// what the library's kernel choices change in the plan: depth splits, the head's ranges, folded BatchNorms
+static void choose_as_the_library(Plan& p) {
+  std::vector<int> readers(p.tensors.size(), 0), reader(p.tensors.size(), -1);
+  for (size_t i = 0; i < p.fops.size(); ++i) {
+    FOp& f = p.fops[i];
+    if (f.x >= 0) { ++readers[f.x]; reader[f.x] = (int)i; }
+    if (f.skip >= 0) { ++readers[f.skip]; reader[f.skip] = (int)i; }
+    if (f.kind == F_CONV && i % 3 == 1) f.fwd_splits = 2 + (int)i % 4;
+    if (f.kind == F_HEAD) f.head_ws = (int64_t)4 * f.N * (f.gap ? f.C : f.classes);
+  }
+  if (p.cfg.storage_mode == 2) return;
+  for (size_t i = 0; i < p.fops.size(); ++i) {
+    FOp& b = p.fops[i];
+    if (b.kind != F_BN_APPLY) continue;
+    if (b.relu && b.skip < 0 && b.mask < 0 && readers[b.out] == 1) {
+      FOp& cv = p.fops[reader[b.out]];
+      if (cv.kind == F_CONV && cv.x == b.out && cv.unit == b.unit && cv.stride == 1) { b.fold = 1; cv.fold_src = (int)i; }
+    }
+    if (b.skip >= 0 && readers[b.skip] == 1)
+      for (size_t j = 0; j < i; ++j) {
+        FOp& s = p.fops[j];
+        if (s.kind == F_BN_APPLY && s.out == b.skip && s.unit == b.unit && !s.relu && s.skip < 0) { s.fold = 1; b.fold_skip = (int)j; }
+      }
+  }
+}
+
+int main() {
+  Plan given;
+  int n_units = 0;
+  optorch_seq_config_t& c = given.cfg;
+  if (std::scanf("%d %d %d %d %d %d %d %d %d %d", &c.k_segments, &c.plan_mode, &c.precision, &c.batch, &c.height, &c.width,
+                 &c.channels, &c.num_classes, &c.storage_mode, &n_units) != 10) return fail("bad header", -1, -1);
+  for (int i = 0; i < n_units; ++i) {
+    optorch_unit_t u{};
+    if (std::scanf("%d %d %d %d %d %d %d %d %d", &u.kind, &u.cin, &u.cout, &u.ksize, &u.stride, &u.pad, &u.has_bn, &u.has_relu,
+                   &u.has_bias) != 9) return fail("bad unit", i, -1);
+    given.units.push_back(u);
+  }
+  Plan first;
+  for (int chosen = 0; chosen < 2; ++chosen) {
+    Plan p = given;
+    if (!build_graph(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
+    if (chosen) choose_as_the_library(p);
+    if (!choose_segments(p) || !build_schedule(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
+    if (check_schedule(p)) return 1;
+    build_inference(p);
+    if (check_inference(p)) return 1;
+    inference_in_schedule(p);
+    if (p.infer_bytes != p.arena_bytes) return fail("inference: not the schedule's arena", -1, -1);
+    if (check_inference(p)) return 1;
+    if (!chosen) first = p;
+  }
+  std::printf("ok %llu %llu %d\n", (unsigned long long)first.arena_bytes, (unsigned long long)first.peak_saved_bytes, first.n_launches);
   return 0;
 }

@@ -873,6 +873,27 @@ def test_inference_epilogues_match_oracle(name, precision):
     assert np.linalg.norm(r["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+def test_inference_is_the_same_bits_for_every_partition(precision):
+    """Shrinking maps and a wide first block: from four segments on the arena of the training schedule is smaller than what the
+    inference schedule takes at offsets of its own, and inference runs at the offsets of the training schedule instead."""
+    from oracle import seqnet_oracle as O
+    from tests.gpu_util import STORAGE
+    units = [W.conv(3, 512, stride=2), W.maxpool(), W.basic_block(512, 512, 2), W.basic_block(512, 64), W.conv(64, 64),
+             W.bottleneck(64, 128), W.gap_linear_ce(128, 10)]
+    p, x, y = _inputs(units, 41, 8, 8, 10, seed=5)
+    first = None
+    for k in (1, 3, 4, 7):
+        for mode in (0, 1):
+            r, _ = gpu_step(units, p, x, y, precision=precision, k=k, classes=10, predict_x=x[::-1].copy(), storage_mode=mode,
+                            loss_scale_init=_scale(precision))
+            first = r if first is None else first
+            assert np.array_equal(r["running"], first["running"]) and np.array_equal(r["params"], first["params"])
+            assert np.array_equal(r["logits"], first["logits"]), "k = %d, storage mode %d" % (k, mode)
+    ref = O.predict(units, first["params"].astype(np.float64), first["running"].astype(np.float64), x[::-1], storage=STORAGE[precision])
+    assert np.linalg.norm(first["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
+
+
 def test_inference_at_benchmark_size_matches_oracle():
     """Inference on the benchmark network at its full batch after one training step (fp32 mode)."""
     from oracle import seqnet_oracle as O

@@ -1,7 +1,8 @@
 """The static plan checked from outside the library: tests/plan_check.cpp is built with the planner's own source under
 AddressSanitizer and UBSan (host code only) and walks the schedule of every benchmark network at several k and both
 storage modes: reads only of live tensors, no overlap of live tensors in the arena, peaks and launch counts as
-reported.  (Kernel choices are left at their defaults there; they change split workspaces, not the walk.)"""
+reported; and inference in both placements, with every activation whole where it is read.  (The checker does it once with
+the planner's defaults and once with workspaces and folded BatchNorms as the library's kernel choices bring them.)"""
 import os
 import shutil
 import subprocess
@@ -69,11 +70,14 @@ def test_small_odd_networks_plan_validly(checker):
         [W.conv(3, 5), W.conv(5, 7, stride=2), W.maxpool(), W.conv(7, 6, ksize=1), W.gap_linear_ce(6, 3)],
         [W.conv(3, 8, bn=False), W.maxpool(), W.conv(8, 8, bn=True, relu=False, bias=True), W.maxpool(), W.flatten_linear_ce(8, 4)],
         [W.conv(3, 8), W.basic_block(8, 16, 2), W.basic_block(16, 16), W.bottleneck(16, 32, 2), W.gap_linear_ce(32, 5)],
+        # from four segments on the schedule's arena is smaller than what inference takes at offsets of its own
+        [W.conv(3, 512, stride=2), W.maxpool(), W.basic_block(512, 512, 2), W.basic_block(512, 64), W.conv(64, 64),
+         W.bottleneck(64, 128), W.gap_linear_ce(128, 10)],
     ]
-    sizes = [(3, 13, 10), (2, 8, 8), (4, 12, 12)]
-    classes = [3, 4, 5]
+    sizes = [(3, 13, 10), (2, 8, 8), (4, 12, 12), (41, 8, 8)]
+    classes = [3, 4, 5, 10]
     for units, (b, h, w), cl in zip(nets, sizes, classes):
         for k in range(1, len(units) + 1):
-            for storage_mode in (0, 1):
+            for storage_mode in (0, 1, 2):
                 for precision in (W.FP32, W.BF16):
                     _run(checker, units, k, k % 3, precision, b, h, w, 3, cl, storage_mode)
