@@ -517,7 +517,8 @@ int launches_of(const SOp& op, const FOp& f) {
   switch (op.kind) {
     case S_BN_STATS: return f.stat_blocks > 0 ? (f.stat_fold > 0 ? 2 : 1) : 2;
     case S_HEAD_FWD: return f.head_ws > 0 ? 5 : 4;
-    case S_HEAD_BWD: return op.out[0] >= 0 || op.out[2] >= 0 ? 4 : 2;
+    case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
+      return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
     case S_BN_BWD: return 3;
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;

@@ -894,6 +894,38 @@ def test_inference_is_the_same_bits_for_every_partition(precision):
     assert np.linalg.norm(first["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
 
 
+LAUNCH_NETS = {  # input channels, H, W, batch, k, units
+    "head_only_gap": (8, 5, 5, 3, 1, [W.gap_linear_ce(8, 5)]),
+    "head_only_flatten": (64, 20, 20, 4, 1, [W.flatten_linear_ce(64, 10)]),
+    "gap_of_many_pixels": (3, 128, 128, 2, 2, [W.conv(3, 8, bn=False), W.gap_linear_ce(8, 5)]),
+    "identity_in_front_of_the_pool": (3, 12, 12, 6, 2, [W.conv(3, 64), W.basic_block(64, 64), W.gap_linear_ce(64, 5)]),
+    "projection_in_front_of_the_pool": (3, 13, 10, 6, 3, [W.conv(3, 64), W.basic_block(64, 128, 2), W.gap_linear_ce(128, 5)]),
+    "pools_and_flatten": (3, 16, 16, 6, 2, [W.conv(3, 8), W.maxpool(), W.conv(8, 8, bn=False), W.flatten_linear_ce(8, 5)]),
+    "bottlenecks": (64, 9, 9, 40, 2, [W.bottleneck(64, 256), W.bottleneck(256, 256), W.gap_linear_ce(256, 10)]),
+}
+
+
+@pytest.mark.parametrize("name", sorted(LAUNCH_NETS))
+@pytest.mark.parametrize("precision", [W.FP32, W.FP16])
+def test_reported_launches_are_those_of_a_step(name, precision):
+    """The number of kernel launches that the plan reports against the launches counted while one step runs."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    cin, h, w, b, k, units = LAUNCH_NETS[name]
+    classes = units[-1].cout
+    p, x, y = _inputs(units, b, h, w, classes, channels=cin)
+    for mode in (0, 1, 2):
+        t = SeqTrainer(units, k_segments=k, precision=precision, batch=b, height=h, width=w, channels=cin, num_classes=classes,
+                       storage_mode=mode, loss_scale_init=_scale(precision))
+        t.set_params(p)
+        t.profile_enable()
+        t.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01)
+        classes_seen = t.profile_read()["classes"]
+        counted = sum(c["launches"] for kind, c in classes_seen.items() if kind != "optimizer")
+        assert counted == t.n_launches, (mode, {kind: (c["launches"], c["entries"]) for kind, c in classes_seen.items()})
+        t.close()
+
+
 def test_inference_at_benchmark_size_matches_oracle():
     """Inference on the benchmark network at its full batch after one training step (fp32 mode)."""
     from oracle import seqnet_oracle as O

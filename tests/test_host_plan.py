@@ -143,14 +143,14 @@ def test_automatic_choice_of_segments_and_storage_mode_under_a_budget():
 def test_pool_is_computed_by_the_kernels_of_the_batchnorm_in_front_of_it():
     # VGG-11-BN has 5 max-pools, each behind a conv-BN-ReLU.  Backward: the BatchNorm backward always does the pool's
     # backward as well (5 launches fewer).  Forward: the BatchNorm apply does the pool too, unless the pool opens a
-    # segment (then it is replayed from the segment's kept input and stays a kernel of its own).  All stored: 100
-    # launches as separate kernels, 90 fused.  Equal-count k = 4 puts boundaries at units 3, 6, 9, all three of them pools.
-    assert _plan(2, k_segments=1).n_launches == 90
+    # segment (then it is replayed from the segment's kept input and stays a kernel of its own).  All stored: 99
+    # launches as separate kernels, 89 fused.  Equal-count k = 4 puts boundaries at units 3, 6, 9, all three of them pools.
+    assert _plan(2, k_segments=1).n_launches == 89
     p = _plan(2, k_segments=4, plan_mode=0)
-    assert p.boundaries == [3, 6, 9] and (p.n_launches, p.n_replay_launches) == (106, 13)
+    assert p.boundaries == [3, 6, 9] and (p.n_launches, p.n_replay_launches) == (105, 13)
     # boundaries behind the pools instead: every pool is fused again, in the first pass and in the replay
     q = _plan(2, k_segments=4, boundaries=[4, 7, 10])
-    assert (q.n_launches, q.n_replay_launches) == (101, 11)
+    assert (q.n_launches, q.n_replay_launches) == (100, 11)
 
 
 def test_peak_shrinks_with_segments_and_plan_is_reproducible():
