@@ -92,13 +92,29 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         f.wgrad_algo = conv_mfma_wgrad_ok(dt, g) ? ALGO_MFMA : conv_smallc_wgrad_ok(g) ? ALGO_SMALLC : ALGO_DIRECT;
         if (f.fwd_algo == ALGO_MFMA) f.fwd_splits = conv_mfma_fwd_splits(dt, g);
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_splits = conv_mfma_dgrad_splits(dt, g);
-        if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g);
-        if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g);
+        if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
+        if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
         if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
       }
     for (FOp& f : p.fops)
-      if (f.kind == F_HEAD) f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes);
+      if (f.kind == F_HEAD) {
+        f.head_ws_in_x = !p.tensors[f.x].needs_grad;
+        f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, f.head_ws_in_x);
+      }
+    // more partial sums where the backward pass of the layer's unit has room for them anyway
+    auto splits_in = [&](const FOp& f, int64_t room) {
+      const ConvGeom g{f.N, f.H, f.W, f.C, f.K, f.R, f.S, f.stride, f.pad, f.P, f.Q};
+      return f.wgrad_algo == ALGO_MFMA ? conv_mfma_wgrad_splits(cfg->precision, g, room)
+             : f.wgrad_algo == ALGO_SMALLC ? conv_smallc_wgrad_splits(cfg->precision, g, room) : f.wgrad_splits;
+    };
+    bool any = false;
+    for (const FOp& f : p.fops) any = any || (f.kind == F_CONV && splits_in(f, (int64_t)1 << 62) != f.wgrad_splits);
+    if (any) {
+      const std::vector<int64_t> room = wgrad_room(p);
+      for (size_t i = 0; i < p.fops.size(); ++i)
+        if (p.fops[i].kind == F_CONV) p.fops[i].wgrad_splits = splits_in(p.fops[i], room[i]);
+    }
     // the BatchNorm statistics operation that follows such a convolution only runs its finishing kernel
     for (size_t i = 0; i + 1 < p.fops.size(); ++i)
       if (p.fops[i].kind == F_CONV && p.fops[i].stat_blocks > 0 && p.fops[i + 1].kind == F_BN_STATS &&
@@ -357,7 +373,8 @@ void run_op(const Ctx& c, const SOp& s) {
     case S_HEAD_FWD:
       launch_head_fwd(st, dt, c.at(s.in[0]), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off),
                       c.w32(f.b_off), c.y, h->scale / (float)f.N, (float*)c.at(s.out[0]), (float*)c.at(s.out[1]),
-                      (float*)c.at(s.out[2]), (float*)c.at(s.out[3]), c.loss(), c.flags(), (float*)c.at(s.out[4]));
+                      (float*)c.at(s.out[2]), (float*)c.at(s.out[3]), c.loss(), c.flags(),
+                      f.head_ws > 0 ? (float*)c.at(f.head_ws_in_x ? s.in[0] : s.out[4]) : nullptr);
       break;
     case S_HEAD_BWD:
       launch_head_bwd(st, dt, (const float*)c.at(s.in[0]), (const float*)c.at(s.in[1]), c.w32(f.w_off), f.N, f.H * f.W, f.C,

@@ -1,6 +1,8 @@
 // Direct (plain FMA) convolution forward / data gradient / weight gradient for shapes the matrix-core
 // kernels do not take: very few channels (the 3-channel stem, the tiny test networks).  NHWC activations,
 // (C_out, kh, kw, C_in) weights, fp32 accumulation in a fixed order.
+#include <algorithm>
+
 #include "dev_common.h"
 #include "epilogue.h"
 #include "kernels.h"
@@ -705,16 +707,16 @@ bool conv_smallc_wgrad_ok(const ConvGeom& g) {
   return g.C <= 4 && g.R * g.S * g.C <= SMALLC_MAX && (g.K <= 64 ? g.K % 8 == 0 : g.K % 64 == 0) &&
          (int64_t)g.N * g.P * g.Q < (1 << 24) && (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
 }
-int conv_smallc_wgrad_splits(int dt, const ConvGeom& g) {
+int conv_smallc_wgrad_splits(int dt, const ConvGeom& g, int64_t room) {
   const int64_t pixels = (int64_t)g.N * g.P * g.Q;
-  if (stem_ok(dt, g)) {  // one tile per block up to two blocks per CU
-    const int64_t b = (pixels + STEM_BM - 1) / STEM_BM;
-    return (int)(b < 512 ? b : 512);
-  }
-  // four tiles of 64 pixels per block, fewer where that would leave CUs idle
-  int64_t b = (pixels + 255) / 256;
-  if (b < 512) b = (pixels + 63) / 64 < 512 ? (pixels + 63) / 64 : 512;
-  return (int)(b < 1 ? 1 : (b > 1024 ? 1024 : b));
+  // four tiles of 64 pixels per block, fewer where that would leave CUs idle and the partial sums fit the room; the 16-bit
+  // kernel of the stem: one tile per block up to two blocks per CU
+  const int64_t four = std::min<int64_t>(std::max<int64_t>((pixels + 255) / 256, 1), 1024);
+  int64_t b = std::min<int64_t>((pixels + 63) / 64, 512);
+  if (stem_ok(dt, g)) b = std::min<int64_t>((pixels + STEM_BM - 1) / STEM_BM, 512);
+  else b = std::max(four, b);
+  const int64_t fit = room / ((int64_t)g.K * g.R * g.S * g.C * 4);
+  return (int)std::max<int64_t>(1, std::min(b, std::max(fit, g.K <= 64 ? four : std::min<int64_t>(four, 64))));
 }
 
 template <class T>
@@ -779,7 +781,7 @@ static void launch_wgrad_smallc_t(hipStream_t st, const T* x, const T* dz, float
   OSEQ_LAUNCH(conv_wgrad_smallc_kernel<T>, grid, block, 0, st, x, dz, dst, g, ceil_div(per, 64) * 64, dq, dpq);
 }
 
-// partial: [splits][K][R*S*C] floats; splits = conv_smallc_wgrad_splits(dt, g)
+// partial: [splits][K][R*S*C] floats; splits: any number, as conv_smallc_wgrad_splits gives it
 void launch_conv_wgrad_smallc(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                               const ConvGeom& g) {
   float* dst = splits > 1 ? partial : dw;

@@ -1566,8 +1566,8 @@ static int wgrad_large_splits(const ConvGeom& g) {
   return (int)(want < 1 ? 1 : want);
 }
 
-int conv_mfma_wgrad_splits(int dt, const ConvGeom& g) {
-  if (conv_wgrad3x3_ok(dt, g)) return conv_wgrad3x3_splits(dt, g);
+int conv_mfma_wgrad_splits(int dt, const ConvGeom& g, int64_t room) {
+  if (conv_wgrad3x3_ok(dt, g)) return conv_wgrad3x3_splits(dt, g, room);
   if (wgrad_large_ok(dt, g)) return wgrad_large_splits(g);
   const int depth = dt == DT_F32 ? 16 : 32;
   const int bm = g.K % 128 == 0 ? 128 : 64, bn = g.C % 128 == 0 ? 128 : 64;
@@ -1694,7 +1694,7 @@ bool conv_fold_wgrad_ok(int dt, const ConvGeom& g) { return dt != DT_F32 && conv
 void launch_conv_wgrad_mfma(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                             const ConvGeom& g, const float* fold) {
   float* dst = splits > 1 ? partial : dw;
-  if (conv_wgrad3x3_ok(dt, g)) launch_conv_wgrad3x3(st, dt, x, dz, dst, g, fold);  // splits == conv_wgrad3x3_splits(dt, g)
+  if (conv_wgrad3x3_ok(dt, g)) launch_conv_wgrad3x3(st, dt, x, dz, dst, splits, g, fold);
   else if (dt == DT_F32) launch_wgrad_t<float, false>(st, x, dz, dst, splits, g, nullptr);
   else if (dt == DT_BF16) {
     if (fold) launch_wgrad_t<bf16_t, true>(st, x, dz, dst, splits, g, fold);

@@ -383,7 +383,9 @@ bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
 
 // everything decided from the layer shape: block shape, sub-tile geometry, number of pixel ranges
 struct W9Plan { W9Args a; int mi, splits; };
-bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
+// room: bytes of partial sums that do not enlarge the activation arena; ranges (when the kernel is launched): the number of
+// ranges that the layer was given, 0: not yet
+bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   if (g.R != 3 || g.S != 3 || g.stride != 1 || g.C % 64 != 0 || g.K % 64 != 0) return false;
   if (g.C >= 1 << 24 || g.K >= 1 << 24) return false;  // 24-bit products
   if (g.H >= 1024 || g.W >= 1024) return false;  // packed (image within the sub-tile, row, column) fields
@@ -401,7 +403,9 @@ bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
   // outweighs the operand reuse (128->128 at 16x16, batch 256, bf16: 49.6 us with 64-channel blocks, 48.1 with
   // 128-channel blocks of four sub-tiles each).  At that size the 75 MB of partial sums written and read back are most
   // of the time: 19 GFLOP would take 8 us at the matrix cores' peak.
-  const bool wide = g.K % 128 == 0 && (dt != DT_F32 || a.tiles_r * a.tiles_c > 1);
+  // fp32: blocks twice as wide mean twice as many ranges and bytes of partial sums, so only where there is room for these.
+  const bool f32 = dt == DT_F32;
+  const bool wide = g.K % 128 == 0 && (!f32 || a.tiles_r * a.tiles_c > 1);
   for (int mi = wide ? 2 : 1; mi >= 1; --mi) {
     const int64_t tiles = (int64_t)(g.K / (64 * mi)) * (g.C / 64);
     int64_t s = tiles >= 256 ? 1 : (256 + tiles / 2) / tiles;  // about one block per CU
@@ -411,6 +415,7 @@ bool w9_plan(int dt, const ConvGeom& g, W9Plan& pl) {
     a.tiles_per_split = (int)((a.NT + s - 1) / s);
     s = (a.NT + a.tiles_per_split - 1) / a.tiles_per_split;  // no empty ranges
     if (mi == 2 && a.tiles_per_split < g_w9_wide_min) continue;
+    if (mi == 2 && f32 && (tiles * s < 128 || (ranges ? s != ranges : s * g.K * 9 * g.C * 4 > room))) continue;
     if (tiles * s < 128) return false;  // too few blocks for the chip: one tap per block does better
     pl.a = a; pl.mi = mi; pl.splits = (int)s;
     return true;
@@ -463,19 +468,19 @@ static constexpr int g_wgrad3x3 = 1;  // compile-time switch
 
 bool conv_wgrad3x3_ok(int dt, const ConvGeom& g) {
   W9Plan pl;
-  return g_wgrad3x3 && w9_plan(dt, g, pl);
+  return g_wgrad3x3 && w9_plan(dt, g, 0, 0, pl);
 }
 
-int conv_wgrad3x3_splits(int dt, const ConvGeom& g) {
+int conv_wgrad3x3_splits(int dt, const ConvGeom& g, int64_t room) {
   W9Plan pl;
-  return w9_plan(dt, g, pl) ? pl.splits : 1;
+  return w9_plan(dt, g, room, 0, pl) ? pl.splits : 1;
 }
 
 // dst: [splits][K][9][C] floats (dw itself when splits == 1); fold: see W9Args (16-bit modes only)
-void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz, float* dst, const ConvGeom& g,
+void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz, float* dst, int splits, const ConvGeom& g,
                           const float* fold) {
   W9Plan pl;
-  if (!w9_plan(dt, g, pl)) return;
+  if (!w9_plan(dt, g, 0, splits, pl)) return;
   pl.a.fold = dt == DT_F32 ? nullptr : fold;
   if (dt == DT_F32 && pl.mi == 2) launch_w9<float, 1, 4, false>(st, x, dz, dst, pl);
   else if (dt == DT_F32) launch_w9<float, 1, 2, false>(st, x, dz, dst, pl);

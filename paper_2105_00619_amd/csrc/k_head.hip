@@ -295,7 +295,10 @@ static void launch_feat_bwd(hipStream_t st, const float* dfeat, void* dx, int N,
 }
 
 // Ranges of pixels (GAP) or of the depth of the linear layer (flatten) over which the head's forward pass is split, from
-// the shape only: about four blocks per CU, ranges of at least 32 rows of threads (GAP) or four pieces per wavefront.
+// the shape only: about four blocks per CU, ranges of at least 32 rows of threads (GAP) or four pieces per wavefront; and no
+// more bytes of partial sums than the head's input has, so that a step's activation arena is not larger for them: the backward
+// pass has the input's gradient in their place, and where there is none (the input is the network's own) they lie in the input
+// itself, which the conversion has read by then.  (GAP reads it while it adds, but has 32 times as many pixels as ranges.)
 static int gap_tx(int C, int V) { const int CG = C / V; return CG < 256 ? CG : 256; }
 int head_ranges(int dt, int N, int HW, int C, int gap, int F, int J) {
   int64_t blocks, most;
@@ -306,14 +309,16 @@ int head_ranges(int dt, int N, int HW, int C, int gap, int F, int J) {
   } else {
     blocks = (int64_t)ceil_div(N, 32) * ceil_div(J, 32) * 2;
     most = F / (16 * 8 * 4);
+    if (most > (int64_t)F * (dt == DT_F32 ? 4 : 2) / (4 * (int64_t)J)) most = (int64_t)F * (dt == DT_F32 ? 4 : 2) / (4 * (int64_t)J);
   }
   int64_t want = (1024 + blocks - 1) / blocks;
   if (want > most) want = most;
   if (want > 128) want = 128;
   return (int)(want < 1 ? 1 : want);
 }
-// floats of workspace the forward pass needs for them
-int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J) {
+// floats of workspace the forward pass needs for them; in_x: it has to lie in the head's input (GAP: then there is none)
+int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J, bool in_x) {
+  if (gap && in_x) return 0;
   const int r = head_ranges(dt, N, HW, C, gap, F, J);
   return r > 1 ? (int64_t)r * N * (gap ? C : J) : 0;
 }
@@ -336,10 +341,10 @@ static void launch_feat_t(hipStream_t st, const T* x, int N, int HW, int C, int 
     OSEQ_LAUNCH(gap_finish_kernel, dim3(ceil_div((int64_t)N * C, 256)), dim3(256), 0, st, partial, feat, (int64_t)N * C, ranges, HW);
 }
 
-// ws: head_ws_floats(...) floats (null if that is 0)
+// ws: head_ws_floats(...) floats (null if that is 0: one range)
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                         const float* b, float* feat, float* logits, float* ws) {
-  const int ranges = head_ranges(dt, N, HW, C, gap, F, J);
+  const int ranges = ws ? head_ranges(dt, N, HW, C, gap, F, J) : 1;
   if (dt == DT_F32) launch_feat_t<float>(st, (const float*)x, N, HW, C, gap, ranges, feat, ws);
   else if (dt == DT_BF16) launch_feat_t<bf16_t>(st, (const bf16_t*)x, N, HW, C, gap, ranges, feat, ws);
   else launch_feat_t<f16_t>(st, (const f16_t*)x, N, HW, C, gap, ranges, feat, ws);

@@ -66,8 +66,9 @@ void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C
 // forward of the head up to the logits (no loss): inference
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                         const float* b, float* feat, float* logits, float* ws);
-// ws: workspace of the forward pass, where its sums are split over ranges (null if that needs none)
-int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J);
+// ws: workspace of the forward pass, where its sums are split over ranges (null: they are not)
+// in_x: it is to lie in the head's input, of which only the first kernel (pooling, conversion) reads
+int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J, bool in_x);
 // dx: gradient of the head's input, or null; dx_image (GAP): the same per image, [N][C] in the storage type, or null
 void launch_head_bwd(hipStream_t st, int dt, const float* feat, const float* dlogits, const float* w, int N, int HW, int C,
                      int gap, int F, int J, float* dw, float* db, float* dfeat, void* dx, void* dx_image);
@@ -82,7 +83,7 @@ void launch_conv_wgrad_direct(hipStream_t st, int dt, const void* x, const void*
 // few input channels (the stem): plain-FMA kernels with the weights in LDS
 bool conv_smallc_fwd_ok(const ConvGeom& g);
 bool conv_smallc_wgrad_ok(const ConvGeom& g);
-int conv_smallc_wgrad_splits(int dt, const ConvGeom& g);
+int conv_smallc_wgrad_splits(int dt, const ConvGeom& g, int64_t room);  // room: as for conv_mfma_wgrad_splits
 int conv_smallc_stat_blocks(int dt, const ConvGeom& g);
 void launch_conv_fwd_smallc(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
                             float* stat_partial, const ConvGeom& g, int relu, const ConvEval& ev = ConvEval());
@@ -127,11 +128,12 @@ void launch_conv_fwd_ws3x3(hipStream_t st, int dt, const void* x, const void* w,
 void launch_conv_dgrad_ws3x3(hipStream_t st, int dt, const void* dz, const void* wt, void* dx, const ConvGeom& g);
 // 3x3 stride-1 weight gradient with all nine taps per block (k_conv_wgrad3x3.hip); used by the MFMA launcher below
 bool conv_wgrad3x3_ok(int dt, const ConvGeom& g);
-int conv_wgrad3x3_splits(int dt, const ConvGeom& g);
-void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz, float* dst, const ConvGeom& g,
+int conv_wgrad3x3_splits(int dt, const ConvGeom& g, int64_t room);
+void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz, float* dst, int splits, const ConvGeom& g,
                           const float* fold);
 bool conv_mfma_wgrad_ok(int dt, const ConvGeom& g);
-int conv_mfma_wgrad_splits(int dt, const ConvGeom& g);
+// room: bytes of partial sums that do not enlarge the activation arena
+int conv_mfma_wgrad_splits(int dt, const ConvGeom& g, int64_t room);
 void launch_conv_wgrad_mfma(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                             const ConvGeom& g, const float* fold = nullptr);
 // Transposed weight copies for the data-gradient GEMMs, all layers in one launch (per 48 layers).  w_off: element

@@ -123,6 +123,7 @@ struct Builder {
           FOp f; f.kind = F_POOL; f.unit = ui; f.x = cur;
           f.N = N; f.H = (int)tx.h; f.W = (int)tx.w; f.C = (int)tx.c; f.K = f.C; f.P = f.H / 2; f.Q = f.W / 2;
           f.out = new_tensor(N, f.P, f.Q, f.C, p.esize, ui);
+          p.tensors[f.out].needs_grad = p.tensors[f.x].needs_grad;
           p.fops.push_back(f);
           cur = f.out;
           break;
@@ -227,6 +228,71 @@ struct FreeList {
     if (it->first + it->second == end_) { end_ = it->first; free_.erase(it); }
   }
 };
+
+// A tensor to be placed: bytes (aligned), the first and last step it is alive at, and where it goes.
+struct Span { uint64_t bytes; int first, last; uint64_t offset; };
+
+// Places tensors, given in the order of their first step, so that no two that are alive at the same step overlap; returns the
+// arena's size.  First in the order of the steps, each at the tightest hole.  Where that leaves holes that a later tensor does
+// not fit (a workspace between kept tensors), also one tensor after the other, each at the lowest offset that is free while it is
+// alive, in these orders: the largest first; those alive at the fullest step ahead of the others; those ahead with most bytes
+// times steps; the order of the steps; each also with the tensor that ended up on top ahead of all others, twice.  The smallest
+// result is kept; the search ends at one of `enough` bytes.
+uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough) {
+  const int n = (int)spans.size();
+  std::vector<std::vector<int>> dies(n_steps);
+  for (int i = 0; i < n; ++i) dies[spans[i].last].push_back(i);
+  FreeList fl;
+  uint64_t alive = 0, least = 0;  // least: what is alive at the fullest step
+  int fullest = 0;
+  for (int t = 0, next = 0; t < n_steps; ++t) {
+    for (; next < n && spans[next].first == t; ++next) {
+      spans[next].offset = fl.alloc(spans[next].bytes);
+      alive += spans[next].bytes;
+    }
+    if (alive > least) { least = alive; fullest = t; }
+    for (int i : dies[t]) { fl.release(spans[i].offset, spans[i].bytes); alive -= spans[i].bytes; }
+  }
+  uint64_t best = fl.high_;
+  enough = std::max(enough, least);
+  std::vector<int> order(n), placed;  // placed: by offset
+  std::vector<uint64_t> at(n);
+  for (int way = 0; way < 4 && best > enough; ++way) {
+    auto ahead = [&](int i) { return way == 1 && spans[i].first <= fullest && spans[i].last >= fullest; };
+    auto weight = [&](int i) { return way == 2 ? spans[i].bytes * (uint64_t)(spans[i].last - spans[i].first + 1) : spans[i].bytes; };
+    for (int i = 0; i < n; ++i) order[i] = i;
+    if (way < 3)
+      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return ahead(a) != ahead(b) ? ahead(a) : weight(a) > weight(b); });
+    for (int tries = 0; tries < 3 && best > enough; ++tries) {
+      uint64_t high = 0;
+      int top = 0;  // its place in the order
+      placed.clear();
+      for (int o = 0; o < n; ++o) {
+        const int i = order[o];
+        const Span& s = spans[i];
+        uint64_t off = 0;
+        for (int j : placed) {
+          const Span& q = spans[j];
+          if (q.last < s.first || s.last < q.first) continue;
+          if (at[j] >= off + s.bytes) break;
+          off = std::max(off, at[j] + q.bytes);
+        }
+        at[i] = off;
+        if (off + s.bytes > high) { high = off + s.bytes; top = o; }
+        if (high >= best) break;
+        placed.insert(std::upper_bound(placed.begin(), placed.end(), off, [&](uint64_t v, int j) { return v < at[j]; }), i);
+      }
+      if (high < best) {
+        best = high;
+        for (int i = 0; i < n; ++i) spans[i].offset = at[i];
+      }
+      std::rotate(order.begin(), order.begin() + top, order.begin() + top + 1);
+    }
+  }
+  return best;
+}
+
+uint64_t aligned(uint64_t bytes) { return align_up(std::max<uint64_t>(bytes, 1)); }
 
 bool is_fwd_kind(SKind k) { return k <= S_HEAD_FWD; }
 
@@ -343,7 +409,7 @@ struct Scheduler {
         s.in[0] = cur[f.x];
         s.out[0] = value_inst(f.aux[0]); s.out[1] = value_inst(f.aux[1]);
         s.out[2] = value_inst(f.aux[2]); s.out[3] = value_inst(f.out);
-        if (f.head_ws > 0) s.out[4] = new_inst(-1, (uint64_t)f.head_ws * 4, false);
+        if (f.head_ws > 0 && !f.head_ws_in_x) s.out[4] = new_inst(-1, (uint64_t)f.head_ws * 4, false);
         break;
       }
     }
@@ -477,8 +543,8 @@ struct Scheduler {
         return true;
       }
       case F_POOL: {
-        if (grad[f.out] < 0) { p.error = "internal: pool output has no gradient"; return false; }
         if (!p.tensors[f.x].needs_grad) return true;
+        if (grad[f.out] < 0) { p.error = "internal: pool output has no gradient"; return false; }
         if (grad[f.x] >= 0) { p.error = "internal: pool input already has a gradient"; return false; }
         if (pool_bwd_fused(fi)) { via_pool[f.x] = grad[f.out]; return true; }
         const int xin = backward_input(f.x, seg);
@@ -542,7 +608,8 @@ bool build_graph(Plan& p) {
   return b.run();
 }
 
-bool build_schedule(Plan& p) {
+// the schedule and the lifetimes of its tensors
+static bool schedule_operations(Plan& p) {
   Scheduler s(p);
   if (!s.run()) return false;
   const int n = (int)p.sched.size();
@@ -574,11 +641,18 @@ bool build_schedule(Plan& p) {
       if (t.fwd_value && (op.phase == PH_BWD || op.phase != d.phase || op.seg != d.seg)) t.held = true;
     }
   }
-  // arena offsets + peak figures, by walking the schedule
+  return true;
+}
+
+bool build_schedule(Plan& p, uint64_t enough) {
+  if (!schedule_operations(p)) return false;
+  const int n = (int)p.sched.size();
+  // peak figures, by walking the schedule, and arena offsets
   std::vector<std::vector<int>> dies(n);
   for (size_t t = 0; t < p.insts.size(); ++t)
     if (p.insts[t].def_op >= 0) dies[p.insts[t].last_use].push_back((int)t);
-  FreeList fl;
+  std::vector<Span> spans;
+  std::vector<int> span_inst;
   uint64_t live_b = 0, held_b = 0;
   p.peak_saved_bytes = p.peak_live_bytes = 0;
   p.n_launches = p.n_replay_launches = 0;
@@ -590,73 +664,88 @@ bool build_schedule(Plan& p) {
     if (op.phase == PH_REPLAY) p.n_replay_launches += nl;
     for (int o : op.out) if (o >= 0) {
       Inst& t = p.insts[o];
-      t.offset = fl.alloc(t.bytes); t.allocated = true;
+      t.allocated = true;
+      spans.push_back(Span{aligned(t.bytes), i, t.last_use, 0});
+      span_inst.push_back(o);
       live_b += t.bytes;
       if (t.held) held_b += t.bytes;
     }
     p.peak_live_bytes = std::max(p.peak_live_bytes, live_b);
     p.peak_saved_bytes = std::max(p.peak_saved_bytes, held_b);
     for (int t : dies[i]) {
-      Inst& x = p.insts[t];
-      fl.release(x.offset, x.bytes);
-      live_b -= x.bytes;
-      if (x.held) held_b -= x.bytes;
+      live_b -= p.insts[t].bytes;
+      if (p.insts[t].held) held_b -= p.insts[t].bytes;
     }
   }
-  p.arena_bytes = fl.high_;
+  p.arena_bytes = place(spans, n, enough);
+  for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
   return true;
+}
+
+std::vector<int64_t> wgrad_room(const Plan& p) {
+  std::vector<int64_t> room(p.fops.size(), 0);
+  for (int mode = 0; mode < 2; ++mode) {
+    Plan q = p;
+    q.cfg.storage_mode = mode;
+    q.seg_begin = {0, (int)q.units.size()};
+    if (!schedule_operations(q)) return room;  // (a network that cannot be scheduled is refused later)
+    std::vector<int64_t> born(q.sched.size() + 1, 0), alive(q.sched.size(), 0), most(q.units.size(), 0);
+    for (const Inst& t : q.insts)
+      if (t.def_op >= 0) { born[t.def_op] += (int64_t)t.bytes; born[t.last_use + 1] -= (int64_t)t.bytes; }
+    int64_t sum = 0;
+    for (size_t i = 0; i < q.sched.size(); ++i) {
+      alive[i] = sum += born[i];
+      const int unit = q.fops[q.sched[i].fop].unit;
+      if (q.sched[i].live && q.sched[i].phase == PH_BWD) most[unit] = std::max(most[unit], sum);
+    }
+    for (size_t i = 0; i < q.sched.size(); ++i) {
+      const SOp& s = q.sched[i];
+      if (!s.live || s.kind != S_WGRAD) continue;
+      const int64_t ws = s.out[0] >= 0 ? (int64_t)q.insts[s.out[0]].bytes : 0;
+      const int64_t r = most[q.fops[s.fop].unit] - (alive[i] - ws);
+      room[s.fop] = mode ? std::min(room[s.fop], r) : r;
+    }
+  }
+  return room;
 }
 
 void build_inference(Plan& p) {
   p.infer.clear();
-  const int n = (int)p.fops.size();
-  std::vector<int> last(p.tensors.size(), -1);  // last operation that reads a tensor
-  for (int i = 0; i < n; ++i) {
-    const FOp& f = p.fops[i];
-    if (f.kind == F_BN_STATS) continue;
-    if (f.x >= 0) last[f.x] = i;
-    if (f.skip >= 0) last[f.skip] = i;
-  }
-  std::vector<int64_t> at(p.tensors.size(), -1);
-  FreeList fl;
-  auto done = [&](int t, int i) {  // operation i has read tensor t
-    if (t >= 0 && last[t] == i && at[t] >= 0) { fl.release((uint64_t)at[t], p.tensors[t].bytes); at[t] = -1; }
+  std::vector<Span> spans;
+  std::vector<int> span(p.tensors.size(), -1);  // [LTensor] -> its span
+  // (until the tensors are placed, the offsets of an entry are spans)
+  auto make = [&](uint64_t bytes) {
+    const int t = (int)p.infer.size();
+    spans.push_back(Span{aligned(bytes), t, t, 0});
+    return (int64_t)spans.size() - 1;
   };
-  for (int i = 0; i < n; ++i) {
+  auto read = [&](int t) -> int64_t {
+    spans[span[t]].last = (int)p.infer.size();
+    return span[t];
+  };
+  for (int i = 0; i < (int)p.fops.size(); ++i) {
     const FOp& f = p.fops[i];
+    if (f.kind == F_BN_STATS || f.kind == F_BN_APPLY) continue;  // in the convolution's epilogue
     IOp o;
     o.fop = i;
-    if (f.x >= 0) o.in = at[f.x];
-    uint64_t ws = 0;
-    switch (f.kind) {
-      case F_CAST_IN: o.kind = S_CAST_IN; o.out = at[f.out] = (int64_t)fl.alloc(p.tensors[f.out].bytes); break;
-      case F_CONV: {
-        o.kind = S_CONV_FWD;
-        int out = f.out;
-        if (f.has_bn) {  // followed by its statistics and apply operations
-          o.apply = i + 2;
-          const FOp& ap = p.fops[o.apply];
-          out = ap.out;
-          if (ap.skip >= 0) o.skip = at[ap.skip];
-        }
-        o.out = at[out] = (int64_t)fl.alloc(p.tensors[out].bytes);
-        if (f.fwd_splits > 1) ws = (uint64_t)f.fwd_splits * f.N * f.P * f.Q * f.K * 4;
-        break;
-      }
-      case F_BN_STATS: continue;
-      case F_BN_APPLY: done(f.skip, i); continue;  // (its x is the convolution's output, which does not exist)
-      case F_POOL: o.kind = S_POOL_FWD; o.out = at[f.out] = (int64_t)fl.alloc(p.tensors[f.out].bytes); break;
-      case F_HEAD:
-        o.kind = S_HEAD_FWD;
-        o.out = (int64_t)fl.alloc(p.tensors[f.aux[0]].bytes);
-        ws = (uint64_t)f.head_ws * 4;
-        break;
+    o.kind = f.kind == F_CAST_IN ? S_CAST_IN : f.kind == F_CONV ? S_CONV_FWD : f.kind == F_POOL ? S_POOL_FWD : S_HEAD_FWD;
+    int out = f.kind == F_HEAD ? f.aux[0] : f.out;
+    if (f.x >= 0) o.in = read(f.x);
+    if (f.kind == F_CONV && f.has_bn) {  // followed by its statistics and apply operations
+      o.apply = i + 2;
+      const FOp& ap = p.fops[o.apply];
+      out = ap.out;
+      if (ap.skip >= 0) o.skip = read(ap.skip);
     }
-    if (ws) { o.ws = (int64_t)fl.alloc(ws); fl.release((uint64_t)o.ws, ws); }
-    done(f.x, i);
+    o.out = span[out] = (int)make(p.tensors[out].bytes);
+    if (f.kind == F_CONV && f.fwd_splits > 1) o.ws = make((uint64_t)f.fwd_splits * f.N * f.P * f.Q * f.K * 4);
+    if (f.kind == F_HEAD && f.head_ws > 0) o.ws = f.head_ws_in_x ? o.in : make((uint64_t)f.head_ws * 4);
     p.infer.push_back(o);
   }
-  p.infer_bytes = fl.high_;
+  p.infer_bytes = place(spans, (int)p.infer.size(), 0);
+  for (IOp& o : p.infer)
+    for (int64_t* off : {&o.in, &o.skip, &o.out, &o.ws})
+      if (*off >= 0) *off = (int64_t)spans[*off].offset;
 }
 
 // Training keeps a convolution's output z until its BatchNorm apply has read it, and the skip connection with it; nothing else
@@ -701,7 +790,7 @@ void inference_in_schedule(Plan& p) {
         }
         at[f.out] = o.out;
         break;
-      case S_HEAD_FWD: o.ws = place(s.out[4]); break;
+      case S_HEAD_FWD: o.ws = f.head_ws_in_x ? o.in : place(s.out[4]); break;
       default: at[f.out] = o.out;  // the input's cast, a pool of its own
     }
     p.infer.push_back(o);
@@ -781,7 +870,7 @@ bool choose_segments(Plan& p) {
   Plan all = p;
   all.cfg.boundaries = nullptr;
   all.seg_begin = {0, nu};
-  if (!build_schedule(all)) { p.error = all.error; return false; }
+  if (!schedule_operations(all)) { p.error = all.error; return false; }
   const SegModel model(all);
   const std::vector<uint64_t>& ck = model.ck;
   const uint64_t INF = ~0ull;
@@ -891,7 +980,7 @@ bool choose_segments(Plan& p) {
     Plan trial = p;
     trial.cfg.boundaries = nullptr;
     trial.seg_begin = *cuts;
-    if (!build_schedule(trial)) { p.error = trial.error; *error = true; return false; }
+    if (!build_schedule(trial, budget)) { p.error = trial.error; *error = true; return false; }
     return trial.arena_bytes <= budget;
   };
   uint64_t T = budget > lo ? budget : lo, too_big = 0;

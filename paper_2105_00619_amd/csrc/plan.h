@@ -52,6 +52,8 @@ struct FOp {
   int64_t rs_off = -1;       // element offset of (running mean, running var) in the running-stat block
   int gap = 0, feat_dim = 0, classes = 0;
   int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
+  bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
+                             // of the head's kernels
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
   int fwd_splits = 1, dgrad_splits = 1;  // fixed by shape only: deterministic split of the GEMM depth
@@ -137,8 +139,13 @@ struct Plan {
 bool build_graph(Plan& p);
 // Chooses segment boundaries (explicit, equal count, or min peak) into plan.seg_begin.
 bool choose_segments(Plan& p);
-// Builds schedule, lifetimes, offsets and peak figures for plan.seg_begin.
-bool build_schedule(Plan& p);
+// Builds schedule, lifetimes, offsets and peak figures for plan.seg_begin.  enough: an arena of that many bytes need not be
+// made smaller.
+bool build_schedule(Plan& p, uint64_t enough = 0);
+// [F_CONV operation] bytes of partial sums its weight gradient can write without becoming the fullest moment of its unit's
+// backward pass: whatever else is alive stays alive throughout that pass, so this holds for every partition; the smaller value
+// of the storage modes that keep and that rebuild activations.  From the network and the kernel choices so far only.
+std::vector<int64_t> wgrad_room(const Plan& p);
 // Builds the inference schedule with offsets of its own; needs the kernel choices of the convolutions (workspaces of split
 // depths).
 void build_inference(Plan& p);

@@ -97,11 +97,11 @@ static int check_inference(const Plan& p) {
     }
     for (int w = 0; w < 2; ++w) {
       const int64_t at = w ? o.ws : o.out;
-      const uint64_t bytes = w ? ws : p.tensors[out].bytes;
+      const uint64_t bytes = w ? ws : p.tensors[out].bytes;  // (a head on the network's own input may lay its workspace over that)
       if (bytes == 0) continue;
       if (at < 0 || at % kAlign != 0 || at + bytes > p.infer_bytes) return fail("inference: outside the arena", op, w ? -1 : out);
       for (const Region& m : mine)
-        if ((uint64_t)at < m.b && m.a < at + bytes) return fail("inference: writes over what it uses", op, m.tensor);
+        if ((uint64_t)at < m.b && m.a < at + bytes && !(w && f.head_ws_in_x && m.tensor == f.x && bytes <= m.b - m.a)) return fail("inference: writes over what it uses", op, m.tensor);
       const Region made{(uint64_t)at, at + bytes, w ? -1 : out};
       std::vector<Region> kept;
       for (const Region& m : mem)
@@ -126,7 +126,10 @@ static void choose_as_the_library(Plan& p) {
     if (f.x >= 0) { ++readers[f.x]; reader[f.x] = (int)i; }
     if (f.skip >= 0) { ++readers[f.skip]; reader[f.skip] = (int)i; }
     if (f.kind == F_CONV && i % 3 == 1) f.fwd_splits = 2 + (int)i % 4;
-    if (f.kind == F_HEAD) f.head_ws = (int64_t)4 * f.N * (f.gap ? f.C : f.classes);
+    if (f.kind == F_HEAD) {
+      f.head_ws_in_x = !p.tensors[f.x].needs_grad;
+      f.head_ws = f.head_ws_in_x ? (int64_t)(p.tensors[f.x].bytes / 4) : (int64_t)4 * f.N * (f.gap ? f.C : f.classes);
+    }
   }
   if (p.cfg.storage_mode == 2) return;
   for (size_t i = 0; i < p.fops.size(); ++i) {

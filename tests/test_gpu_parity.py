@@ -238,6 +238,30 @@ def test_head_products_at_tile_edges(n, h, w, c, classes, gap, precision):
     assert max(errs.values()) <= TOL[precision], errs
 
 
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
+@pytest.mark.parametrize("units,h,w,b", [
+    ([W.flatten_linear_ce(64, 10)], 20, 20, 4), ([W.maxpool(), W.flatten_linear_ce(64, 37)], 41, 20, 33), ([W.gap_linear_ce(64, 10)], 96, 97, 2)],
+    ids=["flatten", "pool_flatten", "gap"])
+def test_head_on_the_networks_own_input(precision, units, h, w, b):
+    """A head whose input has no gradient: the sums of a split feature depth lie in that input.  Two steps and an inference in
+    between, loss, every gradient and the logits against the oracle."""
+    from oracle import seqnet_oracle as O
+    from tests.gpu_util import STORAGE
+    classes = units[-1].cout
+    p, x, y = _inputs(units, b, h, w, classes, channels=64)
+    outs, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=classes, steps=2, lr=0.5, predict_x=x[::-1].copy(),
+                       loss_scale_init=_scale(precision))
+    at = p
+    for r in outs:
+        loss, g = oracle_step(units, at, x, y, precision, _scale(precision))
+        assert not r["skipped"] and abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+        errs = plain_errors(units, h, w, r["grads"], g)
+        assert max(errs.values()) <= TOL[precision], errs
+        at = r["params"]
+        ref = O.predict(units, at.astype(np.float64), r["running"].astype(np.float64), x[::-1], storage=STORAGE[precision])
+        assert np.linalg.norm(r["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("bn", [False, True])
 @pytest.mark.parametrize("precision,cin,cout,stride,pad,h,w,b", [
     (W.BF16, 3, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 128, 2, 1, 13, 10, 9), (W.BF16, 1, 64, 1, 0, 8, 8, 3), (W.FP16, 2, 192, 1, 1, 5, 33, 4),

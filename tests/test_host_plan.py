@@ -268,3 +268,44 @@ def test_planner_against_brute_force_on_small_networks():
             assert m2.planned_peak_saved_bytes <= 1.01 * least
             assert m2.n_replay_launches <= min(r[1] for r in rows if r[0] <= m2.planned_peak_saved_bytes)
             assert m1.planned_peak_saved_bytes <= 1.15 * least
+
+
+# Arenas that sufficed before the head's pooling and products, the fp32 and small-channel weight gradients and the statistics took
+# more workspace: a budget of that size has to be enough still.  Units: kind and channels out [/stride], c = 3x3 convolution +
+# BatchNorm + ReLU, r = bias + ReLU, C and R the same with 1x1, b = basic block, n = bottleneck, p = pool.
+ARENAS = [  # precision, batch, h, w, channels, k, storage mode, plan mode, classes, units, bytes
+    (W.FP32, 8, 32, 32, 3, 1, 0, 2, 1000, "flat", 260864),
+    (W.FP32, 16, 64, 64, 3, 1, 1, 0, 100, "flat", 1585920),
+    (W.FP32, 16, 9, 9, 3, 3, 0, 2, 1000, "n512 b512 p b12 c64/2 flat", 55020800),
+    (W.FP32, 16, 17, 17, 3, 4, 2, 0, 10, "b64/2 c256 b512 gap", 55058688),
+    (W.FP32, 4, 128, 128, 3, 6, 0, 1, 100, "n128/2 b128 r128 b8 p gap", 97255936),
+    (W.FP32, 128, 64, 64, 1, 4, 1, 0, 1000, "b12/2 p b128 n8 gap", 148898304),
+    (W.FP32, 32, 17, 20, 3, 2, 0, 2, 100, "p p n512 flat", 8050688),
+    (W.BF16, 512, 9, 9, 64, 4, 0, 2, 1000, "n64 b256 p R64/2 n64 R64/2 flat", 179012096),
+    (W.FP16, 128, 16, 16, 64, 7, 1, 0, 10, "p b512 c8 p b8 b8 flat", 114294784),
+    (W.BF16, 128, 8, 8, 64, 3, 1, 0, 10, "R128 b256 b256 R256 p p flat", 62982144),
+]
+
+
+@pytest.mark.parametrize("case", ARENAS, ids=[c[9].replace(" ", "_") + "_%d" % c[0] for c in ARENAS])
+def test_a_budget_that_sufficed_still_does(case):
+    precision, batch, h, w, channels, k, mode, plan_mode, classes, text, needed = case
+    units, c = [], channels
+    hh, ww = h, w
+    for word in text.split()[:-1]:
+        word, _, stride = word.partition("/")
+        stride = int(stride or 1)
+        if word == "p":
+            units.append(W.maxpool())
+            hh, ww = hh // 2, ww // 2
+            continue
+        cout = int(word[1:])
+        if word[0] in "crCR":
+            units.append(W.conv(c, cout, 3 if word[0] in "cr" else 1, stride, bn=word[0] in "cC"))
+        else:
+            units.append((W.basic_block if word[0] == "b" else W.bottleneck)(c, cout, stride))
+        c, hh, ww = cout, (hh - 1) // stride + 1, (ww - 1) // stride + 1
+    units.append(W.gap_linear_ce(c, classes) if text.split()[-1] == "gap" else W.flatten_linear_ce(c, classes))
+    p = SeqPlan(units, k_segments=k, precision=precision, batch=batch, height=h, width=w, channels=channels, num_classes=classes,
+                storage_mode=mode, plan_mode=plan_mode, activation_budget_bytes=needed)  # raises where it does not
+    assert p.act_arena_bytes <= needed
