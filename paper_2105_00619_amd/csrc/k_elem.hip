@@ -400,8 +400,9 @@ __global__ void __launch_bounds__(256) bn_apply_kernel(const T* __restrict__ z, 
     load_f32<float, V>(skip_stats + 3 * C + c0, sh2);
 #pragma unroll
     for (int k = 0; k < V; ++k) vs[k] = bn_affine(vs[k], sc2[k], sh2[k]);
-    // (rounded as a store would, in pairs: a scalar conversion may be merged with the multiply-add in front of it into one
-    // instruction that rounds once)
+    // (rounded as a store would: in pairs, or with the value kept apart from the multiply-add in front of it -- a scalar conversion
+    // to fp16 is merged with that into one instruction, which rounds once)
+    if constexpr (V == 1) asm("" : "+v"(vs[0]));
     const Vec<T, V> sv = round_vec<T, V>(vs);
 #pragma unroll
     for (int k = 0; k < V; ++k) vs[k] = to_f32(sv.v[k]);

@@ -918,6 +918,21 @@ def test_inference_is_the_same_bits_for_every_partition(precision):
     assert np.linalg.norm(first["logits"] - ref) <= TOL[precision] * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
+@pytest.mark.parametrize("cout", [20, 12, 24])
+def test_shared_shortcut_batchnorm_rounds_like_its_own_pass(cout, precision):
+    """The BatchNorm of a projection shortcut inside the pass that adds it (storage modes 0 and 1) against a pass of its own
+    (mode 2), bit for bit, at channel counts with and without 16-byte groups: the shortcut's value is rounded to the storage
+    type before it is added, however the compiler arranges the conversion."""
+    units = [W.conv(3, 8), W.basic_block(8, cout, 2), W.bottleneck(cout, 2 * cout), W.gap_linear_ce(2 * cout, 10)]
+    p, x, y = _inputs(units, 48, 33, 32, 10, seed=3)
+    kw = dict(precision=precision, k=2, classes=10, loss_scale_init=_scale(precision))
+    a, _ = gpu_step(units, p, x, y, storage_mode=2, **kw)
+    for mode in (0, 1):
+        b, _ = gpu_step(units, p, x, y, storage_mode=mode, **kw)
+        assert a["loss"] == b["loss"] and np.array_equal(a["grads"], b["grads"]), mode
+
+
 LAUNCH_NETS = {  # input channels, H, W, batch, k, units
     "head_only_gap": (8, 5, 5, 3, 1, [W.gap_linear_ce(8, 5)]),
     "head_only_flatten": (64, 20, 20, 4, 1, [W.flatten_linear_ce(64, 10)]),
