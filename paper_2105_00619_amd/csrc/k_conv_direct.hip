@@ -689,11 +689,15 @@ __global__ void __launch_bounds__(256) partial_reduce_kernel(const float* __rest
   }
 }
 
-// 8 to 31 output channels: with a group of 64 mostly empty the direct kernel is the faster one (3 -> 8 channels, 8 images of
-// 32 x 32, fp32: 5.7 us against 12.5)
+// 8 to 31 output channels leave most of a group of 64 empty, but only as long as the pixels are few is the direct kernel, whose
+// time goes with the outputs and the loads of each, the faster one.  us, direct / tiled, 3 -> K channels: fp32 K = 8 at 8192
+// pixels 6.8 / 14.5, 32 768 12.1 / 15.8, 65 536 18.1 / 16.7, 2 M 315 / 129; K = 24 at 8192 12.9 / 17.0, 16 384 20.7 / 16.4, 2 M
+// 1386 / 133; bf16 K = 16 at 16 384 11.8 / 15.6, 32 768 20.3 / 14.4.  1 -> 16 at 32 768 12.0 / 11.4, 4 -> 16 12.9 / 15.4 (four
+// channels are one load).  The line is drawn at outputs * (loads + 6): 8.7 M at 3 -> 8 and 32 768 pixels, 13 M at 3 -> 24 and 16 384.
 bool conv_smallc_fwd_ok(const ConvGeom& g) {
-  return g.C <= 4 && g.R == 3 && g.S == 3 && g.K % 8 == 0 && g.K >= 32 && (int64_t)g.N * g.P * g.Q < (1 << 24) &&
-         (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
+  const int64_t pixels = (int64_t)g.N * g.P * g.Q;
+  if (g.K < 32 && pixels * g.K * (9 * (g.C % 4 == 0 ? 1 : g.C) + 6) < 10000000) return false;
+  return g.C <= 4 && g.R == 3 && g.S == 3 && g.K % 8 == 0 && pixels < (1 << 24) && (int64_t)g.N * g.H * g.W * g.C < ((int64_t)1 << 31);
 }
 // the 16-bit kernels of the stem
 static bool stem_ok(int dt, const ConvGeom& g) { return dt != DT_F32 && g.C <= 3 && g.R == 3 && g.S == 3 && g.K % 64 == 0; }

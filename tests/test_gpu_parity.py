@@ -266,11 +266,12 @@ def test_head_on_the_networks_own_input(precision, units, h, w, b):
 @pytest.mark.parametrize("precision,cin,cout,stride,pad,h,w,b", [
     (W.BF16, 3, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 128, 2, 1, 13, 10, 9), (W.BF16, 1, 64, 1, 0, 8, 8, 3), (W.FP16, 2, 192, 1, 1, 5, 33, 4),
     (W.BF16, 3, 64, 1, 1, 32, 32, 130), (W.FP32, 3, 128, 1, 1, 11, 6, 4), (W.FP32, 4, 64, 2, 1, 9, 9, 3), (W.FP32, 3, 8, 1, 1, 9, 9, 3),
-    (W.BF16, 4, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 48, 1, 1, 9, 7, 5)])
+    (W.BF16, 4, 64, 1, 1, 9, 7, 5), (W.FP16, 3, 48, 1, 1, 9, 7, 5), (W.FP32, 3, 8, 1, 1, 33, 32, 37), (W.BF16, 3, 24, 1, 1, 31, 33, 13),
+    (W.FP16, 1, 16, 2, 1, 65, 64, 45), (W.FP32, 4, 16, 1, 0, 36, 35, 41)])
 def test_stem_kernels_at_tile_edges(precision, cin, cout, stride, pad, h, w, b, bn):
     """First layers with few input channels: forward (with the channel sums of the BatchNorm behind it, or a bias and ReLU-free)
-    and weight gradient around their tiles of 64 and 128 pixels, channel groups of 64 and fewer, one to four input channels,
-    stride 2, no border.  Against plain float64 with the bars of the single-layer tests."""
+    and weight gradient around their tiles of 64 and 128 pixels, channel groups of 64 and fewer (8 to 24 with so many pixels that
+    the tiled kernel takes them), one to four input channels, stride 2, no border.  Against plain float64 with the bars of the single-layer tests."""
     from oracle import seqnet_oracle as O
     units = [W.conv(cin, cout, 3, stride, pad=pad, bn=bn, relu=False, bias=not bn), W.flatten_linear_ce(cout, 10)]
     rnd = {W.FP32: lambda v: v, W.BF16: O.round_to_bf16, W.FP16: O.round_to_fp16}[precision]
