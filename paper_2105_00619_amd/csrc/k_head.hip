@@ -21,7 +21,7 @@ __global__ void __launch_bounds__(256) flatten_kernel(const T* __restrict__ x, f
 }
 
 // Global average pool: block (image, group of channels, range of pixels) of TX threads of V channels and TY rows of them;
-// a thread adds every TY-th pixel (eight 16-byte loads in flight), the TY sums of a channel are added in order.  Bound by
+// a thread adds every TY-th pixel (eight 16-byte loads in flight, added in pairs), the TY sums of a channel are added in a fixed order.  Bound by
 // reading the map once.  With one range the mean is stored; with several (few images of many pixels, which would leave most
 // CUs idle: 4 images of 256 x 256 x 128 in fp32 took 1153 us in one block per image and 64 channels, 27 us like this) the
 // sums go to `partial` [ranges][N][C] and gap_finish_kernel adds the ranges in order.
@@ -46,9 +46,8 @@ __global__ void __launch_bounds__(256) gap_sum_kernel(const T* __restrict__ x, f
 #pragma unroll
       for (int u = 0; u < U; ++u) load_f32<T, V>(col + (int64_t)(p + u * TY) * C, v[u]);
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int k = 0; k < V; ++k) s[k] += v[u][k];
+      for (int k = 0; k < V; ++k)
+        s[k] += ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k])) + ((v[4][k] + v[5][k]) + (v[6][k] + v[7][k]));
     }
     for (; p < p1; p += TY) {
       float v[V];
@@ -65,7 +64,10 @@ __global__ void __launch_bounds__(256) gap_sum_kernel(const T* __restrict__ x, f
     const int c = blockIdx.y * W + o;
     if (c >= C) continue;
     float t = 0.f;
-    for (int y = 0; y < TY; ++y) t += red[y * W + o];
+    int y = 0;
+    for (; y + 4 <= TY; y += 4)
+      t += (red[y * W + o] + red[(y + 1) * W + o]) + (red[(y + 2) * W + o] + red[(y + 3) * W + o]);
+    for (; y < TY; ++y) t += red[y * W + o];
     if (partial) partial[((int64_t)blockIdx.z * N + n) * C + c] = t;
     else feat[(int64_t)n * C + c] = t / (float)HW;
   }
@@ -86,20 +88,25 @@ __global__ void __launch_bounds__(256) gap_finish_kernel(const float* __restrict
 //   HG_DW   dw[j][f]     =        sum_n dlogits[n][j] * feat[n][f]  rows j, columns f (column F: the bias gradient), depth N
 //   HG_DX   dfeat[n][f]  =        sum_j dlogits[n][j] * w[j][f]     rows n, columns f, depth J
 // A block of KW wavefronts owns a 32 x 32 tile; wavefront w takes the 16-deep pieces w, w + KW, ... of the depth (of the
-// range blockIdx.z, when the depth is split), four of them requested at a time, and the KW partial tiles are added in
-// wavefront order through LDS.  Bound by latency and by the fp32 MFMA rate (64 cycles per 32 x 32 x 2); a wavefront per
+// range blockIdx.z, when the depth is split), UP of them requested at a time (four, or one where there are fewer), and the KW
+// partial tiles are added in pairs through LDS.  SHORT: short chains of fp32 sums -- every piece (half of one, where registers
+// are free) is summed from zero, those of a request are added in pairs, and that joins the wavefront's total.  One running sum over the
+// depth has up to eight times the error of lanes striding over it (logits relative to 64 bits, 4096 samples, 2048
+// features, 1000 classes: 8.1e-7 against 1.25e-7, SHORT 1.1e-7); SHORT costs the forward product 2 % of its time.
+// The weight gradient needs it where one wavefront has a tile to itself (four share the depth otherwise, as they did when a
+// thread owned an output), the feature gradient nowhere: a thread added all classes in a row.
+// Bound by latency and by the fp32 MFMA rate (64 cycles per 32 x 32 x 2); a wavefront per
 // (sample, class), or a thread per feature, re-read one operand per output: with 4096 samples, 1024 features and 100 classes
 // the three took 62, 172 and 54 us (now 24, 36 and 22), with 512 samples and 2048 features the first 74 us (now 22).
 // Lane l of an MFMA holds row (column) l % 32 at depth l / 32; the 16-deep piece gives lane group g the depths [8g, 8g + 8),
-// so that a lane reads eight neighbours where the depth is the fast index.  VEC: those may be read as two 16-byte loads.
+// so that a lane reads eight neighbours where the depth is the fast index.
 enum { HG_FWD = 0, HG_DW = 1, HG_DX = 2 };
-template <int KIND, int KW>
+template <int KIND, int KW, int UP, bool SHORT>
 __global__ void __launch_bounds__(64 * KW) head_gemm_kernel(const float* __restrict__ a, const float* __restrict__ b,
                                                             const float* __restrict__ bias, float* __restrict__ out,
                                                             float* __restrict__ out_bias, int rows, int cols, int depth, int lda,
                                                             int ldb, int depth_per_range) {
   constexpr bool A_FAST = KIND != HG_DW, B_FAST = KIND == HG_FWD;  // is the depth the fast index of the operand?
-  constexpr int UP = 4;                                            // pieces requested at a time
   __shared__ float red[KW > 1 ? KW * 32 * 32 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, l32 = lane & 31;
   const int row0 = blockIdx.y * 32, col0 = blockIdx.x * 32;
@@ -128,19 +135,44 @@ __global__ void __launch_bounds__(64 * KW) head_gemm_kernel(const float* __restr
       piece(ap, A_FAST, lda, k + u * 16 * KW + 8 * g, full, va[u]);
       piece(bp, B_FAST, ldb, k + u * 16 * KW + 8 * g, full, vb[u]);
     }
-#pragma unroll
-    for (int u = 0; u < n; ++u)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        if (KIND == HG_DW) {
-          const int kk = k + u * 16 * KW + 8 * g + t;
-          vb[u][t] = ones ? (full || kk < d1 ? 1.f : 0.f) : vb[u][t];
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[u][t], vb[u][t], acc, 0, 0, 0);
+    auto bv = [&](int u, int t) {  // (the column of the bias gradient: ones)
+      if (KIND == HG_DW) {
+        const int kk = k + u * 16 * KW + 8 * g + t;
+        return ones ? (full || kk < d1 ? 1.f : 0.f) : vb[u][t];
       }
+      return vb[u][t];
+    };
+    if constexpr (!SHORT) {
+#pragma unroll
+      for (int u = 0; u < n; ++u)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[u][t], bv(u, t), acc, 0, 0, 0);
+    } else {
+      constexpr int HALVES = KW == 8 || n == 1 ? 2 : 1, P = n * HALVES;  // pieces, or halves of them where registers are free
+      head_v16f part[P];
+#pragma unroll
+      for (int q = 0; q < P; ++q)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[q][e] = 0.f;
+#pragma unroll
+      for (int t = 0; t < 8 / HALVES; ++t)
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+          const int u = q / HALVES, tt = q % HALVES * 4 + t;
+          part[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[u][tt], bv(u, tt), part[q], 0, 0, 0);
+        }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        float t = part[0][e] + part[1][e];
+        if constexpr (P >= 4) t += part[2][e] + part[3][e];
+        if constexpr (P == 8) t += (part[4][e] + part[5][e]) + (part[6][e] + part[7][e]);
+        acc[e] += t;
+      }
+    }
   };
   int k = d0 + wave * 16;
-  for (; k + (UP - 1) * 16 * KW + 16 <= d1; k += UP * 16 * KW) pieces(std::integral_constant<int, UP>{}, k, true);
+  if constexpr (UP > 1)
+    for (; k + (UP - 1) * 16 * KW + 16 <= d1; k += UP * 16 * KW) pieces(std::integral_constant<int, UP>{}, k, true);
 #pragma unroll 1
   for (; k < d1; k += 16 * KW) pieces(std::integral_constant<int, 1>{}, k, false);
   auto store = [&](int r, int c, float v) {
@@ -160,9 +192,8 @@ __global__ void __launch_bounds__(64 * KW) head_gemm_kernel(const float* __restr
     for (int e = 0; e < 16; ++e) red[wave * 1024 + (8 * (e >> 2) + 4 * g + (e & 3)) * 32 + l32] = acc[e];
     __syncthreads();
     for (int o = threadIdx.x; o < 1024; o += 64 * KW) {
-      float t = red[o];
-#pragma unroll
-      for (int w = 1; w < KW; ++w) t += red[w * 1024 + o];
+      float t = (red[o] + red[1024 + o]) + (red[2048 + o] + red[3072 + o]);
+      if constexpr (KW == 8) t += (red[4096 + o] + red[5120 + o]) + (red[6144 + o] + red[7168 + o]);
       store(row0 + (o >> 5), col0 + (o & 31), t);
     }
   }
@@ -185,15 +216,30 @@ static void launch_head_gemm(hipStream_t st, const float* a, const float* b, con
   const dim3 grid(ceil_div(cols + (KIND == HG_DW ? 1 : 0), 32), ceil_div(rows, 32), ranges);
   const int64_t tiles = (int64_t)grid.x * grid.y * grid.z;
   const int per = ceil_div(ceil_div(depth, ranges), 16) * 16;
-  // wavefronts per tile: about eight per CU in all, no more than there are pieces
-  int kw = tiles >= 2048 ? 1 : tiles >= 512 ? 4 : 8;
+  // wavefronts per tile: about eight per CU in all, at least four for a depth from 1024 on (short chains of sums), no more than
+  // there are pieces
+  int kw = tiles >= 2048 && (per < 1024 || KIND == HG_DX) ? 1 : tiles >= 512 ? 4 : 8;
   while (kw > 1 && kw * 16 > per) kw = kw == 8 ? 4 : 1;
-#define HG_LAUNCH(KW_)                                                                                                     \
-  OSEQ_LAUNCH((head_gemm_kernel<KIND, KW_>), grid, dim3(64 * KW_), 0, st, a, b, bias, out, out_bias, rows, cols, depth, lda, \
-              ldb, per)
-  if (kw == 8) HG_LAUNCH(8);
-  else if (kw == 4) HG_LAUNCH(4);
-  else HG_LAUNCH(1);
+#define HG_LAUNCH(KW_, UP_, SHORT_)                                                                                             \
+  OSEQ_LAUNCH((head_gemm_kernel<KIND, KW_, UP_, SHORT_>), grid, dim3(64 * KW_), 0, st, a, b, bias, out, out_bias, rows, cols, \
+              depth, lda, ldb, per)
+  if constexpr (KIND == HG_FWD) {
+    const bool four = per >= 64 * kw;
+    if (kw == 8) { if (four) HG_LAUNCH(8, 4, true); else HG_LAUNCH(8, 1, true); }
+    else if (kw == 4) { if (four) HG_LAUNCH(4, 4, true); else HG_LAUNCH(4, 1, true); }
+    else if (four) HG_LAUNCH(1, 4, true);
+    else HG_LAUNCH(1, 1, true);
+  } else {
+    if constexpr (KIND == HG_DW) {
+      if (tiles >= 2048 && per > 128) {
+        if (kw == 4) HG_LAUNCH(4, 4, true); else HG_LAUNCH(1, 4, true);
+        return;
+      }
+    }
+    if (kw == 8) HG_LAUNCH(8, 4, false);
+    else if (kw == 4) HG_LAUNCH(4, 4, false);
+    else HG_LAUNCH(1, 4, false);
+  }
 #undef HG_LAUNCH
 }
 

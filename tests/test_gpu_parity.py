@@ -238,6 +238,24 @@ def test_head_products_at_tile_edges(n, h, w, c, classes, gap, precision):
     assert max(errs.values()) <= TOL[precision], errs
 
 
+@pytest.mark.parametrize("n,h,c,classes", [(1024, 1, 2048, 1000), (2048, 1, 4096, 1000), (4096, 2, 1024, 100)])
+def test_logits_keep_the_error_of_short_chains(n, h, c, classes):
+    """fp32 logits of a head on its own against float64, relative L2.  Sixty-four lanes striding over the features and a
+    butterfly come to 1.0e-7 .. 1.25e-7 here (2^-24 per sum, some 32 to 64 of them in a row), one running sum over the features of
+    a tile to 2.9e-7 .. 8e-7; the bar lies between."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.gap_linear_ce(c, classes)]
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=n, height=h, width=h, channels=c, num_classes=classes)
+    p = (np.random.default_rng(5).standard_normal(t.param_count) / np.sqrt(c)).astype(np.float32)
+    x = np.random.default_rng(6).standard_normal((n, h, h, c)).astype(np.float32)
+    t.set_params(p)
+    got = t.predict(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    t.close()
+    ref = x.astype(np.float64).mean(axis=(1, 2)) @ p[:classes * c].astype(np.float64).reshape(classes, c).T + p[classes * c:]
+    assert np.linalg.norm(got - ref) <= 1.8e-7 * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
 @pytest.mark.parametrize("units,h,w,b", [
     ([W.flatten_linear_ce(64, 10)], 20, 20, 4), ([W.maxpool(), W.flatten_linear_ce(64, 37)], 41, 20, 33), ([W.gap_linear_ce(64, 10)], 96, 97, 2)],
