@@ -11,7 +11,8 @@
 //   other's barriers and epilogues.  The next tile's patch is requested before the MFMAs of the current one and waits in
 //   registers.  Results are channels x pixels: a lane holds four consecutive channels of a pixel, rounded in pairs,
 //   through LDS, stored as 16-byte pieces of whole rows; the storing threads keep the channel sums for the BatchNorm that
-//   follows, one row of block sums per block.
+//   follows, a tile at a time, and every WS3_FLUSH tiles add them up, in double, to one row of block sums (no fp32 chain is
+//   longer than those of the patch kernel's rows of 128 pixels, however many tiles a block has).
 // The data gradient is the same computation on dz with the taps in reverse and the transposed weights.
 // Taken where the result is stored as it is (no bias, ReLU, skip connection or addend: those would need registers that are
 // not there, 128 to 264 bytes of them spilled, 117 against 68 us for an inference layer) and from 131 072 pixels on, two
@@ -44,11 +45,13 @@ constexpr int WS3_PITCH = WS3_C + 8;      // elements per staged position and pe
                                           // neighbouring positions read 16 bytes each from all 64 banks)
 constexpr int WS3_SLOTS = 7;              // 16-byte pieces of a patch per thread
 constexpr int WS3_MAX_POS = WS3_SLOTS * 256 / 8;
+constexpr int WS3_FLUSH = 16;             // tiles per row of sums: one addition per thread and tile
 
 struct Ws3Args {
   int N, srcH, srcW, dstH, dstW, Ng, pad, flip;
   int TI, TR, TC;                 // tile: images x rows x columns of output pixels
   int tiles_r, tiles_c, NT;
+  int flushes;                    // rows of sums per block
 };
 
 // FOLD: src is the z of a BatchNorm + ReLU, `fold` its [4][64] statistics tensor
@@ -143,11 +146,20 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
     const int ti = m / (a.TR * a.TC), rr = m - ti * (a.TR * a.TC), tr = rr / a.TC, tc = rr - tr * a.TC;
     oco[i] = m < TP ? (ti << 16) | (tr << 8) | tc : -1;
   }
-  if (STAT) {
-    const float zero[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) store_f32<float, 4>(&sums[j][tid * 4], zero);
-  }
+  // STAT: the threads' sums as one row; a channel's 32 threads are every eighth
+  auto flush = [&](int row) {
+    int id = tid;
+    asm volatile("" : "+v"(id));  // (addresses made here and not kept in registers over the loop: those would be spilled)
+    if (id < 128) {
+      const int which = id >> 6, c = id & 63;
+      const float* p = &sums[which * 2 + ((c & 7) >> 2)][(c >> 3) * 4 + (c & 3)];
+      double t = 0.0;
+#pragma unroll 4
+      for (int r = 0; r < 32; ++r) t += (double)p[r * 32];
+      stat_partial[(((int64_t)row * gridDim.x + blockIdx.x) * 2 + which) * a.Ng + n0 + c] = (float)t;
+    }
+  };
+  int summed = 0, row = 0;  // tiles in the sums, rows written
 
   int tile = blockIdx.x;  // < NT
   pload(tile);
@@ -184,6 +196,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
         *reinterpret_cast<u32x2*>(&stg[(pgrp * 64 + p * 32 + l32) * PITCH + c]) = o;
       }
     if (next < a.NT) pstore();
+    if (STAT && summed == WS3_FLUSH) { flush(row++); summed = 0; }
     __syncthreads();
     {
       int ii, y0, x0;
@@ -204,9 +217,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
         one2[0] = from_f32<T>(1.f); one2[1] = from_f32<T>(1.f);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {  // channels 4j .. 4j + 3 of the thread's eight
-          float s4[4], q4[4];
-          load_f32<float, 4>(&sums[j][tid * 4], s4);
-          load_f32<float, 4>(&sums[2 + j][tid * 4], q4);
+          float s4[4] = {0.f, 0.f, 0.f, 0.f}, q4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int i = 0; i < 4; i += 2)
 #pragma unroll
@@ -216,24 +227,29 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
               s4[k] = Dot2<T>::run(p2, one2, s4[k]);
               q4[k] = Dot2<T>::run(p2, p2, q4[k]);
             }
+          // (the tile from zero, then the total: squares of 16-bit values added to a long sum one pair at a time are rounded
+          // down more often than up -- 1.3e-4 of the variance in fp16 where the mean is 40 deviations off)
+          if (summed) {
+            float s0[4], q0[4];
+            load_f32<float, 4>(&sums[j][tid * 4], s0);
+            load_f32<float, 4>(&sums[2 + j][tid * 4], q0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { s4[k] += s0[k]; q4[k] += q0[k]; }
+          }
           store_f32<float, 4>(&sums[j][tid * 4], s4);
           store_f32<float, 4>(&sums[2 + j][tid * 4], q4);
         }
+        ++summed;
       }
     }
     if (next >= a.NT) break;
     tile = next;
   }
-  if (STAT) {  // a channel's 32 threads (every eighth), added in order
+  if (STAT) {
     __syncthreads();
-    if (tid < 128) {
-      const int which = tid >> 6, c = tid & 63;
-      const float* p = &sums[which * 2 + ((c & 7) >> 2)][(c >> 3) * 4 + (c & 3)];
-      float t = 0.f;
-#pragma unroll 8
-      for (int r = 0; r < 32; ++r) t += p[r * 32];
-      stat_partial[((int64_t)blockIdx.x * 2 + which) * a.Ng + n0 + c] = t;
-    }
+    flush(row++);
+    if (row < a.flushes && tid < 128)  // a block with one tile less than others may have a row less
+      stat_partial[(((int64_t)row * gridDim.x + blockIdx.x) * 2 + (tid >> 6)) * a.Ng + n0 + (tid & 63)] = 0.f;
   }
 }
 
@@ -269,6 +285,7 @@ int ws3_blocks(const Ws3Args& a) {  // two blocks per CU over all channel groups
   const int b = WS3_BLOCKS / groups > 0 ? WS3_BLOCKS / groups : 1;
   return a.NT < b ? a.NT : b;
 }
+int ws3_flushes(const Ws3Args& a) { return ceil_div(ceil_div(a.NT, ws3_blocks(a)), WS3_FLUSH); }
 
 template <class T>
 void launch_ws3(hipStream_t st, const void* src, const void* wmat, const float* fold, void* out, float* stat_partial, const Ws3Args& a) {
@@ -290,7 +307,9 @@ static bool ws3_args(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R,
   if ((int64_t)(dstH + 2) * (dstW + 2) * 64 * (int64_t)(srcC > Ng ? srcC : Ng) >= ((int64_t)1 << 31)) return false;
   a = Ws3Args{};
   a.N = N; a.dstH = dstH; a.dstW = dstW; a.Ng = Ng;
-  return ws3_geometry(N, dstH, dstW, a);
+  if (!ws3_geometry(N, dstH, dstW, a)) return false;
+  a.flushes = ws3_flushes(a);
+  return true;
 }
 bool conv_ws3x3_ok(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride) {
   Ws3Args a;
@@ -298,7 +317,7 @@ bool conv_ws3x3_ok(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R, i
 }
 int conv_ws3x3_stat_blocks(const ConvGeom& g) {
   Ws3Args a;
-  return ws3_args(DT_BF16, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, a) ? ws3_blocks(a) : 0;
+  return ws3_args(DT_BF16, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, a) ? ws3_blocks(a) * a.flushes : 0;
 }
 
 void launch_conv_fwd_ws3x3(hipStream_t st, int dt, const void* x, const void* w, void* out, float* stat_partial, const ConvGeom& g,

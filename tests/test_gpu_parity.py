@@ -387,6 +387,43 @@ def test_more_than_65536_images(precision, cin, cout, ksize, stride, hw, b):
     assert_parity(units, hw, hw, r["grads"], g, TOL[precision])
 
 
+@pytest.mark.parametrize("precision,b,hw,mean", [
+    (W.FP16, 1025, 32, 5.0), (W.BF16, 1037, 64, 5.0), (W.FP16, 512, 32, 40.0), (W.BF16, 190, 27, 5.0)])
+def test_statistics_of_many_tiles_keep_the_variance(precision, b, hw, mean):
+    """Channel sums of the weights-stationary 3x3 kernel where a block has many tiles (up to 65, one more in some blocks than in
+    others): the convolution copies its input, whose channels have means of 5 or 40 deviations, so that the running variance
+    after one step is that of the input.  The second moment is (1 + mean^2) times the variance; half a unit of its last fp32
+    place, 2^-25, is allowed as relative error (root mean square over the channels; a running sum over all tiles has 2 to 9 times
+    that)."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(64, 64, 3, bn=True, relu=False, bias=False), W.gap_linear_ce(64, 10)]
+    t = SeqTrainer(units, k_segments=1, precision=precision, batch=b, height=hw, width=hw, channels=64, num_classes=10,
+                   bn_momentum=1.0, loss_scale_init=1.0, guard_bytes=1 << 16)
+    p = torch.zeros(t.param_count, device="cuda")
+    c = torch.arange(64)
+    p[:64 * 9 * 64].view(64, 3, 3, 64)[c, 1, 1, c] = 1.0
+    p[64 * 9 * 64:64 * 9 * 64 + 64] = 1.0  # gamma
+    t.set_params(p)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((b, hw, hw, 64), generator=g, device="cuda").add_(mean)
+    x = x.to(torch.bfloat16 if precision == W.BF16 else torch.float16).float()
+    t.step(x, torch.zeros(b, dtype=torch.int32, device="cuda"), 0.0)
+    assert t.guards_intact()
+    running = torch.from_numpy(t.running_stats()).double().cuda()
+    t.close()
+    s, q = torch.zeros(2, 64, dtype=torch.float64, device="cuda")
+    for part in x.split(64):
+        d = part.double().view(-1, 64)
+        s += d.sum(0)
+        q += (d * d).sum(0)
+    n = b * hw * hw
+    var = (q / n - (s / n) ** 2) * n / (n - 1)
+    err = float(((running[64:] - var) / var).pow(2).mean().sqrt())
+    assert float(((running[:64] - s / n) / (s / n)).abs().max()) <= 2.0 ** -23
+    assert err <= (1.0 + mean * mean) * 2.0 ** -25, err
+
+
 def _unit_trace(tr, xd, n_units):
     """GPU output of every body unit the plan writes to memory: {unit: float64 array}."""
     from paper_2105_00619_amd.binding import OptorchError
