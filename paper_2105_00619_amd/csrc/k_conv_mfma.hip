@@ -208,15 +208,21 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   unsigned okm[2] = {0u, 0u};  // per generation: bit i set if A chunk i is inside the image
   const int kt0 = SPLIT ? blockIdx.z * a.kt_per_split : 0;
   int tapi = kt0 * BK / srcC, c0 = kt0 * BK - tapi * srcC;  // next depth tile to load: entry of the tap list, first channel
-  auto gload = [&, srcW, srcC, S_, stride](auto P) {
-    constexpr int p = decltype(P)::value;
-    const int tap = a.cls ? (ctaps >> (8 * tapi)) & 0xff : tapi;  // filter tap r*S + s of this depth tile
-    const int r = S_ == 3 ? (tap * 11) >> 5 : tap;                // tap / S, S being 3 or 1
+  int tap = 0;         // its filter tap r * S + s ...
+  int64_t tdist = 0;   // ... and how far that lies from tap (0, 0) (two rows of an image may be more than 2^31 elements)
+  auto next_tap = [&, srcW, srcC, S_, stride]() {
+    tap = a.cls ? (ctaps >> (8 * (tapi & 3))) & 0xff : tapi;
+    const int r = S_ == 3 ? (tap * 11) >> 5 : tap;  // tap / S, S being 3 or 1
     const int s = tap - r * S_;
-    const int kkw = tap * srcC + c0;                              // its depth offset in the weight rows
     const int sh = MODE == IG_DGRAD && stride == 2 ? 1 : 0;
-    const int d = ((r >> sh) * srcW + (s >> sh)) * srcC;
-    const int toff = (MODE == IG_DGRAD ? -d : d) + c0;
+    const int64_t d = ((int64_t)(r >> sh) * srcW + (s >> sh)) * srcC;
+    tdist = MODE == IG_DGRAD ? -d : d;
+  };
+  next_tap();
+  auto gload = [&, srcC](auto P) {
+    constexpr int p = decltype(P)::value;
+    const int kkw = tap * srcC + c0;  // depth offset in the weight rows
+    const int64_t toff = tdist + c0;
     unsigned m = 0u;
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
@@ -228,7 +234,7 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
 #pragma unroll
     for (int i = 0; i < B_CH; ++i) rb[p][i] = *reinterpret_cast<const Chunk*>(brow[i] + kkw);
     c0 += BK;
-    if (c0 >= srcC) { c0 = 0; ++tapi; }
+    if (c0 >= srcC) { c0 = 0; ++tapi; next_tap(); }
   };
   auto sstore = [&](auto P, int stage) {  // register generation p -> LDS stage
     constexpr int p = decltype(P)::value;

@@ -332,6 +332,48 @@ def test_gathered_convolutions_at_the_border(precision, cin, cout, ksize, stride
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
 
 
+def test_gathered_convolution_of_an_image_with_rows_of_2_30_elements():
+    """Strided 3x3 layer on a map of 2 x 2^20 pixels and 1024 channels: the third filter row lies 2^31 elements behind the first.
+    Output columns against float64, the weight gradient of taps in each filter row likewise (a bias gradient is the sum of dz,
+    so dz is known from a head with one weight)."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    w, c, q = 1 << 20, 1024, 1 << 19
+    units = [W.conv(c, 64, 3, 2, bn=False, relu=False, bias=True), W.gap_linear_ce(64, 2)]
+    t = SeqTrainer(units, k_segments=1, precision=W.FP16, batch=1, height=2, width=w, channels=c, num_classes=2, loss_scale_init=1024.0)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    p = torch.randn(t.param_count, generator=g, device="cuda") * 0.02
+    p[:64 * 9 * c] = p[:64 * 9 * c].half().float()
+    t.set_params(p)
+    x = torch.empty((1, 2, w, c), device="cuda")
+    x[0, 0].normal_(generator=g)
+    x[0, 1].normal_(generator=g)
+    got = t.unit_output(x, 0)[0, 0]
+    wt = p[:64 * 9 * c].view(64, 3, 3, c).double()
+    for col in (0, 1, 2, 77777, q // 2, q - 2, q - 1):
+        ref = p[64 * 9 * c:64 * 9 * c + 64].double()
+        for r in (1, 2):
+            for s in range(3):
+                xc = 2 * col + s - 1
+                if 0 <= xc < w:
+                    ref = ref + wt[:, r, s] @ x[0, r - 1, xc].half().double()
+        assert float((got[col].double() - ref).norm() / ref.norm()) <= 1e-3, col
+    grads = torch.empty(t.param_count, device="cuda")
+    r = t.step(x, torch.zeros(1, dtype=torch.int32, device="cuda"), 0.0, grads=grads)
+    assert not r["skipped"]
+    t.close()
+    # dz is the same at every pixel (average pool): dw[k, r, s] = dbias[k] * mean over the pixels of x under the tap, but for
+    # the rounding of dz, which is about 2e-5 here after the loss scale: half a spacing of fp16's denormals is 1.5e-3 of that
+    db = grads[64 * 9 * c:64 * 9 * c + 64].double()
+    dw = grads[:64 * 9 * c].view(64, 3, 3, c).double()
+    for row, s in ((1, 1), (2, 1)):
+        mean = torch.zeros(c, dtype=torch.float64, device="cuda")
+        for part in x[0, row - 1, ::2].split(1 << 16):
+            mean += part.half().double().sum(0)
+        ref = db[:, None] * (mean / q)[None, :]
+        assert float((dw[:, row, s] - ref).norm() / ref.norm()) <= 2e-2, (row, s)
+
+
 @pytest.mark.parametrize("precision,cout,pad,h,w,b", [
     (W.BF16, 64, 1, 32, 32, 128), (W.FP16, 128, 1, 37, 45, 79), (W.BF16, 64, 0, 12, 11, 2800), (W.FP16, 192, 1, 8, 8, 2051),
     (W.BF16, 64, 1, 5, 3, 8741), (W.FP16, 64, 1, 300, 70, 7), (W.BF16, 128, 1, 1, 400, 331), (W.FP16, 64, 1, 16, 17, 515)])
