@@ -16,9 +16,10 @@
 // The data gradient is the same computation on dz with the taps in reverse and the transposed weights.
 // Taken where the result is stored as it is (no bias, ReLU, skip connection or addend: those would need registers that are
 // not there, 128 to 264 bytes of them spilled, 117 against 68 us for an inference layer) and from 131 072 pixels on, two
-// tiles a block.  64 -> 64 channels, bf16, patch kernel -> this one, us at 4.2 M pixels (4096 x 32 x 32): data gradient
-// 478 -> 362, forward on a folded BatchNorm 513 -> 383, with the channel sums 562 -> 463; at 262 144: 36.5 -> 36, 38.6 -> 37,
-// 41 -> 41 (the weights' way into the registers is then a third of it).
+// tiles a block; see ws3_args for maps that the patch kernel's tiles fill.  64 -> 64 channels, bf16, patch kernel -> this
+// one, us at 4.2 M pixels (4096 x 32 x 32): data gradient 478 -> 362, forward on a folded BatchNorm 513 -> 383, with the
+// channel sums 562 -> 463.  Forward, sums finished, plus data gradient at the line, us a layer (a third is the weights' way
+// into the registers): 137 984 pixels of 112 x 112 maps 82 -> 59, 125 440 of 56 x 56 67 -> 56, 132 300 of 21 x 21 58 -> 57.
 #include "bn_fold.h"
 #include "dev_common.h"
 #include "epilogue.h"
@@ -39,7 +40,7 @@ template <> struct Mma3<f16_t> {
   __device__ static __forceinline__ A run(V a, V b, A c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 
-constexpr int64_t WS3_MIN_PIXELS = 131072;
+constexpr int64_t WS3_MIN_PIXELS = 131072, WS3_MIN_WHOLE = 163840;
 constexpr int WS3_C = 64, WS3_PX = 128, WS3_BLOCKS = 512;
 constexpr int WS3_PITCH = WS3_C + 8;      // elements per staged position and per staged output row (144 bytes: 16
                                           // neighbouring positions read 16 bytes each from all 64 banks)
@@ -305,6 +306,12 @@ static bool ws3_args(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R,
   if (dt == DT_F32 || R != 3 || S != 3 || stride != 1 || srcC != WS3_C || Ng % 64 != 0 || Ng > 64 * WS3_BLOCKS) return false;
   if ((int64_t)N * dstH * dstW < WS3_MIN_PIXELS) return false;
   if ((int64_t)(dstH + 2) * (dstW + 2) * 64 * (int64_t)(srcC > Ng ? srcC : Ng) >= ((int64_t)1 << 31)) return false;
+  // Maps that tiles of 128 pixels fill (32 x 32, 8 x 8): the patch kernel wastes nothing there, and with less than two and a
+  // half tiles a block it is ahead.  Four 64 -> 64 layers of a step, forward, sums and data gradients, us in bf16 and fp16,
+  // patch kernel and this one: 131 072 pixels 192, 197 and 200, 200; 163 840: 214, 221 and 216, 217; 196 608: 242, 254 and
+  // 237, 236; 131 072 of 8 x 8 maps: 193, 200 and 201, 199.
+  const bool whole = dstH * dstW <= WS3_PX ? WS3_PX % (dstH * dstW) == 0 : WS3_PX % dstW == 0 && dstH % (WS3_PX / dstW) == 0;
+  if (whole && (int64_t)N * dstH * dstW * (Ng / 64) < WS3_MIN_WHOLE) return false;
   a = Ws3Args{};
   a.N = N; a.dstH = dstH; a.dstW = dstW; a.Ng = Ng;
   if (!ws3_geometry(N, dstH, dstW, a)) return false;

@@ -375,10 +375,10 @@ def test_gathered_convolution_of_an_image_with_rows_of_2_30_elements():
 
 
 @pytest.mark.parametrize("precision,cout,pad,h,w,b", [
-    (W.BF16, 64, 1, 32, 32, 128), (W.FP16, 128, 1, 37, 45, 79), (W.BF16, 64, 0, 12, 11, 2800), (W.FP16, 192, 1, 8, 8, 2051),
+    (W.BF16, 64, 1, 32, 32, 128), (W.BF16, 64, 1, 32, 32, 163), (W.FP16, 64, 1, 8, 8, 2563), (W.FP16, 128, 1, 37, 45, 79), (W.BF16, 64, 0, 12, 11, 2800), (W.FP16, 192, 1, 8, 8, 2051),
     (W.BF16, 64, 1, 5, 3, 8741), (W.FP16, 64, 1, 300, 70, 7), (W.BF16, 128, 1, 1, 400, 331), (W.FP16, 64, 1, 16, 17, 515)])
 def test_weights_stationary_3x3_at_tile_edges(precision, cout, pad, h, w, b):
-    """3x3 layers with 64 input channels and 131 072 pixels or more: tiles of whole rows and of parts of rows, several images a
+    """3x3 layers with 64 input channels and 131 072 pixels or more (163 840 where tiles of 128 pixels fill the map): tiles of whole rows and of parts of rows, several images a
     tile with some missing in the last, one to three channel groups, with and without a border, images larger than a tile either
     way.  The first layer is for the forward pass with the sums of its BatchNorm, the second for the one whose bias beside the
     BatchNorm keeps it off that kernel, the third's data gradient for the weight gradients in front of it.  No ReLU, so against
