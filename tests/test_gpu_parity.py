@@ -110,7 +110,14 @@ LAYER_NETS = {
     "whole_image_tiles_8x8_odd": (256, 8, 193, [W.conv(256, 256), W.conv(256, 256), W.gap_linear_ce(256, 10)]),
     "whole_image_tiles_4x4_odd": (512, 4, 67, [W.conv(512, 512), W.conv(512, 512), W.gap_linear_ce(512, 10)]),
     # 64 channels, 131 072 pixels and more: the 3x3 kernel that keeps its weights, forward on a folded BatchNorm
+    # (also on odd maps: tiles of whole rows with the last ones cut, tiles of parts of rows, several images a tile)
     "stationary_64_at24": (64, 24, 229, [W.basic_block(64, 64), W.gap_linear_ce(64, 10)]),
+    "stationary_64_at21": (64, 21, 299, [W.basic_block(64, 64), W.gap_linear_ce(64, 10)]),
+    "stationary_64_at75": (64, 75, 24, [W.conv(64, 64), W.conv(64, 64), W.gap_linear_ce(64, 10)]),
+    "stationary_64_at5": (64, 5, 5247, [W.conv(64, 64), W.conv(64, 64), W.gap_linear_ce(64, 10)]),
+    # BatchNorm + ReLU under the average pool, whose gradient is read per image, on odd maps
+    "average_pool_odd_15": (64, 15, 21, [W.conv(64, 128), W.gap_linear_ce(128, 10)]),
+    "average_pool_odd_7": (24, 7, 33, [W.conv(24, 24), W.gap_linear_ce(24, 10)]),
     "pointwise_bottlenecks": (64, 16, 64, [W.conv(64, 64, ksize=1), W.bottleneck(64, 256, 1), W.bottleneck(256, 512, 2),
                                            W.gap_linear_ce(512, 10)]),
 }
@@ -120,7 +127,8 @@ LAYER_NETS = {
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
 def test_layers_at_benchmark_shapes_match_oracle(name, precision):
     cin, hw, b, units = LAYER_NETS[name]
-    if precision == W.FP32 and name in ("pointwise_large_tile", "pointwise_rows_128", "pointwise_rows_256", "pointwise_rows_bias"):
+    if precision == W.FP32 and name in ("pointwise_large_tile", "pointwise_rows_128", "pointwise_rows_256", "pointwise_rows_bias",
+                                        "stationary_64_at21", "stationary_64_at75", "stationary_64_at5"):
         pytest.skip("the kernel this case is for exists in the 16-bit modes only")
     p, x, y = _inputs(units, b, hw, hw, 10, seed=9, channels=cin)
     r, info = gpu_step(units, p, x, y, precision=precision, k=2, classes=10, loss_scale_init=_scale(precision))
@@ -400,8 +408,11 @@ def test_weights_stationary_3x3_at_tile_edges(precision, cout, pad, h, w, b):
     assert not r["skipped"]
     loss, g = oracle_step(units, p, x, y)
     # a constant in front of a BatchNorm has no gradient: the bias, and away from the border the beta of the layer before (the
-    # BatchNorm behind the next convolution takes it out); what is left there is compared with the whole gradient's RMS
-    errs = plain_errors(units, h, w, r["grads"], g, zero_names=("u1.b", "u0.beta", "u1.beta"))
+    # BatchNorm behind the next convolution takes it out).  A beta whose float64 gradient is below a tenth of the whole
+    # gradient's RMS is compared with that RMS, any other by itself.
+    rms = np.linalg.norm(g) / np.sqrt(g.size)
+    low = [n for n in ("u0.beta", "u1.beta") if np.linalg.norm(g[slices[n]]) < 0.1 * rms * np.sqrt(g[slices[n]].size)]
+    errs = plain_errors(units, h, w, r["grads"], g, zero_names=["u1.b"] + low)
     assert max(errs.values()) <= TOL[precision], errs
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
 
