@@ -803,8 +803,8 @@ static bool direct_small(const ConvGeom& g) {
   const int64_t most = (int64_t)1 << 30;
   return (int64_t)g.N * g.P * g.Q * g.K < most && (int64_t)g.N * g.H * g.W * g.C < most && (int64_t)g.K * g.R * g.S * g.C < most;
 }
-// the choice of index type and vector width (V: channels per load; their tensors start on 16-byte boundaries or, the
-// weights, at any element: `aligned` says whether those allow it)
+// the choice of index type and vector width (VEC: four channels per load; the caller has looked at the channel count and at
+// the tensors' alignment, weights may start at any element)
 #define DIRECT_LAUNCH(KERNEL, T, VEC, ...)                                                       \
   {                                                                                              \
     if (direct_small(g)) {                                                                       \

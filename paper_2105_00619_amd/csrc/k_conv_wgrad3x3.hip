@@ -396,8 +396,9 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   if (a.TP * 2 < cap) return false;  // short sub-tiles: too little work between barriers
   a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
   // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD; in fp32 where a
-  // sub-tile is part of an image, whose addresses take longer: 128 -> 128 channels at 64 x 64, 262 144 pixels, 847 us with 64
-  // and 690 with 128, but 92.5 and 95 for 128 -> 256 on whole 8 x 8 images), unless the blocks
+  // sub-tile is part of an image, whose addresses take longer: 262 144 pixels, 128 -> 128 channels, us with 64 and with 128 a
+  // block: 756 and 639 on 64 x 64 maps, 670 and 605 on 32 x 32, 678 and 617 on 16 x 16; on whole 8 x 8 images 638 and 609,
+  // and 92.5 and 95 for 128 -> 256 at 16 384 pixels, with twice the partial sums), unless the blocks
   // would then get fewer than g_w9_wide_min sub-tiles each: a block's accumulators (9 taps x 64*MI x 64 floats) are
   // written out once per pixel range and read again by the reduction, and with few sub-tiles per range that traffic
   // outweighs the operand reuse (128->128 at 16x16, batch 256, bf16: 49.6 us with 64-channel blocks, 48.1 with
