@@ -516,10 +516,14 @@ __global__ void __launch_bounds__(256) bn_bwd_apply_kernel(const T* __restrict__
 #pragma unroll
     for (int u = 0; u < RT; ++u) {
       const int64_t off = (r + (int64_t)u * TY) * g.C + c0;
-      load_f32<T, V>(GV ? da + (int64_t)g.div_hw.div((uint32_t)(r + (int64_t)u * TY)) * g.C + c0 : da + off, va[u]);
+      if (!GV) load_f32<T, V>(da + off, va[u]);
       load_f32<T, V>(z + off, vz[u]);
       if (AOUT) load_f32<T, V>(aout + off, vo[u]);
       mb[u] = MS == 2 ? mask[(r + (int64_t)u * TY) * CG + cg] : 0u;
+    }
+    if (GV) {  // (the division in its address stays behind the loads from memory)
+#pragma unroll
+      for (int u = 0; u < RT; ++u) load_f32<T, V>(da + (int64_t)g.div_hw.div((uint32_t)(r + (int64_t)u * TY)) * g.C + c0, va[u]);
     }
 #pragma unroll
     for (int u = 0; u < RT; ++u) one(va[u], vz[u], vo[u], mb[u], rz[u], rs[u]);
