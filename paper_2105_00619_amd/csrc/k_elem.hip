@@ -251,12 +251,12 @@ __device__ __forceinline__ void partial_sums(const float* __restrict__ partial, 
 // Many row blocks (a convolution over a large batch writes one row of sums per 128 pixels): the rows are first added
 // in STAT_FOLD_ROWS fixed ranges, with coalesced reads (thread = channel, four rows in flight per block), so that the
 // finishing kernel, in which a block of 256 threads walks the columns of four channels (of one, where their number is not a
-// multiple of four), has only that many rows left.  Kernel times a layer, us, without and with the fold (one launch more,
-// and room for its rows), 64 channels and 256: 2048 rows 10.3, 9.4 and 9.3, 8.8; 3072: 12.8, 11.8 and 8.8, 9.3; 4096: 15.3,
-// 14.2 and 8.8, 9.0; 16 384: 52, 44 and 17, 13.  Below 2048 the fold loses; the line is where it pays for its launch with
-// something to spare.
+// multiple of four), has only that many rows left.  The line is where the launch more pays at every width (at 2048 rows it
+// does in such a step, but not in the bottleneck network at 8 x 8).  A step of four 1x1 layers, bf16, us without and with the
+// fold, 64, 256 and 1024 channels: 1024 rows 322, 950 and 320, 954; 2048: 488, 1693, 9467 and 476, 1677, 9440; 3072: 650,
+// 2456, 14314 and 623, 2445, 14295; 4095: 822, 3171 and 785, 3135.
 constexpr int STAT_FOLD_ROWS = 64;
-constexpr int STAT_FOLD_MIN = 4096;
+constexpr int STAT_FOLD_MIN = 3072;
 __global__ void __launch_bounds__(256) stat_fold_kernel(const float* __restrict__ partial, int nblk, int C, int rows_per_range,
                                                         float* __restrict__ folded) {
   __shared__ double red[2][4][64];
