@@ -1,4 +1,4 @@
-// Implicit-GEMM convolution on the matrix cores (MFMA 32x32, fp32 accumulate) for gfx950.
+// Implicit-GEMM convolution on the matrix cores (MFMA 32x32, fp32 accumulate; fp32 operands as three bf16 planes) for gfx950.
 //
 // Forward and data gradient share one kernel: out[m][n] = sum_kk A[m][kk] * B[n][kk], where
 //   m  = output pixel (image, row, col),      n = output channel of this GEMM,
@@ -15,11 +15,13 @@
 // Each lane keeps 32 bytes of every operand row per depth tile; global loads for tile t+1 are issued before the
 // MFMAs of tile t (register prefetch + two LDS buffers, one barrier per tile).
 #include <algorithm>
+#include <type_traits>
 
 #include "bn_fold.h"
 #include "dev_common.h"
 #include "epilogue.h"
 #include "kernels.h"
+#include "split32.h"
 
 namespace oseq {
 
@@ -47,75 +49,106 @@ struct IGemmArgs {
   const uint8_t* amask;   // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
 };
 
-template <class T> struct Frag;  // 32 bytes of one operand row, and the MFMAs that consume it
+// How operands lie in LDS and the MFMAs that consume them.  E: staged element; BK: depth of a tile; PITCH: staged elements
+// per operand row: BK values (Split32: the three bf16 planes of BK values one after the other) and 16 bytes that spread the rows
+// over the banks, 80 bytes (Split32: 112).  put: 16 bytes of the tensor, the piece `v` of a row, to LDS.
+// A lane holds BK / 2 of a row's values; they are used up in PHASES groups of MFMAs (steps(ph) each), after each of which
+// the registers that it was the last to read are loaded with the next tile's (load(ph)).
+// ACCS: accumulators per output; depth tile i goes to number i % ACCS.  Split32 has two: the 16-bit MFMA drops what lies eight
+// or more bits below the last one of its largest term, towards minus infinity, so that a sum of 400 MFMAs is too low by 6e-8 of
+// the results' deviation -- a tenth of its error, but the same for every pixel, so that a sum over pixels behind it keeps it.  The
+// second accumulator takes its tiles with the weights negated and is subtracted in the end (6e-9 left of nine taps; a 3x3 layer of
+// 128 channels is off by 3.6e-7 of its deviation that way, 5.1e-7 with one accumulator, 6.0e-7 on the fp32 MFMA).
+// X: the operands' form: the storage type itself, or for fp32 Split32: the 16-bit MFMAs (split32.h).
+struct Split32 {};
+template <class X> struct Frag;
 template <> struct Frag<float> {
-  static constexpr int BK = 16;
-  v4f lo, hi;
-  __device__ __forceinline__ void load(const float* p) { lo = *(const v4f*)p; hi = *(const v4f*)(p + 4); }
-  __device__ __forceinline__ void load_lo(const float* p) { lo = *(const v4f*)p; }
-  __device__ __forceinline__ void load_hi(const float* p) { hi = *(const v4f*)(p + 4); }
-  static constexpr int HALF_STEPS = 4;  // MFMAs per operand half
-  __device__ static __forceinline__ void mma_half(const Frag& a, const Frag& b, v16f& c, int half, int t) {
-    c = half == 0 ? __builtin_amdgcn_mfma_f32_32x32x2f32(a.lo[t], b.lo[t], c, 0, 0, 0)
-                  : __builtin_amdgcn_mfma_f32_32x32x2f32(a.hi[t], b.hi[t], c, 0, 0, 0);
+  typedef float E;
+  static constexpr int BK = 16, PITCH = BK + 4, ACCS = 1;
+  v4f p[2];
+  __device__ static __forceinline__ void put(E* row, int v, const Chunk& c, bool zero, bool = false) {
+    *reinterpret_cast<Chunk*>(row + v * 4) = zero ? zero_chunk() : c;
   }
   static constexpr int lane_off(int g) { return g * 8; }
-  static constexpr int STEPS = 8;
-  __device__ static __forceinline__ void mma_step(const Frag& a, const Frag& b, v16f& c, int t) {
-    c = t < 4 ? __builtin_amdgcn_mfma_f32_32x32x2f32(a.lo[t & 3], b.lo[t & 3], c, 0, 0, 0)
-              : __builtin_amdgcn_mfma_f32_32x32x2f32(a.hi[t & 3], b.hi[t & 3], c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.lo[t], b.lo[t], c, 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.hi[t], b.hi[t], c, 0, 0, 0);
+  static constexpr int PHASES = 2;
+  static constexpr int steps(int) { return 4; }
+  __device__ __forceinline__ void load(const E* r, int ph) { p[ph] = *(const v4f*)(r + ph * 4); }
+  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c, int ph, int st) {
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.p[ph][st], b.p[ph][st], c, 0, 0, 0);
   }
 };
-template <> struct Frag<bf16_t> {
-  static constexpr int BK = 32;
-  v8bf lo, hi;
-  __device__ __forceinline__ void load(const bf16_t* p) { lo = *(const v8bf*)p; hi = *(const v8bf*)(p + 8); }
-  __device__ __forceinline__ void load_lo(const bf16_t* p) { lo = *(const v8bf*)p; }
-  __device__ __forceinline__ void load_hi(const bf16_t* p) { hi = *(const v8bf*)(p + 8); }
-  static constexpr int HALF_STEPS = 1;
-  __device__ static __forceinline__ void mma_half(const Frag& a, const Frag& b, v16f& c, int half, int) {
-    c = half == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, b.lo, c, 0, 0, 0)
-                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, c, 0, 0, 0);
+template <> struct Frag<Split32> {
+  typedef bf16_t E;
+  static constexpr int BK = 16, PITCH = 3 * BK + 8, ACCS = 2;
+  v8bf p[3];
+  __device__ static __forceinline__ void put(E* row, int v, const Chunk& c, bool zero, bool neg = false) {
+    u32x2_t q[3];
+    split32(zero ? zero_chunk() : neg ? __builtin_bit_cast(Chunk, -__builtin_bit_cast(v4f, c)) : c, q);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2_t*>(row + k * BK + v * 4) = q[k];
+  }
+  static constexpr int lane_off(int g) { return g * 8; }
+  static constexpr int PHASES = 3;
+  static constexpr int steps(int ph) { return 3 - ph; }
+  __device__ __forceinline__ void load(const E* r, int ph) { p[2 - ph] = *(const v8bf*)(r + (2 - ph) * BK); }
+  // the smallest planes first, so that their registers are free first; the tile begins with the product that does not need
+  // the planes which were loaded last
+  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c, int ph, int st) {
+    constexpr int QA[3][3] = {{1, 2, 0}, {1, 0, 0}, {0, 0, 0}}, QB[3][3] = {{1, 0, 2}, {0, 1, 0}, {0, 0, 0}};
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[QA[ph][st]], b.p[QB[ph][st]], c, 0, 0, 0);
+  }
+};
+template <class T, class V> struct Frag16 {
+  typedef T E;
+  static constexpr int BK = 32, PITCH = BK + 8, ACCS = 1;
+  V p[2];
+  __device__ static __forceinline__ void put(E* row, int v, const Chunk& c, bool zero, bool = false) {
+    *reinterpret_cast<Chunk*>(row + v * 8) = zero ? zero_chunk() : c;
   }
   static constexpr int lane_off(int g) { return g * 16; }
-  static constexpr int STEPS = 2;
-  __device__ static __forceinline__ void mma_step(const Frag& a, const Frag& b, v16f& c, int t) {
-    c = t == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, b.lo, c, 0, 0, 0)
-               : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, b.lo, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, c, 0, 0, 0);
+  static constexpr int PHASES = 2;
+  static constexpr int steps(int) { return 1; }
+  __device__ __forceinline__ void load(const E* r, int ph) { p[ph] = *(const V*)(r + ph * 8); }
+};
+template <> struct Frag<bf16_t> : Frag16<bf16_t, v8bf> {
+  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c, int ph, int) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[ph], b.p[ph], c, 0, 0, 0);
   }
 };
-template <> struct Frag<f16_t> {
-  static constexpr int BK = 32;
-  v8h lo, hi;
-  __device__ __forceinline__ void load(const f16_t* p) { lo = *(const v8h*)p; hi = *(const v8h*)(p + 8); }
-  __device__ __forceinline__ void load_lo(const f16_t* p) { lo = *(const v8h*)p; }
-  __device__ __forceinline__ void load_hi(const f16_t* p) { hi = *(const v8h*)(p + 8); }
-  static constexpr int HALF_STEPS = 1;
-  __device__ static __forceinline__ void mma_half(const Frag& a, const Frag& b, v16f& c, int half, int) {
-    c = half == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a.lo, b.lo, c, 0, 0, 0)
-                  : __builtin_amdgcn_mfma_f32_32x32x16_f16(a.hi, b.hi, c, 0, 0, 0);
-  }
-  static constexpr int lane_off(int g) { return g * 16; }
-  static constexpr int STEPS = 2;
-  __device__ static __forceinline__ void mma_step(const Frag& a, const Frag& b, v16f& c, int t) {
-    c = t == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a.lo, b.lo, c, 0, 0, 0)
-               : __builtin_amdgcn_mfma_f32_32x32x16_f16(a.hi, b.hi, c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.lo, b.lo, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.hi, b.hi, c, 0, 0, 0);
+template <> struct Frag<f16_t> : Frag16<f16_t, v8h> {
+  __device__ static __forceinline__ void mma(const Frag& a, const Frag& b, v16f& c, int ph, int) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.p[ph], b.p[ph], c, 0, 0, 0);
   }
 };
+
+// fp32: the two accumulators made one; is any of a thread's sums not finite?
+template <int MI, int NI>
+__device__ __forceinline__ bool sums_not_finite(v16f (&acc)[2][MI][NI]) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[0][i][j] -= acc[1][i][j];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s = __fmaf_rn(acc[0][i][j][e], 0.f, s);
+  return !(s == 0.f);
+}
+template <int MI, int NI>
+__device__ __forceinline__ bool sums_not_finite(v16f (&)[1][MI][NI]) { return false; }  // (16-bit: not asked)
+// fp32: the sums of a pass over `rows` block rows in LDS that are not finite, again as one chain of multiply-adds each.
+// chain(row, col): the sum of block row `row` and channel n0 + col, or 0 for a row that is not stored.
+template <int BN, class Chain>
+__device__ __forceinline__ void redo_not_finite(float* ep, int rows, int tid, Chain chain) {
+  for (int i = tid; i < rows * BN; i += 256) {
+    const int row = i / BN, col = i - row * BN;
+    float& v = ep[row * (BN + 4) + col];
+    if (!(__fmaf_rn(v, 0.f, 0.f) == 0.f)) v = chain(row, col);
+  }
+}
 // Within a depth tile the two lane groups (lanes 0-31, 32-63) own disjoint halves of the depth range and every MFMA
 // pairs the same depth indices of A and B, so any assignment of depth indices to (lane group, step) gives the same sum.
 
@@ -126,26 +159,28 @@ template <> struct Frag<f16_t> {
 // global loads of tile j+3 are issued at the top and written to LDS stage j%3 at the end of iteration j+1.
 template <int V> struct IC { static constexpr int value = V; };
 
-template <class T, int BM, int BN> constexpr size_t igemm_smem_bytes() {
-  constexpr size_t stages = (size_t)3 * (BM + BN) * (Frag<T>::BK + 16 / sizeof(T)) * sizeof(T);
+template <class X, int BM, int BN> constexpr size_t igemm_smem_bytes() {
+  constexpr size_t stages = (size_t)3 * (BM + BN) * Frag<X>::PITCH * sizeof(typename Frag<X>::E);
   constexpr size_t epi = (size_t)(BM / 2) * (BN + 4) * 4;
   return stages > epi ? stages : epi;
 }
 
-template <class T, int BM, int BN, int MODE, bool SPLIT>
+template <class T, class X, int BM, int BN, int MODE, bool SPLIT>
 __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ src, const T* __restrict__ wmat,
                                                          const float* __restrict__ bias, const T* __restrict__ addend,
                                                          T* __restrict__ out, float* __restrict__ partial,
                                                          float* __restrict__ stat_partial, IGemmArgs a) {
-  constexpr int BK = Frag<T>::BK;
+  constexpr bool S32 = std::is_same_v<X, Split32>;
+  constexpr int BK = Frag<X>::BK;
   constexpr int EV = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  constexpr int PITCH = BK + EV;            // LDS row pitch in elements (80 bytes)
+  typedef typename Frag<X>::E E;
+  constexpr int PITCH = Frag<X>::PITCH;     // LDS row pitch in staged elements
   constexpr int MI = BM / 64, NI = BN / 64; // 32x32 MFMA tiles per wavefront
   constexpr int A_CH = BM * 4 / 256;        // 16-byte chunks per thread and depth tile (4 chunks per row)
   constexpr int B_CH = BN * 4 / 256;
   constexpr int STAGE = (BM + BN) * PITCH;  // elements per LDS stage: A rows then B rows
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  T* lds = reinterpret_cast<T*>(smem_raw);
+  E* lds = reinterpret_cast<E*>(smem_raw);
 
   // kernel arguments used inside the loaders, as plain scalars
   const int srcH = a.srcH, srcW = a.srcW, srcC = a.srcC, S_ = a.S, stride = a.stride, pad = a.pad;
@@ -238,21 +273,23 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   };
   auto sstore = [&](auto P, int stage) {  // register generation p -> LDS stage
     constexpr int p = decltype(P)::value;
-    T* st = lds + stage * STAGE;
+    E* st = lds + stage * STAGE;
 #pragma unroll
-    for (int i = 0; i < A_CH; ++i)
-      *reinterpret_cast<Chunk*>(&st[(row0 + i * 64) * PITCH + vec * EV]) = ((okm[p] >> i) & 1u) ? ra[p][i] : zero_chunk();
+    for (int i = 0; i < A_CH; ++i) Frag<X>::put(&st[(row0 + i * 64) * PITCH], vec, ra[p][i], !((okm[p] >> i) & 1u));
 #pragma unroll
-    for (int i = 0; i < B_CH; ++i) *reinterpret_cast<Chunk*>(&st[(BM + row0 + i * 64) * PITCH + vec * EV]) = rb[p][i];
+    for (int i = 0; i < B_CH; ++i) Frag<X>::put(&st[(BM + row0 + i * 64) * PITCH], vec, rb[p][i], false, p % Frag<X>::ACCS != 0);
   };
 
-  v16f acc[MI][NI];
+  constexpr int ACCS = Frag<X>::ACCS;
+  v16f acc[ACCS][MI][NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int h = 0; h < ACCS; ++h)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[h][i][j][e] = 0.f;
 
   const int nkt = (a.cls ? a.ntaps[cz] * srcC : a.Kg) / BK;  // depth tiles of this GEMM
   const int kt1 = SPLIT ? (kt0 + a.kt_per_split < nkt ? kt0 + a.kt_per_split : nkt) : nkt;
@@ -262,14 +299,17 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   if (n > 1) { gload(IC<1>{}); sstore(IC<1>{}, 1); }
   if (n > 2) gload(IC<0>{});
   __syncthreads();
-  const int afrag = (wm * (BM / 2) + l32) * PITCH + Frag<T>::lane_off(g);
-  const int bfrag = (BM + wn * (BN / 2) + l32) * PITCH + Frag<T>::lane_off(g);
-  Frag<T> fa[MI], fb[NI];
+  const int afrag = (wm * (BM / 2) + l32) * PITCH + Frag<X>::lane_off(g);
+  const int bfrag = (BM + wn * (BN / 2) + l32) * PITCH + Frag<X>::lane_off(g);
+  Frag<X> fa[MI], fb[NI];
   if (n > 0) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) fa[i].load(lds + afrag + i * 32 * PITCH);
+    for (int ph = 0; ph < Frag<X>::PHASES; ++ph) {
 #pragma unroll
-    for (int jn = 0; jn < NI; ++jn) fb[jn].load(lds + bfrag + jn * 32 * PITCH);
+      for (int i = 0; i < MI; ++i) fa[i].load(lds + afrag + i * 32 * PITCH, ph);
+#pragma unroll
+      for (int jn = 0; jn < NI; ++jn) fb[jn].load(lds + bfrag + jn * 32 * PITCH, ph);
+    }
   }
   // iteration j: generation (j & 1) holds tile j+2 (issued at iteration j-1 or in the prologue)
   // TAIL = 0: steady state, every step unconditional (a branch around the loads would make the compiler wait for
@@ -277,35 +317,25 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
   auto body = [&](auto P, auto TAILC, int j, int stage) {
     constexpr int p = decltype(P)::value;  // = j & 1
     constexpr bool TAIL = decltype(TAILC)::value != 0;
-    const T* nxt = lds + (stage == 2 ? 0 : stage + 1) * STAGE;
+    const E* nxt = lds + (stage == 2 ? 0 : stage + 1) * STAGE;
     const bool has_next = TAIL ? j + 1 < n : true;
     if (!TAIL || j + 3 < n) gload(IC<1 - p>{});
 #pragma unroll
-    for (int st = 0; st < Frag<T>::HALF_STEPS; ++st)
+    for (int ph = 0; ph < Frag<X>::PHASES; ++ph) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
+      for (int st = 0; st < Frag<X>::steps(ph); ++st)
 #pragma unroll
-        for (int jn = 0; jn < NI; ++jn) Frag<T>::mma_half(fa[i], fb[jn], acc[i][jn], 0, st);
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) {
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int i = 0; i < MI; ++i) fa[i].load_lo(nxt + afrag + i * 32 * PITCH);
+          for (int jn = 0; jn < NI; ++jn) Frag<X>::mma(fa[i], fb[jn], acc[p % ACCS][i][jn], ph, st);
+      __builtin_amdgcn_sched_barrier(0);
+      if (has_next) {
 #pragma unroll
-      for (int jn = 0; jn < NI; ++jn) fb[jn].load_lo(nxt + bfrag + jn * 32 * PITCH);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < MI; ++i) fa[i].load(nxt + afrag + i * 32 * PITCH, ph);
 #pragma unroll
-    for (int st = 0; st < Frag<T>::HALF_STEPS; ++st)
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int jn = 0; jn < NI; ++jn) Frag<T>::mma_half(fa[i], fb[jn], acc[i][jn], 1, st);
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) {
-#pragma unroll
-      for (int i = 0; i < MI; ++i) fa[i].load_hi(nxt + afrag + i * 32 * PITCH);
-#pragma unroll
-      for (int jn = 0; jn < NI; ++jn) fb[jn].load_hi(nxt + bfrag + jn * 32 * PITCH);
+        for (int jn = 0; jn < NI; ++jn) fb[jn].load(nxt + bfrag + jn * 32 * PITCH, ph);
+      }
+      if (ph + 1 < Frag<X>::PHASES) __builtin_amdgcn_sched_barrier(0);
     }
     if (!TAIL || j + 2 < n) sstore(P, stage == 0 ? 2 : stage - 1);  // tile j+2 -> stage (j+2)%3
     __syncthreads();
@@ -335,6 +365,32 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
     constexpr int EP_PITCH = BN + 4;
     constexpr int HR = BM / 2;  // rows per pass
     constexpr bool STAT = MODE == IG_FWD && !SPLIT;
+    const bool redo = S32 && __syncthreads_or(sums_not_finite(acc));
+    // the sum over this block's depth tiles, tap by tap and channel by channel
+    auto chain = [&](int grow, int col) -> float {
+      if (grow >= a.M) return 0.f;
+      int pb = grow % a.dstW;
+      const int t = grow / a.dstW;
+      int pa = t % a.dstH;
+      const int pn = t / a.dstH;
+      if (a.cls) { pa = 2 * pa + cph; pb = 2 * pb + cpw; }
+      const T* w = wmat + (int64_t)(n0 + col) * (a.R * a.S * srcC);
+      float sum = 0.f;
+      for (int kt = kt0; kt < kt1 && sum == sum; ++kt) {  // (a NaN stays one)
+        const int ti = kt * BK / srcC, c = kt * BK - ti * srcC;
+        const int tp = a.cls ? (ctaps >> (8 * (ti & 3))) & 0xff : ti;
+        const int r = tp / S_, s2 = tp - r * S_;
+        int y = MODE != IG_DGRAD ? pa * stride + r - pad : pa + pad - r, x = MODE != IG_DGRAD ? pb * stride + s2 - pad : pb + pad - s2;
+        if (MODE == IG_DGRAD && stride == 2) {
+          if ((y | x) & 1) continue;
+          y >>= 1; x >>= 1;
+        }
+        if (y < 0 || y >= srcH || x < 0 || x >= srcW) continue;
+        const T* p = src + (((int64_t)pn * srcH + y) * srcW + x) * srcC + c;
+        for (int k = 0; k < BK; ++k) sum = __fmaf_rn(to_f32(p[k]), to_f32(w[tp * srcC + c + k]), sum);
+      }
+      return sum;
+    };
     float ss[8], qq[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) { ss[k] = 0.f; qq[k] = 0.f; }
@@ -348,9 +404,13 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
           for (int jn = 0; jn < NI; ++jn)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-              ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + jn * 32 + l32] = acc[i][jn][e];
+              ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + jn * 32 + l32] = acc[0][i][jn][e];
       }
       __syncthreads();
+      if (S32 && redo) {
+        redo_not_finite<BN>(ep, HR, tid, [&](int row, int col) { return chain(m0 + u * HR + row, col); });
+        __syncthreads();
+      }
       auto rowoff = [&](int row) -> int64_t {
         const int grow = m0 + u * HR + row;
         if (grow >= a.M) return -1;
@@ -402,13 +462,14 @@ struct PatchArgs {
   int tiles_r, tiles_c, NT;
   int relu;
   int chunks_per_split;      // channel chunks per blockIdx.z (all of them when the depth is not split)
-  int row_pitch;             // bytes between staged patch rows in LDS (>= SC * 80, padded against bank conflicts)
+  int row_pitch;             // bytes between staged patch rows in LDS (at least SC positions, padded against bank conflicts)
   int patch_elems;           // elements of one staged patch buffer (its rows times row_pitch, rounded up to 16 bytes)
   int xcd_group;             // 1: blocks are renumbered so that the row tiles of one weight slice run on one XCD;
                              // 2: so that the channel blocks and depth ranges of one row tile do (row_blocks: row tiles)
   int row_blocks;
   const uint8_t* amask;      // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
   int eval;                  // 1: the EVAL instantiation
+  int split32;               // fp32: 1: the Split32 instantiation
   const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
                              // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
                              // to LDS; positions outside the image stay zero
@@ -416,25 +477,33 @@ struct PatchArgs {
 
 constexpr int PATCH_MAX_POS = 256;  // positions per sub-tile
 
+// least and most wavefronts per SIMD that the registers are to leave room for
+template <class X> constexpr int PATCH_WAVES(int bn, int mi, int most) {
+  if (std::is_same_v<X, Split32>) return mi == 1 ? 3 : bn == 64 ? 2 : 1 + most;
+  return bn == 64 ? 3 : 1 + most;
+}
+
 // EVAL: `bias` is the [2][Ng] scale and shift of the inference-mode BatchNorm behind the layer, `addend` its skip connection
-template <class T, int BN, int MI, int SUBT, bool STAT, bool FOLD = false, bool EVAL = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BN == 64 ? 3 : 1, BN == 64 ? 3 : 2)))
+template <class T, class X, int BN, int MI, int SUBT, bool STAT, bool FOLD = false, bool EVAL = false>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PATCH_WAVES<X>(BN, MI, 0), PATCH_WAVES<X>(BN, MI, 1))))
 conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const float* __restrict__ bias,
                      const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ partial,
                      float* __restrict__ stat_partial, PatchArgs a) {
+  constexpr bool S32 = std::is_same_v<X, Split32>;
   constexpr int ROWS = 64 * MI;              // pixel rows of the block
   constexpr int TPC = ROWS / SUBT;           // rows (pixel capacity) per sub-tile
   constexpr int NSLOT = 4 * SUBT;            // 16-byte patch pieces per thread and channel chunk
   constexpr int SPT = NSLOT / 4;             // pieces requested / stored per tap
-  constexpr int CCE = Frag<T>::BK;           // channels per chunk (64 bytes)
+  constexpr int CCE = Frag<X>::BK;           // channels per chunk (64 bytes)
+  typedef typename Frag<X>::E E;
   constexpr int EV = 16 / (int)sizeof(T);
-  constexpr int PITCH = CCE + EV;            // elements per LDS row (80 bytes)
+  constexpr int PITCH = Frag<X>::PITCH;      // staged elements per LDS row
   constexpr int NI = BN / 64;
   constexpr int B_CH = BN * 4 / 256;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int PBUF = a.patch_elems;                                             // one patch buffer, sized for this layer
-  T* patch = reinterpret_cast<T*>(smem_raw);                                  // [2][PBUF]
-  T* Bs = patch + 2 * PBUF;                                                   // [3][BN][PITCH]
+  E* patch = reinterpret_cast<E*>(smem_raw);                                  // [2][PBUF]
+  E* Bs = patch + 2 * PBUF;                                                   // [3][BN][PITCH]
   int64_t* src_off = reinterpret_cast<int64_t*>(Bs + 3 * BN * PITCH);         // [SUBT*PATCH_MAX_POS]
   int64_t* out_off = src_off + SUBT * PATCH_MAX_POS;                          // [256]
   int* apos = reinterpret_cast<int*>(out_off + 256);                          // [256]
@@ -466,7 +535,7 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
   const int n0c = by * BN;
   const int npos2 = SUBT * a.NPOS;
   const int srcC = a.srcC, flip = a.flip, SC = a.SC;
-  const int RPE = a.row_pitch / (int)sizeof(T);  // elements between staged patch rows
+  const int RPE = a.row_pitch / (int)sizeof(E);  // elements between staged patch rows
 
   // ---- address tables ------------------------------------------------------------------------------------------
   for (int e = tid; e < npos2; e += 256) {
@@ -517,7 +586,7 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
   // patch pieces of this thread: slot sl covers the 16-byte piece idx = sl*256 + tid.  Loads are unconditional
   // (pieces outside the image read the tensor's first pixel) and are zeroed when written to LDS.
   const T* pptr[NSLOT];
-  int pdst[NSLOT];  // LDS element offset of the piece within a patch buffer
+  int pdst[NSLOT];  // LDS element offset of the piece's position within a patch buffer
   unsigned pvalid = 0u, pstore = 0u;
 #pragma unroll
   for (int sl = 0; sl < NSLOT; ++sl) {
@@ -530,7 +599,7 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
       const int64_t o = src_off[pos];
       if (o >= 0) { off = o; pvalid |= 1u << sl; }
       const int prow = pos / SC;
-      dst = prow * RPE + (pos - prow * SC) * PITCH + v * EV;
+      dst = prow * RPE + (pos - prow * SC) * PITCH;
     }
     pptr[sl] = src + off + v * EV;
     pdst[sl] = dst;
@@ -550,7 +619,7 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
     if ((pstore >> slot) & 1u) {
       Chunk v = c;
       if (FOLD) v = bn_fold_chunk<T>(c, fsc, fsh);
-      *reinterpret_cast<Chunk*>(&patch[buf * PBUF + pdst[slot]]) = ((pvalid >> slot) & 1u) ? v : zero_chunk();
+      Frag<X>::put(&patch[buf * PBUF + pdst[slot]], tid & 3, v, !((pvalid >> slot) & 1u));
     }
   };
   const T* wrow = wmat + (int64_t)(n0c + brow0) * Kg + bvec * EV;
@@ -565,8 +634,9 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
   }
 #define B_STORE(t_, stage_)                                                                                   \
   {                                                                                                           \
-    *reinterpret_cast<Chunk*>(&Bs[((stage_) * BN + brow0) * PITCH + bvec * EV]) = BRa[t_];                    \
-    if (B_CH > 1) *reinterpret_cast<Chunk*>(&Bs[((stage_) * BN + brow0 + 64) * PITCH + bvec * EV]) = BRb[t_]; \
+    Frag<X>::put(&Bs[((stage_) * BN + brow0) * PITCH], bvec, BRa[t_], false, (t_) % Frag<X>::ACCS != 0);      \
+    if (B_CH > 1)                                                                                             \
+      Frag<X>::put(&Bs[((stage_) * BN + brow0 + 64) * PITCH], bvec, BRb[t_], false, (t_) % Frag<X>::ACCS != 0); \
   }
 
   // ---- prologue -----------------------------------------------------------------------------------------------
@@ -583,42 +653,48 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
 
   int arow[MI];  // LDS element offset of tap (0,0) for this lane's 32-row groups
 #pragma unroll
-  for (int i = 0; i < MI; ++i) arow[i] = apos[wm * (32 * MI) + i * 32 + l32] + Frag<T>::lane_off(g);
-  const int bfrag = (wn * (BN / 2) + l32) * PITCH + Frag<T>::lane_off(g);  // this lane's row in a weight stage
+  for (int i = 0; i < MI; ++i) arow[i] = apos[wm * (32 * MI) + i * 32 + l32] + Frag<X>::lane_off(g);
+  const int bfrag = (wn * (BN / 2) + l32) * PITCH + Frag<X>::lane_off(g);  // this lane's row in a weight stage
 
-  v16f acc[MI][NI];
+  constexpr int ACCS = Frag<X>::ACCS;  // (by the parity of the tap)
+  v16f acc[ACCS][MI][NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int h = 0; h < ACCS; ++h)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[h][i][j][e] = 0.f;
 
   // Operand fragments live in one set of registers.  Each half (first / second 16 bytes of the 32-byte depth slice) is
   // reloaded for the next step right after the MFMAs that consumed it have been issued, so the LDS reads of step g+1
   // run under the MFMAs of step g and nothing waits on LDS latency.  Weight stage = step % 3; the weight tile of step
   // g+2 is written at the end of step g, the next chunk's patch during taps 4-7, so both are complete one barrier
   // before their first read.
-  Frag<T> fa[MI], fb[NI];
+  Frag<X> fa[MI], fb[NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i) fa[i].load(patch + arow[i]);
+  for (int ph = 0; ph < Frag<X>::PHASES; ++ph) {
 #pragma unroll
-  for (int j = 0; j < NI; ++j) fb[j].load(&Bs[bfrag + j * 32 * PITCH]);
+    for (int i = 0; i < MI; ++i) fa[i].load(patch + arow[i], ph);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fb[j].load(&Bs[bfrag + j * 32 * PITCH], ph);
+  }
 
   // one channel chunk = nine taps; LAST = no chunk follows (no patch prefetch, weight requests stop at the end)
   auto chunk_body = [&](auto LAST, int chunk) {
     constexpr bool last = decltype(LAST)::value != 0;
     const int pbuf = (chunk - cb) & 1;
-    const T* pcur = patch + pbuf * PBUF;
-    const T* pnxt = patch + (pbuf ^ 1) * PBUF;
+    const E* pcur = patch + pbuf * PBUF;
+    const E* pnxt = patch + (pbuf ^ 1) * PBUF;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
       // where the next step reads its operands
       const bool has_next = !last || t + 1 < 9;
       const int tn = (t + 1) % 9;
-      const T* pn = t + 1 < 9 ? pcur : pnxt;
+      const E* pn = t + 1 < 9 ? pcur : pnxt;
       const int tapoff_n = (tn / 3) * RPE + (tn % 3) * PITCH;
-      const T* bn_ = &Bs[((t + 1) % 3) * BN * PITCH + bfrag];
+      const E* bn_ = &Bs[((t + 1) % 3) * BN * PITCH + bfrag];
       // requests: the weight tile this tap will need in the next chunk, two pieces of the next patch during taps 0-3
       if (!last) B_LOAD(t, chunk + 1);
       if (!last && t < 4) {
@@ -626,34 +702,22 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
         for (int q = 0; q < SPT; ++q) PR[SPT * t + q] = patch_load(SPT * t + q, chunk + 1);
         if (t == 0) fold_load(chunk + 1);
       }
-      // first halves
 #pragma unroll
-      for (int st = 0; st < Frag<T>::HALF_STEPS; ++st)
+      for (int ph = 0; ph < Frag<X>::PHASES; ++ph) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int st = 0; st < Frag<X>::steps(ph); ++st)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) Frag<T>::mma_half(fa[i], fb[j], acc[i][j], 0, st);
-      __builtin_amdgcn_sched_barrier(0);
-      if (has_next) {
+          for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i].load_lo(pn + arow[i] + tapoff_n);
+            for (int j = 0; j < NI; ++j) Frag<X>::mma(fa[i], fb[j], acc[t % ACCS][i][j], ph, st);
+        __builtin_amdgcn_sched_barrier(0);
+        if (has_next) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) fb[j].load_lo(bn_ + j * 32 * PITCH);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // second halves
+          for (int i = 0; i < MI; ++i) fa[i].load(pn + arow[i] + tapoff_n, ph);
 #pragma unroll
-      for (int st = 0; st < Frag<T>::HALF_STEPS; ++st)
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j) Frag<T>::mma_half(fa[i], fb[j], acc[i][j], 1, st);
-      __builtin_amdgcn_sched_barrier(0);
-      if (has_next) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i].load_hi(pn + arow[i] + tapoff_n);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) fb[j].load_hi(bn_ + j * 32 * PITCH);
+          for (int j = 0; j < NI; ++j) fb[j].load(bn_ + j * 32 * PITCH, ph);
+        }
+        if (ph + 1 < Frag<X>::PHASES) __builtin_amdgcn_sched_barrier(0);
       }
       // parked data goes to LDS: weight tile of step g+2, patch pieces requested four taps ago
       if (t + 2 < 9) B_STORE(t + 2, (t + 2) % 3) else if (!last) B_STORE(t + 2 - 9, (t + 2) % 3)
@@ -675,6 +739,24 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
     float* ep = reinterpret_cast<float*>(smem_raw);
     constexpr int EP_PITCH = BN + 4;
     constexpr int HR = 32 * MI;  // rows per pass
+    const bool redo = S32 && __syncthreads_or(sums_not_finite(acc));
+    auto chain = [&](int row, int col) -> float {  // the sum over this block's channels, tap by tap
+      const int64_t o = out_off[row];
+      if (o < 0) return 0.f;
+      const int64_t pix = o / a.Ng;
+      const int q = (int)(pix % a.dstW), p = (int)(pix / a.dstW % a.dstH);
+      const int64_t n = pix / a.dstW / a.dstH;
+      const T* w = wmat + (int64_t)(n0c + col) * Kg;
+      float sum = 0.f;
+      for (int t = 0; t < 9 && sum == sum; ++t) {  // (a NaN stays one)
+        const int y = p - a.pad + t / 3, x = q - a.pad + t % 3;
+        if (y < 0 || y >= a.srcH || x < 0 || x >= a.srcW) continue;
+        const T* px = src + ((n * a.srcH + y) * a.srcW + x) * srcC;
+        const T* wt = w + (flip ? 8 - t : t) * srcC;
+        for (int c = cb * CCE; c < ce * CCE; ++c) sum = __fmaf_rn(to_f32(px[c]), to_f32(wt[c]), sum);
+      }
+      return sum;
+    };
     float ss[8], qq[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) { ss[k] = 0.f; qq[k] = 0.f; }
@@ -688,9 +770,13 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
           for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-              ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + j * 32 + l32] = acc[i][j][e];
+              ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + j * 32 + l32] = acc[0][i][j][e];
       }
       __syncthreads();
+      if (S32 && redo) {
+        redo_not_finite<BN>(ep, HR, tid, [&](int row, int col) { return chain(u * HR + row, col); });
+        __syncthreads();
+      }
       auto rowoff = [&](int row) -> int64_t { return out_off[u * HR + row]; };
       if (partial)
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
@@ -798,18 +884,17 @@ static void launch_splitk_epilogue(hipStream_t st, const float* partial, int spl
 }
 
 // LDS of the patch kernel: two patch buffers of patch_elems elements, three weight stages, the address tables
-template <class T> constexpr size_t patch_smem_bytes(int bn, int subt, int64_t patch_elems) {
-  return (size_t)(2 * patch_elems + 3 * bn * (Frag<T>::BK + 16 / sizeof(T))) * sizeof(T) + subt * PATCH_MAX_POS * 8 +
+template <class X> constexpr size_t patch_smem_bytes(int bn, int subt, int64_t patch_elems) {
+  return (size_t)(2 * patch_elems + 3 * bn * Frag<X>::PITCH) * sizeof(typename Frag<X>::E) + subt * PATCH_MAX_POS * 8 +
          256 * 8 + 256 * 4;
 }
-template <class T> constexpr size_t patch_smem_max(int bn, int subt) {
-  return patch_smem_bytes<T>(bn, subt, (int64_t)subt * PATCH_MAX_POS * (Frag<T>::BK + 16 / sizeof(T)));
+template <class X> constexpr size_t patch_smem_max(int bn, int subt) {
+  return patch_smem_bytes<X>(bn, subt, (int64_t)subt * PATCH_MAX_POS * Frag<X>::PITCH);
 }
 
 // tile geometry of the patch kernel for a (dstH x dstW) pixel grid gathered with a 3x3 window and sub-tiles of up to
 // `cap` pixels; false if it does not fit
-static bool patch_geometry(int N, int dstH, int dstW, int cap, PatchArgs& a) {
-  int tc = dstW < cap ? dstW : cap;
+static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchArgs& a) {
   int tr = cap / tc; if (tr > dstH) tr = dstH; if (tr < 1) tr = 1;
   int ti = (tr == dstH && tc == dstW) ? cap / (dstH * dstW) : 1;
   if (ti > N) ti = N; if (ti < 1) ti = 1;
@@ -823,21 +908,34 @@ static bool patch_geometry(int N, int dstH, int dstW, int cap, PatchArgs& a) {
   a.NT = ((N + ti - 1) / ti) * a.tiles_r * a.tiles_c;
   return true;
 }
+// The widest sub-tile, or the narrower one that covers the map with fewer of them: three rows of a wide map are more positions than
+// the buffer has for a whole sub-tile's pixels (64 of 128 on maps of 63 columns or more).
+static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, PatchArgs& a) {
+  bool ok = patch_geometry_of(N, dstH, dstW, dstW < cap ? dstW : cap, cap, a);
+  if (!narrow || a.TI > 1) return ok;  // (whole images)
+  for (int tc = 64; tc >= 8; tc /= 2) {
+    PatchArgs b = a;
+    if (tc >= dstW || !patch_geometry_of(N, dstH, dstW, tc, cap, b)) continue;
+    if (!ok || b.NT < a.NT) { a = b; ok = true; }
+    else if (b.NT == a.NT && a.TC < dstW && b.NPOS < a.NPOS) a = b;
+  }
+  return ok;
+}
 
 // Bytes between staged patch rows.  A lane group reads 16 bytes per lane at consecutive pixels: within a row of TC
-// pixels the 80-byte position pitch spreads them over the LDS banks, and the row pitch is padded so that the next
+// pixels the position pitch (80 bytes, fp32 112) spreads them over the LDS banks, and the row pitch is padded so that the next
 // rows of the tile land on the banks the previous ones left free (TC = 8: 128 mod 256, TC = 4: 64, TC = 2: 32);
-// kept at SC * 80 when the padded rows would not fit the patch buffer.
+// kept at SC positions when the padded rows would not fit the patch buffer.
 static constexpr int g_patch_pad_rows = 1;  // compile-time switch
-static int patch_row_pitch(const PatchArgs& a, int subt) {
-  const int base = a.SC * 80;
+static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes) {
+  const int base = a.SC * pos_bytes;
   int want = -1;
   if (a.TC == 8) want = 128; else if (a.TC == 4) want = 64; else if (a.TC == 2) want = 32;
   if (want < 0 || !g_patch_pad_rows) return base;
   int rp = base / 256 * 256 + want;
   if (rp < base) rp += 256;
   const int64_t rows = (int64_t)subt * a.TI * a.SR;
-  return rows * rp <= (int64_t)subt * PATCH_MAX_POS * 80 ? rp : base;
+  return rows * rp <= (int64_t)subt * PATCH_MAX_POS * pos_bytes ? rp : base;
 }
 
 // Block shapes of the patch kernel, largest first: {MI, SUBT, widest BN}.  The first one that gives the chip
@@ -852,11 +950,12 @@ static constexpr int g_patch_halo2 = 9;         // largest staged positions : pi
 static constexpr int g_patch_target_small = 512;  // blocks aimed at by the depth split for the smallest block shape in fp32
 static constexpr int64_t g_patch_xcd_wbytes = 4 << 20;  // XCD grouping of the blocks: least weight bytes (0: never) ...
 static constexpr int g_patch_xcd_rows = 16;              // ... and most row tiles
-static bool patch_pick(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride, PatchShape& shape,
+static bool patch_pick(int dt, bool split32, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride, PatchShape& shape,
                        PatchArgs& geo) {
   if (R != 3 || S != 3 || stride != 1) return false;
   if (srcC % (dt == DT_F32 ? 16 : 32) != 0 || Ng % 64 != 0) return false;
-  const int wide = Ng % 128 == 0 ? 128 : 64;
+  // (Split32: 128 x 128 tiles take the LDS of a CU alone, and a layer of 128 channels at 262 144 pixels 515 us with them, 445 without)
+  const int wide = Ng % 128 == 0 && !split32 ? 128 : 64;
   // Candidates, largest first.  Two co-resident blocks per CU cover each other's prologue, barriers and epilogue, and
   // measured better than one block of twice the size at every layer of the benchmark networks, so the first
   // candidate that gives g_patch_fill (two per CU) blocks is taken, else the one with the most blocks.
@@ -869,7 +968,7 @@ static bool patch_pick(int dt, int N, int dstH, int dstW, int srcC, int Ng, int 
     if (i == 1 && wide == 64) continue;  // same as candidate 0
     const int cap = 64 * cand[i].mi / cand[i].subt;
     PatchArgs a{};
-    if (!patch_geometry(N, dstH, dstW, cap, a)) continue;
+    if (!patch_geometry(N, dstH, dstW, cap, dt != DT_F32 || split32, a)) continue;
     if (a.TP * 4 < cap * 3) continue;  // tile rows poorly used
     if (a.NPOS * 2 > a.TP * g_patch_halo2) continue;  // almost only halo: the staged patch costs more than it saves
     const int64_t blocks = (int64_t)((a.NT + cand[i].subt - 1) / cand[i].subt) * (Ng / cand[i].bn);
@@ -891,13 +990,14 @@ static bool patch_pick(int dt, int N, int dstH, int dstW, int srcC, int Ng, int 
     if (splits > 4) splits = 4;
     if (splits < 1) splits = 1;
   }
-  geo.row_pitch = patch_row_pitch(geo, shape.subt);
+  geo.split32 = split32;
+  geo.row_pitch = patch_row_pitch(geo, shape.subt, split32 ? Frag<Split32>::PITCH * 2 : Frag<bf16_t>::PITCH * 2);
   geo.chunks_per_split = (nchunks + splits - 1) / splits;
   shape.splits = (nchunks + geo.chunks_per_split - 1) / geo.chunks_per_split;  // no empty ranges
   return true;
 }
 
-template <class T, int BN, int MI, int SUBT, bool FOLD>
+template <class T, class X, int BN, int MI, int SUBT, bool FOLD>
 static void launch_patch_v(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                            float* partial, float* stat_partial, int splits, const PatchArgs& a_in) {
   PatchArgs a = a_in;
@@ -905,12 +1005,12 @@ static void launch_patch_v(hipStream_t st, const void* src, const void* wmat, co
   // The patch buffers are sized for this layer's tile (its staged rows times the row pitch), not for the largest one,
   // so that the 64-channel shapes fit three blocks per CU on most layers.  The epilogue reuses the buffers and the
   // weight stages: they must hold its fp32 tile and the 16 KB of the channel-sum combine.
-  constexpr size_t sm_max = patch_smem_max<T>(BN, SUBT);
-  constexpr int64_t PITCH_E = Frag<T>::BK + 16 / sizeof(T);
+  constexpr size_t sm_max = patch_smem_max<X>(BN, SUBT);
+  constexpr int64_t PITCH_E = Frag<X>::PITCH, ES = sizeof(typename Frag<X>::E);
   const int64_t epi_bytes = std::max<int64_t>((int64_t)32 * MI * (BN + 4) * 4, 16384);
-  int64_t pe = ((int64_t)SUBT * a.TI * a.SR * a.row_pitch + 15) / 16 * 16 / (int64_t)sizeof(T);
-  const int64_t need = (epi_bytes - (int64_t)3 * BN * PITCH_E * (int64_t)sizeof(T) + 1) / 2;  // bytes per buffer
-  if (pe * (int64_t)sizeof(T) < need) pe = (need + 15) / 16 * 16 / (int64_t)sizeof(T);
+  int64_t pe = ((int64_t)SUBT * a.TI * a.SR * a.row_pitch + 15) / 16 * 16 / ES;
+  const int64_t need = (epi_bytes - (int64_t)3 * BN * PITCH_E * ES + 1) / 2;  // bytes per buffer
+  if (pe * ES < need) pe = (need + 15) / 16 * 16 / ES;
   if (pe > (int64_t)SUBT * PATCH_MAX_POS * PITCH_E) pe = (int64_t)SUBT * PATCH_MAX_POS * PITCH_E;
   a.patch_elems = (int)pe;
   // from the shape only: weights of at least g_patch_xcd_wbytes that at most g_patch_xcd_rows row tiles share
@@ -921,55 +1021,55 @@ static void launch_patch_v(hipStream_t st, const void* src, const void* wmat, co
     a.xcd_group = 2;
     grid.x = (grid.x + 7) / 8 * 8;
   }
-  const size_t sm = patch_smem_bytes<T>(BN, SUBT, pe);
+  const size_t sm = patch_smem_bytes<X>(BN, SUBT, pe);
   if constexpr (!FOLD) {
     if (a.eval && splits == 1) {
       static bool eval_attr = false;
       if (!eval_attr) {
-        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, BN, MI, SUBT, false, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
         eval_attr = true;
       }
-      OSEQ_LAUNCH((conv3x3_patch_kernel<T, BN, MI, SUBT, false, false, true>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+      OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, false, true>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                   (const T*)addend, (T*)out, (float*)nullptr, (float*)nullptr, a);
       return;
     }
   }
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, BN, MI, SUBT, false, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
-    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, BN, MI, SUBT, true, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, true, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
     attr_done = true;
   }
   // the variant that also adds up what it stores (BatchNorm statistics) is a separate instantiation, so that the
   // plain one carries none of its registers
   if (splits == 1 && stat_partial)
-    OSEQ_LAUNCH((conv3x3_patch_kernel<T, BN, MI, SUBT, true, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, true, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                        (const T*)addend, (T*)out, (float*)nullptr, stat_partial, a);
   else
-    OSEQ_LAUNCH((conv3x3_patch_kernel<T, BN, MI, SUBT, false, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                        (const T*)addend, (T*)out, splits > 1 ? partial : (float*)nullptr, (float*)nullptr, a);
 }
 
-template <class T>
+template <class T, class X>
 static void launch_patch_t(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                            float* partial, float* stat_partial, const PatchShape& v, const PatchArgs& a) {
   const int sp = v.splits;
   if constexpr (sizeof(T) == 2) {
     if (a.fold) {  // (16-bit modes only)
       if (v.mi == 2) {
-        if (v.bn == 128) launch_patch_v<T, 128, 2, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
-        else launch_patch_v<T, 64, 2, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+        if (v.bn == 128) launch_patch_v<T, X, 128, 2, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+        else launch_patch_v<T, X, 64, 2, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
       } else {
-        launch_patch_v<T, 64, 1, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+        launch_patch_v<T, X, 64, 1, 1, true>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
       }
     }
   }
   if (sizeof(T) != 2 || !a.fold) {
     if (v.mi == 2) {
-      if (v.bn == 128) launch_patch_v<T, 128, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
-      else launch_patch_v<T, 64, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+      if (v.bn == 128) launch_patch_v<T, X, 128, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+      else launch_patch_v<T, X, 64, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
     } else {
-      launch_patch_v<T, 64, 1, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+      launch_patch_v<T, X, 64, 1, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
     }
   }
   if (sp > 1)
@@ -979,9 +1079,10 @@ static void launch_patch_t(hipStream_t st, const void* src, const void* wmat, co
 
 static void launch_patch(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                          float* partial, float* stat_partial, const PatchShape& v, const PatchArgs& a) {
-  if (dt == DT_F32) launch_patch_t<float>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
-  else if (dt == DT_BF16) launch_patch_t<bf16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
-  else launch_patch_t<f16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
+  if (dt == DT_F32 && a.split32) launch_patch_t<float, Split32>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
+  else if (dt == DT_F32) launch_patch_t<float, float>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
+  else if (dt == DT_BF16) launch_patch_t<bf16_t, bf16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
+  else launch_patch_t<f16_t, f16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
 }
 
 static constexpr int g_igemm_spread = 1;                         // compile-time switch
@@ -992,28 +1093,28 @@ constexpr size_t kSpreadLds = 84 * 1024;        // more than half of the 160 KB 
 // take 716 / 646 us with it and 551 / 520 without, the fp32 network on 512 x 512 images 166.4 against 163.2 ms a step.
 constexpr int IGEMM_BM = 128;
 
-template <class T, int MODE>
+template <class T, class X, int MODE>
 static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                            float* partial, float* stat_partial, int splits, const IGemmArgs& a0) {
   IGemmArgs a = a0;
-  const int bk = Frag<T>::BK;
+  const int bk = Frag<X>::BK;
   a.kt_per_split = ceil_div(a.Kg / bk, splits);
-  const bool wide = a.Ng % 128 == 0;
+  const bool wide = a.Ng % 128 == 0 && !std::is_same_v<X, Split32>;  // (Split32: 128 x 128 tiles 207 us where 128 x 64 take 198)
   dim3 grid(ceil_div(a.M, IGEMM_BM), a.Ng / (wide ? 128 : 64), a.cls ? 4 : splits), block(256);  // cls: never split
   // A grid of at most one block per CU asks for more than half of a CU's LDS, so that no CU takes two blocks
   // while another idles.
   const bool spread = g_igemm_spread && (int64_t)grid.x * grid.y * grid.z <= 256;
 #define IGEMM_LAUNCH(BM_, BN_, SPLIT_)                                                                                   \
   {                                                                                                                      \
-    constexpr size_t sm_ = igemm_smem_bytes<T, BM_, BN_>();                                                              \
+    constexpr size_t sm_ = igemm_smem_bytes<X, BM_, BN_>();                                                              \
     constexpr size_t big_ = sm_ > kSpreadLds ? sm_ : kSpreadLds;                                                         \
     static bool attr_ = false;                                                                                           \
     if (!attr_) {                                                                                                        \
-      (void)hipFuncSetAttribute((const void*)conv_igemm_kernel<T, BM_, BN_, MODE_, SPLIT_>,                               \
+      (void)hipFuncSetAttribute((const void*)conv_igemm_kernel<T, X, BM_, BN_, MODE_, SPLIT_>,                               \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)big_);                                  \
       attr_ = true;                                                                                                      \
     }                                                                                                                    \
-    OSEQ_LAUNCH((conv_igemm_kernel<T, BM_, BN_, MODE_, SPLIT_>), grid, block, spread ? big_ : sm_, st,             \
+    OSEQ_LAUNCH((conv_igemm_kernel<T, X, BM_, BN_, MODE_, SPLIT_>), grid, block, spread ? big_ : sm_, st,             \
                        (const T*)src, (const T*)wmat, bias, (const T*)addend, (T*)out, partial, stat_partial, a);        \
   }
   if (splits > 1) {
@@ -1030,11 +1131,12 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
 }
 
 template <int MODE>
-static void launch_igemm(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend,
+static void launch_igemm(hipStream_t st, int dt, bool split32, const void* src, const void* wmat, const float* bias, const void* addend,
                          void* out, float* partial, float* stat_partial, int splits, const IGemmArgs& a) {
-  if (dt == DT_F32) launch_igemm_t<float, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
-  else if (dt == DT_BF16) launch_igemm_t<bf16_t, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
-  else launch_igemm_t<f16_t, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
+  if (dt == DT_F32 && split32) launch_igemm_t<float, Split32, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
+  else if (dt == DT_F32) launch_igemm_t<float, float, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
+  else if (dt == DT_BF16) launch_igemm_t<bf16_t, bf16_t, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
+  else launch_igemm_t<f16_t, f16_t, MODE>(st, src, wmat, bias, addend, out, partial, stat_partial, splits, a);
 }
 
 // depth splits of a GEMM with M rows, Ng columns and depth Kg: from the shape only
@@ -1048,6 +1150,12 @@ static int igemm_splits(int dt, int64_t M, int Ng, int Kg) {
   if (s > 32) s = 32;
   return (int)(s < 1 ? 1 : s);
 }
+// fp32 with the operands split (split32.h): data gradients always; forward passes of 131 072 output pixels or more.  Below,
+// the forward sums keep the rounding of the fp32 MFMA although the split is as exact and faster there too (64 -> 128 channels at
+// 32 768 pixels 48 -> 33 us): another rounding decides some ReLUs and maxima within 1e-6 of a tie the other way, each of which
+// moves the gradients below it by its share of their sums, and over few pixels that is no small one -- a step of the 11-layer
+// network at batch 128 moves by 4e-4 to 9e-3, at 512 x 512 by 2e-5 -- where the same decisions reproduce it to 1e-6.
+static bool fwd_split32(int dt, const ConvGeom& g) { return dt == DT_F32 && (int64_t)g.N * g.P * g.Q >= 131072; }
 static bool fwd_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride); }
 static bool dgrad_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride); }
 // (a layer that takes the weights-stationary 3x3 kernel never splits its depth, nor would the kernel that takes it when
@@ -1056,7 +1164,7 @@ int conv_mfma_fwd_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
   if (fwd_ws3x3(dt, g)) return 1;
   if (conv_pointwise_fwd_ok(dt, g)) return 1;
-  if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, pa)) return v.splits;
+  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, pa)) return v.splits;
   return igemm_splits(dt, (int64_t)g.N * g.P * g.Q, g.K, g.R * g.S * g.C);
 }
 // stride 2, even image, at most 3x3: the data gradient runs as four parity-class GEMMs in one launch
@@ -1068,7 +1176,7 @@ int conv_mfma_dgrad_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
   if (dgrad_ws3x3(dt, g)) return 1;
   if (conv_pointwise_dgrad_ok(dt, g)) return 1;
-  if (patch_pick(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
+  if (patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
   if (dgrad_by_classes(g)) return 1;
   return igemm_splits(dt, (int64_t)g.N * g.H * g.W, g.C, g.R * g.S * g.K);
 }
@@ -1089,7 +1197,7 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias) {
   const int64_t M = (int64_t)g.N * g.P * g.Q;
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_stat_blocks(g);
   if (!bias && fwd_ws3x3(dt, g)) return conv_ws3x3_stat_blocks(g);
-  if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
+  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
     return pv.splits > 1 ? ceil_div(M, split_epi_rows(M, g.K)) : (pa.NT + pv.subt - 1) / pv.subt;
   if (igemm_splits(dt, M, g.K, g.R * g.S * g.C) > 1) return ceil_div(M, split_epi_rows(M, g.K));
   return ceil_div(M, IGEMM_BM);
@@ -1101,7 +1209,7 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias) {
 bool conv_fold_fwd_ok(int dt, const ConvGeom& g) {
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_fold_ok(dt, g);
   PatchShape pv; PatchArgs pa{};
-  return dt != DT_F32 && patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa);
+  return dt != DT_F32 && patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa);
 }
 
 void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
@@ -1117,7 +1225,7 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
     return;
   }
   const bool eval = ev.affine != nullptr;
-  if (patch_pick(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
+  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.H; pa.srcW = g.W; pa.srcC = g.C; pa.dstH = g.P; pa.dstW = g.Q; pa.Ng = g.K;
     pa.pad = g.pad; pa.flip = 0; pa.relu = relu;
     pa.fold = dt == DT_F32 ? nullptr : fold;
@@ -1126,8 +1234,8 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
     return;
   }
   IGemmArgs a{g.H, g.W, g.C, g.P, g.Q, g.N * g.P * g.Q, g.K, g.R * g.S * g.C, g.R, g.S, g.stride, g.pad, relu, 0};
-  if (eval) launch_igemm<IG_EVAL>(st, dt, x, w, ev.affine, ev.skip, out, partial, nullptr, splits, a);
-  else launch_igemm<IG_FWD>(st, dt, x, w, bias, nullptr, out, partial, stat_partial, splits, a);
+  if (eval) launch_igemm<IG_EVAL>(st, dt, fwd_split32(dt, g), x, w, ev.affine, ev.skip, out, partial, nullptr, splits, a);
+  else launch_igemm<IG_FWD>(st, dt, fwd_split32(dt, g), x, w, bias, nullptr, out, partial, stat_partial, splits, a);
 }
 
 // wt: the (C_in, kh, kw, C_out) transpose of the weights, in the compute type
@@ -1143,7 +1251,7 @@ void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* 
     launch_conv_dgrad_ws3x3(st, dt, dz, wt, dx, g);
     return;
   }
-  if (patch_pick(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {
+  if (patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.P; pa.srcW = g.Q; pa.srcC = g.K; pa.dstH = g.H; pa.dstW = g.W; pa.Ng = g.C;
     pa.pad = g.R - 1 - g.pad; pa.flip = 1; pa.relu = 0; pa.amask = amask;
     launch_patch(st, dt, dz, wt, nullptr, addend, dx, partial, nullptr, pv, pa);
@@ -1162,10 +1270,10 @@ void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* 
           if (((ph + g.pad - r) & 1) == 0 && ((pw + g.pad - s2) & 1) == 0)
             a.taps[c] |= (r * g.S + s2) << (8 * a.ntaps[c]++);
     }
-    launch_igemm<IG_DGRAD>(st, dt, dz, wt, nullptr, addend, dx, nullptr, nullptr, 1, a);
+    launch_igemm<IG_DGRAD>(st, dt, true, dz, wt, nullptr, addend, dx, nullptr, nullptr, 1, a);
     return;
   }
-  launch_igemm<IG_DGRAD>(st, dt, dz, wt, nullptr, addend, dx, partial, nullptr, splits, a);
+  launch_igemm<IG_DGRAD>(st, dt, true, dz, wt, nullptr, addend, dx, partial, nullptr, splits, a);
 }
 
 // (C_out, R*S, C_in) fp32 master weights -> (C_in, R*S, C_out) in the compute type, for all layers of a batch in one
@@ -1221,8 +1329,8 @@ void launch_weight_transposes(hipStream_t st, int dt, const float* wbase, void* 
 // One block owns a (BM output channels) x (BN input channels) tile of ONE filter tap and a fixed chunk of the
 // pixel range (blockIdx.z); chunks are summed afterwards in order, so the result does not depend on scheduling.
 // Both operands arrive pixel-major (the reduction index is the slow one), but an MFMA lane wants consecutive
-// reduction elements.  The tiles are stored in LDS exactly as loaded (16-byte chunks, [pixel][channel]); fp32 lanes
-// read them with a stride, 16-bit lanes use the transposing LDS read of gfx950 (ds_read_b64_tr_b16).
+// reduction elements.  The tiles are stored in LDS as loaded (16-byte chunks, [pixel][channel]; fp32 as three such tiles, one
+// per bf16 plane: split32.h) and read with the transposing LDS read of gfx950 (ds_read_b64_tr_b16).
 // ------------------------------------------------------------------------------------------------------------
 struct WGradArgs {
   int H, W, C, K, R, S, stride, pad, P, Q;
@@ -1232,20 +1340,6 @@ struct WGradArgs {
                       // the activation (scale, shift, ReLU, one rounding) on their way to LDS
   int xcd_group;      // 1: the tiles of a pixel range share an XCD (see the kernel); ranges: the number of pixel ranges
   int ranges;
-};
-
-template <class T> struct WFrag;
-template <> struct WFrag<float> {
-  static constexpr int DEPTH = 16;  // pixels per depth tile
-  float v[8];
-  __device__ __forceinline__ void load(const float* tile, int pitch, int col, int g) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = tile[(g * 8 + t) * pitch + col];
-  }
-  __device__ static __forceinline__ void mma(const WFrag& a, const WFrag& b, v16f& c) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[t], b.v[t], c, 0, 0, 0);
-  }
 };
 
 typedef __attribute__((ext_vector_type(4))) short v4s;
@@ -1264,7 +1358,7 @@ __device__ __forceinline__ v8s tr_read8(const T* p0, const T* p1) {
 // 128 x 128 tiles (a 1024 x 256 weight gradient over 262 144 pixels moves 1.07 GB instead of 2.1 GB that way).
 template <class T, int BM, int BN, int WGM>
 constexpr size_t wgrad_lds_bytes() {
-  return (size_t)3 * (sizeof(T) == 4 ? 16 : 32) * (BM + BN + 2 * (sizeof(T) == 4 ? 4 : 16)) * sizeof(T);
+  return (size_t)3 * (sizeof(T) == 4 ? 3 * 16 : 32) * (BM + BN + 2 * 16) * 2;
 }
 
 // PW: a 1x1 layer with unit stride and no padding -- pixel m of x is row m, as it is of dz; the loads of a depth tile
@@ -1281,13 +1375,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
   constexpr int NT = 64 * WGM * WGN;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int MI = WTM / 32, NI = WTN / 32;
-  // one LDS stage, pixel-major exactly as loaded: [DEPTH][BM + pad] then [DEPTH][BN + pad] (pad: 4 floats / 16 halves)
-  constexpr int PADE = F32 ? 4 : 16;
-  constexpr int A_ELEMS = DEPTH * (BM + PADE);
-  constexpr int B_ELEMS = DEPTH * (BN + PADE);
+  // one LDS stage, pixel-major as loaded: [PL][DEPTH][BM + pad] then [PL][DEPTH][BN + pad] (pad: 16 elements; PL: planes)
+  typedef Frag<std::conditional_t<F32, Split32, T>> FR;
+  typedef typename FR::E E;
+  constexpr int PADE = 16, PL = F32 ? 3 : 1;
+  constexpr int A_PL = DEPTH * (BM + PADE), A_ELEMS = PL * A_PL;
+  constexpr int B_PL = DEPTH * (BN + PADE), B_ELEMS = PL * B_PL;
   constexpr int STAGE = A_ELEMS + B_ELEMS;
   extern __shared__ __attribute__((aligned(16))) unsigned char wgrad_smem[];
-  T* lds = reinterpret_cast<T*>(wgrad_smem);
+  E* lds = reinterpret_cast<E*>(wgrad_smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN, g = lane >> 5, l32 = lane & 31;
@@ -1406,8 +1502,19 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
   auto sstore = [&](auto G, auto FULLC, int stage) {
     constexpr int p = decltype(G)::value;
     constexpr bool FULL = PW && decltype(FULLC)::value != 0;
-    T* sa = lds + stage * STAGE;
-    T* sb = sa + A_ELEMS;
+    E* sa = lds + stage * STAGE;
+    E* sb = sa + A_ELEMS;
+    // a piece, or zero, to its place in the tile (fp32: in its three planes)
+    auto put = [&](E* at, int plane, const Chunk& c, bool ok) {
+      if constexpr (F32) {
+        u32x2_t q[3];
+        split32(ok ? c : zero_chunk(), q);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2_t*>(at + k * plane) = q[k];
+      } else {
+        *reinterpret_cast<Chunk*>(at) = ok ? c : zero_chunk();
+      }
+    };
     if (FOLD) {
 #pragma unroll
       for (int i = 0; i < B_CH32; ++i) rb[p][i] = bn_fold_chunk<T>(rb[p][i], fsc, fsh);
@@ -1415,12 +1522,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
 #pragma unroll
     for (int i = 0; i < A_CH32; ++i) {
       const int id = tid + i * NT, px = id / (BM / EV), kv = id % (BM / EV);
-      *reinterpret_cast<Chunk*>(&sa[px * (BM + PADE) + kv * EV]) = (FULL || ((va[p] >> i) & 1u)) ? ra[p][i] : zero_chunk();
+      put(&sa[px * (BM + PADE) + kv * EV], A_PL, ra[p][i], FULL || ((va[p] >> i) & 1u));
     }
 #pragma unroll
     for (int i = 0; i < B_CH32; ++i) {
       const int id = tid + i * NT, px = id / (BN / EV), cv = id % (BN / EV);
-      *reinterpret_cast<Chunk*>(&sb[px * (BN + PADE) + cv * EV]) = (FULL || ((vb[p] >> i) & 1u)) ? rb[p][i] : zero_chunk();
+      put(&sb[px * (BN + PADE) + cv * EV], B_PL, rb[p][i], FULL || ((vb[p] >> i) & 1u));
     }
   };
 
@@ -1432,60 +1539,24 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // operand registers: fp32 8 scalars per 32-row tile (pixels g*8 .. g*8+7 of the depth tile), 16-bit a 32-byte slice
-  float fa32[F32 ? MI : 1][8], fb32[F32 ? NI : 1][8];
-  Frag<T> fa[F32 ? 1 : MI], fb[F32 ? 1 : NI];
-  const int acol = wm * WTM + l32, bcol = wn * WTN + l32;
-  auto load_half = [&](int half, int stage) {
-    const T* sa = lds + stage * STAGE;
-    const T* sb = sa + A_ELEMS;
-    if constexpr (F32) {
-      const float* fsa = reinterpret_cast<const float*>(sa);
-      const float* fsb = reinterpret_cast<const float*>(sb);
+  // Operand registers, loaded in FR::PHASES parts: 16-bit the two halves (16 pixels each) of the depth tile, fp32 the planes.
+  // Transposing LDS read (ds_read_b64_tr_b16): within 16 lanes, lane r points at 4 consecutive channels of pixel
+  // k0 + r/4 starting at channel 4*(r%4); lane l receives channel l of the 16 at pixels k0..k0+3.  Two reads give
+  // 8 pixels for channel (tile base + l32).
+  FR fa[MI], fb[NI];
+  const int r16 = l32 & 15;
+  const int coff = (l32 & 16) + 4 * (r16 & 3);
+  auto load_part = [&](int ph, int stage) {
+    const int part = F32 ? 2 - ph : ph;
+    const int px = (F32 ? g * 8 : g * 16 + ph * 8) + (r16 >> 2);
+    const E* sa = lds + stage * STAGE + (F32 ? part * A_PL : 0) + px * (BM + PADE) + wm * WTM + coff;
+    const E* sb = lds + stage * STAGE + A_ELEMS + (F32 ? part * B_PL : 0) + px * (BN + PADE) + wn * WTN + coff;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int px = g * 8 + half * 4 + t;
+    for (int i = 0; i < MI; ++i)
+      fa[i].p[part] = __builtin_bit_cast(std::remove_reference_t<decltype(fa[i].p[part])>, tr_read8(sa + i * 32, sa + i * 32 + 4 * (BM + PADE)));
 #pragma unroll
-        for (int i = 0; i < MI; ++i) fa32[i][half * 4 + t] = fsa[px * (BM + PADE) + acol + i * 32];
-#pragma unroll
-        for (int j = 0; j < NI; ++j) fb32[j][half * 4 + t] = fsb[px * (BN + PADE) + bcol + j * 32];
-      }
-    } else {
-      // Transposing LDS read (ds_read_b64_tr_b16): within 16 lanes, lane r points at 4 consecutive channels of pixel
-      // k0 + r/4 starting at channel 4*(r%4); lane l receives channel l of the 16 at pixels k0..k0+3.  Two reads give
-      // the 8 pixels of one operand half for channel (tile base + l32).
-      const int r16 = l32 & 15;
-      const int kbase = g * 16 + half * 8 + (r16 >> 2);
-      const int coff = (l32 & 16) + 4 * (r16 & 3);
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const T* pp = sa + kbase * (BM + PADE) + wm * WTM + i * 32 + coff;
-        const v8s v = tr_read8(pp, pp + 4 * (BM + PADE));
-        if (half == 0) fa[i].lo = __builtin_bit_cast(decltype(fa[i].lo), v); else fa[i].hi = __builtin_bit_cast(decltype(fa[i].hi), v);
-      }
-#pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        const T* pp = sb + kbase * (BN + PADE) + wn * WTN + j * 32 + coff;
-        const v8s v = tr_read8(pp, pp + 4 * (BN + PADE));
-        if (half == 0) fb[j].lo = __builtin_bit_cast(decltype(fb[j].lo), v); else fb[j].hi = __builtin_bit_cast(decltype(fb[j].hi), v);
-      }
-    }
-  };
-  auto mma_half = [&](int half) {
-    if constexpr (F32) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa32[i][half * 4 + t], fb32[j][half * 4 + t], acc[i][j], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) Frag<T>::mma_half(fa[i], fb[j], acc[i][j], half, 0);
-    }
+    for (int j = 0; j < NI; ++j)
+      fb[j].p[part] = __builtin_bit_cast(std::remove_reference_t<decltype(fb[j].p[part])>, tr_read8(sb + j * 32, sb + j * 32 + 4 * (BN + PADE)));
   };
 
   // pipeline as in the forward kernel: three LDS stages, two register generations, operand reload under the MFMAs
@@ -1493,7 +1564,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
   if (n > 1) { gload(IC<1>{}, IC<1>{}, 1); sstore(IC<1>{}, IC<0>{}, 1); }
   if (n > 2) gload(IC<0>{}, IC<1>{}, 2);
   __syncthreads();
-  if (n > 0) { load_half(0, 0); load_half(1, 0); }
+  if (n > 0) {
+#pragma unroll
+    for (int ph = 0; ph < FR::PHASES; ++ph) load_part(ph, 0);
+  }
   auto body = [&](auto G, auto TAILC, int j, int stage) {
     constexpr int p = decltype(G)::value;  // = j & 1: this generation holds tile j+2
     constexpr bool TAIL = decltype(TAILC)::value != 0;  // 0: steady state without range checks
@@ -1501,13 +1575,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
     const bool has_next = TAIL ? j + 1 < n : true;
     // steady state: tiles j + 2 and j + 3 are not the range's last one, all of their rows are inside it
     if (!TAIL || j + 3 < n) gload(IC<1 - p>{}, IC<TAIL ? 1 : 0>{}, j + 3);
-    mma_half(0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) load_half(0, nstage);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_half(1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) load_half(1, nstage);
+#pragma unroll
+    for (int ph = 0; ph < FR::PHASES; ++ph) {
+#pragma unroll
+      for (int q = 0; q < FR::steps(ph); ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int jn = 0; jn < NI; ++jn) FR::mma(fa[i], fb[jn], acc[i][jn], ph, q);
+      __builtin_amdgcn_sched_barrier(0);
+      if (has_next) load_part(ph, nstage);
+      if (ph + 1 < FR::PHASES) __builtin_amdgcn_sched_barrier(0);
+    }
     if (!TAIL || j + 2 < n) sstore(G, IC<TAIL ? 0 : 1>{}, stage == 0 ? 2 : stage - 1);
     __syncthreads();
   };
@@ -1542,6 +1621,30 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
         dst[((int64_t)k * a.R * a.S + tap) * C + c] = acc[i][j][e];
       }
     }
+  if constexpr (F32) {  // sums that are not finite, again as fp32 chains (split32.h)
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[i][j][e], 0.f, sum);
+    __threadfence_block();
+    if (!__syncthreads_or(!(sum == 0.f))) return;
+    for (int i = tid; i < BM * BN; i += NT) {
+      const int k = k0 + i / BN, c = c0 + i % BN;
+      float& v = dst[((int64_t)k * a.R * a.S + tap) * C + c];
+      if (__fmaf_rn(v, 0.f, 0.f) == 0.f) continue;
+      float t = 0.f;
+      for (int m = mbeg; m < mend && t == t; ++m) {  // (a NaN stays one)
+        const uint32_t n_ = divPQ.div((uint32_t)m), rem = (uint32_t)m - n_ * divPQ.d;
+        const uint32_t p_ = divQ.div(rem), q_ = rem - p_ * divQ.d;
+        int64_t off;
+        if (tap_offset((int)n_, (int)p_, (int)q_, off)) t = __fmaf_rn(dz[(int64_t)m * K + k], x[off + c], t);
+      }
+      v = t;
+    }
+  }
 }
 
 bool conv_mfma_wgrad_ok(int dt, const ConvGeom& g) {
@@ -1642,9 +1745,20 @@ static void launch_wgrad_t(hipStream_t st, const void* x, const void* dz, float*
   const bool pw = g.R * g.S == 1 && g.stride == 1 && g.pad == 0 && (int64_t)32 * std::max(g.K, g.C) < (1 << 30);
 #define WGRAD_LAUNCH(BM_, BN_)                                                                                              \
   {                                                                                                                         \
-    if (pw) OSEQ_LAUNCH((conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, true>), grid, block, (wgrad_lds_bytes<T, BM_, BN_, 2>()), st, \
+    constexpr size_t sm_ = wgrad_lds_bytes<T, BM_, BN_, 2>();                                                               \
+    if constexpr (sm_ > 65536) {                                                                                            \
+      static bool attr_ = false;                                                                                            \
+      if (!attr_) {                                                                                                         \
+        (void)hipFuncSetAttribute((const void*)conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, true>,                            \
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_);                                    \
+        (void)hipFuncSetAttribute((const void*)conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, false>,                           \
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_);                                    \
+        attr_ = true;                                                                                                       \
+      }                                                                                                                     \
+    }                                                                                                                       \
+    if (pw) OSEQ_LAUNCH((conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, true>), grid, block, sm_, st, \
                         (const T*)x, (const T*)dz, dst, a);                                                                 \
-    else OSEQ_LAUNCH((conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, false>), grid, block, (wgrad_lds_bytes<T, BM_, BN_, 2>()), st,  \
+    else OSEQ_LAUNCH((conv_wgrad_kernel<T, BM_, BN_, 2, 2, FOLD, false>), grid, block, sm_, st,  \
                      (const T*)x, (const T*)dz, dst, a);                                                                    \
   }
   if (m128 && n128) WGRAD_LAUNCH(128, 128)

@@ -15,14 +15,18 @@
 //   channels (the plan says where): 4 x 2 wavefronts with MI = 1, two per SIMD (144 accumulator registers each), so that one
 //   wavefront's LDS reads and address arithmetic run under the other's MFMAs: 256 -> 256 channels at 8 x 8, batch
 //   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 326 us with 4 x 2 (the one-tap-per-block kernel: 479 us).
-//   fp32: MFMA 32x32x2, lanes read single floats of the pixel-major tiles (channel = lane).
-//   16-bit: MFMA 32x32x16, operands come from the transposing LDS read (ds_read_b64_tr_b16), whose per-lane row
-//   addresses make the tap shift a plain change of address.
-//   Two LDS stages; the global loads of the next sub-tile are issued before the MFMAs of the current one, parked
-//   in registers and written to the other stage afterwards: one barrier per sub-tile.
+//   MFMA 32x32x16, operands come from the transposing LDS read (ds_read_b64_tr_b16), whose per-lane row addresses make the
+//   tap shift a plain change of address.  fp32: three bf16 planes per operand, six MFMAs (split32.h).
+//   16-bit: two LDS stages; the global loads of the next sub-tile are issued before the MFMAs of the current one, parked in
+//   registers and written to the other stage afterwards: one barrier per sub-tile.  fp32: one stage, sized for the layer's
+//   sub-tile (79 KB on 8 x 8 pixels), so that two blocks share a CU and one loads and converts while the other computes; nothing
+//   is parked, whose registers the accumulators need (spilled, 64 -> 64 channels at 1 048 576 pixels took 635 us).
+#include <type_traits>
+
 #include "bn_fold.h"
 #include "dev_common.h"
 #include "kernels.h"
+#include "split32.h"
 
 namespace oseq {
 
@@ -56,10 +60,14 @@ template <class T, int MI, int WGM> struct W9Lds {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr int CAP = W9Cfg<T>::CAP, MAXPOS = W9Cfg<T>::MAXPOS;
   static constexpr int BMK = 32 * MI * WGM;
-  static constexpr int PX = F32 ? 64 : 80;          // elements per staged x position (16-bit: 32 bytes of padding)
-  static constexpr int PK = F32 ? BMK : BMK + 16;   // elements per staged dz pixel
-  static constexpr int XS = MAXPOS * PX, DS = CAP * PK, STAGE = XS + DS;
-  static constexpr size_t bytes = (size_t)2 * STAGE * sizeof(T) + CAP * sizeof(int);
+  static constexpr int PX = 80;                     // elements per staged x position (32 bytes of padding)
+  static constexpr int PK = BMK + 16;               // elements per staged dz pixel
+  static constexpr int PL = F32 ? 3 : 1;            // planes
+  // elements of a plane of x (fp32: of the layer's positions, not of the most there can be), of dz; of a stage
+  static constexpr int xs(int npos) { return (F32 ? npos : MAXPOS) * PX; }
+  static constexpr int DS = CAP * PK;
+  static constexpr int stage(int npos) { return PL * (xs(npos) + DS); }
+  static constexpr size_t bytes(int npos) { return (size_t)(F32 ? 1 : 2) * stage(npos) * 2 + CAP * sizeof(int); }
 };
 
 __device__ __forceinline__ v16f mfma16(v8bf a, v8bf b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
@@ -67,15 +75,15 @@ __device__ __forceinline__ v16f mfma16(v8h a, v8h b, v16f c) { return __builtin_
 template <class T> struct V8;
 template <> struct V8<bf16_t> { typedef v8bf type; };
 template <> struct V8<f16_t> { typedef v8h type; };
-template <> struct V8<float> { typedef v8h type; };  // unused
+template <> struct V8<float> { typedef v8bf type; };
 
 // Two transposing 64-bit LDS reads (ds_read_b64_tr_b16).  Within a group of 16 lanes every lane supplies the address
 // of 4 consecutive 16-bit elements, and lane l receives element l%4 of the addresses supplied by lanes l/4, l/4 + 4,
 // l/4 + 8, l/4 + 12.  With lane r addressing channels [4*(r%4), +4) of row r/4 (of four rows), lane l therefore ends
 // up with channel l of the 16 at those four rows.  p0 / p1 address the first / second group of four rows, so the
 // result holds 8 consecutive reduction elements (pixels) of one channel: an MFMA operand.
-template <class T>
-__device__ __forceinline__ typename V8<T>::type tr_read8(const T* p0, const T* p1) {
+template <class T, class E>
+__device__ __forceinline__ typename V8<T>::type tr_read8(const E* p0, const E* p1) {
   const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p0));
   const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p1));
   const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
@@ -89,7 +97,7 @@ __device__ __forceinline__ typename V8<T>::type tr_read8(const T* p0, const T* p
 // column, checks each against the image and multiplies them back together with quarter-rate 32- and 64-bit multiplies,
 // per chunk and sub-tile, in a kernel whose instruction stream is what bounds it.
 template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false>
-__global__ void __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(WGM / 2, WGM / 2)))
+__global__ void __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : WGM / 2, sizeof(T) == 4 ? 2 : WGM / 2)))
 conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* __restrict__ out, W9Args a) {
   typedef W9Lds<T, MI, WGM> L;
   constexpr bool F32 = L::F32;
@@ -100,8 +108,10 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   constexpr int XSLOTS = (MAXPOS * XCP + NTH - 1) / NTH;  // chunks per thread and sub-tile
   constexpr int DSLOTS = CAP * DCP / NTH;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  T* lds = reinterpret_cast<T*>(smem_raw);
-  int* apos = reinterpret_cast<int*>(lds + 2 * L::STAGE);
+  typedef std::conditional_t<F32, bf16_t, T> E;  // staged element
+  const int XS = L::xs(a.NPOS), STAGE = L::stage(a.NPOS);
+  E* lds = reinterpret_cast<E*>(smem_raw);
+  int* apos = reinterpret_cast<int*>(lds + (F32 ? 1 : 2) * STAGE);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, hg = lane >> 5, l32 = lane & 31;
@@ -261,8 +271,8 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     load_f32<float, EV>(a.fold + 3 * C + c0 + (tid % XCP) * EV, fsh);
   }
   auto sstore = [&](int stage) {
-    T* xs = lds + stage * L::STAGE;
-    T* ds = xs + L::XS;
+    E* xs = lds + stage * STAGE;
+    E* ds = xs + L::PL * XS;
     if (FOLD) {
 #pragma unroll
       for (int sl = 0; sl < XSLOTS; ++sl) xr[sl] = bn_fold_chunk<T>(xr[sl], fsc, fsh);
@@ -279,6 +289,64 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     }
   };
 
+  // fp32: a sub-tile from memory to its planes in LDS, half of the pieces of x at a time; addresses as in gload
+  auto stage32 = [&](int tile) {
+    E* xs = lds;
+    E* ds = lds + L::PL * XS;
+    const int ci = tile % a.tiles_c, t2 = tile / a.tiles_c;
+    const int ri = t2 % a.tiles_r, nb = t2 / a.tiles_r * TI;
+    const int yb = ri * TR - pad, xb = ci * TC - pad;
+    const T* xt = x + (int64_t)nb * H * W * C + c0;
+    const T* dt = dz + (int64_t)nb * P * Q * K + k0;
+    auto put = [&](E* at, int plane, const Chunk& c, bool ok) {
+      u32x2_t q[3];
+      split32(ok ? c : zero_chunk(), q);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2_t*>(at + k * plane) = q[k];
+    };
+    constexpr int HALF = (XSLOTS + 1) / 2;
+    auto load_x = [&](auto FIRST) {
+#pragma unroll
+      for (int i = 0; i < HALF; ++i) {
+        const int sl = decltype(FIRST)::value + i;
+        if (sl >= XSLOTS || sl * NTH >= NPOS * XCP) break;
+        const int info = xinfo[sl], ti = info >> 20;
+        const int y = yb + ((info >> 10) & 1023), xx = xb + (info & 1023);
+        const bool ok = info >= 0 && nb + ti < N && (unsigned)y < (unsigned)H && (unsigned)xx < (unsigned)W;
+        const uint32_t pix = ok ? (uint32_t)(__mul24(__mul24(ti, H) + y, W) + xx) : 0u;
+        xr[i] = *reinterpret_cast<const Chunk*>(xt + (uint64_t)(pix & 0xffffffu) * (uint64_t)((uint32_t)C & 0xffffffu) + (sl * NTH + tid) % XCP * EV);
+        xok = i == 0 ? (ok ? 1u : 0u) : xok | (ok ? 1u << i : 0u);
+      }
+    };
+    auto put_x = [&](auto FIRST) {
+#pragma unroll
+      for (int i = 0; i < HALF; ++i) {
+        const int sl = decltype(FIRST)::value + i;
+        if (sl >= XSLOTS || sl * NTH >= NPOS * XCP) break;
+        const int idx = sl * NTH + tid, pos = idx / XCP;
+        if (pos < NPOS) put(&xs[pos * PX + idx % XCP * EV], XS, xr[i], (xok >> i) & 1u);
+      }
+    };
+    load_x(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int sl = 0; sl < DSLOTS; ++sl) {
+      const int info = dinfo[sl], ti = info >> 20;
+      const int p = ri * TR + ((info >> 10) & 1023), q = ci * TC + (info & 1023);
+      const bool ok = info >= 0 && nb + ti < N && p < P && q < Q;
+      const uint32_t pix = ok ? (uint32_t)(__mul24(__mul24(ti, P) + p, Q) + q) : 0u;
+      dr[sl] = *reinterpret_cast<const Chunk*>(dt + (uint64_t)(pix & 0xffffffu) * (uint64_t)((uint32_t)K & 0xffffffu) + (sl * NTH + tid) % DCP * EV);
+      dok = sl == 0 ? (ok ? 1u : 0u) : dok | (ok ? 1u << sl : 0u);
+    }
+    put_x(std::integral_constant<int, 0>{});
+    load_x(std::integral_constant<int, HALF>{});
+#pragma unroll
+    for (int sl = 0; sl < DSLOTS; ++sl) {
+      const int idx = sl * NTH + tid;
+      put(&ds[idx / DCP * PK + idx % DCP * EV], L::DS, dr[sl], (dok >> sl) & 1u);
+    }
+    put_x(std::integral_constant<int, HALF>{});
+  };
+
   v16f acc[MI][9];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -292,35 +360,37 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   for (int t = 0; t < 9; ++t) toff[t] = ((t / 3) * SC + (t % 3)) * PX;
 
   auto compute = [&](int stage) {
-    const T* xs = lds + stage * L::STAGE;
-    const T* ds = xs + L::XS;
+    const E* xs = lds + stage * STAGE;
+    const E* ds = xs + L::PL * XS;
+    const int r16 = l32 & 15;
+    const int colsel = (l32 & 16) + 4 * (r16 & 3);
+    const E* tx = xs + wn * 32 + colsel;
+    const E* td = ds + wm * 32 * MI + colsel;
+    const int nss = (TP + 15) >> 4;
     if constexpr (F32) {
-      const float* fx = reinterpret_cast<const float*>(xs) + wn * 32 + l32;
-      const float* fd = reinterpret_cast<const float*>(ds) + wm * 32 * MI + l32;
-      const int nss = (TP + 7) >> 3;  // rows past the sub-tile's pixels are zero: skipped
 #pragma unroll 1
       for (int ss = 0; ss < nss; ++ss) {
+        const int ma = ss * 16 + hg * 8 + (r16 >> 2), mb = ma + 4;
+        const E* xa = tx + apos[ma] * PX;
+        const E* xb = tx + apos[mb] * PX;
+        v8bf fa[MI][3];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int m = ss * 8 + hg * 4 + t;
-          const float* bx = fx + apos[m] * PX;
-          float av[MI];
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int i = 0; i < MI; ++i) av[i] = fd[m * PK + i * 32];
+          for (int q = 0; q < 3; ++q) fa[i][q] = tr_read8<T>(td + q * L::DS + ma * PK + i * 32, td + q * L::DS + mb * PK + i * 32);
 #pragma unroll
-          for (int tap = 0; tap < 9; ++tap) {
-            const float bv = bx[toff[tap]];
+        for (int tap = 0; tap < 9; ++tap) {
+          v8bf fb[3];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) acc[i][tap] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv, acc[i][tap], 0, 0, 0);
-          }
+          for (int q = 0; q < 3; ++q) fb[q] = tr_read8<T>(xa + q * XS + toff[tap], xb + q * XS + toff[tap]);
+          constexpr int QA[6] = {2, 0, 1, 1, 0, 0}, QB[6] = {0, 2, 1, 0, 1, 0};  // the smallest first
+#pragma unroll
+          for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int i = 0; i < MI; ++i) acc[i][tap] = mfma16(fa[i][QA[q]], fb[QB[q]], acc[i][tap]);
         }
       }
     } else {
-      const int r16 = l32 & 15;
-      const int colsel = (l32 & 16) + 4 * (r16 & 3);
-      const T* tx = xs + wn * 32 + colsel;
-      const T* td = ds + wm * 32 * MI + colsel;
-      const int nss = (TP + 15) >> 4;
 #pragma unroll 2
       for (int ss = 0; ss < nss; ++ss) {
         const int ma = ss * 16 + hg * 8 + (r16 >> 2), mb = ma + 4;
@@ -328,10 +398,10 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         const T* xb = tx + apos[mb] * PX;
         typename V8<T>::type fa[MI];
 #pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i] = tr_read8(td + ma * PK + i * 32, td + mb * PK + i * 32);
+        for (int i = 0; i < MI; ++i) fa[i] = tr_read8<T>(td + ma * PK + i * 32, td + mb * PK + i * 32);
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
-          const typename V8<T>::type fb = tr_read8(xa + toff[tap], xb + toff[tap]);
+          const typename V8<T>::type fb = tr_read8<T>(xa + toff[tap], xb + toff[tap]);
 #pragma unroll
           for (int i = 0; i < MI; ++i) acc[i][tap] = mfma16(fa[i], fb, acc[i][tap]);
         }
@@ -339,15 +409,24 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     }
   };
 
-  if (nst > 0) { gload(t0); sstore(0); }
-  __syncthreads();
-  for (int g = 0; g + 1 < nst; ++g) {  // steady state without range checks
-    gload(t0 + g + 1);
-    compute(g & 1);
-    sstore((g + 1) & 1);
+  if constexpr (F32) {
+    for (int g = 0; g < nst; ++g) {
+      if (g > 0) __syncthreads();
+      stage32(t0 + g);
+      __syncthreads();
+      compute(0);
+    }
+  } else {
+    if (nst > 0) { gload(t0); sstore(0); }
     __syncthreads();
+    for (int g = 0; g + 1 < nst; ++g) {  // steady state without range checks
+      gload(t0 + g + 1);
+      compute(g & 1);
+      sstore((g + 1) & 1);
+      __syncthreads();
+    }
+    if (nst > 0) compute((nst - 1) & 1);
   }
-  if (nst > 0) compute((nst - 1) & 1);
 
   const int64_t outputs = (int64_t)K * 9 * C;
   float* dst = out + (int64_t)bz * outputs;
@@ -362,11 +441,38 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         dst[((int64_t)k * 9 + tap) * C + c] = acc[i][tap][e];
       }
     }
+  if constexpr (F32) {  // sums that are not finite, again as fp32 chains (split32.h)
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[i][tap][e], 0.f, sum);
+    __threadfence_block();
+    if (!__syncthreads_or(!(sum == 0.f))) return;
+    for (int i = tid; i < BMK * 9 * 64; i += NTH) {
+      const int k = k0 + i / (9 * 64), tap = i / 64 % 9, c = c0 + i % 64;
+      float& v = dst[((int64_t)k * 9 + tap) * C + c];
+      if (__fmaf_rn(v, 0.f, 0.f) == 0.f) continue;
+      float t = 0.f;
+      for (int tile = t0; tile < t1 && t == t; ++tile) {  // (a NaN stays one)
+        const int ci = tile % a.tiles_c, t2 = tile / a.tiles_c;
+        const int ri = t2 % a.tiles_r, nb = t2 / a.tiles_r * TI;
+        for (int m = 0; m < TP && t == t; ++m) {
+          const int n = nb + m / (TR * TC), p = ri * TR + m / TC % TR, q = ci * TC + m % TC;
+          const int y = p + tap / 3 - pad, xx = q + tap % 3 - pad;
+          if (n < N && p < P && q < Q && y >= 0 && y < H && xx >= 0 && xx < W)
+            t = __fmaf_rn(dz[(((int64_t)n * P + p) * Q + q) * K + k], x[(((int64_t)n * H + y) * W + xx) * C + c], t);
+        }
+      }
+      v = t;
+    }
+  }
 }
 
 // sub-tile geometry for a (P x Q) output grid: up to `cap` pixels and `maxpos` staged positions
-bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
-  int tc = Q < cap ? Q : cap;
+bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, W9Args& a) {
   int tr = cap / tc; if (tr > P) tr = P; if (tr < 1) tr = 1;
   int ti = (tr == P && tc == Q) ? cap / (P * Q) : 1;
   if (ti > N) ti = N; if (ti < 1) ti = 1;
@@ -379,6 +485,18 @@ bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
   a.tiles_r = (P + tr - 1) / tr; a.tiles_c = (Q + tc - 1) / tc;
   a.NT = ((N + ti - 1) / ti) * a.tiles_r * a.tiles_c;
   return true;
+}
+// The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (512 columns: 32 of 64 with 102
+// staged positions), the narrower one that covers the map with the fewest sub-tiles, then staged positions.
+bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
+  bool ok = w9_geometry_of(N, P, Q, Q < cap ? Q : cap, cap, maxpos, a);
+  if (ok && a.TP * 4 >= cap * 3) return ok;
+  for (int tc = 64; tc >= 8; tc /= 2) {
+    W9Args b = a;
+    if (tc >= Q || !w9_geometry_of(N, P, Q, tc, cap, maxpos, b)) continue;
+    if (!ok || b.NT < a.NT || (b.NT == a.NT && b.NPOS < a.NPOS)) { a = b; ok = true; }
+  }
+  return ok;
 }
 
 // everything decided from the layer shape: block shape, sub-tile geometry, number of pixel ranges
@@ -395,30 +513,29 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   if (!w9_geometry(g.N, g.P, g.Q, cap, maxpos, a)) return false;
   if (a.TP * 2 < cap) return false;  // short sub-tiles: too little work between barriers
   a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
-  // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD; in fp32 where a
-  // sub-tile is part of an image, whose addresses take longer: 262 144 pixels, 128 -> 128 channels, us with 64 and with 128 a
-  // block: 756 and 639 on 64 x 64 maps, 670 and 605 on 32 x 32, 678 and 617 on 16 x 16; on whole 8 x 8 images 638 and 609,
-  // and 92.5 and 95 for 128 -> 256 at 16 384 pixels, with twice the partial sums), unless the blocks
+  // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD), unless the blocks
   // would then get fewer than g_w9_wide_min sub-tiles each: a block's accumulators (9 taps x 64*MI x 64 floats) are
   // written out once per pixel range and read again by the reduction, and with few sub-tiles per range that traffic
   // outweighs the operand reuse (128->128 at 16x16, batch 256, bf16: 49.6 us with 64-channel blocks, 48.1 with
   // 128-channel blocks of four sub-tiles each).  At that size the 75 MB of partial sums written and read back are most
   // of the time: 19 GFLOP would take 8 us at the matrix cores' peak.
-  // fp32: blocks twice as wide mean twice as many ranges and bytes of partial sums, so only where there is room for these.
+  // fp32: 64 output channels per block, two blocks per CU where there is room for their partial sums (64 -> 64 channels at 1 048 576
+  // pixels 367 us, 472 with one; on the fp32 MFMA 800), a quarter of it left for what the placement of the tensors loses.
   const bool f32 = dt == DT_F32;
-  const bool wide = g.K % 128 == 0 && (!f32 || a.tiles_r * a.tiles_c > 1);
-  for (int mi = wide ? 2 : 1; mi >= 1; --mi) {
-    const int64_t tiles = (int64_t)(g.K / (64 * mi)) * (g.C / 64);
-    int64_t s = tiles >= 256 ? 1 : (256 + tiles / 2) / tiles;  // about one block per CU
+  for (int mi = f32 ? 2 : g.K % 128 == 0 ? 2 : 1; mi >= 1; --mi) {
+    const int target = f32 && mi == 2 ? 512 : 256;  // blocks
+    const int bk = f32 ? 64 : 64 * mi;
+    const int64_t tiles = (int64_t)(g.K / bk) * (g.C / 64);
+    int64_t s = tiles >= target ? 1 : (target + tiles / 2) / tiles;
     if (s > a.NT) s = a.NT;
-    if (s > 256) s = 256;
+    if (s > target) s = target;
     if (s < 1) s = 1;
     a.tiles_per_split = (int)((a.NT + s - 1) / s);
     s = (a.NT + a.tiles_per_split - 1) / a.tiles_per_split;  // no empty ranges
     if (mi == 2 && a.tiles_per_split < g_w9_wide_min) continue;
-    if (mi == 2 && f32 && (tiles * s < 128 || (ranges ? s != ranges : s * g.K * 9 * g.C * 4 > room))) continue;
+    if (mi == 2 && f32 && (ranges ? s != ranges : s * g.K * 9 * g.C * 4 > room / 4 * 3)) continue;
     if (tiles * s < 128) return false;  // too few blocks for the chip: one tap per block does better
-    pl.a = a; pl.mi = mi; pl.splits = (int)s;
+    pl.a = a; pl.mi = f32 ? 1 : mi; pl.splits = (int)s;
     return true;
   }
   return false;
@@ -426,13 +543,14 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
 
 template <class T, int MI, int WGM, bool FOLD>
 void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const W9Plan& pl) {
-  constexpr size_t sm = W9Lds<T, MI, WGM>::bytes;
-  constexpr bool WHOLE_TOO = sizeof(T) == 2 || WGM == 2;  // the plan gives whole images in fp32 to the narrow blocks
+  typedef W9Lds<T, MI, WGM> L;
+  constexpr size_t sm_max = L::bytes(W9Cfg<T>::MAXPOS);
+  const size_t sm = L::bytes(pl.a.NPOS);
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    if constexpr (WHOLE_TOO)
-      (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    if constexpr (sizeof(T) == 2)
+      (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
     attr_done = true;
   }
   W9Args a = pl.a;
@@ -444,7 +562,7 @@ void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const 
   const bool whole = a.tiles_r == 1 && a.tiles_c == 1 && a.TR == a.P && a.TC == a.Q && a.H == a.P && a.W == a.Q &&
                      (int64_t)a.N * a.H * a.W + (int64_t)a.TI * a.H * a.W < (1 << 24) && a.C < (1 << 24) && a.K < (1 << 24) &&
                      a.TI < 256 && (int64_t)a.TI * a.H * a.W < (1 << 20);
-  if constexpr (WHOLE_TOO) {
+  if constexpr (sizeof(T) == 2) {
     if (whole) {
       OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
       return;
@@ -483,8 +601,7 @@ void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz,
   W9Plan pl;
   if (!w9_plan(dt, g, 0, splits, pl)) return;
   pl.a.fold = dt == DT_F32 ? nullptr : fold;
-  if (dt == DT_F32 && pl.mi == 2) launch_w9<float, 1, 4, false>(st, x, dz, dst, pl);
-  else if (dt == DT_F32) launch_w9<float, 1, 2, false>(st, x, dz, dst, pl);
+  if (dt == DT_F32) launch_w9<float, 1, 2, false>(st, x, dz, dst, pl);
   else if (dt == DT_BF16) launch_w9_16<bf16_t>(st, x, dz, dst, pl);
   else launch_w9_16<f16_t>(st, x, dz, dst, pl);
 }

@@ -1,0 +1,47 @@
+// fp32 operands on the 16-bit matrix cores.
+//
+// A float is the sum of three bf16 values (8 + 8 + 8 bits of its 24): plane 0 is the value rounded to bf16, plane 1 what
+// that leaves, rounded, plane 2 what the two leave, exact but for its last rounding (2^-27 of the value).  The product of
+// two floats is then the six products of planes whose indices add up to at most two; the three left out are below 2^-26 of
+// it.  The 16-bit MFMAs multiply exactly and add in fp32, so a sum carries the error of its fp32 additions -- of six per 16
+// products, where the fp32 MFMA makes eight -- and six of them take 192 cycles of a SIMD for what the fp32 instruction
+// does in 512: registers only, on normally distributed values (the clock follows the power), 296 TFLOP/s of fp32 products
+// against 155.  Measured in the layers (us, fp32 MFMA -> this): 3x3, 64 -> 64 channels at 1 048 576 pixels forward and data gradient
+// 706 -> 446 (173 TFLOP/s), weight gradient 797 -> 367 (211); 128 -> 128 at 262 144 515 -> 420 and 719 -> 387; strided 64 -> 128
+// 260 -> 245, 227 -> 195 and 570 -> 435.
+//
+// Not finite: a value beyond the largest bf16, an infinity or a NaN makes planes that are not finite, and every sum with it
+// a NaN.  The kernels look for sums that are not finite when they store a tile and compute those again as fp32 chains of
+// multiply-adds, so that infinities and NaNs come out as from fp32 arithmetic.
+#pragma once
+#include "dev_common.h"
+
+namespace oseq {
+
+// two floats -> their three planes, each a pair of bf16 in one register
+__device__ __forceinline__ void split32_pair(float a, float b, uint32_t (&p)[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    p[q] = __builtin_bit_cast(uint32_t, from_f32x2<bf16_t>(a, b));
+    if (q < 2) {
+      const uint32_t lo = p[q] << 16, hi = p[q] & 0xffff0000u;
+      a -= __builtin_bit_cast(float, lo);
+      b -= __builtin_bit_cast(float, hi);
+    }
+  }
+}
+
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+
+// four floats -> their three planes, 8 bytes each
+__device__ __forceinline__ void split32(const Chunk& c, u32x2_t (&p)[3]) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  const f32x4 v = __builtin_bit_cast(f32x4, c);
+  uint32_t lo[3], hi[3];
+  split32_pair(v[0], v[1], lo);
+  split32_pair(v[2], v[3], hi);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) { p[q][0] = lo[q]; p[q][1] = hi[q]; }
+}
+
+}  // namespace oseq

@@ -2,6 +2,8 @@
 
 Tolerances: relative L2 per gradient tensor <= 1e-4 in fp32 mode, <= 2e-2 in bf16/fp16 mode; loss likewise.
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -312,6 +314,77 @@ def test_stem_kernels_at_tile_edges(precision, cin, cout, stride, pad, h, w, b, 
     errs = plain_errors(units, h, w, r["grads"], g)
     assert max(errs.values()) <= TOL[precision], errs
     assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+
+
+def _layer64(x, w, stride):
+    """NHWC "same" convolution in float64 on the GPU, one matrix product per tap."""
+    import torch
+    k = w.shape[1]
+    n, h, wd, _ = x.shape
+    p, q = (h - 1) // stride + 1, (wd - 1) // stride + 1
+    x = torch.nn.functional.pad(x, (0, 0, k // 2, k // 2, k // 2, k // 2))
+    y = sum(x[:, i:i + (p - 1) * stride + 1:stride, j:j + (q - 1) * stride + 1:stride, :].reshape(-1, x.shape[3]) @ w[:, i, j, :].t()
+            for i in range(k) for j in range(k))
+    return y.reshape(n, p, q, -1)
+
+
+@pytest.mark.parametrize("c,cout,ksize,stride,h,w,b", [
+    (64, 64, 3, 1, 73, 129, 14), (64, 128, 3, 1, 200, 9, 73), (80, 64, 3, 1, 37, 41, 87), (64, 64, 3, 1, 8, 8, 2048),  # split forward
+    (64, 128, 3, 2, 129, 257, 16), (128, 64, 1, 1, 61, 67, 33), (64, 64, 1, 2, 127, 255, 17),
+    (64, 64, 3, 1, 65, 70, 3), (64, 128, 3, 1, 4, 4, 9), (128, 64, 3, 1, 2, 2, 41), (128, 128, 3, 2, 15, 9, 5), (192, 64, 1, 1, 7, 5, 3)])
+def test_fp32_on_the_16bit_matrix_cores_is_fp32(c, cout, ksize, stride, h, w, b):
+    """fp32 layers whose operands are split into three bf16 planes: forward (131 072 output pixels or more), data and weight
+    gradient against float64, at edges of the sub-tiles.  Bar: 2^-24 per rounding of a chain of 6 * 9 * 192 / 16 additions and of
+    the ranges, random signs: 2^-24 * sqrt(700) = 1.6e-6."""
+    import torch
+    units = [W.conv(c, c, 1, bn=False, relu=False, bias=True), W.conv(c, cout, ksize, stride, bn=False, relu=False, bias=True),
+             W.gap_linear_ce(cout, 10)]
+    from paper_2105_00619_amd.binding import SeqTrainer
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=b, height=h, width=w, channels=c, num_classes=10)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    shapes = [(c, 1, 1, c), (c,), (cout, ksize, ksize, c), (cout,), (10, cout), (10,)]
+    params = [torch.randn(s, generator=g, device="cuda") * (2.0 / max(1, math.prod(s[1:]))) ** 0.5 for s in shapes]
+    t.set_params(torch.cat([q.flatten() for q in params]))
+    x = torch.randn((b, h, w, c), generator=g, device="cuda") * 10.0 ** torch.randint(-3, 2, (b, 1, 1, c), generator=g, device="cuda")
+    y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
+    grads = torch.empty(t.param_count, device="cuda")
+    t.step(x, y, 0.0, grads=grads)
+    out = t.unit_output(x, 1).double().reshape(b, (h - 1) // stride + 1, (w - 1) // stride + 1, cout)
+    t.close()
+    p64 = [q.double().requires_grad_(True) for q in params]
+    z = _layer64(_layer64(x.double(), p64[0], 1) + p64[1], p64[2], stride) + p64[3]
+    assert float((out - z.detach()).norm() / z.detach().norm()) < 1.6e-6
+    torch.nn.functional.cross_entropy(z.mean((1, 2)) @ p64[4].t() + p64[5], y.long()).backward()
+    at = 0
+    for name, q in zip(("through the data gradient", "bias", "weight gradient"), p64):
+        d = grads[at:at + q.numel()].double().view(q.shape) - q.grad
+        at += q.numel()
+        if name != "bias":
+            assert float(d.norm() / q.grad.norm()) < 1.6e-6, name
+
+
+@pytest.mark.parametrize("ksize,stride", [(3, 1), (3, 2), (1, 1)])
+def test_fp32_infinities_and_nans_come_out_as_from_fp32(ksize, stride):
+    """A pixel with an infinity, one with a NaN and one beyond the largest bf16, in a layer that splits its fp32 operands."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    b, h, c, cout = 8, 128 * stride, 64, 64
+    units = [W.conv(c, cout, ksize, stride, bn=False, relu=False, bias=True), W.gap_linear_ce(cout, 10)]
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=b, height=h, width=h, channels=c, num_classes=10)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    wt = torch.randn((cout, ksize, ksize, c), generator=g, device="cuda") * 0.05
+    t.set_params(torch.cat([wt.flatten(), torch.zeros(cout + 10 * cout + 10, device="cuda")]))
+    x = torch.randn((b, h, h, c), generator=g, device="cuda")
+    x[1, 10, 20, 3] = float("inf")
+    x[2, 60, 40, 5] = float("nan")
+    x[3, 32, 64, 7] = 3.4e38
+    got = t.unit_output(x, 0).reshape(b, h // stride, h // stride, cout).double()
+    t.close()
+    want = _layer64(x.double(), wt.double(), stride)
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got == float("inf"), want == float("inf")) and torch.equal(got == -float("inf"), want == -float("inf"))
+    ok = want.isfinite()
+    assert bool(((got - want).abs()[ok] <= 1e-5 * (want.abs()[ok] + 1.0)).all())
 
 
 @pytest.mark.parametrize("precision", [W.FP32, W.FP16])
