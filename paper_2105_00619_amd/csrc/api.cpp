@@ -94,6 +94,8 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_splits = conv_mfma_dgrad_splits(dt, g);
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
+        f.bwd_fuse = f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g);
+        if (f.bwd_fuse) f.wgrad_splits = conv_bwd1x1_splits(g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
         if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
       }
@@ -105,6 +107,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
     // more partial sums where the backward pass of the layer's unit has room for them anyway
     auto splits_in = [&](const FOp& f, int64_t room) {
       const ConvGeom g{f.N, f.H, f.W, f.C, f.K, f.R, f.S, f.stride, f.pad, f.P, f.Q};
+      if (f.bwd_fuse) return f.wgrad_splits;
       return f.wgrad_algo == ALGO_MFMA ? conv_mfma_wgrad_splits(cfg->precision, g, room)
              : f.wgrad_algo == ALGO_SMALLC ? conv_smallc_wgrad_splits(cfg->precision, g, room) : f.wgrad_splits;
     };
@@ -417,6 +420,14 @@ void run_op(const Ctx& c, const SOp& s) {
       else
         launch_conv_dgrad_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), c.at(s.in[1]), c.at(s.out[0]), geom(f));
       break;
+    case S_CONV_BWD: {
+      const FOp& ap = h->plan.fops[s.fop + 2];
+      launch_conv_bwd1x1(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
+                         (const float*)c.at(s.in[4]) + (int64_t)ap.red_blocks * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
+                         c.at(s.in[5]), (const float*)c.at(s.in[6]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
+                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f));
+      break;
+    }
     case S_POOL_BWD:
       launch_maxpool_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), f.N, f.H, f.W, f.C);
       break;
@@ -428,6 +439,7 @@ int class_of(SKind k, const FOp& f) {
   switch (k) {
     case S_CAST_IN: return OPTORCH_K_CAST_IN;
     case S_CONV_FWD: return pointwise ? OPTORCH_K_CONV1X1_FWD : OPTORCH_K_CONV_FWD;
+    case S_CONV_BWD: return OPTORCH_K_CONV1X1_DGRAD;
     case S_DGRAD: return pointwise ? OPTORCH_K_CONV1X1_DGRAD : OPTORCH_K_CONV_DGRAD;
     case S_WGRAD: return pointwise ? OPTORCH_K_CONV1X1_WGRAD : OPTORCH_K_CONV_WGRAD;
     case S_BN_STATS: return OPTORCH_K_BN_STATS;
@@ -464,8 +476,13 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
       {  // the reduction reads dA, z and the ReLU source; the apply pass reads them again and writes dz (+ the skip gradient)
         const double src = s.in[3] < 0 ? 0.0 : s.variant == 2 ? 1.0 / 16 : 1.0;  // a bit mask is a sixteenth of a tensor
         const double da = s.per_image ? 0.0 : 1.0;  // (a gradient per image is next to nothing)
+        if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + da + src); break; }  // (the sums only)
         *bytes = e * out_px * f.C * (1 + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
+      break;
+    case S_CONV_BWD:  // dA, z and the ReLU source, x, dx, the weights and their gradient
+      *flops = 4 * out_px * wts;
+      *bytes = e * out_px * f.K * (1 + (s.per_image ? 0.0 : 1.0) + (s.in[3] < 0 ? 0.0 : 1.0 / 16)) + e * in_px * f.C * 2 + (e + 4) * wts;
       break;
     case S_POOL_FWD: *bytes = e * (in_px + out_px) * f.C; break;
     case S_POOL_BWD: *bytes = e * (2 * in_px + out_px) * f.C; break;

@@ -1798,7 +1798,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* __restri
   }
 }
 
-static void launch_wgrad_reduce(hipStream_t st, const float* partial, float* out, int64_t n, int splits) {
+void launch_wgrad_reduce(hipStream_t st, const float* partial, float* out, int64_t n, int splits) {
   const int64_t quads = n / 4;  // n is a multiple of 4 (C % 64 == 0)
   if (splits >= 64 || (splits >= 16 && quads < 65536))
     OSEQ_LAUNCH(wgrad_reduce_kernel<16>, dim3(ceil_div(quads, 16)), dim3(256), 0, st, partial, out, n, splits);

@@ -876,6 +876,7 @@ void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const 
   float* coef = ws + (int64_t)nblk * 2 * C;
   FIN_LAUNCH(bn_bwd_finalize_kernel, 0, st, ws, nblk, C, (double)rows, dgamma,
                      dbeta, coef);
+  if (!dz) return;
 #define APPLY(T, V, MS, ...)                                                                                            \
   OSEQ_LAUNCH((bn_bwd_apply_kernel<T, V, MS, __VA_ARGS__>), grid, dim3(256), 0, st, (const T*)da, (const T*)z,             \
                      (const T*)aout, (const uint8_t*)mask, stats, coef, (T*)dz, (T*)dskip, ra)

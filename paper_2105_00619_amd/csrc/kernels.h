@@ -46,6 +46,7 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
                           int C, int relu);
 // per_image (0: no): da is the gradient per image, [rows / per_image][C], of a tensor that only a global average pool reads;
 // then C is a multiple of 16 / element size, aout and dskip are null, rows < 2^32
+// dz null: the sums, dgamma, dbeta and, behind the partial sums in ws, their means [2][C] only
 // ReLU decisions: from mask (bits as launch_bn_apply writes them, applied whatever relu says) if given, else from the
 // sign of aout if given, else redone from z when relu is set
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
@@ -136,6 +137,16 @@ bool conv_mfma_wgrad_ok(int dt, const ConvGeom& g);
 int conv_mfma_wgrad_splits(int dt, const ConvGeom& g, int64_t room);
 void launch_conv_wgrad_mfma(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                             const ConvGeom& g, const float* fold = nullptr);
+// The backward pass of a 1x1 layer and of the BatchNorm behind it as one kernel (k_conv_bwd1x1.hip).  da .. relu, per_image as for
+// launch_bn_bwd (decisions from mask or redone from z); coef: what its finishing kernel left behind the partial sums, [2][C_out];
+// x, fold, partial, splits as for the weight gradient, wt, dx as for the data gradient
+bool conv_bwd1x1_ok(int dt, const ConvGeom& g);
+int conv_bwd1x1_splits(const ConvGeom& g);
+void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* z, const void* mask, const float* stats, const float* coef,
+                        int relu, int per_image, const void* x, const float* fold, const void* wt, void* dx, float* dw, float* partial,
+                        int splits, const ConvGeom& g);
+// adds the pixel ranges' partial sums [splits][n] in order
+void launch_wgrad_reduce(hipStream_t st, const float* partial, float* out, int64_t n, int splits);
 // Transposed weight copies for the data-gradient GEMMs, all layers in one launch (per 48 layers).  w_off: element
 // offset of the layer's weights in the flat parameter vector (the same offset is used in the transposed copy).
 struct TransposeJob { int64_t w_off; int K, RS, C, first_block; };

@@ -298,7 +298,8 @@ bool is_fwd_kind(SKind k) { return k <= S_HEAD_FWD; }
 
 bool has_side_effect(SKind k) {
   // writes parameter gradients, the loss, or BN running statistics
-  return k == S_HEAD_FWD || k == S_HEAD_BWD || k == S_BN_BWD || k == S_BIAS_GRAD || k == S_WGRAD || k == S_BN_STATS;
+  return k == S_HEAD_FWD || k == S_HEAD_BWD || k == S_BN_BWD || k == S_BIAS_GRAD || k == S_WGRAD || k == S_BN_STATS ||
+         k == S_CONV_BWD;
 }
 
 struct Scheduler {
@@ -314,12 +315,13 @@ struct Scheduler {
                                  //              (the gradient through a skip connection is not written out: its
                                  //              reader applies the mask to the block output's gradient itself), or -1
   std::vector<char> per_image;   // [LTensor] -> grad[t] (or image_grad[t]) holds one value per image and channel
+  std::vector<int> fused_bwd;    // [FOp of a convolution] -> entry of the BatchNorm-backward sums that its S_CONV_BWD goes on from, or -1
   std::vector<int> image_grad;   // [LTensor] -> Inst id of the gradient per image of the global average pool's input, or -1
   explicit Scheduler(Plan& pl)
       : p(pl), cur(pl.tensors.size(), -1), grad(pl.tensors.size(), -1), stat_ws(pl.tensors.size(), -1),
         bn_apply_of(pl.tensors.size(), -1), rebuilt(pl.tensors.size(), 0), readers(pl.tensors.size(), 0),
         via_pool(pl.tensors.size(), -1), gmask(pl.tensors.size(), -1), per_image(pl.tensors.size(), 0),
-        image_grad(pl.tensors.size(), -1) {
+        fused_bwd(pl.fops.size(), -1), image_grad(pl.tensors.size(), -1) {
     for (size_t fi = 0; fi < pl.fops.size(); ++fi) {
       const FOp& f = pl.fops[fi];
       if (f.kind == F_BN_APPLY) bn_apply_of[f.out] = (int)fi;
@@ -460,6 +462,17 @@ struct Scheduler {
     return f.skip < 0 || masked_skip_grad_ok(fi);
   }
 
+  // The convolution that the BatchNorm apply operation fi belongs to, if its S_CONV_BWD does that one's backward pass as well:
+  // a gradient of the skip connection must not need a tensor written from it, the ReLU decisions must not come from the
+  // output, and nothing may have been added to the gradient of the convolution's input yet.
+  int fused_conv_of(int fi) const {
+    const FOp& f = p.fops[fi];
+    if (fi < 2 || p.fops[fi - 2].kind != F_CONV || !p.fops[fi - 2].bwd_fuse || p.fops[fi - 2].out != f.x) return -1;
+    if (f.skip >= 0 && (f.mask < 0 || !masked_skip_grad_ok(fi))) return -1;
+    if (!p.tensors[p.fops[fi - 2].x].needs_grad || grad[p.fops[fi - 2].x] >= 0) return -1;
+    return fi - 2;
+  }
+
   bool emit_fop_backward(int fi, int seg) {
     const FOp& f = p.fops[fi];
     switch (f.kind) {
@@ -501,7 +514,9 @@ struct Scheduler {
         } else if (f.mask >= 0) {
           s.in[3] = cur[f.mask]; s.variant = 2;
         }
-        s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
+        const int conv = variant == 0 ? fused_conv_of(fi) : -1;
+        if (conv >= 0) fused_bwd[conv] = (int)p.sched.size() - 1;
+        else { s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1; }
         if (f.skip >= 0 && p.tensors[f.skip].needs_grad) {
           if (grad[f.skip] >= 0) { p.error = "internal: skip gradient must be the first contribution"; return false; }
           if (masked_skip_grad_ok(fi)) {  // nothing written
@@ -514,6 +529,19 @@ struct Scheduler {
         return true;
       }
       case F_CONV: {
+        if (fused_bwd[fi] >= 0) {
+          const int xin = f.fold_src >= 0 ? cur[p.fops[f.fold_src].x] : backward_input(f.x, seg);
+          const SOp sums = p.sched[fused_bwd[fi]];
+          SOp& s = push(S_CONV_BWD, fi, PH_BWD, seg);
+          for (int i = 0; i < 4; ++i) s.in[i] = sums.in[i];
+          s.variant = sums.variant; s.per_image = sums.per_image;
+          s.in[4] = sums.out[2];
+          s.in[5] = xin;
+          if (f.fold_src >= 0) s.in[6] = cur[p.fops[f.fold_src].stats];
+          s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
+          if (f.wgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.wgrad_splits * f.K * f.R * f.S * f.C * 4, false);
+          return true;
+        }
         int g = grad[f.out];
         if (g < 0) { p.error = "internal: conv output has no gradient"; return false; }
         if (!f.has_bn && f.relu) {
@@ -585,9 +613,9 @@ int launches_of(const SOp& op, const FOp& f) {
     case S_HEAD_FWD: return f.head_ws > 0 ? 5 : 4;
     case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
-    case S_BN_BWD: return 3;
+    case S_BN_BWD: return op.out[0] >= 0 ? 3 : 2;
     case S_BIAS_GRAD: return 2;
-    case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;
+    case S_WGRAD: case S_CONV_BWD: return f.wgrad_splits > 1 ? 2 : 1;
     case S_CONV_FWD: return f.fwd_splits > 1 ? 2 : 1;
     case S_DGRAD: return f.dgrad_splits > 1 ? 2 : 1;
     default: return 1;

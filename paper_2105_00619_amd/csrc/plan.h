@@ -54,6 +54,7 @@ struct FOp {
   int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
   bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
                              // of the head's kernels
+  int bwd_fuse = 0;          // F_CONV: 1 = the BatchNorm behind it, whose backward sums are known, and both gradients run as one kernel
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
   int fwd_splits = 1, dgrad_splits = 1;  // fixed by shape only: deterministic split of the GEMM depth
@@ -65,7 +66,8 @@ struct FOp {
 
 enum SKind {
   S_CAST_IN, S_CONV_FWD, S_BN_STATS, S_BN_APPLY, S_POOL_FWD, S_HEAD_FWD,
-  S_HEAD_BWD, S_BN_BWD, S_RELU_BWD, S_BIAS_GRAD, S_WGRAD, S_DGRAD, S_POOL_BWD
+  S_HEAD_BWD, S_BN_BWD, S_RELU_BWD, S_BIAS_GRAD, S_WGRAD, S_DGRAD, S_POOL_BWD,
+  S_CONV_BWD  // FOp::bwd_fuse: apply pass of the BatchNorm backward, weight and data gradient of the convolution `fop`
 };
 enum Phase { PH_FWD_NOSAVE = 0, PH_FWD_LAST = 1, PH_REPLAY = 2, PH_BWD = 3 };
 
@@ -85,7 +87,7 @@ struct SOp {
   SKind kind = S_CONV_FWD;
   int fop = -1;
   int phase = 0, seg = 0;
-  int in[4] = {-1, -1, -1, -1};
+  int in[7] = {-1, -1, -1, -1, -1, -1, -1};
   int out[5] = {-1, -1, -1, -1, -1};
   int variant = 0;  // S_BN_BWD: 1 = in[0] is the gradient of the 2x2 max-pool behind the activation (pooled size);
                     // 2 = in[3] is a bit mask of ReLU decisions (FOp::mask) to apply to in[0], not an activation.
@@ -94,6 +96,9 @@ struct SOp {
                     // and that slot its statistics tensor (FOp::fold_src)
                     // S_BN_APPLY with in[3] >= 0: in[2] is the z of the projection shortcut's BatchNorm, in[3] its
                     // statistics tensor (FOp::fold_skip)
+                    // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
+                    // S_BN_BWD, in[4] its workspace, in[5] the convolution's input (the z of a folded BatchNorm with in[6]
+                    // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
   bool per_image = false;  // S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
   bool live = true;
