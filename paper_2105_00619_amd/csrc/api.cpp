@@ -95,6 +95,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
         f.bwd_fuse = f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g);
+        f.image_addend = f.dgrad_algo == ALGO_MFMA && conv_dgrad_image_addend_ok(dt, g);
         if (f.bwd_fuse) f.wgrad_splits = conv_bwd1x1_splits(g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
         if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
@@ -373,12 +374,15 @@ void run_op(const Ctx& c, const SOp& s) {
     case S_POOL_FWD:
       launch_maxpool_fwd(st, dt, c.at(s.in[0]), c.at(s.out[0]), f.N, f.H, f.W, f.C);
       break;
-    case S_HEAD_FWD:
+    case S_HEAD_FWD: {
+      const HeadApply ap{(const float*)c.at(s.in[1]), c.at(s.in[2]), (const float*)c.at(s.in[3]), c.at(s.out[5]),
+                         s.variant == 1 ? h->plan.fops[s.fop - 1].relu : 0};
       launch_head_fwd(st, dt, c.at(s.in[0]), f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, c.w32(f.w_off),
                       c.w32(f.b_off), c.y, h->scale / (float)f.N, (float*)c.at(s.out[0]), (float*)c.at(s.out[1]),
                       (float*)c.at(s.out[2]), (float*)c.at(s.out[3]), c.loss(), c.flags(),
-                      f.head_ws > 0 ? (float*)c.at(f.head_ws_in_x ? s.in[0] : s.out[4]) : nullptr);
+                      f.head_ws > 0 ? (float*)c.at(f.head_ws_in_x ? s.in[0] : s.out[4]) : nullptr, s.variant == 1 ? &ap : nullptr);
       break;
+    }
     case S_HEAD_BWD:
       launch_head_bwd(st, dt, (const float*)c.at(s.in[0]), (const float*)c.at(s.in[1]), c.w32(f.w_off), f.N, f.H * f.W, f.C,
                       f.gap, f.feat_dim, f.classes, c.g32(f.w_off), c.g32(f.b_off), (float*)c.at(s.out[1]), c.at(s.out[0]), c.at(s.out[2]));
@@ -416,7 +420,7 @@ void run_op(const Ctx& c, const SOp& s) {
     case S_DGRAD:
       if (f.dgrad_algo == ALGO_MFMA)
         launch_conv_dgrad_mfma(st, dt, c.at(s.in[0]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize, c.at(s.in[1]),
-                               c.at(s.in[2]), c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f));
+                               c.at(s.in[2]), s.per_image, c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f));
       else
         launch_conv_dgrad_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), c.at(s.in[1]), c.at(s.out[0]), geom(f));
       break;
@@ -463,7 +467,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_CONV_FWD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K + wts); break;
     case S_DGRAD:
       *flops = 2 * out_px * wts;
-      *bytes = e * (in_px * f.C * (s.in[1] >= 0 ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0);
+      *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0);
       break;
     case S_WGRAD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K) + 4 * wts; break;
     case S_BN_STATS: *bytes = s.in[1] >= 0 ? 8.0 * f.stat_blocks * f.C : e * out_px * f.C; break;  // fused: only the block sums
@@ -488,7 +492,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_POOL_BWD: *bytes = e * (2 * in_px + out_px) * f.C; break;
     case S_RELU_BWD: *bytes = e * 3 * out_px * f.K; break;
     case S_BIAS_GRAD: *bytes = e * out_px * f.K; break;
-    case S_HEAD_FWD: *bytes = e * in_px * f.C; break;
+    case S_HEAD_FWD: *bytes = e * in_px * f.C * (1 + (s.variant == 1 && s.in[2] >= 0 ? 1.0 : 0.0) + (s.out[5] >= 0 ? 1.0 / 16 : 0)); break;
     case S_HEAD_BWD: *bytes = e * in_px * f.C; break;
   }
 }
@@ -688,7 +692,16 @@ extern "C" int optorch_seq_debug_unit_output(optorch_seq_t* h, const float* x_de
   bool found = false;
   for (const SOp& s : p.sched) {
     if (!s.live || (s.phase != PH_FWD_NOSAVE && s.phase != PH_FWD_LAST)) continue;
-    if (s.kind == S_HEAD_FWD) break;
+    if (s.kind == S_HEAD_FWD) {
+      if (s.variant != 1 || p.fops[s.fop - 1].out != lt) break;
+      // the head's pooling kernel does the last apply operation: here on its own, to the place of its z
+      const FOp& f = p.fops[s.fop - 1];
+      launch_bn_apply(st, h->dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.at(s.in[2]), (const float*)c.at(s.in[3]), c.at(s.in[0]),
+                      nullptr, (int64_t)f.N * f.P * f.Q, f.C, f.relu);
+      launch_cast_out(st, h->dt, c.at(s.in[0]), out_dev, (int64_t)n);
+      found = true;
+      break;
+    }
     run_op(c, s);
     for (int o : s.out)
       if (o >= 0 && p.insts[o].logical == lt) found = true;

@@ -21,11 +21,25 @@ typedef __attribute__((ext_vector_type(4))) float epi_v4f;
 // HB: what `bias` is: 0 not used, 1 a bias per channel, EPI_AFFINE the scale of an inference-mode BatchNorm per channel,
 // its shift aff_ld floats behind it (one fused multiply-add on the fp32 sum)
 constexpr int EPI_AFFINE = 2;
-template <int NT, class T, int BN, int HR, int HB, bool HA, bool STAT, class RowOff>
+// addoff(row, ro): element offset of the addend's values for block row `row`, whose output lies at ro: the same place, or that of
+// one row per image (the gradient of a global average pool)
+struct AddSame {
+  __device__ __forceinline__ int64_t operator()(int, int64_t ro) const { return ro; }
+};
+struct AddImage {
+  bool on;        // false: as AddSame
+  FastDiv hw;     // pixels per image
+  int64_t m0;     // the block's first pixel
+  int channels;
+  __device__ __forceinline__ int64_t operator()(int row, int64_t ro) const {
+    return on ? (int64_t)hw.div((uint32_t)(m0 + row)) * channels : ro;
+  }
+};
+template <int NT, class T, int BN, int HR, int HB, bool HA, bool STAT, class RowOff, class AddOff = AddSame>
 __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int n0, const float* __restrict__ bias,
                                                const T* __restrict__ addend, const uint8_t* __restrict__ amask,
                                                T* __restrict__ out, int relu, RowOff rowoff,
-                                               float (&ss)[8], float (&qq)[8], int aff_ld = 0) {
+                                               float (&ss)[8], float (&qq)[8], int aff_ld = 0, AddOff addoff = AddOff()) {
   constexpr int EP_PITCH = BN + 4;
   constexpr int GROUPS = BN / 8;                // 8-channel groups per row
   constexpr int PER_THREAD = HR * GROUPS / NT;  // rows per thread
@@ -50,7 +64,7 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
   if (HA) {  // rows that are not stored read the tensor's first row
 #pragma unroll
     for (int it = 0; it < PER_THREAD; ++it)
-      ad[it] = *reinterpret_cast<const Vec<T, 8>*>(addend + (ro[it] >= 0 ? ro[it] : 0) + col);
+      ad[it] = *reinterpret_cast<const Vec<T, 8>*>(addend + (ro[it] >= 0 ? addoff(erow + it * RG, ro[it]) : 0) + col);
 #pragma unroll
     for (int it = 0; it < PER_THREAD; ++it) {
       mb[it] = 0xffu;
@@ -120,7 +134,7 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
 // issued before stores can be waited for without waiting for those stores.
 template <int NT, class T, int BN, int HR, class RowOff>
 __device__ __forceinline__ void epi_load_addend_nt(int tid, int n0, const T* __restrict__ addend,
-                                                   const uint8_t* __restrict__ amask, RowOff rowoff,
+                                                   const uint8_t* __restrict__ amask, RowOff rowoff, const AddImage& image,
                                                    Vec<T, 8> (&ad)[HR * (BN / 8) / NT], unsigned (&mb)[HR * (BN / 8) / NT]) {
   constexpr int GROUPS = BN / 8, PER_THREAD = HR * GROUPS / NT, RG = NT / GROUPS;
   const int col = n0 + (tid % GROUPS) * 8, erow = tid / GROUPS;
@@ -128,7 +142,9 @@ __device__ __forceinline__ void epi_load_addend_nt(int tid, int n0, const T* __r
   for (int it = 0; it < PER_THREAD; ++it) {
     const int64_t ro = rowoff(erow + it * RG);
     const int64_t e = (ro >= 0 ? ro : 0) + col;  // rows that are not stored read the tensor's first row
-    if constexpr (sizeof(T) == 2) {  // read once, by this block only
+    if (image.on) {
+      ad[it] = *reinterpret_cast<const Vec<T, 8>*>(addend + (ro >= 0 ? image(erow + it * RG, ro) : 0) + col);
+    } else if constexpr (sizeof(T) == 2) {  // read once, by this block only
       typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
       ad[it] = __builtin_bit_cast(Vec<T, 8>, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(addend + e)));
     } else {
@@ -167,25 +183,25 @@ __device__ __forceinline__ void epi_store_rows_pre_nt(const float* ep, int tid, 
 // The uniform choice of the code path.  CAN_BIAS / CAN_ADD: whether the calling kernel is ever given a bias / an
 // addend (forward kernels have no addend, data-gradient kernels no bias); the combinations that cannot occur are not
 // compiled, which keeps their registers out of the kernel.
-template <int NT, class T, int BN, int HR, bool CAN_BIAS, bool CAN_ADD, bool STAT, class RowOff>
+template <int NT, class T, int BN, int HR, bool CAN_BIAS, bool CAN_ADD, bool STAT, class RowOff, class AddOff = AddSame>
 __device__ __forceinline__ void epi_store_pass_nt(const float* ep, int tid, int n0, const float* __restrict__ bias,
                                                   const T* __restrict__ addend, const uint8_t* __restrict__ amask,
                                                   T* __restrict__ out, int relu, RowOff rowoff,
-                                                  float (&ss)[8], float (&qq)[8]) {
+                                                  float (&ss)[8], float (&qq)[8], AddOff addoff = AddOff()) {
   if (CAN_BIAS && bias) {
-    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 1, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 1, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq, 0, addoff);
     else epi_store_rows_nt<NT, T, BN, HR, 1, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
   } else {
-    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 0, true, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+    if (CAN_ADD && addend) epi_store_rows_nt<NT, T, BN, HR, 0, true, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq, 0, addoff);
     else epi_store_rows_nt<NT, T, BN, HR, 0, false, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
   }
 }
-template <class T, int BN, int HR, bool CAN_BIAS, bool CAN_ADD, bool STAT, class RowOff>
+template <class T, int BN, int HR, bool CAN_BIAS, bool CAN_ADD, bool STAT, class RowOff, class AddOff = AddSame>
 __device__ __forceinline__ void epi_store_pass(const float* ep, int tid, int n0, const float* __restrict__ bias,
                                                const T* __restrict__ addend, const uint8_t* __restrict__ amask,
                                                T* __restrict__ out, int relu, RowOff rowoff,
-                                               float (&ss)[8], float (&qq)[8]) {
-  epi_store_pass_nt<256, T, BN, HR, CAN_BIAS, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq);
+                                               float (&ss)[8], float (&qq)[8], AddOff addoff = AddOff()) {
+  epi_store_pass_nt<256, T, BN, HR, CAN_BIAS, CAN_ADD, STAT>(ep, tid, n0, bias, addend, amask, out, relu, rowoff, ss, qq, addoff);
 }
 
 // The store pass of a convolution with the inference-mode BatchNorm behind it: the activation itself is stored, with the

@@ -1238,13 +1238,18 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
   else launch_igemm<IG_FWD>(st, dt, fwd_split32(dt, g), x, w, bias, nullptr, out, partial, stat_partial, splits, a);
 }
 
+// the 1x1 kernels, whose rows are pixels in order
+bool conv_dgrad_image_addend_ok(int dt, const ConvGeom& g) {
+  return conv_pointwise_dgrad_ok(dt, g) && g.stride == 1 && (int64_t)g.N * g.H * g.W < (int64_t)1 << 32;
+}
+
 // wt: the (C_in, kh, kw, C_out) transpose of the weights, in the compute type
 void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                            const void* addend_mask, void* dx, float* partial, int splits, const ConvGeom& g) {
+                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g) {
   PatchShape pv; PatchArgs pa{};
   const uint8_t* amask = addend ? (const uint8_t*)addend_mask : nullptr;
   if (conv_pointwise_dgrad_ok(dt, g)) {
-    launch_conv_dgrad_pointwise(st, dt, dz, wt, addend, amask, dx, g);
+    launch_conv_dgrad_pointwise(st, dt, dz, wt, addend, amask, addend_per_image, dx, g);
     return;
   }
   if (!addend && dgrad_ws3x3(dt, g)) {

@@ -50,6 +50,7 @@ struct PwArgs {
   int dstH, dstW, srcH, srcW;
   FastDiv div_w, div_hw;  // by dstW and dstH * dstW
   const uint8_t* amask;   // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
+  int add_image;          // stride 1: the addend is one row per image, not one per pixel
   int eval;               // 1: the EVAL instantiations (inference-mode BatchNorm in the epilogue, `bias` is its [2][Ng]
                           // scale and shift and `addend` its skip connection)
   const float* fold;      // forward: X is the z of a BatchNorm + ReLU whose [4][Kd] statistics tensor this is; the rows are
@@ -261,7 +262,8 @@ conv1x1_kernel(const T* __restrict__ X, const T* __restrict__ W, const float* __
     };
     if (DGRAD) {
       if (a.scatter) scatter_rows<T, BN>(ep, tid, n0, m0 + u * 64, addend, out, a);
-      else epi_store_pass<T, BN, 64, false, true, false>(ep, tid, n0, bias, addend, a.amask, out, 0, rowoff, ss, qq);
+      else epi_store_pass<T, BN, 64, false, true, false>(ep, tid, n0, bias, addend, a.amask, out, 0, rowoff, ss, qq,
+                                                         AddImage{a.add_image != 0, a.div_hw, m0 + u * 64, a.Ng});
     } else if (EVAL) {
       epi_eval_pass_nt<256, T, BN, 64>(ep, tid, n0, bias, a.Ng, addend, out, a.relu, rowoff);
     } else {
@@ -411,13 +413,14 @@ conv1x1_large_kernel(const T* __restrict__ X, const T* __restrict__ W, const flo
   Vec<T, 8> adn[EPT];
   unsigned mbn[EPT];
   const bool residual = DGRAD && addend != nullptr;
+  auto image_of = [&](int pass) { return AddImage{a.add_image != 0, a.div_hw, m0 + pass * 64, a.Ng}; };
   auto rowoff_of = [&](int pass) {
     return [&a, m0, pass](int row) -> int64_t {
       const int64_t grow = m0 + pass * 64 + row;
       return grow < a.M ? grow * a.Ng : -1;
     };
   };
-  if (residual) epi_load_addend_nt<NT, T, BN, 64>(tid, n0, addend, a.amask, rowoff_of(0), adn, mbn);
+  if (residual) epi_load_addend_nt<NT, T, BN, 64>(tid, n0, addend, a.amask, rowoff_of(0), image_of(0), adn, mbn);
 #pragma unroll
   for (int pass = 0; pass < BM / 64; ++pass) {
     __syncthreads();
@@ -438,7 +441,7 @@ conv1x1_large_kernel(const T* __restrict__ X, const T* __restrict__ W, const flo
       unsigned mb[EPT];
 #pragma unroll
       for (int it = 0; it < EPT; ++it) { ad[it] = adn[it]; mb[it] = mbn[it]; }
-      if (pass + 1 < BM / 64) epi_load_addend_nt<NT, T, BN, 64>(tid, n0, addend, a.amask, rowoff_of(pass + 1), adn, mbn);
+      if (pass + 1 < BM / 64) epi_load_addend_nt<NT, T, BN, 64>(tid, n0, addend, a.amask, rowoff_of(pass + 1), image_of(pass + 1), adn, mbn);
       epi_store_rows_pre_nt<NT, T, BN, 64>(ep, tid, n0, ad, mb, out, rowoff);
     } else if (DGRAD) {
       epi_store_pass_nt<NT, T, BN, 64, false, true, false>(ep, tid, n0, bias, addend, a.amask, out, 0, rowoff, ss, qq);
@@ -562,13 +565,14 @@ conv1x1_rows_kernel(const T* __restrict__ X, const T* __restrict__ W, const T* _
   Vec<T, 8> adn[EPT];
   unsigned mbn[EPT];
   const bool residual = addend != nullptr;
+  auto image_of = [&](int sp) { return AddImage{a.add_image != 0, a.div_hw, m0 + sp * HR, a.Ng}; };
   auto rowoff_of = [&](int sp) {
     return [&a, m0, sp](int row) -> int64_t {
       const int64_t grow = m0 + sp * HR + row;
       return grow < a.M ? grow * a.Ng : -1;
     };
   };
-  if (residual) epi_load_addend_nt<NT, T, BN, HR>(tid, 0, addend, a.amask, rowoff_of(0), adn, mbn);
+  if (residual) epi_load_addend_nt<NT, T, BN, HR>(tid, 0, addend, a.amask, rowoff_of(0), image_of(0), adn, mbn);
   const bool ragged = m0 + BM > a.M;
 
   for (int ps = 0; ps < NP; ++ps) {
@@ -608,8 +612,8 @@ conv1x1_rows_kernel(const T* __restrict__ X, const T* __restrict__ W, const T* _
         unsigned mb[EPT];
 #pragma unroll
         for (int it = 0; it < EPT; ++it) { ad[it] = adn[it]; mb[it] = mbn[it]; }
-        if (sp + 1 < BM / HR) epi_load_addend_nt<NT, T, BN, HR>(tid, n0, addend, a.amask, rowoff_of(sp + 1), adn, mbn);
-        else if (ps + 1 < NP) epi_load_addend_nt<NT, T, BN, HR>(tid, n0 + BN, addend, a.amask, rowoff_of(0), adn, mbn);
+        if (sp + 1 < BM / HR) epi_load_addend_nt<NT, T, BN, HR>(tid, n0, addend, a.amask, rowoff_of(sp + 1), image_of(sp + 1), adn, mbn);
+        else if (ps + 1 < NP) epi_load_addend_nt<NT, T, BN, HR>(tid, n0 + BN, addend, a.amask, rowoff_of(0), image_of(0), adn, mbn);
         epi_store_rows_pre_nt<NT, T, BN, HR>(ep, tid, n0, ad, mb, out, rowoff_of(sp));
       }
     } else {
@@ -1061,8 +1065,9 @@ void launch_conv_fwd_pointwise(hipStream_t st, int dt, const void* x, const void
 
 // wt: the (C_in, C_out) transpose of the weights in the compute type
 void launch_conv_dgrad_pointwise(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                                 const uint8_t* addend_mask, void* dx, const ConvGeom& g) {
+                                 const uint8_t* addend_mask, bool addend_per_image, void* dx, const ConvGeom& g) {
   PwArgs a{};
+  a.add_image = addend_per_image;
   a.amask = addend_mask;  // (stride-1 layers only: the identity shortcut of a block)
   a.Ng = g.C; a.Kd = g.K; a.relu = 0; a.stride = 1;
   a.scatter = g.stride == 2;

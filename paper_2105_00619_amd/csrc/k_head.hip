@@ -25,9 +25,13 @@ __global__ void __launch_bounds__(256) flatten_kernel(const T* __restrict__ x, f
 // reading the map once.  With one range the mean is stored; with several (few images of many pixels, which would leave most
 // CUs idle: 4 images of 256 x 256 x 128 in fp32 took 1153 us in one block per image and 64 channels, 27 us like this) the
 // sums go to `partial` [ranges][N][C] and gap_finish_kernel adds the ranges in order.
-template <class T, int V>
+// APPLY: -1 x is the map; else x is the z of the BatchNorm apply in front, whose output -- the values bn_apply_kernel stores, SKIP
+// as there -- is added without being written, its ReLU decisions going to mask.  (262 144 x 1024 in bf16: apply 287 us and pooling
+// 119 apart.)
+template <class T, int V, int APPLY = -1>
 __global__ void __launch_bounds__(256) gap_sum_kernel(const T* __restrict__ x, float* __restrict__ feat,
-                                                      float* __restrict__ partial, int N, int HW, int C, int TX, int per_range) {
+                                                      float* __restrict__ partial, int N, int HW, int C, int TX, int per_range,
+                                                      HeadApply ap) {
   __shared__ float red[256 * V];
   const int TY = 256 / TX, tx = threadIdx.x % TX, ty = threadIdx.x / TX;
   const int n = blockIdx.x;
@@ -38,20 +42,71 @@ __global__ void __launch_bounds__(256) gap_sum_kernel(const T* __restrict__ x, f
 #pragma unroll
   for (int k = 0; k < V; ++k) s[k] = 0.f;
   if (active) {
-    const T* col = x + (int64_t)n * HW * C + cg * V;
+    const int64_t first = (int64_t)n * HW * C + cg * V;
+    const T* col = x + first;
+    const T* sk = APPLY > 0 ? static_cast<const T*>(ap.skip) + first : nullptr;
+    uint8_t* mk = APPLY >= 0 && ap.mask ? static_cast<uint8_t*>(ap.mask) + first / V : nullptr;
+    float scale[V], shift[V], scale2[V], shift2[V];
+    if (APPLY >= 0) {
+      load_f32<float, V>(ap.stats + 2 * C + cg * V, scale);
+      load_f32<float, V>(ap.stats + 3 * C + cg * V, shift);
+    }
+    if (APPLY == 2) {
+      load_f32<float, V>(ap.skip_stats + 2 * C + cg * V, scale2);
+      load_f32<float, V>(ap.skip_stats + 3 * C + cg * V, shift2);
+    }
+    auto value = [&](const Vec<T, V>& z, const Vec<T, V>& q, int p, float (&v)[V]) {  // pixel p's values
+      if constexpr (APPLY < 0) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) v[k] = to_f32(z.v[k]);
+      } else {
+        float vs[V], vo[V];
+        if (APPLY > 0) {
+#pragma unroll
+          for (int k = 0; k < V; ++k) vs[k] = to_f32(q.v[k]);
+        }
+        if (APPLY == 2) {
+#pragma unroll
+          for (int k = 0; k < V; ++k) vs[k] = bn_affine(vs[k], scale2[k], shift2[k]);
+          const Vec<T, V> sv = round_vec<T, V>(vs);
+#pragma unroll
+          for (int k = 0; k < V; ++k) vs[k] = to_f32(sv.v[k]);
+        }
+        unsigned bits = 0u;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          float y = bn_affine(to_f32(z.v[k]), scale[k], shift[k]);
+          if (APPLY > 0) y = __fadd_rn(y, vs[k]);
+          vo[k] = ap.relu ? fmaxf(y, 0.f) : y;
+          bits |= (vo[k] > 0.f ? 1u : 0u) << k;
+        }
+        if (APPLY > 0 && mk) mk[(int64_t)p * (C / V)] = (uint8_t)bits;
+        const Vec<T, V> t = round_vec<T, V>(vo);
+#pragma unroll
+        for (int k = 0; k < V; ++k) v[k] = to_f32(t.v[k]);
+      }
+    };
     constexpr int U = 8;
     int p = p0 + ty;
     for (; p + (U - 1) * TY < p1; p += U * TY) {
+      Vec<T, V> z[U], q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        z[u] = *reinterpret_cast<const Vec<T, V>*>(col + (int64_t)(p + u * TY) * C);
+        if (APPLY > 0) q[u] = *reinterpret_cast<const Vec<T, V>*>(sk + (int64_t)(p + u * TY) * C);
+      }
       float v[U][V];
 #pragma unroll
-      for (int u = 0; u < U; ++u) load_f32<T, V>(col + (int64_t)(p + u * TY) * C, v[u]);
+      for (int u = 0; u < U; ++u) value(z[u], q[u], p + u * TY, v[u]);
 #pragma unroll
       for (int k = 0; k < V; ++k)
         s[k] += ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k])) + ((v[4][k] + v[5][k]) + (v[6][k] + v[7][k]));
     }
     for (; p < p1; p += TY) {
+      Vec<T, V> q{};
       float v[V];
-      load_f32<T, V>(col + (int64_t)p * C, v);
+      if (APPLY > 0) q = *reinterpret_cast<const Vec<T, V>*>(sk + (int64_t)p * C);
+      value(*reinterpret_cast<const Vec<T, V>*>(col + (int64_t)p * C), q, p, v);
 #pragma unroll
       for (int k = 0; k < V; ++k) s[k] += v[k];
     }
@@ -370,7 +425,8 @@ int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J, bool
 }
 
 template <class T>
-static void launch_feat_t(hipStream_t st, const T* x, int N, int HW, int C, int gap, int ranges, float* feat, float* ws) {
+static void launch_feat_t(hipStream_t st, const T* x, int N, int HW, int C, int gap, int ranges, float* feat, float* ws,
+                          const HeadApply* ap) {
   constexpr int VM = 16 / (int)sizeof(T);
   if (!gap) {
     const int64_t n = (int64_t)N * HW * C;
@@ -381,19 +437,23 @@ static void launch_feat_t(hipStream_t st, const T* x, int N, int HW, int C, int 
   const int V = C % VM == 0 ? VM : 1, TX = gap_tx(C, V), per = ceil_div(HW, ranges);
   const dim3 grid(N, ceil_div(C / V, TX), ranges);
   float* partial = ranges > 1 ? ws : nullptr;
-  if (V == VM) OSEQ_LAUNCH((gap_sum_kernel<T, VM>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per);
-  else OSEQ_LAUNCH((gap_sum_kernel<T, 1>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per);
+  const HeadApply none{};
+  if (ap && ap->skip_stats) OSEQ_LAUNCH((gap_sum_kernel<T, VM, 2>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per, *ap);
+  else if (ap && ap->skip) OSEQ_LAUNCH((gap_sum_kernel<T, VM, 1>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per, *ap);
+  else if (ap) OSEQ_LAUNCH((gap_sum_kernel<T, VM, 0>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per, *ap);
+  else if (V == VM) OSEQ_LAUNCH((gap_sum_kernel<T, VM>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per, none);
+  else OSEQ_LAUNCH((gap_sum_kernel<T, 1>), grid, dim3(256), 0, st, x, feat, partial, N, HW, C, TX, per, none);
   if (partial)
     OSEQ_LAUNCH(gap_finish_kernel, dim3(ceil_div((int64_t)N * C, 256)), dim3(256), 0, st, partial, feat, (int64_t)N * C, ranges, HW);
 }
 
 // ws: head_ws_floats(...) floats (null if that is 0: one range)
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
-                        const float* b, float* feat, float* logits, float* ws) {
+                        const float* b, float* feat, float* logits, float* ws, const HeadApply* apply) {
   const int ranges = ws ? head_ranges(dt, N, HW, C, gap, F, J) : 1;
-  if (dt == DT_F32) launch_feat_t<float>(st, (const float*)x, N, HW, C, gap, ranges, feat, ws);
-  else if (dt == DT_BF16) launch_feat_t<bf16_t>(st, (const bf16_t*)x, N, HW, C, gap, ranges, feat, ws);
-  else launch_feat_t<f16_t>(st, (const f16_t*)x, N, HW, C, gap, ranges, feat, ws);
+  if (dt == DT_F32) launch_feat_t<float>(st, (const float*)x, N, HW, C, gap, ranges, feat, ws, apply);
+  else if (dt == DT_BF16) launch_feat_t<bf16_t>(st, (const bf16_t*)x, N, HW, C, gap, ranges, feat, ws, apply);
+  else launch_feat_t<f16_t>(st, (const f16_t*)x, N, HW, C, gap, ranges, feat, ws, apply);
   if (gap || ranges == 1) {
     launch_head_gemm<HG_FWD>(st, feat, w, b, logits, nullptr, N, J, F, F, F, 1);
   } else {
@@ -404,8 +464,8 @@ void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, in
 
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
-                     float* loss_n, float* loss_out, int* flags, float* ws) {
-  launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits, ws);
+                     float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply) {
+  launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits, ws, apply);
   OSEQ_LAUNCH(softmax_ce_kernel, dim3(ceil_div(N, 4)), dim3(256), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags);
   OSEQ_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, st, loss_n, N, loss_out);
 }

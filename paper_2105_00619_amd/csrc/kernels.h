@@ -61,12 +61,15 @@ void launch_bias_grad(hipStream_t st, int dt, const void* dz, int64_t rows, int 
 void launch_maxpool_fwd(hipStream_t st, int dt, const void* x, void* y, int N, int H, int W, int C);
 void launch_maxpool_bwd(hipStream_t st, int dt, const void* x, const void* dy, void* dx, int N, int H, int W, int C);
 
+// The BatchNorm apply whose output only the head's global average pool reads, done by the pooling kernel (x is then its z): the
+// output itself is never written.  As launch_bn_apply; C a multiple of 16 / element size
+struct HeadApply { const float* stats; const void* skip; const float* skip_stats; void* mask; int relu; };
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
-                     float* loss_n, float* loss_out, int* flags, float* ws);
+                     float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply = nullptr);
 // forward of the head up to the logits (no loss): inference
 void launch_head_logits(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
-                        const float* b, float* feat, float* logits, float* ws);
+                        const float* b, float* feat, float* logits, float* ws, const HeadApply* apply = nullptr);
 // ws: workspace of the forward pass, where its sums are split over ranges (null: they are not)
 // in_x: it is to lie in the head's input, of which only the first kernel (pooling, conversion) reads
 int64_t head_ws_floats(int dt, int N, int HW, int C, int gap, int F, int J, bool in_x);
@@ -108,9 +111,10 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
                           float* partial, float* stat_partial, int splits, const ConvGeom& g, int relu,
                           const float* fold = nullptr, const ConvEval& ev = ConvEval());
 // addend_mask (null, or with an addend): ReLU decisions as bits (as launch_bn_apply writes them); the addend counts
-// as zero where its bit is clear
+// as zero where its bit is clear.  addend_per_image (only where conv_dgrad_image_addend_ok): the addend is [N][C_in]
+bool conv_dgrad_image_addend_ok(int dt, const ConvGeom& g);
 void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                            const void* addend_mask, void* dx, float* partial, int splits, const ConvGeom& g);
+                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g);
 // 1x1 convolutions in 16-bit storage as a streaming GEMM (k_conv_pointwise.hip); used by the MFMA launchers above
 bool conv_pointwise_fwd_ok(int dt, const ConvGeom& g);
 bool conv_pointwise_dgrad_ok(int dt, const ConvGeom& g);
@@ -119,7 +123,7 @@ bool conv_pointwise_fold_ok(int dt, const ConvGeom& g);
 void launch_conv_fwd_pointwise(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
                                float* stat_partial, const ConvGeom& g, int relu, const float* fold, const ConvEval& ev);
 void launch_conv_dgrad_pointwise(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                                 const uint8_t* addend_mask, void* dx, const ConvGeom& g);
+                                 const uint8_t* addend_mask, bool addend_per_image, void* dx, const ConvGeom& g);
 // 3x3 stride-1 layers of 64 input channels and many pixels with the weights stationary (k_conv_ws3x3.hip); used by the MFMA
 // launchers above where nothing is added to the result
 bool conv_ws3x3_ok(int dt, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride);

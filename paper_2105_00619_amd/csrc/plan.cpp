@@ -367,6 +367,18 @@ struct Scheduler {
     return ap.unit >= p.seg_begin[seg] && pool.unit < p.seg_begin[seg + 1];
   }
 
+  // Is forward operation fi a global average pool that does the BatchNorm apply in front of it as well?  Nothing else reads that
+  // one's output, both lie in segment `seg`, whole groups of channels, and backward has the ReLU decisions of an output with
+  // a skip connection as bits.  (storage mode 2 keeps every activation)
+  bool gap_fused(int fi, int seg) const {
+    if (fi < 1 || fi >= (int)p.fops.size() || p.cfg.storage_mode == 2) return false;
+    const FOp& head = p.fops[fi];
+    const FOp& ap = p.fops[fi - 1];
+    if (head.kind != F_HEAD || !head.gap || ap.kind != F_BN_APPLY || head.x != ap.out || ap.fold || readers[ap.out] != 1) return false;
+    if (ap.C % (16 / p.esize) != 0 || (ap.skip >= 0 && ap.mask < 0)) return false;
+    return ap.unit >= p.seg_begin[seg] && head.unit < p.seg_begin[seg + 1];
+  }
+
   void emit_fop_forward(int fi, int phase, int seg) {
     const FOp& f = p.fops[fi];
     switch (f.kind) {
@@ -393,6 +405,7 @@ struct Scheduler {
       }
       case F_BN_APPLY: {
         if (f.fold) break;  // done by the operation that reads it
+        if (gap_fused(fi + 1, seg)) break;  // likewise
         SOp& s = push(S_BN_APPLY, fi, phase, seg);
         s.in[0] = cur[f.x]; s.in[1] = cur[f.stats]; s.in[2] = f.skip >= 0 ? cur[f.skip] : -1;
         if (f.fold_skip >= 0) { s.in[2] = cur[p.fops[f.fold_skip].x]; s.in[3] = cur[p.fops[f.fold_skip].stats]; }
@@ -409,6 +422,13 @@ struct Scheduler {
       case F_HEAD: {
         SOp& s = push(S_HEAD_FWD, fi, phase, seg);
         s.in[0] = cur[f.x];
+        if (gap_fused(fi, seg)) {
+          const FOp& ap = p.fops[fi - 1];
+          s.variant = 1;
+          s.in[0] = cur[ap.x]; s.in[1] = cur[ap.stats]; s.in[2] = ap.skip >= 0 ? cur[ap.skip] : -1;
+          if (ap.fold_skip >= 0) { s.in[2] = cur[p.fops[ap.fold_skip].x]; s.in[3] = cur[p.fops[ap.fold_skip].stats]; }
+          if (ap.mask >= 0) s.out[5] = value_inst(ap.mask);
+        }
         s.out[0] = value_inst(f.aux[0]); s.out[1] = value_inst(f.aux[1]);
         s.out[2] = value_inst(f.aux[2]); s.out[3] = value_inst(f.out);
         if (f.head_ws > 0 && !f.head_ws_in_x) s.out[4] = new_inst(-1, (uint64_t)f.head_ws * 4, false);
@@ -442,6 +462,14 @@ struct Scheduler {
     if (bn_apply_of[f.skip] >= 0 && p.fops[bn_apply_of[f.skip]].unit == f.unit) return true;
     for (int j = p.unit_first_fop[f.unit]; j < p.unit_last_fop[f.unit]; ++j)
       if (p.fops[j].kind == F_CONV && p.fops[j].x == f.skip) return p.fops[j].dgrad_algo == ALGO_MFMA;
+    return false;
+  }
+
+  // Does the first convolution of operation fi's block, which reads its identity skip connection, add a gradient per image?
+  bool image_addend_ok(int fi) const {
+    const FOp& f = p.fops[fi];
+    for (int j = p.unit_first_fop[f.unit]; j < p.unit_last_fop[f.unit]; ++j)
+      if (p.fops[j].kind == F_CONV && p.fops[j].x == f.skip) return p.fops[j].image_addend != 0;
     return false;
   }
 
@@ -485,9 +513,9 @@ struct Scheduler {
           bool whole = true;  // the gradient as a whole tensor
           if (f.gap && ap >= 0 && readers[f.x] == 1 && per_image_ok(ap)) {
             s.out[2] = image_grad[f.x] = new_inst(-1, (uint64_t)f.N * f.C * p.esize, false);
-            // an identity shortcut's data gradient adds it as a tensor
+            // the data gradient of an identity shortcut's first convolution may have to add it as a tensor
             const int skip = p.fops[ap].skip;
-            whole = skip >= 0 && projection_of(ap) < 0 && p.tensors[skip].needs_grad;
+            whole = skip >= 0 && projection_of(ap) < 0 && p.tensors[skip].needs_grad && !image_addend_ok(ap);
           }
           if (whole) { s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; }
         }
@@ -520,7 +548,7 @@ struct Scheduler {
         if (f.skip >= 0 && p.tensors[f.skip].needs_grad) {
           if (grad[f.skip] >= 0) { p.error = "internal: skip gradient must be the first contribution"; return false; }
           if (masked_skip_grad_ok(fi)) {  // nothing written
-            const bool vec = image && projection_of(fi) >= 0;
+            const bool vec = image && (projection_of(fi) >= 0 || image_addend_ok(fi));
             grad[f.skip] = vec ? gin : whole; per_image[f.skip] = vec; gmask[f.skip] = cur[f.mask];
           }
           else { s.out[1] = grad_inst(f.skip); grad[f.skip] = s.out[1]; gmask[f.skip] = -1; }
@@ -565,7 +593,8 @@ struct Scheduler {
         if (p.tensors[f.x].needs_grad) {
           SOp& s = push(S_DGRAD, fi, PH_BWD, seg);
           s.in[0] = g; s.in[1] = grad[f.x]; s.in[2] = grad[f.x] >= 0 ? gmask[f.x] : -1;
-          s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
+          s.per_image = grad[f.x] >= 0 && per_image[f.x];
+          s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1; per_image[f.x] = 0;
           if (f.dgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.dgrad_splits * f.N * f.H * f.W * f.C * 4, false);
         }
         return true;

@@ -54,6 +54,7 @@ struct FOp {
   int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
   bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
                              // of the head's kernels
+  int image_addend = 0;      // F_CONV: 1 = the data gradient can add one row per image (the gradient of a global average pool)
   int bwd_fuse = 0;          // F_CONV: 1 = the BatchNorm behind it, whose backward sums are known, and both gradients run as one kernel
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
@@ -88,7 +89,7 @@ struct SOp {
   int fop = -1;
   int phase = 0, seg = 0;
   int in[7] = {-1, -1, -1, -1, -1, -1, -1};
-  int out[5] = {-1, -1, -1, -1, -1};
+  int out[6] = {-1, -1, -1, -1, -1, -1};
   int variant = 0;  // S_BN_BWD: 1 = in[0] is the gradient of the 2x2 max-pool behind the activation (pooled size);
                     // 2 = in[3] is a bit mask of ReLU decisions (FOp::mask) to apply to in[0], not an activation.
                     // S_DGRAD: in[2] >= 0 is such a mask for the addend in[1]
@@ -99,7 +100,8 @@ struct SOp {
                     // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
                     // S_BN_BWD, in[4] its workspace, in[5] the convolution's input (the z of a folded BatchNorm with in[6]
                     // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
-  bool per_image = false;  // S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
+                    // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
+  bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
   bool live = true;
 };

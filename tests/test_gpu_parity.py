@@ -387,6 +387,79 @@ def test_fp32_infinities_and_nans_come_out_as_from_fp32(ksize, stride):
     assert bool(((got - want).abs()[ok] <= 1e-5 * (want.abs()[ok] + 1.0)).all())
 
 
+def _grads64(layers, blocks, params, x, y):
+    """Gradients in float64 of a run of convolutions + BatchNorm (blocks None; the last argument of a layer: ReLU) or of
+    bottleneck blocks given as (channels in, channels out), a global average pool and a linear layer; params in flat order."""
+    import torch
+    it = iter(params)
+
+    def cbr(v, stride=1, relu=True):
+        z = _layer64(v, next(it), stride)
+        gamma, beta = next(it), next(it)
+        flat = z.reshape(-1, z.shape[3])
+        z = gamma * (z - flat.mean(0)) / torch.sqrt(flat.var(0, unbiased=False) + 1e-5) + beta
+        return z, relu
+
+    def done(zr, add=None):
+        z = zr[0] if add is None else zr[0] + add
+        return torch.relu(z) if zr[1] else z
+
+    for _ in range(layers):
+        x = done(cbr(x))
+    for cin, cout in blocks:
+        v = done(cbr(x))
+        v = done(cbr(v))
+        z = cbr(v)
+        x = done(z, done(cbr(x, relu=False)) if cin != cout else x)
+    logits = x.mean((1, 2)) @ next(it).t() + next(it)
+    torch.nn.functional.cross_entropy(logits, y.long()).backward()
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("chain,blocks,h,w,b", [
+    ([64, 256], [], 16, 17, 241), ([64, 256, 64], [], 15, 17, 259),  # gradient per image; whole, decisions from z
+    ([64], [(64, 256), (256, 256)], 15, 17, 257),  # projection and identity shortcut, BatchNorm folded into the layer's input
+    ([64], [(64, 256)], 32, 32, 64), ([256], [(256, 256), (256, 256)], 9, 7, 521)])  # exactly 65 536 pixels; fewer
+def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w, b):
+    """64 -> 256 channels over 65 536 pixels or more: BatchNorm apply, data and weight gradient as one kernel; the gradient of a
+    global average pool as one row per image, also where an identity shortcut's data gradient adds it, and the last apply
+    operation done by the pooling kernel.  Plain float64 and the bar of the single-layer tests; k segments change no bit."""
+    import torch
+    units = [W.conv(i, o, 1) for i, o in zip([8] + chain, chain)] + [W.bottleneck(i, o) for i, o in blocks]
+    last = blocks[-1][1] if blocks else chain[-1]
+    units.append(W.gap_linear_ce(last, 10))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    shapes = []
+    for i, o in zip([8] + chain, chain):
+        shapes += [(o, 1, 1, i), (o,), (o,)]
+    for i, o in blocks:
+        m = o // 4
+        shapes += [(m, 1, 1, i), (m,), (m,), (m, 3, 3, m), (m,), (m,), (o, 1, 1, m), (o,), (o,)]
+        shapes += [(o, 1, 1, i), (o,), (o,)] if i != o else []
+    shapes += [(10, last), (10,)]
+    params, at = [], 0
+    for s in shapes:
+        v = torch.randn(s, generator=g, device="cuda")
+        if len(s) == 1:
+            v = 1.0 + 0.2 * v if at == 1 else 0.1 * v
+            at += 1
+        else:
+            v, at = v * (2.0 / math.prod(s[1:])) ** 0.5, 1
+        params.append(v)
+    x = torch.randn((b, h, w, 8), generator=g, device="cuda")
+    y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
+    flat = torch.cat([v.flatten() for v in params]).cpu().numpy()
+    r, info = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    assert not r["skipped"]
+    again, _ = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), precision=precision, k=len(units), classes=10,
+                        loss_scale_init=_scale(precision))
+    assert np.array_equal(r["grads"], again["grads"])
+    p64 = [v.double().requires_grad_(True) for v in params]
+    _grads64(len(chain), blocks, p64, x.double(), y)
+    want = torch.cat([q.grad.flatten() for q in p64]).cpu().numpy()
+    assert np.linalg.norm(r["grads"] - want) <= TOL[precision] * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("precision", [W.FP32, W.FP16])
 @pytest.mark.parametrize("cin,cout,ksize,stride,pad,h,w,b", [
     (64, 128, 3, 2, 0, 9, 11, 5), (96, 64, 3, 2, 0, 8, 12, 3), (64, 64, 3, 2, 1, 7, 10, 4), (128, 192, 3, 2, 1, 2, 2, 7),
