@@ -31,6 +31,7 @@ struct optorch_seq {
   float scale = 1.f, scale_init = 1.f, growth = 2.f, backoff = 0.5f, eps = 1e-5f, bn_mom = 0.1f, momentum = 0.f;
   int growth_interval = 0, clean = 0;
   bool dynamic_scale = false;
+  float* host_rb_dev = nullptr;  // the same for the device
   float* host_rb = nullptr;  // pinned read-back buffer: loss + flags
   std::vector<EvalJob> eval_jobs;            // every BatchNorm, for the inference-mode scale / shift table
   std::vector<TransposeJob> transpose_jobs;  // layers whose data gradient reads a transposed weight copy
@@ -102,6 +103,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
       }
     for (FOp& f : p.fops)
       if (f.kind == F_HEAD) {
+        f.head_one = head_loss_in_one(f.N);
         f.head_ws_in_x = !p.tensors[f.x].needs_grad;
         f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, f.head_ws_in_x);
       }
@@ -260,6 +262,8 @@ extern "C" int optorch_seq_bind(optorch_seq_t* h, void* param_arena_dev, uint64_
   if (!h->host_rb) {
     hipError_t e = hipHostMalloc((void**)&h->host_rb, 256, hipHostMallocDefault);
     if (e != hipSuccess) return hip_fail(h, e, "hipHostMalloc");
+    e = hipHostGetDevicePointer((void**)&h->host_rb_dev, h->host_rb, 0);
+    if (e != hipSuccess) return hip_fail(h, e, "hipHostGetDevicePointer");
   }
   h->pbase = (char*)param_arena_dev; h->pbytes = param_arena_bytes;
   h->abase = (char*)act_arena_dev; h->abytes = act_arena_bytes;
@@ -316,6 +320,7 @@ struct Ctx {
   char* abase = nullptr;  // the activation arena this call works in (the bound one unless stated otherwise)
   bool touch_running = true;  // BatchNorm statistics also move the running estimates (a training step's forward)
   // the batch in encoded form instead of x (groups of xz images, Algorithm "Encode"), with the input normalisation
+  const StepBegin* begin = nullptr;  // what the cast of the images starts the step with
   const uint64_t* xa = nullptr; int xz = 0; const float* xscale = nullptr; const float* xshift = nullptr;
   void* at(int inst) const { return inst < 0 ? nullptr : (void*)(abase + h->plan.insts[inst].offset); }
   float* w32(int64_t off) const { return (float*)(h->pbase + h->off_w) + off; }
@@ -339,7 +344,7 @@ void run_op(const Ctx& c, const SOp& s) {
       if (c.xa)  // the decode layer as the first kernel of the step
         launch_decode_cast(st, dt, c.xa, f.N, (int64_t)f.H * f.W * f.C, c.xz, f.C, c.xscale, c.xshift, c.at(s.out[0]));
       else
-        launch_cast_in(st, dt, c.x, c.at(s.out[0]), (int64_t)f.N * f.H * f.W * f.C);
+        launch_cast_in(st, dt, c.x, c.at(s.out[0]), (int64_t)f.N * f.H * f.W * f.C, c.begin);
       break;
     case S_CONV_FWD:
       if (f.fwd_algo == ALGO_MFMA)
@@ -403,7 +408,7 @@ void run_op(const Ctx& c, const SOp& s) {
       launch_relu_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), (int64_t)f.N * f.P * f.Q, f.K);
       break;
     case S_BIAS_GRAD:
-      launch_bias_grad(st, dt, c.at(s.in[0]), (int64_t)f.N * f.P * f.Q, f.K, f.red_blocks, (float*)c.at(s.out[0]),
+      launch_bias_grad(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[1]), (int64_t)f.N * f.P * f.Q, f.K, f.red_blocks, (float*)c.at(s.out[0]),
                        c.g32(f.b_off));
       break;
     case S_WGRAD:
@@ -491,7 +496,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_POOL_FWD: *bytes = e * (in_px + out_px) * f.C; break;
     case S_POOL_BWD: *bytes = e * (2 * in_px + out_px) * f.C; break;
     case S_RELU_BWD: *bytes = e * 3 * out_px * f.K; break;
-    case S_BIAS_GRAD: *bytes = e * out_px * f.K; break;
+    case S_BIAS_GRAD: *bytes = e * out_px * f.K * (s.out[1] >= 0 ? 3 : 1); break;
     case S_HEAD_FWD: *bytes = e * in_px * f.C * (1 + (s.variant == 1 && s.in[2] >= 0 ? 1.0 : 0.0) + (s.out[5] >= 0 ? 1.0 / 16 : 0)); break;
     case S_HEAD_BWD: *bytes = e * in_px * f.C; break;
   }
@@ -734,10 +739,13 @@ extern "C" int optorch_seq_running_stats(const optorch_seq_t* h, float* dst, uin
 }
 
 // one training step on the batch that c describes
-static int step_run(optorch_seq_t* h, const Ctx& c, float lr, float* loss_out, float* grads_dev, uint64_t* peak_saved_bytes,
+static int step_run(optorch_seq_t* h, const Ctx& batch, float lr, float* loss_out, float* grads_dev, uint64_t* peak_saved_bytes,
                     uint64_t* peak_arena_bytes, float* loss_scale_out, int32_t* step_skipped) {
   hipStream_t st = h->stream;
-  launch_step_init(st, c.flags(), c.y, h->plan.cfg.batch, h->plan.cfg.num_classes);
+  Ctx c = batch;
+  const StepBegin begin{c.flags(), c.y, h->plan.cfg.batch, h->plan.cfg.num_classes};
+  if (c.xa) launch_step_init(st, begin);
+  else c.begin = &begin;
   const bool prof = h->profiling;
   if (prof && h->ev_used > (size_t)1 << 16) harvest(h);  // previous steps are complete: each step ends with a sync
   for (size_t si = 0; si < h->plan.sched.size(); ++si) {
@@ -764,7 +772,7 @@ static int step_run(optorch_seq_t* h, const Ctx& c, float lr, float* loss_out, f
     const size_t ev0 = h->ev_used;
     if (timed) g_launch_timer = LaunchTimer{true, next_event_cb, h};
     launch_optim(st, h->dt, c.w32(0), (float*)(h->pbase + h->off_v), c.g32(0), h->pbase + h->off_h, grads_dev, P, lr,
-                 h->momentum, 1.f / h->scale, c.flags());
+                 h->momentum, 1.f / h->scale, c.flags(), c.loss(), h->host_rb_dev);
     if (timed) {
       g_launch_timer.on = false;
       const int k = OPTORCH_K_OPTIMIZER;
@@ -779,8 +787,6 @@ static int step_run(optorch_seq_t* h, const Ctx& c, float lr, float* loss_out, f
   refresh_transposed_weights(h);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "kernel launch");
-  e = hipMemcpyAsync(h->host_rb, h->pbase + h->off_scal, 128, hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return hip_fail(h, e, "hipMemcpyAsync(read-back)");
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
   const int* fl = (const int*)((const char*)h->host_rb + 64);

@@ -100,6 +100,16 @@ __device__ __forceinline__ Chunk zero_chunk() { Chunk c = {0u, 0u, 0u, 0u}; retu
 // ReLU mask rebuilt in backward equals the one applied in forward, bit for bit.
 __device__ __forceinline__ float bn_affine(float z, float scale, float shift) { return __fmaf_rn(z, scale, shift); }
 
+// The start of a training step, by one whole block before anything else of the step runs: flags[0] = a gradient is not finite
+// (set by the optimizer's check), flags[1] = a label lies outside [0, classes).  Either flag makes the update a no-op, and
+// flags[1] also keeps the BatchNorm running statistics as they were.  Stream order makes the flags visible to the later kernels.
+__device__ __forceinline__ void step_begin(const StepBegin& b) {
+  bool bad = false;
+  for (int i = threadIdx.x; i < b.n; i += blockDim.x) bad |= b.y[i] < 0 || b.y[i] >= b.classes;
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x < 4) b.flags[threadIdx.x] = threadIdx.x == 1 ? (any ? 1 : 0) : 0;
+}
+
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 }  // namespace oseq

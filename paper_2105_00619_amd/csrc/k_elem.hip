@@ -12,11 +12,29 @@
 namespace oseq {
 
 // ------------------------------------------------------------------ cast ----
-template <class T>
-__global__ void cast_in_kernel(const float* __restrict__ x, T* __restrict__ out, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) out[i] = from_f32<T>(x[i]);
+// V elements per thread and trip: 8 where the caller's pointer lies on 16 bytes (one element: 268 M elements to bf16 at 4.4 TB/s, 8 at
+// 5.1), the last n % V by the first threads; BEGIN: the first block also starts the training step
+template <class T, int V, bool BEGIN>
+__global__ void __launch_bounds__(256) cast_in_kernel(const float* __restrict__ x, T* __restrict__ out, int64_t n, StepBegin begin) {
+  if (BEGIN && blockIdx.x == 0) step_begin(begin);
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * 256, groups = n / V;
+  for (int64_t i = t; i < groups; i += stride) {
+    float v[V];
+    if constexpr (V == 8) {
+      load_f32<float, 4>(x + i * 8, reinterpret_cast<float (&)[4]>(v[0]));
+      load_f32<float, 4>(x + i * 8 + 4, reinterpret_cast<float (&)[4]>(v[4]));
+    } else {
+      load_f32<float, V>(x + i * V, v);
+    }
+    if constexpr (V == 8 && sizeof(T) == 4) {
+      store_f32<T, 4>(out + i * 8, reinterpret_cast<float (&)[4]>(v[0]));
+      store_f32<T, 4>(out + i * 8 + 4, reinterpret_cast<float (&)[4]>(v[4]));
+    } else {
+      store_f32<T, V>(out + i * V, v);
+    }
+  }
+  if (V > 1 && t < n - groups * V) out[groups * V + t] = from_f32<T>(x[groups * V + t]);
 }
 
 template <class T>
@@ -28,7 +46,8 @@ __global__ void cast_out_kernel(const T* __restrict__ x, float* __restrict__ out
 
 // ----------------------------------------------------- column reductions ----
 // RED_BN_BWD: ReLU decisions redone from z (or none); _AOUT: from the sign of the block output; _MASK: from the bits
-enum { RED_STATS = 0, RED_BN_BWD = 1, RED_BIAS = 2, RED_BN_BWD_AOUT = 3, RED_BN_BWD_MASK = 4 };
+// RED_BIAS_RELU: the gradient behind a ReLU with output aout: where that is positive, stored to dz and summed
+enum { RED_STATS = 0, RED_BN_BWD = 1, RED_BIAS = 2, RED_BN_BWD_AOUT = 3, RED_BN_BWD_MASK = 4, RED_BIAS_RELU = 5 };
 
 struct RedArgs {
   const void* a;       // STATS: z ; BN_BWD: dA ; BIAS: dz
@@ -38,6 +57,7 @@ struct RedArgs {
                        // takes the place of aout (and of the ReLU flag: the bits are applied as they are)
   const float* stats;  // BN_BWD: [4][C] mean, rstd, scale, shift
   float* partial;      // [nblk][2][C]
+  void* dz;            // BIAS_RELU
   int64_t rows;
   int C, relu, nblk, rows_per_block;
   FastDiv div_hw;      // GV: rows per image
@@ -96,7 +116,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
   if (active) {
     const T* a = static_cast<const T*>(g.a);
     const T* z = static_cast<const T*>(g.z);
-    const T* ao = MODE == RED_BN_BWD_AOUT ? static_cast<const T*>(g.aout) : nullptr;
+    const T* ao = MODE == RED_BN_BWD_AOUT || MODE == RED_BIAS_RELU ? static_cast<const T*>(g.aout) : nullptr;
     const uint8_t* mk = MODE == RED_BN_BWD_MASK ? g.mask : nullptr;
     // (the row loads below are non-temporal: nothing a reduction reads is read again from the cache it would fill --
     // -2 % on the BatchNorm backward of the bottleneck networks; in the apply kernels, whose output the next kernel
@@ -106,6 +126,9 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
       if (MODE == RED_STATS) {
 #pragma unroll
         for (int i = 0; i < V; ++i) { s0[i] += va[i]; s1[i] = __fmaf_rn(va[i], va[i], s1[i]); }
+      } else if (MODE == RED_BIAS_RELU) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) s0[i] += vo[i] > 0.f ? va[i] : 0.f;
       } else if (MODE == RED_BIAS) {
 #pragma unroll
         for (int i = 0; i < V; ++i) s0[i] += va[i];
@@ -141,6 +164,16 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
           if (MODE == RED_BN_BWD_MASK) mb[u] = mk[(r + (int64_t)u * TY) * CG + cg];
           else if (MODE == RED_BN_BWD_AOUT) load_f32<T, V>(ao + off, vo[u]);
         }
+        if (MODE == RED_BIAS_RELU) load_f32<T, V>(ao + off, vo[u]);
+      }
+      if (MODE == RED_BIAS_RELU) {
+#pragma unroll
+        for (int u = 0; u < RT; ++u) {
+          float d[V];
+#pragma unroll
+          for (int i = 0; i < V; ++i) d[i] = vo[u][i] > 0.f ? va[u][i] : 0.f;
+          store_f32<T, V>(static_cast<T*>(g.dz) + (r + (int64_t)u * TY) * g.C + c0, d);
+        }
       }
 #pragma unroll
       for (int u = 0; u < RT; ++u) accumulate(va[u], vz[u], vo[u], mb[u]);
@@ -155,6 +188,13 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
         load_f32_nt<T, V>(z + off, vz);
         if (MODE == RED_BN_BWD_MASK) mb = mk[r * CG + cg];
         else if (MODE == RED_BN_BWD_AOUT) load_f32<T, V>(ao + off, vo);
+      }
+      if (MODE == RED_BIAS_RELU) {
+        float d[V];
+        load_f32<T, V>(ao + off, vo);
+#pragma unroll
+        for (int i = 0; i < V; ++i) d[i] = vo[i] > 0.f ? va[i] : 0.f;
+        store_f32<T, V>(static_cast<T*>(g.dz) + off, d);
       }
       accumulate(va, vz, vo, mb);
     }
@@ -764,11 +804,24 @@ __global__ void __launch_bounds__(256) maxpool_bwd_kernel(const T* __restrict__ 
     else OSEQ_LAUNCH(KERNEL<1>, dim3(C), dim3(256), __VA_ARGS__);                           \
   } while (0)
 
-void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n) {
-  const int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  if (dt == DT_F32) OSEQ_LAUNCH(cast_in_kernel<float>, dim3(blocks), dim3(256), 0, st, x, (float*)out, n);
-  else if (dt == DT_BF16) OSEQ_LAUNCH(cast_in_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, x, (bf16_t*)out, n);
-  else OSEQ_LAUNCH(cast_in_kernel<f16_t>, dim3(blocks), dim3(256), 0, st, x, (f16_t*)out, n);
+template <class T, int V>
+static void launch_cast_v(hipStream_t st, const float* x, void* out, int64_t n, const StepBegin* begin) {
+  const int64_t want = (n / V + 255) / 256;
+  const dim3 grid((unsigned)(want < 1 ? 1 : want < 8192 ? want : 8192));
+  const StepBegin none{};
+  if (begin) OSEQ_LAUNCH((cast_in_kernel<T, V, true>), grid, dim3(256), 0, st, x, (T*)out, n, *begin);
+  else OSEQ_LAUNCH((cast_in_kernel<T, V, false>), grid, dim3(256), 0, st, x, (T*)out, n, none);
+}
+template <class T>
+static void launch_cast_t(hipStream_t st, const float* x, void* out, int64_t n, const StepBegin* begin) {
+  // (few elements: one per thread spreads them over more CUs)
+  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0 && n >= 1 << 20) launch_cast_v<T, 8>(st, x, out, n, begin);
+  else launch_cast_v<T, 1>(st, x, out, n, begin);
+}
+void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n, const StepBegin* begin) {
+  if (dt == DT_F32) launch_cast_t<float>(st, x, out, n, begin);
+  else if (dt == DT_BF16) launch_cast_t<bf16_t>(st, x, out, n, begin);
+  else launch_cast_t<f16_t>(st, x, out, n, begin);
 }
 
 void launch_cast_out(hipStream_t st, int dt, const void* x, float* out, int64_t n) {
@@ -923,9 +976,11 @@ void launch_relu_bwd(hipStream_t st, int dt, const void* da, const void* a, void
 #undef CALL
 }
 
-void launch_bias_grad(hipStream_t st, int dt, const void* dz, int64_t rows, int C, int nblk, float* partial, float* dbias) {
-  RedArgs g{}; g.a = dz; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
-  launch_colreduce<RED_BIAS>(st, dt, g);
+void launch_bias_grad(hipStream_t st, int dt, const void* dz, const void* a, void* dz_out, int64_t rows, int C, int nblk, float* partial,
+                      float* dbias) {
+  RedArgs g{}; g.a = dz; g.aout = a; g.dz = dz_out; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
+  if (dz_out) launch_colreduce<RED_BIAS_RELU>(st, dt, g);
+  else launch_colreduce<RED_BIAS>(st, dt, g);
   FIN_LAUNCH(bias_finalize_kernel, 0, st, partial, nblk, C, dbias);
 }
 

@@ -10,6 +10,9 @@ namespace oseq {
 
 typedef __attribute__((ext_vector_type(16))) float head_v16f;
 
+constexpr int HEAD_ONE_BLOCK = 64;
+bool head_loss_in_one(int N) { return N <= HEAD_ONE_BLOCK; }
+
 // flatten: feat[n][f] = x[n][f] in fp32, V features per thread
 template <class T, int V>
 __global__ void __launch_bounds__(256) flatten_kernel(const T* __restrict__ x, float* __restrict__ feat, int64_t groups) {
@@ -300,29 +303,44 @@ static void launch_head_gemm(hipStream_t st, const float* a, const float* b, con
 
 // per sample: loss_n = logsumexp(logits_n) - logits_n[y_n]; dlogits = (softmax - onehot) * gscale
 // one wavefront per sample; lanes stride over the classes, maxima and sums by a fixed butterfly
-__global__ void __launch_bounds__(256) softmax_ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ y,
+// MEAN: few samples (head_loss_in_one): one block of 16 wavefronts takes them all and their mean loss too
+template <bool MEAN>
+__global__ void __launch_bounds__(MEAN ? 1024 : 256) softmax_ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ y,
                                                          float* __restrict__ loss_n, float* __restrict__ dlogits, int N, int J,
-                                                         float gscale, int* __restrict__ flags) {
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
+                                                         float gscale, int* __restrict__ flags, float* __restrict__ loss_out) {
+  __shared__ float losses[MEAN ? HEAD_ONE_BLOCK : 1];
   const int lane = threadIdx.x & 63;
-  const float* lp = logits + (int64_t)n * J;
-  float mx = -INFINITY;
-  for (int j = lane; j < J; j += 64) mx = fmaxf(mx, lp[j]);
+  for (int n = MEAN ? (int)(threadIdx.x >> 6) : (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); n < N; n += MEAN ? 16 : N) {
+    const float* lp = logits + (int64_t)n * J;
+    float mx = -INFINITY;
+    for (int j = lane; j < J; j += 64) mx = fmaxf(mx, lp[j]);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  float se = 0.f;
-  for (int j = lane; j < J; j += 64) se += expf(lp[j] - mx);
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float se = 0.f;
+    for (int j = lane; j < J; j += 64) se += expf(lp[j] - mx);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) se += __shfl_xor(se, off, 64);
-  const float lse = mx + logf(se);
-  int lab = y[n];
-  if (lab < 0 || lab >= J) { if (lane == 0) atomicOr(flags + 1, 1); lab = 0; }
-  if (lane == 0) loss_n[n] = lse - lp[lab];
-  const float inv = 1.f / se;
-  for (int j = lane; j < J; j += 64) {
-    const float pj = expf(lp[j] - mx) * inv;
-    dlogits[(int64_t)n * J + j] = (pj - (j == lab ? 1.f : 0.f)) * gscale;
+    for (int off = 32; off > 0; off >>= 1) se += __shfl_xor(se, off, 64);
+    const float lse = mx + logf(se);
+    int lab = y[n];
+    if (lab < 0 || lab >= J) { if (lane == 0) atomicOr(flags + 1, 1); lab = 0; }
+    if (lane == 0) {
+      loss_n[n] = lse - lp[lab];
+      if (MEAN) losses[n] = lse - lp[lab];
+    }
+    const float inv = 1.f / se;
+    for (int j = lane; j < J; j += 64) {
+      const float pj = expf(lp[j] - mx) * inv;
+      dlogits[(int64_t)n * J + j] = (pj - (j == lab ? 1.f : 0.f)) * gscale;
+    }
+  }
+  if constexpr (MEAN) {  // added as loss_mean_kernel does
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      double t = (int)threadIdx.x < N ? (double)losses[threadIdx.x] : 0.0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+      if (threadIdx.x == 0) loss_out[0] = (float)(t / (double)N);
+    }
   }
 }
 
@@ -466,7 +484,11 @@ void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
                      float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply) {
   launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits, ws, apply);
-  OSEQ_LAUNCH(softmax_ce_kernel, dim3(ceil_div(N, 4)), dim3(256), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags);
+  if (head_loss_in_one(N)) {
+    OSEQ_LAUNCH(softmax_ce_kernel<true>, dim3(1), dim3(1024), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags, loss_out);
+    return;
+  }
+  OSEQ_LAUNCH(softmax_ce_kernel<false>, dim3(ceil_div(N, 4)), dim3(256), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags, loss_out);
   OSEQ_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, st, loss_n, N, loss_out);
 }
 

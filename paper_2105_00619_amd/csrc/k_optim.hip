@@ -8,21 +8,8 @@
 
 namespace oseq {
 
-// Clears the step's flags and validates the labels before anything else runs: flags[0] = a gradient is not finite
-// (set by the check pass), flags[1] = a label lies outside [0, classes).  Either flag makes the update pass a no-op,
-// and flags[1] also keeps the BatchNorm running statistics as they were.  One block; stream order makes the flags
-// visible to every later kernel of the step.
-__global__ void __launch_bounds__(256) step_init_kernel(int* __restrict__ flags, const int32_t* __restrict__ y, int n,
-                                                        int classes) {
-  __shared__ int bad;
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  bool b = false;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) b |= y[i] < 0 || y[i] >= classes;
-  if (b) bad = 1;  // every writer stores the same value
-  __syncthreads();
-  if (threadIdx.x < 4) flags[threadIdx.x] = threadIdx.x == 1 ? bad : 0;
-}
+// (a batch that arrives as fp32 images: done by the kernel that casts them)
+__global__ void __launch_bounds__(256) step_init_kernel(StepBegin b) { step_begin(b); }
 
 typedef __attribute__((ext_vector_type(4))) float opt_v4f;
 
@@ -42,12 +29,27 @@ __global__ void __launch_bounds__(256) optim_check_kernel(const float* __restric
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flags, 1);
 }
 
-template <class T, bool HALF>
-__global__ void __launch_bounds__(256) optim_update_kernel(float* __restrict__ w, float* __restrict__ v,
+// The update pass also reports the step (loss and flags, 32 floats) to page-locked host memory: a copy of its own behind the step took
+// 3 us of it.  CHECK: few parameters (at most 16 per thread of one block): the check pass too, and with it a launch.
+constexpr int OPTIM_SMALL = 16384;
+template <class T, bool HALF, bool CHECK>
+__global__ void __launch_bounds__(CHECK ? 1024 : 256) optim_update_kernel(float* __restrict__ w, float* __restrict__ v,
                                                            const float* __restrict__ g, T* __restrict__ w16,
                                                            float* __restrict__ gout, int64_t n, float lr, float mom,
-                                                           float inv_scale, const int* __restrict__ flags) {
-  if (flags[0] | flags[1]) return;  // non-finite gradient or invalid label: the step changes nothing
+                                                           float inv_scale, int* flags, const float* report, float* report_host) {
+  bool skip;
+  if (CHECK) {
+    bool bad = false;
+    for (int64_t i = threadIdx.x; i < n; i += 1024) bad |= (__float_as_uint(g[i]) & 0x7f800000u) == 0x7f800000u;
+    bad = __syncthreads_or(bad);
+    skip = bad || flags[1];
+    if (threadIdx.x < 32) report_host[threadIdx.x] = threadIdx.x == 16 ? __int_as_float(bad ? 1 : 0) : report[threadIdx.x];
+    if (bad && threadIdx.x == 0) flags[0] = 1;
+  } else {
+    skip = flags[0] | flags[1];
+    if (blockIdx.x == 0 && threadIdx.x < 32) report_host[threadIdx.x] = report[threadIdx.x];
+  }
+  if (skip) return;  // non-finite gradient or invalid label: the step changes nothing
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t n4 = n / 4;
@@ -113,16 +115,24 @@ static int grid_for(int64_t n) { int64_t b = (n + 255) / 256; return (int)(b < 1
 // four parameters per thread and trip
 static int grid4_for(int64_t n) { return grid_for((n + 3) / 4); }
 
-void launch_step_init(hipStream_t st, int* flags, const int32_t* y, int n, int classes) {
-  OSEQ_LAUNCH(step_init_kernel, dim3(1), dim3(256), 0, st, flags, y, n, classes);
+void launch_step_init(hipStream_t st, const StepBegin& begin) { OSEQ_LAUNCH(step_init_kernel, dim3(1), dim3(256), 0, st, begin); }
+
+template <class T, bool HALF>
+static void launch_update(hipStream_t st, float* w, float* v, const float* g, void* w16, float* gout, int64_t n, float lr, float mom,
+                          float inv_scale, int* flags, const float* report, float* report_host) {
+  if (n <= OPTIM_SMALL) {
+    OSEQ_LAUNCH((optim_update_kernel<T, HALF, true>), dim3(1), dim3(1024), 0, st, w, v, g, (T*)w16, gout, n, lr, mom, inv_scale, flags, report, report_host);
+    return;
+  }
+  OSEQ_LAUNCH(optim_check_kernel, dim3(grid4_for(n)), dim3(256), 0, st, g, n, flags);
+  OSEQ_LAUNCH((optim_update_kernel<T, HALF, false>), dim3(grid4_for(n)), dim3(256), 0, st, w, v, g, (T*)w16, gout, n, lr, mom, inv_scale, flags, report, report_host);
 }
 
 void launch_optim(hipStream_t st, int dt, float* w, float* v, const float* g, void* w16, float* gout, int64_t n, float lr,
-                  float mom, float inv_scale, int* flags) {
-  OSEQ_LAUNCH(optim_check_kernel, dim3(grid4_for(n)), dim3(256), 0, st, g, n, flags);
-  if (dt == DT_F32) OSEQ_LAUNCH((optim_update_kernel<float, false>), dim3(grid4_for(n)), dim3(256), 0, st, w, v, g, (float*)nullptr, gout, n, lr, mom, inv_scale, flags);
-  else if (dt == DT_BF16) OSEQ_LAUNCH((optim_update_kernel<bf16_t, true>), dim3(grid4_for(n)), dim3(256), 0, st, w, v, g, (bf16_t*)w16, gout, n, lr, mom, inv_scale, flags);
-  else OSEQ_LAUNCH((optim_update_kernel<f16_t, true>), dim3(grid4_for(n)), dim3(256), 0, st, w, v, g, (f16_t*)w16, gout, n, lr, mom, inv_scale, flags);
+                  float mom, float inv_scale, int* flags, const float* report, float* report_host) {
+  if (dt == DT_F32) launch_update<float, false>(st, w, v, g, nullptr, gout, n, lr, mom, inv_scale, flags, report, report_host);
+  else if (dt == DT_BF16) launch_update<bf16_t, true>(st, w, v, g, w16, gout, n, lr, mom, inv_scale, flags, report, report_host);
+  else launch_update<f16_t, true>(st, w, v, g, w16, gout, n, lr, mom, inv_scale, flags, report, report_host);
 }
 
 void launch_cast_params(hipStream_t st, int dt, const float* w, void* w16, int64_t n) {

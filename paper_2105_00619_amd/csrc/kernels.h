@@ -22,7 +22,10 @@ struct EvalBatch { static constexpr int MAX_JOBS = 96; EvalJob job[MAX_JOBS]; in
 void launch_bn_eval_affine(hipStream_t st, const float* w, const float* running, float eps, float* affine, const EvalJob* jobs,
                            int njobs);
 
-void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n);
+// flags (four ints) cleared, flags[1] = a label lies outside [0, classes)
+struct StepBegin { int* flags; const int32_t* y; int n, classes; };
+// begin: null, or the start of a training step, done by the same launch
+void launch_cast_in(hipStream_t st, int dt, const float* x, void* out, int64_t n, const StepBegin* begin = nullptr);
 // storage type -> fp32 (read-back of an activation for inspection)
 void launch_cast_out(hipStream_t st, int dt, const void* x, float* out, int64_t n);
 void launch_bn_stats(hipStream_t st, int dt, const void* z, int64_t rows, int C, int nblk, float* partial, float eps,
@@ -57,13 +60,17 @@ void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const 
 void launch_bn_bwd_pool(hipStream_t st, int dt, const void* dy, const void* z, const float* stats, int N, int H, int W, int C,
                         int relu, int nblk, float* ws, float* dgamma, float* dbeta, void* dz);
 void launch_relu_bwd(hipStream_t st, int dt, const void* da, const void* a, void* dz, int64_t rows, int C);
-void launch_bias_grad(hipStream_t st, int dt, const void* dz, int64_t rows, int C, int nblk, float* partial, float* dbias);
+// a, dz_out (null: none): dz is the gradient behind a ReLU whose output is a; dz_out receives it with the ReLU applied, and that is summed
+void launch_bias_grad(hipStream_t st, int dt, const void* dz, const void* a, void* dz_out, int64_t rows, int C, int nblk, float* partial,
+                      float* dbias);
 void launch_maxpool_fwd(hipStream_t st, int dt, const void* x, void* y, int N, int H, int W, int C);
 void launch_maxpool_bwd(hipStream_t st, int dt, const void* x, const void* dy, void* dx, int N, int H, int W, int C);
 
 // The BatchNorm apply whose output only the head's global average pool reads, done by the pooling kernel (x is then its z): the
 // output itself is never written.  As launch_bn_apply; C a multiple of 16 / element size
 struct HeadApply { const float* stats; const void* skip; const float* skip_stats; void* mask; int relu; };
+// at most 64 samples: their losses and the mean in one launch
+bool head_loss_in_one(int N);
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
                      float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply = nullptr);
@@ -159,9 +166,10 @@ void launch_weight_transposes(hipStream_t st, int dt, const float* wbase, void* 
 
 // device address and size of the per-GPU static activation arena (optorch_seq_step_static), current device
 hipError_t static_arena(void** ptr, uint64_t* bytes);
-void launch_step_init(hipStream_t st, int* flags, const int32_t* y, int n, int classes);
+void launch_step_init(hipStream_t st, const StepBegin& begin);
 void launch_optim(hipStream_t st, int dt, float* w, float* v, const float* g, void* w16, float* gout, int64_t n, float lr,
-                  float mom, float inv_scale, int* flags);
+                  float mom, float inv_scale, int* flags, const float* report, float* report_host);
+// report, report_host: 32 floats (loss and flags) copied to page-locked host memory when the step's flags are final
 void launch_cast_params(hipStream_t st, int dt, const float* w, void* w16, int64_t n);
 void launch_fill(hipStream_t st, float* p, int64_t n, float v);
 

@@ -572,7 +572,7 @@ struct Scheduler {
         }
         int g = grad[f.out];
         if (g < 0) { p.error = "internal: conv output has no gradient"; return false; }
-        if (!f.has_bn && f.relu) {
+        if (!f.has_bn && f.relu && !f.has_bias) {
           SOp& s = push(S_RELU_BWD, fi, PH_BWD, seg);
           s.in[0] = g; s.in[1] = cur[f.out];
           s.out[0] = grad_inst(f.out); g = s.out[0];
@@ -580,6 +580,7 @@ struct Scheduler {
         if (f.has_bias) {
           SOp& s = push(S_BIAS_GRAD, fi, PH_BWD, seg);
           s.in[0] = g;
+          if (!f.has_bn && f.relu) { s.in[1] = cur[f.out]; s.out[1] = grad_inst(f.out); g = s.out[1]; }
           s.out[0] = new_inst(-1, (uint64_t)f.red_blocks * 2 * f.K * 4, false);
         }
         {
@@ -639,7 +640,7 @@ struct Scheduler {
 int launches_of(const SOp& op, const FOp& f) {
   switch (op.kind) {
     case S_BN_STATS: return f.stat_blocks > 0 ? (f.stat_fold > 0 ? 2 : 1) : 2;
-    case S_HEAD_FWD: return f.head_ws > 0 ? 5 : 4;
+    case S_HEAD_FWD: return (f.head_ws > 0 ? 5 : 4) - (f.head_one ? 1 : 0);
     case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
     case S_BN_BWD: return op.out[0] >= 0 ? 3 : 2;

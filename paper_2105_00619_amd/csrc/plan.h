@@ -52,6 +52,7 @@ struct FOp {
   int64_t rs_off = -1;       // element offset of (running mean, running var) in the running-stat block
   int gap = 0, feat_dim = 0, classes = 0;
   int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
+  bool head_one = false;     // its losses and their mean are one launch (few samples)
   bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
                              // of the head's kernels
   int image_addend = 0;      // F_CONV: 1 = the data gradient can add one row per image (the gradient of a global average pool)
@@ -100,6 +101,8 @@ struct SOp {
                     // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
                     // S_BN_BWD, in[4] its workspace, in[5] the convolution's input (the z of a folded BatchNorm with in[6]
                     // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
+                    // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; out[1]
+                    // receives the gradient in front of it
                     // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
   bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it

@@ -1233,6 +1233,29 @@ def test_inference_at_benchmark_size_matches_oracle():
     assert np.linalg.norm(r["running"] - run) <= 1e-5 * np.linalg.norm(run)
 
 
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16])
+@pytest.mark.parametrize("b", [211, 7])  # 1 053 945 values: groups of eight and one more; few: one per thread
+def test_images_at_any_address(precision, b):
+    """The cast of the images reads 16 bytes at a time where they lie on 16 bytes: the same bits from any address."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(3, 8, 3), W.gap_linear_ce(8, 10)]
+    p, x, y = _inputs(units, b, 45, 37, 10)
+    t = SeqTrainer(units, k_segments=1, precision=precision, batch=b, height=45, width=37, channels=3, num_classes=10)
+    t.set_params(p)
+    room = torch.empty(x.size + 4, device="cuda")
+    yd, got = torch.from_numpy(y).cuda(), []
+    for off in (0, 1, 2):
+        xd = room[off:off + x.size].view(x.shape)
+        xd.copy_(torch.from_numpy(x))
+        grads = torch.empty(t.param_count, device="cuda")
+        loss = t.step(xd, yd, 0.0, grads=grads)["loss"]
+        got.append((loss, grads.cpu().numpy(), t.unit_output(xd, 0).cpu().numpy()))
+    t.close()
+    for loss, grads, out in got[1:]:
+        assert loss == got[0][0] and np.array_equal(grads, got[0][1]) and np.array_equal(out, got[0][2])
+
+
 def test_label_out_of_range_is_an_error():
     from paper_2105_00619_amd.binding import OptorchError
     units, classes = NETS["conv_bn_relu"]
