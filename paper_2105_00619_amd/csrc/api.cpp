@@ -24,7 +24,7 @@ struct optorch_seq {
   char* pbase = nullptr; uint64_t pbytes = 0;
   char* abase = nullptr; uint64_t abytes = 0;
   hipStream_t stream = nullptr;
-  uint64_t off_w = 0, off_v = 0, off_g = 0, off_h = 0, off_wt = 0, off_run = 0, off_scal = 0, param_arena_bytes = 0;
+  uint64_t off_w = 0, off_v = 0, off_g = 0, off_h = 0, off_wt = 0, off_run = 0, off_scal = 0, off_sums = 0, param_arena_bytes = 0;
   bool bound = false, params_set = false;
   bool x_encoded = false;  // the current step's batch came in encoded form
   int dt = 0, in_channels = 0;
@@ -96,6 +96,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
         f.bwd_fuse = f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g);
+        if (f.dgrad_algo == ALGO_MFMA) f.dgrad_sums = conv_dgrad_sum_blocks(dt, g);
         f.image_addend = f.dgrad_algo == ALGO_MFMA && conv_dgrad_image_addend_ok(dt, g);
         if (f.bwd_fuse) f.wgrad_splits = conv_bwd1x1_splits(g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
@@ -212,6 +213,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
   h->off_wt = o; o = align_up(o + P * p.esize);  // transposed conv weights for the data-gradient GEMM
   h->off_run = o; o = align_up(o + p.n_running * 4);
   h->off_scal = o; o = align_up(o + 256);
+  h->off_sums = o; o += 2 * p.scratch_bytes;
   h->param_arena_bytes = o;
   for (size_t i = 0; i < p.fops.size(); ++i)
     if (p.fops[i].kind == F_BN_STATS) {
@@ -322,7 +324,11 @@ struct Ctx {
   // the batch in encoded form instead of x (groups of xz images, Algorithm "Encode"), with the input normalisation
   const StepBegin* begin = nullptr;  // what the cast of the images starts the step with
   const uint64_t* xa = nullptr; int xz = 0; const float* xscale = nullptr; const float* xshift = nullptr;
-  void* at(int inst) const { return inst < 0 ? nullptr : (void*)(abase + h->plan.insts[inst].offset); }
+  void* at(int inst) const {
+    if (inst < 0) return nullptr;
+    const Inst& t = h->plan.insts[inst];
+    return t.scratch >= 0 ? (void*)(h->pbase + h->off_sums + t.scratch * h->plan.scratch_bytes) : (void*)(abase + t.offset);
+  }
   float* w32(int64_t off) const { return (float*)(h->pbase + h->off_w) + off; }
   float* g32(int64_t off) const { return (float*)(h->pbase + h->off_g) + off; }
   const void* wc(int64_t off) const {  // weights in the compute type
@@ -401,14 +407,14 @@ void run_op(const Ctx& c, const SOp& s) {
       // in[3]: the block output whose sign gives the ReLU decisions, or (variant 2) those decisions as a bit mask
       launch_bn_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? nullptr : c.at(s.in[3]),
                     s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]), (int64_t)f.N * f.P * f.Q, f.C,
-                    f.relu, f.red_blocks, (float*)c.at(s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
-                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0);
+                    f.relu, s.rows, (float*)c.at(s.in[4] >= 0 ? s.in[4] : s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
+                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0, s.in[4] >= 0);
       break;
     case S_RELU_BWD:
       launch_relu_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), (int64_t)f.N * f.P * f.Q, f.K);
       break;
     case S_BIAS_GRAD:
-      launch_bias_grad(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[1]), (int64_t)f.N * f.P * f.Q, f.K, f.red_blocks, (float*)c.at(s.out[0]),
+      launch_bias_grad(st, dt, c.at(s.in[0]), c.at(s.in[1]), (int64_t)f.N * f.P * f.Q, f.K, f.red_blocks, (float*)c.at(s.out[0]),
                        c.g32(f.b_off));
       break;
     case S_WGRAD:
@@ -425,16 +431,17 @@ void run_op(const Ctx& c, const SOp& s) {
     case S_DGRAD:
       if (f.dgrad_algo == ALGO_MFMA)
         launch_conv_dgrad_mfma(st, dt, c.at(s.in[0]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize, c.at(s.in[1]),
-                               c.at(s.in[2]), s.per_image, c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f));
+                               c.at(s.in[2]), s.per_image, c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f),
+                               DgradSums{(float*)c.at(s.out[2]), c.at(s.in[3]), (const float*)c.at(s.in[4]), s.variant});
       else
         launch_conv_dgrad_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), c.at(s.in[1]), c.at(s.out[0]), geom(f));
       break;
     case S_CONV_BWD: {
       const FOp& ap = h->plan.fops[s.fop + 2];
       launch_conv_bwd1x1(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
-                         (const float*)c.at(s.in[4]) + (int64_t)ap.red_blocks * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
+                         (const float*)c.at(s.in[4]) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
                          c.at(s.in[5]), (const float*)c.at(s.in[6]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
-                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f));
+                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f), (float*)c.at(s.out[2]));
       break;
     }
     case S_POOL_BWD:
@@ -472,7 +479,8 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_CONV_FWD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K + wts); break;
     case S_DGRAD:
       *flops = 2 * out_px * wts;
-      *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0);
+      *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0) +
+               (s.out[2] >= 0 ? e * in_px * f.C : 0);  // (z of the BatchNorm whose sums it makes)
       break;
     case S_WGRAD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K) + 4 * wts; break;
     case S_BN_STATS: *bytes = s.in[1] >= 0 ? 8.0 * f.stat_blocks * f.C : e * out_px * f.C; break;  // fused: only the block sums
@@ -485,6 +493,10 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
       {  // the reduction reads dA, z and the ReLU source; the apply pass reads them again and writes dz (+ the skip gradient)
         const double src = s.in[3] < 0 ? 0.0 : s.variant == 2 ? 1.0 / 16 : 1.0;  // a bit mask is a sixteenth of a tensor
         const double da = s.per_image ? 0.0 : 1.0;  // (a gradient per image is next to nothing)
+        if (s.in[4] >= 0) {  // the sums came with the gradient
+          *bytes = s.out[0] < 0 ? 8.0 * s.rows * f.C : e * out_px * f.C * (2 + da + src + (s.out[1] >= 0 ? 1 : 0));
+          break;
+        }
         if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + da + src); break; }  // (the sums only)
         *bytes = e * out_px * f.C * (1 + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
@@ -496,7 +508,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_POOL_FWD: *bytes = e * (in_px + out_px) * f.C; break;
     case S_POOL_BWD: *bytes = e * (2 * in_px + out_px) * f.C; break;
     case S_RELU_BWD: *bytes = e * 3 * out_px * f.K; break;
-    case S_BIAS_GRAD: *bytes = e * out_px * f.K * (s.out[1] >= 0 ? 3 : 1); break;
+    case S_BIAS_GRAD: *bytes = e * out_px * f.K * (s.in[1] >= 0 ? 3 : 1); break;
     case S_HEAD_FWD: *bytes = e * in_px * f.C * (1 + (s.variant == 1 && s.in[2] >= 0 ? 1.0 : 0.0) + (s.out[5] >= 0 ? 1.0 / 16 : 0)); break;
     case S_HEAD_BWD: *bytes = e * in_px * f.C; break;
   }

@@ -128,6 +128,49 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
   }
 }
 
+// The store pass of a data gradient whose result is the gradient behind a BatchNorm (+ReLU) without a skip connection: the values
+// are rounded and stored, and the sums that the BatchNorm's backward pass begins with -- of dy and of dy * xhat, dy the stored value
+// where the ReLU let it through -- go to ss and qq, so that no kernel has to read the gradient for them.
+// bn: that BatchNorm's [4][C] statistics tensor, z its input, shaped as the output.
+template <int NT, class T, int BN, int HR, class RowOff>
+__device__ __forceinline__ void epi_bn_sums_rows_nt(const float* ep, int tid, int n0, const float* __restrict__ bn, int C,
+                                                    const T* __restrict__ z, T* __restrict__ out, int relu, RowOff rowoff,
+                                                    float (&ss)[8], float (&qq)[8]) {
+  constexpr int EP_PITCH = BN + 4;
+  constexpr int GROUPS = BN / 8, PER_THREAD = HR * GROUPS / NT, RG = NT / GROUPS;
+  const int c8 = (tid % GROUPS) * 8, erow = tid / GROUPS;
+  const int col = n0 + c8;
+  int64_t ro[PER_THREAD];
+  Vec<T, 8> zv[PER_THREAD];
+#pragma unroll
+  for (int it = 0; it < PER_THREAD; ++it) {
+    ro[it] = rowoff(erow + it * RG);
+    zv[it] = *reinterpret_cast<const Vec<T, 8>*>(z + (ro[it] >= 0 ? ro[it] : 0) + col);  // (rows that are not stored: the first)
+  }
+  float mean[8], rstd[8], scale[8], shift[8];
+  load_f32<float, 8>(bn + col, mean);
+  load_f32<float, 8>(bn + C + col, rstd);
+  load_f32<float, 8>(bn + 2 * C + col, scale);
+  load_f32<float, 8>(bn + 3 * C + col, shift);
+#pragma unroll
+  for (int it = 0; it < PER_THREAD; ++it) {
+    const int row = erow + it * RG;
+    const epi_v4f x0 = *reinterpret_cast<const epi_v4f*>(&ep[row * EP_PITCH + c8]);
+    const epi_v4f x1 = *reinterpret_cast<const epi_v4f*>(&ep[row * EP_PITCH + c8 + 4]);
+    const float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+    const Vec<T, 8> t = round_vec<T, 8>(v);
+    if (ro[it] >= 0) *reinterpret_cast<Vec<T, 8>*>(out + ro[it] + col) = t;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float zf = to_f32(zv[it].v[k]);
+      const bool on = ro[it] >= 0 && (!relu || bn_affine(zf, scale[k], shift[k]) > 0.f);
+      const float dy = on ? to_f32(t.v[k]) : 0.f;
+      ss[k] += dy;
+      qq[k] = __fmaf_rn(dy, (zf - mean[k]) * rstd[k], qq[k]);
+    }
+  }
+}
+
 // The residual-adding pass in two halves, for a kernel whose block owns its CU alone and therefore has nobody to cover
 // the latency of the addend loads: the addend pieces (and mask bytes) of a pass are requested one pass ahead
 // (epi_load_addend_nt), before the stores of the pass in between, and added later (epi_store_rows_pre_nt).  Loads

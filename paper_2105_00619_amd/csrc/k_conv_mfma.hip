@@ -469,6 +469,7 @@ struct PatchArgs {
   int row_blocks;
   const uint8_t* amask;      // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
   int eval;                  // 1: the EVAL instantiation
+  int bn_sums;               // 1: STAT 2
   int split32;               // fp32: 1: the Split32 instantiation
   const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
                              // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
@@ -484,7 +485,9 @@ template <class X> constexpr int PATCH_WAVES(int bn, int mi, int most) {
 }
 
 // EVAL: `bias` is the [2][Ng] scale and shift of the inference-mode BatchNorm behind the layer, `addend` its skip connection
-template <class T, class X, int BN, int MI, int SUBT, bool STAT, bool FOLD = false, bool EVAL = false>
+// STAT: 1 the sums of the BatchNorm behind the layer, 2 (data gradient) those of the BatchNorm backward in front of it: `bias` is then
+// that one's statistics tensor, `addend` its z and a.relu whether a ReLU follows it
+template <class T, class X, int BN, int MI, int SUBT, int STAT, bool FOLD = false, bool EVAL = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PATCH_WAVES<X>(BN, MI, 0), PATCH_WAVES<X>(BN, MI, 1))))
 conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const float* __restrict__ bias,
                      const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ partial,
@@ -782,8 +785,10 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
       else if (EVAL)
         epi_eval_pass_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff);
+      else if constexpr (STAT == 2)
+        epi_bn_sums_rows_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff, ss, qq);
       else
-        epi_store_pass<T, BN, HR, true, !STAT, STAT>(ep, tid, n0c, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
+        epi_store_pass<T, BN, HR, true, STAT == 0, STAT == 1>(ep, tid, n0c, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
     }
     if (STAT)
       epi_stat_combine<BN>(ep, tid, ss, qq, stat_partial + ((int64_t)bx * 2 + 0) * a.Ng + n0c,
@@ -1026,27 +1031,37 @@ static void launch_patch_v(hipStream_t st, const void* src, const void* wmat, co
     if (a.eval && splits == 1) {
       static bool eval_attr = false;
       if (!eval_attr) {
-        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, 0, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
         eval_attr = true;
       }
-      OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, false, true>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+      OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, 0, false, true>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                   (const T*)addend, (T*)out, (float*)nullptr, (float*)nullptr, a);
+      return;
+    }
+    if (a.bn_sums && splits == 1) {
+      static bool sums_attr = false;
+      if (!sums_attr) {
+        (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+        sums_attr = true;
+      }
+      OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, 2>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+                  (const T*)addend, (T*)out, (float*)nullptr, stat_partial, a);
       return;
     }
   }
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
-    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, true, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, 0, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    (void)hipFuncSetAttribute((const void*)conv3x3_patch_kernel<T, X, BN, MI, SUBT, 1, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
     attr_done = true;
   }
   // the variant that also adds up what it stores (BatchNorm statistics) is a separate instantiation, so that the
   // plain one carries none of its registers
   if (splits == 1 && stat_partial)
-    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, true, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, 1, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                        (const T*)addend, (T*)out, (float*)nullptr, stat_partial, a);
   else
-    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, false, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
+    OSEQ_LAUNCH((conv3x3_patch_kernel<T, X, BN, MI, SUBT, 0, FOLD>), grid, block, sm, st, (const T*)src, (const T*)wmat, bias,
                        (const T*)addend, (T*)out, splits > 1 ? partial : (float*)nullptr, (float*)nullptr, a);
 }
 
@@ -1243,9 +1258,20 @@ bool conv_dgrad_image_addend_ok(int dt, const ConvGeom& g) {
   return conv_pointwise_dgrad_ok(dt, g) && g.stride == 1 && (int64_t)g.N * g.H * g.W < (int64_t)1 << 32;
 }
 
+// Row blocks over which the data gradient can produce the sums of the BatchNorm backward in front of the layer, 0: it cannot.  (More
+// rows than the finishing kernel takes without a fold are not worth it.)
+int conv_dgrad_sum_blocks(int dt, const ConvGeom& g) {
+  PatchShape pv; PatchArgs pa{};
+  if (conv_pointwise_dgrad_ok(dt, g) || dgrad_ws3x3(dt, g)) return 0;
+  if (!patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa) || pv.splits > 1) return 0;
+  const int blocks = (pa.NT + pv.subt - 1) / pv.subt;
+  return bn_stats_fold_rows(blocks) > 0 ? 0 : blocks;
+}
+
 // wt: the (C_in, kh, kw, C_out) transpose of the weights, in the compute type
 void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g) {
+                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g,
+                            const DgradSums& sums) {
   PatchShape pv; PatchArgs pa{};
   const uint8_t* amask = addend ? (const uint8_t*)addend_mask : nullptr;
   if (conv_pointwise_dgrad_ok(dt, g)) {
@@ -1259,6 +1285,11 @@ void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* 
   if (patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.P; pa.srcW = g.Q; pa.srcC = g.K; pa.dstH = g.H; pa.dstW = g.W; pa.Ng = g.C;
     pa.pad = g.R - 1 - g.pad; pa.flip = 1; pa.relu = 0; pa.amask = amask;
+    if (sums.partial) {
+      pa.bn_sums = 1; pa.relu = sums.relu;
+      launch_patch(st, dt, dz, wt, sums.stats, sums.z, dx, partial, sums.partial, pv, pa);
+      return;
+    }
     launch_patch(st, dt, dz, wt, nullptr, addend, dx, partial, nullptr, pv, pa);
     return;
   }

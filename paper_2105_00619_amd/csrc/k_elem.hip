@@ -46,7 +46,7 @@ __global__ void cast_out_kernel(const T* __restrict__ x, float* __restrict__ out
 
 // ----------------------------------------------------- column reductions ----
 // RED_BN_BWD: ReLU decisions redone from z (or none); _AOUT: from the sign of the block output; _MASK: from the bits
-// RED_BIAS_RELU: the gradient behind a ReLU with output aout: where that is positive, stored to dz and summed
+// RED_BIAS_RELU: the gradient behind a ReLU with output aout: where that is positive, stored to dz (the same memory) and summed
 enum { RED_STATS = 0, RED_BN_BWD = 1, RED_BIAS = 2, RED_BN_BWD_AOUT = 3, RED_BN_BWD_MASK = 4, RED_BIAS_RELU = 5 };
 
 struct RedArgs {
@@ -915,12 +915,13 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
 
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip, int per_image) {
+                   void* dz, void* dskip, int per_image, bool summed) {
   RedArgs g{}; g.div_hw = make_fastdiv(per_image ? (uint32_t)per_image : 1u); g.a = da; g.z = z; g.aout = aout; g.mask = (const uint8_t*)mask; g.stats = stats; g.partial = ws; g.rows = rows;
   g.C = C; g.relu = relu; g.nblk = nblk;
   // the same choice of the ReLU decisions' source as the apply kernel below makes
   const int vmax = dt == DT_F32 ? 4 : 8;
-  if (per_image) {
+  if (summed) {
+  } else if (per_image) {
     if (mask) launch_colreduce<RED_BN_BWD_MASK, true>(st, dt, g);
     else launch_colreduce<RED_BN_BWD, true>(st, dt, g);
   } else if (mask && C % vmax == 0) launch_colreduce<RED_BN_BWD_MASK>(st, dt, g);
@@ -976,10 +977,10 @@ void launch_relu_bwd(hipStream_t st, int dt, const void* da, const void* a, void
 #undef CALL
 }
 
-void launch_bias_grad(hipStream_t st, int dt, const void* dz, const void* a, void* dz_out, int64_t rows, int C, int nblk, float* partial,
+void launch_bias_grad(hipStream_t st, int dt, void* dz, const void* a, int64_t rows, int C, int nblk, float* partial,
                       float* dbias) {
-  RedArgs g{}; g.a = dz; g.aout = a; g.dz = dz_out; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
-  if (dz_out) launch_colreduce<RED_BIAS_RELU>(st, dt, g);
+  RedArgs g{}; g.a = dz; g.aout = a; g.dz = dz; g.partial = partial; g.rows = rows; g.C = C; g.nblk = nblk;
+  if (a) launch_colreduce<RED_BIAS_RELU>(st, dt, g);
   else launch_colreduce<RED_BIAS>(st, dt, g);
   FIN_LAUNCH(bias_finalize_kernel, 0, st, partial, nblk, C, dbias);
 }

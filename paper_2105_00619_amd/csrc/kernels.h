@@ -54,14 +54,15 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
 // sign of aout if given, else redone from z when relu is set
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip, int per_image);
+                   void* dz, void* dskip, int per_image, bool summed = false);
+// summed: ws holds the nblk rows of partial sums already
 // the same where dy is the gradient of the 2x2 max-pool that follows the activation ([N][H/2][W/2][C]; H, W even): the
 // pool's own backward pass is not run
 void launch_bn_bwd_pool(hipStream_t st, int dt, const void* dy, const void* z, const float* stats, int N, int H, int W, int C,
                         int relu, int nblk, float* ws, float* dgamma, float* dbeta, void* dz);
 void launch_relu_bwd(hipStream_t st, int dt, const void* da, const void* a, void* dz, int64_t rows, int C);
-// a, dz_out (null: none): dz is the gradient behind a ReLU whose output is a; dz_out receives it with the ReLU applied, and that is summed
-void launch_bias_grad(hipStream_t st, int dt, const void* dz, const void* a, void* dz_out, int64_t rows, int C, int nblk, float* partial,
+// a (or null): dz is the gradient behind a ReLU whose output is a; it gets the ReLU applied, in place, and is then summed
+void launch_bias_grad(hipStream_t st, int dt, void* dz, const void* a, int64_t rows, int C, int nblk, float* partial,
                       float* dbias);
 void launch_maxpool_fwd(hipStream_t st, int dt, const void* x, void* y, int N, int H, int W, int C);
 void launch_maxpool_bwd(hipStream_t st, int dt, const void* x, const void* dy, void* dx, int N, int H, int W, int C);
@@ -120,8 +121,13 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
 // addend_mask (null, or with an addend): ReLU decisions as bits (as launch_bn_apply writes them); the addend counts
 // as zero where its bit is clear.  addend_per_image (only where conv_dgrad_image_addend_ok): the addend is [N][C_in]
 bool conv_dgrad_image_addend_ok(int dt, const ConvGeom& g);
+// The gradient that a data gradient writes is the one behind a BatchNorm (+ReLU): its kernel also produces the sums that the
+// BatchNorm's backward pass begins with, partial [conv_dgrad_sum_blocks][2][C_in] (null: not; never with an addend)
+int conv_dgrad_sum_blocks(int dt, const ConvGeom& g);
+struct DgradSums { float* partial = nullptr; const void* z = nullptr; const float* stats = nullptr; int relu = 0; };
 void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* wt, const void* addend,
-                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g);
+                            const void* addend_mask, bool addend_per_image, void* dx, float* partial, int splits, const ConvGeom& g,
+                            const DgradSums& sums = DgradSums());
 // 1x1 convolutions in 16-bit storage as a streaming GEMM (k_conv_pointwise.hip); used by the MFMA launchers above
 bool conv_pointwise_fwd_ok(int dt, const ConvGeom& g);
 bool conv_pointwise_dgrad_ok(int dt, const ConvGeom& g);
@@ -155,7 +161,8 @@ bool conv_bwd1x1_ok(int dt, const ConvGeom& g);
 int conv_bwd1x1_splits(const ConvGeom& g);
 void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* z, const void* mask, const float* stats, const float* coef,
                         int relu, int per_image, const void* x, const float* fold, const void* wt, void* dx, float* dw, float* partial,
-                        int splits, const ConvGeom& g);
+                        int splits, const ConvGeom& g, float* sums);
+// sums (null, or with fold): as DgradSums::partial for the folded BatchNorm, [splits][2][C_in]
 // adds the pixel ranges' partial sums [splits][n] in order
 void launch_wgrad_reduce(hipStream_t st, const float* partial, float* out, int64_t n, int splits);
 // Transposed weight copies for the data-gradient GEMMs, all layers in one launch (per 48 layers).  w_off: element

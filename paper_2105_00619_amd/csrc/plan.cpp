@@ -316,12 +316,13 @@ struct Scheduler {
                                  //              reader applies the mask to the block output's gradient itself), or -1
   std::vector<char> per_image;   // [LTensor] -> grad[t] (or image_grad[t]) holds one value per image and channel
   std::vector<int> fused_bwd;    // [FOp of a convolution] -> entry of the BatchNorm-backward sums that its S_CONV_BWD goes on from, or -1
+  std::vector<int> bn_sums, bn_sum_rows;  // [LTensor] -> Inst id of the BatchNorm-backward sums that came with grad[t], or -1, and their rows
   std::vector<int> image_grad;   // [LTensor] -> Inst id of the gradient per image of the global average pool's input, or -1
   explicit Scheduler(Plan& pl)
       : p(pl), cur(pl.tensors.size(), -1), grad(pl.tensors.size(), -1), stat_ws(pl.tensors.size(), -1),
         bn_apply_of(pl.tensors.size(), -1), rebuilt(pl.tensors.size(), 0), readers(pl.tensors.size(), 0),
         via_pool(pl.tensors.size(), -1), gmask(pl.tensors.size(), -1), per_image(pl.tensors.size(), 0),
-        fused_bwd(pl.fops.size(), -1), image_grad(pl.tensors.size(), -1) {
+        fused_bwd(pl.fops.size(), -1), bn_sums(pl.tensors.size(), -1), bn_sum_rows(pl.tensors.size(), 0), image_grad(pl.tensors.size(), -1) {
     for (size_t fi = 0; fi < pl.fops.size(); ++fi) {
       const FOp& f = pl.fops[fi];
       if (f.kind == F_BN_APPLY) bn_apply_of[f.out] = (int)fi;
@@ -345,6 +346,14 @@ struct Scheduler {
     Inst i; i.logical = logical; i.bytes = bytes; i.fwd_value = fwd_value;
     p.insts.push_back(i);
     return (int)p.insts.size() - 1;
+  }
+  int next_slot = 0;
+  int scratch_inst(uint64_t bytes) {
+    const int i = new_inst(-1, 0, false);
+    p.insts[i].scratch = next_slot;
+    next_slot ^= 1;
+    p.scratch_bytes = std::max(p.scratch_bytes, align_up(bytes));
+    return i;
   }
   int value_inst(int t) { return cur[t] = new_inst(t, p.tensors[t].bytes, true); }
   int grad_inst(int t) { return new_inst(t, p.tensors[t].bytes, false); }
@@ -473,6 +482,16 @@ struct Scheduler {
     return false;
   }
 
+  // May the kernel that writes the gradient of convolution fi's input produce the sums of the BatchNorm backward in front of it?
+  // Inside a unit only, whatever the segments are: a BatchNorm without a skip connection, which nothing else reads.
+  int summed_apply(int fi) const {
+    const FOp& f = p.fops[fi];
+    const int ap = bn_apply_of[f.x];
+    if (ap < 0 || grad[f.x] >= 0 || readers[f.x] != 1) return -1;
+    const FOp& b = p.fops[ap];
+    return b.unit == f.unit && b.skip < 0 && b.mask < 0 ? ap : -1;
+  }
+
   // The projection shortcut's BatchNorm apply whose output operation fi adds, or -1.
   int projection_of(int fi) const {
     const FOp& f = p.fops[fi];
@@ -532,6 +551,7 @@ struct Scheduler {
         if (f.skip >= 0 && !f.relu) { p.error = "skip connection without ReLU is not supported"; return false; }
         const int gin_mask = gmask[f.out];  // the incoming gradient still wants a mask (projection shortcut's BatchNorm)
         SOp& s = push(S_BN_BWD, fi, PH_BWD, seg);
+        const size_t at = p.sched.size() - 1;
         s.variant = variant;
         s.per_image = image;
         s.in[0] = gin; s.in[1] = cur[f.x]; s.in[2] = cur[f.stats];
@@ -553,21 +573,32 @@ struct Scheduler {
           }
           else { s.out[1] = grad_inst(f.skip); grad[f.skip] = s.out[1]; gmask[f.skip] = -1; }
         }
-        s.out[2] = new_inst(-1, ((uint64_t)f.red_blocks * 2 + 2) * f.C * 4, false);
+        SOp& b = p.sched[at];
+        b.rows = f.red_blocks;
+        if (bn_sums[f.out] >= 0 && variant == 0) { b.in[4] = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
+        else b.out[2] = new_inst(-1, ((uint64_t)f.red_blocks * 2 + 2) * f.C * 4, false);
         return true;
       }
       case F_CONV: {
         if (fused_bwd[fi] >= 0) {
-          const int xin = f.fold_src >= 0 ? cur[p.fops[f.fold_src].x] : backward_input(f.x, seg);
+          // (with the sums of the BatchNorm in front it reads that one's z in every storage mode)
+          const int sums_for = summed_apply(fi) >= 0 && p.fops[summed_apply(fi)].relu ? summed_apply(fi) : -1;
+          const int from_z = f.fold_src >= 0 ? f.fold_src : sums_for;
+          const int xin = from_z >= 0 ? cur[p.fops[from_z].x] : backward_input(f.x, seg);
           const SOp sums = p.sched[fused_bwd[fi]];
           SOp& s = push(S_CONV_BWD, fi, PH_BWD, seg);
           for (int i = 0; i < 4; ++i) s.in[i] = sums.in[i];
           s.variant = sums.variant; s.per_image = sums.per_image;
-          s.in[4] = sums.out[2];
+          s.in[4] = sums.in[4] >= 0 ? sums.in[4] : sums.out[2];
           s.in[5] = xin;
-          if (f.fold_src >= 0) s.in[6] = cur[p.fops[f.fold_src].stats];
+          if (from_z >= 0) s.in[6] = cur[p.fops[from_z].stats];
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
+          s.rows = sums.rows;
           if (f.wgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.wgrad_splits * f.K * f.R * f.S * f.C * 4, false);
+          if (sums_for >= 0) {
+            s.out[2] = bn_sums[f.x] = scratch_inst(((uint64_t)f.wgrad_splits * 2 + 2) * f.C * 4);
+            bn_sum_rows[f.x] = f.wgrad_splits;
+          }
           return true;
         }
         int g = grad[f.out];
@@ -580,7 +611,7 @@ struct Scheduler {
         if (f.has_bias) {
           SOp& s = push(S_BIAS_GRAD, fi, PH_BWD, seg);
           s.in[0] = g;
-          if (!f.has_bn && f.relu) { s.in[1] = cur[f.out]; s.out[1] = grad_inst(f.out); g = s.out[1]; }
+          if (!f.has_bn && f.relu) s.in[1] = cur[f.out];  // (and the ReLU, in place: nothing else reads this gradient)
           s.out[0] = new_inst(-1, (uint64_t)f.red_blocks * 2 * f.K * 4, false);
         }
         {
@@ -595,6 +626,12 @@ struct Scheduler {
           SOp& s = push(S_DGRAD, fi, PH_BWD, seg);
           s.in[0] = g; s.in[1] = grad[f.x]; s.in[2] = grad[f.x] >= 0 ? gmask[f.x] : -1;
           s.per_image = grad[f.x] >= 0 && per_image[f.x];
+          const int ap = f.dgrad_sums > 0 ? summed_apply(fi) : -1;
+          if (ap >= 0) {
+            s.in[3] = cur[p.fops[ap].x]; s.in[4] = cur[p.fops[ap].stats]; s.variant = p.fops[ap].relu;
+            s.out[2] = bn_sums[f.x] = scratch_inst(((uint64_t)f.dgrad_sums * 2 + 2) * f.C * 4);
+            bn_sum_rows[f.x] = f.dgrad_sums;
+          }
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1; per_image[f.x] = 0;
           if (f.dgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.dgrad_splits * f.N * f.H * f.W * f.C * 4, false);
         }
@@ -618,6 +655,7 @@ struct Scheduler {
   bool run() {
     const int k = (int)p.seg_begin.size() - 1;
     p.insts.clear(); p.sched.clear();
+    p.scratch_bytes = 0;
     emit_fop_forward(0, k == 1 ? PH_FWD_LAST : PH_FWD_NOSAVE, 0);
     auto forward_seg = [&](int j, int phase) {
       for (int u = p.seg_begin[j]; u < p.seg_begin[j + 1]; ++u)
@@ -643,7 +681,7 @@ int launches_of(const SOp& op, const FOp& f) {
     case S_HEAD_FWD: return (f.head_ws > 0 ? 5 : 4) - (f.head_one ? 1 : 0);
     case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
-    case S_BN_BWD: return op.out[0] >= 0 ? 3 : 2;
+    case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.in[4] >= 0 ? 1 : 0);
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: case S_CONV_BWD: return f.wgrad_splits > 1 ? 2 : 1;
     case S_CONV_FWD: return f.fwd_splits > 1 ? 2 : 1;
@@ -722,6 +760,7 @@ bool build_schedule(Plan& p, uint64_t enough) {
     if (op.phase == PH_REPLAY) p.n_replay_launches += nl;
     for (int o : op.out) if (o >= 0) {
       Inst& t = p.insts[o];
+      if (t.scratch >= 0) continue;
       t.allocated = true;
       spans.push_back(Span{aligned(t.bytes), i, t.last_use, 0});
       span_inst.push_back(o);

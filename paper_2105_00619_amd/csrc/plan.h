@@ -55,6 +55,7 @@ struct FOp {
   bool head_one = false;     // its losses and their mean are one launch (few samples)
   bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
                              // of the head's kernels
+  int dgrad_sums = 0;        // F_CONV: row blocks over which the data gradient can sum for the BatchNorm backward in front of it, or 0
   int image_addend = 0;      // F_CONV: 1 = the data gradient can add one row per image (the gradient of a global average pool)
   int bwd_fuse = 0;          // F_CONV: 1 = the BatchNorm behind it, whose backward sums are known, and both gradients run as one kernel
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
@@ -82,6 +83,7 @@ struct Inst {
   bool fwd_value = false; // produced by a forward-kind operation
   bool held = false;      // checkpoint or kept for backward (counts as "saved")
   bool allocated = false;
+  int scratch = -1;       // >= 0: not in the activation arena but in that slot of the scratch memory behind the parameters
 };
 
 // One entry of the static schedule.
@@ -101,9 +103,13 @@ struct SOp {
                     // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
                     // S_BN_BWD, in[4] its workspace, in[5] the convolution's input (the z of a folded BatchNorm with in[6]
                     // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
-                    // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; out[1]
-                    // receives the gradient in front of it
+                    // S_DGRAD with out[2] >= 0: that receives the sums of the BatchNorm backward in front, whose z is in[3]
+                    // and statistics in[4]; variant: whether a ReLU follows that BatchNorm.  S_CONV_BWD likewise with out[2] (z and statistics are in[5] and in[6]).
+                    // S_BN_BWD with in[4] >= 0: that holds its sums, `rows` of them, and is its workspace
+                    // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; in[0]
+                    // becomes the gradient in front of it, in place
                     // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
+  int rows = 0;  // S_BN_BWD, S_CONV_BWD: rows of partial sums in the BatchNorm backward's workspace
   bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
   bool live = true;
@@ -135,6 +141,9 @@ struct Plan {
   // schedule
   std::vector<Inst> insts;
   std::vector<SOp> sched;
+  // BatchNorm-backward sums that come with a gradient live from one operation to the next or the one after: two slots of this
+  // many bytes, outside the activation arena, whose size they so leave alone
+  uint64_t scratch_bytes = 0;
   uint64_t arena_bytes = 0;       // high-water mark of the activation arena (aligned offsets)
   uint64_t peak_saved_bytes = 0;  // exact tensor sizes, no alignment
   uint64_t peak_live_bytes = 0;   // all live tensors incl. transients, exact sizes
