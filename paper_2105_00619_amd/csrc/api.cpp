@@ -324,11 +324,8 @@ struct Ctx {
   // the batch in encoded form instead of x (groups of xz images, Algorithm "Encode"), with the input normalisation
   const StepBegin* begin = nullptr;  // what the cast of the images starts the step with
   const uint64_t* xa = nullptr; int xz = 0; const float* xscale = nullptr; const float* xshift = nullptr;
-  void* at(int inst) const {
-    if (inst < 0) return nullptr;
-    const Inst& t = h->plan.insts[inst];
-    return t.scratch >= 0 ? (void*)(h->pbase + h->off_sums + t.scratch * h->plan.scratch_bytes) : (void*)(abase + t.offset);
-  }
+  void* at(int inst) const { return inst < 0 ? nullptr : (void*)(abase + h->plan.insts[inst].offset); }
+  float* sums(int slot) const { return slot < 0 ? nullptr : (float*)(h->pbase + h->off_sums + slot * h->plan.scratch_bytes); }
   float* w32(int64_t off) const { return (float*)(h->pbase + h->off_w) + off; }
   float* g32(int64_t off) const { return (float*)(h->pbase + h->off_g) + off; }
   const void* wc(int64_t off) const {  // weights in the compute type
@@ -407,8 +404,9 @@ void run_op(const Ctx& c, const SOp& s) {
       // in[3]: the block output whose sign gives the ReLU decisions, or (variant 2) those decisions as a bit mask
       launch_bn_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? nullptr : c.at(s.in[3]),
                     s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]), (int64_t)f.N * f.P * f.Q, f.C,
-                    f.relu, s.rows, (float*)c.at(s.in[4] >= 0 ? s.in[4] : s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
-                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0, s.in[4] >= 0);
+                    f.relu, s.rows, s.sums_in >= 0 ? c.sums(s.sums_in) : (float*)c.at(s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
+                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0, s.sums_in >= 0,
+                    s.sums_out >= 0 ? BnBwdDual{c.at(s.in[5]), (const float*)c.at(s.in[6]), c.sums(s.sums_out)} : BnBwdDual());
       break;
     case S_RELU_BWD:
       launch_relu_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), (int64_t)f.N * f.P * f.Q, f.K);
@@ -432,16 +430,16 @@ void run_op(const Ctx& c, const SOp& s) {
       if (f.dgrad_algo == ALGO_MFMA)
         launch_conv_dgrad_mfma(st, dt, c.at(s.in[0]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize, c.at(s.in[1]),
                                c.at(s.in[2]), s.per_image, c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f),
-                               DgradSums{(float*)c.at(s.out[2]), c.at(s.in[3]), (const float*)c.at(s.in[4]), s.variant});
+                               DgradSums{c.sums(s.sums_out), c.at(s.in[3]), (const float*)c.at(s.in[4]), s.variant});
       else
         launch_conv_dgrad_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), c.at(s.in[1]), c.at(s.out[0]), geom(f));
       break;
     case S_CONV_BWD: {
       const FOp& ap = h->plan.fops[s.fop + 2];
       launch_conv_bwd1x1(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
-                         (const float*)c.at(s.in[4]) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
+                         (s.sums_in >= 0 ? c.sums(s.sums_in) : (const float*)c.at(s.in[4])) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
                          c.at(s.in[5]), (const float*)c.at(s.in[6]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
-                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f), (float*)c.at(s.out[2]));
+                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f), c.sums(s.sums_out));
       break;
     }
     case S_POOL_BWD:
@@ -480,7 +478,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_DGRAD:
       *flops = 2 * out_px * wts;
       *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0) +
-               (s.out[2] >= 0 ? e * in_px * f.C : 0);  // (z of the BatchNorm whose sums it makes)
+               (s.sums_out >= 0 ? e * in_px * f.C : 0);  // (z of the BatchNorm whose sums it makes)
       break;
     case S_WGRAD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K) + 4 * wts; break;
     case S_BN_STATS: *bytes = s.in[1] >= 0 ? 8.0 * f.stat_blocks * f.C : e * out_px * f.C; break;  // fused: only the block sums
@@ -493,12 +491,12 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
       {  // the reduction reads dA, z and the ReLU source; the apply pass reads them again and writes dz (+ the skip gradient)
         const double src = s.in[3] < 0 ? 0.0 : s.variant == 2 ? 1.0 / 16 : 1.0;  // a bit mask is a sixteenth of a tensor
         const double da = s.per_image ? 0.0 : 1.0;  // (a gradient per image is next to nothing)
-        if (s.in[4] >= 0) {  // the sums came with the gradient
+        if (s.sums_in >= 0) {  // the sums came with the gradient
           *bytes = s.out[0] < 0 ? 8.0 * s.rows * f.C : e * out_px * f.C * (2 + da + src + (s.out[1] >= 0 ? 1 : 0));
           break;
         }
-        if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + da + src); break; }  // (the sums only)
-        *bytes = e * out_px * f.C * (1 + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
+        if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + (s.sums_out >= 0 ? 1 : 0) + da + src); break; }  // (the sums only)
+        *bytes = e * out_px * f.C * (1 + (s.sums_out >= 0 ? 1 : 0) + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
       break;
     case S_CONV_BWD:  // dA, z and the ReLU source, x, dx, the weights and their gradient

@@ -913,16 +913,16 @@ static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchA
   a.NT = ((N + ti - 1) / ti) * a.tiles_r * a.tiles_c;
   return true;
 }
-// The widest sub-tile, or the narrower one that covers the map with fewer of them: three rows of a wide map are more positions than
-// the buffer has for a whole sub-tile's pixels (64 of 128 on maps of 63 columns or more).
+// The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (64 of 128 on maps of 63 columns or
+// more), the narrower one that covers the map with the fewest sub-tiles, then staged positions.
 static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, PatchArgs& a) {
   bool ok = patch_geometry_of(N, dstH, dstW, dstW < cap ? dstW : cap, cap, a);
-  if (!narrow || a.TI > 1) return ok;  // (whole images)
+  if (!narrow || (ok && a.TP * 4 >= cap * 3)) return ok;
   for (int tc = 64; tc >= 8; tc /= 2) {
     PatchArgs b = a;
     if (tc >= dstW || !patch_geometry_of(N, dstH, dstW, tc, cap, b)) continue;
     if (!ok || b.NT < a.NT) { a = b; ok = true; }
-    else if (b.NT == a.NT && a.TC < dstW && b.NPOS < a.NPOS) a = b;
+    else if (b.NT == a.NT && b.NPOS < a.NPOS) a = b;
   }
   return ok;
 }

@@ -58,6 +58,9 @@ struct RedArgs {
   const float* stats;  // BN_BWD: [4][C] mean, rstd, scale, shift
   float* partial;      // [nblk][2][C]
   void* dz;            // BIAS_RELU
+  const void* z2;      // DUAL: z and statistics of a second BatchNorm with the same dA and decisions, and its partial sums
+  const float* stats2;
+  float* partial2;
   int64_t rows;
   int C, relu, nblk, rows_per_block;
   FastDiv div_hw;      // GV: rows per image
@@ -89,7 +92,9 @@ __device__ __forceinline__ void col_combine(float* smem, const float (&s0)[V], c
 
 // GV (the BatchNorm-backward modes): a is the gradient per image, [images][C], of a block output that only a global average
 // pool reads -- the same value at every pixel, so the tensor it would fill is neither written nor read
-template <class T, int V, int MODE, bool GV = false>
+// DUAL (from the bits): a block output's BatchNorm and that of its projection shortcut, which share dA and the decisions, in one pass
+// over them (at 4.2 M x 256 in bf16 two passes took 666 us each)
+template <class T, int V, int MODE, bool GV = false, bool DUAL = false>
 __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
   extern __shared__ float smem[];  // [2][TY][TX*V]
   const int CG = g.C / V;
@@ -99,9 +104,9 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
   const int cg = blockIdx.y * TX + tx;
   const bool active = cg < CG && ty < TY;
   const int c0 = cg * V;
-  float s0[V], s1[V];
+  float s0[V], s1[V], s2[V], mean2[V], rstd2[V];
 #pragma unroll
-  for (int i = 0; i < V; ++i) s0[i] = s1[i] = 0.f;
+  for (int i = 0; i < V; ++i) s0[i] = s1[i] = s2[i] = 0.f;
   constexpr bool BWD = MODE == RED_BN_BWD || MODE == RED_BN_BWD_AOUT || MODE == RED_BN_BWD_MASK;
   float mean[V], rstd[V], scale[V], shift[V];
   if (BWD && active) {
@@ -109,6 +114,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
     for (int i = 0; i < V; ++i) {
       mean[i] = g.stats[c0 + i]; rstd[i] = g.stats[g.C + c0 + i];
       if (MODE == RED_BN_BWD) { scale[i] = g.stats[2 * g.C + c0 + i]; shift[i] = g.stats[3 * g.C + c0 + i]; }
+      if (DUAL) { mean2[i] = g.stats2[c0 + i]; rstd2[i] = g.stats2[g.C + c0 + i]; }
     }
   }
   const int64_t r0 = (int64_t)blockIdx.x * g.rows_per_block;
@@ -122,6 +128,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
     // -2 % on the BatchNorm backward of the bottleneck networks; in the apply kernels, whose output the next kernel
     // reads, the same hint slowed that reader down by as much as it gained)
     // one row's contribution, from values already in registers
+    // (vo: DUAL the second z)
     auto accumulate = [&](const float (&va)[V], const float (&vz)[V], const float (&vo)[V], unsigned bits) {
       if (MODE == RED_STATS) {
 #pragma unroll
@@ -142,6 +149,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
           const float dy = on ? va[i] : 0.f;
           const float xh = (vz[i] - mean[i]) * rstd[i];
           s0[i] += dy; s1[i] = __fmaf_rn(dy, xh, s1[i]);
+          if (DUAL) s2[i] = __fmaf_rn(dy, (vo[i] - mean2[i]) * rstd2[i], s2[i]);
         }
       }
     };
@@ -162,6 +170,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
         if (BWD) {
           load_f32_nt<T, V>(z + off, vz[u]);
           if (MODE == RED_BN_BWD_MASK) mb[u] = mk[(r + (int64_t)u * TY) * CG + cg];
+          if (DUAL) load_f32_nt<T, V>(static_cast<const T*>(g.z2) + off, vo[u]);
           else if (MODE == RED_BN_BWD_AOUT) load_f32<T, V>(ao + off, vo[u]);
         }
         if (MODE == RED_BIAS_RELU) load_f32<T, V>(ao + off, vo[u]);
@@ -188,6 +197,7 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
         load_f32_nt<T, V>(z + off, vz);
         if (MODE == RED_BN_BWD_MASK) mb = mk[r * CG + cg];
         else if (MODE == RED_BN_BWD_AOUT) load_f32<T, V>(ao + off, vo);
+        if (DUAL) load_f32_nt<T, V>(static_cast<const T*>(g.z2) + off, vo);
       }
       if (MODE == RED_BIAS_RELU) {
         float d[V];
@@ -200,6 +210,10 @@ __global__ void __launch_bounds__(256) colreduce_kernel(RedArgs g) {
     }
   }
   col_combine<V>(smem, s0, s1, active, tx, ty, TX, TY, CG, g.C, g.partial);
+  if (DUAL) {
+    __syncthreads();
+    col_combine<V>(smem, s0, s2, active, tx, ty, TX, TY, CG, g.C, g.partial2);
+  }
 }
 
 template <class T, int MODE, bool GV>
@@ -213,6 +227,12 @@ static void launch_colreduce_t(hipStream_t st, const RedArgs& g0) {
   g.rows_per_block = ceil_div(g.rows, g.nblk);
   dim3 grid(g.nblk, ceil_div(CG, TX));
   const size_t sm = (size_t)2 * TY * TX * V * sizeof(float);
+  if constexpr (MODE == RED_BN_BWD_MASK) {
+    if (g.z2) {  // (the bits exist for whole groups only)
+      OSEQ_LAUNCH((colreduce_kernel<T, 16 / sizeof(T), MODE, GV, true>), grid, dim3(256), sm, st, g);
+      return;
+    }
+  }
   if (V == vmax) OSEQ_LAUNCH((colreduce_kernel<T, 16 / sizeof(T), MODE, GV>), grid, dim3(256), sm, st, g);
   else if constexpr (!GV) OSEQ_LAUNCH((colreduce_kernel<T, 1, MODE>), grid, dim3(256), sm, st, g);  // (GV: whole groups only)
 }
@@ -915,9 +935,10 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
 
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip, int per_image, bool summed) {
+                   void* dz, void* dskip, int per_image, bool summed, const BnBwdDual& dual) {
   RedArgs g{}; g.div_hw = make_fastdiv(per_image ? (uint32_t)per_image : 1u); g.a = da; g.z = z; g.aout = aout; g.mask = (const uint8_t*)mask; g.stats = stats; g.partial = ws; g.rows = rows;
   g.C = C; g.relu = relu; g.nblk = nblk;
+  g.z2 = dual.z; g.stats2 = dual.stats; g.partial2 = dual.ws;
   // the same choice of the ReLU decisions' source as the apply kernel below makes
   const int vmax = dt == DT_F32 ? 4 : 8;
   if (summed) {

@@ -52,9 +52,11 @@ void launch_bn_apply_pool(hipStream_t st, int dt, const void* z, const float* st
 // dz null: the sums, dgamma, dbeta and, behind the partial sums in ws, their means [2][C] only
 // ReLU decisions: from mask (bits as launch_bn_apply writes them, applied whatever relu says) if given, else from the
 // sign of aout if given, else redone from z when relu is set
+// dual (with a mask; C a multiple of 16 / element size): also the nblk rows of partial sums of a second BatchNorm with the same da and mask
+struct BnBwdDual { const void* z = nullptr; const float* stats = nullptr; float* ws = nullptr; };
 void launch_bn_bwd(hipStream_t st, int dt, const void* da, const void* z, const void* aout, const void* mask,
                    const float* stats, int64_t rows, int C, int relu, int nblk, float* ws, float* dgamma, float* dbeta,
-                   void* dz, void* dskip, int per_image, bool summed = false);
+                   void* dz, void* dskip, int per_image, bool summed = false, const BnBwdDual& dual = BnBwdDual());
 // summed: ws holds the nblk rows of partial sums already
 // the same where dy is the gradient of the 2x2 max-pool that follows the activation ([N][H/2][W/2][C]; H, W even): the
 // pool's own backward pass is not run

@@ -316,7 +316,7 @@ struct Scheduler {
                                  //              reader applies the mask to the block output's gradient itself), or -1
   std::vector<char> per_image;   // [LTensor] -> grad[t] (or image_grad[t]) holds one value per image and channel
   std::vector<int> fused_bwd;    // [FOp of a convolution] -> entry of the BatchNorm-backward sums that its S_CONV_BWD goes on from, or -1
-  std::vector<int> bn_sums, bn_sum_rows;  // [LTensor] -> Inst id of the BatchNorm-backward sums that came with grad[t], or -1, and their rows
+  std::vector<int> bn_sums, bn_sum_rows;  // [LTensor] -> slot of the BatchNorm-backward sums that came with grad[t], or -1, and their rows
   std::vector<int> image_grad;   // [LTensor] -> Inst id of the gradient per image of the global average pool's input, or -1
   explicit Scheduler(Plan& pl)
       : p(pl), cur(pl.tensors.size(), -1), grad(pl.tensors.size(), -1), stat_ws(pl.tensors.size(), -1),
@@ -348,12 +348,10 @@ struct Scheduler {
     return (int)p.insts.size() - 1;
   }
   int next_slot = 0;
-  int scratch_inst(uint64_t bytes) {
-    const int i = new_inst(-1, 0, false);
-    p.insts[i].scratch = next_slot;
-    next_slot ^= 1;
+  int sums_slot(uint64_t bytes) {
     p.scratch_bytes = std::max(p.scratch_bytes, align_up(bytes));
-    return i;
+    next_slot ^= 1;
+    return next_slot ^ 1;
   }
   int value_inst(int t) { return cur[t] = new_inst(t, p.tensors[t].bytes, true); }
   int grad_inst(int t) { return new_inst(t, p.tensors[t].bytes, false); }
@@ -575,7 +573,15 @@ struct Scheduler {
         }
         SOp& b = p.sched[at];
         b.rows = f.red_blocks;
-        if (bn_sums[f.out] >= 0 && variant == 0) { b.in[4] = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
+        // the BatchNorm of a projection shortcut has the same gradient and decisions (masked_skip_grad_ok): its sums in the same pass
+        const int shortcut = f.skip >= 0 && b.variant == 2 ? projection_of(fi) : -1;
+        if (shortcut >= 0 && gmask[f.skip] >= 0 && grad[f.skip] == b.in[0] && f.C % (16 / p.esize) == 0) {
+          const FOp& q = p.fops[shortcut];
+          b.in[5] = cur[q.x]; b.in[6] = cur[q.stats];
+          b.sums_out = bn_sums[f.skip] = sums_slot(((uint64_t)f.red_blocks * 2 + 2) * f.C * 4);
+          bn_sum_rows[f.skip] = f.red_blocks;
+        }
+        if (bn_sums[f.out] >= 0 && variant == 0) { b.sums_in = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
         else b.out[2] = new_inst(-1, ((uint64_t)f.red_blocks * 2 + 2) * f.C * 4, false);
         return true;
       }
@@ -589,14 +595,14 @@ struct Scheduler {
           SOp& s = push(S_CONV_BWD, fi, PH_BWD, seg);
           for (int i = 0; i < 4; ++i) s.in[i] = sums.in[i];
           s.variant = sums.variant; s.per_image = sums.per_image;
-          s.in[4] = sums.in[4] >= 0 ? sums.in[4] : sums.out[2];
+          s.in[4] = sums.out[2]; s.sums_in = sums.sums_in;
           s.in[5] = xin;
           if (from_z >= 0) s.in[6] = cur[p.fops[from_z].stats];
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
           s.rows = sums.rows;
           if (f.wgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.wgrad_splits * f.K * f.R * f.S * f.C * 4, false);
           if (sums_for >= 0) {
-            s.out[2] = bn_sums[f.x] = scratch_inst(((uint64_t)f.wgrad_splits * 2 + 2) * f.C * 4);
+            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.wgrad_splits * 2 + 2) * f.C * 4);
             bn_sum_rows[f.x] = f.wgrad_splits;
           }
           return true;
@@ -629,7 +635,7 @@ struct Scheduler {
           const int ap = f.dgrad_sums > 0 ? summed_apply(fi) : -1;
           if (ap >= 0) {
             s.in[3] = cur[p.fops[ap].x]; s.in[4] = cur[p.fops[ap].stats]; s.variant = p.fops[ap].relu;
-            s.out[2] = bn_sums[f.x] = scratch_inst(((uint64_t)f.dgrad_sums * 2 + 2) * f.C * 4);
+            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.dgrad_sums * 2 + 2) * f.C * 4);
             bn_sum_rows[f.x] = f.dgrad_sums;
           }
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1; per_image[f.x] = 0;
@@ -681,7 +687,7 @@ int launches_of(const SOp& op, const FOp& f) {
     case S_HEAD_FWD: return (f.head_ws > 0 ? 5 : 4) - (f.head_one ? 1 : 0);
     case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
-    case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.in[4] >= 0 ? 1 : 0);
+    case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.sums_in >= 0 ? 1 : 0);
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: case S_CONV_BWD: return f.wgrad_splits > 1 ? 2 : 1;
     case S_CONV_FWD: return f.fwd_splits > 1 ? 2 : 1;
@@ -760,7 +766,6 @@ bool build_schedule(Plan& p, uint64_t enough) {
     if (op.phase == PH_REPLAY) p.n_replay_launches += nl;
     for (int o : op.out) if (o >= 0) {
       Inst& t = p.insts[o];
-      if (t.scratch >= 0) continue;
       t.allocated = true;
       spans.push_back(Span{aligned(t.bytes), i, t.last_use, 0});
       span_inst.push_back(o);

@@ -83,7 +83,6 @@ struct Inst {
   bool fwd_value = false; // produced by a forward-kind operation
   bool held = false;      // checkpoint or kept for backward (counts as "saved")
   bool allocated = false;
-  int scratch = -1;       // >= 0: not in the activation arena but in that slot of the scratch memory behind the parameters
 };
 
 // One entry of the static schedule.
@@ -101,14 +100,19 @@ struct SOp {
                     // S_BN_APPLY with in[3] >= 0: in[2] is the z of the projection shortcut's BatchNorm, in[3] its
                     // statistics tensor (FOp::fold_skip)
                     // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
-                    // S_BN_BWD, in[4] its workspace, in[5] the convolution's input (the z of a folded BatchNorm with in[6]
+                    // S_BN_BWD, in[4] its workspace (or sums_in), in[5] the convolution's input (the z of a folded BatchNorm with in[6]
                     // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
-                    // S_DGRAD with out[2] >= 0: that receives the sums of the BatchNorm backward in front, whose z is in[3]
-                    // and statistics in[4]; variant: whether a ReLU follows that BatchNorm.  S_CONV_BWD likewise with out[2] (z and statistics are in[5] and in[6]).
-                    // S_BN_BWD with in[4] >= 0: that holds its sums, `rows` of them, and is its workspace
+                    // S_DGRAD with sums_out >= 0: it makes the sums of the BatchNorm backward in front, whose z is in[3] and
+                    // statistics in[4]; variant: whether a ReLU follows that BatchNorm.  S_CONV_BWD likewise (in[5], in[6]).
+                    // S_BN_BWD with sums_out >= 0: it also makes those of the projection shortcut's BatchNorm (z in[5],
+                    // statistics in[6])
                     // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; in[0]
                     // becomes the gradient in front of it, in place
                     // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
+  // Slot of the scratch memory that holds BatchNorm-backward sums: sums_out where this entry writes them for a later one (S_DGRAD,
+  // S_CONV_BWD, S_BN_BWD); sums_in the slot that an S_BN_BWD finds its sums in and uses as its workspace, and that an S_CONV_BWD
+  // reads the means from; -1: none
+  int sums_in = -1, sums_out = -1;
   int rows = 0;  // S_BN_BWD, S_CONV_BWD: rows of partial sums in the BatchNorm backward's workspace
   bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
@@ -141,8 +145,9 @@ struct Plan {
   // schedule
   std::vector<Inst> insts;
   std::vector<SOp> sched;
-  // BatchNorm-backward sums that come with a gradient live from one operation to the next or the one after: two slots of this
-  // many bytes, outside the activation arena, whose size they so leave alone
+  // BatchNorm-backward sums that come with a gradient: two slots of this many bytes behind the parameters, so that the activation
+  // arena is not larger for them.  Taken in turn: no more than one other set is made before a set is used up (a projection
+  // shortcut's, made with its block output's, waits while those of the block's last convolution's input are made).
   uint64_t scratch_bytes = 0;
   uint64_t arena_bytes = 0;       // high-water mark of the activation arena (aligned offsets)
   uint64_t peak_saved_bytes = 0;  // exact tensor sizes, no alignment
