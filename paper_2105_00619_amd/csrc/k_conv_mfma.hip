@@ -1114,7 +1114,11 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
   IGemmArgs a = a0;
   const int bk = Frag<X>::BK;
   a.kt_per_split = ceil_div(a.Kg / bk, splits);
-  const bool wide = a.Ng % 128 == 0 && !std::is_same_v<X, Split32>;  // (Split32: 128 x 128 tiles 207 us where 128 x 64 take 198)
+  // 64 channels per block where 128 leave CUs without one, or two in turn (us, 128 -> 64: inference at batch 16, 18 layers, 2 x 4 x 9
+  // blocks 10.4 -> 8.0, 32 x 1 x 2 11.8 -> 8.7), or where four classes of different depth share few (32 x 2 x 4 23.6 -> 20.7); a
+  // block per CU of equal depth keeps them (64 x 4 of 144 depth tiles 68.8 -> 74).
+  const int64_t blocks128 = (int64_t)ceil_div(a.M, IGEMM_BM) * (a.Ng / 128) * (a.cls ? 4 : splits);
+  const bool wide = a.Ng % 128 == 0 && !std::is_same_v<X, Split32> && blocks128 >= (a.cls ? 512 : 256);
   dim3 grid(ceil_div(a.M, IGEMM_BM), a.Ng / (wide ? 128 : 64), a.cls ? 4 : splits), block(256);  // cls: never split
   // A grid of at most one block per CU asks for more than half of a CU's LDS, so that no CU takes two blocks
   // while another idles.
