@@ -289,8 +289,8 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     }
   };
 
-  // fp32: a sub-tile from memory to its planes in LDS, half of the pieces of x at a time; addresses as in gload
-  auto stage32 = [&](int tile) {
+  // fp32: a sub-tile from memory to its planes in LDS, half of the pieces of x at a time; addresses as in gload; neg: dz negated
+  auto stage32 = [&](int tile, bool neg) {
     E* xs = lds;
     E* ds = lds + L::PL * XS;
     const int ci = tile % a.tiles_c, t2 = tile / a.tiles_c;
@@ -298,9 +298,10 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     const int yb = ri * TR - pad, xb = ci * TC - pad;
     const T* xt = x + (int64_t)nb * H * W * C + c0;
     const T* dt = dz + (int64_t)nb * P * Q * K + k0;
-    auto put = [&](E* at, int plane, const Chunk& c, bool ok) {
+    const uint32_t sign = neg ? 0x80000000u : 0u;
+    auto put = [&](E* at, int plane, const Chunk& c) {
       u32x2_t q[3];
-      split32(ok ? c : zero_chunk(), q);
+      split32(c, q);
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2_t*>(at + k * plane) = q[k];
     };
@@ -324,7 +325,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         const int sl = decltype(FIRST)::value + i;
         if (sl >= XSLOTS || sl * NTH >= NPOS * XCP) break;
         const int idx = sl * NTH + tid, pos = idx / XCP;
-        if (pos < NPOS) put(&xs[pos * PX + idx % XCP * EV], XS, xr[i], (xok >> i) & 1u);
+        if (pos < NPOS) put(&xs[pos * PX + idx % XCP * EV], XS, (xok >> i) & 1u ? xr[i] : zero_chunk());
       }
     };
     load_x(std::integral_constant<int, 0>{});
@@ -342,7 +343,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
 #pragma unroll
     for (int sl = 0; sl < DSLOTS; ++sl) {
       const int idx = sl * NTH + tid;
-      put(&ds[idx / DCP * PK + idx % DCP * EV], L::DS, dr[sl], (dok >> sl) & 1u);
+      put(&ds[idx / DCP * PK + idx % DCP * EV], L::DS, signed_chunk(dr[sl], (dok >> sl) & 1u, sign));
     }
     put_x(std::integral_constant<int, HALF>{});
   };
@@ -410,11 +411,26 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   };
 
   if constexpr (F32) {
-    for (int g = 0; g < nst; ++g) {
-      if (g > 0) __syncthreads();
-      stage32(t0 + g);
-      __syncthreads();
-      compute(0);
+    // (split32.h: half of the sum with dz negated)
+    bool neg = (bz & 1) != 0;
+    auto negate = [&]() {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[i][t] = -acc[i][t];
+    };
+    const int flip = wgrad_flip(nst);
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      const int g1 = half ? nst : flip;
+#pragma unroll 1
+      for (int g = half ? flip : 0; g < g1; ++g) {
+        if (g > 0) __syncthreads();
+        stage32(t0 + g, neg);
+        __syncthreads();
+        compute(0);
+      }
+      if (half == 0 || neg) { neg = !neg; negate(); }
     }
   } else {
     if (nst > 0) { gload(t0); sstore(0); }

@@ -363,6 +363,40 @@ def test_fp32_on_the_16bit_matrix_cores_is_fp32(c, cout, ksize, stride, h, w, b)
             assert float(d.norm() / q.grad.norm()) < 1.6e-6, name
 
 
+@pytest.mark.parametrize("c,cout,ksize,stride,h,w,b", [
+    (64, 64, 3, 1, 64, 64, 256), (64, 64, 3, 1, 61, 67, 257), (128, 128, 1, 1, 64, 64, 256), (64, 128, 3, 2, 65, 63, 500),
+    (2560, 2560, 1, 1, 16, 16, 64)])  # (the last: one pixel range)
+def test_fp32_weight_gradients_over_many_pixels_have_no_offset(c, cout, ksize, stride, h, w, b):
+    """The 16-bit MFMA truncates towards minus infinity; half of each sum is made with a negated operand, so that what is dropped
+    cancels.  Mean over the outputs of the signed error against float64, in units of their deviation.  Bar: the random errors of a
+    sum are below 3e-6 of that, their mean over 36 864 outputs or more below 3e-6 / 192 = 1.6e-8; four times that for errors that
+    outputs share (the softmax gradient's).  Without the negation: -3e-6 over a million pixels, -5e-7 over 16 384."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    p, q = (h - 1) // stride + 1, (w - 1) // stride + 1
+    units = [W.conv(c, cout, ksize, stride, bn=False, relu=False, bias=False), W.flatten_linear_ce(cout, 10)]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w0 = torch.randn((cout, ksize, ksize, c), generator=g, device="cuda") * (1.0 / (ksize * ksize * c)) ** 0.5
+    w1 = torch.randn((10, p * q * cout), generator=g, device="cuda") * (1.0 / (p * q * cout)) ** 0.5
+    x = torch.randn((b, h, w, c), generator=g, device="cuda")
+    y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=b, height=h, width=w, channels=c, num_classes=10)
+    t.set_params(torch.cat([w0.flatten(), w1.flatten(), torch.zeros(10, device="cuda")]))
+    grads = torch.empty(t.param_count, device="cuda")
+    t.step(x, y, 0.0, grads=grads)
+    t.close()
+    x64 = x.double()
+    d = torch.softmax(_layer64(x64, w0.double(), stride).reshape(b, -1) @ w1.double().t(), 1)
+    d[torch.arange(b, device="cuda"), y.long()] -= 1.0
+    dz = (d / b @ w1.double()).reshape(-1, cout)
+    x64 = torch.nn.functional.pad(x64, (0, 0, ksize // 2, ksize // 2, ksize // 2, ksize // 2))
+    want = torch.stack([dz.t() @ x64[:, i:i + (p - 1) * stride + 1:stride, j:j + (q - 1) * stride + 1:stride, :].reshape(-1, c)
+                        for i in range(ksize) for j in range(ksize)], 1).reshape(w0.shape)
+    err = grads[:w0.numel()].view(w0.shape).double() - want
+    assert abs(float(err.mean() / want.pow(2).mean().sqrt())) < 6.4e-8
+    assert float(err.norm() / want.norm()) < 3e-6
+
+
 @pytest.mark.parametrize("ksize,stride", [(3, 1), (3, 2), (1, 1)])
 def test_fp32_infinities_and_nans_come_out_as_from_fp32(ksize, stride):
     """A pixel with an infinity, one with a NaN and one beyond the largest bf16, in a layer that splits its fp32 operands."""
