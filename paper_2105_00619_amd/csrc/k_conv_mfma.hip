@@ -139,15 +139,34 @@ __device__ __forceinline__ bool sums_not_finite(v16f (&acc)[2][MI][NI]) {
 }
 template <int MI, int NI>
 __device__ __forceinline__ bool sums_not_finite(v16f (&)[1][MI][NI]) { return false; }  // (16-bit: not asked)
-// fp32: the sums of a pass over `rows` block rows in LDS that are not finite, again as one chain of multiply-adds each.
-// chain(row, col): the sum of block row `row` and channel n0 + col, or 0 for a row that is not stored.
-template <int BN, class Chain>
-__device__ __forceinline__ void redo_not_finite(float* ep, int rows, int tid, Chain chain) {
-  for (int i = tid; i < rows * BN; i += 256) {
-    const int row = i / BN, col = i - row * BN;
-    float& v = ep[row * (BN + 4) + col];
-    if (!(__fmaf_rn(v, 0.f, 0.f) == 0.f)) v = chain(row, col);
+// a lane's products of one depth tile on the fp32 instruction; a, b: its first row of each operand, whose rows lie 32 * pitch apart
+template <int MI, int NI>
+__device__ __forceinline__ void mma_fp32(const float* a, const float* b, int (&arow)[MI], int bstep, v16f (&acc)[MI][NI]) {
+  Frag<float> fa[MI], fb[NI];
+#pragma unroll
+  for (int ph = 0; ph < 2; ++ph) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) fa[i].load(a + arow[i], ph);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fb[j].load(b + j * bstep, ph);
   }
+#pragma unroll
+  for (int ph = 0; ph < 2; ++ph)
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) Frag<float>::mma(fa[i], fb[j], acc[i][j], ph, st);
+}
+template <int MI, int NI>
+__device__ __forceinline__ void clear_sums(v16f (&acc)[MI][NI]) {
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 }
 // Within a depth tile the two lane groups (lanes 0-31, 32-63) own disjoint halves of the depth range and every MFMA
 // pairs the same depth indices of A and B, so any assignment of depth indices to (lane group, step) gives the same sum.
@@ -358,6 +377,30 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
     }
   }
 
+  if constexpr (S32) {
+    if (__syncthreads_or(sums_not_finite(acc))) {  // the tile again on the fp32 instruction (split32.h)
+      constexpr int FP = Frag<float>::PITCH;
+      float* fl = reinterpret_cast<float*>(smem_raw);
+      int arow[MI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) arow[i] = (wm * (BM / 2) + i * 32 + l32) * FP + Frag<float>::lane_off(g);
+      clear_sums(acc[0]);
+      tapi = kt0 * BK / srcC; c0 = kt0 * BK - tapi * srcC;
+      next_tap();
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) {
+        gload(IC<0>{});
+#pragma unroll
+        for (int i = 0; i < A_CH; ++i) Frag<float>::put(&fl[(row0 + i * 64) * FP], vec, ra[0][i], !((okm[0] >> i) & 1u));
+#pragma unroll
+        for (int i = 0; i < B_CH; ++i) Frag<float>::put(&fl[(BM + row0 + i * 64) * FP], vec, rb[0][i], false);
+        __syncthreads();
+        mma_fp32(fl, fl + (BM + wn * (BN / 2) + l32) * FP + Frag<float>::lane_off(g), arow, 32 * FP, acc[0]);
+        __syncthreads();
+      }
+    }
+  }
+
   // epilogue through LDS, one half of the rows (the two wavefronts with the same wm) at a time, as fp32 [row][BN+4];
   // the store half (bias / addend / ReLU, rounding, stores, BatchNorm sums) is shared with the other kernels
   {
@@ -365,32 +408,6 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
     constexpr int EP_PITCH = BN + 4;
     constexpr int HR = BM / 2;  // rows per pass
     constexpr bool STAT = MODE == IG_FWD && !SPLIT;
-    const bool redo = S32 && __syncthreads_or(sums_not_finite(acc));
-    // the sum over this block's depth tiles, tap by tap and channel by channel
-    auto chain = [&](int grow, int col) -> float {
-      if (grow >= a.M) return 0.f;
-      int pb = grow % a.dstW;
-      const int t = grow / a.dstW;
-      int pa = t % a.dstH;
-      const int pn = t / a.dstH;
-      if (a.cls) { pa = 2 * pa + cph; pb = 2 * pb + cpw; }
-      const T* w = wmat + (int64_t)(n0 + col) * (a.R * a.S * srcC);
-      float sum = 0.f;
-      for (int kt = kt0; kt < kt1 && sum == sum; ++kt) {  // (a NaN stays one)
-        const int ti = kt * BK / srcC, c = kt * BK - ti * srcC;
-        const int tp = a.cls ? (ctaps >> (8 * (ti & 3))) & 0xff : ti;
-        const int r = tp / S_, s2 = tp - r * S_;
-        int y = MODE != IG_DGRAD ? pa * stride + r - pad : pa + pad - r, x = MODE != IG_DGRAD ? pb * stride + s2 - pad : pb + pad - s2;
-        if (MODE == IG_DGRAD && stride == 2) {
-          if ((y | x) & 1) continue;
-          y >>= 1; x >>= 1;
-        }
-        if (y < 0 || y >= srcH || x < 0 || x >= srcW) continue;
-        const T* p = src + (((int64_t)pn * srcH + y) * srcW + x) * srcC + c;
-        for (int k = 0; k < BK; ++k) sum = __fmaf_rn(to_f32(p[k]), to_f32(w[tp * srcC + c + k]), sum);
-      }
-      return sum;
-    };
     float ss[8], qq[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) { ss[k] = 0.f; qq[k] = 0.f; }
@@ -407,10 +424,6 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
               ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + jn * 32 + l32] = acc[0][i][jn][e];
       }
       __syncthreads();
-      if (S32 && redo) {
-        redo_not_finite<BN>(ep, HR, tid, [&](int row, int col) { return chain(m0 + u * HR + row, col); });
-        __syncthreads();
-      }
       auto rowoff = [&](int row) -> int64_t {
         const int grow = m0 + u * HR + row;
         if (grow >= a.M) return -1;
@@ -734,6 +747,36 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
   for (int chunk = cb; chunk + 1 < ce; ++chunk) chunk_body(IC<0>{}, chunk);
   chunk_body(IC<1>{}, ce - 1);
 
+  if constexpr (S32) {
+    if (__syncthreads_or(sums_not_finite(acc))) {  // the tile again on the fp32 instruction (split32.h), a position's values
+      constexpr int FP = PITCH / 2;                // in the place of its planes
+      float* fpatch = reinterpret_cast<float*>(patch);
+      float* fB = reinterpret_cast<float*>(Bs);
+      const float* fb = fB + (wn * (BN / 2) + l32) * FP + Frag<float>::lane_off(g);
+      clear_sums(acc[0]);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) arow[i] = (arow[i] - Frag<X>::lane_off(g)) / 2 + Frag<float>::lane_off(g);
+#pragma unroll 1
+      for (int chunk = cb; chunk < ce; ++chunk) {
+#pragma unroll
+        for (int sl = 0; sl < NSLOT; ++sl) {
+          const Chunk c = patch_load(sl, chunk);
+          if ((pstore >> sl) & 1u) Frag<float>::put(fpatch + pdst[sl] / 2, tid & 3, c, !((pvalid >> sl) & 1u));
+        }
+#pragma unroll 1
+        for (int t = 0; t < 9; ++t) {
+          const T* wp = wrow + (flip ? 8 - t : t) * srcC + chunk * CCE;
+#pragma unroll
+          for (int i = 0; i < B_CH; ++i)
+            Frag<float>::put(fB + (brow0 + i * 64) * FP, bvec, *reinterpret_cast<const Chunk*>(wp + (int64_t)(i * 64) * Kg), false);
+          __syncthreads();
+          mma_fp32(fpatch + (t / 3 * RPE + t % 3 * PITCH) / 2, fb, arow, 32 * FP, acc[0]);
+          __syncthreads();
+        }
+      }
+    }
+  }
+
   // ---- epilogue ---------------------------------------------------------------------------------------------------
   // The accumulators go through LDS (the patch buffers are free now), the rows of one wavefront pair at a time, as
   // fp32 [row][BN + 4]; the store half (bias / addend / ReLU, rounding, stores of whole rows, BatchNorm sums of the
@@ -742,24 +785,6 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
     float* ep = reinterpret_cast<float*>(smem_raw);
     constexpr int EP_PITCH = BN + 4;
     constexpr int HR = 32 * MI;  // rows per pass
-    const bool redo = S32 && __syncthreads_or(sums_not_finite(acc));
-    auto chain = [&](int row, int col) -> float {  // the sum over this block's channels, tap by tap
-      const int64_t o = out_off[row];
-      if (o < 0) return 0.f;
-      const int64_t pix = o / a.Ng;
-      const int q = (int)(pix % a.dstW), p = (int)(pix / a.dstW % a.dstH);
-      const int64_t n = pix / a.dstW / a.dstH;
-      const T* w = wmat + (int64_t)(n0c + col) * Kg;
-      float sum = 0.f;
-      for (int t = 0; t < 9 && sum == sum; ++t) {  // (a NaN stays one)
-        const int y = p - a.pad + t / 3, x = q - a.pad + t % 3;
-        if (y < 0 || y >= a.srcH || x < 0 || x >= a.srcW) continue;
-        const T* px = src + ((n * a.srcH + y) * a.srcW + x) * srcC;
-        const T* wt = w + (flip ? 8 - t : t) * srcC;
-        for (int c = cb * CCE; c < ce * CCE; ++c) sum = __fmaf_rn(to_f32(px[c]), to_f32(wt[c]), sum);
-      }
-      return sum;
-    };
     float ss[8], qq[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) { ss[k] = 0.f; qq[k] = 0.f; }
@@ -776,10 +801,6 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
               ep[(i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * EP_PITCH + wn * (BN / 2) + j * 32 + l32] = acc[0][i][j][e];
       }
       __syncthreads();
-      if (S32 && redo) {
-        redo_not_finite<BN>(ep, HR, tid, [&](int row, int col) { return chain(u * HR + row, col); });
-        __syncthreads();
-      }
       auto rowoff = [&](int row) -> int64_t { return out_off[u * HR + row]; };
       if (partial)
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
@@ -1664,6 +1685,50 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
   }
 
   if (F32 && !odd) negate();  // (from tile `flip` on the sums are those of -dz where the range's first ones are of dz)
+  if constexpr (F32) {
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[i][j][e], 0.f, sum);
+    if (__syncthreads_or(!(sum == 0.f))) {  // the tile again as chains of fp32 multiply-adds (split32.h)
+      float* fa_ = reinterpret_cast<float*>(wgrad_smem);
+      float* fb_ = fa_ + DEPTH * BM;
+      clear_sums(acc);
+#pragma unroll 1
+      for (int t = 0; t < n; ++t) {
+        gload(IC<0>{}, IC<1>{}, t);
+#pragma unroll
+        for (int i = 0; i < A_CH32; ++i) *reinterpret_cast<Chunk*>(fa_ + (tid + i * NT) * EV) = ra[0][i];  // [pixel][BM]
+#pragma unroll
+        for (int i = 0; i < B_CH32; ++i) *reinterpret_cast<Chunk*>(fb_ + (tid + i * NT) * EV) = rb[0][i];
+        __syncthreads();
+#pragma unroll 1
+        for (int px = 0; px < DEPTH; ++px) {  // (pixels that do not count are left out: zero times infinity is none)
+          const int m = mbeg + t * DEPTH + px;
+          if (m >= mend) break;
+          const uint32_t n_ = divPQ.div((uint32_t)m), rem = (uint32_t)m - n_ * divPQ.d;
+          const uint32_t p_ = divQ.div(rem);
+          int64_t off;
+          if (!tap_offset((int)n_, (int)p_, (int)(rem - p_ * divQ.d), off)) continue;
+          float xv[NI];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) xv[j] = fb_[px * BN + wn * WTN + j * 32 + l32];
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const float d = fa_[px * BM + wm * WTM + i * 32 + 8 * (e >> 2) + 4 * g + (e & 3)];
+#pragma unroll
+              for (int j = 0; j < NI; ++j) acc[i][j][e] = __fmaf_rn(d, xv[j], acc[i][j][e]);
+            }
+        }
+        __syncthreads();
+      }
+    }
+  }
   const int64_t outputs = (int64_t)K * a.R * a.S * C;
   float* dst = out + (int64_t)bz * outputs;
 #pragma unroll
@@ -1677,30 +1742,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
         dst[((int64_t)k * a.R * a.S + tap) * C + c] = acc[i][j][e];
       }
     }
-  if constexpr (F32) {  // sums that are not finite, again as fp32 chains (split32.h)
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[i][j][e], 0.f, sum);
-    __threadfence_block();
-    if (!__syncthreads_or(!(sum == 0.f))) return;
-    for (int i = tid; i < BM * BN; i += NT) {
-      const int k = k0 + i / BN, c = c0 + i % BN;
-      float& v = dst[((int64_t)k * a.R * a.S + tap) * C + c];
-      if (__fmaf_rn(v, 0.f, 0.f) == 0.f) continue;
-      float t = 0.f;
-      for (int m = mbeg; m < mend && t == t; ++m) {  // (a NaN stays one)
-        const uint32_t n_ = divPQ.div((uint32_t)m), rem = (uint32_t)m - n_ * divPQ.d;
-        const uint32_t p_ = divQ.div(rem), q_ = rem - p_ * divQ.d;
-        int64_t off;
-        if (tap_offset((int)n_, (int)p_, (int)q_, off)) t = __fmaf_rn(dz[(int64_t)m * K + k], x[off + c], t);
-      }
-      v = t;
-    }
-  }
 }
 
 bool conv_mfma_wgrad_ok(int dt, const ConvGeom& g) {

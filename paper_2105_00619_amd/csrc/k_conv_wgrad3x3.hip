@@ -444,6 +444,62 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     if (nst > 0) compute((nst - 1) & 1);
   }
 
+  if constexpr (F32) {
+    static_assert(!F32 || MI == 1, "one output-channel tile per wavefront");
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[0][t][e], 0.f, sum);
+    if (__syncthreads_or(!(sum == 0.f))) {  // the tile again as chains of fp32 multiply-adds (split32.h)
+      float* fx = reinterpret_cast<float*>(smem_raw);  // [NPOS][64]
+      float* fd = fx + NPOS * 64;                      // [TP][BMK]
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[0][t][e] = 0.f;
+#pragma unroll 1
+      for (int tile = t0; tile < t1; ++tile) {
+        const int ci = tile % a.tiles_c, t2 = tile / a.tiles_c;
+        const int ri = t2 % a.tiles_r, nb = t2 / a.tiles_r * TI;
+        for (int idx = tid; idx < NPOS * XCP; idx += NTH) {
+          const int pos = idx / XCP, ti = pos / (a.SR * SC), rr = pos - ti * (a.SR * SC);
+          const int n = nb + ti, y = ri * TR - pad + rr / SC, xx = ci * TC - pad + rr % SC;
+          const bool ok = n < N && y >= 0 && y < H && xx >= 0 && xx < W;
+          const int64_t off = ok ? (((int64_t)n * H + y) * W + xx) * C : 0;
+          *reinterpret_cast<Chunk*>(fx + idx * EV) = *reinterpret_cast<const Chunk*>(x + off + c0 + idx % XCP * EV);
+        }
+        for (int idx = tid; idx < TP * DCP; idx += NTH) {
+          const int m = idx / DCP, ti = m / (TR * TC), rr = m - ti * (TR * TC);
+          const int n = nb + ti, p = ri * TR + rr / TC, q = ci * TC + rr % TC;
+          const bool ok = n < N && p < P && q < Q;
+          const int64_t off = ok ? (((int64_t)n * P + p) * Q + q) * K : 0;
+          *reinterpret_cast<Chunk*>(fd + idx * EV) = *reinterpret_cast<const Chunk*>(dz + off + k0 + idx % DCP * EV);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int m = 0; m < TP; ++m) {  // (pixels and taps that do not count are left out: zero times infinity is none)
+          const int ti = m / (TR * TC), rr = m - ti * (TR * TC), tr = rr / TC, tc = rr - tr * TC;
+          const int p = ri * TR + tr, q = ci * TC + tc;
+          if (nb + ti >= N || p >= P || q >= Q) continue;
+          const float* xv = fx + ((ti * a.SR + tr) * SC + tc) * 64 + wn * 32 + l32;
+          float d[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) d[e] = fd[m * BMK + wm * 32 + 8 * (e >> 2) + 4 * hg + (e & 3)];
+#pragma unroll
+          for (int tap = 0; tap < 9; ++tap) {
+            const int y = p + tap / 3 - pad, xx = q + tap % 3 - pad;
+            if (y < 0 || y >= H || xx < 0 || xx >= W) continue;
+            const float v = xv[(tap / 3 * SC + tap % 3) * 64];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[0][tap][e] = __fmaf_rn(d[e], v, acc[0][tap][e]);
+          }
+        }
+        __syncthreads();
+      }
+    }
+  }
+
   const int64_t outputs = (int64_t)K * 9 * C;
   float* dst = out + (int64_t)bz * outputs;
 #pragma unroll
@@ -457,34 +513,6 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         dst[((int64_t)k * 9 + tap) * C + c] = acc[i][tap][e];
       }
     }
-  if constexpr (F32) {  // sums that are not finite, again as fp32 chains (split32.h)
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum = __fmaf_rn(acc[i][tap][e], 0.f, sum);
-    __threadfence_block();
-    if (!__syncthreads_or(!(sum == 0.f))) return;
-    for (int i = tid; i < BMK * 9 * 64; i += NTH) {
-      const int k = k0 + i / (9 * 64), tap = i / 64 % 9, c = c0 + i % 64;
-      float& v = dst[((int64_t)k * 9 + tap) * C + c];
-      if (__fmaf_rn(v, 0.f, 0.f) == 0.f) continue;
-      float t = 0.f;
-      for (int tile = t0; tile < t1 && t == t; ++tile) {  // (a NaN stays one)
-        const int ci = tile % a.tiles_c, t2 = tile / a.tiles_c;
-        const int ri = t2 % a.tiles_r, nb = t2 / a.tiles_r * TI;
-        for (int m = 0; m < TP && t == t; ++m) {
-          const int n = nb + m / (TR * TC), p = ri * TR + m / TC % TR, q = ci * TC + m % TC;
-          const int y = p + tap / 3 - pad, xx = q + tap % 3 - pad;
-          if (n < N && p < P && q < Q && y >= 0 && y < H && xx >= 0 && xx < W)
-            t = __fmaf_rn(dz[(((int64_t)n * P + p) * Q + q) * K + k], x[(((int64_t)n * H + y) * W + xx) * C + c], t);
-        }
-      }
-      v = t;
-    }
-  }
 }
 
 // sub-tile geometry for a (P x Q) output grid: up to `cap` pixels and `maxpos` staged positions

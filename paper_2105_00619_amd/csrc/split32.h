@@ -18,8 +18,10 @@
 // 3.5e-6 -> 1.0e-6 and 1.3e-5 -> 1.9e-6, on the fp32 MFMA 1.2e-6 and 2.3e-6; in the same time).
 //
 // Not finite: a value beyond the largest bf16, an infinity or a NaN makes planes that are not finite, and every sum with it
-// a NaN.  The kernels look for sums that are not finite when they store a tile and compute those again as fp32 chains of
-// multiply-adds, so that infinities and NaNs come out as from fp32 arithmetic.
+// a NaN.  A block that finds such a sum when its tile is done makes the tile again -- forward and data gradient on the fp32 MFMA,
+// weight gradients as chains of multiply-adds, pixel by pixel -- so that infinities and NaNs come out as from fp32 arithmetic.
+// (Two 64 -> 64 layers at 1 048 576 pixels, one infinity in the images: 7.1 ms a step, 2.5 without it.  As a chain per such output,
+// one thread each, it was 95 ms.)
 #pragma once
 #include "dev_common.h"
 

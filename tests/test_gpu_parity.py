@@ -421,6 +421,77 @@ def test_fp32_infinities_and_nans_come_out_as_from_fp32(ksize, stride):
     assert bool(((got - want).abs()[ok] <= 1e-5 * (want.abs()[ok] + 1.0)).all())
 
 
+@pytest.mark.parametrize("ksize,stride,h,w,b", [(3, 1, 61, 35, 9), (3, 2, 62, 35, 9), (1, 1, 61, 35, 9), (3, 1, 8, 8, 32)])
+@pytest.mark.parametrize("where", ["image", "weights"])
+def test_fp32_gradients_of_values_beyond_bf16(where, ksize, stride, h, w, b):
+    """Values that a float holds and bf16 does not, in the operands of a weight gradient (one pixel, at the map's last corner) and
+    of a data gradient (one weight): finite results, as from fp32.  Bars: as of the infinities' test, per row of a tensor."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    c, cout = 64, 128
+    units = [W.conv(c, c, 1, bn=False, relu=False, bias=False), W.conv(c, cout, ksize, stride, bn=False, relu=False, bias=False),
+             W.gap_linear_ce(cout, 10)]
+    g = torch.Generator(device="cuda").manual_seed(8)
+    w1 = torch.randn((c, 1, 1, c), generator=g, device="cuda") * 0.1
+    w2 = torch.randn((cout, ksize, ksize, c), generator=g, device="cuda") * 0.05
+    x = torch.randn((b, h, w, c), generator=g, device="cuda")
+    if where == "weights":  # channel 5 between the layers is tiny, one of the weights that it meets huge
+        w1[5] *= 1e-37
+        w2[7, ksize // 2, ksize // 2, 5] = 3.4e38
+    else:                   # channel 5 is the image's own, its weights are tiny
+        w1.zero_()
+        w1[torch.arange(c), 0, 0, torch.arange(c)] = 1.0
+        w2[:, :, :, 5] *= 1e-37
+        x[b - 1, h - 1, w - 1, 5] = 3.4e38
+    head = torch.randn((10, cout), generator=g, device="cuda") * 0.1
+    y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=b, height=h, width=w, channels=c, num_classes=10)
+    t.set_params(torch.cat([w1.flatten(), w2.flatten(), head.flatten(), torch.zeros(10, device="cuda")]))
+    grads = torch.empty(t.param_count, device="cuda")
+    assert not t.step(x, y, 0.0, grads=grads)["skipped"]
+    t.close()
+    p = [v.double().requires_grad_(True) for v in (w1, w2)]
+    logits = _layer64(_layer64(x.double(), p[0], 1), p[1], stride).mean((1, 2)) @ head.double().t()
+    torch.nn.functional.cross_entropy(logits, y.long()).backward()
+    at = 0
+    for v in p:
+        got, want = grads[at:at + v.numel()].double().view(v.shape), v.grad
+        at += v.numel()
+        rows = range(v.shape[3])  # of one input channel: the huge one has a scale of its own
+        for i in (4, 5, 6) if where == "image" else rows[:3]:
+            d, e = got[..., i] - want[..., i], want[..., i]
+            if where == "weights" and v is p[0]:
+                d, e = d[[4, 6]], e[[4, 6]]  # the others' scale; row 5 below
+            assert float(d.norm()) <= 1e-5 * float(e.norm()), i
+        if where == "weights" and v is p[0]:
+            assert float(want[5].abs().max()) > 1e30 and float((got[5] - want[5]).norm()) <= 1e-5 * float(want[5].norm())
+
+
+def test_fp32_step_with_an_infinity_takes_no_longer_than_a_few():
+    """Tiles with sums that are not finite are made twice: a step with one infinity in 1 M pixels took 38 plain ones, now 2.9."""
+    import time
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(64, 64, bn=False), W.conv(64, 64, bn=False), W.gap_linear_ce(64, 10)]
+    t = SeqTrainer(units, k_segments=1, precision=W.FP32, batch=4, height=512, width=512, channels=64, num_classes=10)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    t.set_params(torch.randn(t.param_count, generator=g, device="cuda") * 0.05)
+    x = torch.randn((4, 512, 512, 64), generator=g, device="cuda")
+    y, best = torch.zeros(4, device="cuda", dtype=torch.int32), []
+    for _ in range(2):
+        took = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            r = t.step(x, y, 0.0)
+            took.append(time.perf_counter() - t0)
+        best.append(min(took))
+        assert r["skipped"] == (len(best) == 2)
+        x[2, 256, 256, 0] = float("inf")
+    t.close()
+    assert best[1] < 8 * best[0]
+
+
 def _grads64(layers, blocks, params, x, y):
     """Gradients in float64 of a run of convolutions + BatchNorm (blocks None; the last argument of a layer: ReLU) or of
     bottleneck blocks given as (channels in, channels out), a global average pool and a linear layer; params in flat order."""
