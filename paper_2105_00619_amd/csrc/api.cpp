@@ -104,7 +104,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
       }
     for (FOp& f : p.fops)
       if (f.kind == F_HEAD) {
-        f.head_one = head_loss_in_one(f.N);
+        f.head_one = head_loss_in_one(f.N, f.classes);
         f.head_ws_in_x = !p.tensors[f.x].needs_grad;
         f.head_ws = head_ws_floats(cfg->precision, f.N, f.H * f.W, f.C, f.gap, f.feat_dim, f.classes, f.head_ws_in_x);
       }

@@ -11,7 +11,10 @@ namespace oseq {
 typedef __attribute__((ext_vector_type(16))) float head_v16f;
 
 constexpr int HEAD_ONE_BLOCK = 64;
-bool head_loss_in_one(int N) { return N <= HEAD_ONE_BLOCK; }
+// Samples behind the first sixteen follow one another in that block, and it is one CU's: a step's time, two launches -> one, us, with 16
+// samples and 1000 / 4096 / 32 768 classes -3, -3, +24; 32 and 400 / 1000: -1, +10; 48 and 200 / 400: -2, +1; 64 and 200 / 400 /
+// 1000: -2, +9, +34.
+bool head_loss_in_one(int N, int J) { return N <= HEAD_ONE_BLOCK && J <= 4096 && (int64_t)(N - 16) * J <= 8192; }
 
 // flatten: feat[n][f] = x[n][f] in fp32, V features per thread
 template <class T, int V>
@@ -484,7 +487,7 @@ void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
                      float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply) {
   launch_head_logits(st, dt, x, N, HW, C, gap, F, J, w, b, feat, logits, ws, apply);
-  if (head_loss_in_one(N)) {
+  if (head_loss_in_one(N, J)) {
     OSEQ_LAUNCH(softmax_ce_kernel<true>, dim3(1), dim3(1024), 0, st, logits, y, loss_n, dlogits, N, J, gscale, flags, loss_out);
     return;
   }

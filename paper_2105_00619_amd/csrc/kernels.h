@@ -72,8 +72,8 @@ void launch_maxpool_bwd(hipStream_t st, int dt, const void* x, const void* dy, v
 // The BatchNorm apply whose output only the head's global average pool reads, done by the pooling kernel (x is then its z): the
 // output itself is never written.  As launch_bn_apply; C a multiple of 16 / element size
 struct HeadApply { const float* stats; const void* skip; const float* skip_stats; void* mask; int relu; };
-// at most 64 samples: their losses and the mean in one launch
-bool head_loss_in_one(int N);
+// few samples and classes: the losses and their mean in one launch
+bool head_loss_in_one(int N, int J);
 void launch_head_fwd(hipStream_t st, int dt, const void* x, int N, int HW, int C, int gap, int F, int J, const float* w,
                      const float* b, const int32_t* y, float gscale, float* feat, float* logits, float* dlogits,
                      float* loss_n, float* loss_out, int* flags, float* ws, const HeadApply* apply = nullptr);

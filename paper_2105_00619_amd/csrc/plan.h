@@ -52,7 +52,7 @@ struct FOp {
   int64_t rs_off = -1;       // element offset of (running mean, running var) in the running-stat block
   int gap = 0, feat_dim = 0, classes = 0;
   int64_t head_ws = 0;       // floats of workspace of the head's forward pass; launches_of counts its extra launch
-  bool head_one = false;     // its losses and their mean are one launch (few samples)
+  bool head_one = false;     // its losses and their mean are one launch (few samples and classes)
   bool head_ws_in_x = false; // it lies in the head's input, which is the network's own and read for the last time by the first
                              // of the head's kernels
   int dgrad_sums = 0;        // F_CONV: row blocks over which the data gradient can sum for the BatchNorm backward in front of it, or 0

@@ -1338,6 +1338,16 @@ def test_inference_at_benchmark_size_matches_oracle():
     assert np.linalg.norm(r["running"] - run) <= 1e-5 * np.linalg.norm(run)
 
 
+@pytest.mark.parametrize("b,classes", [(16, 4096), (16, 4097), (32, 512), (32, 513), (64, 170), (64, 171), (3, 1000)])
+def test_losses_on_either_side_of_one_launch(b, classes):
+    units = [W.conv(8, 8, 1), W.gap_linear_ce(8, classes)]
+    p, x, y = _inputs(units, b, 4, 4, classes, channels=8)
+    r, _ = gpu_step(units, p, x, y, precision=W.FP32, k=1, classes=classes)
+    loss, g = oracle_step(units, p, x, y)
+    assert abs(r["loss"] - loss) <= 1e-5 * loss  # fp32 logits of 8 features, one rounding of the mean
+    assert_parity(units, 4, 4, r["grads"], g, TOL[W.FP32])
+
+
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16])
 @pytest.mark.parametrize("b", [211, 7])  # 1 053 945 values: groups of eight and one more; few: one per thread
 def test_images_at_any_address(precision, b):

@@ -153,6 +153,15 @@ def test_pool_is_computed_by_the_kernels_of_the_batchnorm_in_front_of_it():
     assert (q.n_launches, q.n_replay_launches) == (100, 11)
 
 
+def test_losses_of_many_classes_are_not_one_blocks_work():
+    def launches(batch, classes):
+        return SeqPlan([W.conv(8, 8, ksize=1), W.gap_linear_ce(8, classes)], k_segments=1, precision=W.FP32, batch=batch, height=4,
+                       width=4, channels=8, num_classes=classes).n_launches
+    # the losses and their mean are one launch where a wavefront's samples and classes are few
+    for batch, few, many in ((16, 4096, 4097), (32, 512, 513), (64, 170, 171)):
+        assert launches(batch, few) + 1 == launches(batch, many) == launches(65, 10)
+
+
 def test_peak_shrinks_with_segments_and_plan_is_reproducible():
     p1, p4, p4b = _plan(2, k_segments=1), _plan(2, k_segments=4, plan_mode=0), _plan(2, k_segments=4, plan_mode=0)
     assert p4.boundaries == [3, 6, 9] == p4b.boundaries
