@@ -31,8 +31,8 @@ struct optorch_seq {
   float scale = 1.f, scale_init = 1.f, growth = 2.f, backoff = 0.5f, eps = 1e-5f, bn_mom = 0.1f, momentum = 0.f;
   int growth_interval = 0, clean = 0;
   bool dynamic_scale = false;
-  float* host_rb_dev = nullptr;  // the same for the device
   float* host_rb = nullptr;  // pinned read-back buffer: loss + flags
+  float* host_rb_dev = nullptr;  // its address for the GPU of the last bind
   std::vector<EvalJob> eval_jobs;            // every BatchNorm, for the inference-mode scale / shift table
   std::vector<TransposeJob> transpose_jobs;  // layers whose data gradient reads a transposed weight copy
   mutable std::string err;
@@ -264,9 +264,12 @@ extern "C" int optorch_seq_bind(optorch_seq_t* h, void* param_arena_dev, uint64_
   if (!h->host_rb) {
     hipError_t e = hipHostMalloc((void**)&h->host_rb, 256, hipHostMallocDefault);
     if (e != hipSuccess) return hip_fail(h, e, "hipHostMalloc");
-    e = hipHostGetDevicePointer((void**)&h->host_rb_dev, h->host_rb, 0);
-    if (e != hipSuccess) return hip_fail(h, e, "hipHostGetDevicePointer");
   }
+  // (on every bind: the handle may be bound on another GPU, or again after this failed)
+  void* rb_dev = nullptr;
+  const hipError_t e = hipHostGetDevicePointer(&rb_dev, h->host_rb, 0);
+  if (e != hipSuccess) return hip_fail(h, e, "hipHostGetDevicePointer");
+  h->host_rb_dev = (float*)rb_dev;
   h->pbase = (char*)param_arena_dev; h->pbytes = param_arena_bytes;
   h->abase = (char*)act_arena_dev; h->abytes = act_arena_bytes;
   h->stream = (hipStream_t)hip_stream;
