@@ -95,10 +95,9 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_splits = conv_mfma_dgrad_splits(dt, g);
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
-        f.bwd_fuse = f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g);
+        if (f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g)) f.bwd_splits = conv_bwd1x1_splits(g);
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_sums = conv_dgrad_sum_blocks(dt, g);
         f.image_addend = f.dgrad_algo == ALGO_MFMA && conv_dgrad_image_addend_ok(dt, g);
-        if (f.bwd_fuse) f.wgrad_splits = conv_bwd1x1_splits(g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
         if (f.has_bn && f.fwd_algo == ALGO_SMALLC) f.stat_blocks = conv_smallc_stat_blocks(dt, g);
       }
@@ -111,7 +110,6 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
     // more partial sums where the backward pass of the layer's unit has room for them anyway
     auto splits_in = [&](const FOp& f, int64_t room) {
       const ConvGeom g{f.N, f.H, f.W, f.C, f.K, f.R, f.S, f.stride, f.pad, f.P, f.Q};
-      if (f.bwd_fuse) return f.wgrad_splits;
       return f.wgrad_algo == ALGO_MFMA ? conv_mfma_wgrad_splits(cfg->precision, g, room)
              : f.wgrad_algo == ALGO_SMALLC ? conv_smallc_wgrad_splits(cfg->precision, g, room) : f.wgrad_splits;
     };
@@ -442,7 +440,7 @@ void run_op(const Ctx& c, const SOp& s) {
       launch_conv_bwd1x1(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
                          (s.sums_in >= 0 ? c.sums(s.sums_in) : (const float*)c.at(s.in[4])) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
                          c.at(s.in[5]), (const float*)c.at(s.in[6]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
-                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.wgrad_splits, geom(f), c.sums(s.sums_out));
+                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.bwd_splits, geom(f), c.sums(s.sums_out));
       break;
     }
     case S_POOL_BWD:

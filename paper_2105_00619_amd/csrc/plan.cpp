@@ -512,7 +512,7 @@ struct Scheduler {
   // output, and nothing may have been added to the gradient of the convolution's input yet.
   int fused_conv_of(int fi) const {
     const FOp& f = p.fops[fi];
-    if (fi < 2 || p.fops[fi - 2].kind != F_CONV || !p.fops[fi - 2].bwd_fuse || p.fops[fi - 2].out != f.x) return -1;
+    if (fi < 2 || p.fops[fi - 2].kind != F_CONV || p.fops[fi - 2].bwd_splits == 0 || p.fops[fi - 2].out != f.x) return -1;
     if (f.skip >= 0 && (f.mask < 0 || !masked_skip_grad_ok(fi))) return -1;
     if (!p.tensors[p.fops[fi - 2].x].needs_grad || grad[p.fops[fi - 2].x] >= 0) return -1;
     return fi - 2;
@@ -600,10 +600,10 @@ struct Scheduler {
           if (from_z >= 0) s.in[6] = cur[p.fops[from_z].stats];
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
           s.rows = sums.rows;
-          if (f.wgrad_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.wgrad_splits * f.K * f.R * f.S * f.C * 4, false);
+          if (f.bwd_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.bwd_splits * f.K * f.R * f.S * f.C * 4, false);
           if (sums_for >= 0) {
-            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.wgrad_splits * 2 + 2) * f.C * 4);
-            bn_sum_rows[f.x] = f.wgrad_splits;
+            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.bwd_splits * 2 + 2) * f.C * 4);
+            bn_sum_rows[f.x] = f.bwd_splits;
           }
           return true;
         }
@@ -689,7 +689,8 @@ int launches_of(const SOp& op, const FOp& f) {
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
     case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.sums_in >= 0 ? 1 : 0);
     case S_BIAS_GRAD: return 2;
-    case S_WGRAD: case S_CONV_BWD: return f.wgrad_splits > 1 ? 2 : 1;
+    case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;
+    case S_CONV_BWD: return f.bwd_splits > 1 ? 2 : 1;
     case S_CONV_FWD: return f.fwd_splits > 1 ? 2 : 1;
     case S_DGRAD: return f.dgrad_splits > 1 ? 2 : 1;
     default: return 1;

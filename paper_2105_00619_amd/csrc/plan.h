@@ -57,7 +57,8 @@ struct FOp {
                              // of the head's kernels
   int dgrad_sums = 0;        // F_CONV: row blocks over which the data gradient can sum for the BatchNorm backward in front of it, or 0
   int image_addend = 0;      // F_CONV: 1 = the data gradient can add one row per image (the gradient of a global average pool)
-  int bwd_fuse = 0;          // F_CONV: 1 = the BatchNorm behind it, whose backward sums are known, and both gradients run as one kernel
+  int bwd_splits = 0;        // F_CONV: pixel ranges of the kernel that does the BatchNorm backward behind it (whose sums are known) and
+                             // both gradients where the schedule allows it (S_CONV_BWD), 0: there is none for its shape
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
   int fwd_splits = 1, dgrad_splits = 1;  // fixed by shape only: deterministic split of the GEMM depth
@@ -70,7 +71,7 @@ struct FOp {
 enum SKind {
   S_CAST_IN, S_CONV_FWD, S_BN_STATS, S_BN_APPLY, S_POOL_FWD, S_HEAD_FWD,
   S_HEAD_BWD, S_BN_BWD, S_RELU_BWD, S_BIAS_GRAD, S_WGRAD, S_DGRAD, S_POOL_BWD,
-  S_CONV_BWD  // FOp::bwd_fuse: apply pass of the BatchNorm backward, weight and data gradient of the convolution `fop`
+  S_CONV_BWD  // FOp::bwd_splits: apply pass of the BatchNorm backward, weight and data gradient of the convolution `fop`
 };
 enum Phase { PH_FWD_NOSAVE = 0, PH_FWD_LAST = 1, PH_REPLAY = 2, PH_BWD = 3 };
 

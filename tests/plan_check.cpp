@@ -6,8 +6,8 @@
 //   * the reported peaks are what the walk finds;
 //   * inference, at offsets of its own and at those of the schedule: every operation finds the activations it reads whole
 //     where it looks for them, writes neither over them nor over its own workspace, and stays inside its arena.
-// All of it twice: with the planner's defaults, and with workspaces for split depths and with BatchNorms folded into their
-// readers as the library's kernel choices would have it.
+// All of it twice: with the planner's defaults, and as the library's kernel choices would have it: workspaces for split depths,
+// BatchNorms folded into their readers, their backward sums made with the gradient, 1x1 layers whose backward is one kernel.
 // Input: "k plan_mode precision batch height width channels classes storage_mode n_units" then n_units lines of
 // "kind cin cout ksize stride pad has_bn has_relu has_bias".  Output: "ok <arena> <peak_saved> <launches>" or an error.
 #include <cstdio>
@@ -126,6 +126,15 @@ static void choose_as_the_library(Plan& p) {
     if (f.x >= 0) { ++readers[f.x]; reader[f.x] = (int)i; }
     if (f.skip >= 0) { ++readers[f.skip]; reader[f.skip] = (int)i; }
     if (f.kind == F_CONV && i % 3 == 1) f.fwd_splits = 2 + (int)i % 4;
+    if (f.kind == F_CONV) {
+      f.dgrad_algo = ALGO_MFMA;
+      if (f.R == 1 && f.stride == 1) {
+        f.image_addend = 1;
+        if (f.has_bn && !f.has_bias && f.K > f.C) f.bwd_splits = 1 + (int)i % 3;
+      } else {
+        f.dgrad_sums = 1 + (int)i % 5;
+      }
+    }
     if (f.kind == F_HEAD) {
       f.head_ws_in_x = !p.tensors[f.x].needs_grad;
       f.head_ws = f.head_ws_in_x ? (int64_t)(p.tensors[f.x].bytes / 4) : (int64_t)4 * f.N * (f.gap ? f.C : f.classes);
