@@ -24,7 +24,7 @@ struct optorch_seq {
   char* pbase = nullptr; uint64_t pbytes = 0;
   char* abase = nullptr; uint64_t abytes = 0;
   hipStream_t stream = nullptr;
-  uint64_t off_w = 0, off_v = 0, off_g = 0, off_h = 0, off_wt = 0, off_run = 0, off_scal = 0, off_sums = 0, param_arena_bytes = 0;
+  uint64_t off_w = 0, off_v = 0, off_g = 0, off_h = 0, off_wt = 0, off_run = 0, off_scal = 0, param_arena_bytes = 0;
   bool bound = false, params_set = false;
   bool x_encoded = false;  // the current step's batch came in encoded form
   int dt = 0, in_channels = 0;
@@ -131,7 +131,9 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
     // whose forward and weight-gradient kernels can do it themselves, is folded into that convolution: the activation
     // is never written (storage mode 2 keeps every activation instead).  From the network and the layer shapes only.
     // (A BatchNorm without ReLU keeps its apply launch: the folding kernels always apply the ReLU.)
-    if (p.cfg.storage_mode != 2) {
+    Plan folded = p;
+    {
+      Plan& p = folded;
       std::vector<int> readers(p.tensors.size(), 0), reader(p.tensors.size(), -1);
       for (size_t i = 0; i < p.fops.size(); ++i) {
         const FOp& f = p.fops[i];
@@ -158,6 +160,9 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         }
       }
     }
+    choose_sums(p, folded);
+    folded.unit_sums = p.unit_sums;
+    if (p.cfg.storage_mode != 2) p = folded;
     build_inference(p);
     // k_segments 0 and storage_mode -1 leave the choice to the plan: the cheapest candidate in step time whose
     // arena fits the budget -- fewest segments first (each further segment replays more of the forward pass),
@@ -211,7 +216,6 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
   h->off_wt = o; o = align_up(o + P * p.esize);  // transposed conv weights for the data-gradient GEMM
   h->off_run = o; o = align_up(o + p.n_running * 4);
   h->off_scal = o; o = align_up(o + 256);
-  h->off_sums = o; o += 2 * p.scratch_bytes;
   h->param_arena_bytes = o;
   for (size_t i = 0; i < p.fops.size(); ++i)
     if (p.fops[i].kind == F_BN_STATS) {
@@ -326,7 +330,6 @@ struct Ctx {
   const StepBegin* begin = nullptr;  // what the cast of the images starts the step with
   const uint64_t* xa = nullptr; int xz = 0; const float* xscale = nullptr; const float* xshift = nullptr;
   void* at(int inst) const { return inst < 0 ? nullptr : (void*)(abase + h->plan.insts[inst].offset); }
-  float* sums(int slot) const { return slot < 0 ? nullptr : (float*)(h->pbase + h->off_sums + slot * h->plan.scratch_bytes); }
   float* w32(int64_t off) const { return (float*)(h->pbase + h->off_w) + off; }
   float* g32(int64_t off) const { return (float*)(h->pbase + h->off_g) + off; }
   const void* wc(int64_t off) const {  // weights in the compute type
@@ -405,9 +408,9 @@ void run_op(const Ctx& c, const SOp& s) {
       // in[3]: the block output whose sign gives the ReLU decisions, or (variant 2) those decisions as a bit mask
       launch_bn_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? nullptr : c.at(s.in[3]),
                     s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]), (int64_t)f.N * f.P * f.Q, f.C,
-                    f.relu, s.rows, s.sums_in >= 0 ? c.sums(s.sums_in) : (float*)c.at(s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
-                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0, s.sums_in >= 0,
-                    s.sums_out >= 0 ? BnBwdDual{c.at(s.in[5]), (const float*)c.at(s.in[6]), c.sums(s.sums_out)} : BnBwdDual());
+                    f.relu, s.rows, (float*)c.at(s.in[4] >= 0 ? s.in[4] : s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]),
+                    c.at(s.out[1]), s.per_image ? f.P * f.Q : 0, s.in[4] >= 0,
+                    s.out[3] >= 0 ? BnBwdDual{c.at(s.in[5]), (const float*)c.at(s.in[6]), (float*)c.at(s.out[3])} : BnBwdDual());
       break;
     case S_RELU_BWD:
       launch_relu_bwd(st, dt, c.at(s.in[0]), c.at(s.in[1]), c.at(s.out[0]), (int64_t)f.N * f.P * f.Q, f.K);
@@ -431,16 +434,16 @@ void run_op(const Ctx& c, const SOp& s) {
       if (f.dgrad_algo == ALGO_MFMA)
         launch_conv_dgrad_mfma(st, dt, c.at(s.in[0]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize, c.at(s.in[1]),
                                c.at(s.in[2]), s.per_image, c.at(s.out[0]), (float*)c.at(s.out[1]), f.dgrad_splits, geom(f),
-                               DgradSums{c.sums(s.sums_out), c.at(s.in[3]), (const float*)c.at(s.in[4]), s.variant});
+                               DgradSums{(float*)c.at(s.out[2]), c.at(s.in[3]), (const float*)c.at(s.in[4]), s.variant});
       else
         launch_conv_dgrad_direct(st, dt, c.at(s.in[0]), c.wc(f.w_off), c.at(s.in[1]), c.at(s.out[0]), geom(f));
       break;
     case S_CONV_BWD: {
       const FOp& ap = h->plan.fops[s.fop + 2];
       launch_conv_bwd1x1(st, dt, c.at(s.in[0]), c.at(s.in[1]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
-                         (s.sums_in >= 0 ? c.sums(s.sums_in) : (const float*)c.at(s.in[4])) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
+                         (const float*)c.at(s.in[4]) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
                          c.at(s.in[5]), (const float*)c.at(s.in[6]), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
-                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.bwd_splits, geom(f), c.sums(s.sums_out));
+                         c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.bwd_splits, geom(f), (float*)c.at(s.out[2]));
       break;
     }
     case S_POOL_BWD:
@@ -479,7 +482,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_DGRAD:
       *flops = 2 * out_px * wts;
       *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0) +
-               (s.sums_out >= 0 ? e * in_px * f.C : 0);  // (z of the BatchNorm whose sums it makes)
+               (s.out[2] >= 0 ? e * in_px * f.C : 0);  // (z of the BatchNorm whose sums it makes)
       break;
     case S_WGRAD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K) + 4 * wts; break;
     case S_BN_STATS: *bytes = s.in[1] >= 0 ? 8.0 * f.stat_blocks * f.C : e * out_px * f.C; break;  // fused: only the block sums
@@ -492,12 +495,12 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
       {  // the reduction reads dA, z and the ReLU source; the apply pass reads them again and writes dz (+ the skip gradient)
         const double src = s.in[3] < 0 ? 0.0 : s.variant == 2 ? 1.0 / 16 : 1.0;  // a bit mask is a sixteenth of a tensor
         const double da = s.per_image ? 0.0 : 1.0;  // (a gradient per image is next to nothing)
-        if (s.sums_in >= 0) {  // the sums came with the gradient
+        if (s.in[4] >= 0) {  // the sums came with the gradient
           *bytes = s.out[0] < 0 ? 8.0 * s.rows * f.C : e * out_px * f.C * (2 + da + src + (s.out[1] >= 0 ? 1 : 0));
           break;
         }
-        if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + (s.sums_out >= 0 ? 1 : 0) + da + src); break; }  // (the sums only)
-        *bytes = e * out_px * f.C * (1 + (s.sums_out >= 0 ? 1 : 0) + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
+        if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + (s.out[3] >= 0 ? 1 : 0) + da + src); break; }  // (the sums only)
+        *bytes = e * out_px * f.C * (1 + (s.out[3] >= 0 ? 1 : 0) + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
       break;
     case S_CONV_BWD:  // dA, z and the ReLU source, x, dx, the weights and their gradient

@@ -236,9 +236,10 @@ struct Span { uint64_t bytes; int first, last; uint64_t offset; };
 // arena's size.  First in the order of the steps, each at the tightest hole.  Where that leaves holes that a later tensor does
 // not fit (a workspace between kept tensors), also one tensor after the other, each at the lowest offset that is free while it is
 // alive, in these orders: the largest first; those alive at the fullest step ahead of the others; those ahead with most bytes
-// times steps; the order of the steps; each also with the tensor that ended up on top ahead of all others, twice.  The smallest
-// result is kept; the search ends at one of `enough` bytes.
-uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough) {
+// times steps; the order of the steps; the longest alive first; the largest first with every size weighted by a fixed number between
+// a half and one and a half, ways - 5 times over; each also with the tensor that ended up on top ahead of all others, seven times.  The
+// smallest result is kept; the search ends at one of `enough` bytes, mostly at once.
+uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough, int ways = 24) {
   const int n = (int)spans.size();
   std::vector<std::vector<int>> dies(n_steps);
   for (int i = 0; i < n; ++i) dies[spans[i].last].push_back(i);
@@ -257,13 +258,18 @@ uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough) {
   enough = std::max(enough, least);
   std::vector<int> order(n), placed;  // placed: by offset
   std::vector<uint64_t> at(n);
-  for (int way = 0; way < 4 && best > enough; ++way) {
+  for (int way = 0; way < ways && best > enough; ++way) {
     auto ahead = [&](int i) { return way == 1 && spans[i].first <= fullest && spans[i].last >= fullest; };
-    auto weight = [&](int i) { return way == 2 ? spans[i].bytes * (uint64_t)(spans[i].last - spans[i].first + 1) : spans[i].bytes; };
+    auto weight = [&](int i) -> uint64_t {
+      const uint64_t steps = (uint64_t)(spans[i].last - spans[i].first + 1);
+      if (way < 5) return way == 2 ? spans[i].bytes * steps : way == 4 ? steps : spans[i].bytes;
+      const uint32_t h = ((uint32_t)i * 2654435761u + (uint32_t)way * 40503u) * 2246822519u;
+      return spans[i].bytes / 256 * (128 + (h >> 24));
+    };
     for (int i = 0; i < n; ++i) order[i] = i;
-    if (way < 3)
+    if (way != 3)
       std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return ahead(a) != ahead(b) ? ahead(a) : weight(a) > weight(b); });
-    for (int tries = 0; tries < 3 && best > enough; ++tries) {
+    for (int tries = 0; tries < 8 && best > enough; ++tries) {
       uint64_t high = 0;
       int top = 0;  // its place in the order
       placed.clear();
@@ -316,7 +322,7 @@ struct Scheduler {
                                  //              reader applies the mask to the block output's gradient itself), or -1
   std::vector<char> per_image;   // [LTensor] -> grad[t] (or image_grad[t]) holds one value per image and channel
   std::vector<int> fused_bwd;    // [FOp of a convolution] -> entry of the BatchNorm-backward sums that its S_CONV_BWD goes on from, or -1
-  std::vector<int> bn_sums, bn_sum_rows;  // [LTensor] -> slot of the BatchNorm-backward sums that came with grad[t], or -1, and their rows
+  std::vector<int> bn_sums, bn_sum_rows;  // [LTensor] -> Inst id of the BatchNorm-backward sums that came with grad[t], or -1, and their rows
   std::vector<int> image_grad;   // [LTensor] -> Inst id of the gradient per image of the global average pool's input, or -1
   explicit Scheduler(Plan& pl)
       : p(pl), cur(pl.tensors.size(), -1), grad(pl.tensors.size(), -1), stat_ws(pl.tensors.size(), -1),
@@ -347,12 +353,9 @@ struct Scheduler {
     p.insts.push_back(i);
     return (int)p.insts.size() - 1;
   }
-  int next_slot = 0;
-  int sums_slot(uint64_t bytes) {
-    p.scratch_bytes = std::max(p.scratch_bytes, align_up(bytes));
-    next_slot ^= 1;
-    return next_slot ^ 1;
-  }
+  // the sums of a BatchNorm backward over `rows` row blocks, and their means behind them
+  int sums_inst(int rows, int C) { return new_inst(-1, ((uint64_t)rows * 2 + 2) * C * 4, false); }
+  bool sums_ok(int unit, int which) const { return !p.separate && unit >= 0 && unit < (int)p.unit_sums.size() && (p.unit_sums[unit] & which); }
   int value_inst(int t) { return cur[t] = new_inst(t, p.tensors[t].bytes, true); }
   int grad_inst(int t) { return new_inst(t, p.tensors[t].bytes, false); }
 
@@ -378,7 +381,7 @@ struct Scheduler {
   // one's output, both lie in segment `seg`, whole groups of channels, and backward has the ReLU decisions of an output with
   // a skip connection as bits.  (storage mode 2 keeps every activation)
   bool gap_fused(int fi, int seg) const {
-    if (fi < 1 || fi >= (int)p.fops.size() || p.cfg.storage_mode == 2) return false;
+    if (fi < 1 || fi >= (int)p.fops.size() || p.cfg.storage_mode == 2 || p.separate) return false;
     const FOp& head = p.fops[fi];
     const FOp& ap = p.fops[fi - 1];
     if (head.kind != F_HEAD || !head.gap || ap.kind != F_BN_APPLY || head.x != ap.out || ap.fold || readers[ap.out] != 1) return false;
@@ -476,7 +479,7 @@ struct Scheduler {
   bool image_addend_ok(int fi) const {
     const FOp& f = p.fops[fi];
     for (int j = p.unit_first_fop[f.unit]; j < p.unit_last_fop[f.unit]; ++j)
-      if (p.fops[j].kind == F_CONV && p.fops[j].x == f.skip) return p.fops[j].image_addend != 0;
+      if (p.fops[j].kind == F_CONV && p.fops[j].x == f.skip) return p.fops[j].image_addend != 0 && !p.separate;
     return false;
   }
 
@@ -485,7 +488,7 @@ struct Scheduler {
   int summed_apply(int fi) const {
     const FOp& f = p.fops[fi];
     const int ap = bn_apply_of[f.x];
-    if (ap < 0 || grad[f.x] >= 0 || readers[f.x] != 1) return -1;
+    if (ap < 0 || grad[f.x] >= 0 || readers[f.x] != 1 || !sums_ok(f.unit, SUMS_INSIDE)) return -1;
     const FOp& b = p.fops[ap];
     return b.unit == f.unit && b.skip < 0 && b.mask < 0 ? ap : -1;
   }
@@ -512,7 +515,7 @@ struct Scheduler {
   // output, and nothing may have been added to the gradient of the convolution's input yet.
   int fused_conv_of(int fi) const {
     const FOp& f = p.fops[fi];
-    if (fi < 2 || p.fops[fi - 2].kind != F_CONV || p.fops[fi - 2].bwd_splits == 0 || p.fops[fi - 2].out != f.x) return -1;
+    if (fi < 2 || p.separate || p.fops[fi - 2].kind != F_CONV || p.fops[fi - 2].bwd_splits == 0 || p.fops[fi - 2].out != f.x) return -1;
     if (f.skip >= 0 && (f.mask < 0 || !masked_skip_grad_ok(fi))) return -1;
     if (!p.tensors[p.fops[fi - 2].x].needs_grad || grad[p.fops[fi - 2].x] >= 0) return -1;
     return fi - 2;
@@ -575,14 +578,14 @@ struct Scheduler {
         b.rows = f.red_blocks;
         // the BatchNorm of a projection shortcut has the same gradient and decisions (masked_skip_grad_ok): its sums in the same pass
         const int shortcut = f.skip >= 0 && b.variant == 2 ? projection_of(fi) : -1;
-        if (shortcut >= 0 && gmask[f.skip] >= 0 && grad[f.skip] == b.in[0] && f.C % (16 / p.esize) == 0) {
+        if (shortcut >= 0 && gmask[f.skip] >= 0 && grad[f.skip] == b.in[0] && f.C % (16 / p.esize) == 0 && sums_ok(f.unit, SUMS_SHORTCUT)) {
           const FOp& q = p.fops[shortcut];
           b.in[5] = cur[q.x]; b.in[6] = cur[q.stats];
-          b.sums_out = bn_sums[f.skip] = sums_slot(((uint64_t)f.red_blocks * 2 + 2) * f.C * 4);
+          b.out[3] = bn_sums[f.skip] = sums_inst(f.red_blocks, f.C);
           bn_sum_rows[f.skip] = f.red_blocks;
         }
-        if (bn_sums[f.out] >= 0 && variant == 0) { b.sums_in = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
-        else b.out[2] = new_inst(-1, ((uint64_t)f.red_blocks * 2 + 2) * f.C * 4, false);
+        if (bn_sums[f.out] >= 0 && variant == 0) { b.in[4] = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
+        else b.out[2] = sums_inst(f.red_blocks, f.C);
         return true;
       }
       case F_CONV: {
@@ -595,21 +598,22 @@ struct Scheduler {
           SOp& s = push(S_CONV_BWD, fi, PH_BWD, seg);
           for (int i = 0; i < 4; ++i) s.in[i] = sums.in[i];
           s.variant = sums.variant; s.per_image = sums.per_image;
-          s.in[4] = sums.out[2]; s.sums_in = sums.sums_in;
+          s.in[4] = sums.in[4] >= 0 ? sums.in[4] : sums.out[2];
           s.in[5] = xin;
           if (from_z >= 0) s.in[6] = cur[p.fops[from_z].stats];
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1;
           s.rows = sums.rows;
           if (f.bwd_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.bwd_splits * f.K * f.R * f.S * f.C * 4, false);
           if (sums_for >= 0) {
-            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.bwd_splits * 2 + 2) * f.C * 4);
+            s.out[2] = bn_sums[f.x] = sums_inst(f.bwd_splits, f.C);
             bn_sum_rows[f.x] = f.bwd_splits;
           }
           return true;
         }
         int g = grad[f.out];
         if (g < 0) { p.error = "internal: conv output has no gradient"; return false; }
-        if (!f.has_bn && f.relu && !f.has_bias) {
+        const bool in_place = !f.has_bn && f.relu && f.has_bias && !p.separate;
+        if (!f.has_bn && f.relu && !in_place) {
           SOp& s = push(S_RELU_BWD, fi, PH_BWD, seg);
           s.in[0] = g; s.in[1] = cur[f.out];
           s.out[0] = grad_inst(f.out); g = s.out[0];
@@ -617,7 +621,7 @@ struct Scheduler {
         if (f.has_bias) {
           SOp& s = push(S_BIAS_GRAD, fi, PH_BWD, seg);
           s.in[0] = g;
-          if (!f.has_bn && f.relu) s.in[1] = cur[f.out];  // (and the ReLU, in place: nothing else reads this gradient)
+          if (in_place) s.in[1] = cur[f.out];  // (and the ReLU, in place: nothing else reads this gradient)
           s.out[0] = new_inst(-1, (uint64_t)f.red_blocks * 2 * f.K * 4, false);
         }
         {
@@ -635,7 +639,7 @@ struct Scheduler {
           const int ap = f.dgrad_sums > 0 ? summed_apply(fi) : -1;
           if (ap >= 0) {
             s.in[3] = cur[p.fops[ap].x]; s.in[4] = cur[p.fops[ap].stats]; s.variant = p.fops[ap].relu;
-            s.sums_out = bn_sums[f.x] = sums_slot(((uint64_t)f.dgrad_sums * 2 + 2) * f.C * 4);
+            s.out[2] = bn_sums[f.x] = sums_inst(f.dgrad_sums, f.C);
             bn_sum_rows[f.x] = f.dgrad_sums;
           }
           s.out[0] = grad_inst(f.x); grad[f.x] = s.out[0]; gmask[f.x] = -1; per_image[f.x] = 0;
@@ -661,7 +665,6 @@ struct Scheduler {
   bool run() {
     const int k = (int)p.seg_begin.size() - 1;
     p.insts.clear(); p.sched.clear();
-    p.scratch_bytes = 0;
     emit_fop_forward(0, k == 1 ? PH_FWD_LAST : PH_FWD_NOSAVE, 0);
     auto forward_seg = [&](int j, int phase) {
       for (int u = p.seg_begin[j]; u < p.seg_begin[j + 1]; ++u)
@@ -687,7 +690,7 @@ int launches_of(const SOp& op, const FOp& f) {
     case S_HEAD_FWD: return (f.head_ws > 0 ? 5 : 4) - (f.head_one ? 1 : 0);
     case S_HEAD_BWD:  // the weight gradient; the feature gradient and where it goes: the whole map, one value per image
       return 1 + (op.out[0] >= 0 || op.out[2] >= 0) + (op.out[0] >= 0) + (op.out[2] >= 0);
-    case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.sums_in >= 0 ? 1 : 0);
+    case S_BN_BWD: return (op.out[0] >= 0 ? 3 : 2) - (op.in[4] >= 0 ? 1 : 0);
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;
     case S_CONV_BWD: return f.bwd_splits > 1 ? 2 : 1;
@@ -781,26 +784,61 @@ bool build_schedule(Plan& p, uint64_t enough) {
     }
   }
   p.arena_bytes = place(spans, n, enough);
+  if (!p.separate && p.arena_bytes > enough) {
+    // merged passes hold no more at any step, but may be placed worse: then a longer search, so that what a budget allowed without
+    // them it allows with them (of 40 000 random networks 29 are still larger, by up to 2 % or some KB)
+    Plan q = p;
+    q.separate = true;
+    if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), 400);
+  }
   for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
   return true;
+}
+
+// Schedules q as one segment in storage mode `mode`: bytes alive at every operation, and the most at any of a unit's backward pass.
+static bool fullest_moments(Plan& q, int mode, std::vector<int64_t>& alive, std::vector<int64_t>& most) {
+  q.cfg.storage_mode = mode;
+  q.seg_begin = {0, (int)q.units.size()};
+  if (!schedule_operations(q)) return false;
+  std::vector<int64_t> born(q.sched.size() + 1, 0);
+  alive.assign(q.sched.size(), 0);
+  most.assign(q.units.size(), 0);
+  for (const Inst& t : q.insts)
+    if (t.def_op >= 0) { born[t.def_op] += (int64_t)t.bytes; born[t.last_use + 1] -= (int64_t)t.bytes; }
+  int64_t sum = 0;
+  for (size_t i = 0; i < q.sched.size(); ++i) {
+    alive[i] = sum += born[i];
+    const int unit = q.fops[q.sched[i].fop].unit;
+    if (q.sched[i].live && q.sched[i].phase == PH_BWD) most[unit] = std::max(most[unit], sum);
+  }
+  return true;
+}
+
+void choose_sums(Plan& p, const Plan& folded) {
+  const size_t nu = p.units.size();
+  std::vector<char> chosen(nu, 0);
+  for (char which : {SUMS_INSIDE, SUMS_SHORTCUT}) {  // (the sums of a shortcut's BatchNorm are alive for longer)
+    std::vector<char> ok(nu, 1);
+    for (int mode = 0; mode < 3; ++mode) {
+      std::vector<int64_t> alive, before, with;
+      Plan q = mode == 2 ? p : folded, r = q;
+      q.separate = true;
+      r.unit_sums = chosen;
+      for (char& u : r.unit_sums) u = (char)(u | which);
+      if (!fullest_moments(q, mode, alive, before) || !fullest_moments(r, mode, alive, with)) return;
+      for (size_t u = 0; u < nu; ++u) ok[u] = ok[u] && with[u] <= before[u];
+    }
+    for (size_t u = 0; u < nu; ++u) if (ok[u]) chosen[u] = (char)(chosen[u] | which);
+  }
+  p.unit_sums = chosen;
 }
 
 std::vector<int64_t> wgrad_room(const Plan& p) {
   std::vector<int64_t> room(p.fops.size(), 0);
   for (int mode = 0; mode < 2; ++mode) {
     Plan q = p;
-    q.cfg.storage_mode = mode;
-    q.seg_begin = {0, (int)q.units.size()};
-    if (!schedule_operations(q)) return room;  // (a network that cannot be scheduled is refused later)
-    std::vector<int64_t> born(q.sched.size() + 1, 0), alive(q.sched.size(), 0), most(q.units.size(), 0);
-    for (const Inst& t : q.insts)
-      if (t.def_op >= 0) { born[t.def_op] += (int64_t)t.bytes; born[t.last_use + 1] -= (int64_t)t.bytes; }
-    int64_t sum = 0;
-    for (size_t i = 0; i < q.sched.size(); ++i) {
-      alive[i] = sum += born[i];
-      const int unit = q.fops[q.sched[i].fop].unit;
-      if (q.sched[i].live && q.sched[i].phase == PH_BWD) most[unit] = std::max(most[unit], sum);
-    }
+    std::vector<int64_t> alive, most;
+    if (!fullest_moments(q, mode, alive, most)) return room;  // (a network that cannot be scheduled is refused later)
     for (size_t i = 0; i < q.sched.size(); ++i) {
       const SOp& s = q.sched[i];
       if (!s.live || s.kind != S_WGRAD) continue;

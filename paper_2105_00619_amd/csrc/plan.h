@@ -101,19 +101,16 @@ struct SOp {
                     // S_BN_APPLY with in[3] >= 0: in[2] is the z of the projection shortcut's BatchNorm, in[3] its
                     // statistics tensor (FOp::fold_skip)
                     // S_BN_BWD with out[0] < 0: the sums only, for the S_CONV_BWD that follows.  That one has in[0..3] as the
-                    // S_BN_BWD, in[4] its workspace (or sums_in), in[5] the convolution's input (the z of a folded BatchNorm with in[6]
-                    // its statistics tensor), out[0] the data gradient, out[1] the weight gradient's partial sums
-                    // S_DGRAD with sums_out >= 0: it makes the sums of the BatchNorm backward in front, whose z is in[3] and
+                    // S_BN_BWD, in[4] its workspace (for the means behind the sums), in[5] the convolution's input (the z of a
+                    // folded BatchNorm with in[6] its statistics tensor), out[0] the data gradient, out[1] the weight gradient's
+                    // partial sums
+                    // S_DGRAD with out[2] >= 0: it makes the sums of the BatchNorm backward in front, whose z is in[3] and
                     // statistics in[4]; variant: whether a ReLU follows that BatchNorm.  S_CONV_BWD likewise (in[5], in[6]).
-                    // S_BN_BWD with sums_out >= 0: it also makes those of the projection shortcut's BatchNorm (z in[5],
-                    // statistics in[6])
+                    // S_BN_BWD with out[3] >= 0: it also makes those of the projection shortcut's BatchNorm (z in[5],
+                    // statistics in[6]); with in[4] >= 0: its sums, made that way, which are its workspace
                     // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; in[0]
                     // becomes the gradient in front of it, in place
                     // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
-  // Slot of the scratch memory that holds BatchNorm-backward sums: sums_out where this entry writes them for a later one (S_DGRAD,
-  // S_CONV_BWD, S_BN_BWD); sums_in the slot that an S_BN_BWD finds its sums in and uses as its workspace, and that an S_CONV_BWD
-  // reads the means from; -1: none
-  int sums_in = -1, sums_out = -1;
   int rows = 0;  // S_BN_BWD, S_CONV_BWD: rows of partial sums in the BatchNorm backward's workspace
   bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
@@ -129,6 +126,8 @@ struct IOp {
   int64_t in = -1, skip = -1, out = -1, ws = -1;  // head: out = features, skip unused
 };
 
+constexpr char SUMS_INSIDE = 1, SUMS_SHORTCUT = 2;
+
 struct Plan {
   // inputs
   std::vector<optorch_unit_t> units;
@@ -141,15 +140,15 @@ struct Plan {
   std::vector<int> unit_in, unit_out;              // [unit] LTensor ids
   uint64_t n_params = 0;
   uint64_t n_running = 0;  // floats of BN running statistics
+  std::vector<char> unit_sums;  // [unit] SUMS_INSIDE: kernels that write a gradient inside the unit also make the sums of the BatchNorm
+                                // backward in front; SUMS_SHORTCUT: the sums of a projection shortcut's BatchNorm come with its
+                                // block output's (choose_sums); empty: none
+  bool separate = false;        // schedule every pass of the backward as an operation of its own (what choose_sums measures by)
   // partition
   std::vector<int> seg_begin;  // k+1 entries, unit indices
   // schedule
   std::vector<Inst> insts;
   std::vector<SOp> sched;
-  // BatchNorm-backward sums that come with a gradient: two slots of this many bytes behind the parameters, so that the activation
-  // arena is not larger for them.  Taken in turn: no more than one other set is made before a set is used up (a projection
-  // shortcut's, made with its block output's, waits while those of the block's last convolution's input are made).
-  uint64_t scratch_bytes = 0;
   uint64_t arena_bytes = 0;       // high-water mark of the activation arena (aligned offsets)
   uint64_t peak_saved_bytes = 0;  // exact tensor sizes, no alignment
   uint64_t peak_live_bytes = 0;   // all live tensors incl. transients, exact sizes
@@ -171,6 +170,10 @@ bool build_schedule(Plan& p, uint64_t enough = 0);
 // backward pass: whatever else is alive stays alive throughout that pass, so this holds for every partition; the smaller value
 // of the storage modes that keep and that rebuild activations.  From the network and the kernel choices so far only.
 std::vector<int64_t> wgrad_room(const Plan& p);
+// Sets unit_sums: for the units whose backward pass is then no fuller than with every pass an operation of its own, in any storage
+// mode (folded: the plan with its BatchNorms folded, as modes 0 and 1 run it; p without).  Likewise from the network and the kernel
+// choices so far only.
+void choose_sums(Plan& p, const Plan& folded);
 // Builds the inference schedule with offsets of its own; needs the kernel choices of the convolutions (workspaces of split
 // depths).
 void build_inference(Plan& p);

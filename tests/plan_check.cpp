@@ -120,6 +120,7 @@ static int check_inference(const Plan& p) {
 
 // what the library's kernel choices change in the plan: depth splits, the head's ranges, folded BatchNorms
 static void choose_as_the_library(Plan& p) {
+  p.unit_sums.assign(p.units.size(), SUMS_INSIDE | SUMS_SHORTCUT);
   std::vector<int> readers(p.tensors.size(), 0), reader(p.tensors.size(), -1);
   for (size_t i = 0; i < p.fops.size(); ++i) {
     FOp& f = p.fops[i];

@@ -153,6 +153,15 @@ def test_pool_is_computed_by_the_kernels_of_the_batchnorm_in_front_of_it():
     assert (q.n_launches, q.n_replay_launches) == (100, 11)
 
 
+def test_parameter_arena_holds_nothing_of_the_batch():
+    # what a step needs besides parameters and their state is activation memory, which budgets and peaks count
+    for units in ([W.conv(3, 64), W.bottleneck(64, 256), W.bottleneck(256, 256), W.gap_linear_ce(256, 10)],
+                  [W.conv(3, 64), W.basic_block(64, 64), W.basic_block(64, 128, 2), W.gap_linear_ce(128, 10)]):
+        size = {SeqPlan(units, k_segments=1, precision=W.BF16, batch=b, height=32, width=32, channels=3, num_classes=10).param_arena_bytes
+                for b in (1, 64, 512)}
+        assert len(size) == 1
+
+
 def test_losses_of_many_classes_are_not_one_blocks_work():
     def launches(batch, classes):
         return SeqPlan([W.conv(8, 8, ksize=1), W.gap_linear_ce(8, classes)], k_segments=1, precision=W.FP32, batch=batch, height=4,
@@ -293,6 +302,11 @@ ARENAS = [  # precision, batch, h, w, channels, k, storage mode, plan mode, clas
     (W.BF16, 512, 9, 9, 64, 4, 0, 2, 1000, "n64 b256 p R64/2 n64 R64/2 flat", 179012096),
     (W.FP16, 128, 16, 16, 64, 7, 1, 0, 10, "p b512 c8 p b8 b8 flat", 114294784),
     (W.BF16, 128, 8, 8, 64, 3, 1, 0, 10, "R128 b256 b256 R256 p p flat", 62982144),
+    # ... and before passes of the backward were merged and BatchNorm sums made with the gradient
+    (W.FP16, 16, 128, 128, 3, 1, 1, 2, 1000, "R16 n64 b128/2 flat", 273162752),
+    (W.FP32, 1, 64, 64, 64, 3, 1, 0, 10, "n12 b12 r128/2 b8 gap", 3593728),
+    (W.FP16, 41, 16, 19, 3, 1, 2, 2, 10, "b64 R64 flat", 17729024),
+    (W.FP16, 99, 16, 19, 3, 1, 1, 0, 2, "b256 r256 flat", 155248640),
 ]
 
 
