@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from paper_2105_00619_amd import workloads as W
-from tests.gpu_util import TOL, assert_parity, assert_parity_16bit, assert_parity_fp32, gpu_step, oracle_step, plain_errors, record
+from tests.gpu_util import TOL, assert_parity, assert_parity_16bit, assert_parity_fp32, gpu_step, oracle_step, plain_errors, record, tensor_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -492,56 +492,78 @@ def test_fp32_step_with_an_infinity_takes_no_longer_than_a_few():
     assert best[1] < 8 * best[0]
 
 
-def _grads64(layers, blocks, params, x, y):
-    """Gradients in float64 of a run of convolutions + BatchNorm (blocks None; the last argument of a layer: ReLU) or of
-    bottleneck blocks given as (channels in, channels out), a global average pool and a linear layer; params in flat order."""
+def _grads64(units, params, x, y, precision, scale):
+    """Loss and gradients in float64 on the GPU of convolutions + BatchNorm, residual blocks and a pooled linear head, rounded to
+    the storage type where the tensors of a step are stored (activations and their gradients, which carry the loss scale); params:
+    the tensors in flat order (inside a block conv1, conv2, [conv3], then the projection shortcut)."""
     import torch
-    it = iter(params)
+    dtype = {W.FP32: torch.float64, W.BF16: torch.bfloat16, W.FP16: torch.float16}[precision]
 
-    def cbr(v, stride=1, relu=True):
-        z = _layer64(v, next(it), stride)
+    class Stored(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, v):
+            return v.to(dtype).double()
+
+        @staticmethod
+        def backward(ctx, g):
+            return g.to(dtype).double()
+
+    class Cast(torch.autograd.Function):  # weights: gradients in fp32
+        @staticmethod
+        def forward(ctx, v):
+            return v.to(dtype).double()
+
+        @staticmethod
+        def backward(ctx, g):
+            return g
+
+    p64 = [v.double().requires_grad_(True) for v in params]
+    it = iter(p64)
+    stored = Stored.apply
+
+    def cb(v, stride=1):
+        z = stored(_layer64(v, Cast.apply(next(it)), stride))
         gamma, beta = next(it), next(it)
         flat = z.reshape(-1, z.shape[3])
-        z = gamma * (z - flat.mean(0)) / torch.sqrt(flat.var(0, unbiased=False) + 1e-5) + beta
-        return z, relu
+        return gamma * (z - flat.mean(0)) / torch.sqrt(flat.var(0, unbiased=False) + 1e-5) + beta
 
-    def done(zr, add=None):
-        z = zr[0] if add is None else zr[0] + add
-        return torch.relu(z) if zr[1] else z
+    x = x.to(dtype).double()
+    for u in units[:-1]:
+        if u.kind == W.CONV:
+            x = cb(x, u.stride)
+            x = stored(torch.relu(x) if u.has_relu else x)
+        else:
+            bott = u.kind == W.BOTTLENECK
+            v = stored(torch.relu(cb(x, 1 if bott else u.stride)))
+            if bott:
+                v = stored(torch.relu(cb(v, u.stride)))
+            v = cb(v)
+            x = stored(torch.relu(v + (stored(cb(x, u.stride)) if u.cin != u.cout or u.stride != 1 else x)))
+    loss = torch.nn.functional.cross_entropy(x.mean((1, 2)) @ next(it).t() + next(it), y.long())
+    (loss * scale).backward()
+    return float(loss.detach()), (torch.cat([q.grad.flatten() for q in p64]) / scale).cpu().numpy()
 
-    for _ in range(layers):
-        x = done(cbr(x))
-    for cin, cout in blocks:
-        v = done(cbr(x))
-        v = done(cbr(v))
-        z = cbr(v)
-        x = done(z, done(cbr(x, relu=False)) if cin != cout else x)
-    logits = x.mean((1, 2)) @ next(it).t() + next(it)
-    torch.nn.functional.cross_entropy(logits, y.long()).backward()
 
-
-@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
-@pytest.mark.parametrize("chain,blocks,h,w,b", [
-    ([64, 256], [], 16, 17, 241), ([64, 256, 64], [], 15, 17, 259),  # gradient per image; whole, decisions from z
-    ([64], [(64, 256), (256, 256)], 15, 17, 257),  # projection and identity shortcut, BatchNorm folded into the layer's input
-    ([64], [(64, 256)], 32, 32, 64), ([256], [(256, 256), (256, 256)], 9, 7, 521)])  # exactly 65 536 pixels; fewer
-def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w, b):
-    """64 -> 256 channels over 65 536 pixels or more: BatchNorm apply, data and weight gradient as one kernel; the gradient of a
-    global average pool as one row per image, also where an identity shortcut's data gradient adds it, and the last apply
-    operation done by the pooling kernel.  Plain float64 and the bar of the single-layer tests; k segments change no bit."""
+def _against_float64(units, b, h, w, precision, seed=9):
+    """One step in one segment and in as many as there are units against float64 (with the storage type's roundings), tensor by
+    tensor; the trainer's work by class."""
     import torch
-    units = [W.conv(i, o, 1) for i, o in zip([8] + chain, chain)] + [W.bottleneck(i, o) for i, o in blocks]
-    last = blocks[-1][1] if blocks else chain[-1]
-    units.append(W.gap_linear_ce(last, 10))
-    g = torch.Generator(device="cuda").manual_seed(9)
+    from paper_2105_00619_amd.binding import SeqTrainer
+    g = torch.Generator(device="cuda").manual_seed(seed)
     shapes = []
-    for i, o in zip([8] + chain, chain):
-        shapes += [(o, 1, 1, i), (o,), (o,)]
-    for i, o in blocks:
-        m = o // 4
-        shapes += [(m, 1, 1, i), (m,), (m,), (m, 3, 3, m), (m,), (m,), (o, 1, 1, m), (o,), (o,)]
-        shapes += [(o, 1, 1, i), (o,), (o,)] if i != o else []
-    shapes += [(10, last), (10,)]
+    for u in units[:-1]:
+        if u.kind == W.CONV:
+            convs = [(u.cout, u.ksize, u.ksize, u.cin)]
+        elif u.kind == W.BASIC_BLOCK:
+            convs = [(u.cout, 3, 3, u.cin), (u.cout, 3, 3, u.cout)]
+        else:
+            m = u.cout // 4
+            convs = [(m, 1, 1, u.cin), (m, 3, 3, m), (u.cout, 1, 1, m)]
+        if u.kind != W.CONV and (u.cin != u.cout or u.stride != 1):
+            convs.append((u.cout, 1, 1, u.cin))
+        for c in convs:
+            shapes += [c, c[:1], c[:1]]
+    shapes += [(10, units[-1].cin), (10,)]
     params, at = [], 0
     for s in shapes:
         v = torch.randn(s, generator=g, device="cuda")
@@ -551,18 +573,64 @@ def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w,
         else:
             v, at = v * (2.0 / math.prod(s[1:])) ** 0.5, 1
         params.append(v)
-    x = torch.randn((b, h, w, 8), generator=g, device="cuda")
+    x = torch.randn((b, h, w, units[0].cin), generator=g, device="cuda")
     y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
     flat = torch.cat([v.flatten() for v in params]).cpu().numpy()
-    r, info = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    kw = dict(precision=precision, classes=10, loss_scale_init=_scale(precision))
+    r, _ = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), k=1, **kw)
     assert not r["skipped"]
-    again, _ = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), precision=precision, k=len(units), classes=10,
-                        loss_scale_init=_scale(precision))
+    again, _ = gpu_step(units, flat, x.cpu().numpy(), y.cpu().numpy(), k=len(units), **kw)
     assert np.array_equal(r["grads"], again["grads"])
-    p64 = [v.double().requires_grad_(True) for v in params]
-    _grads64(len(chain), blocks, p64, x.double(), y)
-    want = torch.cat([q.grad.flatten() for q in p64]).cpu().numpy()
-    assert np.linalg.norm(r["grads"] - want) <= TOL[precision] * np.linalg.norm(want)
+    loss, want = _grads64(units, params, x, y, precision, _scale(precision))
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+    errs = tensor_errors(units, h, w, r["grads"], want, 1e-3 if precision == W.FP32 else 5e-2)
+    missed = [k for k, e in errs.items() if e > TOL[precision]]
+    if missed:  # several blocks deep roundings cascade: then as close to plain float64 as the rounded evaluation (as assert_parity_16bit)
+        assert precision != W.FP32, errs
+        plain = _grads64(units, params, x, y, W.FP32, 1.0)[1]
+        here, rounded = tensor_errors(units, h, w, r["grads"], plain, 5e-2), tensor_errors(units, h, w, want, plain, 5e-2)
+        for k in missed:
+            assert here[k] <= 1.5 * rounded[k], (k, errs[k], here[k], rounded[k])
+    t = SeqTrainer(units, k_segments=1, precision=precision, batch=b, height=h, width=w, channels=units[0].cin, num_classes=10,
+                   loss_scale_init=_scale(precision))
+    t.set_params(flat)
+    t.profile_enable()
+    t.step(x, y, 0.0)
+    work = t.profile_read()["classes"]
+    t.close()
+    return work
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("chain,blocks,h,w,b,fused", [
+    ([64, 256], [], 16, 17, 241, 1), ([64, 256, 64], [], 15, 17, 259, 1),  # gradient per image; whole, decisions from z
+    # projection and identity shortcut, BatchNorm folded into the layer's input; a ragged last tile
+    ([64], [(64, 256), (256, 256)], 15, 17, 259, 3), ([64], [(64, 256), (256, 256)], 15, 17, 257, 0),  # 65 535 pixels
+    ([64], [(64, 256)], 32, 32, 64, 2), ([256], [(256, 256), (256, 256)], 9, 7, 521, 0),  # exactly 65 536 pixels; fewer
+    # 1x1 data gradients of depth 64 with weights stationary (131 072 pixels or more), ragged: a masked addend of whole tensors and
+    # one per image
+    ([64], [(64, 256), (256, 256), (256, 256)], 33, 33, 121, 4)])
+def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w, b, fused):
+    """64 -> 256 channels over 65 536 pixels or more: BatchNorm apply, data and weight gradient as one kernel; the gradient of a
+    global average pool as one row per image, also where an identity shortcut's data gradient adds it, and the last apply
+    operation done by the pooling kernel.  Bar: the file's, per tensor; k segments change no bit."""
+    units = [W.conv(i, o, 1) for i, o in zip([8] + chain, chain)] + [W.bottleneck(i, o) for i, o in blocks]
+    units.append(W.gap_linear_ce(blocks[-1][1] if blocks else chain[-1], 10))
+    work = _against_float64(units, b, h, w, precision)
+    layers = len(chain) + sum(3 if i != o else 2 for i, o in blocks)
+    assert work["conv1x1_wgrad"]["entries"] == layers - fused  # (a fused layer's counts with the data gradients)
+
+
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
+@pytest.mark.parametrize("body,h,w,b", [
+    ([W.conv(8, 64, 1)], 61, 67, 2), ([W.conv(8, 64, 1), W.basic_block(64, 64)], 61, 67, 2),
+    ([W.conv(8, 64, 1), W.bottleneck(64, 128)], 40, 64, 3),
+    # the shortcut's BatchNorm sums with its block output's: a unit that is fullest at the shortcut
+    ([W.conv(8, 256, 1), W.basic_block(256, 64)], 16, 15, 17), ([W.conv(8, 256, 1), W.basic_block(256, 64, 2)], 9, 16, 33)])
+def test_last_apply_in_pooling_ranges_and_shortcut_sums(precision, body, h, w, b):
+    """The last BatchNorm apply done by the pooling kernel where few images are pooled in several ranges of pixels (plain, identity
+    and projection shortcut), and the sums of a projection shortcut's BatchNorm made with its block output's."""
+    _against_float64(body + [W.gap_linear_ce(body[-1].cout, 10)], b, h, w, precision)
 
 
 @pytest.mark.parametrize("precision", [W.FP32, W.FP16])
