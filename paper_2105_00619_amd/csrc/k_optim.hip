@@ -30,8 +30,9 @@ __global__ void __launch_bounds__(256) optim_check_kernel(const float* __restric
 }
 
 // The update pass also reports the step (loss and flags, 32 floats) to page-locked host memory: a copy of its own behind the step took
-// 3 us of it.  CHECK: few parameters (at most 16 per thread of one block): the check pass too, and with it a launch.
-constexpr int OPTIM_SMALL = 16384;
+// 3 us of it.  CHECK: few parameters (at most 8 per thread of one block): the check pass too, and with it a launch.  (A step of 83 us
+// with 3680 parameters, us less: 2.8; with 8180 1.4; with 16 280, which one CU moves too slowly, 6.5 more.)
+constexpr int OPTIM_SMALL = 8192;
 template <class T, bool HALF, bool CHECK>
 __global__ void __launch_bounds__(CHECK ? 1024 : 256) optim_update_kernel(float* __restrict__ w, float* __restrict__ v,
                                                            const float* __restrict__ g, T* __restrict__ w16,

@@ -1417,6 +1417,23 @@ def test_losses_on_either_side_of_one_launch(b, classes):
 
 
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16])
+@pytest.mark.parametrize("classes", [2, 901, 902])  # 98, 8189 and 8198 parameters: the check of the gradients in the update's launch or before it
+def test_update_of_few_parameters(precision, classes):
+    units = [W.conv(8, 8, 1), W.gap_linear_ce(8, classes)]
+    p, x, y = _inputs(units, 5, 4, 4, classes, channels=8)
+    first, second = gpu_step(units, p, x, y, precision=precision, k=1, classes=classes, lr=0.1, momentum=0.9, steps=2)[0]
+    w1 = p.astype(np.float32) - np.float32(0.1) * first["grads"]
+    v2 = np.float32(0.9) * first["grads"] + second["grads"]
+    for r, want in ((first, w1), (second, first["params"] - np.float32(0.1) * v2)):
+        assert not r["skipped"]
+        # three roundings of values below the weights' size
+        assert np.all(np.abs(r["params"] - want) <= 3 * 2.0 ** -24 * (np.abs(want) + np.abs(p)))
+    bad, _ = gpu_step(units, p, np.where(np.arange(x.size).reshape(x.shape) == 17, np.float32(np.nan), x), y, precision=precision, k=1,
+                      classes=classes, lr=0.1)
+    assert bad["skipped"] and np.array_equal(bad["params"], p.astype(np.float32))
+
+
+@pytest.mark.parametrize("precision", [W.FP32, W.BF16])
 @pytest.mark.parametrize("b", [211, 7])  # 1 053 945 values: groups of eight and one more; few: one per thread
 def test_images_at_any_address(precision, b):
     """The cast of the images reads 16 bytes at a time where they lie on 16 bytes: the same bits from any address."""
