@@ -110,6 +110,21 @@ __device__ __forceinline__ void step_begin(const StepBegin& b) {
   if (threadIdx.x < 4) b.flags[threadIdx.x] = threadIdx.x == 1 ? (any ? 1 : 0) : 0;
 }
 
+// Two transposing 64-bit LDS reads (ds_read_b64_tr_b16).  Within a group of 16 lanes every lane supplies the address
+// of 4 consecutive 16-bit elements, and lane l receives element l%4 of the addresses supplied by lanes l/4, l/4 + 4,
+// l/4 + 8, l/4 + 12.  With lane r addressing channels [4*(r%4), +4) of row r/4 (of four rows), lane l therefore ends
+// up with channel l of the 16 at those four rows.  p0 / p1 address the first / second group of four rows, so the
+// result holds 8 consecutive reduction elements (pixels) of one channel: an MFMA operand of type V.
+template <class V, class E>
+__device__ __forceinline__ V lds_tr_read8(const E* p0, const E* p1) {
+  typedef __attribute__((ext_vector_type(4))) short v4s;
+  typedef __attribute__((ext_vector_type(8))) short v8s;
+  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p0));
+  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p1));
+  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  return __builtin_bit_cast(V, r);
+}
+
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 }  // namespace oseq

@@ -26,8 +26,6 @@ typedef __attribute__((ext_vector_type(16))) float v16f;
 typedef __attribute__((ext_vector_type(4))) float v4f;
 typedef __attribute__((ext_vector_type(8))) __bf16 v8bf;
 typedef __attribute__((ext_vector_type(8))) _Float16 v8h;
-typedef __attribute__((ext_vector_type(4))) short v4s;
-typedef __attribute__((ext_vector_type(8))) short v8s;
 
 template <class T> struct Op;
 template <> struct Op<bf16_t> {
@@ -40,14 +38,6 @@ template <> struct Op<f16_t> {
   __device__ static __forceinline__ v4f mma16(V a, V b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
   __device__ static __forceinline__ v16f mma32(V a, V b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
-
-template <class T>
-__device__ __forceinline__ typename Op<T>::V tr_read8(const T* p0, const T* p1) {
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p0));
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p1));
-  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(typename Op<T>::V, r);
-}
 
 constexpr int BC = 64, BK = 256, PM = 64, NT = 512;
 constexpr int DP = BK + 16, XP = BC + 16, WP = BK + 8, OP = BC + 4;  // LDS row pitches: dz, x, weights; dx (floats)
@@ -198,11 +188,11 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
 #pragma unroll
     for (int s = 0; s < PM / 16; ++s) {
       const T* pa = Ds + (s * 16 + prow) * DP + wave * 32 + coff;
-      const V fa = tr_read8<T>(pa, pa + 4 * DP);
+      const V fa = lds_tr_read8<V>(pa, pa + 4 * DP);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const T* pb = Xs + (s * 16 + prow) * XP + j * 32 + coff;
-        acc[j] = Op<T>::mma32(fa, tr_read8<T>(pb, pb + 4 * XP), acc[j]);
+        acc[j] = Op<T>::mma32(fa, lds_tr_read8<V>(pb, pb + 4 * XP), acc[j]);
       }
     }
     __syncthreads();

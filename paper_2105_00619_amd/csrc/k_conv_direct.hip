@@ -560,8 +560,6 @@ __global__ void __launch_bounds__(256) conv_stem_wgrad_kernel(const T* __restric
                                                               FastDiv divPQ) {
   typedef typename StemMma<T>::V FV;
   typedef typename StemMma<T>::A v16f;
-  typedef __attribute__((ext_vector_type(4))) short v4s;
-  typedef __attribute__((ext_vector_type(8))) short v8s;
   constexpr int RSC = 9 * C, BM = STEM_BM, DP = 64 + 16, XP = BM + 8;
   constexpr int HALF = 16;  // columns gathered by each of a pixel's two threads
   static_assert(RSC <= 32, "one 32-column tile");
@@ -639,10 +637,7 @@ __global__ void __launch_bounds__(256) conv_stem_wgrad_kernel(const T* __restric
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const T* pp = ds + (p0 + (r16 >> 2)) * DP + i * 32 + coff;
-        const v4s u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(pp));
-        const v4s u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(pp + 4 * DP));
-        const v8s u = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
-        acc[i] = StemMma<T>::run(__builtin_bit_cast(FV, u), b, acc[i]);
+        acc[i] = StemMma<T>::run(lds_tr_read8<FV>(pp, pp + 4 * DP), b, acc[i]);
       }
     }
     __syncthreads();

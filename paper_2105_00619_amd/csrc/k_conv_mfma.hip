@@ -493,7 +493,7 @@ constexpr int PATCH_MAX_POS = 256;  // positions per sub-tile
 
 // least and most wavefronts per SIMD that the registers are to leave room for
 template <class X> constexpr int PATCH_WAVES(int bn, int mi, int most) {
-  if (std::is_same_v<X, Split32>) return mi == 1 ? 3 : bn == 64 ? 2 : 1 + most;
+  if (std::is_same_v<X, Split32>) return mi == 1 ? 3 : 2;  // (64 channels per block only)
   return bn == 64 ? 3 : 1 + most;
 }
 
@@ -1102,8 +1102,10 @@ static void launch_patch_t(hipStream_t st, const void* src, const void* wmat, co
   }
   if (sizeof(T) != 2 || !a.fold) {
     if (v.mi == 2) {
-      if (v.bn == 128) launch_patch_v<T, X, 128, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
-      else launch_patch_v<T, X, 64, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+      if constexpr (!std::is_same_v<X, Split32>) {
+        if (v.bn == 128) launch_patch_v<T, X, 128, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
+      }
+      if (v.bn == 64) launch_patch_v<T, X, 64, 2, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
     } else {
       launch_patch_v<T, X, 64, 1, 1, false>(st, src, wmat, bias, addend, out, partial, stat_partial, sp, a);
     }
@@ -1139,7 +1141,8 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
   // blocks 10.4 -> 8.0, 32 x 1 x 2 11.8 -> 8.7), or where four classes of different depth share few (32 x 2 x 4 23.6 -> 20.7); a
   // block per CU of equal depth keeps them (64 x 4 of 144 depth tiles 68.8 -> 74).
   const int64_t blocks128 = (int64_t)ceil_div(a.M, IGEMM_BM) * (a.Ng / 128) * (a.cls ? 4 : splits);
-  const bool wide = a.Ng % 128 == 0 && !std::is_same_v<X, Split32> && blocks128 >= (a.cls ? 512 : 256);
+  constexpr bool S32 = std::is_same_v<X, Split32>;
+  const bool wide = a.Ng % 128 == 0 && !S32 && blocks128 >= (a.cls ? 512 : 256);
   dim3 grid(ceil_div(a.M, IGEMM_BM), a.Ng / (wide ? 128 : 64), a.cls ? 4 : splits), block(256);  // cls: never split
   // A grid of at most one block per CU asks for more than half of a CU's LDS, so that no CU takes two blocks
   // while another idles.
@@ -1160,12 +1163,14 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
   if (splits > 1) {
     // (the depth ranges are stored as they are: the forward and the inference instantiation would be the same kernel)
     constexpr int MODE_ = MODE == IG_EVAL ? IG_FWD : MODE;
-    if (wide) IGEMM_LAUNCH(128, 128, true) else IGEMM_LAUNCH(128, 64, true)
+    if constexpr (!S32) { if (wide) IGEMM_LAUNCH(128, 128, true) }
+    if (!wide) IGEMM_LAUNCH(128, 64, true)
     launch_splitk_epilogue<T>(st, partial, splits, a.M, a.Ng, MODE == IG_EVAL ? nullptr : bias, addend, a.amask, out, stat_partial,
                               a.relu, MODE == IG_EVAL ? bias : nullptr);
   } else {
     constexpr int MODE_ = MODE;
-    if (wide) IGEMM_LAUNCH(128, 128, false) else IGEMM_LAUNCH(128, 64, false)
+    if constexpr (!S32) { if (wide) IGEMM_LAUNCH(128, 128, false) }
+    if (!wide) IGEMM_LAUNCH(128, 64, false)
   }
 #undef IGEMM_LAUNCH
 }
@@ -1403,17 +1408,6 @@ struct WGradArgs {
   int ranges;
 };
 
-typedef __attribute__((ext_vector_type(4))) short v4s;
-typedef __attribute__((ext_vector_type(8))) short v8s;
-// two transposing 64-bit LDS reads (see the weight-gradient kernel): 8 consecutive reduction elements of one channel
-template <class T>
-__device__ __forceinline__ v8s tr_read8(const T* p0, const T* p1) {
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p0));
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p1));
-  v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return r;
-}
-
 // WGM x WGN wavefronts (wave tile BM / WGM x BN / WGN); the 256 x 256 tile of the 1x1 layers with many pixels runs 2 x 4
 // wavefronts, two per SIMD, one block per CU: every operand element then crosses from L2 to a CU half as often as with
 // 128 x 128 tiles (a 1024 x 256 weight gradient over 262 144 pixels moves 1.07 GB instead of 2.1 GB that way).
@@ -1605,9 +1599,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   // Operand registers, loaded in FR::PHASES parts: 16-bit the two halves (16 pixels each) of the depth tile, fp32 the planes.
-  // Transposing LDS read (ds_read_b64_tr_b16): within 16 lanes, lane r points at 4 consecutive channels of pixel
-  // k0 + r/4 starting at channel 4*(r%4); lane l receives channel l of the 16 at pixels k0..k0+3.  Two reads give
-  // 8 pixels for channel (tile base + l32).
+  // (lds_tr_read8: 8 pixels for channel tile base + l32.)
   FR fa[MI], fb[NI];
   const int r16 = l32 & 15;
   const int coff = (l32 & 16) + 4 * (r16 & 3);
@@ -1618,10 +1610,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) conv_wgrad_kernel(const T* __r
     const E* sb = lds + stage * STAGE + A_ELEMS + (F32 ? part * B_PL : 0) + px * (BN + PADE) + wn * WTN + coff;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
-      fa[i].p[part] = __builtin_bit_cast(std::remove_reference_t<decltype(fa[i].p[part])>, tr_read8(sa + i * 32, sa + i * 32 + 4 * (BM + PADE)));
+      fa[i].p[part] = lds_tr_read8<std::remove_reference_t<decltype(fa[i].p[part])>>(sa + i * 32, sa + i * 32 + 4 * (BM + PADE));
 #pragma unroll
     for (int j = 0; j < NI; ++j)
-      fb[j].p[part] = __builtin_bit_cast(std::remove_reference_t<decltype(fb[j].p[part])>, tr_read8(sb + j * 32, sb + j * 32 + 4 * (BN + PADE)));
+      fb[j].p[part] = lds_tr_read8<std::remove_reference_t<decltype(fb[j].p[part])>>(sb + j * 32, sb + j * 32 + 4 * (BN + PADE));
   };
 
   // pipeline as in the forward kernel: three LDS stages, two register generations, operand reload under the MFMAs

@@ -37,8 +37,6 @@ namespace {
 typedef __attribute__((ext_vector_type(16))) float v16f;
 typedef __attribute__((ext_vector_type(8))) __bf16 v8bf;
 typedef __attribute__((ext_vector_type(8))) _Float16 v8h;
-typedef __attribute__((ext_vector_type(4))) short v4s;
-typedef __attribute__((ext_vector_type(8))) short v8s;
 
 struct W9Args {
   int N, H, W, C, K, P, Q, pad;
@@ -76,19 +74,6 @@ template <class T> struct V8;
 template <> struct V8<bf16_t> { typedef v8bf type; };
 template <> struct V8<f16_t> { typedef v8h type; };
 template <> struct V8<float> { typedef v8bf type; };
-
-// Two transposing 64-bit LDS reads (ds_read_b64_tr_b16).  Within a group of 16 lanes every lane supplies the address
-// of 4 consecutive 16-bit elements, and lane l receives element l%4 of the addresses supplied by lanes l/4, l/4 + 4,
-// l/4 + 8, l/4 + 12.  With lane r addressing channels [4*(r%4), +4) of row r/4 (of four rows), lane l therefore ends
-// up with channel l of the 16 at those four rows.  p0 / p1 address the first / second group of four rows, so the
-// result holds 8 consecutive reduction elements (pixels) of one channel: an MFMA operand.
-template <class T, class E>
-__device__ __forceinline__ typename V8<T>::type tr_read8(const E* p0, const E* p1) {
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p0));
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p1));
-  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(typename V8<T>::type, r);
-}
 
 // WHOLE: every sub-tile is TI whole images (small images: 8 x 8, 4 x 4).  The (row, column) part of a chunk's address and
 // of its bounds check is then the same for every sub-tile: a chunk keeps its pixel index within the sub-tile, the
@@ -378,12 +363,12 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int q = 0; q < 3; ++q) fa[i][q] = tr_read8<T>(td + q * L::DS + ma * PK + i * 32, td + q * L::DS + mb * PK + i * 32);
+          for (int q = 0; q < 3; ++q) fa[i][q] = lds_tr_read8<typename V8<T>::type>(td + q * L::DS + ma * PK + i * 32, td + q * L::DS + mb * PK + i * 32);
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
           v8bf fb[3];
 #pragma unroll
-          for (int q = 0; q < 3; ++q) fb[q] = tr_read8<T>(xa + q * XS + toff[tap], xb + q * XS + toff[tap]);
+          for (int q = 0; q < 3; ++q) fb[q] = lds_tr_read8<typename V8<T>::type>(xa + q * XS + toff[tap], xb + q * XS + toff[tap]);
           constexpr int QA[6] = {2, 0, 1, 1, 0, 0}, QB[6] = {0, 2, 1, 0, 1, 0};  // the smallest first
 #pragma unroll
           for (int q = 0; q < 6; ++q)
@@ -399,10 +384,10 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         const T* xb = tx + apos[mb] * PX;
         typename V8<T>::type fa[MI];
 #pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i] = tr_read8<T>(td + ma * PK + i * 32, td + mb * PK + i * 32);
+        for (int i = 0; i < MI; ++i) fa[i] = lds_tr_read8<typename V8<T>::type>(td + ma * PK + i * 32, td + mb * PK + i * 32);
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
-          const typename V8<T>::type fb = tr_read8<T>(xa + toff[tap], xb + toff[tap]);
+          const typename V8<T>::type fb = lds_tr_read8<typename V8<T>::type>(xa + toff[tap], xb + toff[tap]);
 #pragma unroll
           for (int i = 0; i < MI; ++i) acc[i][tap] = mfma16(fa[i], fb, acc[i][tap]);
         }
