@@ -236,10 +236,11 @@ struct Span { uint64_t bytes; int first, last; uint64_t offset; };
 // arena's size.  First in the order of the steps, each at the tightest hole.  Where that leaves holes that a later tensor does
 // not fit (a workspace between kept tensors), also one tensor after the other, each at the lowest offset that is free while it is
 // alive, in these orders: the largest first; those alive at the fullest step ahead of the others; those ahead with most bytes
-// times steps; the order of the steps; the longest alive first; the largest first with every size weighted by a fixed number between
-// a half and one and a half, ways - 5 times over; each also with the tensor that ended up on top ahead of all others, seven times.  The
-// smallest result is kept; the search ends at one of `enough` bytes, mostly at once.
-uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough, int ways = 24) {
+// times steps; the order of the steps; the longest alive first; each also with the tensor that ended up on top ahead of all others,
+// seven times.  The smallest result is kept; the search ends at one of `enough` bytes.  longer: also the largest first with every
+// size weighted by a fixed number between a half and one and a half, 395 times over.  most_alive (or null): what no placement can
+// go below.
+uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough, bool longer = false, uint64_t* most_alive = nullptr) {
   const int n = (int)spans.size();
   std::vector<std::vector<int>> dies(n_steps);
   for (int i = 0; i < n; ++i) dies[spans[i].last].push_back(i);
@@ -254,11 +255,12 @@ uint64_t place(std::vector<Span>& spans, int n_steps, uint64_t enough, int ways 
     if (alive > least) { least = alive; fullest = t; }
     for (int i : dies[t]) { fl.release(spans[i].offset, spans[i].bytes); alive -= spans[i].bytes; }
   }
+  if (most_alive) *most_alive = least;
   uint64_t best = fl.high_;
   enough = std::max(enough, least);
   std::vector<int> order(n), placed;  // placed: by offset
   std::vector<uint64_t> at(n);
-  for (int way = 0; way < ways && best > enough; ++way) {
+  for (int way = 0; way < (longer ? 400 : 5) && best > enough; ++way) {
     auto ahead = [&](int i) { return way == 1 && spans[i].first <= fullest && spans[i].last >= fullest; };
     auto weight = [&](int i) -> uint64_t {
       const uint64_t steps = (uint64_t)(spans[i].last - spans[i].first + 1);
@@ -783,13 +785,14 @@ bool build_schedule(Plan& p, uint64_t enough) {
       if (p.insts[t].held) held_b -= p.insts[t].bytes;
     }
   }
-  p.arena_bytes = place(spans, n, enough);
-  if (!p.separate && p.arena_bytes > enough) {
+  uint64_t most_alive = 0;
+  p.arena_bytes = place(spans, n, enough, false, &most_alive);
+  if (!p.separate && p.arena_bytes > std::max(enough, most_alive)) {
     // merged passes hold no more at any step, but may be placed worse: then a longer search, so that what a budget allowed without
-    // them it allows with them (of 40 000 random networks 29 are still larger, by up to 2 % or some KB)
+    // them it allows with them (of 40 000 random networks 33 are still larger, by up to 2 % or some KB)
     Plan q = p;
     q.separate = true;
-    if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), 400);
+    if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), true);
   }
   for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
   return true;
@@ -816,21 +819,28 @@ static bool fullest_moments(Plan& q, int mode, std::vector<int64_t>& alive, std:
 
 void choose_sums(Plan& p, const Plan& folded) {
   const size_t nu = p.units.size();
-  std::vector<char> chosen(nu, 0);
+  bool inside = false, shortcut = false;
+  for (const FOp& f : p.fops) {
+    inside = inside || f.dgrad_sums > 0 || f.bwd_splits > 0;
+    shortcut = shortcut || (f.skip >= 0 && f.skip != p.unit_in[f.unit]);
+  }
+  p.unit_sums.assign(nu, 0);
+  std::vector<int64_t> alive, with, before[3];
   for (char which : {SUMS_INSIDE, SUMS_SHORTCUT}) {  // (the sums of a shortcut's BatchNorm are alive for longer)
+    if (!(which == SUMS_INSIDE ? inside : shortcut)) continue;
     std::vector<char> ok(nu, 1);
     for (int mode = 0; mode < 3; ++mode) {
-      std::vector<int64_t> alive, before, with;
-      Plan q = mode == 2 ? p : folded, r = q;
+      Plan q = mode == 2 ? p : folded;
       q.separate = true;
-      r.unit_sums = chosen;
-      for (char& u : r.unit_sums) u = (char)(u | which);
-      if (!fullest_moments(q, mode, alive, before) || !fullest_moments(r, mode, alive, with)) return;
-      for (size_t u = 0; u < nu; ++u) ok[u] = ok[u] && with[u] <= before[u];
+      if (before[mode].empty() && !fullest_moments(q, mode, alive, before[mode])) return;
+      q.separate = false;
+      q.unit_sums = p.unit_sums;
+      for (char& u : q.unit_sums) u = (char)(u | which);
+      if (!fullest_moments(q, mode, alive, with)) return;
+      for (size_t u = 0; u < nu; ++u) ok[u] = ok[u] && with[u] <= before[mode][u];
     }
-    for (size_t u = 0; u < nu; ++u) if (ok[u]) chosen[u] = (char)(chosen[u] | which);
+    for (size_t u = 0; u < nu; ++u) if (ok[u]) p.unit_sums[u] = (char)(p.unit_sums[u] | which);
   }
-  p.unit_sums = chosen;
 }
 
 std::vector<int64_t> wgrad_room(const Plan& p) {
