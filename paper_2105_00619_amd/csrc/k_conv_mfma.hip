@@ -935,7 +935,9 @@ static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchA
   return true;
 }
 // The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (64 of 128 on maps of 63 columns or
-// more), the narrower one that covers the map with the fewest sub-tiles, then staged positions.
+// more), the narrower one that covers the map with the fewest sub-tiles, then staged positions.  (bf16, us, without -> with: two forward
+// passes of 128 channels at 16 x 64 x 64 132 -> 85, a data gradient of them 80 -> 54, at 8 x 112 x 112 200 -> 135 and 122 -> 87; 256
+// channels at 2 x 100 x 75 114 -> 70 and 54 -> 33.)
 static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, PatchArgs& a) {
   bool ok = patch_geometry_of(N, dstH, dstW, dstW < cap ? dstW : cap, cap, a);
   if (!narrow || (ok && a.TP * 4 >= cap * 3)) return ok;
@@ -1139,7 +1141,8 @@ static void launch_igemm_t(hipStream_t st, const void* src, const void* wmat, co
   a.kt_per_split = ceil_div(a.Kg / bk, splits);
   // 64 channels per block where 128 leave CUs without one, or two in turn (us, 128 -> 64: inference at batch 16, 18 layers, 2 x 4 x 9
   // blocks 10.4 -> 8.0, 32 x 1 x 2 11.8 -> 8.7), or where four classes of different depth share few (32 x 2 x 4 23.6 -> 20.7); a
-  // block per CU of equal depth keeps them (64 x 4 of 144 depth tiles 68.8 -> 74).
+  // block per CU of equal depth keeps them (64 x 4 of 144 depth tiles 68.8 -> 74).  fp32 forward: 64 x 2 blocks of 8 depth tiles
+  // 16.9 -> 12.6, 32 x 1 x 4 20.6 -> 15.9, of nineteen layers none slower.
   const int64_t blocks128 = (int64_t)ceil_div(a.M, IGEMM_BM) * (a.Ng / 128) * (a.cls ? 4 : splits);
   constexpr bool S32 = std::is_same_v<X, Split32>;
   const bool wide = a.Ng % 128 == 0 && !S32 && blocks128 >= (a.cls ? 512 : 256);
@@ -1200,6 +1203,8 @@ static int igemm_splits(int dt, int64_t M, int Ng, int Kg) {
 // 32 768 pixels 48 -> 33 us): another rounding decides some ReLUs and maxima within 1e-6 of a tie the other way, each of which
 // moves the gradients below it by its share of their sums, and over few pixels that is no small one -- a step of the 11-layer
 // network at batch 128 moves by 4e-4 to 9e-3, at 512 x 512 by 2e-5 -- where the same decisions reproduce it to 1e-6.
+// So the line is a choice between those two and no bound of speed or accuracy; a sample's sums are rounded the one way in a batch
+// below it and the other way in one above.
 static bool fwd_split32(int dt, const ConvGeom& g) { return dt == DT_F32 && (int64_t)g.N * g.P * g.Q >= 131072; }
 static bool fwd_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride); }
 static bool dgrad_ws3x3(int dt, const ConvGeom& g) { return conv_ws3x3_ok(dt, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride); }

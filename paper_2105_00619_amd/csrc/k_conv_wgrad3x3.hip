@@ -516,7 +516,8 @@ bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, W9Args& a)
   return true;
 }
 // The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (512 columns: 32 of 64 with 102
-// staged positions), the narrower one that covers the map with the fewest sub-tiles, then staged positions.
+// staged positions), the narrower one that covers the map with the fewest sub-tiles, then staged positions.  (bf16, three layers of
+// 128 channels at 8 x 112 x 112 232 -> 158 us without -> with, at 16 x 64 x 64 151 -> 137.)
 bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
   bool ok = w9_geometry_of(N, P, Q, Q < cap ? Q : cap, cap, maxpos, a);
   if (ok && a.TP * 4 >= cap * 3) return ok;
