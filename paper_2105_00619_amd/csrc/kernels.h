@@ -161,8 +161,8 @@ void launch_conv_wgrad_mfma(hipStream_t st, int dt, const void* x, const void* d
 // x, fold, partial, splits as for the weight gradient, wt, dx as for the data gradient
 bool conv_bwd1x1_ok(int dt, const ConvGeom& g);
 int conv_bwd1x1_splits(const ConvGeom& g);
-void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* z, const void* mask, const float* stats, const float* coef,
-                        int relu, int per_image, const void* x, const float* fold, const void* wt, void* dx, float* dw, float* partial,
+void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* mask, const float* stats, const float* coef, int relu,
+                        int per_image, const void* x, const float* fold, const void* w, const void* wt, void* dx, float* dw, float* partial,
                         int splits, const ConvGeom& g, float* sums);
 // sums (null, or with fold): as DgradSums::partial for the folded BatchNorm, [splits][2][C_in]
 // adds the pixel ranges' partial sums [splits][n] in order
