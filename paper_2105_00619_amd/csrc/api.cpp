@@ -96,6 +96,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         if (f.wgrad_algo == ALGO_MFMA) f.wgrad_splits = conv_mfma_wgrad_splits(dt, g, 0);
         if (f.wgrad_algo == ALGO_SMALLC) f.wgrad_splits = conv_smallc_wgrad_splits(dt, g, 0);
         if (f.has_bn && !f.has_bias && conv_bwd1x1_ok(dt, g)) f.bwd_splits = conv_bwd1x1_splits(g);
+        if (conv_again_ok(dt, g)) f.again_rows = conv_again_sum_blocks();
         if (f.dgrad_algo == ALGO_MFMA) f.dgrad_sums = conv_dgrad_sum_blocks(dt, g);
         f.image_addend = f.dgrad_algo == ALGO_MFMA && conv_dgrad_image_addend_ok(dt, g);
         if (f.has_bn && f.fwd_algo == ALGO_MFMA) f.stat_blocks = conv_mfma_fwd_stat_blocks(dt, g, f.has_bias != 0);
@@ -160,6 +161,7 @@ extern "C" int optorch_seq_create(const optorch_unit_t* units, int32_t n_units, 
         }
       }
     }
+    choose_again(p, folded);
     choose_sums(p, folded);
     folded.unit_sums = p.unit_sums;
     if (p.cfg.storage_mode != 2) p = folded;
@@ -354,7 +356,10 @@ void run_op(const Ctx& c, const SOp& s) {
         launch_cast_in(st, dt, c.x, c.at(s.out[0]), (int64_t)f.N * f.H * f.W * f.C, c.begin);
       break;
     case S_CONV_FWD:
-      if (f.fwd_algo == ALGO_MFMA)
+      if (s.again && s.phase == PH_REPLAY) break;  // (the statistics are kept, and nothing reads the output)
+      if (s.again)
+        launch_conv_again_stats(st, dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.wc(f.w_off), (float*)c.at(s.out[2]), geom(f));
+      else if (f.fwd_algo == ALGO_MFMA)
         launch_conv_fwd_mfma(st, dt, c.at(s.in[0]), c.wc(f.w_off), f.has_bias ? c.w32(f.b_off) : nullptr, c.at(s.out[0]),
                              (float*)c.at(s.out[1]), (float*)c.at(s.out[2]), f.fwd_splits, geom(f), f.relu,
                              (const float*)c.at(s.in[1]));
@@ -376,6 +381,17 @@ void run_op(const Ctx& c, const SOp& s) {
                         c.touch_running ? (float*)(h->pbase + h->off_run) + f.rs_off : nullptr, c.flags());
       break;
     case S_BN_APPLY:
+      if (s.again) {
+        const FOp& cv = h->plan.fops[s.fop - 2];
+        const AgainSource z{c.at(s.src[0]), (const float*)c.at(s.src[1]), c.wc(cv.w_off), (const float*)c.at(s.in[1])};
+        if (f.again_skip >= 0) {
+          const AgainSource proj{c.at(s.src[2]), (const float*)c.at(s.src[3]), c.wc(h->plan.fops[f.again_skip - 2].w_off), (const float*)c.at(s.in[3])};
+          launch_bn_apply_again(st, dt, z, nullptr, &proj, c.at(s.out[0]), c.at(s.out[2]), geom(cv));
+        } else {
+          launch_bn_apply_again(st, dt, z, c.at(s.in[2]), nullptr, c.at(s.out[0]), c.at(s.out[2]), geom(cv));
+        }
+        break;
+      }
       if (s.out[1] >= 0)  // with the 2x2 max-pool that follows
         launch_bn_apply_pool(st, dt, c.at(s.in[0]), (const float*)c.at(s.in[1]), c.at(s.out[0]), c.at(s.out[1]), f.N, f.P,
                              f.Q, f.C, f.relu);
@@ -403,6 +419,22 @@ void run_op(const Ctx& c, const SOp& s) {
       if (s.variant == 1) {  // in[0] is the gradient of the max-pool behind the activation
         launch_bn_bwd_pool(st, dt, c.at(s.in[0]), c.at(s.in[1]), (const float*)c.at(s.in[2]), f.N, f.P, f.Q, f.C, f.relu,
                            f.red_blocks, (float*)c.at(s.out[2]), c.g32(f.gamma_off), c.g32(f.beta_off), c.at(s.out[0]));
+        break;
+      }
+      if (s.again) {  // the sums (unless they came with the gradient), then their finishing step
+        const FOp& cv = h->plan.fops[s.fop - 2];
+        float* ws = (float*)c.at(s.in[4] >= 0 ? s.in[4] : s.out[2]);
+        if (s.in[4] < 0) {
+          const AgainSource z{c.at(s.src[0]), (const float*)c.at(s.src[1]), c.wc(cv.w_off), (const float*)c.at(s.in[2])};
+          if (s.out[3] >= 0) {
+            const AgainSource proj{c.at(s.src[2]), (const float*)c.at(s.src[3]), c.wc(h->plan.fops[f.again_skip - 2].w_off), (const float*)c.at(s.in[6])};
+            launch_bn_bwd_sums_again(st, dt, c.at(s.in[0]), c.at(s.in[3]), z, &proj, ws, (float*)c.at(s.out[3]), geom(cv));
+          } else {
+            launch_bn_bwd_sums_again(st, dt, c.at(s.in[0]), c.at(s.in[3]), z, nullptr, ws, nullptr, geom(cv));
+          }
+        }
+        launch_bn_bwd(st, dt, nullptr, nullptr, nullptr, nullptr, (const float*)c.at(s.in[2]), (int64_t)f.N * f.P * f.Q, f.C, f.relu,
+                      s.rows, ws, c.g32(f.gamma_off), c.g32(f.beta_off), nullptr, nullptr, 0, true);
         break;
       }
       // in[3]: the block output whose sign gives the ReLU decisions, or (variant 2) those decisions as a bit mask
@@ -478,7 +510,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
   *flops = 0; *bytes = 0;
   switch (s.kind) {
     case S_CAST_IN: *bytes = in_px * f.C * ((h->x_encoded ? 1 : 4) + e); break;  // an encoded batch: one byte per pixel
-    case S_CONV_FWD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + out_px * f.K + wts); break;
+    case S_CONV_FWD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + (s.again ? 0.0 : out_px * f.K) + wts); break;
     case S_DGRAD:
       *flops = 2 * out_px * wts;
       *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0) +
@@ -488,6 +520,9 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
     case S_BN_STATS: *bytes = s.in[1] >= 0 ? 8.0 * f.stat_blocks * f.C : e * out_px * f.C; break;  // fused: only the block sums
     case S_BN_APPLY:
       if (s.out[1] >= 0) *bytes = e * out_px * f.C * (1.0 + (s.out[0] >= 0 ? 1.0 : 0.0) + 0.25);  // z, [a], pooled
+      else if (s.again)  // the inputs of the layers in place of their outputs
+        *bytes = e * out_px * (f.C * ((f.again_skip >= 0 ? 1 : 2) + (s.out[2] >= 0 ? 1.0 / 16 : 0)) +
+                               h->plan.fops[s.fop - 2].C * (f.again_skip >= 0 ? 2 : 1));
       else *bytes = e * out_px * f.C * ((s.in[2] >= 0 ? 3 : 2) + (s.out[2] >= 0 ? 1.0 / 16 : 0));  // + the ReLU bit mask
       break;
     case S_BN_BWD:
@@ -499,6 +534,7 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
           *bytes = s.out[0] < 0 ? 8.0 * s.rows * f.C : e * out_px * f.C * (2 + da + src + (s.out[1] >= 0 ? 1 : 0));
           break;
         }
+        if (s.again) { *bytes = e * out_px * (f.C * (da + src) + h->plan.fops[s.fop - 2].C * (s.out[3] >= 0 ? 2 : 1)); break; }
         if (s.out[0] < 0) { *bytes = e * out_px * f.C * (1 + (s.out[3] >= 0 ? 1 : 0) + da + src); break; }  // (the sums only)
         *bytes = e * out_px * f.C * (1 + (s.out[3] >= 0 ? 1 : 0) + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }

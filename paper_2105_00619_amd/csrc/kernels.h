@@ -165,6 +165,21 @@ void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* mask
                         int per_image, const void* x, const float* fold, const void* w, const void* wt, void* dx, float* dw, float* partial,
                         int splits, const ConvGeom& g, float* sums);
 // sums (null, or with fold): as DgradSums::partial for the folded BatchNorm, [splits][2][C_in]
+// 1x1 layers whose output z (in front of a BatchNorm) is never in memory: made again from the layer's input by whoever reads it
+// (k_conv_again.hip).  x, fold, w: the layer's input, the statistics of a BatchNorm to fold into it (or null), the weights; stats:
+// those of the BatchNorm behind the layer
+struct AgainSource { const void* x; const float* fold; const void* w; const float* stats; };
+bool conv_again_ok(int dt, const ConvGeom& g);
+// the layer's forward pass: its channel sums only (stat_partial as launch_conv_fwd_mfma leaves it)
+void launch_conv_again_stats(hipStream_t st, int dt, const void* x, const float* fold, const void* w, float* stat_partial, const ConvGeom& g);
+// the apply pass with ReLU and a skip connection: the tensor skip, or the BatchNorm of a projection shortcut (proj)
+void launch_bn_apply_again(hipStream_t st, int dt, const AgainSource& z, const void* skip, const AgainSource* proj, void* out, void* mask,
+                           const ConvGeom& g);
+// rows of sums, [conv_again_sum_blocks()][2][C_out], for launch_bn_bwd (summed) from dA and its ReLU decisions as bits; with proj
+// also the shortcut's, into ws2
+int conv_again_sum_blocks();
+void launch_bn_bwd_sums_again(hipStream_t st, int dt, const void* da, const void* mask, const AgainSource& z, const AgainSource* proj,
+                              float* ws, float* ws2, const ConvGeom& g);
 // adds the pixel ranges' partial sums [splits][n] in order
 void launch_wgrad_reduce(hipStream_t st, const float* partial, float* out, int64_t n, int splits);
 // Transposed weight copies for the data-gradient GEMMs, all layers in one launch (per 48 layers).  w_off: element

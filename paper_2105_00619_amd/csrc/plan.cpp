@@ -391,6 +391,23 @@ struct Scheduler {
     return ap.unit >= p.seg_begin[seg] && head.unit < p.seg_begin[seg + 1];
   }
 
+  // Is z, the output of convolution f or the input of the BatchNorm apply f, not written in this phase?  (In storage mode 2 a
+  // projection shortcut's BatchNorm has an apply pass of its own, which reads it.)
+  bool unwritten(const FOp& f, int phase) const {
+    return f.again && !p.separate && p.cfg.storage_mode != 2 && p.z_written < (phase == PH_FWD_NOSAVE ? 1 : 2);
+  }
+  // What the z of a FOp::again convolution is made again from: its input tensor t or, with its statistics, the z of the BatchNorm
+  // that t is the output of -- whichever is alive anyway where the pass keeps something for backward.
+  void again_source(int t, int unit, int phase, int seg, int* src) const {
+    const int fa = bn_apply_of[t];
+    if (fa >= 0 && (p.fops[fa].unit == unit ||
+                    (p.cfg.storage_mode == 1 && phase != PH_FWD_NOSAVE && p.fops[fa].skip < 0 && p.fops[fa].unit >= p.seg_begin[seg]))) {
+      src[0] = cur[p.fops[fa].x]; src[1] = cur[p.fops[fa].stats];
+    } else {
+      src[0] = cur[t];
+    }
+  }
+
   void emit_fop_forward(int fi, int phase, int seg) {
     const FOp& f = p.fops[fi];
     switch (f.kind) {
@@ -399,6 +416,7 @@ struct Scheduler {
         SOp& s = push(S_CONV_FWD, fi, phase, seg);
         s.in[0] = cur[f.x];
         if (f.fold_src >= 0) { s.in[0] = cur[p.fops[f.fold_src].x]; s.in[1] = cur[p.fops[f.fold_src].stats]; }
+        s.again = unwritten(f, phase);
         s.out[0] = value_inst(f.out);
         if (f.fwd_splits > 1) s.out[1] = new_inst(-1, (uint64_t)f.fwd_splits * f.N * f.P * f.Q * f.K * 4, false);
         if (f.stat_blocks > 0 && phase != PH_REPLAY) {  // per-block channel sums for the BatchNorm that follows
@@ -421,6 +439,11 @@ struct Scheduler {
         SOp& s = push(S_BN_APPLY, fi, phase, seg);
         s.in[0] = cur[f.x]; s.in[1] = cur[f.stats]; s.in[2] = f.skip >= 0 ? cur[f.skip] : -1;
         if (f.fold_skip >= 0) { s.in[2] = cur[p.fops[f.fold_skip].x]; s.in[3] = cur[p.fops[f.fold_skip].stats]; }
+        if (unwritten(f, phase)) {
+          s.again = true;
+          again_source(p.fops[fi - 2].x, f.unit, phase, seg, s.src);
+          if (f.again_skip >= 0) again_source(p.fops[f.again_skip - 2].x, f.unit, phase, seg, s.src + 2);
+        }
         s.out[0] = value_inst(f.out);
         if (pool_fused(fi + 1, seg)) s.out[1] = value_inst(p.fops[fi + 1].out);  // the same kernel also pools
         if (f.mask >= 0) s.out[2] = value_inst(f.mask);
@@ -553,10 +576,12 @@ struct Scheduler {
         if (gin < 0) { p.error = "internal: BN output has no gradient"; return false; }
         if (f.skip >= 0 && !f.relu) { p.error = "skip connection without ReLU is not supported"; return false; }
         const int gin_mask = gmask[f.out];  // the incoming gradient still wants a mask (projection shortcut's BatchNorm)
+        const bool again = f.again && !p.separate;
         SOp& s = push(S_BN_BWD, fi, PH_BWD, seg);
         const size_t at = p.sched.size() - 1;
         s.variant = variant;
         s.per_image = image;
+        s.again = again;
         s.in[0] = gin; s.in[1] = cur[f.x]; s.in[2] = cur[f.stats];
         s.in[3] = (f.skip >= 0) ? cur[f.out] : -1;
         if (gin_mask >= 0) {
@@ -577,17 +602,20 @@ struct Scheduler {
           else { s.out[1] = grad_inst(f.skip); grad[f.skip] = s.out[1]; gmask[f.skip] = -1; }
         }
         SOp& b = p.sched[at];
-        b.rows = f.red_blocks;
+        if (again && (conv < 0 || b.variant != 2 || image)) { p.error = "internal: z is made again for a backward pass that reads it"; return false; }
+        b.rows = again ? p.fops[fi - 2].again_rows : f.red_blocks;
         // the BatchNorm of a projection shortcut has the same gradient and decisions (masked_skip_grad_ok): its sums in the same pass
         const int shortcut = f.skip >= 0 && b.variant == 2 ? projection_of(fi) : -1;
         if (shortcut >= 0 && gmask[f.skip] >= 0 && grad[f.skip] == b.in[0] && f.C % (16 / p.esize) == 0 && sums_ok(f.unit, SUMS_SHORTCUT)) {
           const FOp& q = p.fops[shortcut];
           b.in[5] = cur[q.x]; b.in[6] = cur[q.stats];
-          b.out[3] = bn_sums[f.skip] = sums_inst(f.red_blocks, f.C);
-          bn_sum_rows[f.skip] = f.red_blocks;
+          b.out[3] = bn_sums[f.skip] = sums_inst(b.rows, f.C);
+          bn_sum_rows[f.skip] = b.rows;
+          if (again) again_source(p.fops[shortcut - 2].x, f.unit, PH_BWD, seg, b.src + 2);
         }
         if (bn_sums[f.out] >= 0 && variant == 0) { b.in[4] = bn_sums[f.out]; b.rows = bn_sum_rows[f.out]; }
-        else b.out[2] = sums_inst(f.red_blocks, f.C);
+        else b.out[2] = sums_inst(b.rows, f.C);
+        if (again && b.in[4] < 0) again_source(p.fops[fi - 2].x, f.unit, PH_BWD, seg, b.src);
         return true;
       }
       case F_CONV: {
@@ -696,7 +724,7 @@ int launches_of(const SOp& op, const FOp& f) {
     case S_BIAS_GRAD: return 2;
     case S_WGRAD: return f.wgrad_splits > 1 ? 2 : 1;
     case S_CONV_BWD: return f.bwd_splits > 1 ? 2 : 1;
-    case S_CONV_FWD: return f.fwd_splits > 1 ? 2 : 1;
+    case S_CONV_FWD: return op.again && op.phase == PH_REPLAY ? 0 : f.fwd_splits > 1 ? 2 : 1;
     case S_DGRAD: return f.dgrad_splits > 1 ? 2 : 1;
     default: return 1;
   }
@@ -733,7 +761,10 @@ static bool schedule_operations(Plan& p) {
       else if (uses[op.out[1]] == 0) op.out[1] = -1;
     }
     if (live && op.kind == S_BN_APPLY && op.out[2] >= 0 && uses[op.out[2]] == 0) op.out[2] = -1;  // the mask likewise
-    if (live) for (int x : op.in) if (x >= 0) ++uses[x];
+    if (live) {
+      for (int x : op.in) if (x >= 0) ++uses[x];
+      for (int x : op.src) if (x >= 0) ++uses[x];
+    }
   }
   // lifetimes
   for (Inst& t : p.insts) { t.def_op = -1; t.last_use = -1; t.held = false; t.allocated = false; }
@@ -741,7 +772,9 @@ static bool schedule_operations(Plan& p) {
     const SOp& op = p.sched[i];
     if (!op.live) continue;
     for (int o : op.out) if (o >= 0) { p.insts[o].def_op = i; p.insts[o].last_use = std::max(p.insts[o].last_use, i); }
-    for (int x : op.in) if (x >= 0) {
+    for (int i0 = 0; i0 < 11; ++i0) {
+      const int x = i0 < 7 ? op.in[i0] : op.src[i0 - 7];
+      if (x < 0) continue;
       Inst& t = p.insts[x];
       if (t.def_op < 0) { p.error = "internal: operation reads a tensor that was never produced"; return false; }
       t.last_use = std::max(t.last_use, i);
@@ -795,6 +828,21 @@ bool build_schedule(Plan& p, uint64_t enough) {
     if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), true);
   }
   for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
+  if (!p.separate && p.cfg.storage_mode != 2 && p.z_written == 0 && p.arena_bytes > enough &&
+      std::any_of(p.fops.begin(), p.fops.end(), [](const FOp& f) { return f.again != 0; })) {
+    // Where z is not written its source has to stay until the apply pass, which may be the fullest moment of a pass that keeps
+    // nothing: then z is written there, so that what a budget allows does not depend on it.  (The values are the same.)
+    Plan all = p;
+    all.z_written = 2;
+    if (!build_schedule(all, enough)) { p.error = all.error; return false; }
+    if (p.arena_bytes > all.arena_bytes) {
+      Plan some = p;
+      some.z_written = 1;
+      if (!build_schedule(some, enough)) { p.error = some.error; return false; }
+      p = some.arena_bytes > all.arena_bytes ? all : some;
+      p.z_written = 0;
+    }
+  }
   return true;
 }
 
@@ -840,6 +888,36 @@ void choose_sums(Plan& p, const Plan& folded) {
       for (size_t u = 0; u < nu; ++u) ok[u] = ok[u] && with[u] <= before[mode][u];
     }
     for (size_t u = 0; u < nu; ++u) if (ok[u]) p.unit_sums[u] = (char)(p.unit_sums[u] | which);
+  }
+}
+
+void choose_again(Plan& p, Plan& folded) {
+  auto relu_in_front = [&](const FOp& cv) {  // (a BatchNorm in front of the unit: the kernels fold it with its ReLU)
+    for (const FOp& f : folded.fops) if (f.kind == F_BN_APPLY && f.out == cv.x) return cv.fold_src < 0 && f.relu != 0;
+    return cv.fold_src < 0;
+  };
+  auto layer = [&](int apply, bool fold) {  // the convolution two operations ahead
+    if (apply < 2) return false;
+    const FOp& cv = folded.fops[apply - 2];
+    return cv.kind == F_CONV && cv.out == folded.fops[apply].x && cv.again_rows > 0 && cv.bwd_splits > 0 && cv.stat_blocks > 0 &&
+           cv.stat_fold == 0 && !cv.has_bias && folded.tensors[cv.x].needs_grad && (fold ? cv.fold_src >= 0 : relu_in_front(cv));
+  };
+  for (int i = 0; i < (int)folded.fops.size(); ++i) {
+    const FOp& a = folded.fops[i];
+    if (a.kind != F_BN_APPLY || a.skip < 0 || a.mask < 0 || !a.relu || a.fold || !layer(i, true)) continue;
+    if (i + 1 < (int)folded.fops.size() && folded.fops[i + 1].kind == F_HEAD) continue;  // (pooled, the gradient per image: from z)
+    int proj = -1, reader = -1;
+    for (int j = folded.unit_first_fop[a.unit]; j < folded.unit_last_fop[a.unit]; ++j) {
+      if (folded.fops[j].kind == F_BN_APPLY && folded.fops[j].out == a.skip) proj = j;
+      if (folded.fops[j].kind == F_CONV && folded.fops[j].x == a.skip) reader = j;
+    }
+    if (proj >= 0 ? a.fold_skip != proj || !layer(proj, false)
+                  : reader < 0 || folded.fops[reader].dgrad_algo != ALGO_MFMA) continue;
+    for (Plan* q : {&p, &folded}) {
+      q->fops[i].again = q->fops[i - 2].again = 1;
+      q->fops[i].again_skip = proj;
+      if (proj >= 0) q->fops[proj].again = q->fops[proj - 2].again = 1;
+    }
   }
 }
 

@@ -59,6 +59,11 @@ struct FOp {
   int image_addend = 0;      // F_CONV: 1 = the data gradient can add one row per image (the gradient of a global average pool)
   int bwd_splits = 0;        // F_CONV: pixel ranges of the kernel that does the BatchNorm backward behind it (whose sums are known) and
                              // both gradients where the schedule allows it (S_CONV_BWD), 0: there is none for its shape
+  int again_rows = 0;        // F_CONV: there are kernels for its shape that make its output z again from its input, those of the sums of
+                             // the BatchNorm backward over so many row blocks; 0: there are not
+  int again = 0;             // F_CONV, and the F_BN_APPLY behind it: they are used (choose_again) and z is never written.  Its place in
+                             // the arena stays: the plan's figures count it, and inference at the schedule's offsets writes there
+  int again_skip = -1;       // F_BN_APPLY with a skip connection, again: the F_BN_APPLY of its projection shortcut, again too, or -1
   int fwd_algo = ALGO_DIRECT, dgrad_algo = ALGO_DIRECT, wgrad_algo = ALGO_DIRECT;
   int wgrad_splits = 1;      // fixed by shape only: deterministic split of the pixel reduction
   int fwd_splits = 1, dgrad_splits = 1;  // fixed by shape only: deterministic split of the GEMM depth
@@ -111,6 +116,10 @@ struct SOp {
                     // S_BIAS_GRAD with in[1] >= 0: in[0] is the gradient behind the ReLU, in[1] the output of that; in[0]
                     // becomes the gradient in front of it, in place
                     // S_HEAD_FWD: 1 = also the BatchNorm apply operation in front of it, whose in[0..3] it has; out[5] its mask
+  bool again = false;             // FOp::again.  S_CONV_FWD makes the channel sums only, which a replay does without; S_BN_APPLY and
+                                  // S_BN_BWD (the sums) read src in place of their z's:
+  int src[4] = {-1, -1, -1, -1};  // the convolution's input and the statistics tensor of a BatchNorm to fold into it (or -1); those of
+                                  // the projection shortcut's
   int rows = 0;  // S_BN_BWD, S_CONV_BWD: rows of partial sums in the BatchNorm backward's workspace
   bool per_image = false;  // S_DGRAD: in[1] is an addend per image, [N][C]. S_BN_BWD: in[0] is the gradient per image, [N][C] (the output is only read by a global average
                            // pool).  S_HEAD_BWD: out[2] >= 0 receives it, out[0] the whole tensor where a reader needs it
@@ -143,6 +152,7 @@ struct Plan {
   std::vector<char> unit_sums;  // [unit] SUMS_INSIDE: kernels that write a gradient inside the unit also make the sums of the BatchNorm
                                 // backward in front; SUMS_SHORTCUT: the sums of a projection shortcut's BatchNorm come with its
                                 // block output's (choose_sums); empty: none
+  int z_written = 0;            // FOp::again: 0 no z is written, 1 those of passes that keep nothing, 2 all (build_schedule tries)
   bool separate = false;        // schedule every pass of the backward as an operation of its own (what choose_sums measures by)
   // partition
   std::vector<int> seg_begin;  // k+1 entries, unit indices
@@ -174,6 +184,9 @@ std::vector<int64_t> wgrad_room(const Plan& p);
 // mode (folded: the plan with its BatchNorms folded, as modes 0 and 1 run it; p without).  Likewise from the network and the kernel
 // choices so far only.
 void choose_sums(Plan& p, const Plan& folded);
+// Sets FOp::again in p and in folded (the plan with its BatchNorms folded), the same layers in both: from the network and the kernel
+// choices only.
+void choose_again(Plan& p, Plan& folded);
 // Builds the inference schedule with offsets of its own; needs the kernel choices of the convolutions (workspaces of split
 // depths).
 void build_inference(Plan& p);

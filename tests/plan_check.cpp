@@ -7,7 +7,8 @@
 //   * inference, at offsets of its own and at those of the schedule: every operation finds the activations it reads whole
 //     where it looks for them, writes neither over them nor over its own workspace, and stays inside its arena.
 // All of it twice: with the planner's defaults, and as the library's kernel choices would have it: workspaces for split depths,
-// BatchNorms folded into their readers, their backward sums made with the gradient, 1x1 layers whose backward is one kernel.
+// BatchNorms folded into their readers, their backward sums made with the gradient, 1x1 layers whose backward is one kernel or
+// whose outputs are made again where they are read.
 // Input: "k plan_mode precision batch height width channels classes storage_mode n_units" then n_units lines of
 // "kind cin cout ksize stride pad has_bn has_relu has_bias".  Output: "ok <arena> <peak_saved> <launches>" or an error.
 #include <cstdio>
@@ -38,6 +39,12 @@ static int check_schedule(const Plan& p) {
         if (x >= (int)p.insts.size()) return fail("input index out of range", i, x);
         if (!alive[x]) return fail("reads a tensor that is not alive", i, x);
       }
+    if (op.again && op.kind == S_BN_APPLY && (p.fops[op.fop].skip < 0 || op.src[0] < 0 || (p.fops[op.fop].again_skip >= 0 && op.src[2] < 0)))
+      return fail("an apply pass that makes z again has no skip connection or no source", i, -1);
+    if (op.again && op.kind == S_BN_BWD && ((op.in[4] < 0 && op.src[0] < 0) || (op.out[3] >= 0 && op.src[2] < 0) || op.in[3] < 0))
+      return fail("sums that make z again have no source or no mask", i, -1);
+    for (int x : op.src)
+      if (x >= 0 && (x >= (int)p.insts.size() || !alive[x])) return fail("makes a tensor again from one that is not alive", i, x);
     for (int o : op.out)
       if (o >= 0) {
         const Inst& t = p.insts[o];
@@ -132,6 +139,7 @@ static void choose_as_the_library(Plan& p) {
       if (f.R == 1 && f.stride == 1) {
         f.image_addend = 1;
         if (f.has_bn && !f.has_bias && f.K > f.C) f.bwd_splits = 1 + (int)i % 3;
+        if (f.has_bn && !f.has_bias && f.K > f.C) f.again_rows = 1 + (int)i % 7, f.stat_blocks = p.fops[i + 1].stat_blocks = 1 + (int)i % 2;
       } else {
         f.dgrad_sums = 1 + (int)i % 5;
       }
@@ -141,7 +149,7 @@ static void choose_as_the_library(Plan& p) {
       f.head_ws = f.head_ws_in_x ? (int64_t)(p.tensors[f.x].bytes / 4) : (int64_t)4 * f.N * (f.gap ? f.C : f.classes);
     }
   }
-  if (p.cfg.storage_mode == 2) return;
+  Plan given = p;
   for (size_t i = 0; i < p.fops.size(); ++i) {
     FOp& b = p.fops[i];
     if (b.kind != F_BN_APPLY) continue;
@@ -155,6 +163,8 @@ static void choose_as_the_library(Plan& p) {
         if (s.kind == F_BN_APPLY && s.out == b.skip && s.unit == b.unit && !s.relu && s.skip < 0) { s.fold = 1; b.fold_skip = (int)j; }
       }
   }
+  choose_again(given, p);
+  if (p.cfg.storage_mode == 2) p = given;
 }
 
 int main() {

@@ -621,6 +621,29 @@ def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w,
     assert work["conv1x1_wgrad"]["entries"] == layers - fused  # (a fused layer's counts with the data gradients)
 
 
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("relu,blocks,h,w,b", [
+    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128),  # exactly 131 072 pixels: whole tiles
+    (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121),  # ragged; the last block's output is pooled: kept
+    (True, [(64, 256), (256, 64)], 512, 255, 1), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405),  # fewer; 130 815
+    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513)])  # no ReLU in front of the projection shortcut
+def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b):
+    """Last layers and projection shortcuts of 64 -> 256 channels over 131 072 pixels or more: their outputs are never written, the
+    statistics, the apply pass and the sums of the backward pass make them again.  Against plain float64 arithmetic; k segments and
+    the three storage modes (different sources: an activation, or the z of its BatchNorm) change no bit."""
+    units = [W.conv(8, 64, 1, relu=relu)] + [W.bottleneck(i, o) for i, o in blocks] + [W.gap_linear_ce(blocks[-1][1], 10)]
+    _against_float64(units, b, h, w, precision)
+    rng = np.random.default_rng(5)
+    x, y = rng.standard_normal((b, h, w, 8)).astype(np.float32), rng.integers(0, 10, b).astype(np.int32)
+    p = W.make_params(units, h, w, perturb=True)
+    kw = dict(precision=precision, classes=10, loss_scale_init=_scale(precision))
+    want, _ = gpu_step(units, p, x, y, k=1, **kw)
+    for mode in (0, 1, 2):
+        for k in (1, 2, len(units)):
+            r, _ = gpu_step(units, p, x, y, k=k, storage_mode=mode, **kw)
+            assert r["loss"] == want["loss"] and np.array_equal(r["grads"], want["grads"]), (mode, k)
+
+
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
 @pytest.mark.parametrize("body,h,w,b", [
     ([W.conv(8, 64, 1)], 61, 67, 2), ([W.conv(8, 64, 1), W.basic_block(64, 64)], 61, 67, 2),

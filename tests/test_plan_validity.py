@@ -81,3 +81,17 @@ def test_small_odd_networks_plan_validly(checker):
             for storage_mode in (0, 1, 2):
                 for precision in (W.FP32, W.BF16):
                     _run(checker, units, k, k % 3, precision, b, h, w, 3, cl, storage_mode)
+
+
+@pytest.mark.parametrize("storage_mode", [0, 1, 2])
+def test_blocks_whose_outputs_are_made_again_plan_validly(checker, storage_mode):
+    """Bottleneck blocks with and without a projection shortcut, inside the network, at its start, behind a pool and a layer without
+    ReLU, in every partition."""
+    for front in ([W.conv(3, 8)], [W.conv(3, 8), W.maxpool()], [W.conv(3, 8, relu=False)], [W.conv(3, 8, bn=False)]):
+        units = front + [W.bottleneck(8, 32), W.bottleneck(32, 32), W.bottleneck(32, 16), W.bottleneck(16, 64), W.gap_linear_ce(64, 3)]
+        for k in range(1, len(units) + 1):
+            for plan_mode in (0, 2):
+                _run(checker, units, k, plan_mode, W.BF16, 5, 12, 12, 3, 3, storage_mode)
+    units = [W.bottleneck(8, 32), W.bottleneck(32, 32), W.bottleneck(32, 64), W.gap_linear_ce(64, 3)]
+    for k in range(1, len(units) + 1):
+        _run(checker, units, k, 0, W.FP16, 5, 12, 12, 8, 3, storage_mode)
