@@ -20,4 +20,12 @@ __device__ __forceinline__ Chunk bn_fold_chunk(const Chunk& c, const float (&sc)
   return __builtin_bit_cast(Chunk, round_vec<T, EV>(y));
 }
 
+// the same on two neighbouring values of 16 bits
+template <class T>
+__device__ __forceinline__ uint32_t bn_fold_pair(uint32_t c, float sc0, float sh0, float sc1, float sh1) {
+  const Vec<T, 2> t = __builtin_bit_cast(Vec<T, 2>, c);
+  return __builtin_bit_cast(uint32_t, from_f32x2<T>(fmaxf(bn_affine(to_f32(t.v[0]), sc0, sh0), 0.f),
+                                                    fmaxf(bn_affine(to_f32(t.v[1]), sc1, sh1), 0.f)));
+}
+
 }  // namespace oseq

@@ -21,6 +21,7 @@
 #include "dev_common.h"
 #include "epilogue.h"
 #include "kernels.h"
+#include "patch.h"
 #include "split32.h"
 
 namespace oseq {
@@ -467,28 +468,6 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const T* __restrict__ s
 //   The data gradient of a stride-1 convolution is the same computation on dz with the taps visited in reverse and
 //   the border (kh-1-pad).
 // ------------------------------------------------------------------------------------------------------------
-struct PatchArgs {
-  int N, srcH, srcW, srcC;   // gathered tensor
-  int dstH, dstW, Ng;        // pixel grid and channels of the result
-  int pad, flip;             // border of the gather; flip: weight tap index 8 - t (data gradient)
-  int TI, TR, TC, SR, SC, NPOS, TP;
-  int tiles_r, tiles_c, NT;
-  int relu;
-  int chunks_per_split;      // channel chunks per blockIdx.z (all of them when the depth is not split)
-  int row_pitch;             // bytes between staged patch rows in LDS (at least SC positions, padded against bank conflicts)
-  int patch_elems;           // elements of one staged patch buffer (its rows times row_pitch, rounded up to 16 bytes)
-  int xcd_group;             // 1: blocks are renumbered so that the row tiles of one weight slice run on one XCD;
-                             // 2: so that the channel blocks and depth ranges of one row tile do (row_blocks: row tiles)
-  int row_blocks;
-  const uint8_t* amask;      // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
-  int eval;                  // 1: the EVAL instantiation
-  int bn_sums;               // 1: STAT 2
-  int split32;               // fp32: 1: the Split32 instantiation
-  const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
-                             // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
-                             // to LDS; positions outside the image stay zero
-};
-
 constexpr int PATCH_MAX_POS = 256;  // positions per sub-tile
 
 // least and most wavefronts per SIMD that the registers are to leave room for
@@ -806,8 +785,11 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
       else if (EVAL)
         epi_eval_pass_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff);
-      else if constexpr (STAT == 2)
-        epi_bn_sums_rows_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff, ss, qq);
+      else if constexpr (STAT == 2) {
+        Vec<T, 8> zv[HR * (BN / 8) / 256];
+        epi_bn_sums_load_nt<256, T, BN, HR>(tid, n0c, addend, rowoff, zv);
+        epi_bn_sums_rows_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, zv, out, a.relu, rowoff, ss, qq);
+      }
       else
         epi_store_pass<T, BN, HR, true, STAT == 0, STAT == 1>(ep, tid, n0c, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
     }
@@ -920,14 +902,14 @@ template <class X> constexpr size_t patch_smem_max(int bn, int subt) {
 
 // tile geometry of the patch kernel for a (dstH x dstW) pixel grid gathered with a 3x3 window and sub-tiles of up to
 // `cap` pixels; false if it does not fit
-static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchArgs& a) {
+static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchArgs& a, int most = PATCH_MAX_POS) {
   int tr = cap / tc; if (tr > dstH) tr = dstH; if (tr < 1) tr = 1;
   int ti = (tr == dstH && tc == dstW) ? cap / (dstH * dstW) : 1;
   if (ti > N) ti = N; if (ti < 1) ti = 1;
-  while (ti > 1 && ti * (tr + 2) * (tc + 2) > PATCH_MAX_POS) ti /= 2;
-  while (tr > 1 && ti * (tr + 2) * (tc + 2) > PATCH_MAX_POS) --tr;
-  while (tc > 1 && ti * (tr + 2) * (tc + 2) > PATCH_MAX_POS) tc /= 2;
-  if (ti * (tr + 2) * (tc + 2) > PATCH_MAX_POS) return false;
+  while (ti > 1 && ti * (tr + 2) * (tc + 2) > most) ti /= 2;
+  while (tr > 1 && ti * (tr + 2) * (tc + 2) > most) --tr;
+  while (tc > 1 && ti * (tr + 2) * (tc + 2) > most) tc /= 2;
+  if (ti * (tr + 2) * (tc + 2) > most) return false;
   a.TI = ti; a.TR = tr; a.TC = tc; a.SR = tr + 2; a.SC = tc + 2;
   a.NPOS = ti * a.SR * a.SC; a.TP = ti * tr * tc;
   a.tiles_r = (dstH + tr - 1) / tr; a.tiles_c = (dstW + tc - 1) / tc;
@@ -938,12 +920,12 @@ static bool patch_geometry_of(int N, int dstH, int dstW, int tc, int cap, PatchA
 // more), the narrower one that covers the map with the fewest sub-tiles, then staged positions.  (bf16, us, without -> with: two forward
 // passes of 128 channels at 16 x 64 x 64 132 -> 85, a data gradient of them 80 -> 54, at 8 x 112 x 112 200 -> 135 and 122 -> 87; 256
 // channels at 2 x 100 x 75 114 -> 70 and 54 -> 33.)
-static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, PatchArgs& a) {
-  bool ok = patch_geometry_of(N, dstH, dstW, dstW < cap ? dstW : cap, cap, a);
+static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, PatchArgs& a, int most = PATCH_MAX_POS) {
+  bool ok = patch_geometry_of(N, dstH, dstW, dstW < cap ? dstW : cap, cap, a, most);
   if (!narrow || (ok && a.TP * 4 >= cap * 3)) return ok;
   for (int tc = 64; tc >= 8; tc /= 2) {
     PatchArgs b = a;
-    if (tc >= dstW || !patch_geometry_of(N, dstH, dstW, tc, cap, b)) continue;
+    if (tc >= dstW || !patch_geometry_of(N, dstH, dstW, tc, cap, b, most)) continue;
     if (!ok || b.NT < a.NT) { a = b; ok = true; }
     else if (b.NT == a.NT && b.NPOS < a.NPOS) a = b;
   }
@@ -955,7 +937,7 @@ static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, Patc
 // rows of the tile land on the banks the previous ones left free (TC = 8: 128 mod 256, TC = 4: 64, TC = 2: 32);
 // kept at SC positions when the padded rows would not fit the patch buffer.
 static constexpr int g_patch_pad_rows = 1;  // compile-time switch
-static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes) {
+static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes, int most = PATCH_MAX_POS) {
   const int base = a.SC * pos_bytes;
   int want = -1;
   if (a.TC == 8) want = 128; else if (a.TC == 4) want = 64; else if (a.TC == 2) want = 32;
@@ -963,13 +945,13 @@ static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes) {
   int rp = base / 256 * 256 + want;
   if (rp < base) rp += 256;
   const int64_t rows = (int64_t)subt * a.TI * a.SR;
-  return rows * rp <= (int64_t)subt * PATCH_MAX_POS * pos_bytes ? rp : base;
+  return rows * rp <= (int64_t)subt * most * pos_bytes ? rp : base;
 }
 
 // Block shapes of the patch kernel, largest first: {MI, SUBT, widest BN}.  The first one that gives the chip
 // `g_patch_fill` blocks is taken, else the one with the most blocks if that reaches `g_patch_min_blocks`
 // (shape-only rule, so the choice is the same on every run).
-struct PatchShape { int mi, subt, bn, splits; };
+struct PatchShape { int mi, subt, bn, splits; bool wide; };
 static constexpr int g_patch_min_blocks = 64;   // compile-time constants
 static constexpr int g_patch_fill = 512;
 static constexpr int g_patch_shapes = 0x7;      // bit i: candidate i allowed
@@ -978,16 +960,39 @@ static constexpr int g_patch_halo2 = 9;         // largest staged positions : pi
 static constexpr int g_patch_target_small = 512;  // blocks aimed at by the depth split for the smallest block shape in fp32
 static constexpr int64_t g_patch_xcd_wbytes = 4 << 20;  // XCD grouping of the blocks: least weight bytes (0: never) ...
 static constexpr int g_patch_xcd_rows = 16;              // ... and most row tiles
+// 16 bits: tiles of 256 pixels x 256 channels, else x 128, by one wavefront per SIMD (k_conv_patch_wide.hip).  A CU holds one such
+// block, so the rounds of 256 blocks have to be full: at least 85 % of their products have to be wanted ones, which leaves out
+// layers of less than 218 tiles -- one of 128 tiles would leave half of the CUs idle -- and maps that tile badly (14 x 14: 77 %).
+// Exactly 256 tiles of 256 x 128 (128 -> 128 channels at 65 536 pixels, bf16): 31.3 -> 28.8 us forward, data gradient 31.5 -> 30.6.
+static bool patch_pick_wide(int N, int dstH, int dstW, int srcC, int Ng, PatchShape& shape, PatchArgs& geo) {
+  for (int bn = 256; bn >= 128; bn /= 2) {
+    if (Ng % bn != 0) continue;
+    PatchArgs a{};
+    if (!patch_geometry(N, dstH, dstW, 256, true, a, PATCH_WIDE_MAX_POS)) continue;
+    if ((int64_t)a.TI * (dstH + 2) * (dstW + 2) * srcC >= (int64_t)1 << 30) continue;  // 32-bit offsets within a tile's images
+    const int64_t blocks = (int64_t)a.NT * (Ng / bn), offered = (blocks + 255) / 256 * 256 * 256 * bn;
+    if ((int64_t)N * dstH * dstW * Ng * 20 < offered * 17) continue;
+    const auto fits = [&] { return conv_patch_wide_lds(bn, (a.TI * a.SR * a.row_pitch + 15) / 16 * 8) <= 160 * 1024; };
+    a.row_pitch = patch_row_pitch(a, 1, 80, PATCH_WIDE_MAX_POS);
+    if (!fits()) a.row_pitch = a.SC * 80;
+    if (!fits()) continue;
+    shape = PatchShape{4, 1, bn, 1, true};
+    geo = a;
+    return true;
+  }
+  return false;
+}
 static bool patch_pick(int dt, bool split32, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride, PatchShape& shape,
                        PatchArgs& geo) {
   if (R != 3 || S != 3 || stride != 1) return false;
   if (srcC % (dt == DT_F32 ? 16 : 32) != 0 || Ng % 64 != 0) return false;
+  if (dt != DT_F32 && patch_pick_wide(N, dstH, dstW, srcC, Ng, shape, geo)) return true;
   // (Split32: 128 x 128 tiles take the LDS of a CU alone, and a layer of 128 channels at 262 144 pixels 515 us with them, 445 without)
   const int wide = Ng % 128 == 0 && !split32 ? 128 : 64;
   // Candidates, largest first.  Two co-resident blocks per CU cover each other's prologue, barriers and epilogue, and
   // measured better than one block of twice the size at every layer of the benchmark networks, so the first
   // candidate that gives g_patch_fill (two per CU) blocks is taken, else the one with the most blocks.
-  const PatchShape cand[3] = {{2, 1, wide, 1}, {2, 1, 64, 1}, {1, 1, 64, 1}};
+  const PatchShape cand[3] = {{2, 1, wide, 1, false}, {2, 1, 64, 1, false}, {1, 1, 64, 1, false}};
   int best = -1;
   int64_t best_blocks = 0;
   PatchArgs best_geo{};
@@ -1119,7 +1124,8 @@ static void launch_patch_t(hipStream_t st, const void* src, const void* wmat, co
 
 static void launch_patch(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                          float* partial, float* stat_partial, const PatchShape& v, const PatchArgs& a) {
-  if (dt == DT_F32 && a.split32) launch_patch_t<float, Split32>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
+  if (v.wide) launch_conv_patch_wide(st, dt, src, wmat, bias, addend, out, stat_partial, v.bn, a);
+  else if (dt == DT_F32 && a.split32) launch_patch_t<float, Split32>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
   else if (dt == DT_F32) launch_patch_t<float, float>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
   else if (dt == DT_BF16) launch_patch_t<bf16_t, bf16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);
   else launch_patch_t<f16_t, f16_t>(st, src, wmat, bias, addend, out, partial, stat_partial, v, a);

@@ -1,0 +1,40 @@
+// What the two kernels for 3x3 layers of stride 1 that stage a patch of the input share (k_conv_mfma.hip, k_conv_patch_wide.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "fastdiv.h"
+
+namespace oseq {
+
+struct PatchArgs {
+  int N, srcH, srcW, srcC;   // gathered tensor
+  int dstH, dstW, Ng;        // pixel grid and channels of the result
+  int pad, flip;             // border of the gather; flip: weight tap index 8 - t (data gradient)
+  int TI, TR, TC, SR, SC, NPOS, TP;
+  int tiles_r, tiles_c, NT;
+  int relu;
+  int chunks_per_split;      // channel chunks per blockIdx.z (all of them when the depth is not split)
+  int row_pitch;             // bytes between staged patch rows in LDS (at least SC positions, padded against bank conflicts)
+  int patch_elems;           // elements of one staged patch buffer (its rows times row_pitch, rounded up to 16 bytes)
+  int xcd_group;             // 1: blocks are renumbered so that the row tiles of one weight slice run on one XCD;
+                             // 2: so that the channel blocks and depth ranges of one row tile do (row_blocks: row tiles)
+  int row_blocks;
+  const uint8_t* amask;      // data gradient with an addend: ReLU bit mask the addend is multiplied by, or null
+  int eval;                  // 1: the EVAL instantiation
+  int bn_sums;               // 1: STAT 2
+  int split32;               // fp32: 1: the Split32 instantiation
+  const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
+                             // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
+                             // to LDS; positions outside the image stay zero
+  // k_conv_patch_wide.hip: positions of a patch's image and of its row, pixels of a tile's image and of its row, tiles
+  FastDiv div_image, div_row, div_tile, div_tcol, div_tiles_r, div_tiles_c;
+};
+
+// block tiles of 256 pixels x bn (256 or 128) channels by one wavefront per SIMD (k_conv_patch_wide.hip)
+constexpr int PATCH_WIDE_MAX_POS = 576;  // positions of its patch
+size_t conv_patch_wide_lds(int bn, int patch_elems);
+void launch_conv_patch_wide(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
+                            float* stat_partial, int bn, const PatchArgs& a);
+
+}  // namespace oseq

@@ -622,6 +622,38 @@ def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w,
 
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("channels,h,w,b", [
+    (128, 16, 16, 256), (256, 8, 8, 1024),  # exactly 256 tiles of 256 x 128 and of 256 x 256
+    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (512, 8, 8, 511), (128, 16, 16, 217)])
+def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
+    """3x3 layers on tiles of 256 pixels: one image, several, parts of one, a ragged last tile, two channel blocks; in 512 channels and
+    at 217 images fewer tiles than fill the chip (the kernel's other shape, the narrower tiles).  Two basic blocks: forward with sums, with the BatchNorm
+    in front folded in and without sums (replay), data gradients with the sums of the BatchNorm in front and with a masked addend."""
+    units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
+    _against_float64(units, b, h, w, precision)
+
+
+@pytest.mark.parametrize("precision,b", [(W.BF16, 256), (W.FP16, 221)])
+def test_wide_tiles_with_a_bias_and_other_borders(precision, b):
+    """No border and a bias forward (16 x 16 results), a border of two in the second layer's data gradient (to 16 x 16)."""
+    from oracle import seqnet_oracle as O
+    units = [W.conv(32, 128, 3, pad=0, bn=False, relu=False, bias=True), W.conv(128, 128, 3, pad=0, bn=False, relu=False, bias=True),
+             W.conv(128, 8, 1, bn=False, relu=False, bias=True), W.flatten_linear_ce(8, 10)]
+    rnd = O.round_to_bf16 if precision == W.BF16 else O.round_to_fp16
+    p = W.make_params(units, 18, 18, 13, perturb=True)
+    for nm, sl in W.param_slices(units, 18, 18).items():
+        if nm.endswith(".w") and ".lin." not in nm:
+            p[sl] = rnd(p[sl])
+    x = rnd(W.make_images(b, 18, 18, 32, 13, "gauss")).astype(np.float32)
+    y = W.make_labels(b, 10, 13)
+    r, _ = gpu_step(units, p, x, y, precision=precision, k=1, classes=10, loss_scale_init=_scale(precision))
+    loss, g = oracle_step(units, p, x, y)
+    errs = plain_errors(units, 18, 18, r["grads"], g)
+    assert not r["skipped"] and max(errs.values()) <= TOL[precision], errs
+    assert abs(r["loss"] - loss) <= TOL[precision] * max(1.0, abs(loss))
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("relu,blocks,h,w,b", [
     (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128),  # exactly 131 072 pixels: whole tiles
     (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121),  # ragged; the last block's output is pooled: kept
@@ -1327,6 +1359,8 @@ INFER_NETS = {  # input channels, H = W, batch, units: one network per kernel wh
     "stationary_64": (64, 33, 121, [W.conv(64, 256, ksize=1), W.bottleneck(256, 256), W.gap_linear_ce(256, 10)]),
     "stationary_128": (64, 33, 61, [W.conv(64, 512, ksize=1), W.bottleneck(512, 512), W.gap_linear_ce(512, 10)]),
     "stationary_256": (64, 17, 115, [W.conv(64, 1024, ksize=1), W.bottleneck(1024, 1024), W.gap_linear_ce(1024, 10)]),
+    "wide_patch_128": (64, 16, 253, [W.conv(64, 128, 1), W.basic_block(128, 128), W.gap_linear_ce(128, 10)]),
+    "wide_patch_256": (32, 8, 1021, [W.conv(32, 256, 1), W.basic_block(256, 256), W.gap_linear_ce(256, 10)]),
     "large_tile_256": (64, 33, 121, [W.conv(64, 256, ksize=1), W.conv(256, 256, ksize=1), W.gap_linear_ce(256, 10)]),
 }
 
