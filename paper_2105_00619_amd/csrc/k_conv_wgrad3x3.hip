@@ -54,6 +54,8 @@ template <> struct W9Cfg<bf16_t> { static constexpr int CAP = 128, MAXPOS = 256;
 template <> struct W9Cfg<f16_t> { static constexpr int CAP = 128, MAXPOS = 256; };
 
 // WGM wavefront rows of 32 * MI output channels each (2 wavefront columns of 32 input channels): 64 * WGM threads
+// PG: groups of wavefronts that share a block's pixels (see the kernel)
+constexpr int w9_groups(int bytes, int wgm) { return bytes == 2 && wgm == 2 ? 2 : 1; }
 template <class T, int MI, int WGM> struct W9Lds {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr int CAP = W9Cfg<T>::CAP, MAXPOS = W9Cfg<T>::MAXPOS;
@@ -65,7 +67,11 @@ template <class T, int MI, int WGM> struct W9Lds {
   static constexpr int xs(int npos) { return (F32 ? npos : MAXPOS) * PX; }
   static constexpr int DS = CAP * PK;
   static constexpr int stage(int npos) { return PL * (xs(npos) + DS); }
-  static constexpr size_t bytes(int npos) { return (size_t)(F32 ? 1 : 2) * stage(npos) * 2 + CAP * sizeof(int); }
+  static constexpr size_t bytes(int npos) {
+    const size_t loop = (size_t)(F32 ? 1 : 2) * stage(npos) * 2 + CAP * sizeof(int);
+    const size_t sums = w9_groups(sizeof(T), WGM) == 2 ? (size_t)2 * WGM * MI * 9 * 16 * 64 * 4 : 0;  // a group's accumulators
+    return loop > sums ? loop : sums;
+  }
 };
 
 __device__ __forceinline__ v16f mfma16(v8bf a, v8bf b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
@@ -82,11 +88,12 @@ template <> struct V8<float> { typedef v8bf type; };
 // column, checks each against the image and multiplies them back together with quarter-rate 32- and 64-bit multiplies,
 // per chunk and sub-tile, in a kernel whose instruction stream is what bounds it.
 template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false>
-__global__ void __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : WGM / 2, sizeof(T) == 4 ? 2 : WGM / 2)))
+__global__ void __launch_bounds__(128 * WGM * w9_groups(sizeof(T), WGM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* __restrict__ out, W9Args a) {
   typedef W9Lds<T, MI, WGM> L;
   constexpr bool F32 = L::F32;
-  constexpr int NTH = 128 * WGM;                          // threads
+  constexpr int PG = w9_groups(sizeof(T), WGM);
+  constexpr int NTH = 128 * WGM * PG;                     // threads
   constexpr int CAP = L::CAP, MAXPOS = L::MAXPOS, BMK = L::BMK, PX = L::PX, PK = L::PK;
   constexpr int EV = 16 / (int)sizeof(T);
   constexpr int XCP = 64 / EV, DCP = BMK / EV;            // 16-byte chunks per x position / dz pixel
@@ -99,7 +106,8 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   int* apos = reinterpret_cast<int*>(lds + (F32 ? 1 : 2) * STAGE);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, hg = lane >> 5, l32 = lane & 31;
+  const int grp = wave / (2 * WGM), wq = wave % (2 * WGM);
+  const int wm = wq >> 1, wn = wq & 1, hg = lane >> 5, l32 = lane & 31;
   // Block coordinates: (output-channel tile, input-channel tile, pixel range).  The tiles of one pixel range all read
   // the same pixels of x and dz; workgroups go to the 8 XCDs round-robin by their linear index and every XCD has an L2
   // of its own, so with xcd_group the tiles of a range are renumbered onto one XCD, which then fetches those pixels
@@ -378,7 +386,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       }
     } else {
 #pragma unroll 2
-      for (int ss = 0; ss < nss; ++ss) {
+      for (int ss = grp; ss < nss; ss += PG) {
         const int ma = ss * 16 + hg * 8 + (r16 >> 2), mb = ma + 4;
         const T* xa = tx + apos[ma] * PX;
         const T* xb = tx + apos[mb] * PX;
@@ -486,18 +494,33 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   }
 
   const int64_t outputs = (int64_t)K * 9 * C;
-  float* dst = out + (int64_t)bz * outputs;
+  float* dst = out + (int64_t)bz * outputs + (int64_t)(k0 + wm * 32 * MI + 4 * hg) * 9 * C + c0 + wn * 32 + l32;
+  float* red = reinterpret_cast<float*>(smem_raw) + (wq * MI * 9 * 16) * 64 + lane;
+  auto each = [&](auto FIRST, auto LAST, auto body) {  // taps [FIRST, LAST)
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int c = c0 + wn * 32 + l32;
+      for (int tap = decltype(FIRST)::value; tap < decltype(LAST)::value; ++tap) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int k = k0 + wm * 32 * MI + i * 32 + 8 * (e >> 2) + 4 * hg + (e & 3);
-        dst[((int64_t)k * 9 + tap) * C + c] = acc[i][tap][e];
+        for (int e = 0; e < 16; ++e) body(i, tap, e);
+        __builtin_amdgcn_sched_barrier(0);  // (no more than a tap's values at once beside the accumulators)
       }
-    }
+  };
+  auto put = [&](int i, int tap, int e) { red[((i * 9 + tap) * 16 + e) * 64] = acc[i][tap][e]; };
+  auto store = [&](int i, int tap, int e) {
+    const float v = PG == 2 ? acc[i][tap][e] + red[((i * 9 + tap) * 16 + e) * 64] : acc[i][tap][e];
+    dst[((int64_t)(i * 32 + 8 * (e >> 2) + (e & 3)) * 9 + tap) * C] = v;
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 0> I0; typedef integral_constant<int, 5> I5; typedef integral_constant<int, 9> I9;
+  if constexpr (PG == 2) {  // the groups' sums added: the first group stores taps 0 to 4, the second the others
+    __syncthreads();
+    if (grp == 0) each(I5{}, I9{}, put); else each(I0{}, I5{}, put);
+    __syncthreads();
+    if (grp == 0) each(I0{}, I5{}, store); else each(I5{}, I9{}, store);
+  } else {
+    each(I0{}, I9{}, store);
+  }
 }
 
 // sub-tile geometry for a (P x Q) output grid: up to `cap` pixels and `maxpos` staged positions
@@ -587,7 +610,7 @@ void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const 
   const int tiles = (a.K / (32 * MI * WGM)) * (a.C / 64);
   a.splits = pl.splits;
   a.xcd_group = tiles > 1 && pl.splits >= 8;  // (from the shape only)
-  dim3 grid(a.K / (32 * MI * WGM), a.C / 64, a.xcd_group ? (pl.splits + 7) / 8 * 8 : pl.splits), block(128 * WGM);
+  dim3 grid(a.K / (32 * MI * WGM), a.C / 64, a.xcd_group ? (pl.splits + 7) / 8 * 8 : pl.splits), block(128 * WGM * w9_groups(sizeof(T), WGM));
   // sub-tiles of whole images, every index that is multiplied below 2^24, the pixel index within a sub-tile below 2^20
   const bool whole = a.tiles_r == 1 && a.tiles_c == 1 && a.TR == a.P && a.TC == a.Q && a.H == a.P && a.W == a.Q &&
                      (int64_t)a.N * a.H * a.W + (int64_t)a.TI * a.H * a.W < (1 << 24) && a.C < (1 << 24) && a.K < (1 << 24) &&
