@@ -10,17 +10,19 @@
 // this reads dz once instead of nine times and x about twice instead of nine times, which is what bounds the
 // 16-bit kernel (the path from L2 to LDS), and it leaves nine MFMAs per operand fetch.
 //
-//   block = WGM x 2 wavefronts: wavefront (wm, wn) owns k rows [wm*32*MI, +32*MI) and c columns [wn*32, +32) of
-//   every tap: MI x 9 accumulator tiles of 32x32.  64 output channels: 2 x 2 wavefronts, one per SIMD.  128 output
-//   channels (the plan says where): 4 x 2 wavefronts with MI = 1, two per SIMD (144 accumulator registers each), so that one
-//   wavefront's LDS reads and address arithmetic run under the other's MFMAs: 256 -> 256 channels at 8 x 8, batch
-//   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 326 us with 4 x 2 (the one-tap-per-block kernel: 479 us).
+//   block = 8 wavefronts, two per SIMD (144 accumulator registers each), so that one's LDS reads and address arithmetic run
+//   under the other's MFMAs: wavefront (wm, wn) owns k rows [wm*32*MI, +32*MI) and c columns [wn*32, +32) of every tap: MI x 9
+//   accumulator tiles of 32x32.  128 output channels (the plan says where): 4 x 2 of them (256 -> 256 channels at 8 x 8, batch
+//   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 304 us with 4 x 2; the one-tap-per-block kernel: 479 us).  64: 2 x 2 in
+//   two groups that share a sub-tile's pixels, their sums added at the end (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm
+//   folded in: 556 us with four wavefronts, 431 with eight).  fp32: 2 x 2, one per SIMD and block, two blocks per CU.
 //   MFMA 32x32x16, operands come from the transposing LDS read (ds_read_b64_tr_b16), whose per-lane row addresses make the
 //   tap shift a plain change of address.  fp32: three bf16 planes per operand, six MFMAs (split32.h).
-//   16-bit: two LDS stages; the global loads of the next sub-tile are issued before the MFMAs of the current one, parked in
-//   registers and written to the other stage afterwards: one barrier per sub-tile.  fp32: one stage, sized for the layer's
+//   16-bit: two LDS stages; the next sub-tile's pieces are under way in registers during the MFMAs of the current one and go to the
+//   other stage before or behind them (see the loop): one barrier per sub-tile.  fp32: one stage, sized for the layer's
 //   sub-tile (79 KB on 8 x 8 pixels), so that two blocks share a CU and one loads and converts while the other computes; nothing
 //   is parked, whose registers the accumulators need (spilled, 64 -> 64 channels at 1 048 576 pixels took 635 us).
+#include <algorithm>
 #include <type_traits>
 
 #include "bn_fold.h"
@@ -43,6 +45,8 @@ struct W9Args {
   int TI, TR, TC, SR, SC, NPOS, TP;  // sub-tile: images, rows, columns; staged rows / columns; positions; pixels
   int tiles_r, tiles_c, NT;          // sub-tiles per image rows / columns; in total
   int tiles_per_split;
+  int rows;                          // 1: the ROWS instantiation; TC is a multiple of 8
+  FastDiv div_runs, div_tiles_r, div_tiles_c;  // ROWS: runs of eight pixels per row; sub-tiles
   int xcd_group, splits;  // xcd_group: the tiles of a pixel range share an XCD (see the kernel); splits: pixel ranges
   const float* fold;  // FOLD: x is the z of a BatchNorm + ReLU, this its [4][C] statistics tensor; the staged pieces of x
                       // become the activation (scale, shift, ReLU, one rounding); positions outside the image stay zero
@@ -56,12 +60,13 @@ template <> struct W9Cfg<f16_t> { static constexpr int CAP = 128, MAXPOS = 256; 
 // WGM wavefront rows of 32 * MI output channels each (2 wavefront columns of 32 input channels): 64 * WGM threads
 // PG: groups of wavefronts that share a block's pixels (see the kernel)
 constexpr int w9_groups(int bytes, int wgm) { return bytes == 2 && wgm == 2 ? 2 : 1; }
-template <class T, int MI, int WGM> struct W9Lds {
+template <class T, int MI, int WGM, bool ROWS = false> struct W9Lds {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr int CAP = W9Cfg<T>::CAP, MAXPOS = W9Cfg<T>::MAXPOS;
   static constexpr int BMK = 32 * MI * WGM;
-  static constexpr int PX = 80;                     // elements per staged x position (32 bytes of padding)
-  static constexpr int PK = BMK + 16;               // elements per staged dz pixel
+  // elements per staged x position and dz pixel: 32 bytes of padding; ROWS: none, the 64-byte parts are exchanged instead (swz)
+  static constexpr int PX = ROWS ? 64 : 80;
+  static constexpr int PK = ROWS ? BMK : BMK + 16;
   static constexpr int PL = F32 ? 3 : 1;            // planes
   // elements of a plane of x (fp32: of the layer's positions, not of the most there can be), of dz; of a stage
   static constexpr int xs(int npos) { return (F32 ? npos : MAXPOS) * PX; }
@@ -87,10 +92,18 @@ template <> struct V8<float> { typedef v8bf type; };
 // indices and channel counts are below 2^24 where this kernel is chosen) -- the general path decodes image, row and
 // column, checks each against the image and multiplies them back together with quarter-rate 32- and 64-bit multiplies,
 // per chunk and sub-tile, in a kernel whose instruction stream is what bounds it.
-template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false>
+//
+// ROWS: columns are counted in runs of eight (TC, padded with pixels whose dz is zero).  A wavefront takes two runs at a time (one
+// per half of its lanes) down their rows: a row of x is read at its three shifts and paired with the three rows of dz that meet
+// it in the filter's three rows, two of which are in registers from the rows before: 8 transposing reads per nine MFMAs, where
+// a tap at a time takes 20 and LDS is the bound (57 % of its cycles reads, 25 % bank conflicts).  The four pixels of such a read
+// fall on the same banks unless padded; here the 64-byte parts of a pixel are exchanged by its number instead, which any four
+// neighbours keep apart.  What is left is instructions, so nothing is made twice: a staged row has a multiple of four positions,
+// so that a lane's addresses go from row to row by one addition, and a piece's offset from its sub-tile's first pixel is kept.
+template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false, bool ROWS = false>
 __global__ void __launch_bounds__(128 * WGM * w9_groups(sizeof(T), WGM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* __restrict__ out, W9Args a) {
-  typedef W9Lds<T, MI, WGM> L;
+  typedef W9Lds<T, MI, WGM, ROWS> L;
   constexpr bool F32 = L::F32;
   constexpr int PG = w9_groups(sizeof(T), WGM);
   constexpr int NTH = 128 * WGM * PG;                     // threads
@@ -106,7 +119,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   int* apos = reinterpret_cast<int*>(lds + (F32 ? 1 : 2) * STAGE);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = wave / (2 * WGM), wq = wave % (2 * WGM);
+  const int grp = __builtin_amdgcn_readfirstlane(wave / (2 * WGM)), wq = wave % (2 * WGM);
   const int wm = wq >> 1, wn = wq & 1, hg = lane >> 5, l32 = lane & 31;
   // Block coordinates: (output-channel tile, input-channel tile, pixel range).  The tiles of one pixel range all read
   // the same pixels of x and dz; workgroups go to the 8 XCDs round-robin by their linear index and every XCD has an L2
@@ -171,10 +184,51 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     dinfo[sl] = info;
   }
 
+  // ROWS: byte offsets of the pieces from the sub-tile's first position of x (row -pad, column -pad) and first pixel of dz
+  int xoff[ROWS ? XSLOTS : 1], doff[ROWS ? DSLOTS : 1];
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int sl = 0; sl < XSLOTS; ++sl) {
+      const int info = xinfo[sl];
+      xoff[sl] = (((info >> 20) * H + ((info >> 10) & 1023)) * W + (info & 1023)) * C * 2 + tid % XCP * 16;
+    }
+#pragma unroll
+    for (int sl = 0; sl < DSLOTS; ++sl) {
+      const int info = dinfo[sl];
+      doff[sl] = (((info >> 20) * P + ((info >> 10) & 1023)) * Q + (info & 1023)) * K * 2 + tid % DCP * 16;
+    }
+  }
+
   // Loads are unconditional (clamped to the tensor start when outside) and zeroed when written to LDS.
   Chunk xr[XSLOTS], dr[DSLOTS];
   unsigned xok = 0u, dok = 0u;
   auto gload = [&](int tile) {
+    if constexpr (ROWS) {
+      const int t2 = (int)a.div_tiles_c.div((uint32_t)tile), ci = tile - t2 * a.tiles_c;
+      const int ii = (int)a.div_tiles_r.div((uint32_t)t2), ri = t2 - ii * a.tiles_r;
+      const int nb = ii * TI, yb = ri * TR, xb = ci * TC, images = N - nb;
+      const char* xt = reinterpret_cast<const char*>(x + (int64_t)nb * H * W * C + c0);
+      const char* dt = reinterpret_cast<const char*>(dz + (int64_t)nb * P * Q * K + k0);
+      const int xo = ((yb - pad) * W + xb - pad) * C * 2, dof = (yb * Q + xb) * K * 2;
+      unsigned xm = 0u, dm = 0u;
+#pragma unroll
+      for (int sl = 0; sl < XSLOTS; ++sl) {
+        const int info = xinfo[sl];
+        const bool ok = (info >> 20) < images && (unsigned)(((info >> 10) & 1023) + yb - pad) < (unsigned)H &&
+                        (unsigned)((info & 1023) + xb - pad) < (unsigned)W && info >= 0;
+        xr[sl] = *reinterpret_cast<const Chunk*>(xt + (uint32_t)(ok ? xoff[sl] + xo : 0));
+        xm |= ok ? (1u << sl) : 0u;
+      }
+#pragma unroll
+      for (int sl = 0; sl < DSLOTS; ++sl) {
+        const int info = dinfo[sl];
+        const bool ok = (info >> 20) < images && (int)((info >> 10) & 1023) < P - yb && (int)(info & 1023) < Q - xb && info >= 0;
+        dr[sl] = *reinterpret_cast<const Chunk*>(dt + (uint32_t)(ok ? doff[sl] + dof : 0));
+        dm |= ok ? (1u << sl) : 0u;
+      }
+      xok = xm; dok = dm;
+      return;
+    }
     if constexpr (WHOLE) {
       const int nb = tile * TI;
       const uint32_t xbase = (uint32_t)nb * (uint32_t)(H * W), dbase = (uint32_t)nb * (uint32_t)(P * Q);
@@ -263,9 +317,24 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     load_f32<float, EV>(a.fold + 2 * C + c0 + (tid % XCP) * EV, fsc);
     load_f32<float, EV>(a.fold + 3 * C + c0 + (tid % XCP) * EV, fsh);
   }
+  // ROWS: where channel c of a position lies within it
+  auto swz = [](int pos, int c) { return c ^ (((pos >> 1) & 1) << 5); };
+  const int xput = ROWS ? tid / XCP * PX + swz(tid / XCP, tid % XCP * EV) : 0, dput = ROWS ? tid / DCP * PK + swz(tid / DCP, tid % DCP * EV) : 0;
   auto sstore = [&](int stage) {
     E* xs = lds + stage * STAGE;
     E* ds = xs + L::PL * XS;
+    if constexpr (ROWS) {  // (positions 4 n apart keep their parts in the same order)
+      static_assert(NTH / XCP % 4 == 0 && NTH / DCP % 4 == 0 && MAXPOS * XCP % NTH == 0, "a slot's pieces are whole positions");
+#pragma unroll
+      for (int sl = 0; sl < XSLOTS; ++sl) {
+        if (FOLD) xr[sl] = bn_fold_chunk<T>(xr[sl], fsc, fsh);
+        *reinterpret_cast<Chunk*>(&xs[xput + sl * (NTH / XCP) * PX]) = ((xok >> sl) & 1u) ? xr[sl] : zero_chunk();
+      }
+#pragma unroll
+      for (int sl = 0; sl < DSLOTS; ++sl)
+        *reinterpret_cast<Chunk*>(&ds[dput + sl * (NTH / DCP) * PK]) = ((dok >> sl) & 1u) ? dr[sl] : zero_chunk();
+      return;
+    }
     if (FOLD) {
 #pragma unroll
       for (int sl = 0; sl < XSLOTS; ++sl) xr[sl] = bn_fold_chunk<T>(xr[sl], fsc, fsh);
@@ -403,6 +472,66 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     }
   };
 
+  auto compute_rows = [&](int stage) {
+    if constexpr (ROWS) {
+      static_assert(MI == 1 && BMK == 64, "64 channels either way");
+      typedef typename V8<T>::type V;
+      const T* xs = lds + stage * STAGE;
+      const T* ds = xs + XS;
+      const int r16 = l32 & 15, px = r16 >> 2, ch = (l32 & 16) + 4 * (r16 & 3);
+      const int per_row = TC >> 3, runs = TI * per_row, segs = (runs + 1) >> 1;
+      // two groups of wavefronts: every other pair of runs, or, where their number is odd, half of the rows each
+      const bool by_rows = PG == 2 && (segs & 1);
+      const int cut = (TR + 1) >> 1;
+      const int y0 = by_rows && grp ? cut : 0, y1 = by_rows && !grp ? cut : TR;
+      const int xstep = SC * PX, dstep = TC * PK;  // (both counts multiples of four: the parts keep their order)
+#pragma unroll 1
+      for (int seg = by_rows ? 0 : grp; seg < segs; seg += by_rows ? 1 : PG) {
+        int run = 2 * seg + hg;
+        const bool odd = 2 * seg + 1 >= runs;  // an odd number of runs: the last pair's second counts as zero
+        if (odd) run = 2 * seg;
+        const int ti = (int)a.div_runs.div((uint32_t)run), col = (run - ti * per_row) * 8 + px;
+        const int xp = (ti * a.SR + y0) * SC + col, dp = (ti * TR + y0) * TC + col;
+        const T* xq[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) xq[s] = xs + (xp + s) * PX + swz(xp + s, wn * 32 + ch);
+        const T* dq = ds + dp * PK + swz(dp, wm * 32 + ch);
+        auto row = [&](int j, V& now, const V& one, const V& two) {  // row j of x; dz of rows j, j - 1, j - 2
+          V f[3];
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {
+            f[s] = lds_tr_read8<V>(xq[s], xq[s] + 4 * PX);
+            xq[s] += xstep;
+          }
+          if (j < y1) {
+            now = lds_tr_read8<V>(dq, dq + 4 * PK);
+            dq += dstep;
+          }
+          if (j > y0 && j <= y1) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) acc[0][3 + s] = mfma16(one, f[s], acc[0][3 + s]);
+          }
+          if (j > y0 + 1) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) acc[0][6 + s] = mfma16(two, f[s], acc[0][6 + s]);
+          }
+          if (j < y1) {
+            if (odd && hg) now = V{};
+#pragma unroll
+            for (int s = 0; s < 3; ++s) acc[0][s] = mfma16(now, f[s], acc[0][s]);
+          }
+        };
+        V d0 = V{}, d1 = V{}, d2 = V{};
+#pragma unroll 1
+        for (int j = y0; j < y1 + 2; j += 3) {
+          row(j, d0, d2, d1);
+          if (j + 1 < y1 + 2) row(j + 1, d1, d0, d2);
+          if (j + 2 < y1 + 2) row(j + 2, d2, d1, d0);
+        }
+      }
+    }
+  };
+
   if constexpr (F32) {
     // (split32.h: half of the sum with dz negated)
     bool neg = (bz & 1) != 0;
@@ -426,15 +555,34 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       if (half == 0 || neg) { neg = !neg; negate(); }
     }
   } else {
+    auto multiply = [&](int stage) { if constexpr (ROWS) compute_rows(stage); else compute(stage); };
     if (nst > 0) { gload(t0); sstore(0); }
-    __syncthreads();
-    for (int g = 0; g + 1 < nst; ++g) {  // steady state without range checks
-      gload(t0 + g + 1);
-      compute(g & 1);
-      sstore((g + 1) & 1);
+    if constexpr (PG == 2) {
+      // While sub-tile g is multiplied, g + 1 goes from registers to the other stage and g + 2 is requested: by one group of
+      // wavefronts before its MFMAs, by the other behind them, so that on every SIMD the conversions and addresses of one run
+      // under the MFMAs of the other (64 -> 64 channels over 4.2 M pixels: 407 us with both behind, 396 so).
+      auto stage_next = [&](int g) {
+        sstore((g + 1) & 1);
+        if (g + 2 < nst) gload(t0 + g + 2);
+      };
+      if (nst > 1) gload(t0 + 1);
       __syncthreads();
+      for (int g = 0; g + 1 < nst; ++g) {
+        if (grp == 0) stage_next(g);
+        multiply(g & 1);
+        if (grp != 0) stage_next(g);
+        __syncthreads();
+      }
+    } else {  // (128 channels: no gain from that)
+      __syncthreads();
+      for (int g = 0; g + 1 < nst; ++g) {
+        gload(t0 + g + 1);
+        multiply(g & 1);
+        sstore((g + 1) & 1);
+        __syncthreads();
+      }
     }
-    if (nst > 0) compute((nst - 1) & 1);
+    if (nst > 0) multiply((nst - 1) & 1);
   }
 
   if constexpr (F32) {
@@ -524,15 +672,15 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
 }
 
 // sub-tile geometry for a (P x Q) output grid: up to `cap` pixels and `maxpos` staged positions
-bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, W9Args& a) {
+bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, int halo, W9Args& a) {
   int tr = cap / tc; if (tr > P) tr = P; if (tr < 1) tr = 1;
   int ti = (tr == P && tc == Q) ? cap / (P * Q) : 1;
   if (ti > N) ti = N; if (ti < 1) ti = 1;
-  while (ti > 1 && ti * (tr + 2) * (tc + 2) > maxpos) ti /= 2;
-  while (tr > 1 && ti * (tr + 2) * (tc + 2) > maxpos) --tr;
-  while (tc > 1 && ti * (tr + 2) * (tc + 2) > maxpos) tc /= 2;
-  if (ti * (tr + 2) * (tc + 2) > maxpos) return false;
-  a.TI = ti; a.TR = tr; a.TC = tc; a.SR = tr + 2; a.SC = tc + 2;
+  while (ti > 1 && ti * (tr + 2) * (tc + halo) > maxpos) ti /= 2;
+  while (tr > 1 && ti * (tr + 2) * (tc + halo) > maxpos) --tr;
+  while (tc > 1 && ti * (tr + 2) * (tc + halo) > maxpos) tc /= 2;
+  if (ti * (tr + 2) * (tc + halo) > maxpos) return false;
+  a.TI = ti; a.TR = tr; a.TC = tc; a.SR = tr + 2; a.SC = tc + halo;
   a.NPOS = ti * a.SR * a.SC; a.TP = ti * tr * tc;
   a.tiles_r = (P + tr - 1) / tr; a.tiles_c = (Q + tc - 1) / tc;
   a.NT = ((N + ti - 1) / ti) * a.tiles_r * a.tiles_c;
@@ -541,12 +689,13 @@ bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, W9Args& a)
 // The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (512 columns: 32 of 64 with 102
 // staged positions), the narrower one that covers the map with the fewest sub-tiles, then staged positions.  (bf16, three layers of
 // 128 channels at 8 x 112 x 112 232 -> 158 us without -> with, at 16 x 64 x 64 151 -> 137.)
-bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a) {
-  bool ok = w9_geometry_of(N, P, Q, Q < cap ? Q : cap, cap, maxpos, a);
+// halo: staged columns beyond those of the pixels: 2, ROWS 4
+bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a, int halo = 2) {
+  bool ok = w9_geometry_of(N, P, Q, Q < cap ? Q : cap, cap, maxpos, halo, a);
   if (ok && a.TP * 4 >= cap * 3) return ok;
   for (int tc = 64; tc >= 8; tc /= 2) {
     W9Args b = a;
-    if (tc >= Q || !w9_geometry_of(N, P, Q, tc, cap, maxpos, b)) continue;
+    if (tc >= Q || !w9_geometry_of(N, P, Q, tc, cap, maxpos, halo, b)) continue;
     if (!ok || b.NT < a.NT || (b.NT == a.NT && b.NPOS < a.NPOS)) { a = b; ok = true; }
   }
   return ok;
@@ -562,10 +711,17 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   if (g.H >= 1024 || g.W >= 1024) return false;  // packed (image within the sub-tile, row, column) fields
   const int cap = dt == DT_F32 ? W9Cfg<float>::CAP : W9Cfg<bf16_t>::CAP;
   const int maxpos = dt == DT_F32 ? W9Cfg<float>::MAXPOS : W9Cfg<bf16_t>::MAXPOS;
-  W9Args a{};
-  if (!w9_geometry(g.N, g.P, g.Q, cap, maxpos, a)) return false;
-  if (a.TP * 2 < cap) return false;  // short sub-tiles: too little work between barriers
-  a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
+  W9Args any{}, by_rows{};
+  const bool any_ok = w9_geometry(g.N, g.P, g.Q, cap, maxpos, any) && any.TP * 2 >= cap;  // (short sub-tiles: too little work between barriers)
+  // Blocks of 64 channels, 16 bits: by rows in runs of eight columns, unless padding them makes it more than a quarter more MFMAs (64 ->
+  // 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us a tap at a time, 396 by rows; 524 288, fp16: 59 and 56).
+  // (In blocks of 128 channels the rows' addresses are spilled: 256 -> 256 over 262 144 pixels 304 us a tap at a time, 350 by rows.)
+  bool rows_ok = dt != DT_F32 && w9_geometry(g.N, g.P, (g.Q + 7) / 8 * 8, cap, maxpos, by_rows, 4) && by_rows.TC % 8 == 0 &&
+                 by_rows.TP * 2 >= cap &&
+                 (int64_t)(by_rows.TI + 1) * (g.H + 2) * (g.W + 2) * std::max(g.C, g.K) < (int64_t)1 << 30;  // 32-bit offsets within a sub-tile's images
+  if (rows_ok && any_ok)
+    rows_ok = (int64_t)by_rows.NT * ((by_rows.TI * (by_rows.TC / 8) + 1) / 2) * by_rows.TR * 4 <= (int64_t)any.NT * ((any.TP + 15) / 16) * 5;
+  by_rows.rows = 1;
   // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD), unless the blocks
   // would then get fewer than g_w9_wide_min sub-tiles each: a block's accumulators (9 taps x 64*MI x 64 floats) are
   // written out once per pixel range and read again by the reduction, and with few sub-tiles per range that traffic
@@ -576,6 +732,10 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   // pixels 367 us, 472 with one; on the fp32 MFMA 800), a quarter of it left for what the placement of the tensors loses.
   const bool f32 = dt == DT_F32;
   for (int mi = f32 ? 2 : g.K % 128 == 0 ? 2 : 1; mi >= 1; --mi) {
+    const bool rows = mi == 1 && rows_ok;
+    if (!rows && !any_ok) continue;
+    W9Args a = rows ? by_rows : any;
+    a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
     const int target = f32 && mi == 2 ? 512 : 256;  // blocks
     const int bk = f32 ? 64 : 64 * mi;
     const int64_t tiles = (int64_t)(g.K / bk) * (g.C / 64);
@@ -594,34 +754,44 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   return false;
 }
 
-template <class T, int MI, int WGM, bool FOLD>
-void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const W9Plan& pl) {
-  typedef W9Lds<T, MI, WGM> L;
-  constexpr size_t sm_max = L::bytes(W9Cfg<T>::MAXPOS);
-  const size_t sm = L::bytes(pl.a.NPOS);
+template <class T, int MI, int WGM, bool FOLD, bool WHOLE, bool ROWS>
+void launch_w9_one(hipStream_t st, const void* x, const void* dz, float* dst, dim3 grid, const W9Args& a) {
+  typedef W9Lds<T, MI, WGM, ROWS> L;
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
-    if constexpr (sizeof(T) == 2)
-      (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm_max);
+    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)L::bytes(W9Cfg<T>::MAXPOS));
     attr_done = true;
   }
+  OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, ROWS>), grid, dim3(128 * WGM * w9_groups(sizeof(T), WGM)), L::bytes(a.NPOS), st,
+              (const T*)x, (const T*)dz, dst, a);
+}
+template <class T, int MI, int WGM, bool FOLD>
+void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const W9Plan& pl) {
   W9Args a = pl.a;
   const int tiles = (a.K / (32 * MI * WGM)) * (a.C / 64);
   a.splits = pl.splits;
   a.xcd_group = tiles > 1 && pl.splits >= 8;  // (from the shape only)
-  dim3 grid(a.K / (32 * MI * WGM), a.C / 64, a.xcd_group ? (pl.splits + 7) / 8 * 8 : pl.splits), block(128 * WGM * w9_groups(sizeof(T), WGM));
+  dim3 grid(a.K / (32 * MI * WGM), a.C / 64, a.xcd_group ? (pl.splits + 7) / 8 * 8 : pl.splits);
   // sub-tiles of whole images, every index that is multiplied below 2^24, the pixel index within a sub-tile below 2^20
   const bool whole = a.tiles_r == 1 && a.tiles_c == 1 && a.TR == a.P && a.TC == a.Q && a.H == a.P && a.W == a.Q &&
                      (int64_t)a.N * a.H * a.W + (int64_t)a.TI * a.H * a.W < (1 << 24) && a.C < (1 << 24) && a.K < (1 << 24) &&
                      a.TI < 256 && (int64_t)a.TI * a.H * a.W < (1 << 20);
-  if constexpr (sizeof(T) == 2) {
-    if (whole) {
-      OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, true>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
+  if constexpr (sizeof(T) == 2 && WGM == 2) {
+    if (a.rows) {
+      a.div_runs = make_fastdiv((uint32_t)a.TC / 8);
+      a.div_tiles_r = make_fastdiv((uint32_t)a.tiles_r); a.div_tiles_c = make_fastdiv((uint32_t)a.tiles_c);
+      launch_w9_one<T, MI, WGM, FOLD, false, true>(st, x, dz, dst, grid, a);
       return;
     }
   }
-  OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, false>), grid, block, sm, st, (const T*)x, (const T*)dz, dst, a);
+  if constexpr (sizeof(T) == 2) {
+    if (whole) {
+      launch_w9_one<T, MI, WGM, FOLD, true, false>(st, x, dz, dst, grid, a);
+      return;
+    }
+  }
+  launch_w9_one<T, MI, WGM, FOLD, false, false>(st, x, dz, dst, grid, a);
 }
 
 template <class T>
