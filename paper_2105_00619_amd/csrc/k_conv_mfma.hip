@@ -932,20 +932,11 @@ static bool patch_geometry(int N, int dstH, int dstW, int cap, bool narrow, Patc
   return ok;
 }
 
-// Bytes between staged patch rows.  A lane group reads 16 bytes per lane at consecutive pixels: within a row of TC
-// pixels the position pitch (80 bytes, fp32 112) spreads them over the LDS banks, and the row pitch is padded so that the next
-// rows of the tile land on the banks the previous ones left free (TC = 8: 128 mod 256, TC = 4: 64, TC = 2: 32);
-// kept at SC positions when the padded rows would not fit the patch buffer.
-static constexpr int g_patch_pad_rows = 1;  // compile-time switch
+// Bytes between staged patch rows (patch_rows_apart), kept at SC positions when the padded rows would not fit the patch buffer.
 static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes, int most = PATCH_MAX_POS) {
-  const int base = a.SC * pos_bytes;
-  int want = -1;
-  if (a.TC == 8) want = 128; else if (a.TC == 4) want = 64; else if (a.TC == 2) want = 32;
-  if (want < 0 || !g_patch_pad_rows) return base;
-  int rp = base / 256 * 256 + want;
-  if (rp < base) rp += 256;
+  const int rp = patch_rows_apart(a.TC, a.SC, pos_bytes);
   const int64_t rows = (int64_t)subt * a.TI * a.SR;
-  return rows * rp <= (int64_t)subt * most * pos_bytes ? rp : base;
+  return rows * rp <= (int64_t)subt * most * pos_bytes ? rp : a.SC * pos_bytes;
 }
 
 // Block shapes of the patch kernel, largest first: {MI, SUBT, widest BN}.  The first one that gives the chip

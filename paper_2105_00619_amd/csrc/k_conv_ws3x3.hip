@@ -18,12 +18,14 @@
 // not there, 128 to 264 bytes of them spilled, 117 against 68 us for an inference layer) and from 131 072 pixels on, two
 // tiles a block; see ws3_args for maps that the patch kernel's tiles fill.  64 -> 64 channels, bf16, patch kernel -> this
 // one, us at 4.2 M pixels (4096 x 32 x 32): data gradient 478 -> 362, forward on a folded BatchNorm 513 -> 383, with the
-// channel sums 562 -> 463.  Forward, sums finished, plus data gradient at the line, us a layer (a third is the weights' way
+// channel sums 562 -> 463; with rows that keep LDS reads apart (patch_rows_apart) 344 -> 324, 360 -> 350 and 453 -> 443 on another
+// card.  Forward, sums finished, plus data gradient at the line, us a layer (a third is the weights' way
 // into the registers): 137 984 pixels of 112 x 112 maps 82 -> 59, 125 440 of 56 x 56 67 -> 56, 132 300 of 21 x 21 58 -> 57.
 #include "bn_fold.h"
 #include "dev_common.h"
 #include "epilogue.h"
 #include "kernels.h"
+#include "patch.h"
 
 namespace oseq {
 namespace {
@@ -46,12 +48,14 @@ constexpr int WS3_PITCH = WS3_C + 8;      // elements per staged position and pe
                                           // neighbouring positions read 16 bytes each from all 64 banks)
 constexpr int WS3_SLOTS = 7;              // 16-byte pieces of a patch per thread
 constexpr int WS3_MAX_POS = WS3_SLOTS * 256 / 8;
+constexpr int WS3_PATCH = 20480;          // elements of a patch, its padded rows
 constexpr int WS3_FLUSH = 16;             // tiles per row of sums: one addition per thread and tile
 
 struct Ws3Args {
   int N, srcH, srcW, dstH, dstW, Ng, pad, flip;
   int TI, TR, TC;                 // tile: images x rows x columns of output pixels
   int tiles_r, tiles_c, NT;
+  int row_pitch;                  // elements between the rows of a patch
   int flushes;                    // rows of sums per block
 };
 
@@ -64,7 +68,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
   typedef typename Mma3<T>::A v16f;
   typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
   constexpr int PITCH = WS3_PITCH;
-  __shared__ __attribute__((aligned(16))) T patch[WS3_MAX_POS * PITCH];
+  __shared__ __attribute__((aligned(16))) T patch[WS3_PATCH];
   __shared__ __attribute__((aligned(16))) T stg[WS3_PX * PITCH];
   // kept out of registers, of which the weights leave few: the folded BatchNorm's scale and shift, the threads' channel sums
   __shared__ __attribute__((aligned(16))) float ftab[FOLD ? 2 : 1][FOLD ? 64 : 4];
@@ -126,7 +130,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
       Chunk v = pr[i];
       if (FOLD) v = bn_fold_chunk<T>(v, fsc, fsh);
       if (pco[i] >= 0)
-        *reinterpret_cast<Chunk*>(&patch[((tid >> 3) + 32 * i) * PITCH + pc8]) = ((pvalid >> i) & 1u) ? v : zero_chunk();
+        *reinterpret_cast<Chunk*>(&patch[__mul24(__mul24(pco[i] >> 16, SR) + ((pco[i] >> 8) & 255), a.row_pitch) + __mul24(pco[i] & 255, PITCH) + pc8]) = ((pvalid >> i) & 1u) ? v : zero_chunk();
     }
   };
   // LDS position of this lane's two pixels (tap (0, 0)); pixels past the tile's last one read its first
@@ -136,7 +140,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
     int m = pgrp * 64 + p * 32 + l32;
     if (m >= TP) m = 0;
     const int ti = m / (a.TR * a.TC), rr = m - ti * (a.TR * a.TC), tr = rr / a.TC, tc = rr - tr * a.TC;
-    prow[p] = ((ti * SR + tr) * SC + tc) * PITCH + g * 8;
+    prow[p] = (ti * SR + tr) * a.row_pitch + tc * PITCH + g * 8;
   }
   // this thread's rows of the staged results: packed coordinates as above
   const int c8 = (tid & 7) * 8, erow = tid >> 3;
@@ -167,7 +171,7 @@ conv_ws3x3_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const f
   if (FOLD) __syncthreads();  // the table
   pstore();
   __syncthreads();
-  const int row1 = SC * PITCH, row2 = 2 * SC * PITCH;
+  const int row1 = a.row_pitch, row2 = 2 * a.row_pitch;
   for (;;) {
     const int next = tile + gridDim.x;
     if (next < a.NT) pload(next);
@@ -278,6 +282,8 @@ bool ws3_geometry(int N, int dstH, int dstW, Ws3Args& a) {
   }
   if (best < 0 || best >= ((int64_t)1 << 30)) return false;
   a.NT = (int)best;
+  a.row_pitch = patch_rows_apart(a.TC, a.TC + 2, WS3_PITCH * 2) / 2;
+  if (a.TI * (a.TR + 2) * a.row_pitch > WS3_PATCH) a.row_pitch = (a.TC + 2) * WS3_PITCH;
   return true;
 }
 
