@@ -93,13 +93,16 @@ template <> struct V8<float> { typedef v8bf type; };
 // column, checks each against the image and multiplies them back together with quarter-rate 32- and 64-bit multiplies,
 // per chunk and sub-tile, in a kernel whose instruction stream is what bounds it.
 //
-// ROWS: columns are counted in runs of eight (TC, padded with pixels whose dz is zero).  A wavefront takes two runs at a time (one
-// per half of its lanes) down their rows: a row of x is read at its three shifts and paired with the three rows of dz that meet
-// it in the filter's three rows, two of which are in registers from the rows before: 8 transposing reads per nine MFMAs, where
-// a tap at a time takes 20 and LDS is the bound (57 % of its cycles reads, 25 % bank conflicts).  The four pixels of such a read
-// fall on the same banks unless padded; here the 64-byte parts of a pixel are exchanged by its number instead, which any four
-// neighbours keep apart.  What is left is instructions, so nothing is made twice: a staged row has a multiple of four positions,
-// so that a lane's addresses go from row to row by one addition, and a piece's offset from its sub-tile's first pixel is kept.
+// ROWS: columns are counted in runs of eight (TC, in blocks of 64 channels padded with pixels whose dz is zero), so that the four
+// pixels of a transposing read are neighbours in a row.  They fall on the same banks unless padded; here the 64-byte parts of a
+// pixel are exchanged by its number instead (swz), which any four neighbours keep apart, and a staged row has a multiple of four
+// positions, so that this order is that of the rows above and below.
+//   Blocks of 64 channels: a wavefront takes two runs at a time (one per half of its lanes) down their rows: a row of x is read at
+// its three shifts and paired with the three rows of dz that meet it in the filter's three rows, two of which are in registers
+// from the rows before: 8 reads per nine MFMAs, where a tap at a time takes 20 and LDS is the bound (57 % of its cycles reads,
+// 25 % bank conflicts).  What is left is instructions, so a piece's offset from its sub-tile's first pixel is kept.
+//   Blocks of 128 channels: a tap at a time (by rows 350 us for the 304 below: spilled); without conflicts and with one address per two
+// reads 304 -> 287 us for 256 -> 256 channels over 262 144 pixels in bf16, 40.4 -> 37.3 for 128 -> 128 over 65 536.
 template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false, bool ROWS = false>
 __global__ void __launch_bounds__(128 * WGM * w9_groups(sizeof(T), WGM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* __restrict__ out, W9Args a) {
@@ -185,8 +188,8 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   }
 
   // ROWS: byte offsets of the pieces from the sub-tile's first position of x (row -pad, column -pad) and first pixel of dz
-  int xoff[ROWS ? XSLOTS : 1], doff[ROWS ? DSLOTS : 1];
-  if constexpr (ROWS) {
+  int xoff[ROWS && PG == 2 ? XSLOTS : 1], doff[ROWS && PG == 2 ? DSLOTS : 1];
+  if constexpr (ROWS && PG == 2) {
 #pragma unroll
     for (int sl = 0; sl < XSLOTS; ++sl) {
       const int info = xinfo[sl];
@@ -203,7 +206,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   Chunk xr[XSLOTS], dr[DSLOTS];
   unsigned xok = 0u, dok = 0u;
   auto gload = [&](int tile) {
-    if constexpr (ROWS) {
+    if constexpr (ROWS && PG == 2) {
       const int t2 = (int)a.div_tiles_c.div((uint32_t)tile), ci = tile - t2 * a.tiles_c;
       const int ii = (int)a.div_tiles_r.div((uint32_t)t2), ri = t2 - ii * a.tiles_r;
       const int nb = ii * TI, yb = ri * TR, xb = ci * TC, images = N - nb;
@@ -319,7 +322,8 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   }
   // ROWS: where channel c of a position lies within it
   auto swz = [](int pos, int c) { return c ^ (((pos >> 1) & 1) << 5); };
-  const int xput = ROWS ? tid / XCP * PX + swz(tid / XCP, tid % XCP * EV) : 0, dput = ROWS ? tid / DCP * PK + swz(tid / DCP, tid % DCP * EV) : 0;
+  auto swz_d = [](int m, int c) { return c ^ (BMK == 128 ? (m & 3) << 5 : ((m >> 1) & 1) << 5); };
+  const int xput = ROWS ? tid / XCP * PX + swz(tid / XCP, tid % XCP * EV) : 0, dput = ROWS ? tid / DCP * PK + swz_d(tid / DCP, tid % DCP * EV) : 0;
   auto sstore = [&](int stage) {
     E* xs = lds + stage * STAGE;
     E* ds = xs + L::PL * XS;
@@ -453,6 +457,20 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
             for (int i = 0; i < MI; ++i) acc[i][tap] = mfma16(fa[i][QA[q]], fb[QB[q]], acc[i][tap]);
         }
       }
+    } else if constexpr (ROWS) {  // blocks of 128 channels: a tap at a time, from the same places
+#pragma unroll 2
+      for (int ss = 0; ss < nss; ++ss) {
+        const int m = ss * 16 + hg * 8 + (r16 >> 2), pos = apos[m];
+        const typename V8<T>::type f = lds_tr_read8<typename V8<T>::type>(ds + m * PK + swz_d(m, wm * 32 + colsel), ds + m * PK + swz_d(m, wm * 32 + colsel) + 4 * PK);
+        const T* xq[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) xq[s] = xs + (pos + s) * PX + swz(pos + s, wn * 32 + colsel);
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+          const T* q = xq[tap % 3] + tap / 3 * SC * PX;
+          acc[0][tap] = mfma16(f, lds_tr_read8<typename V8<T>::type>(q, q + 4 * PX), acc[0][tap]);
+        }
+      }
     } else {
 #pragma unroll 2
       for (int ss = grp; ss < nss; ss += PG) {
@@ -473,7 +491,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   };
 
   auto compute_rows = [&](int stage) {
-    if constexpr (ROWS) {
+    if constexpr (ROWS && PG == 2) {
       static_assert(MI == 1 && BMK == 64, "64 channels either way");
       typedef typename V8<T>::type V;
       const T* xs = lds + stage * STAGE;
@@ -495,7 +513,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
         const T* xq[3];
 #pragma unroll
         for (int s = 0; s < 3; ++s) xq[s] = xs + (xp + s) * PX + swz(xp + s, wn * 32 + ch);
-        const T* dq = ds + dp * PK + swz(dp, wm * 32 + ch);
+        const T* dq = ds + dp * PK + swz_d(dp, wm * 32 + ch);
         auto row = [&](int j, V& now, const V& one, const V& two) {  // row j of x; dz of rows j, j - 1, j - 2
           V f[3];
 #pragma unroll
@@ -555,7 +573,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       if (half == 0 || neg) { neg = !neg; negate(); }
     }
   } else {
-    auto multiply = [&](int stage) { if constexpr (ROWS) compute_rows(stage); else compute(stage); };
+    auto multiply = [&](int stage) { if constexpr (ROWS && PG == 2) compute_rows(stage); else compute(stage); };
     if (nst > 0) { gload(t0); sstore(0); }
     if constexpr (PG == 2) {
       // While sub-tile g is multiplied, g + 1 goes from registers to the other stage and g + 2 is requested: by one group of
@@ -713,9 +731,8 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   const int maxpos = dt == DT_F32 ? W9Cfg<float>::MAXPOS : W9Cfg<bf16_t>::MAXPOS;
   W9Args any{}, by_rows{};
   const bool any_ok = w9_geometry(g.N, g.P, g.Q, cap, maxpos, any) && any.TP * 2 >= cap;  // (short sub-tiles: too little work between barriers)
-  // Blocks of 64 channels, 16 bits: by rows in runs of eight columns, unless padding them makes it more than a quarter more MFMAs (64 ->
-  // 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us a tap at a time, 396 by rows; 524 288, fp16: 59 and 56).
-  // (In blocks of 128 channels the rows' addresses are spilled: 256 -> 256 over 262 144 pixels 304 us a tap at a time, 350 by rows.)
+  // 16 bits: ROWS, unless the padding of columns makes it more than a quarter more MFMAs; in blocks of 128 channels where none is
+  // needed (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us -> 396; 524 288, fp16: 59 -> 56; 128: see the kernel).
   bool rows_ok = dt != DT_F32 && w9_geometry(g.N, g.P, (g.Q + 7) / 8 * 8, cap, maxpos, by_rows, 4) && by_rows.TC % 8 == 0 &&
                  by_rows.TP * 2 >= cap &&
                  (int64_t)(by_rows.TI + 1) * (g.H + 2) * (g.W + 2) * std::max(g.C, g.K) < (int64_t)1 << 30;  // 32-bit offsets within a sub-tile's images
@@ -732,7 +749,7 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   // pixels 367 us, 472 with one; on the fp32 MFMA 800), a quarter of it left for what the placement of the tensors loses.
   const bool f32 = dt == DT_F32;
   for (int mi = f32 ? 2 : g.K % 128 == 0 ? 2 : 1; mi >= 1; --mi) {
-    const bool rows = mi == 1 && rows_ok;
+    const bool rows = rows_ok && (mi == 1 || g.Q % 8 == 0);
     if (!rows && !any_ok) continue;
     W9Args a = rows ? by_rows : any;
     a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
@@ -782,6 +799,13 @@ void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const 
       a.div_runs = make_fastdiv((uint32_t)a.TC / 8);
       a.div_tiles_r = make_fastdiv((uint32_t)a.tiles_r); a.div_tiles_c = make_fastdiv((uint32_t)a.tiles_c);
       launch_w9_one<T, MI, WGM, FOLD, false, true>(st, x, dz, dst, grid, a);
+      return;
+    }
+  }
+  if constexpr (sizeof(T) == 2 && WGM == 4) {
+    if (a.rows) {
+      if (whole) launch_w9_one<T, MI, WGM, FOLD, true, true>(st, x, dz, dst, grid, a);
+      else launch_w9_one<T, MI, WGM, FOLD, false, true>(st, x, dz, dst, grid, a);
       return;
     }
   }
