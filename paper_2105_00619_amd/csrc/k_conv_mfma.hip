@@ -957,7 +957,7 @@ static constexpr int g_patch_xcd_rows = 16;              // ... and most row til
 // Exactly 256 tiles of 256 x 128 (128 -> 128 channels at 65 536 pixels, bf16): 31.3 -> 28.8 us forward, data gradient 31.5 -> 30.6.
 static bool patch_pick_wide(int N, int dstH, int dstW, int srcC, int Ng, PatchShape& shape, PatchArgs& geo) {
   for (int bn = 256; bn >= 128; bn /= 2) {
-    if (Ng % bn != 0) continue;
+    if (Ng % bn != 0 || (int64_t)N * dstH * dstW * Ng * 20 < (int64_t)17 * 256 * 256 * bn) continue;  // (fewer than a round's)
     PatchArgs a{};
     if (!patch_geometry(N, dstH, dstW, 256, true, a, PATCH_WIDE_MAX_POS)) continue;
     if ((int64_t)a.TI * (dstH + 2) * (dstW + 2) * srcC >= (int64_t)1 << 30) continue;  // 32-bit offsets within a tile's images

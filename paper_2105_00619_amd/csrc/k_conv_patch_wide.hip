@@ -48,7 +48,7 @@ constexpr int epi_bytes(int bn) { return std::max(256 * (bn + 8) * 2, 2 * HR * (
 template <class T, int MI, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 conv3x3_wide_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const float* __restrict__ bias,
-                    const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ stat_partial, PatchArgs a) {
+                    const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ stat_partial, PatchWideArgs a) {
   typedef typename Op<T>::V V;
   constexpr int ROWS = 64 * MI, BN = 64 * NI;
   constexpr int NW = BN / 64;  // weight pieces per thread and tap
@@ -365,7 +365,7 @@ conv3x3_wide_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const
 
 template <class T, int MI, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
 void launch_one(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out, float* stat_partial,
-                dim3 grid, size_t sm, const PatchArgs& a) {
+                dim3 grid, size_t sm, const PatchWideArgs& a) {
   static bool done = false;
   if (!done) {
     (void)hipFuncSetAttribute((const void*)conv3x3_wide_kernel<T, MI, NI, STAT, FOLD, EVAL, ADD>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -377,7 +377,9 @@ void launch_one(hipStream_t st, const void* src, const void* wmat, const float* 
 
 template <class T, int MI, int NI>
 void launch_shape(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out, float* stat_partial,
-                  PatchArgs a) {
+                  const PatchArgs& shape) {
+  PatchWideArgs a;
+  static_cast<PatchArgs&>(a) = shape;
   dim3 grid(a.NT, a.Ng / (64 * NI));
   a.patch_elems = (a.TI * a.SR * a.row_pitch + 15) / 16 * 16 / (int)sizeof(T);
   a.row_blocks = (int)grid.x;

@@ -729,15 +729,10 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   if (g.H >= 1024 || g.W >= 1024) return false;  // packed (image within the sub-tile, row, column) fields
   const int cap = dt == DT_F32 ? W9Cfg<float>::CAP : W9Cfg<bf16_t>::CAP;
   const int maxpos = dt == DT_F32 ? W9Cfg<float>::MAXPOS : W9Cfg<bf16_t>::MAXPOS;
-  W9Args a{}, by_rows{};
+  W9Args a{};
   if (!w9_geometry(g.N, g.P, g.Q, cap, maxpos, a)) return false;
   if (a.TP * 2 < cap) return false;  // short sub-tiles: too little work between barriers
   a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.P = g.P; a.Q = g.Q; a.pad = g.pad;
-  // 16 bits: ROWS, unless the padding of columns makes it more than a quarter more MFMAs; in blocks of 128 channels where none is
-  // needed (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us -> 396; 524 288, fp16: 59 -> 56; 128: see the kernel).
-  const bool rows_ok = dt != DT_F32 && w9_geometry(g.N, g.P, (g.Q + 7) / 8 * 8, cap, maxpos, by_rows, 4) && by_rows.TC % 8 == 0 &&
-                       (int64_t)by_rows.NT * ((by_rows.TI * (by_rows.TC / 8) + 1) / 2) * by_rows.TR * 4 <= (int64_t)a.NT * ((a.TP + 15) / 16) * 5 &&
-                       (int64_t)(by_rows.TI + 1) * (g.H + 2) * (g.W + 2) * std::max(g.C, g.K) < (int64_t)1 << 30;  // 32-bit offsets within a sub-tile's images
   // 128 output channels per block when possible (fewer operand fetches per MFMA, two wavefronts per SIMD), unless the blocks
   // would then get fewer than g_w9_wide_min sub-tiles each: a block's accumulators (9 taps x 64*MI x 64 floats) are
   // written out once per pixel range and read again by the reduction, and with few sub-tiles per range that traffic
@@ -760,14 +755,17 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
     if (mi == 2 && a.tiles_per_split < g_w9_wide_min) continue;
     if (mi == 2 && f32 && (ranges ? s != ranges : s * g.K * 9 * g.C * 4 > room / 4 * 3)) continue;
     if (tiles * s < 128) return false;  // too few blocks for the chip: one tap per block does better
-    if (rows_ok && (mi == 1 || g.Q % 8 == 0)) {  // its own sub-tiles, in no more ranges (whose sums take room in the activation arena)
-      W9Args r = a;
-      r.TI = by_rows.TI; r.TR = by_rows.TR; r.TC = by_rows.TC; r.SR = by_rows.SR; r.SC = by_rows.SC; r.NPOS = by_rows.NPOS; r.TP = by_rows.TP;
-      r.tiles_r = by_rows.tiles_r; r.tiles_c = by_rows.tiles_c; r.NT = by_rows.NT;
-      r.rows = 1;
-      r.tiles_per_split = (int)((r.NT + s - 1) / s);
-      s = (r.NT + r.tiles_per_split - 1) / r.tiles_per_split;
+    // 16 bits: ROWS, unless the padding of columns makes it more than a quarter more MFMAs; in blocks of 128 channels where none is
+    // needed (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us -> 396; 524 288, fp16: 59 -> 56; 128: see the
+    // kernel).  Its own sub-tiles, in no more ranges (whose sums take room in the activation arena).
+    W9Args r = a;
+    if (!f32 && (mi == 1 || g.Q % 8 == 0) && w9_geometry(g.N, g.P, (g.Q + 7) / 8 * 8, cap, maxpos, r, 4) && r.TC % 8 == 0 &&
+        (int64_t)r.NT * ((r.TI * (r.TC / 8) + 1) / 2) * r.TR * 4 <= (int64_t)a.NT * ((a.TP + 15) / 16) * 5 &&
+        (int64_t)(r.TI + 1) * (g.H + 2) * (g.W + 2) * std::max(g.C, g.K) < (int64_t)1 << 30) {  // 32-bit offsets within a sub-tile's images
       a = r;
+      a.rows = 1;
+      a.tiles_per_split = (int)((a.NT + s - 1) / s);
+      s = (a.NT + a.tiles_per_split - 1) / a.tiles_per_split;
     }
     pl.a = a; pl.mi = f32 ? 1 : mi; pl.splits = (int)s;
     return true;

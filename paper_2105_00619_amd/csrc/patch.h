@@ -27,7 +27,10 @@ struct PatchArgs {
   const float* fold;         // FOLD (forward): src is the z of a BatchNorm + ReLU, this its [4][srcC] statistics tensor; the
                              // pieces of the patch become the activation (scale, shift, ReLU, one rounding) on their way
                              // to LDS; positions outside the image stay zero
-  // k_conv_patch_wide.hip: positions of a patch's image and of its row, pixels of a tile's image and of its row, tiles
+};
+
+struct PatchWideArgs : PatchArgs {  // k_conv_patch_wide.hip
+  // positions of a patch's image and of its row, pixels of a tile's image and of its row, tiles
   FastDiv div_image, div_row, div_tile, div_tcol, div_tiles_r, div_tiles_c;
 };
 
