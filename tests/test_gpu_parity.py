@@ -624,7 +624,7 @@ def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w,
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b", [
     (128, 16, 16, 256), (256, 8, 8, 1024),  # exactly 256 tiles of 256 x 128 and of 256 x 256
-    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (512, 8, 8, 511), (128, 16, 16, 217)])
+    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217)])
 def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
     """3x3 layers on tiles of 256 pixels: one image, several, parts of one, a ragged last tile, two channel blocks; in 512 channels and
     at 217 images fewer tiles than fill the chip (the kernel's other shape, the narrower tiles).  Two basic blocks: forward with sums, with the BatchNorm
