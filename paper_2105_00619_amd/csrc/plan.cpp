@@ -394,7 +394,7 @@ struct Scheduler {
   // Is z, the output of convolution f or the input of the BatchNorm apply f, not written in this phase?  (In storage mode 2 a
   // projection shortcut's BatchNorm has an apply pass of its own, which reads it.)
   bool unwritten(const FOp& f, int phase) const {
-    return f.again && !p.separate && p.cfg.storage_mode != 2 && p.z_written < (phase == PH_FWD_NOSAVE ? 1 : 2);
+    return f.again && !p.separate && p.cfg.storage_mode != 2 && !(p.z_written && phase == PH_FWD_NOSAVE);
   }
   // What the z of a FOp::again convolution is made again from: its input tensor t or, with its statistics, the z of the BatchNorm
   // that t is the output of -- whichever is alive anyway where the pass keeps something for backward.
@@ -785,6 +785,30 @@ static bool schedule_operations(Plan& p) {
   return true;
 }
 
+// The most bytes alive at a step if passes that keep nothing wrote every z (an arena of such a plan is no smaller); ~0 if they do.
+static uint64_t alive_with_z_written(const Plan& p) {
+  std::vector<int> last(p.insts.size(), -1);
+  bool differs = false;
+  for (int i = 0; i < (int)p.sched.size(); ++i) {
+    const SOp& op = p.sched[i];
+    if (!op.live) continue;
+    for (int o : op.out) if (o >= 0) last[o] = i;
+    for (int x : op.in) if (x >= 0) last[x] = i;
+    if (op.phase == PH_FWD_NOSAVE && op.kind == S_BN_APPLY) differs = differs || op.again;
+    else for (int x : op.src) if (x >= 0) last[x] = i;
+  }
+  if (!differs) return ~0ull;
+  std::vector<int64_t> born(p.sched.size() + 1, 0);
+  for (size_t t = 0; t < p.insts.size(); ++t)
+    if (last[t] >= 0) {
+      born[p.insts[t].def_op] += (int64_t)aligned(p.insts[t].bytes);
+      born[last[t] + 1] -= (int64_t)aligned(p.insts[t].bytes);
+    }
+  int64_t alive = 0, most = 0;
+  for (int64_t b : born) most = std::max(most, alive += b);
+  return (uint64_t)most;
+}
+
 bool build_schedule(Plan& p, uint64_t enough) {
   if (!schedule_operations(p)) return false;
   const int n = (int)p.sched.size();
@@ -828,19 +852,17 @@ bool build_schedule(Plan& p, uint64_t enough) {
     if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), true);
   }
   for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
-  if (!p.separate && p.cfg.storage_mode != 2 && p.z_written == 0 && p.arena_bytes > enough &&
-      std::any_of(p.fops.begin(), p.fops.end(), [](const FOp& f) { return f.again != 0; })) {
-    // Where z is not written its source has to stay until the apply pass, which may be the fullest moment of a pass that keeps
-    // nothing: then z is written there, so that what a budget allows does not depend on it.  (The values are the same.)
-    Plan all = p;
-    all.z_written = 2;
-    if (!build_schedule(all, enough)) { p.error = all.error; return false; }
-    if (p.arena_bytes > all.arena_bytes) {
-      Plan some = p;
-      some.z_written = 1;
-      if (!build_schedule(some, enough)) { p.error = some.error; return false; }
-      p = some.arena_bytes > all.arena_bytes ? all : some;
-      p.z_written = 0;
+  if (p.arena_bytes > std::max(enough, alive_with_z_written(p))) {
+    // ... and the same for a z that is not written: what it is made from stays until the apply pass, which may be the fullest moment of a
+    // pass that keeps nothing, or placed worse.  Then z is written in those passes, so that what a budget allows does not depend on it.
+    // (The values are the same.  Passes that keep something keep the source too.  Of 420 000 random networks 15 are smaller with it
+    // written; comparing the bytes alive first leaves 1.6 % of those with such layers to be built twice.)
+    Plan q = p;
+    q.z_written = true;
+    if (!build_schedule(q, enough)) { p.error = q.error; return false; }
+    if (q.arena_bytes < p.arena_bytes) {
+      p = q;
+      p.z_written = false;
     }
   }
   return true;

@@ -152,7 +152,7 @@ struct Plan {
   std::vector<char> unit_sums;  // [unit] SUMS_INSIDE: kernels that write a gradient inside the unit also make the sums of the BatchNorm
                                 // backward in front; SUMS_SHORTCUT: the sums of a projection shortcut's BatchNorm come with its
                                 // block output's (choose_sums); empty: none
-  int z_written = 0;            // FOp::again: 0 no z is written, 1 those of passes that keep nothing, 2 all (build_schedule tries)
+  bool z_written = false;       // FOp::again: passes that keep nothing write z nevertheless (build_schedule compares)
   bool separate = false;        // schedule every pass of the backward as an operation of its own (what choose_sums measures by)
   // partition
   std::vector<int> seg_begin;  // k+1 entries, unit indices

@@ -8,16 +8,33 @@
 //     where it looks for them, writes neither over them nor over its own workspace, and stays inside its arena.
 // All of it twice: with the planner's defaults, and as the library's kernel choices would have it: workspaces for split depths,
 // BatchNorms folded into their readers, their backward sums made with the gradient, 1x1 layers whose backward is one kernel or
-// whose outputs are made again where they are read.
+// whose outputs are made again where they are read; and those once more with such outputs written in passes that keep nothing, which
+// the planner does where it makes the arena smaller.
 // Input: "k plan_mode precision batch height width channels classes storage_mode n_units" then n_units lines of
-// "kind cin cout ksize stride pad has_bn has_relu has_bias".  Output: "ok <arena> <peak_saved> <launches>" or an error.
+// "kind cin cout ksize stride pad has_bn has_relu has_bias".  Output: "ok <arena> <peak_saved> <launches>" or an error; with an
+// argument instead, for the library's choices, "again <outputs made again> <outputs written in passes that keep nothing> <memory
+// allocations of the schedule> <those of one whose comparison with written outputs is left out>".
 #include <cstdio>
 #include <cstdlib>
+#include <new>
 #include <vector>
 
 #include "plan.h"
 
 using namespace oseq;
+
+static long g_allocations = 0;
+void* operator new(std::size_t n, const std::nothrow_t&) noexcept {
+  ++g_allocations;
+  return std::malloc(n ? n : 1);
+}
+void* operator new(std::size_t n) {
+  if (void* q = operator new(n, std::nothrow)) return q;
+  throw std::bad_alloc();
+}
+void operator delete(void* q, const std::nothrow_t&) noexcept { std::free(q); }
+void operator delete(void* q) noexcept { std::free(q); }
+void operator delete(void* q, std::size_t) noexcept { std::free(q); }
 
 static int fail(const char* what, int op, int inst) {
   std::printf("error: %s (operation %d, tensor %d)\n", what, op, inst);
@@ -167,7 +184,32 @@ static void choose_as_the_library(Plan& p) {
   if (p.cfg.storage_mode == 2) p = given;
 }
 
-int main() {
+// The chosen plan with z written in passes that keep nothing: valid, and no smaller; how often z is made again, what building took.
+static int check_written(const Plan& p, Plan built, bool print) {
+  Plan q = p;
+  long at = g_allocations;
+  if (!build_schedule(q)) return fail("a second build fails", -1, -1);
+  const long whole = g_allocations - at;
+  if (q.arena_bytes != built.arena_bytes) return fail("a second build gives another arena", -1, -1);
+  Plan w = p;
+  w.z_written = true;
+  at = g_allocations;
+  if (!build_schedule(w)) return fail("no plan with z written", -1, -1);
+  const long once = g_allocations - at;
+  if (check_schedule(w)) return 1;
+  if (built.arena_bytes > w.arena_bytes) return fail("the arena is larger than with z written", -1, -1);
+  int again = 0, written = 0;
+  for (const SOp& s : built.sched)
+    if (s.live && s.kind == S_CONV_FWD && built.fops[s.fop].again) {
+      again += s.again;
+      written += !s.again;
+      if (!s.again && s.phase != PH_FWD_NOSAVE) return fail("z is written in a pass that keeps something", -1, -1);
+    }
+  if (print) std::printf("again %d %d %ld %ld\n", again, written, whole, once);
+  return 0;
+}
+
+int main(int argc, char**) {
   Plan given;
   int n_units = 0;
   optorch_seq_config_t& c = given.cfg;
@@ -184,8 +226,11 @@ int main() {
     Plan p = given;
     if (!build_graph(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
     if (chosen) choose_as_the_library(p);
-    if (!choose_segments(p) || !build_schedule(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
+    if (!choose_segments(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
+    const Plan unbuilt = p;
+    if (!build_schedule(p)) { std::printf("error: %s\n", p.error.c_str()); return 1; }
     if (check_schedule(p)) return 1;
+    if (chosen && p.cfg.storage_mode != 2 && check_written(unbuilt, p, argc > 1)) return 1;
     build_inference(p);
     if (check_inference(p)) return 1;
     inference_in_schedule(p);
@@ -193,6 +238,6 @@ int main() {
     if (check_inference(p)) return 1;
     if (!chosen) first = p;
   }
-  std::printf("ok %llu %llu %d\n", (unsigned long long)first.arena_bytes, (unsigned long long)first.peak_saved_bytes, first.n_launches);
+  if (argc == 1) std::printf("ok %llu %llu %d\n", (unsigned long long)first.arena_bytes, (unsigned long long)first.peak_saved_bytes, first.n_launches);
   return 0;
 }

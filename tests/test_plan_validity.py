@@ -95,3 +95,29 @@ def test_blocks_whose_outputs_are_made_again_plan_validly(checker, storage_mode)
     units = [W.bottleneck(8, 32), W.bottleneck(32, 32), W.bottleneck(32, 64), W.gap_linear_ce(64, 3)]
     for k in range(1, len(units) + 1):
         _run(checker, units, k, 0, W.FP16, 5, 12, 12, 8, 3, storage_mode)
+
+
+def _again(exe, units, k, plan_mode, batch, h, w, c, storage_mode):
+    lines = ["%d %d %d %d %d %d %d 3 %d %d" % (k, plan_mode, W.BF16, batch, h, w, c, storage_mode, len(units))]
+    lines += ["%d %d %d %d %d %d %d %d %d" % (u.kind, u.cin, u.cout, u.ksize, u.stride, u.pad, u.has_bn, u.has_relu, u.has_bias) for u in units]
+    r = subprocess.run([exe, "again"], input="\n".join(lines) + "\n", capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("again "), (r.stdout + r.stderr)[-2000:]
+    return [int(v) for v in r.stdout.split()[1:]]
+
+
+@pytest.mark.parametrize("storage_mode", [0, 1])
+def test_a_plan_with_outputs_made_again_is_built_once(checker, storage_mode):
+    """Whether a pass that keeps nothing should write them is told from the bytes alive, without a second schedule: no more memory
+    allocations than a schedule that is compared with nothing, and a few."""
+    units = [W.conv(3, 8), W.bottleneck(8, 32), W.bottleneck(32, 32), W.bottleneck(32, 64, 2), W.bottleneck(64, 64), W.gap_linear_ce(64, 3)]
+    for k in range(1, len(units) + 1):
+        again, written, whole, once = _again(checker, units, k, 2, 5, 24, 24, 3, storage_mode)
+        assert again > 0 and written == 0
+        assert whole <= 1.1 * once, k
+
+
+def test_outputs_are_written_in_passes_that_keep_nothing_where_that_is_smaller(checker):
+    """The one layer's input would outlive it in the first segment, in whose pass nothing is kept, at that pass's fullest step."""
+    units = [W.maxpool(), W.bottleneck(8, 8), W.conv(8, 16, stride=2), W.gap_linear_ce(16, 3)]
+    again, written, _, _ = _again(checker, units, 2, 2, 3, 17, 16, 8, 1)
+    assert (again, written) == (1, 1)
