@@ -472,7 +472,7 @@ void run_op(const Ctx& c, const SOp& s) {
       break;
     case S_CONV_BWD: {
       const FOp& ap = h->plan.fops[s.fop + 2];
-      launch_conv_bwd1x1(st, dt, c.at(s.in[0]), s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
+      launch_conv_bwd1x1(st, dt, c.at(s.in[0]), s.per_image ? c.at(s.in[1]) : nullptr, s.variant == 2 ? c.at(s.in[3]) : nullptr, (const float*)c.at(s.in[2]),
                          (const float*)c.at(s.in[4]) + (int64_t)s.rows * 2 * ap.C, ap.relu, s.per_image ? ap.P * ap.Q : 0,
                          c.at(s.in[5]), (const float*)c.at(s.in[6]), c.wc(f.w_off), h->pbase + h->off_wt + (uint64_t)f.w_off * h->plan.esize,
                          c.at(s.out[0]), c.g32(f.w_off), (float*)c.at(s.out[1]), f.bwd_splits, geom(f), (float*)c.at(s.out[2]));
@@ -539,9 +539,9 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
         *bytes = e * out_px * f.C * (1 + (s.out[3] >= 0 ? 1 : 0) + da + src + 2 + da + src + (s.out[1] >= 0 ? 1 : 0));
       }
       break;
-    case S_CONV_BWD:  // dA and the ReLU source, x, dx, the weights and their gradient (z is made again from x)
+    case S_CONV_BWD:  // dA and the ReLU source, x, dx, the weights and their gradient (z is made again from x; dA per image: z is read)
       *flops = 4 * out_px * wts;
-      *bytes = e * out_px * f.K * ((s.per_image ? 0.0 : 1.0) + (s.in[3] < 0 ? 0.0 : 1.0 / 16)) + e * in_px * f.C * 2 + (e + 4) * wts;
+      *bytes = e * out_px * f.K * (1.0 + (s.in[3] < 0 ? 0.0 : 1.0 / 16)) + e * in_px * f.C * 2 + (e + 4) * wts;
       break;
     case S_POOL_FWD: *bytes = e * (in_px + out_px) * f.C; break;
     case S_POOL_BWD: *bytes = e * (2 * in_px + out_px) * f.C; break;

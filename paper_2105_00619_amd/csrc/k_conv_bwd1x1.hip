@@ -8,9 +8,12 @@
 //
 // Apart, these are three kernels: the first reads dA and z and writes dz, the others read dz again, one of them x -- at 4.2 M
 // pixels in bf16 1176 + 516 + 520 us for 6.6 + 2.7 + 2.7 GB.  Here a pixel's dz exists in LDS only, and its z too: that is the
-// layer's own output, made again from the x that is here for the weight gradient (a fifth of the products, in the forward kernel's
-// order, hence its bits).  3.2 GB; reading z too (5.4 GB) was bound by HBM at 1140 us, with dA per image 908; now 790 (869 with a
-// BatchNorm in front, 932 per image), where the LDS (100 KB a tile) and the vector instructions around it take as long as memory.
+// layer's own output, made again from the x that is here for the weight gradient (a third of the products, in the forward kernel's
+// order, hence its bits).  Reading z (5.4 GB) was bound by HBM; without it (3.3 GB) the LDS (100 KB a tile) and the vector
+// instructions around it take as long as memory.  us, z read -> made again, also where it is in memory anyway, without and with a
+// BatchNorm in front: 4.2 M pixels 1134 -> 820, 1087 -> 905; 131 072 43 -> 35, 42 -> 38.5; 65 536 26 -> 23.5, 26.8 -> 25.9.
+// With dA per image z is the one large tensor to read, and always there: read, at the same three sizes, 811, 35.3 and 24.4
+// (made again 950, 38.4 and 26.7).
 //
 // A block of 512 threads (8 wavefronts, one block per CU: 256 blocks) walks a range of tiles of 64 pixels.  Per tile, two barriers:
 // dz of the tile from z (LDS) and the pieces of dA and mask, requested a tile ahead, and the next tile's x into LDS; then every
@@ -53,15 +56,16 @@ struct Bwd1Args {
 };
 
 // MS: ReLU decisions redone from z (0; none if relu is not set) or from the bits of mask (2); GV: dA is the gradient per image
-// (both as in bn_bwd_apply_kernel).  FOLD: x is the z of a BatchNorm + ReLU, fold its statistics.
+// (both as in bn_bwd_apply_kernel), and z is read.  FOLD: x is the z of a BatchNorm + ReLU, fold its statistics.
 // sums (with FOLD, or null): the block's row of the sums that the folded BatchNorm's backward pass begins with, dx being the gradient
 // behind it and its z at hand (at 4.2 M pixels the pass over both took 183 us)
 template <class T, int MS, bool GV, bool FOLD>
-__global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ da, const uint8_t* __restrict__ mask,
-                                                         const float* __restrict__ stats, const float* __restrict__ coef,
-                                                         const T* __restrict__ x, const float* __restrict__ fold,
-                                                         const T* __restrict__ w, const T* __restrict__ wt, T* __restrict__ dx,
-                                                         float* __restrict__ dw, float* __restrict__ sums, Bwd1Args a) {
+__global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ da, const T* __restrict__ z,
+                                                         const uint8_t* __restrict__ mask, const float* __restrict__ stats,
+                                                         const float* __restrict__ coef, const T* __restrict__ x,
+                                                         const float* __restrict__ fold, const T* __restrict__ w,
+                                                         const T* __restrict__ wt, T* __restrict__ dx, float* __restrict__ dw,
+                                                         float* __restrict__ sums, Bwd1Args a) {
   typedef typename Op<T>::V V;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* Ds = reinterpret_cast<T*>(smem_raw);
@@ -74,7 +78,7 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
   const int hg = lane >> 5, l32 = lane & 31;
   // weights: [256][64]
 #pragma unroll
-  for (int i = 0; i < BC * BK / 8 / NT; ++i) {
+  for (int i = 0; i < (GV ? 0 : BC * BK / 8 / NT); ++i) {
     const int id = tid + i * NT, k = id / (BC / 8), c8 = id % (BC / 8);
     *reinterpret_cast<Chunk*>(&Ws[k * WP + c8 * 8]) = *reinterpret_cast<const Chunk*>(w + (int64_t)k * BC + c8 * 8);
   }
@@ -108,7 +112,7 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
   const int64_t t1 = t0 + a.tiles_per_block < ntiles ? t0 + a.tiles_per_block : ntiles;
 
   constexpr int ND = PM * (BK / 8) / NT;  // pieces of dz per thread
-  Chunk ra[ND], rx;
+  Chunk ra[ND], rz[GV ? ND : 1], rx;
   unsigned rm[ND];
   auto gload_x = [&](int64_t t) {  // pixels past the last one read that one
     int64_t m = t * PM + px;
@@ -120,8 +124,9 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
     for (int i = 0; i < ND; ++i) {
       int64_t m = t * PM + pd + i * (PM / ND);
       m = m < a.M ? m : a.M - 1;
-      // (read once; non-temporal 1166 -> 1139 us at 4.2 M pixels)
-      if (!GV) ra[i] = __builtin_nontemporal_load(reinterpret_cast<const Chunk*>(da + m * BK + k0));
+      // (read once; non-temporal 1166 -> 1139 us at 4.2 M pixels, z under a pool 879 -> 904)
+      if (GV) rz[i] = *reinterpret_cast<const Chunk*>(z + m * BK + k0);
+      else ra[i] = __builtin_nontemporal_load(reinterpret_cast<const Chunk*>(da + m * BK + k0));
       rm[i] = MS == 2 ? mask[m * (BK / 8) + (tid & 31)] : 0u;
     }
     if (GV) {  // (the divisions stay behind the loads from memory)
@@ -141,7 +146,8 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       const int p = pd + i * (PM / ND);
-      const Vec<T, 8> va = __builtin_bit_cast(Vec<T, 8>, ra[i]), vz = *reinterpret_cast<const Vec<T, 8>*>(&Zs[p * ZP + k0]);
+      const Vec<T, 8> va = __builtin_bit_cast(Vec<T, 8>, ra[i]);
+      const Vec<T, 8> vz = GV ? __builtin_bit_cast(Vec<T, 8>, rz[GV ? i : 0]) : *reinterpret_cast<const Vec<T, 8>*>(&Zs[p * ZP + k0]);
       float r[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -198,9 +204,11 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
     xstore(t0);
     xz = rx;
     gload_x(t0 + 1);
-    __syncthreads();
-    zstore(t0);
-    __syncthreads();
+    if (!GV) {
+      __syncthreads();
+      zstore(t0);
+      __syncthreads();
+    }
   }
   for (int64_t t = t0; t < t1; ++t) {
     dzstore(t);
@@ -232,7 +240,7 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
         acc[j] = Op<T>::mma32(fa, lds_tr_read8<V>(pb, pb + 4 * XP), acc[j]);
       }
     }
-    if (t + 1 < t1) zstore(t + 1);
+    if (!GV && t + 1 < t1) zstore(t + 1);
     __syncthreads();
     const int64_t m = t * PM + px;
     const v4f* oa = reinterpret_cast<const v4f*>(&Os[px * OP + c0]);
@@ -270,35 +278,36 @@ __global__ void __launch_bounds__(NT) conv1x1_bwd_kernel(const T* __restrict__ d
 }
 
 template <class T, int MS, bool GV, bool FOLD>
-void launch_t(hipStream_t st, const void* da, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
+void launch_t(hipStream_t st, const void* da, const void* z, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
               const void* w, const void* wt, void* dx, float* dw, float* sums, int blocks, const Bwd1Args& a) {
   static bool attr_done = false;
   if (!attr_done) {
     (void)hipFuncSetAttribute((const void*)conv1x1_bwd_kernel<T, MS, GV, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BWD1_LDS);
     attr_done = true;
   }
-  OSEQ_LAUNCH((conv1x1_bwd_kernel<T, MS, GV, FOLD>), dim3(blocks), dim3(NT), BWD1_LDS, st, (const T*)da, mask, stats, coef, (const T*)x,
+  OSEQ_LAUNCH((conv1x1_bwd_kernel<T, MS, GV, FOLD>), dim3(blocks), dim3(NT), BWD1_LDS, st, (const T*)da, (const T*)z, mask, stats, coef, (const T*)x,
               fold, (const T*)w, (const T*)wt, (T*)dx, dw, sums, a);
 }
 
 template <class T, int MS, bool GV>
-void launch_f(hipStream_t st, const void* da, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
+void launch_f(hipStream_t st, const void* da, const void* z, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
               const void* w, const void* wt, void* dx, float* dw, float* sums, int blocks, const Bwd1Args& a) {
-  if (fold) launch_t<T, MS, GV, true>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
-  else launch_t<T, MS, GV, false>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  if (fold) launch_t<T, MS, GV, true>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  else launch_t<T, MS, GV, false>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
 }
 
 template <class T>
-void launch_dt(hipStream_t st, const void* da, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
+void launch_dt(hipStream_t st, const void* da, const void* z, const uint8_t* mask, const float* stats, const float* coef, const void* x, const float* fold,
                const void* w, const void* wt, void* dx, float* dw, float* sums, int blocks, const Bwd1Args& a, bool gv) {
-  if (mask && gv) launch_f<T, 2, true>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
-  else if (mask) launch_f<T, 2, false>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
-  else if (gv) launch_f<T, 0, true>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
-  else launch_f<T, 0, false>(st, da, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  if (mask && gv) launch_f<T, 2, true>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  else if (mask) launch_f<T, 2, false>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  else if (gv) launch_f<T, 0, true>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
+  else launch_f<T, 0, false>(st, da, z, mask, stats, coef, x, fold, w, wt, dx, dw, sums, blocks, a);
 }
 
-// Four tiles a block.  A step of a 64 -> 256 and a 256 -> 256 block in bf16, us with separate kernels -> with this one: 65 536 pixels 636 -> 566,
-// 131 072 932 -> 811; below the line it would gain too (16 384: 442 -> 413), down to one tile a block at 4096 (369 -> 344).
+// Four tiles a block.  A step of a 64 -> 256 and a 256 -> 256 block in bf16, us with separate kernels -> with this one in its form that
+// reads z (which is slower than this one throughout, see above): 65 536 pixels 636 -> 566, 131 072 932 -> 811; below the line that
+// gained too (16 384: 442 -> 413), down to one tile a block at 4096 (369 -> 344).
 constexpr int64_t g_bwd1_min_pixels = 65536;
 
 }  // namespace
@@ -313,7 +322,7 @@ int conv_bwd1x1_splits(const ConvGeom& g) {
   return (int)((tiles + per - 1) / per);  // no empty ranges
 }
 
-void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* mask, const float* stats, const float* coef, int relu,
+void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* z, const void* mask, const float* stats, const float* coef, int relu,
                         int per_image, const void* x, const float* fold, const void* w, const void* wt, void* dx, float* dw, float* partial,
                         int splits, const ConvGeom& g, float* sums) {
   Bwd1Args a;
@@ -322,8 +331,8 @@ void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* mask
   a.relu = relu;
   a.div_hw = make_fastdiv((uint32_t)(per_image > 0 ? per_image : 1));
   float* dst = splits > 1 ? partial : dw;
-  if (dt == DT_BF16) launch_dt<bf16_t>(st, da, (const uint8_t*)mask, stats, coef, x, fold, w, wt, dx, dst, sums, splits, a, per_image > 0);
-  else launch_dt<f16_t>(st, da, (const uint8_t*)mask, stats, coef, x, fold, w, wt, dx, dst, sums, splits, a, per_image > 0);
+  if (dt == DT_BF16) launch_dt<bf16_t>(st, da, z, (const uint8_t*)mask, stats, coef, x, fold, w, wt, dx, dst, sums, splits, a, per_image > 0);
+  else launch_dt<f16_t>(st, da, z, (const uint8_t*)mask, stats, coef, x, fold, w, wt, dx, dst, sums, splits, a, per_image > 0);
   if (splits > 1) launch_wgrad_reduce(st, partial, dw, (int64_t)BK * BC, splits);
 }
 

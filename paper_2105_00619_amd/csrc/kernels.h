@@ -157,11 +157,11 @@ int conv_mfma_wgrad_splits(int dt, const ConvGeom& g, int64_t room);
 void launch_conv_wgrad_mfma(hipStream_t st, int dt, const void* x, const void* dz, float* dw, float* partial, int splits,
                             const ConvGeom& g, const float* fold = nullptr);
 // The backward pass of a 1x1 layer and of the BatchNorm behind it as one kernel (k_conv_bwd1x1.hip).  da .. relu, per_image as for
-// launch_bn_bwd (decisions from mask or redone from z); coef: what its finishing kernel left behind the partial sums, [2][C_out];
+// launch_bn_bwd (decisions from mask or redone from z; z: only read with per_image, made again otherwise); coef: what its finishing kernel left behind the partial sums, [2][C_out];
 // x, fold, partial, splits as for the weight gradient, wt, dx as for the data gradient
 bool conv_bwd1x1_ok(int dt, const ConvGeom& g);
 int conv_bwd1x1_splits(const ConvGeom& g);
-void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* mask, const float* stats, const float* coef, int relu,
+void launch_conv_bwd1x1(hipStream_t st, int dt, const void* da, const void* z, const void* mask, const float* stats, const float* coef, int relu,
                         int per_image, const void* x, const float* fold, const void* w, const void* wt, void* dx, float* dw, float* partial,
                         int splits, const ConvGeom& g, float* sums);
 // sums (null, or with fold): as DgradSums::partial for the folded BatchNorm, [splits][2][C_in]

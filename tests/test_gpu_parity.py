@@ -622,6 +622,20 @@ def test_backward_of_wide_1x1_layers_in_one_pass(precision, chain, blocks, h, w,
 
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("block", [False, True])
+def test_backward_under_a_pool_reads_the_output_it_has(precision, block):
+    """The last layer's output is in memory, and its gradient is one row per image: the output is read, not made again."""
+    b, h, w = 259, 15, 17
+    units = [W.conv(8, 64, 1)] + ([W.bottleneck(64, 256)] if block else [W.conv(64, 256, 1)]) + [W.gap_linear_ce(256, 10)]
+    work = _against_float64(units, b, h, w, precision)
+    px = b * h * w
+    layer = 2 * px * (256 + 2 * 64) + 6 * 64 * 256  # z, x and dx, the weights and their gradient
+    if block:  # two of them, with their ReLU decisions as bits, and the first layer's data gradient with an addend
+        layer = 2 * (layer + 2 * px * 16) + 2 * (px * 64 * 3 + 64 * 64)
+    assert work["conv1x1_dgrad"]["bytes"] == layer
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b", [
     (128, 16, 16, 256), (256, 8, 8, 1024),  # exactly 256 tiles of 256 x 128 and of 256 x 256
     (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217)])
