@@ -510,7 +510,11 @@ void work_of(const optorch_seq_t* h, const SOp& s, double* flops, double* bytes)
   *flops = 0; *bytes = 0;
   switch (s.kind) {
     case S_CAST_IN: *bytes = in_px * f.C * ((h->x_encoded ? 1 : 4) + e); break;  // an encoded batch: one byte per pixel
-    case S_CONV_FWD: *flops = 2 * out_px * wts; *bytes = e * (in_px * f.C + (s.again ? 0.0 : out_px * f.K) + wts); break;
+    case S_CONV_FWD:
+      if (s.again && s.phase == PH_REPLAY) break;  // (not run)
+      *flops = 2 * out_px * wts;
+      *bytes = e * (in_px * f.C + (s.again ? 0.0 : out_px * f.K) + wts);
+      break;
     case S_DGRAD:
       *flops = 2 * out_px * wts;
       *bytes = e * (in_px * f.C * (s.in[1] >= 0 && !s.per_image ? 2 : 1) + out_px * f.K + wts) + (s.in[2] >= 0 ? e * in_px * f.C / 16 : 0) +

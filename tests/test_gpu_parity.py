@@ -701,6 +701,23 @@ def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b):
             assert r["loss"] == want["loss"] and np.array_equal(r["grads"], want["grads"]), (mode, k)
 
 
+def test_work_of_a_replay_without_block_outputs():
+    """A replay leaves out the forward passes of layers whose outputs are made again, and counts no work for them."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(8, 64, 1), W.bottleneck(64, 256), W.bottleneck(256, 64), W.gap_linear_ce(64, 10)]
+    b, h, w = 128, 32, 32
+    t = SeqTrainer(units, k_segments=2, boundaries=[2], precision=W.BF16, batch=b, height=h, width=w, channels=8, num_classes=10)
+    t.set_params(W.make_params(units, h, w, perturb=True))
+    t.profile_enable()
+    t.step(torch.ones((b, h, w, 8), device="cuda"), torch.zeros(b, device="cuda", dtype=torch.int32), 0.0)
+    replay = [e for e in t.profile_read_entries() if e["phase"] == 2 and e["unit"] == 1 and e["kind"] == "conv1x1_fwd"]
+    t.close()
+    run = [e for e in replay if e["gpu_ms"] > 0]
+    assert len(replay) == 3 and len(run) == 1  # the first layer; the last one and the projection shortcut are not run
+    assert all((e["flops"] > 0) == (e["gpu_ms"] > 0) and (e["bytes"] > 0) == (e["gpu_ms"] > 0) for e in replay)
+
+
 @pytest.mark.parametrize("precision", [W.FP32, W.BF16, W.FP16])
 @pytest.mark.parametrize("body,h,w,b", [
     ([W.conv(8, 64, 1)], 61, 67, 2), ([W.conv(8, 64, 1), W.basic_block(64, 64)], 61, 67, 2),
