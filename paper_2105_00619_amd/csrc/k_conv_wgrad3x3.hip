@@ -122,7 +122,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
   int* apos = reinterpret_cast<int*>(lds + (F32 ? 1 : 2) * STAGE);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = __builtin_amdgcn_readfirstlane(wave / (2 * WGM)), wq = wave % (2 * WGM);
+  const int grp = PG == 2 ? __builtin_amdgcn_readfirstlane(wave / (2 * WGM)) : 0, wq = PG == 2 ? wave % (2 * WGM) : wave;
   const int wm = wq >> 1, wn = wq & 1, hg = lane >> 5, l32 = lane & 31;
   // Block coordinates: (output-channel tile, input-channel tile, pixel range).  The tiles of one pixel range all read
   // the same pixels of x and dz; workgroups go to the 8 XCDs round-robin by their linear index and every XCD has an L2
