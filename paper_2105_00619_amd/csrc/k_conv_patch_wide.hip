@@ -386,11 +386,9 @@ void launch_shape(hipStream_t st, const void* src, const void* wmat, const float
   a.div_image = make_fastdiv(a.SR * a.SC); a.div_row = make_fastdiv(a.SC);
   a.div_tile = make_fastdiv(a.TR * a.TC); a.div_tcol = make_fastdiv(a.TC);
   a.div_tiles_r = make_fastdiv(a.tiles_r); a.div_tiles_c = make_fastdiv(a.tiles_c);
-  a.xcd_group = 0;
-  if (grid.y >= 2 && grid.x >= 64) {  // (from the shape only)
-    a.xcd_group = 2;
-    grid.x = (grid.x + 7) / 8 * 8;
-  }
+  const int per_xcd = conv_patch_wide_rows_per_xcd(a.NT, (int)grid.y);
+  a.xcd_group = per_xcd > 0 ? 2 : 0;
+  if (per_xcd > 0) grid.x = per_xcd * 8;
   const size_t sm = conv_patch_wide_lds(64 * NI, a.patch_elems);
 #define LAUNCH(STAT, FOLD, EVAL, ADD) launch_one<T, MI, NI, STAT, FOLD, EVAL, ADD>(st, src, wmat, bias, addend, out, stat_partial, grid, sm, a)
   if (a.eval && addend) LAUNCH(0, false, true, true);
@@ -412,6 +410,14 @@ void launch_type(hipStream_t st, const void* src, const void* wmat, const float*
 }
 
 }  // namespace
+
+// From the shape only.  Not where the 32 CUs of an XCD would have more rounds to do than the 256 have together: three channel blocks of
+// 84 row tiles are 252 blocks, but 33 of them on an XCD (256 -> 384 channels over 21 504 pixels in bf16, us forward: narrow tiles 48, with
+// the blocks grouped 66, without 38; 640 -> 640 over 25 600 361, 444 and 314).
+int conv_patch_wide_rows_per_xcd(int row_tiles, int channel_blocks) {
+  const int64_t rows = (row_tiles + (int64_t)7) / 8, rounds = ((int64_t)row_tiles * channel_blocks + 255) / 256;
+  return channel_blocks >= 2 && row_tiles >= 64 && (rows * channel_blocks + 31) / 32 <= rounds ? (int)rows : 0;
+}
 
 size_t conv_patch_wide_lds(int bn, int patch_elems) {
   return (size_t)HEAD + std::max<size_t>((size_t)(2 * patch_elems + 3 * bn * PITCH) * 2, (size_t)epi_bytes(bn));

@@ -48,6 +48,8 @@ inline int patch_rows_apart(int tc, int sc, int pos_bytes) {
 // block tiles of 256 pixels x bn (256 or 128) channels by one wavefront per SIMD (k_conv_patch_wide.hip)
 constexpr int PATCH_WIDE_MAX_POS = 576;  // positions of its patch
 size_t conv_patch_wide_lds(int bn, int patch_elems);
+// row tiles whose channel blocks run on one XCD, 0: blocks in their own order
+int conv_patch_wide_rows_per_xcd(int row_tiles, int channel_blocks);
 void launch_conv_patch_wide(hipStream_t st, int dt, const void* src, const void* wmat, const float* bias, const void* addend, void* out,
                             float* stat_partial, int bn, const PatchArgs& a);
 
