@@ -951,18 +951,46 @@ static constexpr int g_patch_halo2 = 9;         // largest staged positions : pi
 static constexpr int g_patch_target_small = 512;  // blocks aimed at by the depth split for the smallest block shape in fp32
 static constexpr int64_t g_patch_xcd_wbytes = 4 << 20;  // XCD grouping of the blocks: least weight bytes (0: never) ...
 static constexpr int g_patch_xcd_rows = 16;              // ... and most row tiles
+enum PatchUse { PATCH_FWD, PATCH_EVAL, PATCH_DGRAD };  // forward pass of a step, inference, data gradient
 // 16 bits: tiles of 256 pixels x 256 channels, else x 128, by one wavefront per SIMD (k_conv_patch_wide.hip).  A CU holds one such
 // block, so the rounds of 256 blocks have to be full: at least 85 % of their products have to be wanted ones, which leaves out
 // layers of less than 218 tiles -- one of 128 tiles would leave half of the CUs idle -- and maps that tile badly (14 x 14: 77 %).
-// Exactly 256 tiles of 256 x 128 (128 -> 128 channels at 65 536 pixels, bf16): 31.3 -> 28.8 us forward, data gradient 31.5 -> 30.6.
-static bool patch_pick_wide(int N, int dstH, int dstW, int srcC, int Ng, PatchShape& shape, PatchArgs& geo) {
+// Then, in bf16, time over the narrow tiles' at 16 x 16 pixels a map, one round at 88 % and at 99 %:
+//   forward with sums   channels 32 -> 128 0.84 0.85, 64 -> 128 0.85 0.88, 128 -> 128 0.83 0.96, 128 -> 256 0.87 0.90, 512 -> 512 0.77 0.89
+//   data gradient       128 -> 128 0.88 1.01, 256 -> 256 0.85 0.96
+// Beyond a round nothing covers a block's epilogue and the next one's beginning, where two narrow blocks on a CU are no longer in
+// step.  What that costs depends on the products a block has in between:
+//   tiles of 128 channels, two rounds and more: 32 -> 128 1.11 - 1.30, 64 -> 128 1.03 - 1.12, 128 -> 128 0.99 - 1.12 forward and 1.03 - 1.25 in
+//     the data gradient (a step of a block 1.00 - 1.06).  256 -> 256, with the BatchNorm sums of a data gradient that 256 pixels a
+//     tile make few enough to come with it: a step 0.98 - 0.99, from the fourth round on 0.99 - 1.02 below 93 % and 0.98 above;
+//     384 -> 384 0.97 - 1.00, 640 -> 640 0.94 - 0.99
+//   of 256 channels: 32 -> 256 0.98 - 1.12, 64 -> 256 0.94 - 1.04, 128 -> 256 0.90 - 0.99, 256 -> 256 and deeper 0.79 - 0.95
+// Where the narrow tiles fit a map a tenth worse (4 x 4 and 7 x 7) or not at all the wide ones are ahead at every depth (128 -> 128
+// over 131 072 pixels 0.64 and 0.84), and in inference, whose epilogue is short, too: 128 -> 128 in several rounds 0.91, at 64 x 128 1.0.
+static bool patch_wide_pays(PatchUse use, int N, int dstH, int dstW, int srcC, int bn, int64_t wanted, const PatchArgs& a, int64_t blocks) {
+  const int64_t rounds = (blocks + 255) / 256, offered = rounds * 256 * 256 * bn;
+  if (wanted * 20 < offered * 17) return false;
+  if (rounds == 1 || use == PATCH_EVAL) return true;
+  if (srcC >= (bn == 256 ? 128 : 384)) return true;
+  if (srcC >= (bn == 256 ? 64 : 256) && (wanted * 100 >= offered * 93 || (bn == 128 && rounds <= 3))) return true;
+  PatchArgs n{};
+  return !patch_geometry(N, dstH, dstW, 128, true, n) || n.TP * 4 < 128 * 3 || n.NPOS * 2 > n.TP * g_patch_halo2 ||
+         (int64_t)n.NT * 10 >= (int64_t)2 * a.NT * 11;
+}
+static bool patch_pick_wide(PatchUse use, int N, int dstH, int dstW, int srcC, int Ng, PatchShape& shape, PatchArgs& geo) {
+  const int64_t wanted = (int64_t)N * dstH * dstW * Ng;
   for (int bn = 256; bn >= 128; bn /= 2) {
-    if (Ng % bn != 0 || (int64_t)N * dstH * dstW * Ng * 20 < (int64_t)17 * 256 * 256 * bn) continue;  // (fewer than a round's)
+    if (Ng % bn != 0 || wanted * 20 < (int64_t)17 * 256 * 256 * bn) continue;  // (fewer than a round's)
     PatchArgs a{};
     if (!patch_geometry(N, dstH, dstW, 256, true, a, PATCH_WIDE_MAX_POS)) continue;
+    // as few tiles with a fifth fewer staged positions (wide maps: 16 x 16 pixels for 2 x 128; 128 -> 128 channels at 64 x 128, one full
+    // round, forward and data gradient 1.02 and 1.06 of the narrow tiles' time -> 0.98 and 1.01)
+    for (int tc = 64; tc >= 8; tc /= 2) {
+      PatchArgs b{};
+      if (tc < dstW && patch_geometry_of(N, dstH, dstW, tc, 256, b, PATCH_WIDE_MAX_POS) && b.NT <= a.NT && b.NPOS * 5 <= a.NPOS * 4) a = b;
+    }
     if ((int64_t)a.TI * (dstH + 2) * (dstW + 2) * srcC >= (int64_t)1 << 30) continue;  // 32-bit offsets within a tile's images
-    const int64_t blocks = (int64_t)a.NT * (Ng / bn), offered = (blocks + 255) / 256 * 256 * 256 * bn;
-    if ((int64_t)N * dstH * dstW * Ng * 20 < offered * 17) continue;
+    if (!patch_wide_pays(use, N, dstH, dstW, srcC, bn, wanted, a, (int64_t)a.NT * (Ng / bn))) continue;
     const auto fits = [&] { return conv_patch_wide_lds(bn, (a.TI * a.SR * a.row_pitch + 15) / 16 * 8) <= 160 * 1024; };
     a.row_pitch = patch_row_pitch(a, 1, 80, PATCH_WIDE_MAX_POS);
     if (!fits()) a.row_pitch = a.SC * 80;
@@ -973,16 +1001,16 @@ static bool patch_pick_wide(int N, int dstH, int dstW, int srcC, int Ng, PatchSh
   }
   return false;
 }
-static bool patch_pick(int dt, bool split32, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride, PatchShape& shape,
-                       PatchArgs& geo) {
+static bool patch_pick(int dt, bool split32, PatchUse use, int N, int dstH, int dstW, int srcC, int Ng, int R, int S, int stride,
+                       PatchShape& shape, PatchArgs& geo) {
   if (R != 3 || S != 3 || stride != 1) return false;
   if (srcC % (dt == DT_F32 ? 16 : 32) != 0 || Ng % 64 != 0) return false;
-  if (dt != DT_F32 && patch_pick_wide(N, dstH, dstW, srcC, Ng, shape, geo)) return true;
+  if (dt != DT_F32 && patch_pick_wide(use, N, dstH, dstW, srcC, Ng, shape, geo)) return true;
   // (Split32: 128 x 128 tiles take the LDS of a CU alone, and a layer of 128 channels at 262 144 pixels 515 us with them, 445 without)
   const int wide = Ng % 128 == 0 && !split32 ? 128 : 64;
-  // Candidates, largest first.  Two co-resident blocks per CU cover each other's prologue, barriers and epilogue, and
-  // measured better than one block of twice the size at every layer of the benchmark networks, so the first
-  // candidate that gives g_patch_fill (two per CU) blocks is taken, else the one with the most blocks.
+  // What is left: fp32, and in 16 bits few pixels or little depth.  Candidates, largest first.  Two co-resident blocks per CU cover
+  // each other's prologue, barriers and epilogue, and measured better here than one block of twice the size at every layer of the
+  // benchmark networks, so the first candidate that gives g_patch_fill (two per CU) blocks is taken, else the one with the most blocks.
   const PatchShape cand[3] = {{2, 1, wide, 1, false}, {2, 1, 64, 1, false}, {1, 1, 64, 1, false}};
   int best = -1;
   int64_t best_blocks = 0;
@@ -1211,7 +1239,7 @@ int conv_mfma_fwd_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
   if (fwd_ws3x3(dt, g)) return 1;
   if (conv_pointwise_fwd_ok(dt, g)) return 1;
-  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, pa)) return v.splits;
+  if (patch_pick(dt, fwd_split32(dt, g), PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, pa)) return v.splits;
   return igemm_splits(dt, (int64_t)g.N * g.P * g.Q, g.K, g.R * g.S * g.C);
 }
 // stride 2, even image, at most 3x3: the data gradient runs as four parity-class GEMMs in one launch
@@ -1223,7 +1251,7 @@ int conv_mfma_dgrad_splits(int dt, const ConvGeom& g) {
   PatchShape v; PatchArgs pa{};
   if (dgrad_ws3x3(dt, g)) return 1;
   if (conv_pointwise_dgrad_ok(dt, g)) return 1;
-  if (patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
+  if (patch_pick(dt, dt == DT_F32, PATCH_DGRAD, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
   if (dgrad_by_classes(g)) return 1;
   return igemm_splits(dt, (int64_t)g.N * g.H * g.W, g.C, g.R * g.S * g.K);
 }
@@ -1244,7 +1272,7 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias) {
   const int64_t M = (int64_t)g.N * g.P * g.Q;
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_stat_blocks(g);
   if (!bias && fwd_ws3x3(dt, g)) return conv_ws3x3_stat_blocks(g);
-  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
+  if (patch_pick(dt, fwd_split32(dt, g), PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa))
     return pv.splits > 1 ? ceil_div(M, split_epi_rows(M, g.K)) : (pa.NT + pv.subt - 1) / pv.subt;
   if (igemm_splits(dt, M, g.K, g.R * g.S * g.C) > 1) return ceil_div(M, split_epi_rows(M, g.K));
   return ceil_div(M, IGEMM_BM);
@@ -1256,7 +1284,7 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias) {
 bool conv_fold_fwd_ok(int dt, const ConvGeom& g) {
   if (conv_pointwise_fwd_ok(dt, g)) return conv_pointwise_fold_ok(dt, g);
   PatchShape pv; PatchArgs pa{};
-  return dt != DT_F32 && patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa);
+  return dt != DT_F32 && patch_pick(dt, fwd_split32(dt, g), PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa);
 }
 
 void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, const float* bias, void* out,
@@ -1272,7 +1300,7 @@ void launch_conv_fwd_mfma(hipStream_t st, int dt, const void* x, const void* w, 
     return;
   }
   const bool eval = ev.affine != nullptr;
-  if (patch_pick(dt, fwd_split32(dt, g), g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
+  if (patch_pick(dt, fwd_split32(dt, g), eval ? PATCH_EVAL : PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.H; pa.srcW = g.W; pa.srcC = g.C; pa.dstH = g.P; pa.dstW = g.Q; pa.Ng = g.K;
     pa.pad = g.pad; pa.flip = 0; pa.relu = relu;
     pa.fold = dt == DT_F32 ? nullptr : fold;
@@ -1295,7 +1323,7 @@ bool conv_dgrad_image_addend_ok(int dt, const ConvGeom& g) {
 int conv_dgrad_sum_blocks(int dt, const ConvGeom& g) {
   PatchShape pv; PatchArgs pa{};
   if (conv_pointwise_dgrad_ok(dt, g) || dgrad_ws3x3(dt, g)) return 0;
-  if (!patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa) || pv.splits > 1) return 0;
+  if (!patch_pick(dt, dt == DT_F32, PATCH_DGRAD, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa) || pv.splits > 1) return 0;
   const int blocks = (pa.NT + pv.subt - 1) / pv.subt;
   return bn_stats_fold_rows(blocks) > 0 ? 0 : blocks;
 }
@@ -1314,7 +1342,7 @@ void launch_conv_dgrad_mfma(hipStream_t st, int dt, const void* dz, const void* 
     launch_conv_dgrad_ws3x3(st, dt, dz, wt, dx, g);
     return;
   }
-  if (patch_pick(dt, dt == DT_F32, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {
+  if (patch_pick(dt, dt == DT_F32, PATCH_DGRAD, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, pv, pa)) {
     pa.N = g.N; pa.srcH = g.P; pa.srcW = g.Q; pa.srcC = g.K; pa.dstH = g.H; pa.dstW = g.W; pa.Ng = g.C;
     pa.pad = g.R - 1 - g.pad; pa.flip = 1; pa.relu = 0; pa.amask = amask;
     if (sums.partial) {

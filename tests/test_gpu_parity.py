@@ -546,7 +546,7 @@ def _grads64(units, params, x, y, precision, scale):
 
 def _against_float64(units, b, h, w, precision, seed=9):
     """One step in one segment and in as many as there are units against float64 (with the storage type's roundings), tensor by
-    tensor; the trainer's work by class."""
+    tensor; the trainer's work by class and by entry."""
     import torch
     from paper_2105_00619_amd.binding import SeqTrainer
     g = torch.Generator(device="cuda").manual_seed(seed)
@@ -597,6 +597,7 @@ def _against_float64(units, b, h, w, precision, seed=9):
     t.profile_enable()
     t.step(x, y, 0.0)
     work = t.profile_read()["classes"]
+    work["entries"] = t.profile_read_entries()
     t.close()
     return work
 
@@ -638,13 +639,20 @@ def test_backward_under_a_pool_reads_the_output_it_has(precision, block):
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b", [
     (128, 16, 16, 256), (256, 8, 8, 1024),  # exactly 256 tiles of 256 x 128 and of 256 x 256
-    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217)])
+    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217),
+    # row tiles that the grouping by XCD pads with blocks that end at once (127 of two channel blocks); three channel blocks, grouped and not
+    (512, 8, 8, 507), (384, 8, 8, 320), (384, 8, 8, 336),
+    (256, 15, 17, 254), (128, 4, 4, 8190), (256, 16, 16, 384), (128, 16, 16, 512)])  # several rounds of blocks; the last on narrow tiles
 def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
-    """3x3 layers on tiles of 256 pixels: one image, several, parts of one, a ragged last tile, two channel blocks; in 512 channels and
-    at 217 images fewer tiles than fill the chip (the kernel's other shape, the narrower tiles).  Two basic blocks: forward with sums, with the BatchNorm
-    in front folded in and without sums (replay), data gradients with the sums of the BatchNorm in front and with a masked addend."""
+    """3x3 layers on tiles of 256 pixels: one image, several, parts of one, a ragged last tile, two channel blocks, which are a full round
+    in 512 channels; at 217 images fewer tiles than fill the chip (the narrower tiles).  Two basic blocks: forward with sums, with the
+    BatchNorm in front folded in and without sums (replay), data gradients with the sums of the BatchNorm in front and with a masked
+    addend.  (test_kernel_choice.py: which of these take the wide tiles.)"""
+    from tests.test_kernel_choice import _forward_rows
     units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
-    _against_float64(units, b, h, w, precision)
+    work = _against_float64(units, b, h, w, precision)
+    sums = [e["bytes"] for e in work["entries"] if e["kind"] == "bn_stats" and e["unit"] > 0]
+    assert sums == [8 * channels * _forward_rows(precision, b, h, w, channels, channels)] * 4
 
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
@@ -656,6 +664,28 @@ def test_weight_gradient_of_64_channels_by_rows(precision, channels, h, w, b):
     """3x3 weight gradients of blocks of 64 output channels, with the BatchNorm in front folded into x and without."""
     units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
     _against_float64(units, b, h, w, precision)
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("cin,cout,h,w,wide,narrow", [
+    (128, 128, 16, 16, 256, 217), (128, 128, 16, 16, 512, 200), (64, 256, 16, 16, 250, 90), (256, 384, 16, 16, 84, 20), (128, 128, 64, 128, 8, 3),
+    (512, 512, 7, 7, 640, 99)])
+def test_wide_tiles_give_the_narrow_tiles_bits(precision, cin, cout, h, w, wide, narrow):
+    """The products of a depth in the same order and one rounding: images of a batch whose 3x3 layers take the wide tiles have the logits
+    that they have in a batch that is too small for them (plain layers, a skip connection added, a bias)."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(cin, cout), W.basic_block(cout, cout), W.conv(cout, cout, bn=False), W.gap_linear_ce(cout, 10)]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((wide, h, w, cin), generator=g, device="cuda")
+    p, out = W.make_params(units, h, w, perturb=True), []
+    for b in (wide, narrow):
+        t = SeqTrainer(units, k_segments=1, precision=precision, batch=b, height=h, width=w, channels=cin, num_classes=10)
+        t.set_params(p)
+        out.append(t.predict(x[:b].contiguous()).clone())
+        t.close()
+    assert bool(torch.isfinite(out[0]).all()) and float(out[0].std()) > 0
+    assert torch.equal(out[0][:narrow], out[1])
 
 
 @pytest.mark.parametrize("precision,b", [(W.BF16, 256), (W.FP16, 221)])
@@ -679,17 +709,20 @@ def test_wide_tiles_with_a_bias_and_other_borders(precision, b):
 
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
-@pytest.mark.parametrize("relu,blocks,h,w,b", [
-    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128),  # exactly 131 072 pixels: whole tiles
-    (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121),  # ragged; the last block's output is pooled: kept
-    (True, [(64, 256), (256, 64)], 512, 255, 1), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405),  # fewer; 130 815
-    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513)])  # no ReLU in front of the projection shortcut
-def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b):
+@pytest.mark.parametrize("relu,blocks,h,w,b,unwritten", [
+    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128, 3),  # exactly 131 072 pixels: whole tiles
+    (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121, 3),  # ragged; the last block's output is pooled: kept
+    (True, [(64, 256), (256, 64)], 512, 255, 1, 0), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405, 0),  # fewer; 130 815
+    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513, 1)])  # no ReLU in front of the projection shortcut: only the second block's
+def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b, unwritten):
     """Last layers and projection shortcuts of 64 -> 256 channels over 131 072 pixels or more: their outputs are never written, the
     statistics, the apply pass and the sums of the backward pass make them again.  Against plain float64 arithmetic; k segments and
     the three storage modes (different sources: an activation, or the z of its BatchNorm) change no bit."""
     units = [W.conv(8, 64, 1, relu=relu)] + [W.bottleneck(i, o) for i, o in blocks] + [W.gap_linear_ce(blocks[-1][1], 10)]
-    _against_float64(units, b, h, w, precision)
+    work = _against_float64(units, b, h, w, precision)
+    layers = [(8, 64)] + [p for i, o in blocks for p in [(i, o // 4), (o // 4, o)] + ([(i, o)] if i != o else [])]
+    whole = 2 * sum(b * h * w * (i + o) + i * o for i, o in layers)  # every 1x1 layer reads its input and writes its output
+    assert whole - work["conv1x1_fwd"]["bytes"] == unwritten * 2 * b * h * w * 256
     rng = np.random.default_rng(5)
     x, y = rng.standard_normal((b, h, w, 8)).astype(np.float32), rng.integers(0, 10, b).astype(np.int32)
     p = W.make_params(units, h, w, perturb=True)
@@ -699,6 +732,37 @@ def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b):
         for k in (1, 2, len(units)):
             r, _ = gpu_step(units, p, x, y, k=k, storage_mode=mode, **kw)
             assert r["loss"] == want["loss"] and np.array_equal(r["grads"], want["grads"]), (mode, k)
+
+
+def test_block_outputs_written_in_passes_that_keep_nothing():
+    """A network whose arena is smaller if the passes that keep nothing write the output that is made again elsewhere (a plan for
+    storage mode 1 in six segments): the same bits as in one segment and as with every output written."""
+    from paper_2105_00619_amd.binding import SeqTrainer
+    units = [W.conv(3, 64), W.conv(64, 64, 1, stride=2), W.conv(64, 512, 3, stride=2, relu=False), W.basic_block(512, 256),
+             W.bottleneck(256, 256), W.bottleneck(256, 256), W.gap_linear_ce(256, 10)]
+    b, h, w = 867, 50, 57
+    kw = dict(precision=W.FP16, batch=b, height=h, width=w, channels=3, num_classes=10, loss_scale_init=_scale(W.FP16))
+    t = SeqTrainer(units, k_segments=6, storage_mode=1, **kw)
+    t.set_params(W.make_params(units, h, w, perturb=True))
+    t.profile_enable()
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn((b, h, w, 3), generator=g, device="cuda")
+    y = torch.randint(0, 10, (b,), generator=g, device="cuda", dtype=torch.int32)
+    first = torch.empty(t.param_count, dtype=torch.float32, device="cuda")
+    r = t.step(x, y, 0.0, grads=first)
+    layer = 2 * (b * 13 * 15 * 64 + 64 * 256)  # without the output
+    third = [e for e in t.profile_read_entries() if e["unit"] == 4 and e["kind"] == "conv1x1_fwd"]
+    t.close()
+    assert [e["bytes"] > layer for e in third if e["phase"] == 0] == [True, True]  # written
+    assert [e["flops"] > 0 for e in third if e["phase"] == 2] == [True, False]  # not run in the replay
+    for k, mode in ((1, 0), (2, 1), (6, 2)):
+        t = SeqTrainer(units, k_segments=k, storage_mode=mode, **kw)
+        t.set_params(W.make_params(units, h, w, perturb=True))
+        grads = torch.empty(t.param_count, dtype=torch.float32, device="cuda")
+        again = t.step(x, y, 0.0, grads=grads)
+        t.close()
+        assert again["loss"] == r["loss"] and torch.equal(grads, first), (k, mode)
 
 
 def test_work_of_a_replay_without_block_outputs():

@@ -28,3 +28,41 @@ def test_grouping_blocks_by_xcd_adds_no_round():
                 assert -(-rows * blocks // 32) <= -(-tiles * blocks // 256), (tiles, blocks)
     assert grouped > 1000
     assert rows_per_xcd(84, 3) == 0 and rows_per_xcd(80, 3) == 10 and rows_per_xcd(127, 2) == 16
+
+
+class ConvGeom(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("N", "H", "W", "C", "K", "R", "S", "stride", "pad", "P", "Q")]
+
+
+def _conv3x3(n, h, w, cin, cout):
+    return C.byref(ConvGeom(n, h, w, cin, cout, 3, 3, 1, 1, h, w))
+
+
+def _forward_rows(dt, *layer):
+    """Rows of channel sums of a forward pass: row tiles of 256 pixels where it takes the wide tiles, of 128 and less elsewhere."""
+    return _function("_ZN4oseq25conv_mfma_fwd_stat_blocksEiRKNS_8ConvGeomEb", C.c_int, C.c_void_p, C.c_bool)(dt, _conv3x3(*layer), False)
+
+
+def _data_gradient_rows(dt, *layer):
+    return _function("_ZN4oseq21conv_dgrad_sum_blocksEiRKNS_8ConvGeomE", C.c_int, C.c_void_p)(dt, _conv3x3(*layer))
+
+
+@pytest.mark.parametrize("dt", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layer,rows", [
+    # the layers of test_wide_tiles_of_3x3_layers and of the bit comparison (test_gpu_parity.py); 218 images against 217
+    ((256, 16, 16, 128, 128), 256), ((1024, 8, 8, 256, 256), 256), ((254, 15, 17, 256, 256), 254), ((1279, 7, 7, 256, 256), 256),
+    ((8, 64, 128, 128, 128), 256), ((4091, 4, 4, 128, 128), 256), ((4096, 4, 4, 256, 256), 256), ((511, 8, 8, 512, 512), 128),
+    ((507, 8, 8, 512, 512), 127), ((320, 8, 8, 384, 384), 80), ((336, 8, 8, 384, 384), 84), ((8190, 4, 4, 128, 128), 512),
+    ((217, 16, 16, 128, 128), 434), ((218, 16, 16, 128, 128), 218),
+    # beyond one round of 256: not with little depth, unless the narrow tiles fit the map badly
+    ((512, 16, 16, 128, 128), 1024), ((509, 15, 17, 128, 128), 509), ((512, 16, 16, 32, 128), 1024), ((256, 16, 16, 32, 128), 256),
+    ((512, 16, 16, 32, 256), 1024), ((508, 16, 16, 64, 256), 508), ((450, 16, 16, 64, 256), 900), ((450, 16, 16, 128, 256), 450),
+    ((645, 7, 7, 128, 128), 323), ((1210, 7, 7, 128, 128), 242), ((2360, 7, 7, 128, 128), 472),
+    # 256 channels that tiles of 256 do not fit, in tiles of 128: up to three rounds, beyond that 93 % of the products
+    ((384, 16, 16, 256, 256), 384), ((550, 16, 16, 256, 256), 1100), ((600, 16, 16, 256, 256), 600), ((750, 16, 16, 384, 384), 750)])
+def test_wide_tiles_are_taken_where_they_are_faster(dt, layer, rows):
+    n, h, w, cin, cout = layer
+    assert _forward_rows(dt, *layer) == rows
+    # the data gradient goes by the same rule (0: too many rows to be worth it)
+    assert _data_gradient_rows(dt, n, h, w, cout, cin) in (rows, 0)
+    assert _forward_rows(W.FP32, *layer) != rows or rows > n * h * w // 200
