@@ -132,28 +132,21 @@ __device__ __forceinline__ void epi_store_rows_nt(const float* ep, int tid, int 
 // are rounded and stored, and the sums that the BatchNorm's backward pass begins with -- of dy and of dy * xhat, dy the stored value
 // where the ReLU let it through -- go to ss and qq, so that no kernel has to read the gradient for them.
 // bn: that BatchNorm's [4][C] statistics tensor, z its input, shaped as the output.
-// zv: the pieces of z as epi_bn_sums_load_nt requests them.
-template <int NT, class T, int BN, int HR, class RowOff>
-__device__ __forceinline__ void epi_bn_sums_load_nt(int tid, int n0, const T* __restrict__ z, RowOff rowoff,
-                                                    Vec<T, 8> (&zv)[HR * (BN / 8) / NT]) {
-  constexpr int GROUPS = BN / 8, PER_THREAD = HR * GROUPS / NT, RG = NT / GROUPS;
-#pragma unroll
-  for (int it = 0; it < PER_THREAD; ++it) {
-    const int64_t ro = rowoff(tid / GROUPS + it * RG);  // (rows that are not stored: the first)
-    zv[it] = *reinterpret_cast<const Vec<T, 8>*>(z + (ro >= 0 ? ro : 0) + n0 + (tid % GROUPS) * 8);
-  }
-}
 template <int NT, class T, int BN, int HR, class RowOff>
 __device__ __forceinline__ void epi_bn_sums_rows_nt(const float* ep, int tid, int n0, const float* __restrict__ bn, int C,
-                                                    const Vec<T, 8> (&zv)[HR * (BN / 8) / NT], T* __restrict__ out, int relu,
-                                                    RowOff rowoff, float (&ss)[8], float (&qq)[8]) {
+                                                    const T* __restrict__ z, T* __restrict__ out, int relu, RowOff rowoff,
+                                                    float (&ss)[8], float (&qq)[8]) {
   constexpr int EP_PITCH = BN + 4;
   constexpr int GROUPS = BN / 8, PER_THREAD = HR * GROUPS / NT, RG = NT / GROUPS;
   const int c8 = (tid % GROUPS) * 8, erow = tid / GROUPS;
   const int col = n0 + c8;
   int64_t ro[PER_THREAD];
+  Vec<T, 8> zv[PER_THREAD];
 #pragma unroll
-  for (int it = 0; it < PER_THREAD; ++it) ro[it] = rowoff(erow + it * RG);
+  for (int it = 0; it < PER_THREAD; ++it) {
+    ro[it] = rowoff(erow + it * RG);
+    zv[it] = *reinterpret_cast<const Vec<T, 8>*>(z + (ro[it] >= 0 ? ro[it] : 0) + col);  // (rows that are not stored: the first)
+  }
   float mean[8], rstd[8], scale[8], shift[8];
   load_f32<float, 8>(bn + col, mean);
   load_f32<float, 8>(bn + C + col, rstd);

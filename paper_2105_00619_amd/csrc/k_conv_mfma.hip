@@ -785,11 +785,8 @@ conv3x3_patch_kernel(const T* __restrict__ src, const T* __restrict__ wmat, cons
         epi_store_partial<BN, HR>(ep, tid, n0c, partial + (int64_t)bz * ((int64_t)a.N * a.dstH * a.dstW * a.Ng), rowoff);
       else if (EVAL)
         epi_eval_pass_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff);
-      else if constexpr (STAT == 2) {
-        Vec<T, 8> zv[HR * (BN / 8) / 256];
-        epi_bn_sums_load_nt<256, T, BN, HR>(tid, n0c, addend, rowoff, zv);
-        epi_bn_sums_rows_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, zv, out, a.relu, rowoff, ss, qq);
-      }
+      else if constexpr (STAT == 2)
+        epi_bn_sums_rows_nt<256, T, BN, HR>(ep, tid, n0c, bias, a.Ng, addend, out, a.relu, rowoff, ss, qq);
       else
         epi_store_pass<T, BN, HR, true, STAT == 0, STAT == 1>(ep, tid, n0c, bias, addend, a.amask, out, a.relu, rowoff, ss, qq);
     }

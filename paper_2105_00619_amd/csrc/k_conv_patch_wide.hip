@@ -36,25 +36,26 @@ template <> struct Op<f16_t> {
   __device__ static __forceinline__ void mma(const V& a, const V& b, v16f& c) { c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 
+constexpr int ROWS = 256;                 // pixels of a tile
 constexpr int CCE = 32, PITCH = CCE + 8;  // channels of a chunk, elements of a position in LDS
 constexpr int NSLOT = PATCH_WIDE_MAX_POS * 4 / 256;  // 16-byte pieces of a patch per thread
 constexpr int HR = 32;                    // rows of an epilogue pass in fp32
-// bytes in front of the buffers: out_off[256] (int64), apos[256] (int), 1 KB that pieces beyond the patch are written to
-constexpr int HEAD = 256 * 8 + 256 * 4 + 1024;
+// bytes in front of the buffers: out_off[ROWS] (int64), apos[ROWS] (int), 1 KB that pieces beyond the patch are written to
+constexpr int HEAD = ROWS * 8 + ROWS * 4 + 1024;
 
-constexpr int epi_bytes(int bn) { return std::max(256 * (bn + 8) * 2, 2 * HR * (bn + 4) * 4); }
+constexpr int epi_bytes(int bn) { return std::max(ROWS * (bn + 8) * 2, 2 * HR * (bn + 4) * 4); }
 
 // EVAL, STAT and what bias, addend and a.relu are then: as conv3x3_patch_kernel; ADD: an addend (STAT 0)
-template <class T, int MI, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
+template <class T, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 conv3x3_wide_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const float* __restrict__ bias,
                     const T* __restrict__ addend, T* __restrict__ out, float* __restrict__ stat_partial, PatchWideArgs a) {
   typedef typename Op<T>::V V;
-  constexpr int ROWS = 64 * MI, BN = 64 * NI;
+  constexpr int MI = ROWS / 64, BN = 64 * NI;
   constexpr int NW = BN / 64;  // weight pieces per thread and tap
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   int64_t* out_off = reinterpret_cast<int64_t*>(smem_raw);
-  int* apos = reinterpret_cast<int*>(out_off + 256);
+  int* apos = reinterpret_cast<int*>(out_off + ROWS);
   T* patch = reinterpret_cast<T*>(smem_raw + HEAD);
   const int PBUF = a.patch_elems;
   T* Bs = patch + 2 * PBUF;
@@ -85,7 +86,7 @@ conv3x3_wide_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const
   {
     int64_t off = -1;
     int ap = 0;
-    if (tid < ROWS && tid < a.TP) {
+    if (tid < a.TP) {
       const int ti = a.div_tile.div(tid), rr = tid - ti * (a.TR * a.TC);
       const int tr = a.div_tcol.div(rr), tc = rr - tr * a.TC;
       const int n = n_first + ti, p = ri * a.TR + tr, q = ci * a.TC + tc;
@@ -363,19 +364,19 @@ conv3x3_wide_kernel(const T* __restrict__ src, const T* __restrict__ wmat, const
                          stat_partial + ((int64_t)bx * 2 + 1) * a.Ng + n0c);
 }
 
-template <class T, int MI, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
+template <class T, int NI, int STAT, bool FOLD, bool EVAL, bool ADD>
 void launch_one(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out, float* stat_partial,
                 dim3 grid, size_t sm, const PatchWideArgs& a) {
   static bool done = false;
   if (!done) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_wide_kernel<T, MI, NI, STAT, FOLD, EVAL, ADD>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)conv3x3_wide_kernel<T, NI, STAT, FOLD, EVAL, ADD>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     done = true;
   }
-  OSEQ_LAUNCH((conv3x3_wide_kernel<T, MI, NI, STAT, FOLD, EVAL, ADD>), grid, dim3(256), sm, st, (const T*)src, (const T*)wmat, bias,
+  OSEQ_LAUNCH((conv3x3_wide_kernel<T, NI, STAT, FOLD, EVAL, ADD>), grid, dim3(256), sm, st, (const T*)src, (const T*)wmat, bias,
               (const T*)addend, (T*)out, stat_partial, a);
 }
 
-template <class T, int MI, int NI>
+template <class T, int NI>
 void launch_shape(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out, float* stat_partial,
                   const PatchArgs& shape) {
   PatchWideArgs a;
@@ -390,7 +391,7 @@ void launch_shape(hipStream_t st, const void* src, const void* wmat, const float
   a.xcd_group = per_xcd > 0 ? 2 : 0;
   if (per_xcd > 0) grid.x = per_xcd * 8;
   const size_t sm = conv_patch_wide_lds(64 * NI, a.patch_elems);
-#define LAUNCH(STAT, FOLD, EVAL, ADD) launch_one<T, MI, NI, STAT, FOLD, EVAL, ADD>(st, src, wmat, bias, addend, out, stat_partial, grid, sm, a)
+#define LAUNCH(STAT, FOLD, EVAL, ADD) launch_one<T, NI, STAT, FOLD, EVAL, ADD>(st, src, wmat, bias, addend, out, stat_partial, grid, sm, a)
   if (a.eval && addend) LAUNCH(0, false, true, true);
   else if (a.eval) LAUNCH(0, false, true, false);
   else if (a.bn_sums) LAUNCH(2, false, false, false);
@@ -405,8 +406,8 @@ void launch_shape(hipStream_t st, const void* src, const void* wmat, const float
 template <class T>
 void launch_type(hipStream_t st, const void* src, const void* wmat, const float* bias, const void* addend, void* out, float* stat_partial,
                  int bn, const PatchArgs& a) {
-  if (bn == 128) launch_shape<T, 4, 2>(st, src, wmat, bias, addend, out, stat_partial, a);
-  else launch_shape<T, 4, 4>(st, src, wmat, bias, addend, out, stat_partial, a);
+  if (bn == 128) launch_shape<T, 2>(st, src, wmat, bias, addend, out, stat_partial, a);
+  else launch_shape<T, 4>(st, src, wmat, bias, addend, out, stat_partial, a);
 }
 
 }  // namespace
