@@ -34,17 +34,17 @@ COPY_REPS = 4
 
 # kernel-name fragments of the groups bench.py reports
 GROUP_KERNELS = {
-    "conv_fwd+conv_dgrad": ("conv3x3_patch_kernel", "conv_ws3x3_kernel", "conv_igemm_kernel", "splitk_epilogue_kernel",
+    "conv_fwd+conv_dgrad": ("conv3x3_patch_kernel", "conv3x3_wide_kernel", "conv_ws3x3_kernel", "conv_igemm_kernel", "splitk_epilogue_kernel",
                             "conv_fwd_smallc_kernel", "conv_stem_fwd_kernel", "conv_fwd_direct_kernel", "conv_dgrad_direct_kernel"),
-    # (conv1x1_bwd_kernel: data and weight gradient of a wide 1x1 layer in one pass)
+    # (conv1x1_bwd_kernel: data and weight gradient of a wide 1x1 layer in one pass; again_...: its output made again where it is needed)
     "conv1x1_fwd+conv1x1_dgrad": ("conv1x1_kernel", "conv1x1_large_kernel", "conv1x1_ws_kernel", "conv1x1_rows_kernel",
-                                  "conv1x1_bwd_kernel"),
+                                  "conv1x1_bwd_kernel", "again_stats_kernel"),
     # one kernel family serves the 1x1 and the other weight gradients: counted together
     "conv_wgrad": ("conv_wgrad3x3_kernel", "conv_wgrad_kernel", "conv_wgrad_smallc_kernel", "conv_stem_wgrad_kernel",
                    "wgrad_reduce_kernel", "partial_reduce_kernel", "conv_wgrad_direct_kernel"),
-    "bn_apply": ("bn_apply_kernel", "bn_apply_pool_kernel"),
+    "bn_apply": ("bn_apply_kernel", "bn_apply_pool_kernel", "again_apply_kernel"),
     # the reduction pass (colreduce_kernel in its BatchNorm-backward modes, template arguments 1, 3 and 4) and the apply pass
-    "bn_bwd": ("bn_bwd_apply_kernel", "bn_bwd_finalize_kernel", "bn_bwd_pool")
+    "bn_bwd": ("bn_bwd_apply_kernel", "bn_bwd_finalize_kernel", "bn_bwd_pool", "again_sums_kernel")
               + tuple("ELi%dELb%dELb%dEEEvNS_7RedArgsE" % (m, gv, dual) for m in (1, 3, 4) for gv in (0, 1) for dual in (0, 1))
               + tuple(", %d, %s, %s>(oseq::RedArgs)" % (m, gv, dual) for m in (1, 3, 4) for gv in ("false", "true")
                       for dual in ("false", "true")),
