@@ -416,8 +416,9 @@ void stats_f(hipStream_t st, const void* x, const float* fold, const void* w, fl
 
 }  // namespace
 
-// Where the weights-stationary forward kernel is taken (its partition of the sums is this file's) and the backward kernel that reads no
-// z: four tiles of 128 pixels a block, 130 945 pixels.
+// Where the weights-stationary forward kernel is taken and the backward kernel that reads no z: four tiles of 128 pixels a block, 130 945
+// pixels.  Below it the forward kernel's sums are another partition's, and the bits of a step would depend on whether z is kept.  The step of
+// c64 n256 n256 n256 in bf16 at 131 072 pixels 1333 us with z in memory, 1239 so.
 bool conv_again_ok(int dt, const ConvGeom& g) {
   const int64_t M = (int64_t)g.N * g.P * g.Q;
   return conv_bwd1x1_ok(dt, g) && g.C == BC && g.K == BK && conv_pointwise_fwd_ok(dt, g) && conv_pointwise_stat_blocks(g) == ST_BLOCKS &&

@@ -13,7 +13,7 @@
 //   block = 8 wavefronts, two per SIMD (144 accumulator registers each), so that one's LDS reads and address arithmetic run
 //   under the other's MFMAs: wavefront (wm, wn) owns k rows [wm*32*MI, +32*MI) and c columns [wn*32, +32) of every tap: MI x 9
 //   accumulator tiles of 32x32.  128 output channels (the plan says where): 4 x 2 of them (256 -> 256 channels at 8 x 8, batch
-//   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 304 us with 4 x 2; the one-tap-per-block kernel: 479 us).  64: 2 x 2 in
+//   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 304 us with 4 x 2, now 287; the one-tap-per-block kernel: 479 us).  64: 2 x 2 in
 //   two groups that share a sub-tile's pixels, their sums added at the end (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm
 //   folded in: 556 us with four wavefronts, 431 with eight).  fp32: 2 x 2, one per SIMD and block, two blocks per CU.
 //   MFMA 32x32x16, operands come from the transposing LDS read (ds_read_b64_tr_b16), whose per-lane row addresses make the
@@ -837,6 +837,11 @@ static constexpr int g_wgrad3x3 = 1;  // compile-time switch
 bool conv_wgrad3x3_ok(int dt, const ConvGeom& g) {
   W9Plan pl;
   return g_wgrad3x3 && w9_plan(dt, g, 0, 0, pl);
+}
+
+bool conv_wgrad3x3_by_rows(int dt, const ConvGeom& g) {
+  W9Plan pl;
+  return w9_plan(dt, g, 0, 0, pl) && pl.a.rows;
 }
 
 int conv_wgrad3x3_splits(int dt, const ConvGeom& g, int64_t room) {

@@ -66,3 +66,16 @@ def test_wide_tiles_are_taken_where_they_are_faster(dt, layer, rows):
     # the data gradient goes by the same rule (0: too many rows to be worth it)
     assert _data_gradient_rows(dt, n, h, w, cout, cin) in (rows, 0)
     assert _forward_rows(W.FP32, *layer) != rows or rows > n * h * w // 200
+
+
+@pytest.mark.parametrize("dt", [W.BF16, W.FP16])
+@pytest.mark.parametrize("channels,h,w,b,rows", [
+    # the layers of test_weight_gradient_of_64_channels_by_rows (test_gpu_parity.py), and wider blocks
+    (64, 8, 8, 257, True), (64, 24, 24, 41, True), (64, 9, 40, 61, True), (64, 32, 32, 17, True), (64, 7, 7, 401, True),
+    (64, 14, 13, 120, True), (64, 2, 64, 150, True), (64, 1, 100, 301, False), (64, 4, 4, 1100, False), (64, 5, 5, 700, False),
+    (128, 16, 16, 70, True), (192, 16, 16, 70, True), (256, 8, 8, 1024, True), (256, 14, 14, 512, False), (256, 7, 7, 1279, False)])
+def test_weight_gradients_by_rows(dt, channels, h, w, b, rows):
+    by_rows = _function("_ZN4oseq21conv_wgrad3x3_by_rowsEiRKNS_8ConvGeomE", C.c_int, C.c_void_p)
+    by_rows.restype = C.c_bool
+    assert by_rows(dt, _conv3x3(b, h, w, channels, channels)) == rows
+    assert not by_rows(W.FP32, _conv3x3(b, h, w, channels, channels))
