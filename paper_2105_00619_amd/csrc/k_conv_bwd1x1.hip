@@ -9,11 +9,11 @@
 // Apart, these are three kernels: the first reads dA and z and writes dz, the others read dz again, one of them x -- at 4.2 M
 // pixels in bf16 1176 + 516 + 520 us for 6.6 + 2.7 + 2.7 GB.  Here a pixel's dz exists in LDS only, and its z too: that is the
 // layer's own output, made again from the x that is here for the weight gradient (a third of the products, in the forward kernel's
-// order, hence its bits).  Reading z (5.4 GB) was bound by HBM; without it (3.3 GB) the LDS (100 KB a tile) and the vector
-// instructions around it take as long as memory.  us, z read -> made again, also where it is in memory anyway, without and with a
-// BatchNorm in front: 4.2 M pixels 1134 -> 820, 1087 -> 905; 131 072 43 -> 35, 42 -> 38.5; 65 536 26 -> 23.5, 26.8 -> 25.9.
-// With dA per image z is the one large tensor to read, and always there: read, at the same three sizes, 811, 35.3 and 24.4
-// (made again 950, 38.4 and 26.7).
+// order, hence its bits).  Reading z (5.4 GB) was bound by HBM; without it (3.4 GB counted) the LDS (100 KB a tile; busy half of
+// the cycles, a third of those conflicts) and the vector instructions around it take as long as memory.  us, z read -> made again,
+// also where it is in memory anyway, without and with a BatchNorm in front: 4.2 M pixels 1134 -> 820, 1087 -> 905; 131 072
+// 43 -> 35, 42 -> 38.5; 65 536 26 -> 23.5, 26.8 -> 25.9.  With dA per image z is the one large tensor to read, and always there:
+// read, at the same three sizes, 811, 35.3 and 24.4 (made again 950, 38.4 and 26.7).
 //
 // A block of 512 threads (8 wavefronts, one block per CU: 256 blocks) walks a range of tiles of 64 pixels.  Per tile, two barriers:
 // dz of the tile from z (LDS) and the pieces of dA and mask, requested a tile ahead, and the next tile's x into LDS; then every
