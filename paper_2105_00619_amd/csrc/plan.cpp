@@ -847,9 +847,12 @@ bool build_schedule(Plan& p, uint64_t enough) {
   if (!p.separate && p.arena_bytes > std::max(enough, most_alive)) {
     // merged passes hold no more at any step, but may be placed worse: then a longer search, so that what a budget allowed without
     // them it allows with them (of 40 000 random networks 33 are still larger, by up to 2 % or some KB)
-    Plan q = p;
-    q.separate = true;
-    if (build_schedule(q) && q.arena_bytes < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, q.arena_bytes), true);
+    if (p.separate_arena == 0) {
+      Plan q = p;
+      q.separate = true;
+      p.separate_arena = build_schedule(q) ? q.arena_bytes : ~0ull;
+    }
+    if (p.separate_arena < p.arena_bytes) p.arena_bytes = place(spans, n, std::max(enough, p.separate_arena), true);
   }
   for (size_t i = 0; i < spans.size(); ++i) p.insts[span_inst[i]].offset = spans[i].offset;
   if (p.arena_bytes > std::max(enough, alive_with_z_written(p))) {
@@ -865,6 +868,7 @@ bool build_schedule(Plan& p, uint64_t enough) {
       p.z_written = false;
     }
   }
+  p.separate_arena = 0;
   return true;
 }
 

@@ -154,6 +154,7 @@ struct Plan {
                                 // block output's (choose_sums); empty: none
   bool z_written = false;       // FOp::again: passes that keep nothing write z nevertheless (build_schedule compares)
   bool separate = false;        // schedule every pass of the backward as an operation of its own (what choose_sums measures by)
+  uint64_t separate_arena = 0;  // while build_schedule runs: the arena of such a schedule of this partition, 0 unknown
   // partition
   std::vector<int> seg_begin;  // k+1 entries, unit indices
   // schedule
