@@ -36,9 +36,9 @@ CONV_CLASSES = MFMA_CLASSES + ("conv1x1_fwd", "conv1x1_dgrad", "conv1x1_wgrad")
 GROUPS = {"conv_fwd": "conv_fwd+conv_dgrad", "conv_dgrad": "conv_fwd+conv_dgrad",
           "conv1x1_fwd": "conv1x1_fwd+conv1x1_dgrad", "conv1x1_dgrad": "conv1x1_fwd+conv1x1_dgrad"}
 GROUP_KERNELS = {
-    "conv_fwd+conv_dgrad": "conv3x3_patch_kernel, conv_ws3x3_kernel, conv_igemm_kernel (+ splitk_epilogue_kernel), conv_stem_fwd_kernel / conv_fwd_smallc_kernel",
+    "conv_fwd+conv_dgrad": "conv3x3_wide_kernel, conv3x3_patch_kernel, conv_ws3x3_kernel, conv_igemm_kernel (+ splitk_epilogue_kernel), conv_stem_fwd_kernel / conv_fwd_smallc_kernel",
     "conv_wgrad": "conv_wgrad3x3_kernel, conv_wgrad_kernel, conv_stem_wgrad_kernel / conv_wgrad_smallc_kernel (+ wgrad_reduce_kernel, partial_reduce_kernel)",
-    "conv1x1_fwd+conv1x1_dgrad": "conv1x1_ws_kernel, conv1x1_bwd_kernel, conv1x1_rows_kernel, conv1x1_large_kernel, conv1x1_kernel, conv_igemm_kernel (strided or few pixels)",
+    "conv1x1_fwd+conv1x1_dgrad": "conv1x1_ws_kernel, again_stats_kernel, conv1x1_bwd_kernel, conv1x1_rows_kernel, conv1x1_large_kernel, conv1x1_kernel, conv_igemm_kernel (strided or few pixels)",
     "conv1x1_wgrad": "conv_wgrad_kernel (+ wgrad_reduce_kernel)",
 }
 DTYPE_NAME = {0: "f32", 1: "bf16", 2: "f16"}
