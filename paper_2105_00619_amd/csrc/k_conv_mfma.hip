@@ -936,6 +936,13 @@ static int patch_row_pitch(const PatchArgs& a, int subt, int pos_bytes, int most
   return rows * rp <= (int64_t)subt * most * pos_bytes ? rp : a.SC * pos_bytes;
 }
 
+// Blocks of the patch kernel whose LDS (given out in units of 1280 bytes) a CU holds.
+static int patch_blocks_per_cu(const PatchArgs& a, int row_pitch, int subt, int bn, int pos_bytes) {
+  const int64_t patch = ((int64_t)subt * a.TI * a.SR * row_pitch + 15) / 16 * 16;
+  const int64_t bytes = 2 * patch + (int64_t)3 * bn * pos_bytes + subt * PATCH_MAX_POS * 8 + 256 * 8 + 256 * 4;
+  return (int)(160 * 1024 / ((bytes + 1279) / 1280 * 1280));
+}
+
 // Block shapes of the patch kernel, largest first: {MI, SUBT, widest BN}.  The first one that gives the chip
 // `g_patch_fill` blocks is taken, else the one with the most blocks if that reaches `g_patch_min_blocks`
 // (shape-only rule, so the choice is the same on every run).
@@ -1040,7 +1047,14 @@ static bool patch_pick(int dt, bool split32, PatchUse use, int N, int dstH, int 
     if (splits < 1) splits = 1;
   }
   geo.split32 = split32;
-  geo.row_pitch = patch_row_pitch(geo, shape.subt, split32 ? Frag<Split32>::PITCH * 2 : Frag<bf16_t>::PITCH * 2);
+  const int pos_bytes = split32 ? Frag<Split32>::PITCH * 2 : Frag<bf16_t>::PITCH * 2;
+  geo.row_pitch = patch_row_pitch(geo, shape.subt, pos_bytes);
+  // (not padded where that takes a block's room that the registers leave: 64 -> 64 channels over 70 000 pixels of 50 x 50 maps in fp16,
+  // two blocks a CU with padded rows, three without, two layers forward 41 -> 33 us, data gradients 42 -> 33.5)
+  const int held = split32 ? shape.mi == 1 ? 3 : 2 : shape.bn == 64 ? 3 : 2;
+  if (patch_blocks_per_cu(geo, geo.row_pitch, shape.subt, shape.bn, pos_bytes) <
+      std::min(held, patch_blocks_per_cu(geo, geo.SC * pos_bytes, shape.subt, shape.bn, pos_bytes)))
+    geo.row_pitch = geo.SC * pos_bytes;
   geo.chunks_per_split = (nchunks + splits - 1) / splits;
   shape.splits = (nchunks + geo.chunks_per_split - 1) / geo.chunks_per_split;  // no empty ranges
   return true;
@@ -1251,6 +1265,14 @@ int conv_mfma_dgrad_splits(int dt, const ConvGeom& g) {
   if (patch_pick(dt, dt == DT_F32, PATCH_DGRAD, g.N, g.H, g.W, g.K, g.C, g.R, g.S, g.stride, v, pa)) return v.splits;
   if (dgrad_by_classes(g)) return 1;
   return igemm_splits(dt, (int64_t)g.N * g.H * g.W, g.C, g.R * g.S * g.K);
+}
+
+int conv_patch_blocks_per_cu(int dt, const ConvGeom& g, bool unpadded) {
+  PatchShape v; PatchArgs a{};
+  const bool split32 = fwd_split32(dt, g);
+  if (!patch_pick(dt, split32, PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, a) || v.wide) return 0;
+  const int pos_bytes = (split32 ? Frag<Split32>::PITCH : Frag<bf16_t>::PITCH) * 2;
+  return patch_blocks_per_cu(a, unpadded ? a.SC * pos_bytes : a.row_pitch, v.subt, v.bn, pos_bytes);
 }
 
 bool conv_mfma_fwd_ok(int dt, const ConvGeom& g) {

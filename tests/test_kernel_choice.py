@@ -79,3 +79,20 @@ def test_weight_gradients_by_rows(dt, channels, h, w, b, rows):
     by_rows.restype = C.c_bool
     assert by_rows(dt, _conv3x3(b, h, w, channels, channels)) == rows
     assert not by_rows(W.FP32, _conv3x3(b, h, w, channels, channels))
+
+
+def test_padded_patch_rows_leave_a_cu_its_blocks():
+    """Rows of a staged patch are padded against bank conflicts only where that leaves a CU the blocks that its registers hold: three of
+    64 channels, two of 128."""
+    blocks = _function("_ZN4oseq24conv_patch_blocks_per_cuEiRKNS_8ConvGeomEb", C.c_int, C.c_void_p, C.c_bool)
+    seen = 0
+    for h in range(5, 130, 3):
+        for w in list(range(4, 66)) + [80, 96, 100, 112, 128]:
+            for c, held in ((64, 3), (128, 2)):
+                for dt in (W.BF16, W.FP32):
+                    layer = _conv3x3(max(1, 70000 // (h * w)), h, w, c, c)
+                    n = blocks(dt, layer, False)
+                    seen += n > 0
+                    assert n >= min(held, blocks(dt, layer, True)), (dt, c, h, w)
+    assert seen > 10000
+    assert blocks(W.FP16, _conv3x3(28, 50, 50, 64, 64), False) == 3
