@@ -15,7 +15,7 @@
 //   accumulator tiles of 32x32.  128 output channels (the plan says where): 4 x 2 of them (256 -> 256 channels at 8 x 8, batch
 //   4096, bf16: 481 us with 2 x 2 wavefronts of MI = 2, 304 us with 4 x 2, now 287; the one-tap-per-block kernel: 479 us).  64: 2 x 2 in
 //   two groups that share a sub-tile's pixels, their sums added at the end (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm
-//   folded in: 556 us with four wavefronts, 431 with eight).  fp32: 2 x 2, one per SIMD and block, two blocks per CU.
+//   folded in: 556 us with four wavefronts, 431 with eight, 411 with the next sub-tile staged at different times).  fp32: 2 x 2, one per SIMD and block, two blocks per CU.
 //   MFMA 32x32x16, operands come from the transposing LDS read (ds_read_b64_tr_b16), whose per-lane row addresses make the
 //   tap shift a plain change of address.  fp32: three bf16 planes per operand, six MFMAs (split32.h).
 //   16-bit: two LDS stages; the next sub-tile's pieces are under way in registers during the MFMAs of the current one and go to the
@@ -45,8 +45,7 @@ struct W9Args {
   int TI, TR, TC, SR, SC, NPOS, TP;  // sub-tile: images, rows, columns; staged rows / columns; positions; pixels
   int tiles_r, tiles_c, NT;          // sub-tiles per image rows / columns; in total
   int tiles_per_split;
-  int rows;                          // 1: the ROWS instantiation; TC is a multiple of 8
-  FastDiv div_runs, div_tiles_r, div_tiles_c;  // ROWS: runs of eight pixels per row; sub-tiles
+  int swap;                          // 1: the SWAP instantiation; TC is a multiple of 8
   int xcd_group, splits;  // xcd_group: the tiles of a pixel range share an XCD (see the kernel); splits: pixel ranges
   const float* fold;  // FOLD: x is the z of a BatchNorm + ReLU, this its [4][C] statistics tensor; the staged pieces of x
                       // become the activation (scale, shift, ReLU, one rounding); positions outside the image stay zero
@@ -60,13 +59,13 @@ template <> struct W9Cfg<f16_t> { static constexpr int CAP = 128, MAXPOS = 256; 
 // WGM wavefront rows of 32 * MI output channels each (2 wavefront columns of 32 input channels): 64 * WGM threads
 // PG: groups of wavefronts that share a block's pixels (see the kernel)
 constexpr int w9_groups(int bytes, int wgm) { return bytes == 2 && wgm == 2 ? 2 : 1; }
-template <class T, int MI, int WGM, bool ROWS = false> struct W9Lds {
+template <class T, int MI, int WGM, bool SWAP = false> struct W9Lds {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr int CAP = W9Cfg<T>::CAP, MAXPOS = W9Cfg<T>::MAXPOS;
   static constexpr int BMK = 32 * MI * WGM;
-  // elements per staged x position and dz pixel: 32 bytes of padding; ROWS: none, the 64-byte parts are exchanged instead (swz)
-  static constexpr int PX = ROWS ? 64 : 80;
-  static constexpr int PK = ROWS ? BMK : BMK + 16;
+  // elements per staged x position and dz pixel: 32 bytes of padding; SWAP: none, the 64-byte parts are exchanged instead (swz)
+  static constexpr int PX = SWAP ? 64 : 80;
+  static constexpr int PK = SWAP ? BMK : BMK + 16;
   static constexpr int PL = F32 ? 3 : 1;            // planes
   // elements of a plane of x (fp32: of the layer's positions, not of the most there can be), of dz; of a stage
   static constexpr int xs(int npos) { return (F32 ? npos : MAXPOS) * PX; }
@@ -93,20 +92,17 @@ template <> struct V8<float> { typedef v8bf type; };
 // column, checks each against the image and multiplies them back together with quarter-rate 32- and 64-bit multiplies,
 // per chunk and sub-tile, in a kernel whose instruction stream is what bounds it.
 //
-// ROWS: columns are counted in runs of eight (TC, in blocks of 64 channels padded with pixels whose dz is zero), so that the four
-// pixels of a transposing read are neighbours in a row.  They fall on the same banks unless padded; here the 64-byte parts of a
-// pixel are exchanged by its number instead (swz), which any four neighbours keep apart, and a staged row has a multiple of four
-// positions, so that this order is that of the rows above and below.
-//   Blocks of 64 channels: a wavefront takes two runs at a time (one per half of its lanes) down their rows: a row of x is read at
-// its three shifts and paired with the three rows of dz that meet it in the filter's three rows, two of which are in registers
-// from the rows before: 8 reads per nine MFMAs, where a tap at a time takes 20 and LDS is the bound (57 % of its cycles reads,
-// 25 % bank conflicts).  What is left is instructions, so a piece's offset from its sub-tile's first pixel is kept.
-//   Blocks of 128 channels: a tap at a time (by rows 350 us for the 304 below: spilled); without conflicts and with one address per two
-// reads 304 -> 287 us for 256 -> 256 channels over 262 144 pixels in bf16, 40.4 -> 37.3 for 128 -> 128 over 65 536.
-template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false, bool ROWS = false>
+// SWAP (blocks of 128 channels, TC a multiple of eight): the four pixels of a transposing read are neighbours in a row.  They fall on the
+// same banks unless padded; here the 64-byte parts of a pixel are exchanged by its number instead (swz), which any four neighbours keep
+// apart, and a staged row has a multiple of four positions, so that this order is that of the rows above and below.  Without conflicts and
+// with one address per two reads 304 -> 287 us for 256 -> 256 channels over 262 144 pixels in bf16, 40.4 -> 37.3 for 128 -> 128 over
+// 65 536.  (Going down a sub-tile's rows, a row of x at its three shifts for three rows of dz, 8 reads per nine MFMAs for 20: 350 us, spilled.
+// In blocks of 64 channels nothing spills, but a tap at a time is as fast or faster on every map -- over 330 000 pixels, 64 -> 64, 92 us for 92 at
+// 32 x 32, 95 for 106 at 24 x 24, 93 for 133 at 41 x 41 -- since what bounds them is the instructions around the staging.)
+template <class T, int MI, int WGM, bool FOLD = false, bool WHOLE = false, bool SWAP = false>
 __global__ void __launch_bounds__(128 * WGM * w9_groups(sizeof(T), WGM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* __restrict__ out, W9Args a) {
-  typedef W9Lds<T, MI, WGM, ROWS> L;
+  typedef W9Lds<T, MI, WGM, SWAP> L;
   constexpr bool F32 = L::F32;
   constexpr int PG = w9_groups(sizeof(T), WGM);
   constexpr int NTH = 128 * WGM * PG;                     // threads
@@ -187,51 +183,10 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     dinfo[sl] = info;
   }
 
-  // ROWS: byte offsets of the pieces from the sub-tile's first position of x (row -pad, column -pad) and first pixel of dz
-  int xoff[ROWS && PG == 2 ? XSLOTS : 1], doff[ROWS && PG == 2 ? DSLOTS : 1];
-  if constexpr (ROWS && PG == 2) {
-#pragma unroll
-    for (int sl = 0; sl < XSLOTS; ++sl) {
-      const int info = xinfo[sl];
-      xoff[sl] = (((info >> 20) * H + ((info >> 10) & 1023)) * W + (info & 1023)) * C * 2 + tid % XCP * 16;
-    }
-#pragma unroll
-    for (int sl = 0; sl < DSLOTS; ++sl) {
-      const int info = dinfo[sl];
-      doff[sl] = (((info >> 20) * P + ((info >> 10) & 1023)) * Q + (info & 1023)) * K * 2 + tid % DCP * 16;
-    }
-  }
-
   // Loads are unconditional (clamped to the tensor start when outside) and zeroed when written to LDS.
   Chunk xr[XSLOTS], dr[DSLOTS];
   unsigned xok = 0u, dok = 0u;
   auto gload = [&](int tile) {
-    if constexpr (ROWS && PG == 2) {
-      const int t2 = (int)a.div_tiles_c.div((uint32_t)tile), ci = tile - t2 * a.tiles_c;
-      const int ii = (int)a.div_tiles_r.div((uint32_t)t2), ri = t2 - ii * a.tiles_r;
-      const int nb = ii * TI, yb = ri * TR, xb = ci * TC, images = N - nb;
-      const char* xt = reinterpret_cast<const char*>(x + (int64_t)nb * H * W * C + c0);
-      const char* dt = reinterpret_cast<const char*>(dz + (int64_t)nb * P * Q * K + k0);
-      const int xo = ((yb - pad) * W + xb - pad) * C * 2, dof = (yb * Q + xb) * K * 2;
-      unsigned xm = 0u, dm = 0u;
-#pragma unroll
-      for (int sl = 0; sl < XSLOTS; ++sl) {
-        const int info = xinfo[sl];
-        const bool ok = (info >> 20) < images && (unsigned)(((info >> 10) & 1023) + yb - pad) < (unsigned)H &&
-                        (unsigned)((info & 1023) + xb - pad) < (unsigned)W && info >= 0;
-        xr[sl] = *reinterpret_cast<const Chunk*>(xt + (uint32_t)(ok ? xoff[sl] + xo : 0));
-        xm |= ok ? (1u << sl) : 0u;
-      }
-#pragma unroll
-      for (int sl = 0; sl < DSLOTS; ++sl) {
-        const int info = dinfo[sl];
-        const bool ok = (info >> 20) < images && (int)((info >> 10) & 1023) < P - yb && (int)(info & 1023) < Q - xb && info >= 0;
-        dr[sl] = *reinterpret_cast<const Chunk*>(dt + (uint32_t)(ok ? doff[sl] + dof : 0));
-        dm |= ok ? (1u << sl) : 0u;
-      }
-      xok = xm; dok = dm;
-      return;
-    }
     if constexpr (WHOLE) {
       const int nb = tile * TI;
       const uint32_t xbase = (uint32_t)nb * (uint32_t)(H * W), dbase = (uint32_t)nb * (uint32_t)(P * Q);
@@ -320,14 +275,15 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     load_f32<float, EV>(a.fold + 2 * C + c0 + (tid % XCP) * EV, fsc);
     load_f32<float, EV>(a.fold + 3 * C + c0 + (tid % XCP) * EV, fsh);
   }
-  // ROWS: where channel c of a position lies within it
+  // SWAP: where channel c of a position (of x, of dz) lies within it
   auto swz = [](int pos, int c) { return c ^ (((pos >> 1) & 1) << 5); };
-  auto swz_d = [](int m, int c) { return c ^ (BMK == 128 ? (m & 3) << 5 : ((m >> 1) & 1) << 5); };
-  const int xput = ROWS ? tid / XCP * PX + swz(tid / XCP, tid % XCP * EV) : 0, dput = ROWS ? tid / DCP * PK + swz_d(tid / DCP, tid % DCP * EV) : 0;
+  auto swz_d = [](int m, int c) { return c ^ ((m & 3) << 5); };
+  const int xput = SWAP ? tid / XCP * PX + swz(tid / XCP, tid % XCP * EV) : 0, dput = SWAP ? tid / DCP * PK + swz_d(tid / DCP, tid % DCP * EV) : 0;
   auto sstore = [&](int stage) {
     E* xs = lds + stage * STAGE;
     E* ds = xs + L::PL * XS;
-    if constexpr (ROWS) {  // (positions 4 n apart keep their parts in the same order)
+    if constexpr (SWAP) {  // (positions 4 n apart keep their parts in the same order)
+      static_assert(BMK == 128, "the order of dz is that of four parts");
       static_assert(NTH / XCP % 4 == 0 && NTH / DCP % 4 == 0 && MAXPOS * XCP % NTH == 0, "a slot's pieces are whole positions");
 #pragma unroll
       for (int sl = 0; sl < XSLOTS; ++sl) {
@@ -457,7 +413,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
             for (int i = 0; i < MI; ++i) acc[i][tap] = mfma16(fa[i][QA[q]], fb[QB[q]], acc[i][tap]);
         }
       }
-    } else if constexpr (ROWS) {  // blocks of 128 channels: a tap at a time, from the same places
+    } else if constexpr (SWAP) {
 #pragma unroll 2
       for (int ss = 0; ss < nss; ++ss) {
         const int m = ss * 16 + hg * 8 + (r16 >> 2), pos = apos[m];
@@ -490,66 +446,6 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
     }
   };
 
-  auto compute_rows = [&](int stage) {
-    if constexpr (ROWS && PG == 2) {
-      static_assert(MI == 1 && BMK == 64, "64 channels either way");
-      typedef typename V8<T>::type V;
-      const T* xs = lds + stage * STAGE;
-      const T* ds = xs + XS;
-      const int r16 = l32 & 15, px = r16 >> 2, ch = (l32 & 16) + 4 * (r16 & 3);
-      const int per_row = TC >> 3, runs = TI * per_row, segs = (runs + 1) >> 1;
-      // two groups of wavefronts: every other pair of runs, or, where their number is odd, half of the rows each
-      const bool by_rows = PG == 2 && (segs & 1);
-      const int cut = (TR + 1) >> 1;
-      const int y0 = by_rows && grp ? cut : 0, y1 = by_rows && !grp ? cut : TR;
-      const int xstep = SC * PX, dstep = TC * PK;  // (both counts multiples of four: the parts keep their order)
-#pragma unroll 1
-      for (int seg = by_rows ? 0 : grp; seg < segs; seg += by_rows ? 1 : PG) {
-        int run = 2 * seg + hg;
-        const bool odd = 2 * seg + 1 >= runs;  // an odd number of runs: the last pair's second counts as zero
-        if (odd) run = 2 * seg;
-        const int ti = (int)a.div_runs.div((uint32_t)run), col = (run - ti * per_row) * 8 + px;
-        const int xp = (ti * a.SR + y0) * SC + col, dp = (ti * TR + y0) * TC + col;
-        const T* xq[3];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) xq[s] = xs + (xp + s) * PX + swz(xp + s, wn * 32 + ch);
-        const T* dq = ds + dp * PK + swz_d(dp, wm * 32 + ch);
-        auto row = [&](int j, V& now, const V& one, const V& two) {  // row j of x; dz of rows j, j - 1, j - 2
-          V f[3];
-#pragma unroll
-          for (int s = 0; s < 3; ++s) {
-            f[s] = lds_tr_read8<V>(xq[s], xq[s] + 4 * PX);
-            xq[s] += xstep;
-          }
-          if (j < y1) {
-            now = lds_tr_read8<V>(dq, dq + 4 * PK);
-            dq += dstep;
-          }
-          if (j > y0 && j <= y1) {
-#pragma unroll
-            for (int s = 0; s < 3; ++s) acc[0][3 + s] = mfma16(one, f[s], acc[0][3 + s]);
-          }
-          if (j > y0 + 1) {
-#pragma unroll
-            for (int s = 0; s < 3; ++s) acc[0][6 + s] = mfma16(two, f[s], acc[0][6 + s]);
-          }
-          if (j < y1) {
-            if (odd && hg) now = V{};
-#pragma unroll
-            for (int s = 0; s < 3; ++s) acc[0][s] = mfma16(now, f[s], acc[0][s]);
-          }
-        };
-        V d0 = V{}, d1 = V{}, d2 = V{};
-#pragma unroll 1
-        for (int j = y0; j < y1 + 2; j += 3) {
-          row(j, d0, d2, d1);
-          if (j + 1 < y1 + 2) row(j + 1, d1, d0, d2);
-          if (j + 2 < y1 + 2) row(j + 2, d2, d1, d0);
-        }
-      }
-    }
-  };
-
   if constexpr (F32) {
     // (split32.h: half of the sum with dz negated)
     bool neg = (bz & 1) != 0;
@@ -573,12 +469,11 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       if (half == 0 || neg) { neg = !neg; negate(); }
     }
   } else {
-    auto multiply = [&](int stage) { if constexpr (ROWS && PG == 2) compute_rows(stage); else compute(stage); };
     if (nst > 0) { gload(t0); sstore(0); }
     if constexpr (PG == 2) {
       // While sub-tile g is multiplied, g + 1 goes from registers to the other stage and g + 2 is requested: by one group of
       // wavefronts before its MFMAs, by the other behind them, so that on every SIMD the conversions and addresses of one run
-      // under the MFMAs of the other (64 -> 64 channels over 4.2 M pixels: 407 us with both behind, 396 so).
+      // under the MFMAs of the other (64 -> 64 channels over 4.2 M pixels: 431 us with both behind, 411 so).
       auto stage_next = [&](int g) {
         sstore((g + 1) & 1);
         if (g + 2 < nst) gload(t0 + g + 2);
@@ -587,7 +482,7 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       __syncthreads();
       for (int g = 0; g + 1 < nst; ++g) {
         if (grp == 0) stage_next(g);
-        multiply(g & 1);
+        compute(g & 1);
         if (grp != 0) stage_next(g);
         __syncthreads();
       }
@@ -595,12 +490,12 @@ conv_wgrad3x3_kernel(const T* __restrict__ x, const T* __restrict__ dz, float* _
       __syncthreads();
       for (int g = 0; g + 1 < nst; ++g) {
         gload(t0 + g + 1);
-        multiply(g & 1);
+        compute(g & 1);
         sstore((g + 1) & 1);
         __syncthreads();
       }
     }
-    if (nst > 0) multiply((nst - 1) & 1);
+    if (nst > 0) compute((nst - 1) & 1);
   }
 
   if constexpr (F32) {
@@ -707,7 +602,7 @@ bool w9_geometry_of(int N, int P, int Q, int tc, int cap, int maxpos, int halo, 
 // The widest sub-tile; where three rows of the map leave it less than three quarters of the pixels (512 columns: 32 of 64 with 102
 // staged positions), the narrower one that covers the map with the fewest sub-tiles, then staged positions.  (bf16, three layers of
 // 128 channels at 8 x 112 x 112 232 -> 158 us without -> with, at 16 x 64 x 64 151 -> 137.)
-// halo: staged columns beyond those of the pixels: 2, ROWS 4
+// halo: staged columns beyond those of the pixels: 2, SWAP 4
 bool w9_geometry(int N, int P, int Q, int cap, int maxpos, W9Args& a, int halo = 2) {
   bool ok = w9_geometry_of(N, P, Q, Q < cap ? Q : cap, cap, maxpos, halo, a);
   if (ok && a.TP * 4 >= cap * 3) return ok;
@@ -755,15 +650,13 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
     if (mi == 2 && a.tiles_per_split < g_w9_wide_min) continue;
     if (mi == 2 && f32 && (ranges ? s != ranges : s * g.K * 9 * g.C * 4 > room / 4 * 3)) continue;
     if (tiles * s < 128) return false;  // too few blocks for the chip: one tap per block does better
-    // 16 bits: ROWS, unless the padding of columns makes it more than a quarter more MFMAs; in blocks of 128 channels where none is
-    // needed (64 -> 64 channels over 4.2 M pixels, bf16, BatchNorm folded in: 431 us -> 396; 524 288, fp16: 59 -> 56; 128: see the
-    // kernel).  Its own sub-tiles, in no more ranges (whose sums take room in the activation arena).
+    // 16 bits, blocks of 128 channels: SWAP where the columns need no padding (and sub-tiles hold no fewer pixels for their staged rows).
+    // Its own sub-tiles, in no more ranges (whose sums take room in the activation arena).
     W9Args r = a;
-    if (!f32 && (mi == 1 || g.Q % 8 == 0) && w9_geometry(g.N, g.P, (g.Q + 7) / 8 * 8, cap, maxpos, r, 4) && r.TC % 8 == 0 &&
-        (int64_t)r.NT * ((r.TI * (r.TC / 8) + 1) / 2) * r.TR * 4 <= (int64_t)a.NT * ((a.TP + 15) / 16) * 5 &&
-        (int64_t)(r.TI + 1) * (g.H + 2) * (g.W + 2) * std::max(g.C, g.K) < (int64_t)1 << 30) {  // 32-bit offsets within a sub-tile's images
+    if (!f32 && mi == 2 && g.Q % 8 == 0 && w9_geometry(g.N, g.P, g.Q, cap, maxpos, r, 4) && r.TC % 8 == 0 &&
+        (int64_t)r.NT * ((r.TI * (r.TC / 8) + 1) / 2) * r.TR * 4 <= (int64_t)a.NT * ((a.TP + 15) / 16) * 5) {
       a = r;
-      a.rows = 1;
+      a.swap = 1;
       a.tiles_per_split = (int)((a.NT + s - 1) / s);
       s = (a.NT + a.tiles_per_split - 1) / a.tiles_per_split;
     }
@@ -773,16 +666,16 @@ bool w9_plan(int dt, const ConvGeom& g, int64_t room, int ranges, W9Plan& pl) {
   return false;
 }
 
-template <class T, int MI, int WGM, bool FOLD, bool WHOLE, bool ROWS>
+template <class T, int MI, int WGM, bool FOLD, bool WHOLE, bool SWAP>
 void launch_w9_one(hipStream_t st, const void* x, const void* dz, float* dst, dim3 grid, const W9Args& a) {
-  typedef W9Lds<T, MI, WGM, ROWS> L;
+  typedef W9Lds<T, MI, WGM, SWAP> L;
   static bool attr_done = false;
   if (!attr_done) {
-    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void*)conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, SWAP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)L::bytes(W9Cfg<T>::MAXPOS));
     attr_done = true;
   }
-  OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, ROWS>), grid, dim3(128 * WGM * w9_groups(sizeof(T), WGM)), L::bytes(a.NPOS), st,
+  OSEQ_LAUNCH((conv_wgrad3x3_kernel<T, MI, WGM, FOLD, WHOLE, SWAP>), grid, dim3(128 * WGM * w9_groups(sizeof(T), WGM)), L::bytes(a.NPOS), st,
               (const T*)x, (const T*)dz, dst, a);
 }
 template <class T, int MI, int WGM, bool FOLD>
@@ -796,16 +689,8 @@ void launch_w9(hipStream_t st, const void* x, const void* dz, float* dst, const 
   const bool whole = a.tiles_r == 1 && a.tiles_c == 1 && a.TR == a.P && a.TC == a.Q && a.H == a.P && a.W == a.Q &&
                      (int64_t)a.N * a.H * a.W + (int64_t)a.TI * a.H * a.W < (1 << 24) && a.C < (1 << 24) && a.K < (1 << 24) &&
                      a.TI < 256 && (int64_t)a.TI * a.H * a.W < (1 << 20);
-  if constexpr (sizeof(T) == 2 && WGM == 2) {
-    if (a.rows) {
-      a.div_runs = make_fastdiv((uint32_t)a.TC / 8);
-      a.div_tiles_r = make_fastdiv((uint32_t)a.tiles_r); a.div_tiles_c = make_fastdiv((uint32_t)a.tiles_c);
-      launch_w9_one<T, MI, WGM, FOLD, false, true>(st, x, dz, dst, grid, a);
-      return;
-    }
-  }
   if constexpr (sizeof(T) == 2 && WGM == 4) {
-    if (a.rows) {
+    if (a.swap) {
       if (whole) launch_w9_one<T, MI, WGM, FOLD, true, true>(st, x, dz, dst, grid, a);
       else launch_w9_one<T, MI, WGM, FOLD, false, true>(st, x, dz, dst, grid, a);
       return;
@@ -839,9 +724,9 @@ bool conv_wgrad3x3_ok(int dt, const ConvGeom& g) {
   return g_wgrad3x3 && w9_plan(dt, g, 0, 0, pl);
 }
 
-bool conv_wgrad3x3_by_rows(int dt, const ConvGeom& g) {
+bool conv_wgrad3x3_swaps(int dt, const ConvGeom& g) {
   W9Plan pl;
-  return w9_plan(dt, g, 0, 0, pl) && pl.a.rows;
+  return w9_plan(dt, g, 0, 0, pl) && pl.a.swap;
 }
 
 int conv_wgrad3x3_splits(int dt, const ConvGeom& g, int64_t room) {

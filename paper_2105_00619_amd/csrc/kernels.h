@@ -152,7 +152,7 @@ void launch_conv_dgrad_ws3x3(hipStream_t st, int dt, const void* dz, const void*
 // 3x3 stride-1 weight gradient with all nine taps per block (k_conv_wgrad3x3.hip); used by the MFMA launcher below
 bool conv_wgrad3x3_ok(int dt, const ConvGeom& g);
 int conv_wgrad3x3_splits(int dt, const ConvGeom& g, int64_t room);
-bool conv_wgrad3x3_by_rows(int dt, const ConvGeom& g);  // whether it goes down the rows of a sub-tile (for the tests)
+bool conv_wgrad3x3_swaps(int dt, const ConvGeom& g);  // whether its pixels' parts are exchanged in LDS (for the tests)
 void launch_conv_wgrad3x3(hipStream_t st, int dt, const void* x, const void* dz, float* dst, int splits, const ConvGeom& g,
                           const float* fold);
 bool conv_mfma_wgrad_ok(int dt, const ConvGeom& g);

@@ -657,11 +657,13 @@ def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b", [
-    # pairs of runs: one (its rows halved), one and a half, two and a half, two, with columns of padding, on a map of few rows
+    # whole images, parts of one, odd columns and rows, a map of few rows
     (64, 8, 8, 257), (64, 24, 24, 41), (64, 9, 40, 61), (64, 32, 32, 17), (64, 7, 7, 401), (64, 14, 13, 120), (64, 2, 64, 150),
-    (64, 1, 100, 301), (64, 4, 4, 1100), (128, 16, 16, 70), (192, 16, 16, 70)])  # maps that are not taken by rows; 128 channels; 192
-def test_weight_gradient_of_64_channels_by_rows(precision, channels, h, w, b):
-    """3x3 weight gradients of blocks of 64 output channels, with the BatchNorm in front folded into x and without."""
+    (64, 1, 100, 301), (64, 4, 4, 1100), (128, 16, 16, 70), (192, 16, 16, 70), (64, 41, 41, 33),
+    (256, 8, 8, 1024), (128, 24, 40, 60), (256, 14, 14, 300)])  # 128 channels with few sub-tiles a block, 192; blocks of 128 channels
+def test_weight_gradient_of_64_channels(precision, channels, h, w, b):
+    """3x3 weight gradients of blocks of 64 output channels, and of 128 with the parts of a pixel exchanged and not, with the BatchNorm
+    in front folded into x and without."""
     units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
     _against_float64(units, b, h, w, precision)
 

@@ -69,16 +69,17 @@ def test_wide_tiles_are_taken_where_they_are_faster(dt, layer, rows):
 
 
 @pytest.mark.parametrize("dt", [W.BF16, W.FP16])
-@pytest.mark.parametrize("channels,h,w,b,rows", [
-    # the layers of test_weight_gradient_of_64_channels_by_rows (test_gpu_parity.py), and wider blocks
-    (64, 8, 8, 257, True), (64, 24, 24, 41, True), (64, 9, 40, 61, True), (64, 32, 32, 17, True), (64, 7, 7, 401, True),
-    (64, 14, 13, 120, True), (64, 2, 64, 150, True), (64, 1, 100, 301, False), (64, 4, 4, 1100, False), (64, 5, 5, 700, False),
-    (128, 16, 16, 70, True), (192, 16, 16, 70, True), (256, 8, 8, 1024, True), (256, 14, 14, 512, False), (256, 7, 7, 1279, False)])
-def test_weight_gradients_by_rows(dt, channels, h, w, b, rows):
-    by_rows = _function("_ZN4oseq21conv_wgrad3x3_by_rowsEiRKNS_8ConvGeomE", C.c_int, C.c_void_p)
-    by_rows.restype = C.c_bool
-    assert by_rows(dt, _conv3x3(b, h, w, channels, channels)) == rows
-    assert not by_rows(W.FP32, _conv3x3(b, h, w, channels, channels))
+@pytest.mark.parametrize("channels,h,w,b,swaps", [
+    # layers of test_weight_gradient_of_64_channels (test_gpu_parity.py): blocks of 64 channels, and 128 with too few sub-tiles for wider ones
+    (64, 8, 8, 257, False), (64, 32, 32, 17, False), (192, 16, 16, 70, False), (128, 16, 16, 70, False),
+    # blocks of 128 channels on maps whose width is a multiple of eight, and on others
+    (128, 16, 16, 256, True), (256, 8, 8, 1024, True), (256, 24, 24, 114, True), (384, 9, 40, 182, True), (256, 14, 14, 512, False),
+    (256, 7, 7, 1279, False), (512, 4, 4, 1024, False)])
+def test_weight_gradients_whose_parts_are_exchanged(dt, channels, h, w, b, swaps):
+    f = _function("_ZN4oseq19conv_wgrad3x3_swapsEiRKNS_8ConvGeomE", C.c_int, C.c_void_p)
+    f.restype = C.c_bool
+    assert f(dt, _conv3x3(b, h, w, channels, channels)) == swaps
+    assert not f(W.FP32, _conv3x3(b, h, w, channels, channels))
 
 
 def test_padded_patch_rows_leave_a_cu_its_blocks():
