@@ -1049,9 +1049,10 @@ static bool patch_pick(int dt, bool split32, PatchUse use, int N, int dstH, int 
   geo.split32 = split32;
   const int pos_bytes = split32 ? Frag<Split32>::PITCH * 2 : Frag<bf16_t>::PITCH * 2;
   geo.row_pitch = patch_row_pitch(geo, shape.subt, pos_bytes);
-  // (not padded where that takes a block's room that the registers leave: 64 -> 64 channels over 70 000 pixels of 50 x 50 maps in fp16,
-  // two blocks a CU with padded rows, three without, two layers forward 41 -> 33 us, data gradients 42 -> 33.5)
-  const int held = split32 ? shape.mi == 1 ? 3 : 2 : shape.bn == 64 ? 3 : 2;
+  // (not padded where that takes the room of a block that the registers leave and the grid has: 64 -> 64 channels over 70 000 pixels of
+  // 50 x 50 maps in fp16, two blocks a CU with padded rows, three without, two layers forward 41 -> 33 us, data gradients 42 -> 33.5;
+  // where a CU gets two blocks at most the padding stays: a step of 256 and 512 channels on 8 x 8 and 4 x 4 maps, batch 256, 701 -> 682)
+  const int held = (int)std::min<int64_t>(split32 ? shape.mi == 1 ? 3 : 2 : shape.bn == 64 ? 3 : 2, (best_blocks + 255) / 256);
   if (patch_blocks_per_cu(geo, geo.row_pitch, shape.subt, shape.bn, pos_bytes) <
       std::min(held, patch_blocks_per_cu(geo, geo.SC * pos_bytes, shape.subt, shape.bn, pos_bytes)))
     geo.row_pitch = geo.SC * pos_bytes;

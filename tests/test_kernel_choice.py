@@ -83,8 +83,8 @@ def test_weight_gradients_whose_parts_are_exchanged(dt, channels, h, w, b, swaps
 
 
 def test_padded_patch_rows_leave_a_cu_its_blocks():
-    """Rows of a staged patch are padded against bank conflicts only where that leaves a CU the blocks that its registers hold: three of
-    64 channels, two of 128."""
+    """Rows of a staged patch are padded against bank conflicts only where that leaves a CU the blocks that its registers hold and the
+    grid has: three of 64 channels, two of 128."""
     blocks = _function("_ZN4oseq24conv_patch_blocks_per_cuEiRKNS_8ConvGeomEb", C.c_int, C.c_void_p, C.c_bool)
     seen = 0
     for h in range(5, 130, 3):
@@ -97,3 +97,5 @@ def test_padded_patch_rows_leave_a_cu_its_blocks():
                     assert n >= min(held, blocks(dt, layer, True)), (dt, c, h, w)
     assert seen > 10000
     assert blocks(W.FP16, _conv3x3(28, 50, 50, 64, 64), False) == 3
+    # two blocks a CU: padded, though a third would fit without
+    assert blocks(W.FP16, _conv3x3(256, 8, 8, 256, 256), False) == 2 and blocks(W.FP16, _conv3x3(256, 8, 8, 256, 256), True) == 3
