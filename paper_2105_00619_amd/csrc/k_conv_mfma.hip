@@ -943,6 +943,16 @@ static int patch_blocks_per_cu(const PatchArgs& a, int row_pitch, int subt, int 
   return (int)(160 * 1024 / ((bytes + 1279) / 1280 * 1280));
 }
 
+// Tiles of 64 pixels that read more weights than an XCD's L2 holds for all the blocks it runs, at different depths: rows stay unpadded,
+// except in tiles of 8 and 4 columns.  Freed from bank conflicts the blocks drift apart and miss the L2 more often.  One layer forward on
+// 15 x 5 maps of 24 675 pixels in bf16, padded to unpadded: 768 -> 768 channels 1.13, 896 -> 896 1.48, 1024 -> 1024 1.21, 1280 -> 896
+// 1.59 (at 12 000 pixels), data gradients alike; to either side 704 -> 704 0.92, 1280 -> 640 0.90, 512 -> 1024 0.95, 1280 -> 1280 0.99,
+// and 896 -> 896 on 3000 pixels 0.95.  The data gradient in fp32 on 12 000 pixels: 1280 channels 1.12, 1024 0.97.
+static bool patch_weights_missed(int dt, int mi, int tiles, int srcC, int Ng) {
+  const int64_t bytes = (int64_t)9 * srcC * Ng * (dt == DT_F32 ? 4 : 2);
+  return mi == 1 && tiles >= 128 && srcC >= 640 && Ng > 640 && bytes >= (dt == DT_F32 ? 48'000'000 : 10'000'000);
+}
+
 // Block shapes of the patch kernel, largest first: {MI, SUBT, widest BN}.  The first one that gives the chip
 // `g_patch_fill` blocks is taken, else the one with the most blocks if that reaches `g_patch_min_blocks`
 // (shape-only rule, so the choice is the same on every run).
@@ -1054,7 +1064,8 @@ static bool patch_pick(int dt, bool split32, PatchUse use, int N, int dstH, int 
   // where a CU gets two blocks at most the padding stays: a step of 256 and 512 channels on 8 x 8 and 4 x 4 maps, batch 256, 701 -> 682)
   const int held = (int)std::min<int64_t>(split32 ? shape.mi == 1 ? 3 : 2 : shape.bn == 64 ? 3 : 2, (best_blocks + 255) / 256);
   if (patch_blocks_per_cu(geo, geo.row_pitch, shape.subt, shape.bn, pos_bytes) <
-      std::min(held, patch_blocks_per_cu(geo, geo.SC * pos_bytes, shape.subt, shape.bn, pos_bytes)))
+      std::min(held, patch_blocks_per_cu(geo, geo.SC * pos_bytes, shape.subt, shape.bn, pos_bytes)) ||
+      (geo.TC != 8 && geo.TC != 4 && patch_weights_missed(dt, shape.mi, geo.NT, srcC, Ng)))
     geo.row_pitch = geo.SC * pos_bytes;
   geo.chunks_per_split = (nchunks + splits - 1) / splits;
   shape.splits = (nchunks + geo.chunks_per_split - 1) / geo.chunks_per_split;  // no empty ranges
@@ -1274,6 +1285,13 @@ int conv_patch_blocks_per_cu(int dt, const ConvGeom& g, bool unpadded) {
   if (!patch_pick(dt, split32, PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, a) || v.wide) return 0;
   const int pos_bytes = (split32 ? Frag<Split32>::PITCH : Frag<bf16_t>::PITCH) * 2;
   return patch_blocks_per_cu(a, unpadded ? a.SC * pos_bytes : a.row_pitch, v.subt, v.bn, pos_bytes);
+}
+
+bool conv_patch_rows_padded(int dt, const ConvGeom& g) {
+  PatchShape v; PatchArgs a{};
+  const bool split32 = fwd_split32(dt, g);
+  return patch_pick(dt, split32, PATCH_FWD, g.N, g.P, g.Q, g.C, g.K, g.R, g.S, g.stride, v, a) &&
+         a.row_pitch > a.SC * (split32 ? Frag<Split32>::PITCH : Frag<bf16_t>::PITCH) * 2;
 }
 
 bool conv_mfma_fwd_ok(int dt, const ConvGeom& g) {

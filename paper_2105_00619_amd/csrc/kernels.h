@@ -114,6 +114,8 @@ int conv_mfma_fwd_stat_blocks(int dt, const ConvGeom& g, bool bias);  // bias: t
 // blocks of the forward pass's 3x3 patch kernel whose LDS a CU holds (unpadded: would hold without padding between the rows of a
 // patch), 0: the layer does not take it; for the tests
 int conv_patch_blocks_per_cu(int dt, const ConvGeom& g, bool unpadded);
+// whether it keeps the rows of a patch apart in LDS; for the tests
+bool conv_patch_rows_padded(int dt, const ConvGeom& g);
 // fold (null: none): x is not the input activation but the z of the BatchNorm + ReLU in front of the layer, and fold
 // that BatchNorm's [4][C_in] statistics tensor (mean, rstd, scale, shift): the kernel turns z into the activation --
 // the very values the apply kernel would have stored -- while it stages its operand.  Only where conv_fold_fwd_ok /

@@ -99,3 +99,18 @@ def test_padded_patch_rows_leave_a_cu_its_blocks():
     assert blocks(W.FP16, _conv3x3(28, 50, 50, 64, 64), False) == 3
     # two blocks a CU: padded, though a third would fit without
     assert blocks(W.FP16, _conv3x3(256, 8, 8, 256, 256), False) == 2 and blocks(W.FP16, _conv3x3(256, 8, 8, 256, 256), True) == 3
+
+
+@pytest.mark.parametrize("dt", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layer,padded", [
+    # n, h, w, C_in, C_out in tiles of 64 pixels
+    ((329, 15, 5, 704, 704), True), ((329, 15, 5, 768, 704), True), ((329, 15, 5, 768, 768), False), ((329, 15, 5, 896, 704), False),
+    ((329, 15, 5, 1280, 640), True), ((329, 15, 5, 576, 1024), True), ((329, 15, 5, 640, 896), False), ((329, 15, 5, 1024, 1024), False),
+    # few tiles; columns that were padded before
+    ((42, 15, 5, 896, 896), True), ((80, 15, 5, 896, 896), False), ((80, 16, 8, 1024, 1024), True), ((400, 15, 4, 1024, 1024), True),
+    # tiles of 128 pixels
+    ((250, 7, 7, 1024, 1024), True), ((120, 10, 5, 1024, 1024), True)])
+def test_rows_are_not_padded_where_weights_miss_the_cache(dt, layer, padded):
+    f = _function("_ZN4oseq22conv_patch_rows_paddedEiRKNS_8ConvGeomE", C.c_int, C.c_void_p)
+    f.restype = C.c_bool
+    assert f(dt, _conv3x3(*layer)) == padded
