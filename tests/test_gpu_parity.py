@@ -546,7 +546,7 @@ def _grads64(units, params, x, y, precision, scale):
 
 def _against_float64(units, b, h, w, precision, seed=9):
     """One step in one segment and in as many as there are units against float64 (with the storage type's roundings), tensor by
-    tensor; the trainer's work by class and by entry."""
+    tensor; the trainer's work by class."""
     import torch
     from paper_2105_00619_amd.binding import SeqTrainer
     g = torch.Generator(device="cuda").manual_seed(seed)
@@ -597,7 +597,6 @@ def _against_float64(units, b, h, w, precision, seed=9):
     t.profile_enable()
     t.step(x, y, 0.0)
     work = t.profile_read()["classes"]
-    work["entries"] = t.profile_read_entries()
     t.close()
     return work
 
@@ -639,19 +638,43 @@ def test_backward_under_a_pool_reads_the_output_it_has(precision, block):
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b", [
     (128, 16, 16, 256), (256, 8, 8, 1024),  # exactly 256 tiles of 256 x 128 and of 256 x 256
-    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217),
-    # row tiles that the grouping by XCD pads with blocks that end at once (127 of two channel blocks); three channel blocks, grouped and not
-    (512, 8, 8, 507), (384, 8, 8, 320), (384, 8, 8, 336),
-    (256, 15, 17, 254), (128, 4, 4, 8190), (256, 16, 16, 384), (128, 16, 16, 512)])  # several rounds of blocks; the last on narrow tiles
+    (128, 15, 17, 509), (256, 7, 7, 1279), (128, 64, 128, 8), (128, 4, 4, 4091), (256, 4, 4, 4096), (512, 8, 8, 511), (128, 16, 16, 217)])
 def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
     """3x3 layers on tiles of 256 pixels: one image, several, parts of one, a ragged last tile, two channel blocks, which are a full round
     in 512 channels; at 217 images fewer tiles than fill the chip (the narrower tiles).  Two basic blocks: forward with sums, with the
     BatchNorm in front folded in and without sums (replay), data gradients with the sums of the BatchNorm in front and with a masked
     addend.  (test_kernel_choice.py: which of these take the wide tiles.)"""
+    units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
+    _against_float64(units, b, h, w, precision)
+
+
+def _profile(units, b, h, w, precision):
+    """The work of one step, by class and by entry."""
+    import torch
+    from paper_2105_00619_amd.binding import SeqTrainer
+    t = SeqTrainer(units, k_segments=1, precision=precision, batch=b, height=h, width=w, channels=units[0].cin, num_classes=10,
+                   loss_scale_init=_scale(precision))
+    t.set_params(W.make_params(units, h, w, perturb=True))
+    t.profile_enable()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    t.step(torch.randn((b, h, w, units[0].cin), generator=g, device="cuda"), torch.zeros(b, device="cuda", dtype=torch.int32), 0.0)
+    work = t.profile_read()["classes"], t.profile_read_entries()
+    t.close()
+    return work
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("channels,h,w,b", [
+    # row tiles that the grouping by XCD pads with blocks that end at once (127 of two channel blocks); three channel blocks, grouped and not
+    (512, 8, 8, 507), (384, 8, 8, 320), (384, 8, 8, 336),
+    # several rounds of blocks; the last on narrow tiles
+    (256, 15, 17, 254), (128, 4, 4, 8190), (256, 16, 16, 384), (128, 16, 16, 512), (128, 16, 16, 768)])
+def test_wide_tiles_in_several_rounds_and_channel_blocks(precision, channels, h, w, b):
+    """Two basic blocks, as above; and the step makes as many rows of sums as the rule's tiles have."""
     from tests.test_kernel_choice import _forward_rows
     units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
-    work = _against_float64(units, b, h, w, precision)
-    sums = [e["bytes"] for e in work["entries"] if e["kind"] == "bn_stats" and e["unit"] > 0]
+    _against_float64(units, b, h, w, precision)
+    sums = [e["bytes"] for e in _profile(units, b, h, w, precision)[1] if e["kind"] == "bn_stats" and e["unit"] > 0]
     assert sums == [8 * channels * _forward_rows(precision, b, h, w, channels, channels)] * 4
 
 
@@ -659,11 +682,17 @@ def test_wide_tiles_of_3x3_layers(precision, channels, h, w, b):
 @pytest.mark.parametrize("channels,h,w,b", [
     # whole images, parts of one, odd columns and rows, a map of few rows
     (64, 8, 8, 257), (64, 24, 24, 41), (64, 9, 40, 61), (64, 32, 32, 17), (64, 7, 7, 401), (64, 14, 13, 120), (64, 2, 64, 150),
-    (64, 1, 100, 301), (64, 4, 4, 1100), (128, 16, 16, 70), (192, 16, 16, 70), (64, 41, 41, 33),
-    (256, 8, 8, 1024), (128, 24, 40, 60), (256, 14, 14, 300)])  # 128 channels with few sub-tiles a block, 192; blocks of 128 channels
-def test_weight_gradient_of_64_channels(precision, channels, h, w, b):
-    """3x3 weight gradients of blocks of 64 output channels, and of 128 with the parts of a pixel exchanged and not, with the BatchNorm
-    in front folded into x and without."""
+    (64, 1, 100, 301), (64, 4, 4, 1100), (128, 16, 16, 70), (192, 16, 16, 70)])  # 128 channels with few sub-tiles a block, 192
+def test_weight_gradient_of_64_channels_by_rows(precision, channels, h, w, b):
+    """3x3 weight gradients of blocks of 64 output channels, with the BatchNorm in front folded into x and without."""
+    units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
+    _against_float64(units, b, h, w, precision)
+
+
+@pytest.mark.parametrize("precision", [W.BF16, W.FP16])
+@pytest.mark.parametrize("channels,h,w,b", [(64, 41, 41, 33), (256, 8, 8, 1024), (128, 24, 40, 60), (256, 14, 14, 300)])
+def test_weight_gradient_of_128_channel_blocks(precision, channels, h, w, b):
+    """The same on a map with a short last sub-tile, and of blocks of 128 channels with the parts of a pixel exchanged and not."""
     units = [W.conv(8, channels, 1)] + [W.basic_block(channels, channels)] * 2 + [W.gap_linear_ce(channels, 10)]
     _against_float64(units, b, h, w, precision)
 
@@ -711,20 +740,17 @@ def test_wide_tiles_with_a_bias_and_other_borders(precision, b):
 
 
 @pytest.mark.parametrize("precision", [W.BF16, W.FP16])
-@pytest.mark.parametrize("relu,blocks,h,w,b,unwritten", [
-    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128, 3),  # exactly 131 072 pixels: whole tiles
-    (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121, 3),  # ragged; the last block's output is pooled: kept
-    (True, [(64, 256), (256, 64)], 512, 255, 1, 0), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405, 0),  # fewer; 130 815
-    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513, 1)])  # no ReLU in front of the projection shortcut: only the second block's
-def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b, unwritten):
+@pytest.mark.parametrize("relu,blocks,h,w,b", [
+    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128),  # exactly 131 072 pixels: whole tiles
+    (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121),  # ragged; the last block's output is pooled: kept
+    (True, [(64, 256), (256, 64)], 512, 255, 1), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405),  # fewer; 130 815
+    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513)])  # no ReLU in front of the projection shortcut
+def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b):
     """Last layers and projection shortcuts of 64 -> 256 channels over 131 072 pixels or more: their outputs are never written, the
     statistics, the apply pass and the sums of the backward pass make them again.  Against plain float64 arithmetic; k segments and
     the three storage modes (different sources: an activation, or the z of its BatchNorm) change no bit."""
     units = [W.conv(8, 64, 1, relu=relu)] + [W.bottleneck(i, o) for i, o in blocks] + [W.gap_linear_ce(blocks[-1][1], 10)]
-    work = _against_float64(units, b, h, w, precision)
-    layers = [(8, 64)] + [p for i, o in blocks for p in [(i, o // 4), (o // 4, o)] + ([(i, o)] if i != o else [])]
-    whole = 2 * sum(b * h * w * (i + o) + i * o for i, o in layers)  # every 1x1 layer reads its input and writes its output
-    assert whole - work["conv1x1_fwd"]["bytes"] == unwritten * 2 * b * h * w * 256
+    _against_float64(units, b, h, w, precision)
     rng = np.random.default_rng(5)
     x, y = rng.standard_normal((b, h, w, 8)).astype(np.float32), rng.integers(0, 10, b).astype(np.int32)
     p = W.make_params(units, h, w, perturb=True)
@@ -734,6 +760,18 @@ def test_block_outputs_without_their_z(precision, relu, blocks, h, w, b, unwritt
         for k in (1, 2, len(units)):
             r, _ = gpu_step(units, p, x, y, k=k, storage_mode=mode, **kw)
             assert r["loss"] == want["loss"] and np.array_equal(r["grads"], want["grads"]), (mode, k)
+
+
+@pytest.mark.parametrize("relu,blocks,h,w,b,unwritten", [
+    (True, [(64, 256), (256, 256), (256, 64)], 32, 32, 128, 3), (True, [(64, 256), (256, 256), (256, 64), (64, 256)], 33, 33, 121, 3),
+    (True, [(64, 256), (256, 64)], 512, 255, 1, 0), (True, [(64, 256), (256, 256), (256, 64)], 17, 19, 405, 0),
+    (False, [(64, 256), (256, 256), (256, 64)], 16, 16, 513, 1)])  # no ReLU in front of the projection shortcut: only the second block's
+def test_block_outputs_that_are_not_written(relu, blocks, h, w, b, unwritten):
+    """Of the networks above: how many outputs of 1x1 layers a step does without."""
+    units = [W.conv(8, 64, 1, relu=relu)] + [W.bottleneck(i, o) for i, o in blocks] + [W.gap_linear_ce(blocks[-1][1], 10)]
+    layers = [(8, 64)] + [p for i, o in blocks for p in [(i, o // 4), (o // 4, o)] + ([(i, o)] if i != o else [])]
+    whole = 2 * sum(b * h * w * (i + o) + i * o for i, o in layers)  # every 1x1 layer reads its input and writes its output
+    assert whole - _profile(units, b, h, w, W.BF16)[0]["conv1x1_fwd"]["bytes"] == unwritten * 2 * b * h * w * 256
 
 
 def test_block_outputs_written_in_passes_that_keep_nothing():

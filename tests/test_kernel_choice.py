@@ -70,7 +70,7 @@ def test_wide_tiles_are_taken_where_they_are_faster(dt, layer, rows):
 
 @pytest.mark.parametrize("dt", [W.BF16, W.FP16])
 @pytest.mark.parametrize("channels,h,w,b,swaps", [
-    # layers of test_weight_gradient_of_64_channels (test_gpu_parity.py): blocks of 64 channels, and 128 with too few sub-tiles for wider ones
+    # layers of test_weight_gradient_of_64_channels_by_rows (test_gpu_parity.py): blocks of 64 channels, and 128 with too few sub-tiles for wider ones
     (64, 8, 8, 257, False), (64, 32, 32, 17, False), (192, 16, 16, 70, False), (128, 16, 16, 70, False),
     # blocks of 128 channels on maps whose width is a multiple of eight, and on others
     (128, 16, 16, 256, True), (256, 8, 8, 1024, True), (256, 24, 24, 114, True), (384, 9, 40, 182, True), (256, 14, 14, 512, False),
