@@ -974,9 +974,11 @@ enum PatchUse { PATCH_FWD, PATCH_EVAL, PATCH_DGRAD };  // forward pass of a step
 //   data gradient       128 -> 128 0.88 1.01, 256 -> 256 0.85 0.96
 // Beyond a round nothing covers a block's epilogue and the next one's beginning, where two narrow blocks on a CU are no longer in
 // step.  What that costs depends on the products a block has in between:
-//   tiles of 128 channels, two rounds and more: 32 -> 128 1.11 - 1.30, 64 -> 128 1.03 - 1.12, 128 -> 128 0.99 - 1.12 forward and 1.03 - 1.25 in
-//     the data gradient (a step of a block 1.00 - 1.06).  256 -> 256, with the BatchNorm sums of a data gradient that 256 pixels a
-//     tile make few enough to come with it: a step 0.98 - 0.99, from the fourth round on 0.99 - 1.02 below 93 % and 0.98 above;
+//   tiles of 128 channels: 32 -> 128 1.11 - 1.30 from two rounds on.  64 and 128 -> 128 in tile rows of up to 32 pixels, of a step
+//     with two such layers or blocks on 8 x 8, 16 x 16 or 32 x 32 maps: two rounds 0.96 - 1.01, three 0.98 - 1.01, from the fourth on
+//     1.00 - 1.03 (the kernels 0.99 - 1.12 forward, 1.03 - 1.25 in the data gradient); in rows of 64 pixels, with a fifth more
+//     positions to stage, 1.02 - 1.04 from the second round on.  256 -> 256, with the BatchNorm sums of a data gradient that 256 pixels
+//     a tile make few enough to come with it: a step 0.98 - 0.99, from the fourth round on 0.99 - 1.02 below 93 % and 0.98 above;
 //     384 -> 384 0.97 - 1.00, 640 -> 640 0.94 - 0.99
 //   of 256 channels: 32 -> 256 0.98 - 1.12, 64 -> 256 0.94 - 1.04, 128 -> 256 0.90 - 0.99, 256 -> 256 and deeper 0.79 - 0.95
 // Where the narrow tiles fit a map a tenth worse (4 x 4 and 7 x 7) or not at all the wide ones are ahead at every depth (128 -> 128
@@ -987,6 +989,7 @@ static bool patch_wide_pays(PatchUse use, int N, int dstH, int dstW, int srcC, i
   if (rounds == 1 || use == PATCH_EVAL) return true;
   if (srcC >= (bn == 256 ? 128 : 384)) return true;
   if (srcC >= (bn == 256 ? 64 : 256) && (wanted * 100 >= offered * 93 || (bn == 128 && rounds <= 3))) return true;
+  if (bn == 128 && srcC >= 64 && rounds <= 3 && a.TC <= 32) return true;
   PatchArgs n{};
   return !patch_geometry(N, dstH, dstW, 128, true, n) || n.TP * 4 < 128 * 3 || n.NPOS * 2 > n.TP * g_patch_halo2 ||
          (int64_t)n.NT * 10 >= (int64_t)2 * a.NT * 11;

@@ -668,7 +668,7 @@ def _profile(units, b, h, w, precision):
     # row tiles that the grouping by XCD pads with blocks that end at once (127 of two channel blocks); three channel blocks, grouped and not
     (512, 8, 8, 507), (384, 8, 8, 320), (384, 8, 8, 336),
     # several rounds of blocks; the last on narrow tiles
-    (256, 15, 17, 254), (128, 4, 4, 8190), (256, 16, 16, 384), (128, 16, 16, 512), (128, 16, 16, 768)])
+    (256, 15, 17, 254), (128, 4, 4, 8190), (256, 16, 16, 384), (128, 16, 16, 512), (128, 32, 64, 64)])
 def test_wide_tiles_in_several_rounds_and_channel_blocks(precision, channels, h, w, b):
     """Two basic blocks, as above; and the step makes as many rows of sums as the rule's tiles have."""
     from tests.test_kernel_choice import _forward_rows

@@ -54,8 +54,9 @@ def _data_gradient_rows(dt, *layer):
     ((8, 64, 128, 128, 128), 256), ((4091, 4, 4, 128, 128), 256), ((4096, 4, 4, 256, 256), 256), ((511, 8, 8, 512, 512), 128),
     ((507, 8, 8, 512, 512), 127), ((320, 8, 8, 384, 384), 80), ((336, 8, 8, 384, 384), 84), ((8190, 4, 4, 128, 128), 512),
     ((217, 16, 16, 128, 128), 434), ((218, 16, 16, 128, 128), 218),
-    # beyond one round of 256: not with little depth, unless the narrow tiles fit the map badly
-    ((512, 16, 16, 128, 128), 1024), ((509, 15, 17, 128, 128), 509), ((512, 16, 16, 32, 128), 1024), ((256, 16, 16, 32, 128), 256),
+    # up to three rounds of 256 where rows of a tile are short, not with least depth; beyond that only where the narrow tiles fit the map badly
+    ((512, 16, 16, 128, 128), 512), ((440, 16, 16, 128, 128), 440), ((768, 16, 16, 128, 128), 768), ((1024, 16, 16, 128, 128), 2048),
+    ((512, 16, 16, 96, 128), 512), ((64, 32, 64, 128, 128), 1024), ((509, 15, 17, 128, 128), 509), ((512, 16, 16, 32, 128), 1024), ((256, 16, 16, 32, 128), 256),
     ((512, 16, 16, 32, 256), 1024), ((508, 16, 16, 64, 256), 508), ((450, 16, 16, 64, 256), 900), ((450, 16, 16, 128, 256), 450),
     ((645, 7, 7, 128, 128), 323), ((1210, 7, 7, 128, 128), 242), ((2360, 7, 7, 128, 128), 472),
     # 256 channels that tiles of 256 do not fit, in tiles of 128: up to three rounds, beyond that 93 % of the products
